@@ -149,6 +149,40 @@ __device__ __forceinline__ uint32_t float_to_bf16_rne(float x) {
   return (u + 0x7fffu + ((u >> 16) & 1u)) >> 16;
 }
 
+// two floats -> packed bf16 pair, round to nearest even (one v_cvt_pk_bf16_f32)
+__device__ __forceinline__ uint32_t pack_bf16_pair(float a, float b) {
+  typedef __attribute__((ext_vector_type(2))) float f2;
+  typedef __attribute__((ext_vector_type(2))) __bf16 b2;
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector(f2{a, b}, b2));
+}
+
+// A pair of floats as three packed bf16 pairs whose sums are the floats: each term is the nearest
+// bf16 of what the terms before it leave (the differences are exact), 3 x 8 significant bits.
+struct Split3 { uint32_t t[3]; };
+__device__ __forceinline__ Split3 split3(float a, float b) {
+  Split3 s;
+#pragma unroll
+  for (int p = 0; p < 3; ++p) {
+    s.t[p] = pack_bf16_pair(a, b);
+    a -= __uint_as_float(s.t[p] << 16);
+    b -= __uint_as_float(s.t[p] & 0xffff0000u);
+  }
+  return s;
+}
+
+// out[row][n] of in . B in plain float32, index by index: for the outputs of a split product that
+// are not finite (an infinity, or an overflow of a term).  Ends at the first NaN of its own.
+template <bool B_KCONTIG>
+__device__ __noinline__ float plain_dot(const float* in, const float* P, int row, int n, int d, int h, int kv) {
+  const int C = B_KCONTIG ? h * kv : d;
+  float s = 0.f;
+  for (int c = 0; c < C && s == s; ++c) {
+    const size_t at = B_KCONTIG ? ((size_t)(c / kv) * d + n) * kv + c % kv : ((size_t)(n / kv) * d + c) * kv + n % kv;
+    s = fmaf(in[(size_t)row * C + c], P[at], s);
+  }
+  return s;
+}
+
 __device__ __forceinline__ float wave_max(float x) {
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) x = fmaxf(x, __shfl_xor(x, o));

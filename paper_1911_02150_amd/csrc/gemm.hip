@@ -1,190 +1,293 @@
 // Large float32 GEMMs of the projections (prompt-sized row counts, the feed-forward and
 // vocabulary matrices of the decoder stack): out[rows, N] = in[rows, C] . B[C, N] with B addressed
-// inside the projection tensor P [h, d, kv] exactly as in project.hip.  float32 products and
-// accumulation on the matrix cores (v_mfma_f32_32x32x2_f32).
+// inside the projection tensor P [h, d, kv] exactly as in project.hip.
 //
-// Workgroup tile BM x BN (128 x 128 or 64 x 64) over K-steps of 32, four waves in a 2 x 2
-// arrangement, each wave (BM/2) x (BN/2) = RB x CB blocks of 32 x 32.  Tiles go global ->
-// registers -> LDS (double buffered, one barrier per K-step; the next tile's global loads are in
-// flight while the current one is multiplied).
+// The float32 matrix instructions are the bound of such a product (157 TFLOP/s against 2.5 PFLOP/s
+// in bf16), so every float32 operand is written as three bf16 terms x = x0 + x1 + x2 (each the
+// nearest bf16 of what the terms before it leave: 24 significant bits, so the sum IS x) and the
+// product as the six bf16 products of order up to 2^-16,
+//   a.b = a0b0 + (a0b1 + a1b0) + (a0b2 + a1b1 + a2b0)        (what is dropped is below 2^-25 |a||b|)
+// accumulated in float32 on v_mfma_f32_32x32x16_bf16.  A bf16 product is exact in float32 and an
+// instruction adds 16 of them with one rounding of the running sum, where the float32
+// instruction rounds after every second one: relative error of a 1024-term sum of normal
+// deviates 5.0e-7 against 5.8e-7, of a 4096-term one 1.0e-6 against 1.15e-6.
+// An infinity has no such split (inf - inf), and a term may overflow where the sum does not: an
+// output that is not finite is computed again in plain float32.
 //
-// LDS layouts and MFMA contraction slots.  An MFMA contracts two indices: lane (i, kk) supplies
-// A[i][slot kk] and B[slot kk][i].  Which c a slot stands for is free as long as A and B agree;
-// the K-step's 16 MFMAs are numbered (u, e), u, e = 0..3, and slot kk of MFMA (u, e) is
-// c = 8u + 4kk + e.  So a lane's A values for fixed u are 4 consecutive c: one 16-byte LDS read
-// from As[row][c] (pitch 36 floats: 8 consecutive rows hit 8 different 16-byte bank groups).
-//   B with c contiguous in memory (the output projection, P_o / tied embedding): staged like A
-//   as Bs[n][c], 16-byte reads.
-//   B with n contiguous in memory (q, K, V projections, feed-forward): staged as Bs[c][n] (pitch
-//   132) with 16-byte writes and read with 4-byte reads, 32 consecutive n per half wave; the rows
-//   of the two lane groups kk = 0, 1 are 4 apart = 16 banks apart.
+// Measured (b=128, n=128 prompt: rows = 16384, TFLOP/s of the float32 product; before: 128x128 tiles of
+// v_mfma_f32_32x32x2_f32): 1024 x 4096: 126 -> 224; 4096 x 1024: 129 -> 228; 1024 x 1024: 122 -> 220,
+// i.e. 1.35 PFLOP/s of bf16 products at 72 % matrix-core utilisation and the 1.6 GHz the card clocks
+// down to under this load (hipBLASLt's 8192^3 bf16 product reaches 1.29 here).  128x128 tiles, fewer
+// flops per staged byte: 104 -> 165 at 1024 x 1024 . 1024 x 4096, logits of 128 rows 101 -> 145.
+//
+// Workgroup: 512 threads, two waves per SIMD, tile BM x BN, WR x WC waves in each of KG groups; a
+// stage holds 16*KG contraction indices, group kg works on 16 of them.  Stages go
+// global -> registers (one stage ahead) -> split -> LDS (two buffers, one barrier per stage).
+// Threads 0..255 stage A before they multiply, threads 256..511 stage B after they have: the
+// two waves of a SIMD are then out of step and one splits while the other multiplies.
+//
+// A lane (i, g) of a 32x32x16 operand reads 16 bytes, k = 8g..8g+7 of row i; 32 rows of a half are 512
+// contiguous bytes in LDS.  A lane's JB accumulator blocks are JB adjacent columns (one store of
+// 4*JB bytes).
 #include "common.hpp"
+
+#include <type_traits>
 
 namespace mqa {
 namespace {
 
 typedef __attribute__((ext_vector_type(16))) float floatx16;
+typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
+typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 
-constexpr int BK = 32;
-constexpr int kAPitch = BK + 4;          // As[row][c], Bs[n][c]
-
-template <int BN> constexpr int b_tile_floats(bool kcontig) { return kcontig ? BN * kAPitch : BK * (BN + 4); }
+// LDS of a stage, in bytes: per group A's three planes, then B's three planes; a plane is two halves g
+// of 16 bytes per row (A) or slot (B): contraction indices 8g .. 8g+7.  Column n of the tile lives in slot
+// n / JB of column block n % JB.  The few bytes between the halves, groups and column blocks put what
+// eight consecutive lanes write (two halves of four rows, two groups of two rows, or two column
+// blocks of four slots) on different banks.
+template <int BM, int BN, int JB, int KG> struct SplitTile {
+  static constexpr int QCOLS = BN / JB;
+  static constexpr int B_BLOCK = QCOLS * 16 + (JB == 4 ? 32 : 0);
+  static constexpr int A_G = BM * 16 + 64 / KG, B_G = JB * B_BLOCK + 64 / KG;
+  static constexpr int A_PLANE = 2 * A_G, B_PLANE = 2 * B_G;
+  static constexpr int GROUP = 3 * (A_PLANE + B_PLANE) + (KG == 2 ? 64 : 0);
+  static constexpr int STAGE = KG * GROUP;
+  static __device__ __host__ constexpr int slot_bytes(int block, int slot) { return block * B_BLOCK + slot * 16; }
+};
 
 // B_KCONTIG = false: B[c][n] = P[(n / kv) * d * kv + c * kv + n % kv]   (C = d, N = h * kv)
 // B_KCONTIG = true : B[c][n] = P[(c / kv) * d * kv + n * kv + c % kv]   (C = h * kv, N = d)
-template <bool B_KCONTIG, int BM, int BN>
-__global__ __launch_bounds__(256)
-void gemm_tiled_kernel(const float* __restrict__ in, const float* __restrict__ P, float* out,
-                       int rows, int d, int h, int kv, int epilogue) {
-  constexpr int RB = BM / 64, CB = BN / 64;            // 32x32 blocks per wave in each direction
-  constexpr int A_F4 = BM * BK / 4 / 256;              // float4 loads per thread per K-step
-  constexpr int B_F4 = BN * BK / 4 / 256;
-  constexpr int A_FLOATS = BM * kAPitch;
-  constexpr int B_FLOATS = b_tile_floats<BN>(B_KCONTIG);
-  constexpr int BPITCH = BN + 4;                       // Bs[c][n]
-  extern __shared__ __align__(16) float smem[];
-  constexpr int STAGE = A_FLOATS + B_FLOATS;            // one buffer of the double buffer: A tile, then B tile
+template <bool B_KCONTIG, int BM, int BN, int WR, int WC, int KG, int PD>
+__global__ __launch_bounds__(512)
+void gemm_split_kernel(const float* __restrict__ in, const float* __restrict__ P, float* out,
+                       int rows, int d, int h, int kv, int epilogue, int tiles_m, int tiles_n) {
+  static_assert(WR * WC * KG == 8 && BM * KG == 256 && BN * KG == 256, "512 threads, 16 staged values of each operand per thread of a half");
+  constexpr int RB = BM / WR / 32, JB = BN / WC / 32;      // 32x32 blocks per wave
+  typedef SplitTile<BM, BN, JB, KG> L;
+  constexpr int KO = 2 * KG;                               // groups of eight contraction indices in a stage
+  extern __shared__ __align__(16) unsigned char smem[];
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int i32 = lane & 31, kk = lane >> 5;
-  const int row0 = blockIdx.y * BM;
-  const int n0 = blockIdx.x * BN;
+  // tiles: every XCD takes a contiguous run of tiles, column-major inside groups of 8 tile rows, so that
+  // the workgroups that run together on an XCD share their operands in its L2
+  const int per_xcd = gridDim.x >> 3;
+  const int tile = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+  if (tile >= tiles_m * tiles_n) return;
+  const int band = tile / (8 * tiles_n), in_band = tile - band * 8 * tiles_n;
+  const int band_rows = min(8, tiles_m - band * 8);
+  const int row0 = (band * 8 + in_band % band_rows) * BM, n0 = (in_band / band_rows) * BN;
+
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int i32 = lane & 31, g = lane >> 5;
+  const int kg = wave / (WR * WC), wr = (wave / WC) % WR, wc = wave % WC;
   const int C = B_KCONTIG ? h * kv : d;
   const int N = B_KCONTIG ? d : h * kv;
-  const int wrow = (wave >> 1) * (BM / 2), wcol = (wave & 1) * (BN / 2);
   const size_t head_stride = (size_t)d * kv;
+  const int ts = tid & 255;
+  const int nst = (C + 16 * KG - 1) / (16 * KG);
 
-  // ---- global -> register staging.  A (and B when c is contiguous): thread -> (row t/8 + 32 i, c 4 (t%8)).
-  const float* a_src[A_F4];
+  // ---- staging: 16 values per thread and stage.  Loads are unconditional (indices past the contraction
+  // are clamped and their values zeroed when the last stage is split), so that the compiler can
+  // count the loads in flight.
+  //   A, and B with c contiguous: thread -> eight indices (octet ts % KO) of rows ts / KO + (256 / KO) i
+  //   B with n contiguous: thread -> columns 2 pair, 2 pair + 1 at the eight indices of an octet
+  const int o_row = ts % KO, r_row = ts / KO;
+  const int w4 = wave & 3;
+  const int pair = lane + 64 * (w4 % (BN / 128)), o_col = w4 / (BN / 128);
+  auto run = [&](auto role, auto&& multiply) {
+    constexpr bool STAGE_A = decltype(role)::value, BY_ROWS = STAGE_A || B_KCONTIG;
+    const float* src[BY_ROWS ? 2 : 1];
+    if constexpr (BY_ROWS) {
 #pragma unroll
-  for (int i = 0; i < A_F4; ++i) a_src[i] = in + (size_t)min(row0 + (tid >> 3) + 32 * i, rows - 1) * C + 4 * (tid & 7);
-  // B: per-thread base pointers (without the c offset)
-  const float* b_src[B_F4];
-#pragma unroll
-  for (int i = 0; i < B_F4; ++i) {
-    if (B_KCONTIG) {
-      const int n = min(n0 + (tid >> 3) + 32 * i, N - 1);
-      b_src[i] = P + (size_t)n * kv;                                         // + (c / kv) * head_stride + c % kv
+      for (int i = 0; i < 2; ++i) {
+        const int r = r_row + (256 / KO) * i;
+        if constexpr (STAGE_A) src[i] = in + (size_t)min(row0 + r, rows - 1) * C;                            // + c
+        else src[i] = P + (size_t)min(n0 + JB * (r % L::QCOLS) + r / L::QCOLS, N - 1) * kv;                  // r is the slot; + head of c, c % kv
+      }
     } else {
-      // thread -> (c = t / (BN/4) + (1024/BN) i, n = 4 (t % (BN/4)))
-      const int n = min(n0 + 4 * (tid % (BN / 4)), N - 4);
-      b_src[i] = P + (size_t)(n / kv) * head_stride + (n % kv);              // + c * kv
+      const int n = min(n0 + 2 * pair, N - 2);
+      src[0] = P + (size_t)(n / kv) * head_stride + (n % kv);                                                // + c * kv
     }
-  }
-  float4 ra[A_F4], rb[B_F4];
-  auto load_global = [&](int c0) {
-    const int ca = c0 + 4 * (tid & 7);
+    struct Regs { float x[16]; };              // [row][8 indices], or [8 indices][column]
+    auto load_stage = [&](int st, Regs& rg) {
+      if constexpr (BY_ROWS) {
+        const int c = min(st * 16 * KG + 8 * o_row, C - 8);
+        const size_t off = STAGE_A ? (size_t)c : (size_t)(c / kv) * head_stride + (c % kv);
 #pragma unroll
-    for (int i = 0; i < A_F4; ++i)
-      ra[i] = ca < C ? *reinterpret_cast<const float4*>(a_src[i] + c0) : make_float4(0.f, 0.f, 0.f, 0.f);
-#pragma unroll
-    for (int i = 0; i < B_F4; ++i) {
-      if (B_KCONTIG) {
-        rb[i] = ca < C ? *reinterpret_cast<const float4*>(b_src[i] + (size_t)(ca / kv) * head_stride + (ca % kv))
-                       : make_float4(0.f, 0.f, 0.f, 0.f);
+        for (int i = 0; i < 4; ++i) {
+          const float4 v = *reinterpret_cast<const float4*>(src[i >> 1] + off + 4 * (i & 1));
+          rg.x[4 * i] = v.x; rg.x[4 * i + 1] = v.y; rg.x[4 * i + 2] = v.z; rg.x[4 * i + 3] = v.w;
+        }
       } else {
-        const int c = c0 + tid / (BN / 4) + (1024 / BN) * i;
-        rb[i] = c < C ? *reinterpret_cast<const float4*>(b_src[i] + (size_t)c * kv) : make_float4(0.f, 0.f, 0.f, 0.f);
+        const float* at = src[0] + (size_t)min(st * 16 * KG + 8 * o_col, C - 8) * kv;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+          const float2 v = *reinterpret_cast<const float2*>(at + (size_t)i * kv);
+          rg.x[2 * i] = v.x; rg.x[2 * i + 1] = v.y;
+        }
+      }
+    };
+    auto store_stage = [&](int st, Regs& rg) {
+      unsigned char* base = smem + (st & 1) * L::STAGE;
+      const int octet = BY_ROWS ? o_row : o_col;
+      if (st * 16 * KG + 16 * KG > C && st * 16 * KG + 8 * octet >= C) {         // (C is a multiple of 8)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) rg.x[i] = 0.f;
+      }
+      base += (octet >> 1) * L::GROUP + (octet & 1) * (STAGE_A ? L::A_G : L::B_G) + (STAGE_A ? 0 : 3 * L::A_PLANE);
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {            // two rows / columns of eight indices
+        u32x4 t[3];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          const Split3 s = BY_ROWS ? split3(rg.x[8 * i + 2 * k], rg.x[8 * i + 2 * k + 1]) : split3(rg.x[4 * k + i], rg.x[4 * k + 2 + i]);
+          t[0][k] = s.t[0]; t[1][k] = s.t[1]; t[2][k] = s.t[2];
+        }
+        const int r = r_row + (256 / KO) * i;
+        const int at = STAGE_A ? 16 * r : BY_ROWS ? L::slot_bytes(r / L::QCOLS, r % L::QCOLS) : L::slot_bytes((2 * pair + i) % JB, (2 * pair + i) / JB);
+#pragma unroll
+        for (int p = 0; p < 3; ++p) *reinterpret_cast<u32x4*>(base + p * (STAGE_A ? L::A_PLANE : L::B_PLANE) + at) = t[p];
+      }
+    };
+    Regs regs[PD];                             // the PD stages after the one in LDS, on their way
+    load_stage(0, regs[0]);
+    store_stage(0, regs[0]);
+#pragma unroll
+    for (int u = 0; u < PD; ++u) {
+      load_stage(1 + u, regs[(1 + u) % PD]);
+      __builtin_amdgcn_sched_barrier(0);       // requested in the order of use
+    }
+    __syncthreads();
+    for (int s0 = 0; s0 < nst; s0 += PD) {
+#pragma unroll
+      for (int u = 0; u < PD; ++u) {
+        const int st = s0 + u;
+        if (st >= nst) break;
+        if constexpr (STAGE_A) multiply(st & 1);
+        store_stage(st + 1, regs[(u + 1) % PD]);
+        load_stage(st + 1 + PD, regs[(u + 1) % PD]);
+        if constexpr (!STAGE_A) multiply(st & 1);
+        __syncthreads();
       }
     }
   };
-  auto store_lds = [&](int buf) {
-    float* Asb = smem + buf * STAGE;
-    float* Bsb = Asb + A_FLOATS;
-#pragma unroll
-    for (int i = 0; i < A_F4; ++i)
-      *reinterpret_cast<float4*>(Asb + ((tid >> 3) + 32 * i) * kAPitch + 4 * (tid & 7)) = ra[i];
-#pragma unroll
-    for (int i = 0; i < B_F4; ++i) {
-      if (B_KCONTIG)
-        *reinterpret_cast<float4*>(Bsb + ((tid >> 3) + 32 * i) * kAPitch + 4 * (tid & 7)) = rb[i];
-      else
-        *reinterpret_cast<float4*>(Bsb + (tid / (BN / 4) + (1024 / BN) * i) * BPITCH + 4 * (tid % (BN / 4))) = rb[i];
-    }
-  };
 
-  floatx16 acc[RB][CB];
+  floatx16 acc[RB][JB];
 #pragma unroll
   for (int r = 0; r < RB; ++r)
 #pragma unroll
-    for (int c = 0; c < CB; ++c)
+    for (int j = 0; j < JB; ++j)
 #pragma unroll
-      for (int e = 0; e < 16; ++e) acc[r][c][e] = 0.f;
+      for (int e = 0; e < 16; ++e) acc[r][j][e] = 0.f;
 
-  const int nk = (C + BK - 1) / BK;
-  load_global(0);
-  store_lds(0);
-  __syncthreads();
-  for (int kt = 0; kt < nk; ++kt) {
-    const int buf = kt & 1;
-    const float* Asb = smem + buf * STAGE;
-    const float* Bsb = Asb + A_FLOATS;
-    if (kt + 1 < nk) load_global((kt + 1) * BK);
+  auto multiply = [&](int buf) {
+    const unsigned char* As = smem + buf * L::STAGE + kg * L::GROUP + g * L::A_G + (wr * RB * 32 + i32) * 16;
+    const unsigned char* Bs = smem + buf * L::STAGE + kg * L::GROUP + 3 * L::A_PLANE + g * L::B_G + L::slot_bytes(0, wc * 32 + i32);
+    bf16x8 a[3][RB], b[3][JB];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      float4 a[RB];
-      float b[CB][4];
+    for (int p = 0; p < 3; ++p) {
 #pragma unroll
-      for (int r = 0; r < RB; ++r)
-        a[r] = *reinterpret_cast<const float4*>(Asb + (wrow + 32 * r + i32) * kAPitch + 8 * u + 4 * kk);
+      for (int r = 0; r < RB; ++r) a[p][r] = *reinterpret_cast<const bf16x8*>(As + p * L::A_PLANE + r * 512);
 #pragma unroll
-      for (int c = 0; c < CB; ++c) {
-        if (B_KCONTIG) {
-          const float4 t = *reinterpret_cast<const float4*>(Bsb + (wcol + 32 * c + i32) * kAPitch + 8 * u + 4 * kk);
-          b[c][0] = t.x; b[c][1] = t.y; b[c][2] = t.z; b[c][3] = t.w;
-        } else {
-#pragma unroll
-          for (int e = 0; e < 4; ++e) b[c][e] = Bsb[(8 * u + 4 * kk + e) * BPITCH + wcol + 32 * c + i32];
-        }
-      }
-#pragma unroll
-      for (int r = 0; r < RB; ++r)
-#pragma unroll
-        for (int c = 0; c < CB; ++c) {
-          acc[r][c] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[r].x, b[c][0], acc[r][c], 0, 0, 0);
-          acc[r][c] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[r].y, b[c][1], acc[r][c], 0, 0, 0);
-          acc[r][c] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[r].z, b[c][2], acc[r][c], 0, 0, 0);
-          acc[r][c] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[r].w, b[c][3], acc[r][c], 0, 0, 0);
-        }
+      for (int j = 0; j < JB; ++j) b[p][j] = *reinterpret_cast<const bf16x8*>(Bs + p * L::B_PLANE + L::slot_bytes(j, 0));
     }
-    if (kt + 1 < nk) store_lds(buf ^ 1);
+    auto product = [&](int pa, int pb) {
+#pragma unroll
+      for (int r = 0; r < RB; ++r)
+#pragma unroll
+        for (int j = 0; j < JB; ++j) acc[r][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[pa][r], b[pb][j], acc[r][j], 0, 0, 0);
+    };
+    product(0, 0); product(0, 1); product(1, 0); product(1, 1); product(0, 2); product(2, 0);
+  };
+
+  if (wave < 4) run(std::true_type{}, multiply);
+  else run(std::false_type{}, multiply);
+
+  // KG = 2: the second group hands its partial tile over through LDS (free after the last barrier)
+  if constexpr (KG == 2) {
+    float* part = reinterpret_cast<float*>(smem) + (size_t)(wave & 3) * (RB * JB * 16 * 64) + lane;
+    if (kg == 1) {
+#pragma unroll
+      for (int r = 0; r < RB; ++r)
+#pragma unroll
+        for (int j = 0; j < JB; ++j)
+#pragma unroll
+          for (int e = 0; e < 16; ++e) part[((r * JB + j) * 16 + e) * 64] = acc[r][j][e];
+    }
     __syncthreads();
+    if (kg == 1) return;
+#pragma unroll
+    for (int r = 0; r < RB; ++r)
+#pragma unroll
+      for (int j = 0; j < JB; ++j)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc[r][j][e] += part[((r * JB + j) * 16 + e) * 64];
   }
 
-  // D layout of the 32x32 tile: register e of lane (j, g) is element (8 (e/4) + 4 g + e%4, j)
+  // D layout of a 32x32 block: register e of lane (i, g) is element (8 (e/4) + 4 g + e%4, i); the lane's
+  // JB blocks are columns n .. n + JB - 1
+  const int n = n0 + JB * (wc * 32 + i32);
+  if (n >= N) return;                          // (N is a multiple of 8: all JB columns are in or out)
+  typedef __attribute__((ext_vector_type(JB))) float vec;
+  uint32_t redo = 0;                           // rows of the lane with an output that is not finite
+  auto row_of = [&](int re) { return row0 + wr * RB * 32 + 32 * (re >> 4) + 8 * ((re >> 2) & 3) + 4 * g + (re & 3); };
+  auto finish = [&](float* dst, vec x) {
+    if (epilogue == 1) {
 #pragma unroll
-  for (int r = 0; r < RB; ++r)
+      for (int j = 0; j < JB; ++j) x[j] = fmaxf(x[j], 0.f);
+    } else if (epilogue == 2) {
+      x += *reinterpret_cast<vec*>(dst);
+    }
+    *reinterpret_cast<vec*>(dst) = x;
+  };
 #pragma unroll
-    for (int c = 0; c < CB; ++c) {
-      const int n = n0 + wcol + 32 * c + i32;
+  for (int re = 0; re < RB * 16; ++re) {
+    vec x;
+    bool finite = true;
 #pragma unroll
-      for (int e = 0; e < 16; ++e) {
-        const int row = row0 + wrow + 32 * r + 8 * (e >> 2) + 4 * kk + (e & 3);
-        if (row >= rows || n >= N) continue;
-        float* dst = out + (size_t)row * N + n;
-        *dst = apply_epilogue(acc[r][c][e], dst, epilogue);
+    for (int j = 0; j < JB; ++j) {
+      x[j] = acc[re >> 4][j][re & 15];
+      finite = finite && fabsf(x[j]) < INFINITY;
+    }
+    const int row = row_of(re);
+    if (row >= rows) continue;
+    if (!finite) redo |= 1u << re;
+    else finish(out + (size_t)row * N + n, x);
+  }
+  while (redo) {
+    const int row = row_of(__builtin_ctz(redo));
+    redo &= redo - 1;
+    vec x;
+    for (int j = 0; j < JB; ++j) {
+      const float y = plain_dot<B_KCONTIG>(in, P, row, n + j, d, h, kv);
+      if (j == 0) x[0] = y;
+      if (j == 1) x[1] = y;
+      if constexpr (JB == 4) {
+        if (j == 2) x[2] = y;
+        if (j == 3) x[3] = y;
       }
     }
+    finish(out + (size_t)row * N + n, x);
+  }
 }
 
-template <bool KC, int BM, int BN>
-hipError_t launch_tiled(const float* in, const float* P, float* out, int rows, int d, int h, int kv, int N,
+template <bool KC, int BM, int BN, int WR, int WC, int KG, int PD>
+hipError_t launch_split(const float* in, const float* P, float* out, int rows, int d, int h, int kv, int N,
                         int epilogue, hipStream_t st) {
-  constexpr size_t lds = 2 * (size_t)(BM * kAPitch + b_tile_floats<BN>(KC)) * sizeof(float);
-  auto kern = gemm_tiled_kernel<KC, BM, BN>;
-  if (lds > 64 * 1024) {
-    static bool done[64] = {};
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) dev = 0;
-    if (!done[dev]) {
-      hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
-                                         hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-      if (e != hipSuccess) return e;
-      done[dev] = true;
-    }
+  constexpr size_t lds = 2 * (size_t)SplitTile<BM, BN, BN / WC / 32, KG>::STAGE;       // 98 / 99 KiB
+  auto kern = gemm_split_kernel<KC, BM, BN, WR, WC, KG, PD>;
+  static bool done[64] = {};
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) dev = 0;
+  if (!done[dev]) {
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+    done[dev] = true;
   }
-  const dim3 grid((N + BN - 1) / BN, (rows + BM - 1) / BM), block(256);
-  hipLaunchKernelGGL(kern, grid, block, lds, st, in, P, out, rows, d, h, kv, epilogue);
+  const int tm = (rows + BM - 1) / BM, tn = (N + BN - 1) / BN;
+  const long long tiles = (long long)tm * tn;
+  const dim3 grid((unsigned)((tiles + 7) / 8 * 8)), block(512);
+  hipLaunchKernelGGL(kern, grid, block, lds, st, in, P, out, rows, d, h, kv, epilogue, tm, tn);
   return hipGetLastError();
 }
 
@@ -197,15 +300,17 @@ hipError_t launch_gemm_tiled(int mode, const float* in, const float* P, float* o
   const bool outp = (mode == 3);
   const int N = outp ? d : h * kv;
   const long long t128 = (long long)((N + 127) / 128) * ((rows + 127) / 128);
-  const long long t64 = (long long)((N + 63) / 64) * ((rows + 63) / 64);
-  if (N < 64 || rows < 64) return hipErrorNotSupported;
-  if (t128 >= 192)
-    return outp ? launch_tiled<true, 128, 128>(in, P, out, rows, d, h, kv, N, epilogue, st)
-                : launch_tiled<false, 128, 128>(in, P, out, rows, d, h, kv, N, epilogue, st);
-  if (t64 >= 256)
-    return outp ? launch_tiled<true, 64, 64>(in, P, out, rows, d, h, kv, N, epilogue, st)
-                : launch_tiled<false, 64, 64>(in, P, out, rows, d, h, kv, N, epilogue, st);
-  return hipErrorNotSupported;
+  const long long t256 = (long long)((N + 255) / 256) * ((rows + 255) / 256);
+  if (N < 64 || rows < 64 || t128 < 192) return hipErrorNotSupported;
+  // One tile per compute unit at a time.  A 256 x 256 tile takes about three times a 128 x 128 one (four times the
+  // work at 1.35 times the rate): the form with the shorter sum of rounds.  2000 x 1000 . 1000 x 5008: 145 us in three
+  // rounds of 128 x 128 tiles, 120 us in one of 256 x 256; 4096 x 1024 . 1024 x 1024: one round of 128 x 128 tiles, 51 us.
+  const bool wide = 3 * ((t256 + 255) / 256) <= (t128 + 255) / 256;
+  if (wide)
+    return outp ? launch_split<true, 256, 256, 4, 2, 1, 1>(in, P, out, rows, d, h, kv, N, epilogue, st)
+                : launch_split<false, 256, 256, 4, 2, 1, 1>(in, P, out, rows, d, h, kv, N, epilogue, st);
+  return outp ? launch_split<true, 128, 128, 2, 2, 2, 4>(in, P, out, rows, d, h, kv, N, epilogue, st)
+              : launch_split<false, 128, 128, 2, 2, 2, 4>(in, P, out, rows, d, h, kv, N, epilogue, st);
 }
 
 }  // namespace mqa

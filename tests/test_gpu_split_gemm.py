@@ -1,0 +1,84 @@
+"""The large float32 products made of bf16 terms (csrc/gemm.hip): edges of both tile sizes, both weight
+layouts, the epilogues, and values that have no split."""
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+DEV = "cuda:0"
+
+
+@pytest.fixture(scope="module")
+def m():
+    import paper_1911_02150_amd as lib
+    lib.load_library()
+    return lib
+
+
+def product(m, layout, x, W, out=None, epilogue=None):
+    """x [rows,C] . W [C,N] through the entry point whose weights are laid out n-contiguous or c-contiguous."""
+    rows, C = x.shape
+    if layout == "n":
+        return m.mqa_project_qkvo_ex(m.MQA_PROJ_LINEAR, x, W, out=out, epilogue=epilogue or m.MQA_EPI_STORE)
+    kv = 128 if C % 128 == 0 else C
+    P = W.t().contiguous().view(-1, C // kv, kv).permute(1, 0, 2).contiguous()      # [h, N, kv]
+    return m.mqa_project_qkvo_ex(m.MQA_PROJ_O, x.view(rows, C // kv, kv), P, out=out, epilogue=epilogue or m.MQA_EPI_STORE)
+
+
+def bound(x, W):
+    # six products per 16 contraction indices round the running sum once each (2^-24 of it), the terms
+    # dropped are below 2^-25 |a||b|, and the last store rounds once more
+    return (0.375 * x.shape[1] + 4) * 2.0 ** -24 * (x.double().abs() @ W.double().abs())
+
+
+SIZES = [
+    # rows, C, N                            tiles
+    (128, 1024, 24584),      # 128 x 128: one tile row, 8 columns in the last tile column
+    (1601, 72, 2056),        # 128 x 128: one row in the last tile, contraction tail of 8 in a stage of 32
+    (1600, 8, 2048),         # 128 x 128: fewer indices than a stage
+    (4096, 1024, 4096),      # 256 x 256: whole tiles only
+    (4097, 136, 4104),       # 256 x 256: one row, eight columns in the last tiles, tail of 8 in a stage of 16
+    (16000, 40, 1024),       # 256 x 256: tile rows that do not fill a band of eight
+]
+
+
+@pytest.mark.parametrize("layout", ["n", "c"])
+@pytest.mark.parametrize("rows,C,N", SIZES)
+def test_split_gemm(m, layout, rows, C, N):
+    g = torch.Generator(device=DEV)
+    g.manual_seed(rows + C + N)
+    x = torch.randn(rows, C, generator=g, device=DEV) * torch.exp(3 * torch.randn(rows, 1, generator=g, device=DEV))
+    W = torch.randn(C, N, generator=g, device=DEV) * torch.exp(2 * torch.randn(C, 1, generator=g, device=DEV))
+    ref, most = x.double() @ W.double(), bound(x, W)
+    assert ((product(m, layout, x, W).double() - ref).abs() <= most).all()
+    got = product(m, layout, x, W, epilogue=m.MQA_EPI_RELU)
+    assert ((got.double() - ref.clamp(min=0)).abs() <= most).all() and float(got.min()) >= 0
+    held = torch.randn(rows, N, generator=g, device=DEV)
+    got = product(m, layout, x, W, out=held.clone(), epilogue=m.MQA_EPI_ADD)
+    assert ((got.double() - (ref + held.double())).abs() <= most + 2.0 ** -23 * (ref.abs() + held.double().abs())).all()
+
+
+@pytest.mark.parametrize("layout", ["n", "c"])
+@pytest.mark.parametrize("rows,C,N", [(1601, 72, 2056), (4097, 136, 4104)])
+def test_split_gemm_values_without_a_split(m, layout, rows, C, N):
+    """Infinities, NaN, the largest floats (their first term would round to infinity) and overflowing outputs."""
+    g = torch.Generator(device=DEV)
+    g.manual_seed(5)
+    x = torch.randn(rows, C, generator=g, device=DEV)
+    W = torch.randn(C, N, generator=g, device=DEV) / 16
+    big = float(np.finfo(np.float32).max)
+    x[3, 5], x[rows - 1, 0] = float("inf"), float("-inf")
+    x[7], x[130, C - 1] = float("nan"), float("nan")
+    x[9, :] = 0
+    x[9, 11] = big                           # one product of the largest float per output of the row
+    x[11, :8] = 1e30
+    W[:8, 2] = 1e30                          # that output overflows
+    W[:, N - 1] = 0                          # inf . 0
+    ref = (x.double() @ W.double()).float()
+    got = product(m, layout, x, W)
+    assert torch.equal(torch.isnan(got), torch.isnan(ref))
+    assert torch.equal(torch.isposinf(got), torch.isposinf(ref)) and torch.equal(torch.isneginf(got), torch.isneginf(ref))
+    fine = torch.isfinite(ref)
+    lim = torch.nan_to_num(bound(x, W), nan=0.0, posinf=0.0)
+    assert ((got.double() - ref.double()).abs()[fine] <= lim[fine] + 2.0 ** -23 * ref.double().abs()[fine]).all()
