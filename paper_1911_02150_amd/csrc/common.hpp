@@ -156,22 +156,28 @@ __device__ __forceinline__ uint32_t pack_bf16_pair(float a, float b) {
   return __builtin_bit_cast(uint32_t, __builtin_convertvector(f2{a, b}, b2));
 }
 
-// A pair of floats as three packed bf16 pairs whose sums are the floats: each term is the nearest
-// bf16 of what the terms before it leave (the differences are exact), 3 x 8 significant bits.
-struct Split3 { uint32_t t[3]; };
-__device__ __forceinline__ Split3 split3(float a, float b) {
-  Split3 s;
-#pragma unroll
-  for (int p = 0; p < 3; ++p) {
-    s.t[p] = pack_bf16_pair(a, b);
-    a -= __uint_as_float(s.t[p] << 16);
-    b -= __uint_as_float(s.t[p] & 0xffff0000u);
-  }
+// A pair of floats as two packed fp16 pairs whose sums are nearly the floats: each term is the nearest
+// fp16 of what the terms before it leave (the difference is exact).  The floats are scaled beforehand:
+// below 2^-2 the second term loses bits, above 65504 the first overflows.
+struct Split2 { uint32_t hi, lo; };
+__device__ __forceinline__ Split2 split2(float a, float b) {
+  typedef __attribute__((ext_vector_type(2))) float f2;
+  typedef __attribute__((ext_vector_type(2))) _Float16 h2;
+  Split2 s;
+  s.hi = __builtin_bit_cast(uint32_t, __builtin_convertvector(f2{a, b}, h2));
+  asm("" : "+v"(s.hi));            // (the two halves are read from the packed register, not rounded once more each)
+  const h2 h = __builtin_bit_cast(h2, s.hi);
+  s.lo = __builtin_bit_cast(uint32_t, __builtin_convertvector(f2{a - (float)h[0], b - (float)h[1]}, h2));
   return s;
 }
+// The power of two that takes `most` to [2^9, 2^10), and the exponent that takes it back.
+__device__ __forceinline__ float split_scale(float most) {
+  return __uint_as_float((uint32_t)min(254, 263 - (int)(__float_as_uint(most) >> 23)) << 23);
+}
+__device__ __forceinline__ int split_exponent(float scale) { return 127 - (int)(__float_as_uint(scale) >> 23); }
 
 // out[row][n] of in . B in plain float32, index by index: for the outputs of a split product that
-// are not finite (an infinity, or an overflow of a term).  Ends at the first NaN of its own.
+// are not finite (an infinity, or an overflow).  Ends at the first NaN of its own.
 template <bool B_KCONTIG>
 __device__ __noinline__ float plain_dot(const float* in, const float* P, int row, int n, int d, int h, int kv) {
   const int C = B_KCONTIG ? h * kv : d;

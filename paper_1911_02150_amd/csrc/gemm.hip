@@ -3,22 +3,27 @@
 // inside the projection tensor P [h, d, kv] exactly as in project.hip.
 //
 // The float32 matrix instructions are the bound of such a product (157 TFLOP/s against 2.5 PFLOP/s
-// in bf16), so every float32 operand is written as three bf16 terms x = x0 + x1 + x2 (each the
-// nearest bf16 of what the terms before it leave: 24 significant bits, so the sum IS x) and the
-// product as the six bf16 products of order up to 2^-16,
-//   a.b = a0b0 + (a0b1 + a1b0) + (a0b2 + a1b1 + a2b0)        (what is dropped is below 2^-25 |a||b|)
-// accumulated in float32 on v_mfma_f32_32x32x16_bf16.  A bf16 product is exact in float32 and an
+// in 16 bits), so every float32 operand x is scaled by a power of two and written as two fp16 terms,
+// x s = h + l, each the nearest fp16 of what is left (22 to 24 significant bits), and the product as
+//   a.b = ah bh + (ah bl + al bh)                            (al bl is below 2^-22 |a||b|, 2^-25 typically)
+// accumulated in float32 on v_mfma_f32_32x32x16_f16.  An fp16 product is exact in float32 and an
 // instruction adds 16 of them with one rounding of the running sum, where the float32
-// instruction rounds after every second one: relative error of a 1024-term sum of normal
-// deviates 5.0e-7 against 5.8e-7, of a 4096-term one 1.0e-6 against 1.15e-6.
-// An infinity has no such split (inf - inf), and a term may overflow where the sum does not: an
-// output that is not finite is computed again in plain float32.
+// instruction rounds after every second one: the shorter chain of roundings more than pays for the terms.
+// Relative error of a 1024-term sum of normal deviates 3.6e-7 (float32 instructions: 5.7e-7), of a
+// 4096-term one 7.2e-7 (1.15e-6), of a 520-term one 2.7e-7.
+// Scales: one per row of A and per column of B in a tile, such that the largest value among the first
+// stage's comes to [2^9, 2^10): the terms are then full for values down to 2^-11 of it, below that the
+// error is 2^-35 of it.  The largest value is followed through the whole contraction; if one
+// comes to more than 2^15 (or, in a row that began with zeros, all stay below 2^4), the scales are set
+// again from the largest values and the tile is multiplied again.
+// An infinity or NaN has no such split: an output that is not finite is computed again in plain float32.
 //
-// Measured (b=128, n=128 prompt: rows = 16384, TFLOP/s of the float32 product; before: 128x128 tiles of
-// v_mfma_f32_32x32x2_f32): 1024 x 4096: 126 -> 224; 4096 x 1024: 129 -> 228; 1024 x 1024: 122 -> 220,
-// i.e. 1.35 PFLOP/s of bf16 products at 72 % matrix-core utilisation and the 1.6 GHz the card clocks
-// down to under this load (hipBLASLt's 8192^3 bf16 product reaches 1.29 here).  128x128 tiles, fewer
-// flops per staged byte: 104 -> 165 at 1024 x 1024 . 1024 x 4096, logits of 128 rows 101 -> 145.
+// Measured (b=128, n=128 prompt: rows = 16384, TFLOP/s of the float32 product; 128x128 tiles of
+// v_mfma_f32_32x32x2_f32 / three bf16 terms and six products / this): 1024 x 4096: 126 / 224 / 335; 4096 x 1024:
+// 129 / 228 / 340; 1024 x 1024: 122 / 220 / 327; logits of 128 rows 101 / 145 / 200.  That is 1.0 PFLOP/s of fp16
+// products with the matrix cores busy 51 % of the 1.9 GHz the card runs at under this load (hipBLASLt's 8192^3 bf16
+// product reaches 1.29 here); vector instructions take 30 %, LDS 22 %.  More stages ahead in registers (2, 3), or two
+// stages per barrier in LDS, measured the same.
 //
 // Workgroup: 512 threads, two waves per SIMD, tile BM x BN, WR x WC waves in each of KG groups; a
 // stage holds 16*KG contraction indices, group kg works on 16 of them.  Stages go
@@ -37,10 +42,10 @@ namespace mqa {
 namespace {
 
 typedef __attribute__((ext_vector_type(16))) float floatx16;
-typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
+typedef __attribute__((ext_vector_type(8))) _Float16 halfx8;
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 
-// LDS of a stage, in bytes: per group A's three planes, then B's three planes; a plane is two halves g
+// LDS of a stage, in bytes: per group A's two planes, then B's two planes; a plane is two halves g
 // of 16 bytes per row (A) or slot (B): contraction indices 8g .. 8g+7.  Column n of the tile lives in slot
 // n / JB of column block n % JB.  The few bytes between the halves, groups and column blocks put what
 // eight consecutive lanes write (two halves of four rows, two groups of two rows, or two column
@@ -50,8 +55,13 @@ template <int BM, int BN, int JB, int KG> struct SplitTile {
   static constexpr int B_BLOCK = QCOLS * 16 + (JB == 4 ? 32 : 0);
   static constexpr int A_G = BM * 16 + 64 / KG, B_G = JB * B_BLOCK + 64 / KG;
   static constexpr int A_PLANE = 2 * A_G, B_PLANE = 2 * B_G;
-  static constexpr int GROUP = 3 * (A_PLANE + B_PLANE) + (KG == 2 ? 64 : 0);
+  static constexpr int GROUP = 2 * (A_PLANE + B_PLANE) + (KG == 2 ? 64 : 0);
   static constexpr int STAGE = KG * GROUP;
+  // behind the two stages (and, KG = 2, the partial tile that re-uses them): the largest values and the
+  // scales' exponents of the tile's rows and columns, and a flag
+  static constexpr int PART = KG == 2 ? BM * BN * 4 : 0;
+  static constexpr int STATE = 2 * STAGE > PART ? 2 * STAGE : PART;
+  static constexpr int BYTES = STATE + (BM + BN) * 8 + 16;
   static __device__ __host__ constexpr int slot_bytes(int block, int slot) { return block * B_BLOCK + slot * 16; }
 };
 
@@ -85,6 +95,9 @@ void gemm_split_kernel(const float* __restrict__ in, const float* __restrict__ P
   const size_t head_stride = (size_t)d * kv;
   const int ts = tid & 255;
   const int nst = (C + 16 * KG - 1) / (16 * KG);
+  uint32_t* most = reinterpret_cast<uint32_t*>(smem + L::STATE);        // [BM + BN] bits of the largest |value| seen
+  int* expo = reinterpret_cast<int*>(most + BM + BN);                   // [BM + BN] the tile holds x . 2^-expo
+  int* again = expo + BM + BN;
 
   // ---- staging: 16 values per thread and stage.  Loads are unconditional (indices past the contraction
   // are clamped and their values zeroed when the last stage is split), so that the compiler can
@@ -94,8 +107,14 @@ void gemm_split_kernel(const float* __restrict__ in, const float* __restrict__ P
   const int o_row = ts % KO, r_row = ts / KO;
   const int w4 = wave & 3;
   const int pair = lane + 64 * (w4 % (BN / 128)), o_col = w4 / (BN / 128);
-  auto run = [&](auto role, auto&& multiply) {
+  auto run = [&](auto role, auto&& clear, auto&& multiply) {
     constexpr bool STAGE_A = decltype(role)::value, BY_ROWS = STAGE_A || B_KCONTIG;
+    uint32_t* const my_most = most + (STAGE_A ? 0 : BM);
+    int* const my_expo = expo + (STAGE_A ? 0 : BM);
+    int line[2];                               // the thread's two rows of A or columns of B (by their place in LDS)
+#pragma unroll
+    for (int i = 0; i < 2; ++i) line[i] = BY_ROWS ? r_row + (256 / KO) * i : 2 * pair + i;
+    float scale[2], peak[2];                   // of these two: the scale, and the largest scaled |value| so far
     const float* src[BY_ROWS ? 2 : 1];
     if constexpr (BY_ROWS) {
 #pragma unroll
@@ -127,81 +146,136 @@ void gemm_split_kernel(const float* __restrict__ in, const float* __restrict__ P
         }
       }
     };
-    auto store_stage = [&](int st, Regs& rg) {
-      unsigned char* base = smem + (st & 1) * L::STAGE;
-      const int octet = BY_ROWS ? o_row : o_col;
-      if (st * 16 * KG + 16 * KG > C && st * 16 * KG + 8 * octet >= C) {         // (C is a multiple of 8)
+    auto value = [&](const Regs& rg, int i, int k) -> float { return BY_ROWS ? rg.x[8 * i + k] : rg.x[2 * k + i]; };
+    auto drop_tail = [&](int st, Regs& rg) {   // (C is a multiple of 8)
+      if (st * 16 * KG + 16 * KG > C && st * 16 * KG + 8 * (BY_ROWS ? o_row : o_col) >= C) {
 #pragma unroll
         for (int i = 0; i < 16; ++i) rg.x[i] = 0.f;
       }
-      base += (octet >> 1) * L::GROUP + (octet & 1) * (STAGE_A ? L::A_G : L::B_G) + (STAGE_A ? 0 : 3 * L::A_PLANE);
+    };
+    auto store_stage = [&](int st, Regs& rg) {
+      unsigned char* base = smem + (st & 1) * L::STAGE;
+      const int octet = BY_ROWS ? o_row : o_col;
+      drop_tail(st, rg);
+      base += (octet >> 1) * L::GROUP + (octet & 1) * (STAGE_A ? L::A_G : L::B_G) + (STAGE_A ? 0 : 2 * L::A_PLANE);
 #pragma unroll
       for (int i = 0; i < 2; ++i) {            // two rows / columns of eight indices
-        u32x4 t[3];
+        u32x4 t[2];
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
-          const Split3 s = BY_ROWS ? split3(rg.x[8 * i + 2 * k], rg.x[8 * i + 2 * k + 1]) : split3(rg.x[4 * k + i], rg.x[4 * k + 2 + i]);
-          t[0][k] = s.t[0]; t[1][k] = s.t[1]; t[2][k] = s.t[2];
+          const float a = value(rg, i, 2 * k) * scale[i], b = value(rg, i, 2 * k + 1) * scale[i];
+          peak[i] = fmaxf(peak[i], fmaxf(fabsf(a), fabsf(b)));
+          const Split2 s = split2(a, b);
+          t[0][k] = s.hi; t[1][k] = s.lo;
         }
-        const int r = r_row + (256 / KO) * i;
-        const int at = STAGE_A ? 16 * r : BY_ROWS ? L::slot_bytes(r / L::QCOLS, r % L::QCOLS) : L::slot_bytes((2 * pair + i) % JB, (2 * pair + i) / JB);
+        const int at = BY_ROWS && !STAGE_A ? L::slot_bytes(line[i] / L::QCOLS, line[i] % L::QCOLS) : STAGE_A ? 16 * line[i] : L::slot_bytes(line[i] % JB, line[i] / JB);
 #pragma unroll
-        for (int p = 0; p < 3; ++p) *reinterpret_cast<u32x4*>(base + p * (STAGE_A ? L::A_PLANE : L::B_PLANE) + at) = t[p];
+        for (int p = 0; p < 2; ++p) *reinterpret_cast<u32x4*>(base + p * (STAGE_A ? L::A_PLANE : L::B_PLANE) + at) = t[p];
+      }
+    };
+    // scales from the largest values known; a line of zeros so far takes the largest of the tile's lines
+    auto set_scales = [&]() {
+      float whole = 0.f;
+#pragma unroll
+      for (int i = 0; i < (STAGE_A ? BM : BN) / 64; ++i) whole = fmaxf(whole, __uint_as_float(my_most[lane + 64 * i]));
+      whole = wave_max(whole);
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        const float m = __uint_as_float(my_most[line[i]]);
+        scale[i] = split_scale(m > 0.f ? m : whole > 0.f ? whole : 1.f);
+        my_expo[line[i]] = split_exponent(scale[i]);
+        peak[i] = 0.f;
       }
     };
     Regs regs[PD];                             // the PD stages after the one in LDS, on their way
-    load_stage(0, regs[0]);
-    store_stage(0, regs[0]);
+    for (int round = 0;; ++round) {
+      load_stage(0, regs[0]);
+      if (round == 0) {
+        drop_tail(0, regs[0]);
 #pragma unroll
-    for (int u = 0; u < PD; ++u) {
-      load_stage(1 + u, regs[(1 + u) % PD]);
-      __builtin_amdgcn_sched_barrier(0);       // requested in the order of use
-    }
-    __syncthreads();
-    for (int s0 = 0; s0 < nst; s0 += PD) {
+        for (int i = 0; i < 2; ++i) {
+          float m = 0.f;
 #pragma unroll
-      for (int u = 0; u < PD; ++u) {
-        const int st = s0 + u;
-        if (st >= nst) break;
-        if constexpr (STAGE_A) multiply(st & 1);
-        store_stage(st + 1, regs[(u + 1) % PD]);
-        load_stage(st + 1 + PD, regs[(u + 1) % PD]);
-        if constexpr (!STAGE_A) multiply(st & 1);
+          for (int k = 0; k < 8; ++k) m = fmaxf(m, fabsf(value(regs[0], i, k)));
+          atomicMax(&my_most[line[i]], __float_as_uint(m));
+        }
         __syncthreads();
       }
+      set_scales();
+      clear();
+      store_stage(0, regs[0]);
+#pragma unroll
+      for (int u = 0; u < PD; ++u) {
+        load_stage(1 + u, regs[u]);
+        __builtin_amdgcn_sched_barrier(0);     // requested in the order of use
+      }
+      __syncthreads();
+      for (int s0 = 0; s0 < nst; s0 += PD) {
+#pragma unroll
+        for (int u = 0; u < PD; ++u) {
+          const int st = s0 + u;
+          if (st >= nst) break;
+          if constexpr (STAGE_A) multiply(st & 1);
+          store_stage(st + 1, regs[u]);
+          load_stage(st + 1 + PD, regs[u]);
+          if constexpr (!STAGE_A) multiply(st & 1);
+          __syncthreads();
+        }
+      }
+      // did the scales fit the whole contraction?  (a scaled value that overflowed is an infinity here: the next
+      // round, with the smallest scale, finds the true largest values for the one after it)
+      if (round == 2) break;
+#pragma unroll
+      for (int i = 0; i < 2; ++i) my_most[line[i]] = 0;
+      __syncthreads();
+#pragma unroll
+      for (int i = 0; i < 2; ++i) atomicMax(&my_most[line[i]], __float_as_uint(ldexpf(peak[i], split_exponent(scale[i]))));
+      __syncthreads();
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        const float m = __uint_as_float(my_most[line[i]]), ms = m * scale[i];
+        if ((ms > 32768.f && (m < INFINITY || scale[i] > split_scale(INFINITY))) || (ms > 0.f && ms < 16.f)) *again = round + 1;
+      }
+      __syncthreads();
+      if (*again != round + 1) break;
     }
   };
 
   floatx16 acc[RB][JB];
+  auto clear = [&]() {
 #pragma unroll
-  for (int r = 0; r < RB; ++r)
+    for (int r = 0; r < RB; ++r)
 #pragma unroll
-    for (int j = 0; j < JB; ++j)
+      for (int j = 0; j < JB; ++j)
 #pragma unroll
-      for (int e = 0; e < 16; ++e) acc[r][j][e] = 0.f;
+        for (int e = 0; e < 16; ++e) acc[r][j][e] = 0.f;
+  };
 
   auto multiply = [&](int buf) {
     const unsigned char* As = smem + buf * L::STAGE + kg * L::GROUP + g * L::A_G + (wr * RB * 32 + i32) * 16;
-    const unsigned char* Bs = smem + buf * L::STAGE + kg * L::GROUP + 3 * L::A_PLANE + g * L::B_G + L::slot_bytes(0, wc * 32 + i32);
-    bf16x8 a[3][RB], b[3][JB];
+    const unsigned char* Bs = smem + buf * L::STAGE + kg * L::GROUP + 2 * L::A_PLANE + g * L::B_G + L::slot_bytes(0, wc * 32 + i32);
+    halfx8 a[2][RB], b[2][JB];
 #pragma unroll
-    for (int p = 0; p < 3; ++p) {
+    for (int p = 0; p < 2; ++p) {
 #pragma unroll
-      for (int r = 0; r < RB; ++r) a[p][r] = *reinterpret_cast<const bf16x8*>(As + p * L::A_PLANE + r * 512);
+      for (int r = 0; r < RB; ++r) a[p][r] = *reinterpret_cast<const halfx8*>(As + p * L::A_PLANE + r * 512);
 #pragma unroll
-      for (int j = 0; j < JB; ++j) b[p][j] = *reinterpret_cast<const bf16x8*>(Bs + p * L::B_PLANE + L::slot_bytes(j, 0));
+      for (int j = 0; j < JB; ++j) b[p][j] = *reinterpret_cast<const halfx8*>(Bs + p * L::B_PLANE + L::slot_bytes(j, 0));
     }
     auto product = [&](int pa, int pb) {
 #pragma unroll
       for (int r = 0; r < RB; ++r)
 #pragma unroll
-        for (int j = 0; j < JB; ++j) acc[r][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[pa][r], b[pb][j], acc[r][j], 0, 0, 0);
+        for (int j = 0; j < JB; ++j) acc[r][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[pa][r], b[pb][j], acc[r][j], 0, 0, 0);
     };
-    product(0, 0); product(0, 1); product(1, 0); product(1, 1); product(0, 2); product(2, 0);
+    product(0, 0); product(0, 1); product(1, 0);
   };
 
-  if (wave < 4) run(std::true_type{}, multiply);
-  else run(std::false_type{}, multiply);
+  for (int i = tid; i < BM + BN; i += 512) most[i] = 0;
+  if (tid == 0) *again = 0;
+  __syncthreads();
+  if (wave < 4) run(std::true_type{}, clear, multiply);
+  else run(std::false_type{}, clear, multiply);
 
   // KG = 2: the second group hands its partial tile over through LDS (free after the last barrier)
   if constexpr (KG == 2) {
@@ -229,8 +303,12 @@ void gemm_split_kernel(const float* __restrict__ in, const float* __restrict__ P
   const int n = n0 + JB * (wc * 32 + i32);
   if (n >= N) return;                          // (N is a multiple of 8: all JB columns are in or out)
   typedef __attribute__((ext_vector_type(JB))) float vec;
+  int col_expo[JB];                            // (column q JB + j of the tile: by slots where c is contiguous)
+#pragma unroll
+  for (int j = 0; j < JB; ++j) col_expo[j] = expo[BM + (B_KCONTIG ? j * L::QCOLS + wc * 32 + i32 : n - n0 + j)];
   uint32_t redo = 0;                           // rows of the lane with an output that is not finite
-  auto row_of = [&](int re) { return row0 + wr * RB * 32 + 32 * (re >> 4) + 8 * ((re >> 2) & 3) + 4 * g + (re & 3); };
+  auto row_in_tile = [&](int re) { return wr * RB * 32 + 32 * (re >> 4) + 8 * ((re >> 2) & 3) + 4 * g + (re & 3); };
+  auto row_of = [&](int re) { return row0 + row_in_tile(re); };
   auto finish = [&](float* dst, vec x) {
     if (epilogue == 1) {
 #pragma unroll
@@ -244,9 +322,10 @@ void gemm_split_kernel(const float* __restrict__ in, const float* __restrict__ P
   for (int re = 0; re < RB * 16; ++re) {
     vec x;
     bool finite = true;
+    const int row_expo = expo[row_in_tile(re)];
 #pragma unroll
     for (int j = 0; j < JB; ++j) {
-      x[j] = acc[re >> 4][j][re & 15];
+      x[j] = ldexpf(acc[re >> 4][j][re & 15], row_expo + col_expo[j]);
       finite = finite && fabsf(x[j]) < INFINITY;
     }
     const int row = row_of(re);
@@ -274,7 +353,7 @@ void gemm_split_kernel(const float* __restrict__ in, const float* __restrict__ P
 template <bool KC, int BM, int BN, int WR, int WC, int KG, int PD>
 hipError_t launch_split(const float* in, const float* P, float* out, int rows, int d, int h, int kv, int N,
                         int epilogue, hipStream_t st) {
-  constexpr size_t lds = 2 * (size_t)SplitTile<BM, BN, BN / WC / 32, KG>::STAGE;       // 98 / 99 KiB
+  constexpr size_t lds = SplitTile<BM, BN, BN / WC / 32, KG>::BYTES;       // 70 KiB
   auto kern = gemm_split_kernel<KC, BM, BN, WR, WC, KG, PD>;
   static bool done[64] = {};
   int dev = 0;
@@ -309,8 +388,8 @@ hipError_t launch_gemm_tiled(int mode, const float* in, const float* P, float* o
   if (wide)
     return outp ? launch_split<true, 256, 256, 4, 2, 1, 1>(in, P, out, rows, d, h, kv, N, epilogue, st)
                 : launch_split<false, 256, 256, 4, 2, 1, 1>(in, P, out, rows, d, h, kv, N, epilogue, st);
-  return outp ? launch_split<true, 128, 128, 2, 2, 2, 4>(in, P, out, rows, d, h, kv, N, epilogue, st)
-              : launch_split<false, 128, 128, 2, 2, 2, 4>(in, P, out, rows, d, h, kv, N, epilogue, st);
+  return outp ? launch_split<true, 128, 128, 2, 2, 2, 3>(in, P, out, rows, d, h, kv, N, epilogue, st)
+              : launch_split<false, 128, 128, 2, 2, 2, 3>(in, P, out, rows, d, h, kv, N, epilogue, st);
 }
 
 }  // namespace mqa

@@ -1,4 +1,4 @@
-"""The large float32 products made of bf16 terms (csrc/gemm.hip): edges of both tile sizes, both weight
+"""The large float32 products made of fp16 terms (csrc/gemm.hip): edges of both tile sizes, both weight
 layouts, the epilogues, and values that have no split."""
 import numpy as np
 import pytest
@@ -27,9 +27,13 @@ def product(m, layout, x, W, out=None, epilogue=None):
 
 
 def bound(x, W):
-    # six products per 16 contraction indices round the running sum once each (2^-24 of it), the terms
-    # dropped are below 2^-25 |a||b|, and the last store rounds once more
-    return (0.375 * x.shape[1] + 4) * 2.0 ** -24 * (x.double().abs() @ W.double().abs())
+    # three products per 16 contraction indices round the running sum once each (2^-24 of it); two terms hold an
+    # operand to 2^-23 and the product of the second terms, at most 2^-22 |a||b|, is dropped (together 8 . 2^-24);
+    # the scaling back and the last store round once more each; and terms below 2^-24 of the scaled operand
+    # cost 2^-35 of a row's (column's) largest value (x 2 for the scale's power of two and the dropped product)
+    a, b = x.double().abs(), W.double().abs()
+    small = 2.0 ** -34 * (a.amax(1, keepdim=True) * b.sum(0, keepdim=True) + a.sum(1, keepdim=True) * b.amax(0, keepdim=True))
+    return (0.1875 * x.shape[1] + 12) * 2.0 ** -24 * (a @ b) + small
 
 
 SIZES = [
@@ -57,6 +61,27 @@ def test_split_gemm(m, layout, rows, C, N):
     held = torch.randn(rows, N, generator=g, device=DEV)
     got = product(m, layout, x, W, out=held.clone(), epilogue=m.MQA_EPI_ADD)
     assert ((got.double() - (ref + held.double())).abs() <= most + 2.0 ** -23 * (ref.abs() + held.double().abs())).all()
+
+
+@pytest.mark.parametrize("layout", ["n", "c"])
+@pytest.mark.parametrize("rows,C,N", [(1601, 72, 2056), (4097, 136, 4104)])
+def test_split_gemm_scales(m, layout, rows, C, N):
+    """Lines that begin with zeros or with values far from those that follow: the scales are set a second time."""
+    g = torch.Generator(device=DEV)
+    g.manual_seed(7)
+    x = torch.randn(rows, C, generator=g, device=DEV)
+    W = torch.randn(C, N, generator=g, device=DEV)
+    x[:, :40] *= torch.where(torch.rand(rows, 1, generator=g, device=DEV) < 0.02, 0.0, 1.0)
+    x[5, :40], x[6, :40], x[rows - 1, :40] = 1e-6, 1e-30, 0
+    x[8] *= 1e-30
+    x[17] *= 1e25
+    W[:40, 3], W[:40, 300], W[:40, N - 1] = 0, 1e-20, 1e-3
+    W[40:, 301] *= 1e-12
+    W[:, 302] *= 1e-30
+    x[20] = 0
+    W[:, 40] = 0
+    ref, got = x.double() @ W.double(), product(m, layout, x, W).double()
+    assert ((got - ref).abs() <= bound(x, W) + 2.0 ** -149).all()
 
 
 @pytest.mark.parametrize("layout", ["n", "c"])
