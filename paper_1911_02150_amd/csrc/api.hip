@@ -115,6 +115,16 @@ CombineSegment segment_of(const DecodeParams& p) {
   return sg;
 }
 
+// Float32 caches, and bf16 caches the bf16 MFMA kernel does not cover: the float32 matrix instructions where they
+// fit (k = v = 64 or 128), else plain float32.
+hipError_t launch_decode_float(const DecodeParams& p, bool is_bf16, bool force_generic, hipStream_t st) {
+  if (!force_generic) {
+    const hipError_t e = launch_decode_direct(p, is_bf16, st);
+    if (e != hipErrorNotSupported) return e;
+  }
+  return launch_decode_generic(p, is_bf16, st);
+}
+
 int check_decode_args(const float* q, const void* K, const void* V, const int32_t* lens, const float* o,
                       int b, int h, int cap, int k, int v, int dt, bool need_qkv) {
   if (!lens || !o || (need_qkv && (!q || !K || !V))) return MQA_ERR_NULL;
@@ -189,7 +199,7 @@ int decode_impl(const float* q, const void* K, const void* V, const int32_t* len
   if (phase & 1) {
     if (order && launch_length_order(lens, p.lens_div, nseq, cap, order, st) != hipSuccess) return MQA_ERR_LAUNCH;
     hipError_t e = pl.use_mfma ? launch_decode_mfma(p, tn.flags, st)
-                               : launch_decode_generic(p, dt == MQA_BF16, st);
+                               : launch_decode_float(p, dt == MQA_BF16, tn.kernel == 1, st);
     if (e != hipSuccess) return MQA_ERR_LAUNCH;
   }
   if ((phase & 2) && pl.S > 1) {
@@ -456,9 +466,9 @@ int mqa_decode_step_beams(const float* q, const void* K_src, const void* V_src, 
     if (launch_decode_mfma_two(ps, (long long)ps.nseq * ps.S * hg_src, (long long)po.nseq * po.S * hg_own, st) != hipSuccess)
       return MQA_ERR_LAUNCH;
   } else {
-    hipError_t e = bp.src.use_mfma ? launch_decode_mfma(ps, 0, st) : launch_decode_generic(ps, dt == MQA_BF16, st);
+    hipError_t e = bp.src.use_mfma ? launch_decode_mfma(ps, 0, st) : launch_decode_float(ps, dt == MQA_BF16, false, st);
     if (e != hipSuccess) return MQA_ERR_LAUNCH;
-    e = bp.own.use_mfma ? launch_decode_mfma(po, 0, st) : launch_decode_generic(po, dt == MQA_BF16, st);
+    e = bp.own.use_mfma ? launch_decode_mfma(po, 0, st) : launch_decode_float(po, dt == MQA_BF16, false, st);
     if (e != hipSuccess) return MQA_ERR_LAUNCH;
   }
   CombineParams c;

@@ -90,6 +90,9 @@ hipError_t launch_decode_mfma(const DecodeParams& p, int flags, hipStream_t st);
 // both segments in one launch (p.seg1 filled in, 32 heads per workgroup in both); p.order must be null
 hipError_t launch_decode_mfma_two(const DecodeParams& p, long long nblocks0, long long nblocks1, hipStream_t st);
 
+// decode_direct.hip: k = v = 64 or 128 in float32, 64 in bf16 (hipErrorNotSupported: another shape).
+hipError_t launch_decode_direct(const DecodeParams& p, int is_bf16, hipStream_t st);
+
 // decode_generic.hip: any k, v <= 256, float32 or bf16 cache.
 hipError_t launch_decode_generic(const DecodeParams& p, int is_bf16, hipStream_t st);
 

@@ -1,6 +1,6 @@
 // Generic decode attention: float32 or bf16 cache, any k, v <= 256 (multiples of 8), any
 // number of heads, plain float32 FMAs.  Same contract and partial-state format as the MFMA
-// kernel; used for float32 caches and for shapes the MFMA kernel does not cover.  One
+// kernel; used for the widths that neither decode_mfma.hip nor decode_direct.hip covers.  One
 // workgroup per (KV group, position range); heads are processed in groups of 8, positions in
 // tiles of 64 or 128 whose K and V rows are staged in LDS with wide loads all in flight at once
 // (these shapes are latency-bound: the point is few dependent round trips, not bandwidth).
