@@ -26,8 +26,11 @@
 // stages per barrier in LDS, measured the same.
 //
 // Workgroup: 512 threads, two waves per SIMD, tile BM x BN, WR x WC waves in each of KG groups; a
-// stage holds 16*KG contraction indices, group kg works on 16 of them.  Stages go
-// global -> registers (one stage ahead) -> split -> LDS (two buffers, one barrier per stage).
+// stage holds 16*KG contraction indices, group kg works on 16 of them (KG > 1: the groups' tiles are added in
+// LDS at the end).  Tiles of 256 (KG = 1) to 32 (KG = 8) square: the smaller ones stage more indices at a time, so that
+// every form moves the same 32 KiB of operands per barrier, and below 128 two workgroups share a compute unit, one
+// loading while the other multiplies (2048 x 1024 . 1024 x 2048 in 64 x 64 tiles: 65 -> 50 us).  Stages go
+// global -> registers (PD stages ahead) -> split -> LDS (two buffers, one barrier per stage).
 // Threads 0..255 stage A before they multiply, threads 256..511 stage B after they have: the
 // two waves of a SIMD are then out of step and one splits while the other multiplies.
 //
@@ -36,6 +39,7 @@
 // 4*JB bytes).
 #include "common.hpp"
 
+#include <math.h>
 #include <type_traits>
 
 namespace mqa {
@@ -53,22 +57,30 @@ typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 template <int BM, int BN, int JB, int KG> struct SplitTile {
   static constexpr int QCOLS = BN / JB;
   static constexpr int B_BLOCK = QCOLS * 16 + (JB == 4 ? 32 : 0);
-  static constexpr int A_G = BM * 16 + 64 / KG, B_G = JB * B_BLOCK + 64 / KG;
+  static constexpr int PAD = KG >= 4 ? 16 : 64 / KG;
+  static constexpr int A_G = BM * 16 + PAD, B_G = JB * B_BLOCK + PAD;
   static constexpr int A_PLANE = 2 * A_G, B_PLANE = 2 * B_G;
-  static constexpr int GROUP = 2 * (A_PLANE + B_PLANE) + (KG == 2 ? 64 : 0);
+  static constexpr int GROUP = 2 * (A_PLANE + B_PLANE) + (KG >= 4 ? 32 : KG == 2 ? 64 : 0);
   static constexpr int STAGE = KG * GROUP;
-  // behind the two stages (and, KG = 2, the partial tile that re-uses them): the largest values and the
-  // scales' exponents of the tile's rows and columns, and a flag
-  static constexpr int PART = KG == 2 ? BM * BN * 4 : 0;
+  // behind the two stages (and, KG > 1, the groups' partial tiles that re-use them): the largest values and
+  // the scales' exponents of the tile's rows and columns, and a flag
+  static constexpr int PART = KG > 1 ? KG * BM * BN * 4 : 0;
   static constexpr int STATE = 2 * STAGE > PART ? 2 * STAGE : PART;
   static constexpr int BYTES = STATE + (BM + BN) * 8 + 16;
   static __device__ __host__ constexpr int slot_bytes(int block, int slot) { return block * B_BLOCK + slot * 16; }
+  // n contiguous, one column block: even columns in the first half of the slots, odd ones in the second, so
+  // that the lanes of a pair of columns each write neighbouring slots
+  static __device__ __host__ constexpr int column_at(int column) { return JB > 1 ? slot_bytes(column % JB, column / JB) : slot_bytes(0, (column & 1) * (BN / 2) + (column >> 1)); }
 };
+
+template <typename V> __device__ __forceinline__ V load_at(const float* base, uint32_t bytes) {
+  return *reinterpret_cast<const V*>(reinterpret_cast<const char*>(base) + bytes);
+}
 
 // B_KCONTIG = false: B[c][n] = P[(n / kv) * d * kv + c * kv + n % kv]   (C = d, N = h * kv)
 // B_KCONTIG = true : B[c][n] = P[(c / kv) * d * kv + n * kv + c % kv]   (C = h * kv, N = d)
 template <bool B_KCONTIG, int BM, int BN, int WR, int WC, int KG, int PD>
-__global__ __launch_bounds__(512)
+__global__ __launch_bounds__(512, KG >= 4 ? 4 : 2)      // (waves per SIMD: two workgroups per compute unit of the small tiles)
 void gemm_split_kernel(const float* __restrict__ in, const float* __restrict__ P, float* out,
                        int rows, int d, int h, int kv, int epilogue, int tiles_m, int tiles_n) {
   static_assert(WR * WC * KG == 8 && BM * KG == 256 && BN * KG == 256, "512 threads, 16 staged values of each operand per thread of a half");
@@ -105,8 +117,7 @@ void gemm_split_kernel(const float* __restrict__ in, const float* __restrict__ P
   //   A, and B with c contiguous: thread -> eight indices (octet ts % KO) of rows ts / KO + (256 / KO) i
   //   B with n contiguous: thread -> columns 2 pair, 2 pair + 1 at the eight indices of an octet
   const int o_row = ts % KO, r_row = ts / KO;
-  const int w4 = wave & 3;
-  const int pair = lane + 64 * (w4 % (BN / 128)), o_col = w4 / (BN / 128);
+  const int pair = ts % (BN / 2), o_col = ts / (BN / 2);
   auto run = [&](auto role, auto&& clear, auto&& multiply) {
     constexpr bool STAGE_A = decltype(role)::value, BY_ROWS = STAGE_A || B_KCONTIG;
     uint32_t* const my_most = most + (STAGE_A ? 0 : BM);
@@ -115,33 +126,40 @@ void gemm_split_kernel(const float* __restrict__ in, const float* __restrict__ P
 #pragma unroll
     for (int i = 0; i < 2; ++i) line[i] = BY_ROWS ? r_row + (256 / KO) * i : 2 * pair + i;
     float scale[2], peak[2];                   // of these two: the scale, and the largest scaled |value| so far
-    const float* src[BY_ROWS ? 2 : 1];
+    // a base that is the same in every lane (scalar registers) and a 32-bit offset in bytes of the lane (split_fits)
+    const float* base_of = STAGE_A ? in + (size_t)row0 * C : B_KCONTIG ? P + (size_t)n0 * kv : P + (size_t)(n0 / kv) * head_stride + n0 % kv;
+    uint32_t src[BY_ROWS ? 2 : 1];
     if constexpr (BY_ROWS) {
 #pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        const int r = r_row + (256 / KO) * i;
-        if constexpr (STAGE_A) src[i] = in + (size_t)min(row0 + r, rows - 1) * C;                            // + c
-        else src[i] = P + (size_t)min(n0 + JB * (r % L::QCOLS) + r / L::QCOLS, N - 1) * kv;                  // r is the slot; + head of c, c % kv
-      }
+      for (int i = 0; i < 2; ++i)
+        src[i] = STAGE_A ? (uint32_t)min(line[i], rows - 1 - row0) * (4u * (uint32_t)C)
+                         : (uint32_t)min(JB * (line[i] % L::QCOLS) + line[i] / L::QCOLS, N - 1 - n0) * (4u * (uint32_t)kv);        // line: the slot
     } else {
-      const int n = min(n0 + 2 * pair, N - 2);
-      src[0] = P + (size_t)(n / kv) * head_stride + (n % kv);                                                // + c * kv
+      const int n = n0 + min(2 * pair, N - 2 - n0);
+      src[0] = (uint32_t)(n / kv - n0 / kv) * (uint32_t)(4 * head_stride) + 4u * (uint32_t)(n % kv) - 4u * (uint32_t)(n0 % kv);
     }
     struct Regs { float x[16]; };              // [row][8 indices], or [8 indices][column]
     auto load_stage = [&](int st, Regs& rg) {
+      const int c0 = min(st, nst - 1) * 16 * KG, c = min(8 * (BY_ROWS ? o_row : o_col), C - 8 - c0);
       if constexpr (BY_ROWS) {
-        const int c = min(st * 16 * KG + 8 * o_row, C - 8);
-        const size_t off = STAGE_A ? (size_t)c : (size_t)(c / kv) * head_stride + (c % kv);
+        const float* at = base_of + c0;
+        uint32_t off = 4u * (uint32_t)c;
+        if constexpr (!STAGE_A) {              // eight indices stay inside one head (kv % 8 == 0), a stage need not
+          const int head = c0 / kv, in_head = c0 - head * kv;
+          at = base_of + (size_t)head * head_stride + in_head;
+          if (in_head + 16 * KG > kv) off += (uint32_t)((in_head + c) / kv) * (uint32_t)(4 * (head_stride - kv));
+        }
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-          const float4 v = *reinterpret_cast<const float4*>(src[i >> 1] + off + 4 * (i & 1));
+          const float4 v = load_at<float4>(at + 4 * (i & 1), src[i >> 1] + off);
           rg.x[4 * i] = v.x; rg.x[4 * i + 1] = v.y; rg.x[4 * i + 2] = v.z; rg.x[4 * i + 3] = v.w;
         }
       } else {
-        const float* at = src[0] + (size_t)min(st * 16 * KG + 8 * o_col, C - 8) * kv;
+        const float* at = base_of + (size_t)c0 * kv;
+        const uint32_t off = src[0] + (uint32_t)c * (4u * (uint32_t)kv);
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
-          const float2 v = *reinterpret_cast<const float2*>(at + (size_t)i * kv);
+          const float2 v = load_at<float2>(at + (size_t)i * kv, off);
           rg.x[2 * i] = v.x; rg.x[2 * i + 1] = v.y;
         }
       }
@@ -168,7 +186,7 @@ void gemm_split_kernel(const float* __restrict__ in, const float* __restrict__ P
           const Split2 s = split2(a, b);
           t[0][k] = s.hi; t[1][k] = s.lo;
         }
-        const int at = BY_ROWS && !STAGE_A ? L::slot_bytes(line[i] / L::QCOLS, line[i] % L::QCOLS) : STAGE_A ? 16 * line[i] : L::slot_bytes(line[i] % JB, line[i] / JB);
+        const int at = STAGE_A ? 16 * line[i] : B_KCONTIG ? L::slot_bytes(line[i] / L::QCOLS, line[i] % L::QCOLS) : L::column_at(line[i]);
 #pragma unroll
         for (int p = 0; p < 2; ++p) *reinterpret_cast<u32x4*>(base + p * (STAGE_A ? L::A_PLANE : L::B_PLANE) + at) = t[p];
       }
@@ -177,7 +195,7 @@ void gemm_split_kernel(const float* __restrict__ in, const float* __restrict__ P
     auto set_scales = [&]() {
       float whole = 0.f;
 #pragma unroll
-      for (int i = 0; i < (STAGE_A ? BM : BN) / 64; ++i) whole = fmaxf(whole, __uint_as_float(my_most[lane + 64 * i]));
+      for (int i = 0; i < (STAGE_A ? BM : BN); i += 64) whole = fmaxf(whole, __uint_as_float(my_most[(lane + i) % (STAGE_A ? BM : BN)]));
       whole = wave_max(whole);
 #pragma unroll
       for (int i = 0; i < 2; ++i) {
@@ -277,36 +295,31 @@ void gemm_split_kernel(const float* __restrict__ in, const float* __restrict__ P
   if (wave < 4) run(std::true_type{}, clear, multiply);
   else run(std::false_type{}, clear, multiply);
 
-  // KG = 2: the second group hands its partial tile over through LDS (free after the last barrier)
-  if constexpr (KG == 2) {
-    float* part = reinterpret_cast<float*>(smem) + (size_t)(wave & 3) * (RB * JB * 16 * 64) + lane;
-    if (kg == 1) {
-#pragma unroll
-      for (int r = 0; r < RB; ++r)
-#pragma unroll
-        for (int j = 0; j < JB; ++j)
-#pragma unroll
-          for (int e = 0; e < 16; ++e) part[((r * JB + j) * 16 + e) * 64] = acc[r][j][e];
-    }
-    __syncthreads();
-    if (kg == 1) return;
+  // KG > 1: the groups' partial tiles meet in LDS (free after the last barrier); group kg finishes the
+  // registers [kg SHARE, (kg + 1) SHARE) of all of them
+  constexpr int SHARE = RB * 16 / KG;
+  float* part = reinterpret_cast<float*>(smem) + lane;
+  if constexpr (KG > 1) {
+    float* mine = part + (size_t)wave * (RB * JB * 16 * 64);
 #pragma unroll
     for (int r = 0; r < RB; ++r)
 #pragma unroll
-      for (int j = 0; j < JB; ++j)
+      for (int e = 0; e < 16; ++e)
 #pragma unroll
-        for (int e = 0; e < 16; ++e) acc[r][j][e] += part[((r * JB + j) * 16 + e) * 64];
+        for (int j = 0; j < JB; ++j) mine[((r * 16 + e) * JB + j) * 64] = acc[r][j][e];
+    __syncthreads();
   }
 
   // D layout of a 32x32 block: register e of lane (i, g) is element (8 (e/4) + 4 g + e%4, i); the lane's
   // JB blocks are columns n .. n + JB - 1
-  const int n = n0 + JB * (wc * 32 + i32);
+  const int slot = wc * 32 + i32;
+  const int n = n0 + (JB == 1 && !B_KCONTIG ? 2 * (slot % (BN / 2)) + slot / (BN / 2) : JB * slot);
   if (n >= N) return;                          // (N is a multiple of 8: all JB columns are in or out)
   typedef __attribute__((ext_vector_type(JB))) float vec;
   int col_expo[JB];                            // (column q JB + j of the tile: by slots where c is contiguous)
 #pragma unroll
-  for (int j = 0; j < JB; ++j) col_expo[j] = expo[BM + (B_KCONTIG ? j * L::QCOLS + wc * 32 + i32 : n - n0 + j)];
-  uint32_t redo = 0;                           // rows of the lane with an output that is not finite
+  for (int j = 0; j < JB; ++j) col_expo[j] = expo[BM + (B_KCONTIG ? j * L::QCOLS + slot : n - n0 + j)];
+  uint32_t redo = 0;                           // of the rows finished here: those with an output that is not finite
   auto row_in_tile = [&](int re) { return wr * RB * 32 + 32 * (re >> 4) + 8 * ((re >> 2) & 3) + 4 * g + (re & 3); };
   auto row_of = [&](int re) { return row0 + row_in_tile(re); };
   auto finish = [&](float* dst, vec x) {
@@ -318,41 +331,50 @@ void gemm_split_kernel(const float* __restrict__ in, const float* __restrict__ P
     }
     *reinterpret_cast<vec*>(dst) = x;
   };
+  const int re0 = kg * SHARE;
 #pragma unroll
-  for (int re = 0; re < RB * 16; ++re) {
+  for (int k = 0; k < SHARE; ++k) {
     vec x;
     bool finite = true;
-    const int row_expo = expo[row_in_tile(re)];
+    const int row_expo = expo[row_in_tile(re0 + k)];
 #pragma unroll
     for (int j = 0; j < JB; ++j) {
-      x[j] = ldexpf(acc[re >> 4][j][re & 15], row_expo + col_expo[j]);
+      float y = 0.f;
+      if constexpr (KG == 1) y = acc[k >> 4][j][k & 15];
+      else
+#pragma unroll
+        for (int q = 0; q < KG; ++q) y += part[((size_t)(q * WR * WC + wave % (WR * WC)) * (RB * 16) + re0 + k) * (JB * 64) + j * 64];
+      x[j] = ldexpf(y, row_expo + col_expo[j]);
       finite = finite && fabsf(x[j]) < INFINITY;
     }
-    const int row = row_of(re);
+    const int row = row_of(re0 + k);
     if (row >= rows) continue;
-    if (!finite) redo |= 1u << re;
+    if (!finite) redo |= 1u << k;
     else finish(out + (size_t)row * N + n, x);
   }
   while (redo) {
-    const int row = row_of(__builtin_ctz(redo));
+    const int row = row_of(re0 + __builtin_ctz(redo));
     redo &= redo - 1;
     vec x;
-    for (int j = 0; j < JB; ++j) {
-      const float y = plain_dot<B_KCONTIG>(in, P, row, n + j, d, h, kv);
-      if (j == 0) x[0] = y;
-      if (j == 1) x[1] = y;
-      if constexpr (JB == 4) {
-        if (j == 2) x[2] = y;
-        if (j == 3) x[3] = y;
-      }
-    }
+#pragma unroll
+    for (int j = 0; j < JB; ++j) x[j] = plain_dot<B_KCONTIG>(in, P, row, n + j, d, h, kv);
     finish(out + (size_t)row * N + n, x);
   }
+}
+
+// The 32-bit offsets inside a tile: of its rows and columns and of the heads that a tile (n contiguous) or a stage
+// (c contiguous) reaches over.
+bool split_fits(bool outp, int d, int h, int kv, int tile, int stage) {
+  const long long C = outp ? (long long)h * kv : d, most = 1ll << 30;      // floats: 4 GiB
+  if (C * tile >= most || (long long)kv * (tile > stage ? tile : stage) >= most) return false;
+  const int reach = outp ? stage : tile;
+  return h == 1 || kv % reach == 0 || (long long)d * kv * (reach / kv + 2) < most;
 }
 
 template <bool KC, int BM, int BN, int WR, int WC, int KG, int PD>
 hipError_t launch_split(const float* in, const float* P, float* out, int rows, int d, int h, int kv, int N,
                         int epilogue, hipStream_t st) {
+  if (!split_fits(KC, d, h, kv, BM, 16 * KG)) return hipErrorNotSupported;
   constexpr size_t lds = SplitTile<BM, BN, BN / WC / 32, KG>::BYTES;       // 70 KiB
   auto kern = gemm_split_kernel<KC, BM, BN, WR, WC, KG, PD>;
   static bool done[64] = {};
@@ -372,24 +394,38 @@ hipError_t launch_split(const float* in, const float* P, float* out, int rows, i
 
 }  // namespace
 
-// Returns hipErrorNotSupported when the GEMM is too small for these tiles to fill the chip (the
-// caller then uses the split-contraction kernel of project.hip).
+// Returns hipErrorNotSupported when the split-contraction kernel of project.hip is the faster one (the caller
+// then uses it); `apart` is what a launch of its own costs the caller more (us).
+// The forms differ in how they fill the chip and in what a staged byte is worth.  Measured, us = 5 + C / 1024 times
+//   32 x 32 tiles: 5.7 up to 256 of them, 10.5 for each 512 (two per compute unit)     128 x 1024 x 4096 (C = 1024): 15
+//   64 x 64:       12                     22.5                                         1024 x 1024 x 1024: 17, 2048 x 2048: 50
+//   128 x 128:     33 for each 256 (one per compute unit)                              4096 x 1024 x 1024: 38
+//   256 x 256:     70                                                                  2000 x 1000 x 5008: 88
+// and the split-contraction kernel on float32 instructions 5 + 2 rows N C / 64 TFLOP/s (80 with n contiguous): 128 x
+// 1024 x 1024: 9.2; 128 x 4096 x 1024, long sums and few tiles: 24, 32 x 32 tiles 26; 1024 x 1024 x 1024: 32; 768 x
+// 4096 x 1024: 104, 64 x 64 tiles 50.
 hipError_t launch_gemm_tiled(int mode, const float* in, const float* P, float* out,
-                             int rows, int d, int h, int kv, int epilogue, hipStream_t st) {
+                             int rows, int d, int h, int kv, int epilogue, int apart, hipStream_t st) {
   const bool outp = (mode == 3);
   const int N = outp ? d : h * kv;
-  const long long t128 = (long long)((N + 127) / 128) * ((rows + 127) / 128);
-  const long long t256 = (long long)((N + 255) / 256) * ((rows + 255) / 256);
-  if (N < 64 || rows < 64 || t128 < 192) return hipErrorNotSupported;
-  // One tile per compute unit at a time.  A 256 x 256 tile takes about three times a 128 x 128 one (four times the
-  // work at 1.35 times the rate): the form with the shorter sum of rounds.  2000 x 1000 . 1000 x 5008: 145 us in three
-  // rounds of 128 x 128 tiles, 120 us in one of 256 x 256; 4096 x 1024 . 1024 x 1024: one round of 128 x 128 tiles, 51 us.
-  const bool wide = 3 * ((t256 + 255) / 256) <= (t128 + 255) / 256;
-  if (wide)
-    return outp ? launch_split<true, 256, 256, 4, 2, 1, 1>(in, P, out, rows, d, h, kv, N, epilogue, st)
-                : launch_split<false, 256, 256, 4, 2, 1, 1>(in, P, out, rows, d, h, kv, N, epilogue, st);
-  return outp ? launch_split<true, 128, 128, 2, 2, 2, 3>(in, P, out, rows, d, h, kv, N, epilogue, st)
-              : launch_split<false, 128, 128, 2, 2, 2, 3>(in, P, out, rows, d, h, kv, N, epilogue, st);
+  const double C = outp ? (double)h * kv : (double)d;
+  auto tiles = [&](int t) { return (double)((N + t - 1) / t) * (double)((rows + t - 1) / t); };
+  auto rounds = [&](int t, double per_round) { return ceil(tiles(t) / per_round); };
+  const double w[4] = {tiles(32) <= 256 ? 5.7 : 10.5 * rounds(32, 512), tiles(64) <= 256 ? 12. : 22.5 * rounds(64, 512),
+                       33. * rounds(128, 256), 70. * rounds(256, 256)};
+  int best = 0;
+  for (int f = 1; f < 4; ++f)
+    if (w[f] < w[best]) best = f;
+  const double split_contraction = 5. + 2. * ((rows + 15) / 16 * 16) * N * C / (outp ? 64e6 : 80e6);
+  if (5. + apart + C / 1024. * w[best] > 0.9 * split_contraction) return hipErrorNotSupported;
+#define MQA_SPLIT(BM, WR, WC, KG, PD) \
+  return outp ? launch_split<true, BM, BM, WR, WC, KG, PD>(in, P, out, rows, d, h, kv, N, epilogue, st) \
+              : launch_split<false, BM, BM, WR, WC, KG, PD>(in, P, out, rows, d, h, kv, N, epilogue, st)
+  if (best == 0) MQA_SPLIT(32, 1, 1, 8, 1);
+  if (best == 1) MQA_SPLIT(64, 2, 1, 4, 1);
+  if (best == 2) MQA_SPLIT(128, 2, 2, 2, 3);
+  MQA_SPLIT(256, 4, 2, 1, 1);
+#undef MQA_SPLIT
 }
 
 }  // namespace mqa

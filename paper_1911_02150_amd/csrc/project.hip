@@ -302,6 +302,7 @@ void project_qkv_append_kernel(const float* __restrict__ x, const float* __restr
 // (16x64), multi-head 1024 x 3072: 21.8 -> 17.6 (32x64).  A second row block only pays when it
 // holds real rows (rows > 16).  32x32 MFMA blocks (T = 32, which gemm_tile also supports) were
 // slower than these at every such shape (1024 x 4096: 21.4) and are not instantiated.
+constexpr int kApart = 4;      // us: a launch of its own for q
 struct Tile { int RB, CB; };
 static inline long long tiles_of(const Tile& t, long long ncols, int rows) {
   const long long tm = t.RB * 16, tn = t.CB * 16;
@@ -326,7 +327,7 @@ hipError_t launch_project(int mode, const float* in, const float* P, float* out,
   const bool outp = (mode == 3);
   const bool f64 = (mode == 1 || mode == 2);        // new K / V rows: float64 accumulation, split-contraction kernel only
   if (!f64) {
-    const hipError_t big = launch_gemm_tiled(mode, in, P, out, rows, d, h, kv, epilogue, st);     // large GEMMs: LDS-tiled kernel
+    const hipError_t big = launch_gemm_tiled(mode, in, P, out, rows, d, h, kv, epilogue, 0, st);     // large GEMMs: LDS-tiled kernel
     if (big != hipErrorNotSupported) return big;
   }
   const int N = outp ? d : h * kv;
@@ -355,7 +356,7 @@ hipError_t launch_project_qkv_append(const float* x, const float* P_q, const flo
                                      int mem_rows, hipStream_t st) {
   // prompt-sized row counts: q through the LDS-tiled kernel, then only the K / V columns here
   // (h = 0: no q at all, the projection of a memory)
-  const hipError_t big = h > 0 ? launch_gemm_tiled(0, x, P_q, q, rows, d, h, k, 0, st) : hipErrorNotSupported;
+  const hipError_t big = h > 0 ? launch_gemm_tiled(0, x, P_q, q, rows, d, h, k, 0, kApart, st) : hipErrorNotSupported;
   if (big != hipErrorNotSupported && big != hipSuccess) return big;
   const bool q_done = (big == hipSuccess);
   const int nq = h * k;

@@ -44,6 +44,10 @@ SIZES = [
     (4096, 1024, 4096),      # 256 x 256: whole tiles only
     (4097, 136, 4104),       # 256 x 256: one row, eight columns in the last tiles, tail of 8 in a stage of 16
     (16000, 40, 1024),       # 256 x 256: tile rows that do not fill a band of eight
+    (500, 1000, 1000),       # 32 x 32: last tiles of 20 rows and 8 columns, 104 indices in the last stage
+    (129, 1024, 4104),       # 32 x 32: one row, eight columns in the last tiles
+    (1001, 1000, 1000),      # 64 x 64: 41 rows, 40 columns, 40 indices in the last stage
+    (768, 4096, 1024),       # 64 x 64: whole tiles only
 ]
 
 
@@ -64,7 +68,7 @@ def test_split_gemm(m, layout, rows, C, N):
 
 
 @pytest.mark.parametrize("layout", ["n", "c"])
-@pytest.mark.parametrize("rows,C,N", [(1601, 72, 2056), (4097, 136, 4104)])
+@pytest.mark.parametrize("rows,C,N", [(1601, 72, 2056), (4097, 136, 4104), (500, 1000, 1000), (1001, 1000, 1000)])
 def test_split_gemm_scales(m, layout, rows, C, N):
     """Lines that begin with zeros or with values far from those that follow: the scales are set a second time."""
     g = torch.Generator(device=DEV)
@@ -85,7 +89,7 @@ def test_split_gemm_scales(m, layout, rows, C, N):
 
 
 @pytest.mark.parametrize("layout", ["n", "c"])
-@pytest.mark.parametrize("rows,C,N", [(1601, 72, 2056), (4097, 136, 4104)])
+@pytest.mark.parametrize("rows,C,N", [(1601, 72, 2056), (4097, 136, 4104), (500, 1000, 1000), (1001, 1000, 1000)])
 def test_split_gemm_values_without_a_split(m, layout, rows, C, N):
     """Infinities, NaN, the largest floats (their first term would round to infinity) and overflowing outputs."""
     g = torch.Generator(device=DEV)
@@ -107,3 +111,21 @@ def test_split_gemm_values_without_a_split(m, layout, rows, C, N):
     fine = torch.isfinite(ref)
     lim = torch.nan_to_num(bound(x, W), nan=0.0, posinf=0.0)
     assert ((got.double() - ref.double()).abs()[fine] <= lim[fine] + 2.0 ** -23 * ref.double().abs()[fine]).all()
+
+
+@pytest.mark.parametrize("kv", [8, 24, 72])
+@pytest.mark.parametrize("rows,width", [(500, 1000), (1001, 1000), (4096, 1024), (4096, 4096)])
+def test_split_gemm_small_heads(m, kv, rows, width):
+    """Column tiles (q) and stages of the contraction (output) that reach over several heads, in every tile size."""
+    g = torch.Generator(device=DEV)
+    g.manual_seed(kv + rows)
+    h = width // kv
+    x = torch.randn(rows, width, generator=g, device=DEV)
+    P = torch.randn(h, width, kv, generator=g, device=DEV)
+    W = P.permute(1, 0, 2).reshape(width, h * kv)
+    got = m.mqa_project_qkvo(m.MQA_PROJ_Q, x, P).view(rows, h * kv)
+    assert ((got.double() - x.double() @ W.double()).abs() <= bound(x, W)).all()
+    o = torch.randn(rows, h, kv, generator=g, device=DEV)
+    W = P.permute(0, 2, 1).reshape(h * kv, width)
+    got = m.mqa_project_qkvo(m.MQA_PROJ_O, o, P)
+    assert ((got.double() - o.view(rows, -1).double() @ W.double()).abs() <= bound(o.view(rows, -1), W)).all()
