@@ -104,14 +104,22 @@ def status_string(status: int) -> str:
     return load_library().mqa_status_string(int(status)).decode()
 
 
+# A decode step is a few launches of a few microseconds: what a call costs on the host counts.  Addresses and the
+# stream are passed as plain integers, and the stream is asked for as one (torch.cuda.current_stream() builds a
+# Stream object: 3.0 us of a call's 8 to 12; the call into the library with its launch is 3.1).
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
+
+
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
 
 
 def _stream(stream):
-    if stream is None:
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream)
+    if stream is not None:
+        return stream.cuda_stream
+    if _raw_stream is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(torch.cuda.current_device())
 
 
 def _tuning(tuning):
@@ -132,12 +140,13 @@ def _cache_dtype(K):
 
 
 def _check(t, name, dtype=None):
+    if t.is_cuda and t.is_contiguous() and (dtype is None or t.dtype == dtype):
+        return
     if not t.is_cuda:
         raise ValueError(f"{name} must be a device tensor")
     if not t.is_contiguous():
         raise ValueError(f"{name} must be contiguous")
-    if dtype is not None and t.dtype != dtype:
-        raise TypeError(f"{name} must be {dtype}")
+    raise TypeError(f"{name} must be {dtype}")
 
 
 def mqa_decode_workspace_bytes(b, h, cap, v) -> int:
@@ -193,12 +202,12 @@ def _decode(fn_name, multi_head, q, K, V, lens, o, scale, workspace, stream, tun
     cap, v = V.shape[-2], V.shape[-1]
     want_k = (b, h, cap, k) if multi_head else (b, cap, k)
     want_v = (b, h, cap, v) if multi_head else (b, cap, v)
-    if tuple(K.shape) != want_k or tuple(V.shape) != want_v or K.dtype != V.dtype or lens.numel() != b:
+    if K.shape != want_k or V.shape != want_v or K.dtype != V.dtype or lens.numel() != b:
         raise ValueError(f"shape mismatch: q {tuple(q.shape)} K {tuple(K.shape)} V {tuple(V.shape)} lens {tuple(lens.shape)}")
     if o is None:
         o = torch.empty((b, h, v), dtype=torch.float32, device=q.device)
     _check(o, "o", torch.float32)
-    if tuple(o.shape) != (b, h, v):
+    if o.shape != (b, h, v):
         raise ValueError("o must be [b,h,v]")
     if workspace is None:
         nbytes = mha_decode_workspace_bytes(b, h, cap, v) if multi_head else mqa_decode_workspace_bytes(b, h, cap, v)
@@ -236,8 +245,8 @@ def mqa_decode_step_noalloc(q, K, V, lens, o, scale=1.0, stream=None):
     _check(q, "q", torch.float32), _check(K, "K"), _check(V, "V"), _check(lens, "lens", torch.int32), _check(o, "o", torch.float32)
     b, h, k = q.shape
     cap, v = V.shape[-2], V.shape[-1]
-    if (tuple(K.shape) != (b, cap, k) or tuple(V.shape) != (b, cap, v) or K.dtype != V.dtype or lens.numel() != b
-            or tuple(o.shape) != (b, h, v)):
+    if (K.shape != (b, cap, k) or V.shape != (b, cap, v) or K.dtype != V.dtype or lens.numel() != b
+            or o.shape != (b, h, v)):
         raise ValueError("shape mismatch in mqa_decode_step_noalloc")
     rc = lib.mqa_decode_step_noalloc(_ptr(q), _ptr(K), _ptr(V), _ptr(lens), _ptr(o), b, h, cap, k, v, _cache_dtype(K),
                                      float(scale), _stream(stream))
@@ -309,7 +318,7 @@ def mqa_prefill_attention(q, K, V, lens, o=None, scale=1.0, workspace=None, stre
     _check(q, "q", torch.float32), _check(K, "K"), _check(V, "V"), _check(lens, "lens", torch.int32)
     b, n, h, k = q.shape
     cap, v = V.shape[-2], V.shape[-1]
-    if tuple(K.shape) != (b, cap, k) or tuple(V.shape) != (b, cap, v) or lens.numel() != b:
+    if K.shape != (b, cap, k) or V.shape != (b, cap, v) or lens.numel() != b:
         raise ValueError("shape mismatch in mqa_prefill_attention")
     if o is None:
         o = torch.empty((b, n, h, v), dtype=torch.float32, device=q.device)
@@ -329,7 +338,7 @@ def mha_prefill_attention(q, K, V, lens, o=None, scale=1.0, workspace=None, stre
     _check(q, "q", torch.float32), _check(K, "K"), _check(V, "V"), _check(lens, "lens", torch.int32)
     b, h, n, k = q.shape
     cap, v = V.shape[-2], V.shape[-1]
-    if tuple(K.shape) != (b, h, cap, k) or tuple(V.shape) != (b, h, cap, v) or lens.numel() != b:
+    if K.shape != (b, h, cap, k) or V.shape != (b, h, cap, v) or lens.numel() != b:
         raise ValueError("shape mismatch in mha_prefill_attention")
     if o is None:
         o = torch.empty((b, h, n, v), dtype=torch.float32, device=q.device)
@@ -347,18 +356,18 @@ def mqa_project_append_qkv(x, P_q, P_k, P_v, K, V, lens_in, lens_out, q=None, st
     """x [b,d], P_q [h,d,k], P_k [d,k] or [h,d,k], P_v likewise, K/V caches, lens_in/lens_out [b] int32
     (different tensors) -> q [b,h,k]; the new rows are written into the caches."""
     lib = load_library()
-    for name, t in (("x", x), ("P_q", P_q), ("P_k", P_k), ("P_v", P_v)):
-        _check(t, name, torch.float32)
-    _check(K, "K"), _check(V, "V"), _check(lens_in, "lens_in", torch.int32), _check(lens_out, "lens_out", torch.int32)
+    f32, i32 = torch.float32, torch.int32
+    _check(x, "x", f32), _check(P_q, "P_q", f32), _check(P_k, "P_k", f32), _check(P_v, "P_v", f32)
+    _check(K, "K"), _check(V, "V"), _check(lens_in, "lens_in", i32), _check(lens_out, "lens_out", i32)
     b, d = x.shape
-    h, _, k = P_q.shape
-    v = P_v.shape[-1]
-    h_kv = P_k.shape[0] if P_k.dim() == 3 else 1
-    cap = K.shape[-2]
-    kshape = (b, cap, k) if K.dim() == 3 else (b, h_kv, cap, k)
-    if (tuple(P_q.shape) != (h, d, k) or tuple(P_k.shape)[-2:] != (d, k) or tuple(P_v.shape)[-2:] != (d, v)
-            or P_v.dim() != P_k.dim() or (K.dim() == 3) != (P_k.dim() == 2) or tuple(K.shape) != kshape
-            or tuple(V.shape) != kshape[:-1] + (v,) or K.dtype != V.dtype or lens_in.numel() != b or lens_out.numel() != b):
+    h, d_q, k = P_q.shape
+    k_shape, v_shape, cache = P_k.shape, P_v.shape, K.shape
+    v, one = v_shape[-1], len(k_shape) == 2
+    h_kv = k_shape[0] if len(k_shape) == 3 else 1
+    cap = cache[-2]
+    if (d_q != d or k_shape[-2:] != (d, k) or v_shape[-2:] != (d, v) or len(v_shape) != len(k_shape)
+            or cache != ((b, cap, k) if one else (b, h_kv, cap, k)) or V.shape != ((b, cap, v) if one else (b, h_kv, cap, v))
+            or K.dtype != V.dtype or lens_in.numel() != b or lens_out.numel() != b):
         raise ValueError("shape mismatch in mqa_project_append_qkv")
     if q is None:
         q = torch.empty((b, h, k), dtype=torch.float32, device=x.device)
@@ -383,8 +392,8 @@ def mqa_project_memory_kv(M, P_k, P_v, K, V, lens, mem_lens=None, stream=None):
     h_kv = P_k.shape[0] if P_k.dim() == 3 else 1
     cap = K.shape[-2]
     kshape = (b, cap, k) if K.dim() == 3 else (b, h_kv, cap, k)
-    if (tuple(P_k.shape)[-2:] != (d, k) or tuple(P_v.shape)[-2:] != (d, v) or P_v.dim() != P_k.dim()
-            or (K.dim() == 3) != (P_k.dim() == 2) or tuple(K.shape) != kshape or tuple(V.shape) != kshape[:-1] + (v,)
+    if (P_k.shape[-2:] != (d, k) or P_v.shape[-2:] != (d, v) or P_v.dim() != P_k.dim()
+            or (K.dim() == 3) != (P_k.dim() == 2) or K.shape != kshape or V.shape != kshape[:-1] + (v,)
             or K.dtype != V.dtype or lens.numel() != b or (mem_lens is not None and mem_lens.numel() != b)):
         raise ValueError("shape mismatch in mqa_project_memory_kv")
     rc = lib.mqa_project_memory_kv(_ptr(M), _ptr(P_k), _ptr(P_v), _ptr(K), _ptr(V), _ptr(mem_lens), _ptr(lens),
@@ -400,7 +409,7 @@ def mqa_memory_decode_step(q, K, V, lens, o=None, scale=1.0, workspace=None, str
     _check(q, "q", torch.float32), _check(K, "K"), _check(V, "V"), _check(lens, "lens", torch.int32)
     b, nq, h, k = q.shape
     cap, v = V.shape[-2], V.shape[-1]
-    if tuple(K.shape) != (b, cap, k) or tuple(V.shape) != (b, cap, v) or K.dtype != V.dtype or lens.numel() != b:
+    if K.shape != (b, cap, k) or V.shape != (b, cap, v) or K.dtype != V.dtype or lens.numel() != b:
         raise ValueError("shape mismatch in mqa_memory_decode_step")
     if o is None:
         o = torch.empty((b, nq, h, v), dtype=torch.float32, device=q.device)
@@ -429,8 +438,8 @@ def mqa_decode_step_beams(q, K_src, V_src, lens_src, K_own, V_own, lens_own, o=N
     b, beam, h, k = q.shape
     cap_src, v = V_src.shape[-2], V_src.shape[-1]
     cap_own = V_own.shape[-2]
-    if (tuple(K_src.shape) != (b, cap_src, k) or tuple(V_src.shape) != (b, cap_src, v)
-            or tuple(K_own.shape) != (b, beam, cap_own, k) or tuple(V_own.shape) != (b, beam, cap_own, v)
+    if (K_src.shape != (b, cap_src, k) or V_src.shape != (b, cap_src, v)
+            or K_own.shape != (b, beam, cap_own, k) or V_own.shape != (b, beam, cap_own, v)
             or lens_src.numel() != b or lens_own.numel() != b * beam or K_own.dtype != K_src.dtype):
         raise ValueError("shape mismatch in mqa_decode_step_beams")
     dt = _cache_dtype(K_src)
