@@ -140,6 +140,17 @@ int mqa_project_append_qkv(const float* x, const float* P_q, const float* P_k, c
                            int b, int d, int h, int h_kv, int cap, int k, int v, mqa_dtype dt, void* stream);
 
 /*
+ * The new K and V rows of n positions per sequence (a prompt), projected and appended in one launch: rows
+ * x[i,p,:] . P_k, x[i,p,:] . P_v for p < n go behind the lens_in[i] rows sequence i has, lens_out[i] = lens_in[i] + n;
+ * a sequence that cannot hold all n keeps its cache and length.  Same cache rows, bit for bit, as
+ * mqa_project_qkvo (KV or KV_MH) followed by mqa_append_kv_rows.  x [b,n,d]; P_k, P_v, K, V and the limits as in
+ * mqa_project_append_qkv; n <= cap; lens_in and lens_out must be different arrays.
+ */
+int mqa_project_append_kv_rows(const float* x, const float* P_k, const float* P_v, void* K, void* V,
+                               const int32_t* lens_in, int32_t* lens_out, int b, int n, int d, int h_kv, int cap,
+                               int k, int v, mqa_dtype dt, void* stream);
+
+/*
  * Encoder-decoder ("memory") attention: the one-query-against-a-memory form of the paper's
  * Section 2.2 listing under the Section 3 rule (K, V, P_k, P_v lose the heads dimension) -- the
  * attention kind that, with the two self-attentions, Section 4.1 converts to multi-query.  The

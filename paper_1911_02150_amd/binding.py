@@ -17,7 +17,7 @@ MQA_PROJ_Q, MQA_PROJ_KV, MQA_PROJ_KV_MH, MQA_PROJ_O, MQA_PROJ_LINEAR = 0, 1, 2, 
 MQA_EPI_STORE, MQA_EPI_RELU, MQA_EPI_ADD = 0, 1, 2
 
 EXPORTS = [
-    "mqa_project_qkvo", "mqa_project_qkvo_ex", "mqa_project_append_qkv", "mqa_append_kv", "mqa_decode_step", "mha_decode_step",
+    "mqa_project_qkvo", "mqa_project_qkvo_ex", "mqa_project_append_qkv", "mqa_project_append_kv_rows", "mqa_append_kv", "mqa_decode_step", "mha_decode_step",
     "mqa_decode_step_window", "mha_decode_step_window", "mqa_append_kv_rows", "mqa_prefill_attention", "mha_prefill_attention",
     "mqa_decode_step_beams", "mqa_decode_beams_workspace_bytes", "mqa_beam_reorder_kv", "mqa_decode_step_ex", "mha_decode_step_ex", "mqa_decode_partials", "mqa_decode_combine",
     "mqa_decode_workspace_bytes", "mha_decode_workspace_bytes", "mqa_decode_workspace_bytes_default", "mqa_decode_num_splits",
@@ -55,6 +55,7 @@ def load_library(path: str = LIB_PATH):
     lib.mqa_project_qkvo.argtypes = [ci, vp, vp, vp, ci, ci, ci, ci, vp]
     lib.mqa_project_qkvo_ex.argtypes = [ci, vp, vp, vp, ci, ci, ci, ci, ci, vp]
     lib.mqa_project_append_qkv.argtypes = [vp] * 9 + [ci] * 8 + [vp]
+    lib.mqa_project_append_kv_rows.argtypes = [vp] * 7 + [ci] * 8 + [vp]
     lib.mqa_append_kv.argtypes = [vp, vp, vp, vp, vp, ci, ci, ci, ci, ci, ci, vp]
     lib.mqa_project_memory_kv.argtypes = [vp] * 7 + [ci] * 8 + [vp]
     lib.mqa_memory_decode_step.argtypes = [vp, vp, vp, vp, vp, ci, ci, ci, ci, ci, ci, ci, cf, vp, sz, vp]
@@ -376,6 +377,28 @@ def mqa_project_append_qkv(x, P_q, P_k, P_v, K, V, lens_in, lens_out, q=None, st
     if rc != 0:
         raise MqaError("mqa_project_append_qkv", rc)
     return q
+
+
+def mqa_project_append_kv_rows(x, P_k, P_v, K, V, lens_in, lens_out, stream=None):
+    """x [b,n,d], P_k [d,k] or [h,d,k], P_v likewise, caches K/V ([b,cap,k] or [b,h,cap,k]), lens_in/lens_out [b] int32
+    (different tensors): projects the new rows of n positions per sequence and appends them, in one launch."""
+    lib = load_library()
+    f32, i32 = torch.float32, torch.int32
+    _check(x, "x", f32), _check(P_k, "P_k", f32), _check(P_v, "P_v", f32), _check(K, "K"), _check(V, "V")
+    _check(lens_in, "lens_in", i32), _check(lens_out, "lens_out", i32)
+    b, n, d = x.shape
+    k, v = P_k.shape[-1], P_v.shape[-1]
+    one = P_k.dim() == 2
+    h_kv = 1 if one else P_k.shape[0]
+    cap = K.shape[-2]
+    if (P_k.shape != ((d, k) if one else (h_kv, d, k)) or P_v.shape != ((d, v) if one else (h_kv, d, v))
+            or K.shape != ((b, cap, k) if one else (b, h_kv, cap, k)) or V.shape != ((b, cap, v) if one else (b, h_kv, cap, v))
+            or K.dtype != V.dtype or lens_in.numel() != b or lens_out.numel() != b):
+        raise ValueError("shape mismatch in mqa_project_append_kv_rows")
+    rc = lib.mqa_project_append_kv_rows(_ptr(x), _ptr(P_k), _ptr(P_v), _ptr(K), _ptr(V), _ptr(lens_in), _ptr(lens_out),
+                                        b, n, d, h_kv, cap, k, v, _cache_dtype(K), _stream(stream))
+    if rc != 0:
+        raise MqaError("mqa_project_append_kv_rows", rc)
 
 
 def mqa_project_memory_kv(M, P_k, P_v, K, V, lens, mem_lens=None, stream=None):

@@ -529,7 +529,23 @@ int mqa_project_append_qkv(const float* x, const float* P_q, const float* P_k, c
       misaligned(V) || misaligned(lens_in) || misaligned(lens_out))
     return MQA_ERR_ALIGN;
   if (launch_project_qkv_append(x, P_q, P_k, P_v, q, K, V, lens_in, lens_out, b, d, h, h_kv, cap, k, v,
-                                dt == MQA_BF16, 0, static_cast<hipStream_t>(stream)) != hipSuccess)
+                                dt == MQA_BF16, 0, 0, static_cast<hipStream_t>(stream)) != hipSuccess)
+    return MQA_ERR_LAUNCH;
+  return MQA_OK;
+}
+
+int mqa_project_append_kv_rows(const float* x, const float* P_k, const float* P_v, void* K, void* V,
+                               const int32_t* lens_in, int32_t* lens_out, int b, int n, int d, int h_kv, int cap,
+                               int k, int v, mqa_dtype dt, void* stream) {
+  if (!x || !P_k || !P_v || !K || !V || !lens_in || !lens_out) return MQA_ERR_NULL;
+  if (dt != MQA_F32 && dt != MQA_BF16) return MQA_ERR_DTYPE;
+  if (b <= 0 || n <= 0 || d <= 0 || h_kv <= 0 || cap <= 0 || k <= 0 || v <= 0 || n > cap) return MQA_ERR_SHAPE;
+  if ((d & 7) || (k & 15) || (v & 15) || (long long)b * n > (1ll << 30) || lens_in == lens_out) return MQA_ERR_SHAPE;
+  if (misaligned(x) || misaligned(P_k) || misaligned(P_v) || misaligned(K) || misaligned(V) || misaligned(lens_in) ||
+      misaligned(lens_out))
+    return MQA_ERR_ALIGN;
+  if (launch_project_qkv_append(x, nullptr, P_k, P_v, nullptr, K, V, lens_in, lens_out, b * n, d, 0, h_kv, cap, k, v,
+                                dt == MQA_BF16, n, 1, static_cast<hipStream_t>(stream)) != hipSuccess)
     return MQA_ERR_LAUNCH;
   return MQA_OK;
 }
@@ -545,7 +561,7 @@ int mqa_project_memory_kv(const float* M, const float* P_k, const float* P_v, vo
       (mem_lens && misaligned(mem_lens)))
     return MQA_ERR_ALIGN;
   if (launch_project_qkv_append(M, nullptr, P_k, P_v, nullptr, K, V, mem_lens, lens, b * m, d, 0, h_kv, cap, k, v,
-                                dt == MQA_BF16, m, static_cast<hipStream_t>(stream)) != hipSuccess)
+                                dt == MQA_BF16, m, 0, static_cast<hipStream_t>(stream)) != hipSuccess)
     return MQA_ERR_LAUNCH;
   return MQA_OK;
 }

@@ -229,6 +229,8 @@ template <> __device__ __forceinline__ uint16_t cache_value<uint16_t>(float x) {
 // Section 2.2 listing, projected once): input row r is row r % mem_rows of sequence r / mem_rows
 // and goes to that position of the cache; lens_in, if given, holds the number of valid memory
 // rows per sequence, and lens_out receives it clamped to [0, mem_rows] (mem_rows if not given).
+// append: the mem_rows rows of a sequence go behind the lens_in[] rows it has; one that cannot hold them all
+// keeps its cache and its length.
 template <int T, int RB, int CB, typename CT>
 __global__ __launch_bounds__(NWAVES * 64)
 void project_qkv_append_kernel(const float* __restrict__ x, const float* __restrict__ P_q,
@@ -236,7 +238,7 @@ void project_qkv_append_kernel(const float* __restrict__ x, const float* __restr
                                float* __restrict__ q, CT* __restrict__ K, CT* __restrict__ V,
                                const int32_t* __restrict__ lens_in, int32_t* __restrict__ lens_out,
                                int rows, int d, int h, int h_kv, int cap, int k, int v, int nq_tiles, int kv_narrow,
-                               int mem_rows) {
+                               int mem_rows, int append) {
   constexpr int TM = RB * T, TN = CB * T;
   __shared__ __align__(16) double red_raw[NWAVES * T * TN];       // = RB <= 2 float32 row blocks
   static_assert(RB <= 2, "a q tile's float32 partial tiles must fit the float64 buffer");
@@ -272,7 +274,11 @@ void project_qkv_append_kernel(const float* __restrict__ x, const float* __restr
       const int row = row0 + rb * T + e / width, n = n0 + e % width;
       if (row >= rows) continue;
       const int seq = mem_rows > 0 ? row / mem_rows : row;
-      const int L = mem_rows > 0 ? row - seq * mem_rows : lens_in[row];
+      int L = mem_rows > 0 ? row - seq * mem_rows : lens_in[row];
+      if (append) {
+        const int have = lens_in[seq];
+        L = have < 0 || have + mem_rows > cap ? -1 : L + have;
+      }
       if (L < 0 || L >= cap) continue;
       dst[(((size_t)seq * h_kv + n / kv) * cap + L) * kv + (n % kv)] = cache_value<CT>(sum_partials(red_raw, e, T * width));
     }
@@ -282,7 +288,8 @@ void project_qkv_append_kernel(const float* __restrict__ x, const float* __restr
     if (mem_rows > 0) {
       if (row % mem_rows == 0) {
         const int L = lens_in ? lens_in[row / mem_rows] : mem_rows;
-        lens_out[row / mem_rows] = L < 0 ? 0 : (L > mem_rows ? mem_rows : L);
+        if (append) lens_out[row / mem_rows] = (L < 0 || L + mem_rows > cap) ? L : L + mem_rows;
+        else lens_out[row / mem_rows] = L < 0 ? 0 : (L > mem_rows ? mem_rows : L);
       }
     } else {
       const int L = lens_in[row];
@@ -353,12 +360,17 @@ hipError_t launch_project(int mode, const float* in, const float* P, float* out,
 hipError_t launch_project_qkv_append(const float* x, const float* P_q, const float* P_k, const float* P_v,
                                      float* q, void* K, void* V, const int32_t* lens_in, int32_t* lens_out,
                                      int rows, int d, int h, int h_kv, int cap, int k, int v, int is_bf16,
-                                     int mem_rows, hipStream_t st) {
+                                     int mem_rows, int append, hipStream_t st) {
   // prompt-sized row counts: q through the LDS-tiled kernel, then only the K / V columns here
   // (h = 0: no q at all, the projection of a memory)
   const hipError_t big = h > 0 ? launch_gemm_tiled(0, x, P_q, q, rows, d, h, k, 0, kApart, st) : hipErrorNotSupported;
   if (big != hipErrorNotSupported && big != hipSuccess) return big;
   const bool q_done = (big == hipSuccess);
+  if (is_bf16 && (h == 0 || q_done)) {
+    const hipError_t e = mem_rows > 0 ? launch_project_kv_exact(x, P_k, P_v, K, V, lens_in, lens_out, rows, mem_rows, append, d, h_kv, cap, k, v, st)
+                                      : launch_project_kv_exact(x, P_k, P_v, K, V, lens_in, lens_out, rows, 1, 1, d, h_kv, cap, k, v, st);
+    if (e != hipErrorNotSupported) return e;
+  }
   const int nq = h * k;
   const int ntot = nq + h_kv * (k + v);
   // column tiles must not straddle q / K / V: the tile width divides k and v (both multiples of 16)
@@ -375,9 +387,9 @@ hipError_t launch_project_qkv_append(const float* x, const float* P_q, const flo
     const int nq_tiles = q_done ? 0 : nq / (CB_ * 16);                                                               \
     const dim3 grid(nq_tiles + (ntot - nq) / (kv_narrow ? 16 : CB_ * 16), (rows + RB_ * 16 - 1) / (RB_ * 16));       \
     if (is_bf16) hipLaunchKernelGGL((project_qkv_append_kernel<16, RB_, CB_, uint16_t>), grid, block, 0, st, x, P_q, P_k, P_v, q, \
-                                    (uint16_t*)K, (uint16_t*)V, lens_in, lens_out, rows, d, h, h_kv, cap, k, v, nq_tiles, kv_narrow, mem_rows); \
+                                    (uint16_t*)K, (uint16_t*)V, lens_in, lens_out, rows, d, h, h_kv, cap, k, v, nq_tiles, kv_narrow, mem_rows, append); \
     else hipLaunchKernelGGL((project_qkv_append_kernel<16, RB_, CB_, float>), grid, block, 0, st, x, P_q, P_k, P_v, q, \
-                            (float*)K, (float*)V, lens_in, lens_out, rows, d, h, h_kv, cap, k, v, nq_tiles, kv_narrow, mem_rows);  \
+                            (float*)K, (float*)V, lens_in, lens_out, rows, d, h, h_kv, cap, k, v, nq_tiles, kv_narrow, mem_rows, append);  \
     launched = true;                                                                                                 \
   }
   MQA_TILES(MQA_QKV)

@@ -98,9 +98,14 @@ class DecoderStack:
         for l, w in enumerate(self.layers):
             hx = B.mqa_stack_layernorm(x)
             q = B.mqa_project_qkvo(B.MQA_PROJ_Q, hx, w["P_q"]).view(b, n, self.h, self.k)
-            kn = B.mqa_project_qkvo(B.MQA_PROJ_KV, hx, w["P_k"]).view(b, n, self.k)
-            vn = B.mqa_project_qkvo(B.MQA_PROJ_KV, hx, w["P_v"]).view(b, n, self.v)
-            B.mqa_append_kv_rows(self.K[l], self.V[l], kn, vn, self.lens[l])
+            if self.k % 16 == 0 and self.v % 16 == 0:
+                B.mqa_project_append_kv_rows(hx.view(b, n, self.d), w["P_k"], w["P_v"], self.K[l], self.V[l], self.lens[l],
+                                             self._lens_next[l])
+                self.lens[l], self._lens_next[l] = self._lens_next[l], self.lens[l]
+            else:
+                kn = B.mqa_project_qkvo(B.MQA_PROJ_KV, hx, w["P_k"]).view(b, n, self.k)
+                vn = B.mqa_project_qkvo(B.MQA_PROJ_KV, hx, w["P_v"]).view(b, n, self.v)
+                B.mqa_append_kv_rows(self.K[l], self.V[l], kn, vn, self.lens[l])
             o = B.mqa_prefill_attention(q, self.K[l], self.V[l], self.lens[l])
             B.mqa_project_qkvo_ex(B.MQA_PROJ_O, o.view(b * n, self.h, self.v), w["P_o"], out=x, epilogue=B.MQA_EPI_ADD)
             u = B.mqa_project_qkvo_ex(B.MQA_PROJ_LINEAR, B.mqa_stack_layernorm(x), w["W1"], epilogue=B.MQA_EPI_RELU)

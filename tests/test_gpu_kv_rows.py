@@ -1,0 +1,116 @@
+"""New K / V rows of many positions (csrc/project_kv.hip and the float64 kernel it stands in for): the cache holds the
+correctly rounded product, bit for bit, whatever the values."""
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+DEV = "cuda:0"
+
+
+@pytest.fixture(scope="module")
+def m():
+    import paper_1911_02150_amd as lib
+    lib.load_library()
+    return lib
+
+
+def rounded(X, W):
+    """float64 products and sums, rounded to float32 and then to bfloat16."""
+    return (X.double() @ W.double()).float().to(torch.bfloat16)
+
+
+def same(got, want):
+    nan = torch.isnan(want)
+    return torch.equal(torch.isnan(got), nan) and torch.equal(got[~nan], want[~nan])
+
+
+def inputs(b, n, d, heads, k, v, seed):
+    g = torch.Generator(device=DEV)
+    g.manual_seed(seed)
+    one = (heads,) if heads else ()
+    x = torch.randn(b, n, d, generator=g, device=DEV)
+    return x, torch.randn(*one, d, k, generator=g, device=DEV) * d ** -0.5, torch.randn(*one, d, v, generator=g, device=DEV) * d ** -0.5
+
+
+def expected(x, P, heads):
+    b, n, d = x.shape
+    X = x.reshape(b * n, d)
+    if not heads:
+        return rounded(X, P).view(b, n, -1)
+    return torch.stack([rounded(X, P[j]).view(b, n, -1) for j in range(heads)], 1)
+
+
+def caches(b, heads, cap, k, v, dtype=torch.bfloat16):
+    one = (heads,) if heads else ()
+    return torch.full((b, *one, cap, k), 7.0, dtype=dtype, device=DEV), torch.full((b, *one, cap, v), 7.0, dtype=dtype, device=DEV)
+
+
+# rows and columns past whole tiles of 128, contraction tails of 8 and of 24 in a stage of 32, heads inside a column tile;
+# the last two are too small for the integer kernel
+SHAPES = [(64, 300, 1000, 0, 128, 128), (23, 811, 72, 0, 128, 64), (40, 500, 88, 5, 48, 80), (70, 257, 520, 2, 256, 16),
+          (3, 40, 512, 0, 128, 128), (2, 9, 72, 3, 16, 32)]
+
+
+@pytest.mark.parametrize("b,n,d,heads,k,v", SHAPES)
+def test_memory_rows(m, b, n, d, heads, k, v):
+    x, P_k, P_v = inputs(b, n, d, heads, k, v, n)
+    K, V = caches(b, heads, n + 3, k, v)
+    lens = torch.zeros(b, dtype=torch.int32, device=DEV)
+    m.mqa_project_memory_kv(x, P_k, P_v, K, V, lens)
+    assert torch.equal(K[..., :n, :], expected(x, P_k, heads)) and torch.equal(V[..., :n, :], expected(x, P_v, heads))
+    assert (K[..., n:, :] == 7).all() and (V[..., n:, :] == 7).all() and (lens == n).all()
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("b,n,d,heads,k,v", SHAPES)
+def test_append_rows(m, b, n, d, heads, k, v, dtype):
+    """Behind what is there; a sequence without room (or with a negative length) stays as it is."""
+    x, P_k, P_v = inputs(b, n, d, heads, k, v, n + 1)
+    cap = n + 10
+    K, V = caches(b, heads, cap, k, v, dtype)
+    lens = torch.arange(b, dtype=torch.int32, device=DEV) % 11
+    lens[b - 1] = 11
+    lens[0] = -2
+    after = torch.zeros_like(lens)
+    m.mqa_project_append_kv_rows(x, P_k, P_v, K, V, lens, after)
+    wk, wv = caches(b, heads, cap, k, v, dtype)
+    for i, L in enumerate(lens.tolist()):
+        if 0 <= L <= 10:
+            for w, P in ((wk, P_k), (wv, P_v)):
+                if dtype == torch.bfloat16:
+                    w[i, ..., L:L + n, :] = expected(x[i:i + 1], P, heads)[0]
+                else:
+                    w[i, ..., L:L + n, :] = (x[i].double() @ P.double()).float()
+    if dtype == torch.bfloat16:
+        assert torch.equal(K, wk) and torch.equal(V, wv)
+    else:      # (the order of the float64 sum may show in the last place)
+        assert torch.allclose(K, wk, rtol=2.0 ** -23, atol=1e-12) and torch.allclose(V, wv, rtol=2.0 ** -23, atol=1e-12)
+    assert after.tolist() == [L + n if 0 <= L <= 10 else L for L in lens.tolist()]
+
+
+def test_rows_of_any_values(m):
+    """Zeros, ties, wide ranges inside a row and a column, sums that cancel, subnormals, infinities and NaN."""
+    b, n, d = 64, 300, 200
+    x, P_k, P_v = inputs(b, n, d, 0, 128, 128, 9)
+    x[0, :40] = 0
+    x[1, 3], x[1, 4] = x[1, 3].abs() * 1e30, x[1, 4] * 1e-30
+    x[2] *= torch.exp(4 * torch.randn(n, d, device=DEV))
+    x[3, :, 100:] = -x[3, :, :100]
+    x[4, 5] = 1e-42
+    x[5, 7, 9], x[5, 8, 9], x[6, 0, 0] = float("inf"), float("nan"), float("-inf")
+    x[7] = torch.randint(-4, 5, (n, d), device=DEV).float()
+    P_k[100:, 16:64] = P_k[:100, 16:64]       # x[3]: sums that cancel
+    P_k[:, 3] = 0
+    P_k[:, 5] = torch.randint(-2, 3, (d,), device=DEV).float() * 2.0 ** -9      # with x[7]: sums that are exact ties
+    P_k[:, 6] *= torch.exp(4 * torch.randn(d, device=DEV))
+    P_k[17, 8], P_k[18, 9] = float("inf"), float("nan")
+    P_k[:, 10] *= 1e-35
+    K, V = caches(b, 0, n, 128, 128)
+    lens = torch.zeros(b, dtype=torch.int32, device=DEV)
+    m.mqa_project_memory_kv(x, P_k, P_v, K, V, lens)
+    want = expected(x, P_k, 0)
+    # sums that cancel to nothing are what the order of the 64-bit sum leaves: 200 roundings of sums below 100
+    assert float(K[3, :, 16:64].abs().max()) < 200 * 100 * 2.0 ** -53
+    K[3, :, 16:64] = want[3, :, 16:64]
+    assert same(K, want) and same(V, expected(x, P_v, 0))
