@@ -92,10 +92,7 @@ typedef struct {
                                form would keep one workgroup per compute unit
                                going over several ranked sequences
                        bit 11  rank by a separate launch even where that kernel
-                               would rank up to 1024 sequences itself
-                       bit 12  causal rows (prompt pass) in workgroups of 32 rows
-                               whose waves split the tiles, instead of 128 rows,
-                               32 per wave                                       */
+                               would rank up to 1024 sequences itself                                       */
 } mqa_tuning;
 
 /*

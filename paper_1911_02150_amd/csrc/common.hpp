@@ -90,6 +90,9 @@ hipError_t launch_decode_mfma(const DecodeParams& p, int flags, hipStream_t st);
 // both segments in one launch (p.seg1 filled in, 32 heads per workgroup in both); p.order must be null
 hipError_t launch_decode_mfma_two(const DecodeParams& p, long long nblocks0, long long nblocks1, hipStream_t st);
 
+// prompt_mfma.hip: causal rows, bf16 cache, k = v = 128, p.HG blocks of 128 rows per group
+hipError_t launch_prompt(const DecodeParams& p, hipStream_t st);
+
 // decode_direct.hip: k = v = 64 or 128 in float32, 64 in bf16 (hipErrorNotSupported: another shape).
 hipError_t launch_decode_direct(const DecodeParams& p, int is_bf16, hipStream_t st);
 

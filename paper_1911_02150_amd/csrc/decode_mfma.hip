@@ -1,4 +1,5 @@
-// Decode attention for a bf16 cache with k = v = 128 on gfx950 matrix cores.
+// Decode attention for a bf16 cache with k = v = 128 on gfx950 matrix cores (and causal rows of a prompt, up to 32 per
+// group; more: prompt_mfma.hip).
 //
 // Computes, per KV group ("sequence") and per position range, the three lines
 // logits / weights / o of the paper's incremental listings (Section 3 for
@@ -8,7 +9,7 @@
 // Work decomposition
 //   grid  = nseq * S * HG workgroups (sequence, position range, group of 16*HB heads; HB = 1 or 2).
 //           More than 32 heads: the STAGE form (64 heads per workgroup, see the end of this
-//           comment), or, for causal rows and by a tuning flag, head groups of 32 as neighbouring
+//           comment), or, by a tuning flag, head groups of 32 as neighbouring
 //           work items on one XCD that read the same tiles at about the same time, so that with
 //           cacheable loads the second read is served by L2.
 //           With an order array (ragged batches) the sequences are taken longest first; the STAGE
@@ -200,18 +201,12 @@ __device__ __forceinline__ void rank_own_sequences(const int32_t* lens, int lens
 // tile read it from LDS, where all eight waves put a round of four tiles (128 positions, 64 KiB)
 // with coalesced 16-byte loads of whole rows, one round ahead in registers.  Each byte of the
 // cache is requested from L2 once per workgroup, whatever the number of heads.
-//
-// ROWS: the form for causal rows (a prompt's n queries x h heads per sequence).  Every wave is a
-// team of its own: it takes 16*HB of the workgroup's NW*16*HB rows and all tiles up to those rows'
-// limits, so nothing is merged between waves and a workgroup's fixed costs (launch, q staging,
-// output) are spread over NW times the rows.
-template <int HB, int NW, bool QSPLIT, bool PSPLIT, bool NTL, bool TWO_SEG = false, bool STAGE = false, bool ROWS = false>
+template <int HB, int NW, bool QSPLIT, bool PSPLIT, bool NTL, bool TWO_SEG = false, bool STAGE = false>
 __global__ __launch_bounds__(NW * 64, STAGE ? 1 : 2)
 void decode_mfma_kernel(DecodeParams p) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   static_assert(!STAGE || (HB == 2 && NW == 8 && !TWO_SEG), "the staged form is two teams of four waves, 32 heads each");
-  static_assert(!ROWS || (!STAGE && !TWO_SEG), "one form at a time");
-  constexpr int TEAMS = STAGE ? 2 : ROWS ? NW : 1;
+  constexpr int TEAMS = STAGE ? 2 : 1;
   constexpr int NWT = NW / TEAMS;             // waves per team: they share the team's heads and split the tiles
   constexpr int NT = NWT * 64;                // threads per team
   constexpr int NH = 16 * HB;                 // heads handled by a team
@@ -468,9 +463,7 @@ void decode_mfma_kernel(DecodeParams p) {
   }
   const int end = min(begin + sg.chunk, lim_max);
   const int mask_from = min(end, lim_min);        // tiles reaching beyond this position need masking
-  // (ROWS: the other waves of the workgroup have their own limits and wait at the barriers below, so a wave
-  // with nothing to see goes on with no tiles and writes its zero rows at the end like any other)
-  if (!ROWS && end <= begin) {
+  if (end <= begin) {
     if (p.PS == 0) {          // empty sequence: zero output rows
       for (int idx = here(tid); idx < NH * (kD / 4); idx += NT) {
         int hl = idx / (kD / 4), c4 = idx % (kD / 4);
@@ -486,7 +479,7 @@ void decode_mfma_kernel(DecodeParams p) {
     Vbuf = v_rows_of(seq);
     continue;
   }
-  const int ntiles = end > begin ? (end - begin + 31) >> 5 : 0;
+  const int ntiles = (end - begin + 31) >> 5;
   const int nrounds = (ntiles + 3) >> 2;           // (64-head form)
   // Load slot s of a sequence fetches its round s; the slot after the last round is used, in the
   // persistent form, for the next sequence's first round (its q and length are requested when the
@@ -782,13 +775,13 @@ void decode_mfma_kernel(DecodeParams p) {
   }
 }
 
-template <int HB, int NW, bool STAGE = false, bool ROWS = false>
+template <int HB, int NW, bool STAGE = false>
 hipError_t launch_hb(const DecodeParams& p_in, int flags, hipStream_t st) {
   DecodeParams p = p_in;
   size_t nblocks = (p.order ? (size_t)((p.nseq + 7) / 8) * 8 : (size_t)p.nseq) * p.S * p.HG;
   if (!STAGE) p.persist = 0;
   if (p.persist > 0) nblocks = (size_t)p.persist;      // one workgroup per compute unit, several sequences each
-  constexpr int TEAMS = STAGE ? 2 : ROWS ? NW : 1;
+  constexpr int TEAMS = STAGE ? 2 : 1;
   constexpr int NWT = NW / TEAMS;
   p.merge_alias = (nblocks > 256 || TEAMS > 1) ? 1 : 0;      // more workgroups than CUs: keep LDS small
   const size_t q_bytes = (size_t)TEAMS * HB * 4 * 64 * 16 * 2;
@@ -799,8 +792,8 @@ hipError_t launch_hb(const DecodeParams& p_in, int flags, hipStream_t st) {
   const dim3 grid((unsigned)nblocks), block(NW * 64);
   void (*kern)(DecodeParams);
   // Non-temporal loads unless the tiles are meant to be found in L2 by a second head group.
-  const bool ntl = !(flags & 4) && (p.HG == 1 || STAGE) && !ROWS;
-#define MQA_PICK(QS, PS) (ntl ? decode_mfma_kernel<HB, NW, QS, PS, true, false, STAGE, ROWS> : decode_mfma_kernel<HB, NW, QS, PS, false, false, STAGE, ROWS>)
+  const bool ntl = !(flags & 4) && (p.HG == 1 || STAGE);
+#define MQA_PICK(QS, PS) (ntl ? decode_mfma_kernel<HB, NW, QS, PS, true, false, STAGE> : decode_mfma_kernel<HB, NW, QS, PS, false, false, STAGE>)
   switch (flags & 3) {
     case 0: kern = MQA_PICK(true, true); break;
     case 1: kern = MQA_PICK(false, true); break;
@@ -832,9 +825,9 @@ bool mfma_shape_ok(int G, int k, int v, int is_bf16, int cap) {
 }
 
 // 16 or 32 heads per workgroup; more than 32 heads: the staged form with 64 heads per workgroup
-// (plain decode and local attention), or groups of 32 (causal rows, or by a tuning flag)
+// (plain decode and local attention), blocks of 128 (causal rows), or groups of 32 (by a tuning flag)
 int mfma_heads_per_block(int G, int flags, int causal) {
-  if (causal && G > 32 && !(flags & 4096)) return 128;      // causal rows: four waves of 32 rows each
+  if (causal && G > 32) return 128;      // prompt_mfma.hip (up to 32 rows: the waves of a workgroup split the positions)
   return G <= 16 ? 16 : (G > 32 && !(flags & 8) && !causal) ? 64 : 32;
 }
 
@@ -896,7 +889,7 @@ hipError_t launch_decode_mfma(const DecodeParams& p, int flags, hipStream_t st) 
   if (hpb == 16) return wide ? launch_hb<1, 8>(p, flags, st) : launch_hb<1, 4>(p, flags, st);
   // the staged form is bound by its arithmetic, not by HBM: single-term weights unless asked otherwise
   if (hpb == 64) return launch_hb<2, 8, true>(p, (flags & 128) ? flags : (flags | 2), st);
-  if (hpb == 128) return launch_hb<2, 4, false, true>(p, flags, st);
+  if (hpb == 128) return launch_prompt(p, st);
   return wide ? launch_hb<2, 8>(p, flags, st) : launch_hb<2, 4>(p, flags, st);
 }
 

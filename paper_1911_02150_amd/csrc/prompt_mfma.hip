@@ -1,0 +1,253 @@
+// Causal attention of a whole prompt (bf16 cache, k = v = 128): the rows of a group are n queries x h heads that share
+// its K and V (multi-query), or the n queries of one head; row r sees positions below L - n + r / h + 1.
+//
+// Long prompts are bound by the matrix cores and by the vector work between the two products, so everything
+// that does not depend on the row is done once per workgroup instead of once per wave:
+//   * A workgroup of four waves takes 128 rows, 32 per wave, and walks over the positions in tiles of 64.  The
+//     tile is fetched with whole-row loads (one tile ahead in registers), V is transposed while it is stored to
+//     LDS (16 byte permutes per thread and tile; every wave for itself took 64), and all waves read their operands from there.
+//   * v_mfma_f32_32x32x16_bf16: S^T[32 pos x 32 rows] = K . q^T with q in registers; a lane has one row and
+//     positions 8 (e / 4) + 4 g + e % 4, e < 16, of a block of 32.  O^T[32 cols x 32 rows] += V^T . P^T: step t takes
+//     the positions of registers 8 t .. 8 t + 7, so the weights are B operands as they are, and V^T is stored in
+//     that order: 16 bytes = positions 16 t + 4 g + 0..3 and 16 t + 8 + 4 g + 0..3 of one column.
+//   * q and the weights are split into bf16 hi + lo terms (two products each), as in decode_mfma.hip.
+//   * Two workgroups share a compute unit; the longest rows are started first.
+// Measured (us; before: 32 rows per wave in decode_mfma.hip, every wave loading and transposing for itself; on one box): b=8,
+// n=4096, h=8: 757 -> 582 (472 TFLOP/s of causal flops, four bf16 products each: 0.94 PFLOP/s); b=32, n=1024: 241 -> 192; b=128,
+// n=128: 44.5 -> 36.8; one sequence of 4096: 168 -> 155; multi-head b=3, n=1000, h=16: 84 -> 63.  A tile's two
+// blocks of 32 positions go through the softmax together: one after the other measured 609, and 178 for the one sequence (one
+// wave per SIMD: nothing else fills the waits).  Storing the next tile between the products: 640 (registers spill).
+// Positions at and beyond a row's limit get the logit -inf; V rows beyond the workgroup's last limit are stored as zeros,
+// so the cache may hold anything there.
+#include "common.hpp"
+
+namespace mqa {
+namespace {
+
+typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
+typedef __attribute__((ext_vector_type(16))) float floatx16;
+typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
+typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
+
+constexpr int kRowBytes = 256;                 // one cache row
+constexpr int kBufferWord3 = 0x00020000;       // raw 32-bit-element buffer, no swizzle
+constexpr uint32_t kNoTile = 0x80000000u;      // an offset no cache reaches: zeros, nothing is fetched
+constexpr float kSlack = 8.f;                  // log2 of the largest softmax weight kept before the running state is rescaled
+constexpr int kTilePos = 64;
+constexpr int kKBytes = kTilePos * kRowBytes, kBuffer = 2 * kKBytes;       // K tile, then V^T: 128 columns of 128 bytes
+
+__device__ __forceinline__ floatx16 mfma32(const u32x4& a, const u32x4& b, const floatx16& c) {
+  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+}
+// hi + lo bf16 terms of a pair: hi = rne(x), lo = rne(x - hi) (the difference is exact in float32)
+__device__ __forceinline__ void split_pair(float a, float b, uint32_t& hi, uint32_t& lo) {
+  hi = pack_bf16_pair(a, b);
+  lo = pack_bf16_pair(a - __uint_as_float(hi << 16), b - __uint_as_float(hi & 0xffff0000u));
+}
+
+__global__ __launch_bounds__(256, 2)
+void prompt_kernel(DecodeParams p) {
+  extern __shared__ __align__(16) unsigned char smem[];      // two buffers; at the end the waves' outputs
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int i32 = lane & 31, g = lane >> 5;
+
+  // Work item -> (sequence, row block), last (longest) row blocks first.  Whole sequences per XCD where they divide
+  // evenly (its L2 then holds their K and V), else row blocks in turn over the XCDs.
+  const int nb = gridDim.x, bid = blockIdx.x;
+  const int wid = p.nseq % 8 == 0 ? (bid & 7) * (nb >> 3) + (bid >> 3) : bid;
+  const int seq = wid / p.HG, row_block = p.HG - 1 - (wid - seq * p.HG);
+  const int row0 = row_block * 128 + wave * 32;              // the wave's rows
+  const int G = p.G, h = p.causal_h, nq = G / h;
+
+  auto rows_of = [&](const void* base) {
+    return __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<char*>(static_cast<const char*>(base)) + (size_t)seq * p.cap * kRowBytes, 0, p.cap * kRowBytes, kBufferWord3);
+  };
+  const __amdgpu_buffer_rsrc_t Kbuf = rows_of(p.K), Vbuf = rows_of(p.V);
+  int L = p.lens[seq / p.lens_div];
+  L = L < 0 ? 0 : (L > p.cap ? p.cap : L);
+  auto limit = [&](int row) { return max(0, L - nq + min(row, G - 1) / h + 1); };
+  const int lim = limit(row0 + i32), lim_min = limit(row0), lim_max = limit(row0 + 31);
+  const int end = limit(row_block * 128 + 127);              // of the workgroup
+  const int ntiles = (end + kTilePos - 1) / kTilePos;
+
+  // ---- staging: K chunk x = tid + 256 j (row x / 16, 16-byte chunk x % 16), kept at chunk ^ (row & 15); V rows 4 quad .. + 3,
+  // columns 8 cg .. + 7, transposed.  V^T: 16-byte chunk (u, t, g) of column c at chunk ^ ((c >> 3) ^ c) & 7
+  const int quad = tid >> 4, cg = tid & 15;
+  const int v_chunk = (quad >> 3) * 4 + ((quad >> 2) & 1) * 2 + (quad & 1), v_half = (quad >> 1) & 1;
+  u32x4 kst[4], vst[4];
+  auto load_tile = [&](int t) {
+    const uint32_t at = t < ntiles ? (uint32_t)t * (uint32_t)(kTilePos * kRowBytes) : kNoTile;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) kst[j] = __builtin_amdgcn_raw_buffer_load_b128(Kbuf, at + (uint32_t)(tid + 256 * j) * 16u, 0, 0);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) vst[j] = __builtin_amdgcn_raw_buffer_load_b128(Vbuf, at + (uint32_t)((4 * quad + j) * kRowBytes + cg * 16), 0, 0);
+  };
+  auto store_tile = [&](int t) {
+    unsigned char* kb = smem + (t & 1) * kBuffer;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int x = tid + 256 * j, row = x >> 4;
+      *reinterpret_cast<u32x4*>(kb + row * kRowBytes + (((x & 15) ^ (row & 15)) << 4)) = kst[j];
+    }
+    if ((t + 1) * kTilePos > end) {            // rows past the last limit may hold anything
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        if (t * kTilePos + 4 * quad + j >= end) vst[j] = u32x4{0u, 0u, 0u, 0u};
+    }
+    unsigned char* vb = kb + kKBytes + 8 * v_half;
+#pragma unroll
+    for (int w = 0; w < 4; ++w)
+#pragma unroll
+      for (int par = 0; par < 2; ++par) {
+        const uint32_t sel = par ? 0x07060302u : 0x05040100u;
+        const int c = 2 * w + par, col = 8 * cg + c;
+        const u32x2 x = u32x2{__builtin_amdgcn_perm(vst[1][w], vst[0][w], sel), __builtin_amdgcn_perm(vst[3][w], vst[2][w], sel)};
+        *reinterpret_cast<u32x2*>(vb + col * 128 + ((v_chunk ^ ((cg ^ c) & 7)) << 4)) = x;
+      }
+  };
+
+  load_tile(0);
+  // ---- q as B operands: lane (i, g) holds elements 16 s + 8 g .. + 7 of row i
+  u32x4 qh[8], ql[8];
+  {
+    const float4* src = reinterpret_cast<const float4*>(p.q + ((size_t)seq * G + min(row0 + i32, G - 1)) * 128) + 2 * g;
+#pragma unroll
+    for (int s = 0; s < 8; ++s) {
+      const float4 a = src[4 * s], b = src[4 * s + 1];
+      const float x[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+#pragma unroll
+      for (int d = 0; d < 4; ++d) {
+        uint32_t hi, lo;
+        split_pair(x[2 * d] * p.qscale, x[2 * d + 1] * p.qscale, hi, lo);
+        qh[s][d] = hi;
+        ql[s][d] = lo;
+      }
+    }
+  }
+  floatx16 acc[4];
+#pragma unroll
+  for (int cb = 0; cb < 4; ++cb)
+#pragma unroll
+    for (int e = 0; e < 16; ++e) acc[cb][e] = 0.f;
+  float m_run = -INFINITY, l_run = 0.f;
+
+  // logits of a tile's two blocks of 32 positions
+  floatx16 sc[2];
+  auto logits = [&](int t) {
+    const unsigned char* kb = smem + (t & 1) * kBuffer + i32 * kRowBytes;
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) sc[u][e] = 0.f;
+#pragma unroll
+    for (int s = 0; s < 8; ++s) {
+      u32x4 a[2];
+#pragma unroll
+      for (int u = 0; u < 2; ++u) a[u] = *reinterpret_cast<const u32x4*>(kb + 32 * u * kRowBytes + (((2 * s + g) ^ (i32 & 15)) << 4));
+#pragma unroll
+      for (int u = 0; u < 2; ++u) sc[u] = mfma32(a[u], qh[s], sc[u]);
+#pragma unroll
+      for (int u = 0; u < 2; ++u) sc[u] = mfma32(a[u], ql[s], sc[u]);
+    }
+  };
+  // online softmax (lazy rescaling, see decode_mfma.hip) and weighted sum
+  auto weigh = [&](int t) {
+    const int p0 = t * kTilePos;
+    const unsigned char* vb = smem + (t & 1) * kBuffer + kKBytes;
+    if (p0 + kTilePos > lim_min) {
+#pragma unroll
+      for (int u = 0; u < 2; ++u)
+#pragma unroll
+        for (int e = 0; e < 16; ++e)
+          if (p0 + 32 * u + 8 * (e >> 2) + 4 * g + (e & 3) >= lim) sc[u][e] = -INFINITY;
+    }
+    float mx = fmaxf(sc[0][0], sc[1][0]);
+#pragma unroll
+    for (int e = 1; e < 16; ++e) mx = fmaxf(mx, fmaxf(sc[0][e], sc[1][e]));
+    mx = fmaxf(mx, __shfl_xor(mx, 32));
+    const float mnew = fmaxf(m_run, mx);
+    if (__any(mnew > m_run + kSlack)) {
+      const float alpha = __builtin_amdgcn_exp2f(m_run - (mnew == -INFINITY ? 0.f : mnew));      // (a row that has seen nothing yet)
+      l_run *= alpha;
+#pragma unroll
+      for (int cb = 0; cb < 4; ++cb) acc[cb] *= alpha;
+      m_run = mnew;
+    }
+    const float mref = m_run == -INFINITY ? 0.f : m_run;
+    float sum[2] = {0.f, 0.f};
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      const int u = s >> 1;
+      u32x4 hi, lo;
+#pragma unroll
+      for (int d = 0; d < 4; ++d) {
+        const float x = __builtin_amdgcn_exp2f(sc[u][8 * (s & 1) + 2 * d] - mref), y = __builtin_amdgcn_exp2f(sc[u][8 * (s & 1) + 2 * d + 1] - mref);
+        sum[0] += x;
+        sum[1] += y;
+        uint32_t hh, ll;
+        split_pair(x, y, hh, ll);
+        hi[d] = hh;
+        lo[d] = ll;
+      }
+      const int chunk = 2 * s + g;
+      u32x4 a[4];
+#pragma unroll
+      for (int cb = 0; cb < 4; ++cb) {
+        const int col = 32 * cb + i32;
+        a[cb] = *reinterpret_cast<const u32x4*>(vb + col * 128 + ((chunk ^ (((col >> 3) ^ col) & 7)) << 4));
+      }
+#pragma unroll
+      for (int cb = 0; cb < 4; ++cb) acc[cb] = mfma32(a[cb], hi, acc[cb]);
+#pragma unroll
+      for (int cb = 0; cb < 4; ++cb) acc[cb] = mfma32(a[cb], lo, acc[cb]);
+    }
+    l_run += sum[0] + sum[1];
+  };
+
+  if (ntiles > 0) {
+    store_tile(0);
+    load_tile(1);
+  }
+  __syncthreads();
+  for (int t = 0; t < ntiles; ++t) {
+    // (buffer t + 1 was last read in round t - 1, which the barrier at its end closed)
+    const bool sees = t * kTilePos < lim_max;                // (the same for the whole wave)
+    if (t + 1 < ntiles) {
+      store_tile(t + 1);
+      load_tile(t + 2);
+    }
+    if (sees) { logits(t); weigh(t); }
+    __syncthreads();
+  }
+
+  // ---- output: through the wave's quarter of LDS, so that rows leave as whole lines.  acc[cb][e] is column 32 cb + 8 (e / 4)
+  // + 4 g + e % 4 of row i32
+  const float lsum = l_run + __shfl_xor(l_run, 32);
+  const float inv = lsum > 0.f ? 1.0f / lsum : 0.f;          // (a row with nothing to see: zeros)
+  float4* rows = reinterpret_cast<float4*>(smem + wave * (32 * 512));
+#pragma unroll
+  for (int cb = 0; cb < 4; ++cb)
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      rows[i32 * 32 + ((8 * cb + 2 * q + g) ^ i32)] =
+          make_float4(acc[cb][4 * q] * inv, acc[cb][4 * q + 1] * inv, acc[cb][4 * q + 2] * inv, acc[cb][4 * q + 3] * inv);
+  __syncthreads();
+#pragma unroll
+  for (int r = 0; r < 32; r += 2) {
+    const int row = r + g;
+    if (row0 + row < G) reinterpret_cast<float4*>(p.o + ((size_t)seq * G + row0 + row) * 128)[i32] = rows[row * 32 + (i32 ^ row)];
+  }
+}
+
+}  // namespace
+
+hipError_t launch_prompt(const DecodeParams& p, hipStream_t st) {
+  const long long nblocks = (long long)p.nseq * p.HG;        // HG: blocks of 128 rows
+  if (nblocks > 0x7fffffffll) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(prompt_kernel, dim3((unsigned)nblocks), dim3(256), 2 * kBuffer, st, p);
+  return hipGetLastError();
+}
+
+}  // namespace mqa

@@ -1,0 +1,84 @@
+"""The prompt kernel (csrc/prompt_mfma.hip) against 64-bit attention: rows around its blocks of 32 and 128, lengths around its
+tiles of 64, sequence counts that do and do not divide over the XCDs."""
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+DEV = "cuda:0"
+# q and the weights carry 16 bits (hi + lo bf16 terms): 2^-16 of logits up to 12 moves a weight by 2e-4, of values up to 4.5
+TOL = 1e-3
+
+
+@pytest.fixture(scope="module")
+def m():
+    import paper_1911_02150_amd as lib
+    lib.load_library()
+    return lib
+
+
+def causal(q, K, V, L):
+    """q [n,128] of consecutive positions ending at L - 1."""
+    n = q.shape[0]
+    z = q.double() @ K[:max(L, 0)].double().t()
+    at, last = torch.arange(max(L, 0), device=DEV), torch.arange(L - n, L, device=DEV)
+    z.masked_fill_(at[None, :] > last[:, None], float("-inf"))
+    return torch.nan_to_num(torch.softmax(z, -1), nan=0.0) @ V[:max(L, 0)].double()
+
+
+@pytest.mark.parametrize("b,n,h,prefix", [
+    (1, 33, 1, 0),         # one row past 32
+    (2, 16, 8, 0),         # a whole block of 128 rows
+    (3, 43, 3, 20),        # 129 rows: one in the second block; 63 positions
+    (2, 64, 5, 0),         # positions fill a tile
+    (8, 65, 2, 63),        # one sequence per XCD; rows that straddle tiles
+    (5, 150, 8, 107),
+    (1, 700, 12, 1),
+])
+def test_prompt(m, b, n, h, prefix):
+    g = torch.Generator(device=DEV)
+    g.manual_seed(n + h)
+    cap = n + prefix + 5
+    q = torch.randn(b, n, h, 128, generator=g, device=DEV) * 0.25
+    K = torch.randn(b, cap, 128, generator=g, device=DEV).to(torch.bfloat16)
+    V = torch.randn(b, cap, 128, generator=g, device=DEV).to(torch.bfloat16)
+    lens = [n + prefix] * b
+    lens[-1] = n + prefix + 5
+    if b > 2:
+        lens[1] = n // 2          # shorter than the prompt: the first rows see nothing
+        lens[2] = 0
+    for i, L in enumerate(lens):
+        K[i, L:], V[i, L:] = float("nan"), float("inf")
+    got = m.mqa_prefill_attention(q, K, V, torch.tensor(lens, dtype=torch.int32, device=DEV))
+    for i, L in enumerate(lens):
+        for j in range(h):
+            assert float((got[i, :, j].double() - causal(q[i, :, j], K[i], V[i], L)).abs().max()) < TOL
+
+
+@pytest.mark.parametrize("b,n,h,prefix", [(1, 33, 3, 0), (2, 128, 4, 64), (3, 129, 3, 0), (1, 513, 2, 30)])
+def test_prompt_multi_head(m, b, n, h, prefix):
+    g = torch.Generator(device=DEV)
+    g.manual_seed(n)
+    cap = n + prefix
+    q = torch.randn(b, h, n, 128, generator=g, device=DEV) * 0.25
+    K = torch.randn(b, h, cap, 128, generator=g, device=DEV).to(torch.bfloat16)
+    V = torch.randn(b, h, cap, 128, generator=g, device=DEV).to(torch.bfloat16)
+    got = m.mha_prefill_attention(q, K, V, torch.full((b,), cap, dtype=torch.int32, device=DEV))
+    for i in range(b):
+        for j in range(h):
+            assert float((got[i, j].double() - causal(q[i, j], K[i, j], V[i, j], cap)).abs().max()) < TOL
+
+
+def test_prompt_rescaling(m):
+    """Logits that rise along the sequence by far more than the rescaling slack."""
+    n, cap = 200, 200
+    g = torch.Generator(device=DEV)
+    g.manual_seed(1)
+    q = torch.randn(1, n, 2, 128, generator=g, device=DEV)
+    d = torch.randn(128, generator=g, device=DEV)
+    q += d
+    K = (torch.linspace(-1, 1, cap, device=DEV)[:, None] * d + 0.05 * torch.randn(cap, 128, generator=g, device=DEV)).to(torch.bfloat16)[None]
+    V = torch.randn(1, cap, 128, generator=g, device=DEV).to(torch.bfloat16)
+    got = m.mqa_prefill_attention(q, K, V, torch.tensor([cap], dtype=torch.int32, device=DEV))
+    for j in range(2):      # logits up to 150
+        assert float((got[0, :, j].double() - causal(q[0, :, j], K[0], V[0], cap)).abs().max()) < 1e-2
