@@ -51,10 +51,31 @@ struct Plan {
   int S, chunk, HG;
 };
 
+// Fewer ranges than fill the compute units, where that is faster.  Estimated us of a launch over S ranges: 3.5, and either
+// the positions of the fullest compute unit (one workgroup streams about 33 GB/s; 14 ns a position at least) or all
+// bytes at the card's read rate, and 3.5 for the merge launch if S > 1.  What that catches (measured, before -> now): the
+// last, nearly empty round of workgroups (b=200, cap=512, 400 workgroups on 256 compute units: 16.6 -> 12.3; 130 of 20
+// heads in float32: 36 -> 25) and short caches whose merge costs more than it spreads (b=128, cap=256: 8.0 -> 7.0;
+// b=64: 8.3 -> 6.4).  At b=64, cap=512 four ranges stay: 9.3 against 10.4 in one.
+int fewer_ranges(long long groups, int cap, int S, int pos_bytes) {
+  const double ns = pos_bytes / 33. > 14. ? pos_bytes / 33. : 14.;
+  const double all = (double)groups * cap * pos_bytes / 5.9e6;
+  auto cost = [&](int s) {
+    const int chunk = ((cap + s - 1) / s + 31) & ~31;
+    const long long per_cu = (groups * ((cap + chunk - 1) / chunk) + kTargetBlocks - 1) / kTargetBlocks;
+    const double fullest = 1e-3 * ns * (double)per_cu * chunk;
+    return 3.5 + (fullest > all ? fullest : all) + (s > 1 ? 3.5 : 0.);
+  };
+  int best = S;
+  for (int s = S - 1; s >= 1; --s)
+    if (cost(s) < 0.97 * cost(best)) best = s;
+  return best;
+}
+
 // Split of the position axis.  Every range is a multiple of 32 positions; a
 // range is at least 128 (MFMA: one tile per wave) or 256 (generic) positions.
 int plan_decode(int nseq, int G, int cap_all, int window, int k, int v, int is_bf16, const Tuning& tn, Plan* pl,
-                int causal = 0) {
+                int causal = 0, bool merged_anyway = false) {
   // with a window a sequence attends to at most window positions, lying in at most
   // ceil(window/32)+1 tiles counted from the 32-aligned start of the window
   int cap = cap_all;
@@ -80,6 +101,9 @@ int plan_decode(int nseq, int G, int cap_all, int window, int k, int v, int is_b
     const long long groups = (long long)nseq * pl->HG;
     S = (int)((kTargetBlocks + groups - 1) / groups);
     if (S > max_s) S = max_s;
+    const bool streams = pl->use_mfma ? pl->HG == 1 && mfma_heads_per_block(G, tn.flags, causal) <= 32
+                                      : tn.kernel != 1 && direct_shape_ok(k, v, is_bf16, cap_all);
+    if (S > 1 && streams && !merged_anyway) S = fewer_ranges(groups, cap, S, (k + v) * (is_bf16 ? 2 : 4));
   }
   if (S < 1) S = 1;
   int chunk = (cap + S - 1) / S;
@@ -228,9 +252,9 @@ int plan_beams(int b, int beam, int h, int cap_src, int cap_own, int k, int v, i
   if ((k & 7) || (v & 7) || k > 256 || v > 256) return MQA_ERR_SHAPE;
   if ((long long)b * beam * h > (1ll << 24) || cap_src > (1 << 24) || cap_own > (1 << 24)) return MQA_ERR_SHAPE;
   Tuning tn;
-  int rc = plan_decode(b, beam * h, cap_src, 0, k, v, dt == MQA_BF16, tn, &bp->src);
+  int rc = plan_decode(b, beam * h, cap_src, 0, k, v, dt == MQA_BF16, tn, &bp->src, 0, true);      // (the two caches are merged in any case)
   if (rc) return rc;
-  rc = plan_decode(b * beam, h, cap_own, 0, k, v, dt == MQA_BF16, tn, &bp->own);
+  rc = plan_decode(b * beam, h, cap_own, 0, k, v, dt == MQA_BF16, tn, &bp->own, 0, true);
   if (rc) return rc;
   bp->slots = bp->src.S + bp->own.S;
   return MQA_OK;

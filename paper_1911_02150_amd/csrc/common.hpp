@@ -94,6 +94,7 @@ hipError_t launch_decode_mfma_two(const DecodeParams& p, long long nblocks0, lon
 hipError_t launch_prompt(const DecodeParams& p, hipStream_t st);
 
 // decode_direct.hip: k = v = 64 or 128 in float32, 64 in bf16 (hipErrorNotSupported: another shape).
+bool direct_shape_ok(int k, int v, int is_bf16, int cap);
 hipError_t launch_decode_direct(const DecodeParams& p, int is_bf16, hipStream_t st);
 
 // decode_generic.hip: any k, v <= 256, float32 or bf16 cache.

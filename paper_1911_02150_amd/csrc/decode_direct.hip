@@ -288,14 +288,15 @@ hipError_t pick_direct(const DecodeParams& p, hipStream_t st) {
 
 }  // namespace
 
+bool direct_shape_ok(int k, int v, int is_bf16, int cap) {
+  return k == v && (k == 64 || (k == 128 && !is_bf16)) && (long long)cap * k * (is_bf16 ? 2 : 4) < (1ll << 31);      // 31-bit byte offsets
+}
+
 // Returns hipErrorNotSupported for shapes this kernel does not cover (the caller then uses the generic one).
 hipError_t launch_decode_direct(const DecodeParams& p, int is_bf16, hipStream_t st) {
-  if (p.k != p.v || p.causal_h > 0) return hipErrorNotSupported;
-  if ((long long)p.cap * p.k * (is_bf16 ? 2 : 4) >= (1ll << 31)) return hipErrorNotSupported;      // 31-bit byte offsets
-  if (!is_bf16 && p.k == 128) return pick_direct<float, 128>(p, st);
-  if (!is_bf16 && p.k == 64) return pick_direct<float, 64>(p, st);
-  if (is_bf16 && p.k == 64) return pick_direct<uint16_t, 64>(p, st);
-  return hipErrorNotSupported;
+  if (!direct_shape_ok(p.k, p.v, is_bf16, p.cap) || p.causal_h > 0) return hipErrorNotSupported;
+  if (is_bf16) return pick_direct<uint16_t, 64>(p, st);
+  return p.k == 128 ? pick_direct<float, 128>(p, st) : pick_direct<float, 64>(p, st);
 }
 
 }  // namespace mqa
