@@ -376,7 +376,10 @@ hipError_t launch_project_qkv_append(const float* x, const float* P_q, const flo
   // column tiles must not straddle q / K / V: the tile width divides k and v (both multiples of 16)
   int g = k, r = v;
   while (r) { const int t2 = g % r; g = r; r = t2; }
-  const Tile t = pick_tile(q_done ? ntot - nq : ntot, rows, g);
+  Tile t = pick_tile(q_done ? ntot - nq : ntot, rows, g);
+  // A decode step whose K / V columns outweigh q's: their float64 tiles take one row block at a time, so a second one in
+  // the workgroup only makes it longer (b=256, h=8 multi-head: 50.7 -> 39.9 us; b=128: 27.6 either way)
+  if (t.RB == 2 && t.CB == 4 && rows <= 512 && ntot - nq > nq) t.RB = 1;
   // a decode step's rows and K / V columns that are a small part of the product (multi-query): K / V tiles of
   // 16 columns (b=128, h=8: 14.2 -> 10.4 us; multi-head, where they are two thirds of it: 25.9 -> 31.6 us, so not there)
   const int kv_narrow = (rows <= 512 && 2 * (ntot - nq) <= nq) ? 1 : 0;
