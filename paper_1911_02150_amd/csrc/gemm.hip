@@ -401,8 +401,8 @@ hipError_t launch_split(const float* in, const float* P, float* out, int rows, i
 //   64 x 64:       12                     22.5                                         1024 x 1024 x 1024: 17, 2048 x 2048: 50
 //   128 x 128:     33 for each 256 (one per compute unit)                              4096 x 1024 x 1024: 38
 //   256 x 256:     70                                                                  2000 x 1000 x 5008: 88
-// and the split-contraction kernel on float32 instructions 5 + 2 rows N C / 64 TFLOP/s (80 with n contiguous): 128 x
-// 1024 x 1024: 9.2; 128 x 4096 x 1024, long sums and few tiles: 24, 32 x 32 tiles 26; 1024 x 1024 x 1024: 32; 768 x
+// and the split-contraction kernel on float32 instructions 5 (less below C = 1024, in proportion) + 2 rows N C / 64
+// TFLOP/s (80 with n contiguous): 128 x 512 x 4096: 9.1 (32 x 32 tiles 10.6); 128 x 1024 x 1024: 9.2; 128 x 4096 x 1024, long sums and few tiles: 24, 32 x 32 tiles 26; 1024 x 1024 x 1024: 32; 768 x
 // 4096 x 1024: 104, 64 x 64 tiles 50.
 hipError_t launch_gemm_tiled(int mode, const float* in, const float* P, float* out,
                              int rows, int d, int h, int kv, int epilogue, int apart, hipStream_t st) {
@@ -416,7 +416,7 @@ hipError_t launch_gemm_tiled(int mode, const float* in, const float* P, float* o
   int best = 0;
   for (int f = 1; f < 4; ++f)
     if (w[f] < w[best]) best = f;
-  const double split_contraction = 5. + 2. * ((rows + 15) / 16 * 16) * N * C / (outp ? 64e6 : 80e6);
+  const double split_contraction = (C < 1024. ? 5. * C / 1024. : 5.) + 2. * ((rows + 15) / 16 * 16) * N * C / (outp ? 64e6 : 80e6);
   if (5. + apart + C / 1024. * w[best] > 0.9 * split_contraction) return hipErrorNotSupported;
 #define MQA_SPLIT(BM, WR, WC, KG, PD) \
   return outp ? launch_split<true, BM, BM, WR, WC, KG, PD>(in, P, out, rows, d, h, kv, N, epilogue, st) \
