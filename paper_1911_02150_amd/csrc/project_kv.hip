@@ -272,7 +272,9 @@ void project_kv_exact_kernel(KvParams p) {
         const int e = (int)(bits >> 23) & 255, e_out = e + 24 - row_up - col_up[j];
         // the sum's bf16 is open if a tie (the middle of the low 16 bits) is no further off than the bound and the
         // rounding to float, in units of the last place; one that leaves the normal floats is open as well
-        const float off = fabsf((float)((int)(bits & 0xffffu) - 0x8000)) - 1.f;
+        // (just above a power of two the tie below is in the next binade: half the spacing, 0x4000 below the power itself)
+        const int low = (int)(bits & 0xffffu);
+        const float off = (bits & 0x7f0000u) ? fabsf((float)(low - 0x8000)) - 1.f : (float)min(abs(low - 0x8000) - 1, low + 0x4000 - 2);
         open[j] = e == 0 || e_out < 2 || e_out > 253 || !(ldexpf(err, 150 - e) < off);
         uint32_t v = float_to_bf16_rne(__uint_as_float((bits & 0x807fffffu) | (uint32_t)(e_out & 255) << 23));
         if (row_most == 0 || col_most[j] == 0) { v = 0; open[j] = false; }

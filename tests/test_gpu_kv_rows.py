@@ -114,3 +114,21 @@ def test_rows_of_any_values(m):
     assert float(K[3, :, 16:64].abs().max()) < 200 * 100 * 2.0 ** -53
     K[3, :, 16:64] = want[3, :, 16:64]
     assert same(K, want) and same(V, expected(x, P_v, 0))
+
+
+@pytest.mark.parametrize("sign", [1, -1])
+def test_sums_around_a_power_of_two(m, sign):
+    """Sums that end just above and just below 2^42, whose error bound (what the fixed point drops of the values beside one
+    of 1.25 . 2^30) reaches the nearest tie: below the power of two the ties lie half as far apart."""
+    b, n, d, big = 64, 512, 8, 1.25 * 2.0 ** 30
+    x = torch.tensor([big] * 4 + [-0.99] * 3 + [0.0], device=DEV).repeat(b, n, 1)
+    x[..., 7] = torch.linspace(3262, 3302, b * n, device=DEV).view(b, n)
+    x[::2, :, 7] = x[::2, :, 7].floor()
+    w = sign * torch.tensor([-0.99] * 4 + [big] * 4, device=DEV)
+    P = w[:, None] * 2.0 ** torch.arange(-64, 64, device=DEV)
+    K, V = caches(b, 0, n, 128, 128)
+    lens = torch.zeros(b, dtype=torch.int32, device=DEV)
+    m.mqa_project_memory_kv(x, P, P * 2, K, V, lens)
+    want = expected(x, P, 0)
+    assert (want[..., 64].abs() < 2.0 ** 42).any() and (want[..., 64].abs() > 2.0 ** 42).any()
+    assert torch.equal(K, want) and torch.equal(V, expected(x, P * 2, 0))
