@@ -277,7 +277,7 @@ void project_qkv_append_kernel(const float* __restrict__ x, const float* __restr
       int L = mem_rows > 0 ? row - seq * mem_rows : lens_in[row];
       if (append) {
         const int have = lens_in[seq];
-        L = have < 0 || have + mem_rows > cap ? -1 : L + have;
+        L = have < 0 || have > cap - mem_rows ? -1 : L + have;      // (mem_rows <= cap; a sum could wrap)
       }
       if (L < 0 || L >= cap) continue;
       dst[(((size_t)seq * h_kv + n / kv) * cap + L) * kv + (n % kv)] = cache_value<CT>(sum_partials(red_raw, e, T * width));
@@ -288,7 +288,7 @@ void project_qkv_append_kernel(const float* __restrict__ x, const float* __restr
     if (mem_rows > 0) {
       if (row % mem_rows == 0) {
         const int L = lens_in ? lens_in[row / mem_rows] : mem_rows;
-        if (append) lens_out[row / mem_rows] = (L < 0 || L + mem_rows > cap) ? L : L + mem_rows;
+        if (append) lens_out[row / mem_rows] = (L < 0 || L > cap - mem_rows) ? L : L + mem_rows;
         else lens_out[row / mem_rows] = L < 0 ? 0 : (L > mem_rows ? mem_rows : L);
       }
     } else {

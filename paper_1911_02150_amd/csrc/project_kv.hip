@@ -225,7 +225,7 @@ void project_kv_exact_kernel(KvParams p) {
     int at = row - seq * p.n;
     if (p.append) {
       const int L = p.lens_in[seq];
-      if (L < 0 || L + p.n > p.cap) return nullptr;
+      if (L < 0 || L > p.cap - p.n) return nullptr;            // (n <= cap; a sum could wrap)
       at += L;
     }
     return p.dst[which] + (((size_t)seq * p.h_kv + col / kv) * p.cap + at) * kv + col % kv;
@@ -324,7 +324,7 @@ void project_kv_exact_kernel(KvParams p) {
   if (which == 0 && tile_n == 0 && tid < kTile && row0 + tid < rows && (row0 + tid) % p.n == 0) {
     const int seq = (row0 + tid) / p.n;
     const int L = p.lens_in ? p.lens_in[seq] : p.n;
-    if (p.append) p.lens_out[seq] = (L < 0 || L + p.n > p.cap) ? L : L + p.n;
+    if (p.append) p.lens_out[seq] = (L < 0 || L > p.cap - p.n) ? L : L + p.n;
     else p.lens_out[seq] = L < 0 ? 0 : (L > p.n ? p.n : L);
   }
 }

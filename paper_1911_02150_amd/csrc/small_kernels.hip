@@ -268,7 +268,7 @@ void append_kernel(T* K, T* V, const float* k_new, const float* v_new, int32_t* 
   const int i = blockIdx.x;
   const int L = lens[i];
   __syncthreads();
-  if (L < 0 || L + n > cap) return;
+  if (L < 0 || L > cap - n) return;      // (n <= cap; a sum could wrap)
   for (int idx = threadIdx.x; idx < n * h_kv * k; idx += 256) {
     const int r = idx / (h_kv * k), rem = idx - r * (h_kv * k);
     const int j = rem / k, c = rem - j * k;

@@ -132,3 +132,47 @@ def test_sums_around_a_power_of_two(m, sign):
     want = expected(x, P, 0)
     assert (want[..., 64].abs() < 2.0 ** 42).any() and (want[..., 64].abs() > 2.0 ** 42).any()
     assert torch.equal(K, want) and torch.equal(V, expected(x, P * 2, 0))
+
+
+FULL = [2 ** 31 - 1, 2 ** 31 - 2, 2 ** 31 - 5, 2 ** 30, -1, -2 ** 31]      # lengths no cache has room behind
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("b,n,d,heads,k,v", [(64, 300, 1000, 0, 128, 128), (6, 9, 72, 3, 16, 32)])
+def test_append_to_any_length(m, b, n, d, heads, k, v, dtype):
+    """Lengths up to the largest integer: the cache and the length stay as they are."""
+    x, P_k, P_v = inputs(b, n, d, heads, k, v, 3)
+    lens = torch.zeros(b, dtype=torch.int32, device=DEV)
+    lens[:6] = torch.tensor(FULL, dtype=torch.int32, device=DEV)
+    K, V = caches(b, heads, n, k, v, dtype)
+    after = torch.zeros_like(lens)
+    m.mqa_project_append_kv_rows(x, P_k, P_v, K, V, lens, after)
+    assert after.tolist() == FULL + [n] * (b - 6) and (K[:6] == 7).all() and (V[:6] == 7).all()
+    K2, V2 = caches(b, heads, n, k, v, dtype)
+    one = (b, n, heads) if heads else (b, n)
+    held = lens.clone()
+    m.mqa_append_kv_rows(K2, V2, torch.ones(*one, k, device=DEV), torch.ones(*one, v, device=DEV), held)
+    assert held.tolist() == FULL + [n] * (b - 6) and (K2[:6] == 7).all() and (V2[:6] == 7).all()
+
+
+@pytest.mark.parametrize("b,d,h,k,v", [(1300, 512, 8, 128, 128), (40, 72, 3, 16, 32)])
+def test_decode_step_to_any_length(m, b, d, h, k, v):
+    """The fused projection of one position per sequence, multi-head: enough rows and columns for the integer kernel, and few."""
+    cap = 3
+    x, P_k, P_v = inputs(b, 1, d, h, k, v, 4)
+    x = x.view(b, d)
+    P_q = torch.randn(h, d, k, device=DEV) * d ** -0.5
+    lens = torch.arange(b, dtype=torch.int32, device=DEV) % (cap + 1)
+    lens[:6] = torch.tensor(FULL, dtype=torch.int32, device=DEV)
+    K, V = caches(b, h, cap, k, v)
+    after = torch.zeros_like(lens)
+    q = m.mqa_project_append_qkv(x, P_q, P_k, P_v, K, V, lens, after)
+    wk, wv = caches(b, h, cap, k, v)
+    new_k, new_v = expected(x.view(b, 1, d), P_k, h)[:, :, 0], expected(x.view(b, 1, d), P_v, h)[:, :, 0]
+    for i, L in enumerate(lens.tolist()):
+        if 0 <= L < cap:
+            wk[i, :, L], wv[i, :, L] = new_k[i], new_v[i]
+    assert torch.equal(K, wk) and torch.equal(V, wv)
+    assert after.tolist() == [L + 1 if 0 <= L < cap else L for L in lens.tolist()]
+    want = torch.stack([x.double() @ P_q[j].double() for j in range(h)], 1)
+    assert float((q.double() - want).abs().max()) < 1e-5
