@@ -18,7 +18,10 @@
 // blocks of 32 positions go through the softmax together: one after the other measured 609, and 178 for the one sequence (one
 // wave per SIMD: nothing else fills the waits).  Storing the next tile between the products: 640 (registers spill).
 // Positions at and beyond a row's limit get the logit -inf; V rows beyond the workgroup's last limit are stored as zeros,
-// so the cache may hold anything there.
+// so the cache may hold anything there.  Before that limit a weight of 0 meets what V holds, and 0 . infinity is not 0: the tiles
+// that not all rows see whole are searched for values that are not finite while they are stored, and a workgroup that
+// finds one computes its rows again position by position.  The search costs 1 % at most (clearing the operands of
+// such positions instead: 2 to 15 %, the product loop has no registers left for the masks).
 #include "common.hpp"
 
 namespace mqa {
@@ -43,6 +46,37 @@ __device__ __forceinline__ floatx16 mfma32(const u32x4& a, const u32x4& b, const
 __device__ __forceinline__ void split_pair(float a, float b, uint32_t& hi, uint32_t& lo) {
   hi = pack_bf16_pair(a, b);
   lo = pack_bf16_pair(a - __uint_as_float(hi << 16), b - __uint_as_float(hi & 0xffff0000u));
+}
+
+// One row by one wave in plain float32 over the positions below its limit: a lane has a position of 64 for the
+// logits, then two columns for the weighted sum.
+__device__ __forceinline__ void plain_row(const DecodeParams& p, int seq, int row, int lim, int lane) {
+  const float* q = p.q + ((size_t)seq * p.G + row) * 128;
+  const uint16_t* K = static_cast<const uint16_t*>(p.K) + (size_t)seq * p.cap * 128;
+  const uint32_t* V = static_cast<const uint32_t*>(p.V) + (size_t)seq * p.cap * 64;
+  float m = -INFINITY, l = 0.f, a = 0.f, b = 0.f;
+  for (int p0 = 0; p0 < lim; p0 += 64) {
+    const int n = min(64, lim - p0);
+    float z = -INFINITY;
+    if (lane < n) {
+      z = 0.f;
+      for (int c = 0; c < 128; ++c) z = fmaf(q[c] * p.qscale, bf16_bits_to_float(K[(size_t)(p0 + lane) * 128 + c]), z);
+    }
+    const float mnew = fmaxf(m, wave_max(z)), ref = mnew == -INFINITY ? 0.f : mnew;
+    const float w = lane < n ? __builtin_amdgcn_exp2f(z - ref) : 0.f, alpha = __builtin_amdgcn_exp2f(m - ref);
+    l = l * alpha + wave_sum(w);
+    a *= alpha;
+    b *= alpha;
+    m = mnew;
+    for (int j = 0; j < n; ++j) {
+      const uint32_t v = V[(size_t)(p0 + j) * 64 + lane];
+      const float x = __shfl(w, j);
+      a = fmaf(x, bf16_bits_to_float(v & 0xffffu), a);
+      b = fmaf(x, __uint_as_float(v & 0xffff0000u), b);
+    }
+  }
+  const float inv = l > 0.f ? 1.0f / l : 0.f;                // (a row with nothing to see: zeros)
+  *reinterpret_cast<float2*>(p.o + ((size_t)seq * p.G + row) * 128 + 2 * lane) = make_float2(a * inv, b * inv);
 }
 
 __global__ __launch_bounds__(256, 2)
@@ -70,7 +104,10 @@ void prompt_kernel(DecodeParams p) {
   auto limit = [&](int row) { return max(0, L - nq + min(row, G - 1) / h + 1); };
   const int lim = limit(row0 + i32), lim_min = limit(row0), lim_max = limit(row0 + 31);
   const int end = limit(row_block * 128 + 127);              // of the workgroup
+  const int lim_first = limit(row_block * 128);              // its first row's
   const int ntiles = (end + kTilePos - 1) / kTilePos;
+  int* const any_odd = reinterpret_cast<int*>(smem + 2 * kBuffer);
+  int odd = 0;                                               // V holds something not finite that not all rows see
 
   // ---- staging: K chunk x = tid + 256 j (row x / 16, 16-byte chunk x % 16), kept at chunk ^ (row & 15); V rows 4 quad .. + 3,
   // columns 8 cg .. + 7, transposed.  V^T: 16-byte chunk (u, t, g) of column c at chunk ^ ((c >> 3) ^ c) & 7
@@ -91,10 +128,15 @@ void prompt_kernel(DecodeParams p) {
       const int x = tid + 256 * j, row = x >> 4;
       *reinterpret_cast<u32x4*>(kb + row * kRowBytes + (((x & 15) ^ (row & 15)) << 4)) = kst[j];
     }
-    if ((t + 1) * kTilePos > end) {            // rows past the last limit may hold anything
+    if ((t + 1) * kTilePos > lim_first) {      // rows past the last limit may hold anything
+      uint32_t most = 0;
 #pragma unroll
-      for (int j = 0; j < 4; ++j)
+      for (int j = 0; j < 4; ++j) {
         if (t * kTilePos + 4 * quad + j >= end) vst[j] = u32x4{0u, 0u, 0u, 0u};
+#pragma unroll
+        for (int w = 0; w < 4; ++w) most = max(most, max(vst[j][w] & 0x7fff0000u, vst[j][w] << 16 & 0x7fff0000u));
+      }
+      if (__any(most >= 0x7f800000u)) odd = 1;
     }
     unsigned char* vb = kb + kKBytes + 8 * v_half;
 #pragma unroll
@@ -109,6 +151,7 @@ void prompt_kernel(DecodeParams p) {
   };
 
   load_tile(0);
+  if (tid == 0) *any_odd = 0;
   // ---- q as B operands: lane (i, g) holds elements 16 s + 8 g .. + 7 of row i
   u32x4 qh[8], ql[8];
   {
@@ -218,8 +261,14 @@ void prompt_kernel(DecodeParams p) {
       store_tile(t + 1);
       load_tile(t + 2);
     }
+    if (odd) *any_odd = 1;
     if (sees) { logits(t); weigh(t); }
     __syncthreads();
+  }
+
+  if (__builtin_expect(*any_odd, 0)) {
+    for (int row = row0; row < min(row0 + 32, G); ++row) plain_row(p, seq, row, limit(row), lane);
+    return;
   }
 
   // ---- output: through the wave's quarter of LDS, so that rows leave as whole lines.  acc[cb][e] is column 32 cb + 8 (e / 4)
@@ -246,7 +295,16 @@ void prompt_kernel(DecodeParams p) {
 hipError_t launch_prompt(const DecodeParams& p, hipStream_t st) {
   const long long nblocks = (long long)p.nseq * p.HG;        // HG: blocks of 128 rows
   if (nblocks > 0x7fffffffll) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(prompt_kernel, dim3((unsigned)nblocks), dim3(256), 2 * kBuffer, st, p);
+  constexpr int lds = 2 * kBuffer + 16;
+  static bool done[64] = {};                   // once per device
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) dev = 0;
+  if (!done[dev]) {
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(prompt_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    if (e != hipSuccess) return e;
+    done[dev] = true;
+  }
+  hipLaunchKernelGGL(prompt_kernel, dim3((unsigned)nblocks), dim3(256), lds, st, p);
   return hipGetLastError();
 }
 

@@ -82,3 +82,40 @@ def test_prompt_rescaling(m):
     got = m.mqa_prefill_attention(q, K, V, torch.tensor([cap], dtype=torch.int32, device=DEV))
     for j in range(2):      # logits up to 150
         assert float((got[0, :, j].double() - causal(q[0, :, j], K[0], V[0], cap)).abs().max()) < 1e-2
+
+
+@pytest.mark.parametrize("multi_head", [False, True])
+@pytest.mark.parametrize("n,h,prefix,at", [
+    (200, 8, 0, 23),       # inside a wave's 32 rows
+    (200, 8, 30, 200),
+    (150, 3, 5, 154),      # the last position
+    (300, 1, 0, 40),
+    (300, 1, 17, 129),
+])
+@pytest.mark.parametrize("value", [float("inf"), float("nan")])
+def test_prompt_values_that_are_not_finite(m, multi_head, n, h, prefix, at, value):
+    """A V row that is not finite reaches the rows that see its position and no others, also inside a block of rows."""
+    g = torch.Generator(device=DEV)
+    g.manual_seed(n + h + at)
+    cap = n + prefix
+    if multi_head:
+        q = torch.randn(1, h, n, 128, generator=g, device=DEV) * 0.25
+        K = torch.randn(1, h, cap, 128, generator=g, device=DEV).to(torch.bfloat16)
+        V = torch.randn(1, h, cap, 128, generator=g, device=DEV).to(torch.bfloat16)
+    else:
+        q = torch.randn(1, n, h, 128, generator=g, device=DEV) * 0.25
+        K = torch.randn(1, cap, 128, generator=g, device=DEV).to(torch.bfloat16)
+        V = torch.randn(1, cap, 128, generator=g, device=DEV).to(torch.bfloat16)
+    V[..., at, :] = value
+    attend = m.mha_prefill_attention if multi_head else m.mqa_prefill_attention
+    got = attend(q, K, V, torch.tensor([cap], dtype=torch.int32, device=DEV))
+    clean = V.clone()
+    clean[..., at, :] = 0
+    first = at - prefix                       # the first query that sees position `at`
+    for j in range(h):
+        o = got[0, j] if multi_head else got[0, :, j]
+        Kj, Vj = (K[0, j], clean[0, j]) if multi_head else (K[0], clean[0])
+        qj = q[0, j] if multi_head else q[0, :, j]
+        want = causal(qj, Kj, Vj, cap)
+        assert float((o[:first].double() - want[:first]).abs().max()) < TOL
+        assert not torch.isfinite(o[first:]).any()
