@@ -148,6 +148,16 @@ int mqa_project_append_kv_rows(const float* x, const float* P_k, const float* P_
                                int k, int v, mqa_dtype dt, void* stream);
 
 /*
+ * Which kernel a projection takes (on the host; nothing is launched).  mqa_project_plan: the edge (32, 64, 128, 256) of the
+ * tiles of the split-operand kernel that mqa_project_qkvo(_ex) uses for this product, or 0 for the float32 (new K / V rows:
+ * float64) kernel.  mqa_project_kv_plan: 1 if the K / V rows of mqa_project_memory_kv and mqa_project_append_kv_rows
+ * (h = 0; rows = b*m, b*n) or of mqa_project_append_qkv (h heads of q; rows = b) come from integer products, 0 if
+ * from float64 ones (the same values).  Negative: -(the status the call itself would return for the sizes).
+ */
+int mqa_project_plan(mqa_proj_mode mode, int rows, int d, int h, int kv);
+int mqa_project_kv_plan(int rows, int d, int h, int h_kv, int k, int v, mqa_dtype dt);
+
+/*
  * Encoder-decoder ("memory") attention: the one-query-against-a-memory form of the paper's
  * Section 2.2 listing under the Section 3 rule (K, V, P_k, P_v lose the heads dimension) -- the
  * attention kind that, with the two self-attentions, Section 4.1 converts to multi-query.  The

@@ -17,7 +17,7 @@ MQA_PROJ_Q, MQA_PROJ_KV, MQA_PROJ_KV_MH, MQA_PROJ_O, MQA_PROJ_LINEAR = 0, 1, 2, 
 MQA_EPI_STORE, MQA_EPI_RELU, MQA_EPI_ADD = 0, 1, 2
 
 EXPORTS = [
-    "mqa_project_qkvo", "mqa_project_qkvo_ex", "mqa_project_append_qkv", "mqa_project_append_kv_rows", "mqa_append_kv", "mqa_decode_step", "mha_decode_step",
+    "mqa_project_qkvo", "mqa_project_qkvo_ex", "mqa_project_append_qkv", "mqa_project_append_kv_rows", "mqa_project_plan", "mqa_project_kv_plan", "mqa_append_kv", "mqa_decode_step", "mha_decode_step",
     "mqa_decode_step_window", "mha_decode_step_window", "mqa_append_kv_rows", "mqa_prefill_attention", "mha_prefill_attention",
     "mqa_decode_step_beams", "mqa_decode_beams_workspace_bytes", "mqa_beam_reorder_kv", "mqa_decode_step_ex", "mha_decode_step_ex", "mqa_decode_partials", "mqa_decode_combine",
     "mqa_decode_workspace_bytes", "mha_decode_workspace_bytes", "mqa_decode_workspace_bytes_default", "mqa_decode_num_splits",
@@ -56,6 +56,8 @@ def load_library(path: str = LIB_PATH):
     lib.mqa_project_qkvo_ex.argtypes = [ci, vp, vp, vp, ci, ci, ci, ci, ci, vp]
     lib.mqa_project_append_qkv.argtypes = [vp] * 9 + [ci] * 8 + [vp]
     lib.mqa_project_append_kv_rows.argtypes = [vp] * 7 + [ci] * 8 + [vp]
+    lib.mqa_project_plan.argtypes = [ci] * 5
+    lib.mqa_project_kv_plan.argtypes = [ci] * 7
     lib.mqa_append_kv.argtypes = [vp, vp, vp, vp, vp, ci, ci, ci, ci, ci, ci, vp]
     lib.mqa_project_memory_kv.argtypes = [vp] * 7 + [ci] * 8 + [vp]
     lib.mqa_memory_decode_step.argtypes = [vp, vp, vp, vp, vp, ci, ci, ci, ci, ci, ci, ci, cf, vp, sz, vp]
@@ -377,6 +379,16 @@ def mqa_project_append_qkv(x, P_q, P_k, P_v, K, V, lens_in, lens_out, q=None, st
     if rc != 0:
         raise MqaError("mqa_project_append_qkv", rc)
     return q
+
+
+def mqa_project_plan(mode, rows, d, h, kv) -> int:
+    """The edge of the split-operand kernel's tiles that mqa_project_qkvo uses for this product, or 0 (see mqa.h)."""
+    return load_library().mqa_project_plan(int(mode), rows, d, h, kv)
+
+
+def mqa_project_kv_plan(rows, d, h, h_kv, k, v, dt) -> int:
+    """1 if the new K / V rows of this call come from integer products, 0 if from float64 ones (see mqa.h)."""
+    return load_library().mqa_project_kv_plan(rows, d, h, h_kv, k, v, int(dt))
 
 
 def mqa_project_append_kv_rows(x, P_k, P_v, K, V, lens_in, lens_out, stream=None):

@@ -558,6 +558,19 @@ int mqa_project_append_qkv(const float* x, const float* P_q, const float* P_k, c
   return MQA_OK;
 }
 
+int mqa_project_plan(mqa_proj_mode mode, int rows, int d, int h, int kv) {
+  if ((int)mode < 0 || (int)mode > 4) return -MQA_ERR_DTYPE;
+  if (mode == MQA_PROJ_KV || mode == MQA_PROJ_LINEAR) h = 1;
+  if (rows <= 0 || d <= 0 || h <= 0 || kv <= 0 || (d & 7) || (kv & 7)) return -MQA_ERR_SHAPE;
+  return (mode == MQA_PROJ_KV || mode == MQA_PROJ_KV_MH) ? 0 : gemm_form(mode, rows, d, h, kv, 0);
+}
+
+int mqa_project_kv_plan(int rows, int d, int h, int h_kv, int k, int v, mqa_dtype dt) {
+  if (dt != MQA_F32 && dt != MQA_BF16) return -MQA_ERR_DTYPE;
+  if (rows <= 0 || d <= 0 || h < 0 || h_kv <= 0 || k <= 0 || v <= 0 || (d & 7) || (k & 15) || (v & 15)) return -MQA_ERR_SHAPE;
+  return dt == MQA_BF16 && (h == 0 || gemm_form(MQA_PROJ_Q, rows, d, h, k, kApart)) && project_kv_exact_pays(rows, d, h_kv, k, v);
+}
+
 int mqa_project_append_kv_rows(const float* x, const float* P_k, const float* P_v, void* K, void* V,
                                const int32_t* lens_in, int32_t* lens_out, int b, int n, int d, int h_kv, int cap,
                                int k, int v, mqa_dtype dt, void* stream) {

@@ -118,6 +118,8 @@ hipError_t launch_project(int mode, const float* in, const float* P, float* out,
                           int rows, int d, int h, int kv, int epilogue, hipStream_t st);
 
 // gemm.hip: the same GEMM for large row counts / wide outputs (hipErrorNotSupported: too small, use launch_project's own kernel)
+int gemm_form(int mode, int rows, int d, int h, int kv, int apart);      // the edge of its tiles; 0: not this kernel
+constexpr int kApart = 4;      // `apart` of the fused q/K/V projection, us: a launch of its own for q
 hipError_t launch_gemm_tiled(int mode, const float* in, const float* P, float* out,
                              int rows, int d, int h, int kv, int epilogue, int apart, hipStream_t st);
 hipError_t launch_project_qkv_append(const float* x, const float* P_q, const float* P_k, const float* P_v,
@@ -127,6 +129,7 @@ hipError_t launch_project_qkv_append(const float* x, const float* P_q, const flo
 
 // project_kv.hip: the new K / V rows of many positions into a bf16 cache (n rows per sequence; append: behind the
 // lens_in[] rows already there, else lens_in[] valid rows from position 0 on; hipErrorNotSupported: too few)
+bool project_kv_exact_pays(int rows, int d, int h_kv, int k, int v);
 hipError_t launch_project_kv_exact(const float* x, const float* P_k, const float* P_v, void* K, void* V,
                                    const int32_t* lens_in, int32_t* lens_out, int rows, int n, int append, int d, int h_kv,
                                    int cap, int k, int v, hipStream_t st);

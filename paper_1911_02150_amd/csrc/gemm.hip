@@ -374,7 +374,6 @@ bool split_fits(bool outp, int d, int h, int kv, int tile, int stage) {
 template <bool KC, int BM, int BN, int WR, int WC, int KG, int PD>
 hipError_t launch_split(const float* in, const float* P, float* out, int rows, int d, int h, int kv, int N,
                         int epilogue, hipStream_t st) {
-  if (!split_fits(KC, d, h, kv, BM, 16 * KG)) return hipErrorNotSupported;
   constexpr size_t lds = SplitTile<BM, BN, BN / WC / 32, KG>::BYTES;       // 70 KiB
   auto kern = gemm_split_kernel<KC, BM, BN, WR, WC, KG, PD>;
   static bool done[64] = {};
@@ -394,8 +393,8 @@ hipError_t launch_split(const float* in, const float* P, float* out, int rows, i
 
 }  // namespace
 
-// Returns hipErrorNotSupported when the split-contraction kernel of project.hip is the faster one (the caller
-// then uses it); `apart` is what a launch of its own costs the caller more (us).
+// The edge of the tiles that a product takes here; 0 where the split-contraction kernel of project.hip is the faster one
+// or the offsets do not fit.  `apart` is what a launch of its own costs the caller more (us).
 // The forms differ in how they fill the chip and in what a staged byte is worth.  Measured, us = 5 + C / 1024 times
 //   32 x 32 tiles: 5.7 up to 256 of them, 10.5 for each 512 (two per compute unit)     128 x 1024 x 4096 (C = 1024): 15
 //   64 x 64:       12                     22.5                                         1024 x 1024 x 1024: 17, 2048 x 2048: 50
@@ -404,8 +403,7 @@ hipError_t launch_split(const float* in, const float* P, float* out, int rows, i
 // and the split-contraction kernel on float32 instructions 5 (less below C = 1024, in proportion) + 2 rows N C / 64
 // TFLOP/s (80 with n contiguous): 128 x 512 x 4096: 9.1 (32 x 32 tiles 10.6); 128 x 1024 x 1024: 9.2; 128 x 4096 x 1024, long sums and few tiles: 24, 32 x 32 tiles 26; 1024 x 1024 x 1024: 32; 768 x
 // 4096 x 1024: 104, 64 x 64 tiles 50.
-hipError_t launch_gemm_tiled(int mode, const float* in, const float* P, float* out,
-                             int rows, int d, int h, int kv, int epilogue, int apart, hipStream_t st) {
+int gemm_form(int mode, int rows, int d, int h, int kv, int apart) {
   const bool outp = (mode == 3);
   const int N = outp ? d : h * kv;
   const double C = outp ? (double)h * kv : (double)d;
@@ -417,15 +415,27 @@ hipError_t launch_gemm_tiled(int mode, const float* in, const float* P, float* o
   for (int f = 1; f < 4; ++f)
     if (w[f] < w[best]) best = f;
   const double split_contraction = (C < 1024. ? 5. * C / 1024. : 5.) + 2. * ((rows + 15) / 16 * 16) * N * C / (outp ? 64e6 : 80e6);
-  if (5. + apart + C / 1024. * w[best] > 0.9 * split_contraction) return hipErrorNotSupported;
+  if (5. + apart + C / 1024. * w[best] > 0.9 * split_contraction) return 0;
+  const int edge = 32 << best;
+  return split_fits(outp, d, h, kv, edge, 16 * (256 / edge)) ? edge : 0;
+}
+
+// hipErrorNotSupported: no form (gemm_form); the caller then uses the split-contraction kernel
+hipError_t launch_gemm_tiled(int mode, const float* in, const float* P, float* out,
+                             int rows, int d, int h, int kv, int epilogue, int apart, hipStream_t st) {
+  const bool outp = (mode == 3);
+  const int N = outp ? d : h * kv;
 #define MQA_SPLIT(BM, WR, WC, KG, PD) \
   return outp ? launch_split<true, BM, BM, WR, WC, KG, PD>(in, P, out, rows, d, h, kv, N, epilogue, st) \
               : launch_split<false, BM, BM, WR, WC, KG, PD>(in, P, out, rows, d, h, kv, N, epilogue, st)
-  if (best == 0) MQA_SPLIT(32, 1, 1, 8, 1);
-  if (best == 1) MQA_SPLIT(64, 2, 1, 4, 1);
-  if (best == 2) MQA_SPLIT(128, 2, 2, 2, 3);
-  MQA_SPLIT(256, 4, 2, 1, 1);
+  switch (gemm_form(mode, rows, d, h, kv, apart)) {
+    case 32: MQA_SPLIT(32, 1, 1, 8, 1);
+    case 64: MQA_SPLIT(64, 2, 1, 4, 1);
+    case 128: MQA_SPLIT(128, 2, 2, 2, 3);
+    case 256: MQA_SPLIT(256, 4, 2, 1, 1);
+  }
 #undef MQA_SPLIT
+  return hipErrorNotSupported;
 }
 
 }  // namespace mqa

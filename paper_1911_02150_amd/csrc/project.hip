@@ -309,7 +309,6 @@ void project_qkv_append_kernel(const float* __restrict__ x, const float* __restr
 // (16x64), multi-head 1024 x 3072: 21.8 -> 17.6 (32x64).  A second row block only pays when it
 // holds real rows (rows > 16).  32x32 MFMA blocks (T = 32, which gemm_tile also supports) were
 // slower than these at every such shape (1024 x 4096: 21.4) and are not instantiated.
-constexpr int kApart = 4;      // us: a launch of its own for q
 struct Tile { int RB, CB; };
 static inline long long tiles_of(const Tile& t, long long ncols, int rows) {
   const long long tm = t.RB * 16, tn = t.CB * 16;

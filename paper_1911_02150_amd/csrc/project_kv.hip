@@ -331,26 +331,31 @@ void project_kv_exact_kernel(KvParams p) {
 
 }  // namespace
 
+// Is this kernel the faster one?  Rounds of one tile per compute unit, 100 us each at d = 1024, against the float64 kernel's
+// 42 TFLOP/s: pays from about 140 tiles on (at 256: 105 against 210 us)
+static long long tiles_n_of(int h_kv, int kv) { return ((long long)h_kv * kv + kTile - 1) / kTile; }
+bool project_kv_exact_pays(int rows, int d, int h_kv, int k, int v) {
+  if (d > kMaxC || (k & 1) || (v & 1)) return false;
+  const long long tiles = (rows + kTile - 1) / kTile * (tiles_n_of(h_kv, k) + tiles_n_of(h_kv, v));
+  const double exact_us = 5. + 100. * d / 1024. * (double)((tiles + 255) / 256);
+  const double f64_us = 5. + 2. * rows * ((double)h_kv * k + (double)h_kv * v) * d / 42e6;
+  return exact_us <= 0.9 * f64_us;
+}
+
 hipError_t launch_project_kv_exact(const float* x, const float* P_k, const float* P_v, void* K, void* V,
                                    const int32_t* lens_in, int32_t* lens_out, int rows, int n, int append, int d, int h_kv,
                                    int cap, int k, int v, hipStream_t st) {
-  if (d > kMaxC || (k & 1) || (v & 1)) return hipErrorNotSupported;
+  if (!project_kv_exact_pays(rows, d, h_kv, k, v)) return hipErrorNotSupported;
   KvParams p = {};
   p.x = x; p.P[0] = P_k; p.P[1] = P_v;
   p.dst[0] = (uint16_t*)K; p.dst[1] = (uint16_t*)V;
   p.lens_in = lens_in; p.lens_out = lens_out;
   p.rows = rows; p.C = d; p.h_kv = h_kv; p.cap = cap; p.n = n; p.append = append;
   p.kv[0] = k; p.kv[1] = v;
-  const long long nk = (long long)h_kv * k, nv = (long long)h_kv * v;
-  p.tiles[0] = (int)((nk + kTile - 1) / kTile);
-  p.tiles[1] = (int)((nv + kTile - 1) / kTile);
+  p.tiles[0] = (int)tiles_n_of(h_kv, k);
+  p.tiles[1] = (int)tiles_n_of(h_kv, v);
   p.tiles_m = (rows + kTile - 1) / kTile;
   const long long tiles = (long long)p.tiles_m * (p.tiles[0] + p.tiles[1]);
-  // Rounds of one tile per compute unit, 100 us each at d = 1024, against the float64 kernel's 42 TFLOP/s: pays from
-  // about 140 tiles on (at 256: 105 against 210 us)
-  const double exact_us = 5. + 100. * d / 1024. * (double)((tiles + 255) / 256);
-  const double f64_us = 5. + 2. * rows * (double)(nk + nv) * d / 42e6;
-  if (exact_us > 0.9 * f64_us) return hipErrorNotSupported;
   constexpr size_t lds = 2 * kStage + 1280 * 4 + 16;
   static bool done[64] = {};
   int dev = 0;

@@ -48,8 +48,14 @@ def caches(b, heads, cap, k, v, dtype=torch.bfloat16):
 
 # rows and columns past whole tiles of 128, contraction tails of 8 and of 24 in a stage of 32, heads inside a column tile;
 # the last two are too small for the integer kernel
-SHAPES = [(64, 300, 1000, 0, 128, 128), (23, 811, 72, 0, 128, 64), (40, 500, 88, 5, 48, 80), (70, 257, 520, 2, 256, 16),
+SHAPES = [(64, 300, 1000, 0, 128, 128), (46, 811, 72, 0, 128, 64), (40, 500, 88, 5, 48, 80), (70, 257, 520, 2, 256, 16),
           (3, 40, 512, 0, 128, 128), (2, 9, 72, 3, 16, 32)]
+
+
+def test_shapes_take_the_kernel_they_are_for(m):
+    taken = [m.mqa_project_kv_plan(b * n, d, 0, heads or 1, k, v, m.MQA_BF16) for b, n, d, heads, k, v in SHAPES]
+    assert taken == [1, 1, 1, 1, 0, 0]
+    assert m.mqa_project_kv_plan(64 * 300, 1000, 0, 1, 128, 128, m.MQA_F32) == 0
 
 
 @pytest.mark.parametrize("b,n,d,heads,k,v", SHAPES)
@@ -92,6 +98,7 @@ def test_append_rows(m, b, n, d, heads, k, v, dtype):
 def test_rows_of_any_values(m):
     """Zeros, ties, wide ranges inside a row and a column, sums that cancel, subnormals, infinities and NaN."""
     b, n, d = 64, 300, 200
+    assert m.mqa_project_kv_plan(b * n, d, 0, 1, 128, 128, m.MQA_BF16) == 1
     x, P_k, P_v = inputs(b, n, d, 0, 128, 128, 9)
     x[0, :40] = 0
     x[1, 3], x[1, 4] = x[1, 3].abs() * 1e30, x[1, 4] * 1e-30
@@ -121,6 +128,7 @@ def test_sums_around_a_power_of_two(m, sign):
     """Sums that end just above and just below 2^42, whose error bound (what the fixed point drops of the values beside one
     of 1.25 . 2^30) reaches the nearest tie: below the power of two the ties lie half as far apart."""
     b, n, d, big = 64, 512, 8, 1.25 * 2.0 ** 30
+    assert m.mqa_project_kv_plan(b * n, d, 0, 1, 128, 128, m.MQA_BF16) == 1
     x = torch.tensor([big] * 4 + [-0.99] * 3 + [0.0], device=DEV).repeat(b, n, 1)
     x[..., 7] = torch.linspace(3262, 3302, b * n, device=DEV).view(b, n)
     x[::2, :, 7] = x[::2, :, 7].floor()
@@ -155,10 +163,11 @@ def test_append_to_any_length(m, b, n, d, heads, k, v, dtype):
     assert held.tolist() == FULL + [n] * (b - 6) and (K2[:6] == 7).all() and (V2[:6] == 7).all()
 
 
-@pytest.mark.parametrize("b,d,h,k,v", [(1300, 512, 8, 128, 128), (40, 72, 3, 16, 32)])
-def test_decode_step_to_any_length(m, b, d, h, k, v):
+@pytest.mark.parametrize("b,d,h,k,v,integer", [(1300, 1024, 8, 128, 128, 1), (40, 72, 3, 16, 32, 0)])
+def test_decode_step_to_any_length(m, b, d, h, k, v, integer):
     """The fused projection of one position per sequence, multi-head: enough rows and columns for the integer kernel, and few."""
     cap = 3
+    assert m.mqa_project_kv_plan(b, d, h, h, k, v, m.MQA_BF16) == integer
     x, P_k, P_v = inputs(b, 1, d, h, k, v, 4)
     x = x.view(b, d)
     P_q = torch.randn(h, d, k, device=DEV) * d ** -0.5

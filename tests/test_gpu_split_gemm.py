@@ -36,24 +36,36 @@ def bound(x, W):
     return (0.1875 * x.shape[1] + 12) * 2.0 ** -24 * (a @ b) + small
 
 
+def tiles_of(m, layout, rows, C, N):
+    """The edge of the tiles that `product` takes for these sizes; 0: another kernel."""
+    if layout == "n":
+        return m.mqa_project_plan(m.MQA_PROJ_LINEAR, rows, C, 1, N)
+    kv = 128 if C % 128 == 0 else C
+    return m.mqa_project_plan(m.MQA_PROJ_O, rows, N, C // kv, kv)
+
+
 SIZES = [
-    # rows, C, N                            tiles
-    (128, 1024, 24584),      # 128 x 128: one tile row, 8 columns in the last tile column
-    (1601, 72, 2056),        # 128 x 128: one row in the last tile, contraction tail of 8 in a stage of 32
-    (1600, 8, 2048),         # 128 x 128: fewer indices than a stage
-    (4096, 1024, 4096),      # 256 x 256: whole tiles only
-    (4097, 136, 4104),       # 256 x 256: one row, eight columns in the last tiles, tail of 8 in a stage of 16
-    (16000, 40, 1024),       # 256 x 256: tile rows that do not fill a band of eight
-    (500, 1000, 1000),       # 32 x 32: last tiles of 20 rows and 8 columns, 104 indices in the last stage
-    (129, 1024, 4104),       # 32 x 32: one row, eight columns in the last tiles
-    (1001, 1000, 1000),      # 64 x 64: 41 rows, 40 columns, 40 indices in the last stage
-    (768, 4096, 1024),       # 64 x 64: whole tiles only
+    # tiles, rows, C, N
+    (128, 128, 1024, 24584),     # one tile row, 8 columns in the last tile column
+    (128, 1601, 136, 2056),      # one row, eight columns in the last tiles, tail of 8 in a stage of 32
+    (256, 12000, 8, 4104),       # fewer indices than a stage of 16, a last tile of 8 columns (shorter products of the other edges
+                                 # are left to the split-contraction kernel)
+    (256, 4096, 1024, 4096),     # whole tiles only
+    (256, 4097, 136, 4104),      # one row, eight columns in the last tiles, tail of 8 in a stage of 16
+    (256, 16000, 40, 1024),      # tile rows that do not fill a band of eight
+    (32, 500, 1000, 1000),       # last tiles of 20 rows and 8 columns, 104 indices in the last stage
+    (32, 225, 1000, 2024),       # one row, eight columns in the last tiles
+    (64, 129, 1024, 4104),       # one row, eight columns in the last tiles
+    (64, 1001, 1000, 1000),      # 41 rows, 40 columns, 40 indices in the last stage
+    (64, 768, 4096, 1024),       # whole tiles only
 ]
+EDGES = [(128, 1601, 136, 2056), (256, 4097, 136, 4104), (32, 500, 1000, 1000), (64, 1001, 1000, 1000)]
 
 
 @pytest.mark.parametrize("layout", ["n", "c"])
-@pytest.mark.parametrize("rows,C,N", SIZES)
-def test_split_gemm(m, layout, rows, C, N):
+@pytest.mark.parametrize("tiles,rows,C,N", SIZES)
+def test_split_gemm(m, layout, tiles, rows, C, N):
+    assert tiles_of(m, layout, rows, C, N) == tiles
     g = torch.Generator(device=DEV)
     g.manual_seed(rows + C + N)
     x = torch.randn(rows, C, generator=g, device=DEV) * torch.exp(3 * torch.randn(rows, 1, generator=g, device=DEV))
@@ -68,9 +80,10 @@ def test_split_gemm(m, layout, rows, C, N):
 
 
 @pytest.mark.parametrize("layout", ["n", "c"])
-@pytest.mark.parametrize("rows,C,N", [(1601, 72, 2056), (4097, 136, 4104), (500, 1000, 1000), (1001, 1000, 1000)])
-def test_split_gemm_scales(m, layout, rows, C, N):
+@pytest.mark.parametrize("tiles,rows,C,N", EDGES)
+def test_split_gemm_scales(m, layout, tiles, rows, C, N):
     """Lines that begin with zeros or with values far from those that follow: the scales are set a second time."""
+    assert tiles_of(m, layout, rows, C, N) == tiles
     g = torch.Generator(device=DEV)
     g.manual_seed(7)
     x = torch.randn(rows, C, generator=g, device=DEV)
@@ -89,9 +102,10 @@ def test_split_gemm_scales(m, layout, rows, C, N):
 
 
 @pytest.mark.parametrize("layout", ["n", "c"])
-@pytest.mark.parametrize("rows,C,N", [(1601, 72, 2056), (4097, 136, 4104), (500, 1000, 1000), (1001, 1000, 1000)])
-def test_split_gemm_values_without_a_split(m, layout, rows, C, N):
+@pytest.mark.parametrize("tiles,rows,C,N", EDGES)
+def test_split_gemm_values_without_a_split(m, layout, tiles, rows, C, N):
     """Infinities, NaN, the largest floats (their first term would round to infinity) and overflowing outputs."""
+    assert tiles_of(m, layout, rows, C, N) == tiles
     g = torch.Generator(device=DEV)
     g.manual_seed(5)
     x = torch.randn(rows, C, generator=g, device=DEV)
@@ -114,12 +128,13 @@ def test_split_gemm_values_without_a_split(m, layout, rows, C, N):
 
 
 @pytest.mark.parametrize("kv", [8, 24, 72])
-@pytest.mark.parametrize("rows,width", [(500, 1000), (1001, 1000), (4096, 1024), (4096, 4096)])
-def test_split_gemm_small_heads(m, kv, rows, width):
+@pytest.mark.parametrize("tiles,rows,width", [(32, 512, 1024), (64, 1001, 1000), (128, 4096, 1024), (256, 4096, 4096)])
+def test_split_gemm_small_heads(m, kv, tiles, rows, width):
     """Column tiles (q) and stages of the contraction (output) that reach over several heads, in every tile size."""
     g = torch.Generator(device=DEV)
     g.manual_seed(kv + rows)
     h = width // kv
+    assert m.mqa_project_plan(m.MQA_PROJ_Q, rows, width, h, kv) == m.mqa_project_plan(m.MQA_PROJ_O, rows, width, h, kv) == tiles
     x = torch.randn(rows, width, generator=g, device=DEV)
     P = torch.randn(h, width, kv, generator=g, device=DEV)
     W = P.permute(1, 0, 2).reshape(width, h * kv)
