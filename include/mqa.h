@@ -101,8 +101,12 @@ typedef struct {
  * out, float32 accumulation -- except the new K / V rows (MQA_PROJ_KV, _KV_MH
  * and the K / V part of mqa_project_append_qkv), whose products are summed in
  * float64 and rounded once to float32: what is then rounded into a bf16 cache
- * is the correctly rounded projection, whatever the summation order.  `rows`
- * is the number of input rows (b for a decode step, b*m when projecting a whole
+ * is the correctly rounded projection, whatever the summation order.  Large
+ * products (mqa_project_plan > 0) are formed from two 16-bit terms per operand,
+ * which together hold nearly every value of a row of `in` and of a column of P
+ * to 2^-21 of itself, mostly 2^-23; where a row's or column's values lie too far
+ * apart for that (about 2^11), and for infinities, from the float32 values
+ * themselves.  `rows` is the number of input rows (b for a decode step, b*m when projecting a whole
  * memory M as in the Section 2.2 one-query listing).  `kv` is k or v.  `out` is
  * overwritten.
  */

@@ -186,24 +186,11 @@ __device__ __forceinline__ Split2 split2(float a, float b) {
   s.lo = __builtin_bit_cast(uint32_t, __builtin_convertvector(f2{a - (float)h[0], b - (float)h[1]}, h2));
   return s;
 }
-// The power of two that takes `most` to [2^9, 2^10), and the exponent that takes it back.
-__device__ __forceinline__ float split_scale(float most) {
-  return __uint_as_float((uint32_t)min(254, 263 - (int)(__float_as_uint(most) >> 23)) << 23);
+// The power of two that takes `most` to [2^top, 2^(top + 1)), and the exponent that takes it back.
+__device__ __forceinline__ float split_scale(float most, int top) {
+  return __uint_as_float((uint32_t)min(254, 254 + top - (int)(__float_as_uint(most) >> 23)) << 23);
 }
 __device__ __forceinline__ int split_exponent(float scale) { return 127 - (int)(__float_as_uint(scale) >> 23); }
-
-// out[row][n] of in . B in plain float32, index by index: for the outputs of a split product that
-// are not finite (an infinity, or an overflow).  Ends at the first NaN of its own.
-template <bool B_KCONTIG>
-__device__ __noinline__ float plain_dot(const float* in, const float* P, int row, int n, int d, int h, int kv) {
-  const int C = B_KCONTIG ? h * kv : d;
-  float s = 0.f;
-  for (int c = 0; c < C && s == s; ++c) {
-    const size_t at = B_KCONTIG ? ((size_t)(c / kv) * d + n) * kv + c % kv : ((size_t)(n / kv) * d + c) * kv + n % kv;
-    s = fmaf(in[(size_t)row * C + c], P[at], s);
-  }
-  return s;
-}
 
 __device__ __forceinline__ float wave_max(float x) {
 #pragma unroll

@@ -11,18 +11,23 @@
 // instruction rounds after every second one: the shorter chain of roundings more than pays for the terms.
 // Relative error of a 1024-term sum of normal deviates 3.6e-7 (float32 instructions: 5.7e-7), of a
 // 4096-term one 7.2e-7 (1.15e-6), of a 520-term one 2.7e-7.
-// Scales: one per row of A and per column of B in a tile, such that the largest value among the first
-// stage's comes to [2^9, 2^10): the terms are then full for values down to 2^-11 of it, below that the
-// error is 2^-35 of it.  The largest value is followed through the whole contraction; if one
-// comes to more than 2^15 (or, in a row that began with zeros, all stay below 2^4), the scales are set
-// again from the largest values and the tile is multiplied again.
-// An infinity or NaN has no such split: an output that is not finite is computed again in plain float32.
+// Scales: one per row of A and per column of B in a tile, such that the largest value among its first indices (32 at
+// least) comes to [2^9, 2^10).  A scaled value is held to 2^-23 of itself from 2^-2 on, to 2^-21 from 2^-4 on, and to
+// 2^-25 below: products as good as float32 ones need nearly all values of a line above 2^-4, wherever the line's largest
+// value is and whatever it meets.  So the octets (eight consecutive indices) with a smaller value other than 0 are
+// counted, per line, while they are staged: few may have one (see `holds`).  Where too many have, or a value outgrew
+// the scale, the scales are set again from the largest values of all and, if the counts are right then, the tile is multiplied
+// again; if not (a line whose values lie more than about 2^11 apart, an infinity) it is multiplied on float32 instructions
+// (v_mfma_f32_32x32x2_f32), the values themselves in the place of their two terms.  So are contractions of
+// less than 64, too short to count.  Measured (us, rows = 16384, 1024 x 4096; without the counting / with it / on float32
+// instructions alone): normal deviates 393 / 420 / 1095; one channel 2^6 times the others 735 / 1020 / 1095 (scales set
+// again); 2^12 times 727 / 1660 / 1095 (float32 after that).  Without it the others' part of such sums was lost from 2^14 on.
 //
 // Measured (b=128, n=128 prompt: rows = 16384, TFLOP/s of the float32 product; 128x128 tiles of
-// v_mfma_f32_32x32x2_f32 / three bf16 terms and six products / this): 1024 x 4096: 126 / 224 / 335; 4096 x 1024:
-// 129 / 228 / 340; 1024 x 1024: 122 / 220 / 327; logits of 128 rows 101 / 145 / 200.  That is 1.0 PFLOP/s of fp16
+// v_mfma_f32_32x32x2_f32 / three bf16 terms and six products / this): 1024 x 4096: 126 / 224 / 327; 4096 x 1024:
+// 129 / 228 / 340; 1024 x 1024: 122 / 220 / 322; logits of 128 rows 101 / 145 / 200.  That is 1.0 PFLOP/s of fp16
 // products with the matrix cores busy 51 % of the 1.9 GHz the card runs at under this load (hipBLASLt's 8192^3 bf16
-// product reaches 1.29 here); vector instructions take 30 %, LDS 22 %.  More stages ahead in registers (2, 3), or two
+// product reaches 1.29 here); vector instructions take 30 %, LDS 22 % (counters before the counting of octets).  More stages ahead in registers (2, 3), or two
 // stages per barrier in LDS, measured the same.
 //
 // Workgroup: 512 threads, two waves per SIMD, tile BM x BN, WR x WC waves in each of KG groups; a
@@ -46,8 +51,12 @@ namespace mqa {
 namespace {
 
 typedef __attribute__((ext_vector_type(16))) float floatx16;
+typedef __attribute__((ext_vector_type(4))) float floatx4;
 typedef __attribute__((ext_vector_type(8))) _Float16 halfx8;
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
+
+constexpr int kFirstTop = 9, kLastTop = 14;    // log2 of what the scales take a line's largest value to: in the first stage, of all
+constexpr float kFull = 0.0625f;               // scaled values from here on are held to 2^-21 of themselves, 2^-23 from 2^-2 on
 
 // LDS of a stage, in bytes: per group A's two planes, then B's two planes; a plane is two halves g
 // of 16 bytes per row (A) or slot (B): contraction indices 8g .. 8g+7.  Column n of the tile lives in slot
@@ -62,11 +71,11 @@ template <int BM, int BN, int JB, int KG> struct SplitTile {
   static constexpr int A_PLANE = 2 * A_G, B_PLANE = 2 * B_G;
   static constexpr int GROUP = 2 * (A_PLANE + B_PLANE) + (KG >= 4 ? 32 : KG == 2 ? 64 : 0);
   static constexpr int STAGE = KG * GROUP;
-  // behind the two stages (and, KG > 1, the groups' partial tiles that re-use them): the largest values and
-  // the scales' exponents of the tile's rows and columns, and a flag
+  // behind the two stages (and, KG > 1, the groups' partial tiles that re-use them): the largest values, the scales'
+  // exponents, the counts of short octets and of octets of zeros of the tile's rows and columns, and flags
   static constexpr int PART = KG > 1 ? KG * BM * BN * 4 : 0;
   static constexpr int STATE = 2 * STAGE > PART ? 2 * STAGE : PART;
-  static constexpr int BYTES = STATE + (BM + BN) * 8 + 16;
+  static constexpr int BYTES = STATE + (BM + BN) * 16 + 16;
   static __device__ __host__ constexpr int slot_bytes(int block, int slot) { return block * B_BLOCK + slot * 16; }
   // n contiguous, one column block: even columns in the first half of the slots, odd ones in the second, so
   // that the lanes of a pair of columns each write neighbouring slots
@@ -109,7 +118,9 @@ void gemm_split_kernel(const float* __restrict__ in, const float* __restrict__ P
   const int nst = (C + 16 * KG - 1) / (16 * KG);
   uint32_t* most = reinterpret_cast<uint32_t*>(smem + L::STATE);        // [BM + BN] bits of the largest |value| seen
   int* expo = reinterpret_cast<int*>(most + BM + BN);                   // [BM + BN] the tile holds x . 2^-expo
-  int* again = expo + BM + BN;
+  int* shorts = expo + BM + BN;                                         // [BM + BN] octets with a value that the terms hold in few bits
+  int* zeros = shorts + BM + BN;                                        // [BM + BN] octets of zeros (one stage of them behind the last)
+  int* again = zeros + BM + BN;                                         // [3] something did not fit; what does not in any scale; what did not in the first
 
   // ---- staging: 16 values per thread and stage.  Loads are unconditional (indices past the contraction
   // are clamped and their values zeroed when the last stage is split), so that the compiler can
@@ -118,14 +129,20 @@ void gemm_split_kernel(const float* __restrict__ in, const float* __restrict__ P
   //   B with n contiguous: thread -> columns 2 pair, 2 pair + 1 at the eight indices of an octet
   const int o_row = ts % KO, r_row = ts / KO;
   const int pair = ts % (BN / 2), o_col = ts / (BN / 2);
-  auto run = [&](auto role, auto&& clear, auto&& multiply) {
+  auto run = [&](auto role, auto&& clear, auto&& multiply, auto&& finite) {
     constexpr bool STAGE_A = decltype(role)::value, BY_ROWS = STAGE_A || B_KCONTIG;
     uint32_t* const my_most = most + (STAGE_A ? 0 : BM);
     int* const my_expo = expo + (STAGE_A ? 0 : BM);
+    int* const my_short = shorts + (STAGE_A ? 0 : BM);
+    int* const my_zeros = zeros + (STAGE_A ? 0 : BM);
     int line[2];                               // the thread's two rows of A or columns of B (by their place in LDS)
 #pragma unroll
     for (int i = 0; i < 2; ++i) line[i] = BY_ROWS ? r_row + (256 / KO) * i : 2 * pair + i;
-    float scale[2], peak[2];                   // of these two: the scale, and the largest scaled |value| so far
+    float scale[2];                            // of these two
+    // octets of them with a value that the terms hold in few bits (short), and of zeros; where the scale is not the
+    // line's own also the largest value (every octet is looked at then: suspect)
+    int short_octets[2], zero_octets[2];
+    float peak[2], suspect;
     // a base that is the same in every lane (scalar registers) and a 32-bit offset in bytes of the lane (split_fits)
     const float* base_of = STAGE_A ? in + (size_t)row0 * C : B_KCONTIG ? P + (size_t)n0 * kv : P + (size_t)(n0 / kv) * head_stride + n0 % kv;
     uint32_t src[BY_ROWS ? 2 : 1];
@@ -171,57 +188,81 @@ void gemm_split_kernel(const float* __restrict__ in, const float* __restrict__ P
         for (int i = 0; i < 16; ++i) rg.x[i] = 0.f;
       }
     };
-    auto store_stage = [&](int st, Regs& rg) {
+    // |x| in order, zero last
+    auto order = [](float x) -> uint32_t { return (__float_as_uint(x) << 1) - 2u; };
+    auto count = [&](const Regs& rg) {
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        uint32_t u = ~0u;
+#pragma unroll
+        for (int k = 0; k < 8; ++k) u = min(u, order(value(rg, i, k)));
+        if (suspect > kFull) {
+#pragma unroll
+          for (int k = 0; k < 8; ++k) peak[i] = fmaxf(peak[i], fabsf(value(rg, i, k)));
+        }
+        short_octets[i] += u < order(ldexpf(kFull, split_exponent(scale[i]))) ? 1 : 0;
+        zero_octets[i] += u >= order(0.f) ? 1 : 0;
+      }
+    };
+    auto store_stage = [&](auto plain, int st, Regs& rg) {
       unsigned char* base = smem + (st & 1) * L::STAGE;
       const int octet = BY_ROWS ? o_row : o_col;
       drop_tail(st, rg);
       base += (octet >> 1) * L::GROUP + (octet & 1) * (STAGE_A ? L::A_G : L::B_G) + (STAGE_A ? 0 : 2 * L::A_PLANE);
+      float least[2] = {INFINITY, INFINITY};
 #pragma unroll
       for (int i = 0; i < 2; ++i) {            // two rows / columns of eight indices
         u32x4 t[2];
+        if constexpr (decltype(plain)::value) {      // the values themselves, four in each plane
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          const float a = value(rg, i, 2 * k) * scale[i], b = value(rg, i, 2 * k + 1) * scale[i];
-          peak[i] = fmaxf(peak[i], fmaxf(fabsf(a), fabsf(b)));
-          const Split2 s = split2(a, b);
-          t[0][k] = s.hi; t[1][k] = s.lo;
+          for (int k = 0; k < 8; ++k) t[k >> 2][k & 3] = __float_as_uint(value(rg, i, k));
+        } else {
+#pragma unroll
+          for (int k = 0; k < 4; ++k) {
+            const float a = value(rg, i, 2 * k) * scale[i], b = value(rg, i, 2 * k + 1) * scale[i];
+            least[i] = fminf(least[i], fminf(fabsf(a), fabsf(b)));
+            const Split2 s = split2(a, b);
+            t[0][k] = s.hi; t[1][k] = s.lo;
+          }
         }
         const int at = STAGE_A ? 16 * line[i] : B_KCONTIG ? L::slot_bytes(line[i] / L::QCOLS, line[i] % L::QCOLS) : L::column_at(line[i]);
 #pragma unroll
         for (int p = 0; p < 2; ++p) *reinterpret_cast<u32x4*>(base + p * (STAGE_A ? L::A_PLANE : L::B_PLANE) + at) = t[p];
       }
+      if (!decltype(plain)::value && fminf(least[0], least[1]) < suspect) count(rg);      // (a zero, or one of some ten thousand normal deviates)
     };
     // scales from the largest values known; a line of zeros so far takes the largest of the tile's lines
-    auto set_scales = [&]() {
+    auto set_scales = [&](int top) {
       float whole = 0.f;
 #pragma unroll
       for (int i = 0; i < (STAGE_A ? BM : BN); i += 64) whole = fmaxf(whole, __uint_as_float(my_most[(lane + i) % (STAGE_A ? BM : BN)]));
       whole = wave_max(whole);
+      suspect = kFull;
 #pragma unroll
       for (int i = 0; i < 2; ++i) {
         const float m = __uint_as_float(my_most[line[i]]);
-        scale[i] = split_scale(m > 0.f ? m : whole > 0.f ? whole : 1.f);
+        scale[i] = split_scale(m > 0.f ? m : whole > 0.f ? whole : 1.f, top);
+        if (m == 0.f) suspect = INFINITY;
         my_expo[line[i]] = split_exponent(scale[i]);
+        short_octets[i] = zero_octets[i] = 0;
         peak[i] = 0.f;
       }
     };
+    auto largest = [&](Regs& rg) {             // (into peak)
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int k = 0; k < 8; ++k) peak[i] = fmaxf(peak[i], fabsf(value(rg, i, k)));
+    };
+    auto tell_peaks = [&]() {
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+        if (peak[i] > 0.f) atomicMax(&my_most[line[i]], __float_as_uint(peak[i]));
+    };
     Regs regs[PD];                             // the PD stages after the one in LDS, on their way
-    for (int round = 0;; ++round) {
-      load_stage(0, regs[0]);
-      if (round == 0) {
-        drop_tail(0, regs[0]);
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
-          float m = 0.f;
-#pragma unroll
-          for (int k = 0; k < 8; ++k) m = fmaxf(m, fabsf(value(regs[0], i, k)));
-          atomicMax(&my_most[line[i]], __float_as_uint(m));
-        }
-        __syncthreads();
-      }
-      set_scales();
+    auto sweep = [&](auto plain) {             // (the first stage is in regs[0])
       clear();
-      store_stage(0, regs[0]);
+      store_stage(plain, 0, regs[0]);
 #pragma unroll
       for (int u = 0; u < PD; ++u) {
         load_stage(1 + u, regs[u]);
@@ -233,29 +274,94 @@ void gemm_split_kernel(const float* __restrict__ in, const float* __restrict__ P
         for (int u = 0; u < PD; ++u) {
           const int st = s0 + u;
           if (st >= nst) break;
-          if constexpr (STAGE_A) multiply(st & 1);
-          store_stage(st + 1, regs[u]);
+          if constexpr (STAGE_A) multiply(plain, st & 1);
+          store_stage(plain, st + 1, regs[u]);
           load_stage(st + 1 + PD, regs[u]);
-          if constexpr (!STAGE_A) multiply(st & 1);
+          if constexpr (!STAGE_A) multiply(plain, st & 1);
           __syncthreads();
         }
       }
-      // did the scales fit the whole contraction?  (a scaled value that overflowed is an infinity here: the next
-      // round, with the smallest scale, finds the true largest values for the one after it)
-      if (round == 2) break;
+    };
+    // a line: some value of it is far above what the terms cut off, and few octets (none of up to 7 with anything but zeros,
+    // 2 and an eighth of more) hold a value that is not
+    auto holds = [&](int i) -> bool {
+      const int n = my_short[line[i]], octets = (nst + 1) * KO - my_zeros[line[i]];
+      return n <= (octets < 8 ? 0 : 2 + octets / 8) && (n == 0 || __uint_as_float(my_most[line[i]]) * scale[i] >= 128.f);
+    };
+    bool plain = C < 64;                       // (too few octets to tell)
+    auto tell_counts = [&]() {
 #pragma unroll
-      for (int i = 0; i < 2; ++i) my_most[line[i]] = 0;
+      for (int i = 0; i < 2; ++i) {
+        if (short_octets[i] > 0) atomicAdd(&my_short[line[i]], short_octets[i]);
+        if (zero_octets[i] > 0) atomicAdd(&my_zeros[line[i]], zero_octets[i]);
+      }
+    };
+    auto scan = [&](auto&& look) {             // (a stage of zeros at the end, as in a sweep)
+#pragma unroll 1
+      for (int st = 0; st <= nst; ++st) {
+        load_stage(st, regs[0]);
+        drop_tail(st, regs[0]);
+        look(regs[0]);
+      }
+    };
+    for (int top = kFirstTop; !plain; top = kLastTop) {
+      if (top == kFirstTop) {                  // the first 32 indices at least
+        constexpr int LOOK = KG < 2 ? 2 : 1;
+        peak[0] = peak[1] = 0.f;
+#pragma unroll 1
+        for (int u = LOOK - 1; u >= 0; --u) {
+          load_stage(u, regs[0]);
+          drop_tail(u, regs[0]);
+          largest(regs[0]);
+        }
+        tell_peaks();
+        __syncthreads();
+        set_scales(top);
+      } else {
+        load_stage(0, regs[0]);
+      }
+      sweep(std::false_type{});
+      if (top == kLastTop) break;              // (counted beforehand)
+      // Did the terms hold the lines?  (a scaled value that overflowed leaves nothing finite of its line)
+      if (!finite()) again[0] = 1;
+      tell_counts();
+      tell_peaks();
       __syncthreads();
 #pragma unroll
-      for (int i = 0; i < 2; ++i) atomicMax(&my_most[line[i]], __float_as_uint(ldexpf(peak[i], split_exponent(scale[i]))));
+      for (int i = 0; i < 2; ++i)
+        if (!holds(i)) again[0] = again[2] = 1;
+      __syncthreads();
+      if (__builtin_expect(again[0] == 0, 1)) break;
+      // Would they with the right scales?  The largest values, then the counts
+      peak[0] = peak[1] = 0.f;
+      scan([&](Regs& rg) { largest(rg); });
+      tell_peaks();
+#pragma unroll
+      for (int i = 0; i < 2; ++i) my_short[line[i]] = my_zeros[line[i]] = 0;
       __syncthreads();
 #pragma unroll
       for (int i = 0; i < 2; ++i) {
-        const float m = __uint_as_float(my_most[line[i]]), ms = m * scale[i];
-        if ((ms > 32768.f && (m < INFINITY || scale[i] > split_scale(INFINITY))) || (ms > 0.f && ms < 16.f)) *again = round + 1;
+        const float m = __uint_as_float(my_most[line[i]]);
+        if (!(m * scale[i] < 65520.f)) again[2] = 1;
+        if (m == INFINITY) again[1] = 1;
       }
       __syncthreads();
-      if (*again != round + 1) break;
+      if (!again[2]) break;                    // (a NaN alone, and the outputs are what they were to be)
+      set_scales(kLastTop);
+      scan([&](Regs& rg) { count(rg); });
+      tell_counts();
+      __syncthreads();
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+        if (!holds(i)) again[1] = 1;
+      __syncthreads();
+      plain = again[1];
+    }
+    if (__builtin_expect(plain, 0)) {
+#pragma unroll
+      for (int i = 0; i < 2; ++i) my_expo[line[i]] = 0;
+      load_stage(0, regs[0]);
+      sweep(std::true_type{});
     }
   };
 
@@ -269,17 +375,38 @@ void gemm_split_kernel(const float* __restrict__ in, const float* __restrict__ P
         for (int e = 0; e < 16; ++e) acc[r][j][e] = 0.f;
   };
 
-  auto multiply = [&](int buf) {
+  auto finite = [&]() -> bool {
+    float s = 0.f;
+#pragma unroll
+    for (int r = 0; r < RB; ++r)
+#pragma unroll
+      for (int j = 0; j < JB; ++j)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) s = fmaf(acc[r][j][e], 0.f, s);
+    return s == 0.f;
+  };
+  auto multiply = [&](auto plain, int buf) {
     const unsigned char* As = smem + buf * L::STAGE + kg * L::GROUP + g * L::A_G + (wr * RB * 32 + i32) * 16;
     const unsigned char* Bs = smem + buf * L::STAGE + kg * L::GROUP + 2 * L::A_PLANE + g * L::B_G + L::slot_bytes(0, wc * 32 + i32);
-    halfx8 a[2][RB], b[2][JB];
+    typedef std::conditional_t<decltype(plain)::value, floatx4, halfx8> operand;
+    operand a[2][RB], b[2][JB];
 #pragma unroll
     for (int p = 0; p < 2; ++p) {
 #pragma unroll
-      for (int r = 0; r < RB; ++r) a[p][r] = *reinterpret_cast<const halfx8*>(As + p * L::A_PLANE + r * 512);
+      for (int r = 0; r < RB; ++r) a[p][r] = *reinterpret_cast<const operand*>(As + p * L::A_PLANE + r * 512);
 #pragma unroll
-      for (int j = 0; j < JB; ++j) b[p][j] = *reinterpret_cast<const halfx8*>(Bs + p * L::B_PLANE + L::slot_bytes(j, 0));
+      for (int j = 0; j < JB; ++j) b[p][j] = *reinterpret_cast<const operand*>(Bs + p * L::B_PLANE + L::slot_bytes(j, 0));
     }
+    if constexpr (decltype(plain)::value) {      // step (p, e): the indices 4 p + e of both octets
+#pragma unroll
+      for (int p = 0; p < 2; ++p)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+          for (int r = 0; r < RB; ++r)
+#pragma unroll
+            for (int j = 0; j < JB; ++j) acc[r][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[p][r][e], b[p][j][e], acc[r][j], 0, 0, 0);
+    } else {
     auto product = [&](int pa, int pb) {
 #pragma unroll
       for (int r = 0; r < RB; ++r)
@@ -287,13 +414,14 @@ void gemm_split_kernel(const float* __restrict__ in, const float* __restrict__ P
         for (int j = 0; j < JB; ++j) acc[r][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[pa][r], b[pb][j], acc[r][j], 0, 0, 0);
     };
     product(0, 0); product(0, 1); product(1, 0);
+    }
   };
 
-  for (int i = tid; i < BM + BN; i += 512) most[i] = 0;
-  if (tid == 0) *again = 0;
+  for (int i = tid; i < BM + BN; i += 512) most[i] = 0, shorts[i] = zeros[i] = 0;
+  if (tid < 3) again[tid] = 0;
   __syncthreads();
-  if (wave < 4) run(std::true_type{}, clear, multiply);
-  else run(std::false_type{}, clear, multiply);
+  if (wave < 4) run(std::true_type{}, clear, multiply, finite);
+  else run(std::false_type{}, clear, multiply, finite);
 
   // KG > 1: the groups' partial tiles meet in LDS (free after the last barrier); group kg finishes the
   // registers [kg SHARE, (kg + 1) SHARE) of all of them
@@ -319,9 +447,7 @@ void gemm_split_kernel(const float* __restrict__ in, const float* __restrict__ P
   int col_expo[JB];                            // (column q JB + j of the tile: by slots where c is contiguous)
 #pragma unroll
   for (int j = 0; j < JB; ++j) col_expo[j] = expo[BM + (B_KCONTIG ? j * L::QCOLS + slot : n - n0 + j)];
-  uint32_t redo = 0;                           // of the rows finished here: those with an output that is not finite
   auto row_in_tile = [&](int re) { return wr * RB * 32 + 32 * (re >> 4) + 8 * ((re >> 2) & 3) + 4 * g + (re & 3); };
-  auto row_of = [&](int re) { return row0 + row_in_tile(re); };
   auto finish = [&](float* dst, vec x) {
     if (epilogue == 1) {
 #pragma unroll
@@ -335,7 +461,6 @@ void gemm_split_kernel(const float* __restrict__ in, const float* __restrict__ P
 #pragma unroll
   for (int k = 0; k < SHARE; ++k) {
     vec x;
-    bool finite = true;
     const int row_expo = expo[row_in_tile(re0 + k)];
 #pragma unroll
     for (int j = 0; j < JB; ++j) {
@@ -345,20 +470,9 @@ void gemm_split_kernel(const float* __restrict__ in, const float* __restrict__ P
 #pragma unroll
         for (int q = 0; q < KG; ++q) y += part[((size_t)(q * WR * WC + wave % (WR * WC)) * (RB * 16) + re0 + k) * (JB * 64) + j * 64];
       x[j] = ldexpf(y, row_expo + col_expo[j]);
-      finite = finite && fabsf(x[j]) < INFINITY;
     }
-    const int row = row_of(re0 + k);
-    if (row >= rows) continue;
-    if (!finite) redo |= 1u << k;
-    else finish(out + (size_t)row * N + n, x);
-  }
-  while (redo) {
-    const int row = row_of(re0 + __builtin_ctz(redo));
-    redo &= redo - 1;
-    vec x;
-#pragma unroll
-    for (int j = 0; j < JB; ++j) x[j] = plain_dot<B_KCONTIG>(in, P, row, n + j, d, h, kv);
-    finish(out + (size_t)row * N + n, x);
+    const int row = row0 + row_in_tile(re0 + k);
+    if (row < rows) finish(out + (size_t)row * N + n, x);
   }
 }
 
@@ -374,7 +488,7 @@ bool split_fits(bool outp, int d, int h, int kv, int tile, int stage) {
 template <bool KC, int BM, int BN, int WR, int WC, int KG, int PD>
 hipError_t launch_split(const float* in, const float* P, float* out, int rows, int d, int h, int kv, int N,
                         int epilogue, hipStream_t st) {
-  constexpr size_t lds = SplitTile<BM, BN, BN / WC / 32, KG>::BYTES;       // 70 KiB
+  constexpr size_t lds = SplitTile<BM, BN, BN / WC / 32, KG>::BYTES;       // 67 KiB (32, 64), 132 (128: the groups' partial tiles), 74 (256)
   auto kern = gemm_split_kernel<KC, BM, BN, WR, WC, KG, PD>;
   static bool done[64] = {};
   int dev = 0;

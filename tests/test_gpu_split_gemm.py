@@ -26,14 +26,26 @@ def product(m, layout, x, W, out=None, epilogue=None):
     return m.mqa_project_qkvo_ex(m.MQA_PROJ_O, x.view(rows, C // kv, kv), P, out=out, epilogue=epilogue or m.MQA_EPI_STORE)
 
 
+def cut_off(a):
+    """Per line of a [lines, C]: where the terms may begin to hold its values in fewer bits.  Few octets may hold such a value
+    (none of up to 7 that are not all zeros, 2 and an eighth of more), so it is no more than the smallest
+    value of the octet that is next."""
+    least = torch.nn.functional.pad(a, (0, -a.shape[1] % 8)).view(a.shape[0], -1, 8)
+    least = torch.where(least > 0, least, float("inf")).amin(2).sort(1).values
+    octets = torch.isfinite(least).sum(1)
+    allowed = torch.where(octets < 8, 0, 2 + octets // 8)
+    return least.gather(1, allowed[:, None].clamp(max=least.shape[1] - 1))
+
+
 def bound(x, W):
-    # three products per 16 contraction indices round the running sum once each (2^-24 of it); two terms hold an
-    # operand to 2^-23 and the product of the second terms, at most 2^-22 |a||b|, is dropped (together 8 . 2^-24);
-    # the scaling back and the last store round once more each; and terms below 2^-24 of the scaled operand
-    # cost 2^-35 of a row's (column's) largest value (x 2 for the scale's power of two and the dropped product)
+    # three products per 16 contraction indices round the running sum once each (2^-24 of it); two terms hold an operand
+    # from its cut-off on to 2^-21 (2^-23 from four times the cut-off on) and the product of the second terms, at most
+    # 2^-22 |a||b|, is dropped (together 20 . 2^-24); the scaling back and the last store round once more each; and the few
+    # values below a line's cut-off are off by 2^-21 of it
     a, b = x.double().abs(), W.double().abs()
-    small = 2.0 ** -34 * (a.amax(1, keepdim=True) * b.sum(0, keepdim=True) + a.sum(1, keepdim=True) * b.amax(0, keepdim=True))
-    return (0.1875 * x.shape[1] + 12) * 2.0 ** -24 * (a @ b) + small
+    ta, tb = cut_off(a), cut_off(b.t().contiguous()).t()
+    small = 2.0 ** -21 * (torch.where(a < ta, ta, 0.0) @ b + a @ torch.where(b < tb, tb, 0.0))
+    return (0.1875 * x.shape[1] + 24) * 2.0 ** -24 * (a @ b) + torch.nan_to_num(small, nan=0.0)
 
 
 def tiles_of(m, layout, rows, C, N):
@@ -125,6 +137,68 @@ def test_split_gemm_values_without_a_split(m, layout, tiles, rows, C, N):
     fine = torch.isfinite(ref)
     lim = torch.nan_to_num(bound(x, W), nan=0.0, posinf=0.0)
     assert ((got.double() - ref.double()).abs()[fine] <= lim[fine] + 2.0 ** -23 * ref.double().abs()[fine]).all()
+
+
+def off(got, x, W):
+    """The largest error of a row and of a column, 2-norm over 2-norm."""
+    ref = x.double() @ W.double()
+    e = (got.double() - ref).square()
+    one = lambda dim: float((e.sum(dim) / ref.square().sum(dim).clamp(min=1e-300)).max()) ** 0.5
+    return max(one(0), one(1))
+
+
+@pytest.mark.parametrize("layout", ["n", "c"])
+@pytest.mark.parametrize("tiles,rows,C,N", EDGES)
+@pytest.mark.parametrize("ratio", [2.0 ** 6, 2.0 ** 10, 2.0 ** 14, 2.0 ** 17, 2.0 ** 20, 2.0 ** 24, 2.0 ** 40])
+def test_split_gemm_wide_lines(m, layout, tiles, rows, C, N, ratio):
+    """Values far above the rest of their row or column that meet zeros, or weights as far below: what float32 products
+    keep of the rest is kept.  float32 instructions are off by 5.7e-7 at C = 1024, as the root of C; four times that."""
+    assert tiles_of(m, layout, rows, C, N) == tiles
+    g = torch.Generator(device=DEV)
+    g.manual_seed(int(ratio) % 1000 + C)
+    most = 2.3e-6 * max(0.5, (C / 1024) ** 0.5)
+    x0 = torch.randn(rows, C, generator=g, device=DEV)
+    W0 = torch.randn(C, N, generator=g, device=DEV)
+    for at in ([3], [C // 2], [C - 1], list(range(C // 2, C))):
+        x, W = x0.clone(), W0.clone()
+        x[:, at] *= ratio                    # a channel of every row
+        W[at] = 0
+        assert off(product(m, layout, x, W), x, W) < most, ("rows", at[0])
+        x, W = x0.clone(), W0.clone()
+        W[at] *= ratio                       # of every column
+        x[:, at] = 0
+        assert off(product(m, layout, x, W), x, W) < most, ("columns", at[0])
+        x, W = x0.clone(), W0.clone()
+        x[5, at] *= ratio                    # of one row, one column
+        W[at, 7] = 0
+        W[C // 3, 9] *= ratio
+        x[11, C // 3] = 0
+        got, ref = product(m, layout, x, W).double(), x.double() @ W.double()
+        for r, n in ((5, 7), (11, 9)):
+            assert abs(float(got[r, n] - ref[r, n])) < 4 * most * float((x[r].double() * W[:, n].double()).norm())
+    x, W = x0.clone(), W0.clone()
+    x[:, C // 2] *= ratio
+    W[C // 2] /= ratio
+    assert off(product(m, layout, x, W), x, W) < most
+
+
+@pytest.mark.parametrize("layout", ["n", "c"])
+@pytest.mark.parametrize("tiles,rows,C,N", EDGES)
+def test_split_gemm_sparse_lines(m, layout, tiles, rows, C, N):
+    """Rows of mostly zeros: few values, some of them far below the other rows', and rows whose only values come late."""
+    assert tiles_of(m, layout, rows, C, N) == tiles
+    g = torch.Generator(device=DEV)
+    g.manual_seed(3)
+    x = torch.randn(rows, C, generator=g, device=DEV).clamp(min=0)
+    W = torch.randn(C, N, generator=g, device=DEV)
+    x[::3] *= (torch.rand(rows, C, generator=g, device=DEV) < 0.05)[::3]
+    for r, (c, v) in enumerate([(2, 1e-9), (C - 2, 1e-9), (C // 2, 1e-20), (40, 1e-6), (C - 9, 1e12)]):
+        x[7 + r] = 0
+        x[7 + r, c] = v
+    x[rows - 1, :C - 8] = 0
+    x[rows - 1, C - 8:] *= 1e-8
+    most = 2.3e-6 * max(0.5, (C / 1024) ** 0.5)
+    assert off(product(m, layout, x, W), x, W) < most
 
 
 @pytest.mark.parametrize("kv", [8, 24, 72])
