@@ -4,7 +4,7 @@
 // float64 matrix instructions run at 1/32 of the 16-bit rate and bounded this product (32768 rows, d = 1024, 256
 // columns: 42 TFLOP/s, 410 us; this kernel 205: of a tile's 100 us about 20 are the first pass and 20 the open elements; the
 // matrix cores are busy 18 %, vector instructions 34 %; two and three stages ahead measured the same).  Here the sum is found with a bound on its error from exact integer products, and
-// only the elements whose rounding to bf16 the bound leaves open (one in some thousands) are summed in float64.
+// only the elements whose rounding to bf16 the bound leaves open (0.09 % of normal deviates at d = 1024) are summed in float64.
 //   * Fixed point: a row of the input and a column of the weights are scaled by a power of two that takes
 //     their largest value to [2^29, 2^31 - 2^24], and truncated to integers X, Y of four balanced base-256 digits,
 //     X = d3 2^24 + d2 2^16 + d1 2^8 + d0, every digit an int8.
@@ -14,7 +14,8 @@
 //     Cauchy-Schwarz below 2^16 (|d2||e0| + |d1||e1| + |d0||e2|) + 2^9 2^14 C; the digits' norms are summed
 //     while they are staged (v_dot4), and |X| <= 2^24 (|d3| + 1).
 //   * An element is done if both ends of sum +- bound round to the same bf16 (through float32, as the float64
-//     kernel rounds): its distance from the nearest tie against the bound; the others are summed by one wave each, in float64.  Rows or columns with a NaN are NaN; one
+//     kernel rounds): its distance from the nearest tie against the bound; the others are summed by one wave each, in float64,
+//     or, where a tile has many (rows or columns of a few large values), all of it on the float64 instructions.  Rows or columns with a NaN are NaN; one
 //     with an infinity has no fixed point and goes the float64 way.
 //
 // Workgroup: 512 threads, 128 x 128 tile, wave (wr, wc) of 4 x 2 holds 32 x 64 of it.  A first pass over the
@@ -38,6 +39,11 @@ constexpr int kHalf = 2 * kBlock;              // halves, or four columns of eac
 constexpr int kPlane = 2 * kHalf;              // one digit of 32 indices
 constexpr int kOperand = 4 * kPlane;
 constexpr int kStage = 2 * kOperand;
+// Open elements of a tile from which its waves sum all of it in float64 instead.  A wave spends some 8 us on one element (the
+// weights are a cache line each), the whole tile takes 270 us: us for 32768 rows, d = 1024, with one channel of the rows 2^6
+// times the others and its weights as much smaller (210 open elements a tile) one by one 439, all 485; 2^8 times (650) 978
+// and 481; 2^10 times 2419 and 478; the float64 kernel takes 410, normal deviates 213.
+constexpr int kMostOpen = 256;
 constexpr int kMaxC = 16384;                   // four products of 2^14 per index in an int32
 
 struct KvParams {
@@ -62,6 +68,62 @@ __device__ __forceinline__ int fixed_exponent(uint32_t bits) {           // x . 
   int up = 30 + 127 - e;
   if ((bits & 0x7fffffu) > 0x7d0000u) --up;                             // (2 - 2^-6) 2^30 = 2^31 - 2^24
   return up > 127 ? 127 : up;
+}
+
+// 32 rows x 64 columns by one wave, in float64 from global memory: register e of lane (i, kk) of a 16 x 16 block is row
+// 4 e + kk, column i; step s contracts the indices 4 kk + s of sixteen.
+template <typename Place>
+__device__ __forceinline__ void float64_tile(const KvParams& p, const float* P, int which, int row0, int n0, int lane, Place&& place) {
+  typedef __attribute__((ext_vector_type(4))) double double4v;
+  const int i = lane & 15, kk = lane >> 4, kv = p.kv[which], N = p.h_kv * kv, C = p.C;
+  const float* xr[2];
+  const float* w[4];
+#pragma unroll
+  for (int r = 0; r < 2; ++r) xr[r] = p.x + (size_t)min(row0 + 16 * r + i, p.rows - 1) * C;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const int n = min(n0 + 16 * j + i, N - 1);
+    w[j] = P + (size_t)(n / kv) * C * kv + n % kv;
+  }
+  double4v acc[2][4];
+#pragma unroll
+  for (int r = 0; r < 2; ++r)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) acc[r][j] = double4v{0., 0., 0., 0.};
+  for (int c0 = 0; c0 < C; c0 += 16) {
+    const int c = min(c0 + 4 * kk, C - 4);
+    const bool in = c0 + 4 * kk < C;           // (C is a multiple of 8)
+    float a[2][4], b[4][4];
+#pragma unroll
+    for (int r = 0; r < 2; ++r) {
+      const float4 v = *reinterpret_cast<const float4*>(xr[r] + c);
+      a[r][0] = in ? v.x : 0.f; a[r][1] = in ? v.y : 0.f; a[r][2] = in ? v.z : 0.f; a[r][3] = in ? v.w : 0.f;
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        const float v = w[j][(size_t)(c + s) * kv];
+        b[j][s] = in ? v : 0.f;
+      }
+#pragma unroll
+    for (int s = 0; s < 4; ++s)
+#pragma unroll
+      for (int r = 0; r < 2; ++r)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) acc[r][j] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)a[r][s], (double)b[j][s], acc[r][j], 0, 0, 0);
+  }
+#pragma unroll
+  for (int r = 0; r < 2; ++r)
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int row = row0 + 16 * r + 4 * e + kk, n = n0 + 16 * j + i;
+        if (row >= p.rows || n >= N) continue;
+        uint16_t* at = place(row, n);
+        if (at) *at = (uint16_t)to_bf16(acc[r][j][e]);
+      }
 }
 
 __global__ __launch_bounds__(512)
@@ -295,7 +357,8 @@ void project_kv_exact_kernel(KvParams p) {
   }
   __syncthreads();
   const int left = *count;
-  for (int i = wave; i < left; i += 8) {
+  if (left > kMostOpen) float64_tile(p, P, which, row0 + wr * 32, n0 + wc * 64, lane, place);
+  else for (int i = wave; i < left; i += 8) {
     const int r = list[i] >> 7, col = n0 + (list[i] & 127);
     const float* xr = p.x + (size_t)(row0 + r) * C;
     const float* w = P + (size_t)(col / kv) * head_stride + col % kv;

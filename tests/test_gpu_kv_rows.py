@@ -95,6 +95,23 @@ def test_append_rows(m, b, n, d, heads, k, v, dtype):
     assert after.tolist() == [L + n if 0 <= L <= 10 else L for L in lens.tolist()]
 
 
+@pytest.mark.parametrize("ratio", [2.0 ** 6, 2.0 ** 12, 2.0 ** 40])
+@pytest.mark.parametrize("b,n,d,heads,k,v", [s for s in SHAPES if s[0] > 3])
+def test_one_large_channel(m, b, n, d, heads, k, v, ratio):
+    """One channel far above the others, its weights as far below: the bounds leave from a few elements of a tile to all of
+    it open."""
+    x, P_k, P_v = inputs(b, n, d, heads, k, v, n + 2)
+    assert m.mqa_project_kv_plan(b * n, d, 0, heads or 1, k, v, m.MQA_BF16) == 1
+    x[..., d // 3] *= ratio
+    P_k[..., d // 3, :] /= ratio
+    P_v[..., d // 3, :] /= ratio
+    K, V = caches(b, heads, n + 3, k, v)
+    lens = torch.zeros(b, dtype=torch.int32, device=DEV)
+    m.mqa_project_memory_kv(x, P_k, P_v, K, V, lens)
+    assert torch.equal(K[..., :n, :], expected(x, P_k, heads)) and torch.equal(V[..., :n, :], expected(x, P_v, heads))
+    assert (K[..., n:, :] == 7).all() and (V[..., n:, :] == 7).all()
+
+
 def test_rows_of_any_values(m):
     """Zeros, ties, wide ranges inside a row and a column, sums that cancel, subnormals, infinities and NaN."""
     b, n, d = 64, 300, 200
