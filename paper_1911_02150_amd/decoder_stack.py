@@ -99,17 +99,19 @@ class DecoderStack:
             hx = B.mqa_stack_layernorm(x)
             q = B.mqa_project_qkvo(B.MQA_PROJ_Q, hx, w["P_q"]).view(b, n, self.h, self.k)
             if self.k % 16 == 0 and self.v % 16 == 0:
-                B.mqa_project_append_kv_rows(hx.view(b, n, self.d), w["P_k"], w["P_v"], self.K[l], self.V[l], self.lens[l],
-                                             self._lens_next[l])
-                self.lens[l], self._lens_next[l] = self._lens_next[l], self.lens[l]
+                now = self._lens_next[l]
+                B.mqa_project_append_kv_rows(hx.view(b, n, self.d), w["P_k"], w["P_v"], self.K[l], self.V[l], self.lens[l], now)
             else:
+                now = self.lens[l]
                 kn = B.mqa_project_qkvo(B.MQA_PROJ_KV, hx, w["P_k"]).view(b, n, self.k)
                 vn = B.mqa_project_qkvo(B.MQA_PROJ_KV, hx, w["P_v"]).view(b, n, self.v)
                 B.mqa_append_kv_rows(self.K[l], self.V[l], kn, vn, self.lens[l])
-            o = B.mqa_prefill_attention(q, self.K[l], self.V[l], self.lens[l])
+            o = B.mqa_prefill_attention(q, self.K[l], self.V[l], now)
             B.mqa_project_qkvo_ex(B.MQA_PROJ_O, o.view(b * n, self.h, self.v), w["P_o"], out=x, epilogue=B.MQA_EPI_ADD)
             u = B.mqa_project_qkvo_ex(B.MQA_PROJ_LINEAR, B.mqa_stack_layernorm(x), w["W1"], epilogue=B.MQA_EPI_RELU)
             B.mqa_project_qkvo_ex(B.MQA_PROJ_LINEAR, u, w["W2"], out=x, epilogue=B.MQA_EPI_ADD)
+        if now is not self.lens[-1]:      # the lengths advance in the arrays they are in: a caller may hold them
+            torch._foreach_copy_(self.lens, self._lens_next)
         last = x.view(b, n, self.d)[:, n - 1].contiguous()
         return self.logits(last)
 

@@ -181,3 +181,23 @@ def test_stack_prefill_matches_incremental_and_oracle(m):
     tok = ods.greedy_token(logits_ref)
     nxt = a.step(torch.from_numpy(tok.astype(np.int32)).to(DEV), n)
     assert np.max(np.abs(nxt.cpu().numpy() - ref.step(tok, n))) <= 2e-3 * scale
+
+
+def test_stack_prefill_advances_the_lengths_in_place(m):
+    """The length arrays of a stack stay the same tensors through a prompt (a caller may hold them, and a captured
+    prompt reads and writes the ones it was captured with)."""
+    from paper_1911_02150_amd.decoder_stack import DecoderStack
+    g = mi.rng(3200, 0)
+    draw = lambda *s: g.standard_normal(s, dtype=np.float32) * np.float32(0.1)
+    d, h, ff, vocab, b, n = 64, 2, 128, 40, 3, 5
+    layers = [dict(P_q=draw(h, d, 128), P_k=draw(d, 128), P_v=draw(d, 128), P_o=draw(h, d, 128), W1=draw(d, ff), W2=draw(ff, d))
+              for _ in range(2)]
+    stack = DecoderStack(dict(E=draw(vocab, d), pos=draw(2 * n, d), layers=layers), b, 2 * n, False, device=DEV)
+    held, spare = list(stack.lens), list(stack._lens_next)
+    prompts = torch.from_numpy(g.integers(0, vocab, size=(b, n)).astype(np.int32)).to(DEV)
+    logits = stack.prefill(prompts)
+    for l in range(2):
+        assert stack.lens[l] is held[l] and stack._lens_next[l] is spare[l] and held[l].tolist() == [n] * b
+    for t in held:
+        t.zero_()
+    assert torch.equal(stack.prefill(prompts), logits) and all(t.tolist() == [n] * b for t in held)
