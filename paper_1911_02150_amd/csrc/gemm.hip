@@ -20,12 +20,12 @@
 // again; if not (a line whose values lie more than about 2^11 apart, an infinity) it is multiplied on float32 instructions
 // (v_mfma_f32_32x32x2_f32), the values themselves in the place of their two terms.  So are contractions of
 // less than 64, too short to count.  Measured (us, rows = 16384, 1024 x 4096; without the counting / with it / on float32
-// instructions alone): normal deviates 393 / 420 / 1095; one channel 2^6 times the others 735 / 1020 / 1095 (scales set
+// instructions alone): normal deviates 386 / 407 / 1095; one channel 2^6 times the others 735 / 1020 / 1095 (scales set
 // again); 2^12 times 727 / 1660 / 1095 (float32 after that).  Without it the others' part of such sums was lost from 2^14 on.
 //
 // Measured (b=128, n=128 prompt: rows = 16384, TFLOP/s of the float32 product; 128x128 tiles of
-// v_mfma_f32_32x32x2_f32 / three bf16 terms and six products / this): 1024 x 4096: 126 / 224 / 327; 4096 x 1024:
-// 129 / 228 / 340; 1024 x 1024: 122 / 220 / 322; logits of 128 rows 101 / 145 / 200.  That is 1.0 PFLOP/s of fp16
+// v_mfma_f32_32x32x2_f32 / three bf16 terms and six products / this): 1024 x 4096: 126 / 224 / 338; 4096 x 1024:
+// 129 / 228 / 350; 1024 x 1024: 122 / 220 / 334; logits of 128 rows 101 / 145 / 200.  That is 1.0 PFLOP/s of fp16
 // products with the matrix cores busy 51 % of the 1.9 GHz the card runs at under this load (hipBLASLt's 8192^3 bf16
 // product reaches 1.29 here); vector instructions take 30 %, LDS 22 % (counters before the counting of octets).  More stages ahead in registers (2, 3), or two
 // stages per barrier in LDS, measured the same.
@@ -190,7 +190,7 @@ void gemm_split_kernel(const float* __restrict__ in, const float* __restrict__ P
     };
     // |x| in order, zero last
     auto order = [](float x) -> uint32_t { return (__float_as_uint(x) << 1) - 2u; };
-    auto count = [&](const Regs& rg) {
+    auto count = [&](bool past, const Regs& rg) {
 #pragma unroll
       for (int i = 0; i < 2; ++i) {
         uint32_t u = ~0u;
@@ -200,14 +200,20 @@ void gemm_split_kernel(const float* __restrict__ in, const float* __restrict__ P
 #pragma unroll
           for (int k = 0; k < 8; ++k) peak[i] = fmaxf(peak[i], fabsf(value(rg, i, k)));
         }
-        short_octets[i] += u < order(ldexpf(kFull, split_exponent(scale[i]))) ? 1 : 0;
-        zero_octets[i] += u >= order(0.f) ? 1 : 0;
+        short_octets[i] += !past && u < order(ldexpf(kFull, split_exponent(scale[i]))) ? 1 : 0;
+        zero_octets[i] += past || u >= order(0.f) ? 1 : 0;
       }
     };
     auto store_stage = [&](auto plain, int st, Regs& rg) {
       unsigned char* base = smem + (st & 1) * L::STAGE;
       const int octet = BY_ROWS ? o_row : o_col;
-      drop_tail(st, rg);
+      // Past the end: zeros; or, in the large tiles, scaled by 0 (two selections instead of sixteen moves a stage, 412 -> 394 us
+      // at 16384 x 4096 x 1024; the small ones have no register for it).  An infinity there is in the line as well and takes
+      // it to the float32 instructions.
+      constexpr bool CLEAR = decltype(plain)::value || KG >= 4;
+      const bool past = !CLEAR && st * 16 * KG + 8 * octet >= C;
+      const float by[2] = {past ? 0.f : scale[0], past ? 0.f : scale[1]};
+      if constexpr (CLEAR) drop_tail(st, rg);
       base += (octet >> 1) * L::GROUP + (octet & 1) * (STAGE_A ? L::A_G : L::B_G) + (STAGE_A ? 0 : 2 * L::A_PLANE);
       float least[2] = {INFINITY, INFINITY};
 #pragma unroll
@@ -219,7 +225,7 @@ void gemm_split_kernel(const float* __restrict__ in, const float* __restrict__ P
         } else {
 #pragma unroll
           for (int k = 0; k < 4; ++k) {
-            const float a = value(rg, i, 2 * k) * scale[i], b = value(rg, i, 2 * k + 1) * scale[i];
+            const float a = value(rg, i, 2 * k) * by[i], b = value(rg, i, 2 * k + 1) * by[i];
             least[i] = fminf(least[i], fminf(fabsf(a), fabsf(b)));
             const Split2 s = split2(a, b);
             t[0][k] = s.hi; t[1][k] = s.lo;
@@ -229,7 +235,7 @@ void gemm_split_kernel(const float* __restrict__ in, const float* __restrict__ P
 #pragma unroll
         for (int p = 0; p < 2; ++p) *reinterpret_cast<u32x4*>(base + p * (STAGE_A ? L::A_PLANE : L::B_PLANE) + at) = t[p];
       }
-      if (!decltype(plain)::value && fminf(least[0], least[1]) < suspect) count(rg);      // (a zero, or one of some ten thousand normal deviates)
+      if (!decltype(plain)::value && fminf(least[0], least[1]) < suspect) count(past, rg);      // (a zero, or one of some ten thousand normal deviates)
     };
     // scales from the largest values known; a line of zeros so far takes the largest of the tile's lines
     auto set_scales = [&](int top) {
@@ -348,7 +354,7 @@ void gemm_split_kernel(const float* __restrict__ in, const float* __restrict__ P
       __syncthreads();
       if (!again[2]) break;                    // (a NaN alone, and the outputs are what they were to be)
       set_scales(kLastTop);
-      scan([&](Regs& rg) { count(rg); });
+      scan([&](Regs& rg) { count(false, rg); });
       tell_counts();
       __syncthreads();
 #pragma unroll

@@ -123,7 +123,7 @@ def test_split_gemm_values_without_a_split(m, layout, tiles, rows, C, N):
     x = torch.randn(rows, C, generator=g, device=DEV)
     W = torch.randn(C, N, generator=g, device=DEV) / 16
     big = float(np.finfo(np.float32).max)
-    x[3, 5], x[rows - 1, 0] = float("inf"), float("-inf")
+    x[3, 5], x[rows - 1, 0], x[13, C - 1] = float("inf"), float("-inf"), float("inf")
     x[7], x[130, C - 1] = float("nan"), float("nan")
     x[9, :] = 0
     x[9, 11] = big                           # one product of the largest float per output of the row
