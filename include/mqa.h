@@ -92,7 +92,9 @@ typedef struct {
                                form would keep one workgroup per compute unit
                                going over several ranked sequences
                        bit 11  rank by a separate launch even where that kernel
-                               would rank up to 1024 sequences itself                                       */
+                               would rank up to 1024 sequences itself
+                       bit 12  no effect (it chose between two kernels for causal
+                               rows, of which one is left)                        */
 } mqa_tuning;
 
 /*
@@ -143,8 +145,9 @@ int mqa_project_append_qkv(const float* x, const float* P_q, const float* P_k, c
 /*
  * The new K and V rows of n positions per sequence (a prompt), projected and appended in one launch: rows
  * x[i,p,:] . P_k, x[i,p,:] . P_v for p < n go behind the lens_in[i] rows sequence i has, lens_out[i] = lens_in[i] + n;
- * a sequence that cannot hold all n keeps its cache and length.  Same cache rows, bit for bit, as
- * mqa_project_qkvo (KV or KV_MH) followed by mqa_append_kv_rows.  x [b,n,d]; P_k, P_v, K, V and the limits as in
+ * a sequence that cannot hold all n keeps its cache and length.  Same cache rows as mqa_project_qkvo (KV or
+ * KV_MH) followed by mqa_append_kv_rows: the correctly rounded products, and so bit for bit, except where products cancel
+ * so far that the rounding of the float64 sums themselves decides the stored value.  x [b,n,d]; P_k, P_v, K, V and the limits as in
  * mqa_project_append_qkv; n <= cap; lens_in and lens_out must be different arrays.
  */
 int mqa_project_append_kv_rows(const float* x, const float* P_k, const float* P_v, void* K, void* V,

@@ -333,7 +333,7 @@ hipError_t launch_project(int mode, const float* in, const float* P, float* out,
   const bool outp = (mode == 3);
   const bool f64 = (mode == 1 || mode == 2);        // new K / V rows: float64 accumulation, split-contraction kernel only
   if (!f64) {
-    const hipError_t big = launch_gemm_tiled(mode, in, P, out, rows, d, h, kv, epilogue, 0, st);     // large GEMMs: LDS-tiled kernel
+    const hipError_t big = launch_gemm_tiled(mode, in, P, out, rows, d, h, kv, epilogue, 0, st);     // large GEMMs: the split-operand kernel (gemm.hip)
     if (big != hipErrorNotSupported) return big;
   }
   const int N = outp ? d : h * kv;
@@ -360,7 +360,7 @@ hipError_t launch_project_qkv_append(const float* x, const float* P_q, const flo
                                      float* q, void* K, void* V, const int32_t* lens_in, int32_t* lens_out,
                                      int rows, int d, int h, int h_kv, int cap, int k, int v, int is_bf16,
                                      int mem_rows, int append, hipStream_t st) {
-  // prompt-sized row counts: q through the LDS-tiled kernel, then only the K / V columns here
+  // prompt-sized row counts: q through the split-operand kernel (gemm.hip), then only the K / V columns here
   // (h = 0: no q at all, the projection of a memory)
   const hipError_t big = h > 0 ? launch_gemm_tiled(0, x, P_q, q, rows, d, h, k, 0, kApart, st) : hipErrorNotSupported;
   if (big != hipErrorNotSupported && big != hipSuccess) return big;
@@ -377,7 +377,9 @@ hipError_t launch_project_qkv_append(const float* x, const float* P_q, const flo
   while (r) { const int t2 = g % r; g = r; r = t2; }
   Tile t = pick_tile(q_done ? ntot - nq : ntot, rows, g);
   // A decode step whose K / V columns outweigh q's: their float64 tiles take one row block at a time, so a second one in
-  // the workgroup only makes it longer (b=256, h=8 multi-head: 50.7 -> 39.9 us; b=128: 27.6 either way)
+  // the workgroup only makes it longer (multi-head, d=1024, h=8: b=192: 38.5 -> 33.1 us, 256: 49.6 -> 38.3, 384: 62.5 ->
+  // 57.5, 512: 74.6 -> 73.3; up to 160 rows the tiles are this narrow anyway; d = 512 and 2048, h = 4 and 16 alike; 640
+  // rows on: within 3 % either way)
   if (t.RB == 2 && t.CB == 4 && rows <= 512 && ntot - nq > nq) t.RB = 1;
   // a decode step's rows and K / V columns that are a small part of the product (multi-query): K / V tiles of
   // 16 columns (b=128, h=8: 14.2 -> 10.4 us; multi-head, where they are two thirds of it: 25.9 -> 31.6 us, so not there)

@@ -1,10 +1,13 @@
 // New K / V rows of many positions at once (a memory, a prompt) into a bf16 cache: the correctly rounded
-// value of the float64 product, bit for bit what the float64 kernel of project.hip writes, without its cost.
+// value of the product, which is what the float64 kernel of project.hip writes, without its cost.  (Where the products
+// cancel so far that the rounding of the float64 sums themselves decides the bf16 value, the order of those sums shows,
+// as it does between any two float64 kernels.)
 //
 // float64 matrix instructions run at 1/32 of the 16-bit rate and bounded this product (32768 rows, d = 1024, 256
 // columns: 42 TFLOP/s, 410 us; this kernel 205: of a tile's 100 us about 20 are the first pass and 20 the open elements; the
 // matrix cores are busy 18 %, vector instructions 34 %; two and three stages ahead measured the same).  Here the sum is found with a bound on its error from exact integer products, and
 // only the elements whose rounding to bf16 the bound leaves open (0.09 % of normal deviates at d = 1024) are summed in float64.
+// (Exact products of operands cut into slices of few bits: after Ozaki, Ogita, Oishi, Rump 2012; here in integers.)
 //   * Fixed point: a row of the input and a column of the weights are scaled by a power of two that takes
 //     their largest value to [2^29, 2^31 - 2^24], and truncated to integers X, Y of four balanced base-256 digits,
 //     X = d3 2^24 + d2 2^16 + d1 2^8 + d0, every digit an int8.
