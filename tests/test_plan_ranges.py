@@ -40,3 +40,20 @@ def test_ranges_stay_within_what_filled_the_chip():
                 most = max(1, min(-(-256 // b), -(-cap // least)))
                 assert 1 <= S <= most and chunk % 32 == 0 and (S - 1) * chunk < cap <= S * chunk
                 assert m.mqa_decode_workspace_bytes_default(b, 8, cap, k, k, dt) <= most * b * 8 * (k + 2) * 4 + 16 + 4 * b
+
+
+def test_projection_plans():
+    """Which kernel a projection takes: refused sizes as the calls refuse them, small products and new K / V rows not in the
+    split-operand kernel, larger ones in larger tiles, offsets past 32 bits not."""
+    import paper_1911_02150_amd as m
+    plan, kv = m.mqa_project_plan, m.mqa_project_kv_plan
+    assert plan(9, 4, 64, 2, 16) == -5 and plan(m.MQA_PROJ_Q, 4, 60, 2, 16) == -2 and plan(m.MQA_PROJ_O, 0, 64, 2, 16) == -2
+    assert plan(m.MQA_PROJ_LINEAR, 4, 64, 0, 16) == 0                     # h is ignored
+    assert plan(m.MQA_PROJ_Q, 128, 1024, 8, 128) == plan(m.MQA_PROJ_O, 128, 1024, 8, 128) == 0
+    assert plan(m.MQA_PROJ_KV, 1 << 15, 1024, 1, 4096) == plan(m.MQA_PROJ_KV_MH, 1 << 15, 1024, 8, 128) == 0
+    assert [plan(m.MQA_PROJ_LINEAR, rows, 1024, 1, N) for rows, N in ((512, 1024), (1024, 1024), (4096, 1024), (16384, 4096))] == [32, 64, 128, 256]
+    assert plan(m.MQA_PROJ_LINEAR, 512, 1 << 23, 1, 4096) == 0            # rows of a tile 8 GiB apart
+    assert kv(4, 64, 0, 1, 20, 16, m.MQA_BF16) == -2 and kv(4, 64, 0, 1, 16, 16, 7) == -5 and kv(4, 64, -1, 1, 16, 16, m.MQA_BF16) == -2
+    assert kv(1 << 15, 1024, 0, 1, 128, 128, m.MQA_BF16) == 1 and kv(1 << 15, 1024, 0, 1, 128, 128, m.MQA_F32) == 0
+    assert kv(128, 1024, 8, 8, 128, 128, m.MQA_BF16) == 0 and kv(128, 1024, 0, 1, 128, 128, m.MQA_BF16) == 0
+    assert kv(1 << 15, 1 << 15, 0, 1, 128, 128, m.MQA_BF16) == 0          # sums of digit products past 32 bits
