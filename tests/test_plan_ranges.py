@@ -52,7 +52,7 @@ def test_projection_plans():
     assert plan(m.MQA_PROJ_Q, 128, 1024, 8, 128) == plan(m.MQA_PROJ_O, 128, 1024, 8, 128) == 0
     assert plan(m.MQA_PROJ_KV, 1 << 15, 1024, 1, 4096) == plan(m.MQA_PROJ_KV_MH, 1 << 15, 1024, 8, 128) == 0
     assert [plan(m.MQA_PROJ_LINEAR, rows, 1024, 1, N) for rows, N in ((512, 1024), (1024, 1024), (4096, 1024), (16384, 4096))] == [32, 64, 128, 256]
-    assert plan(m.MQA_PROJ_LINEAR, 512, 1 << 23, 1, 4096) == 0            # rows of a tile 8 GiB apart
+    assert plan(m.MQA_PROJ_LINEAR, 512, 1 << 24, 1, 4096) == 0            # 64 rows of a tile reach over 4 GiB
     assert kv(4, 64, 0, 1, 20, 16, m.MQA_BF16) == -2 and kv(4, 64, 0, 1, 16, 16, 7) == -5 and kv(4, 64, -1, 1, 16, 16, m.MQA_BF16) == -2
     assert kv(1 << 15, 1024, 0, 1, 128, 128, m.MQA_BF16) == 1 and kv(1 << 15, 1024, 0, 1, 128, 128, m.MQA_F32) == 0
     assert kv(128, 1024, 8, 8, 128, 128, m.MQA_BF16) == 0 and kv(128, 1024, 0, 1, 128, 128, m.MQA_BF16) == 0
