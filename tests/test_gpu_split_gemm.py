@@ -74,14 +74,30 @@ SIZES = [
 EDGES = [(128, 1601, 136, 2056), (256, 4097, 136, 4104), (32, 500, 1000, 1000), (64, 1001, 1000, 1000)]
 
 
+def kept_in_terms(a, top, known):
+    """Do the fp16 terms hold all lines of a [lines, C], scaled such that `known` (per line) comes to 2^top?"""
+    x = torch.nn.functional.pad(a.abs() * (2.0 ** top / known)[:, None], (0, -a.shape[1] % 8)).view(a.shape[0], -1, 8)
+    octets = (x > 0).any(2).sum(1)
+    short = ((x > 0) & (x < 2.0 ** -4)).any(2).sum(1)
+    return bool(((short <= torch.where(octets < 8, 0, 2 + octets // 8)) & (x.amax((1, 2)) < 65520)).all())
+
+
+@pytest.mark.parametrize("spread", [0, 4])
 @pytest.mark.parametrize("layout", ["n", "c"])
 @pytest.mark.parametrize("tiles,rows,C,N", SIZES)
-def test_split_gemm(m, layout, tiles, rows, C, N):
+def test_split_gemm(m, layout, tiles, rows, C, N, spread):
+    """spread 0: fp16 terms throughout; 4: columns of W too wide for them, float32 instructions."""
     assert tiles_of(m, layout, rows, C, N) == tiles
     g = torch.Generator(device=DEV)
     g.manual_seed(rows + C + N)
     x = torch.randn(rows, C, generator=g, device=DEV) * torch.exp(3 * torch.randn(rows, 1, generator=g, device=DEV))
-    W = torch.randn(C, N, generator=g, device=DEV) * torch.exp(2 * torch.randn(C, 1, generator=g, device=DEV))
+    W = torch.randn(C, N, generator=g, device=DEV) * torch.exp(spread * torch.randn(C, 1, generator=g, device=DEV))
+    if C >= 64:                                # (shorter ones are not tried in terms)
+        for a in (x, W.t()):
+            # at the smallest scale that the first 32 to 128 indices lead to / the largest that the line allows
+            if spread == 0:
+                assert kept_in_terms(a, 9, a[:, :128].abs().amax(1))
+        assert spread == 0 or not kept_in_terms(W.t(), 15, W.abs().amax(0))
     ref, most = x.double() @ W.double(), bound(x, W)
     assert ((product(m, layout, x, W).double() - ref).abs() <= most).all()
     got = product(m, layout, x, W, epilogue=m.MQA_EPI_RELU)
