@@ -155,10 +155,25 @@ int mqa_project_append_kv_rows(const float* x, const float* P_k, const float* P_
                                int k, int v, mqa_dtype dt, void* stream);
 
 /*
+ * mqa_project_append_kv_rows and mqa_project_memory_kv (below) with scratch memory for the call: given
+ * mqa_project_kv_workspace_bytes(...) bytes (16-byte aligned; b sequences of n rows) the weights are prepared once, in a
+ * launch of its own, instead of by every tile of rows (32768 rows, d = 1024: 205 us without, about half with).  0 means
+ * that this shape uses none; given less (or NULL) the call is the one without.  Same rows either way.  The workspace is
+ * written and read by this call's launches only.
+ */
+size_t mqa_project_kv_workspace_bytes(int b, int n, int d, int h_kv, int k, int v, mqa_dtype dt);
+int mqa_project_append_kv_rows_ws(const float* x, const float* P_k, const float* P_v, void* K, void* V,
+                                  const int32_t* lens_in, int32_t* lens_out, int b, int n, int d, int h_kv, int cap,
+                                  int k, int v, mqa_dtype dt, void* workspace, size_t workspace_bytes, void* stream);
+int mqa_project_memory_kv_ws(const float* M, const float* P_k, const float* P_v, void* K, void* V,
+                             const int32_t* mem_lens, int32_t* lens, int b, int m, int d, int h_kv, int cap,
+                             int k, int v, mqa_dtype dt, void* workspace, size_t workspace_bytes, void* stream);
+
+/*
  * Which kernel a projection takes (on the host; nothing is launched).  mqa_project_plan: the edge (32, 64, 128, 256) of the
  * tiles of the split-operand kernel that mqa_project_qkvo(_ex) uses for this product, or 0 for the float32 (new K / V rows:
  * float64) kernel.  mqa_project_kv_plan: 1 if the K / V rows of mqa_project_memory_kv and mqa_project_append_kv_rows
- * (h = 0; rows = b*m, b*n) or of mqa_project_append_qkv (h heads of q; rows = b) come from integer products, 0 if
+ * (h = 0; rows = b*m, b*n; with a workspace) or of mqa_project_append_qkv (h heads of q; rows = b) come from integer products, 0 if
  * from float64 ones (the same values).  Negative: -(the status the call itself would return for the sizes).
  */
 int mqa_project_plan(mqa_proj_mode mode, int rows, int d, int h, int kv);

@@ -17,11 +17,11 @@ MQA_PROJ_Q, MQA_PROJ_KV, MQA_PROJ_KV_MH, MQA_PROJ_O, MQA_PROJ_LINEAR = 0, 1, 2, 
 MQA_EPI_STORE, MQA_EPI_RELU, MQA_EPI_ADD = 0, 1, 2
 
 EXPORTS = [
-    "mqa_project_qkvo", "mqa_project_qkvo_ex", "mqa_project_append_qkv", "mqa_project_append_kv_rows", "mqa_project_plan", "mqa_project_kv_plan", "mqa_append_kv", "mqa_decode_step", "mha_decode_step",
+    "mqa_project_qkvo", "mqa_project_qkvo_ex", "mqa_project_append_qkv", "mqa_project_append_kv_rows", "mqa_project_append_kv_rows_ws", "mqa_project_kv_workspace_bytes", "mqa_project_plan", "mqa_project_kv_plan", "mqa_append_kv", "mqa_decode_step", "mha_decode_step",
     "mqa_decode_step_window", "mha_decode_step_window", "mqa_append_kv_rows", "mqa_prefill_attention", "mha_prefill_attention",
     "mqa_decode_step_beams", "mqa_decode_beams_workspace_bytes", "mqa_beam_reorder_kv", "mqa_decode_step_ex", "mha_decode_step_ex", "mqa_decode_partials", "mqa_decode_combine",
     "mqa_decode_workspace_bytes", "mha_decode_workspace_bytes", "mqa_decode_workspace_bytes_default", "mqa_decode_num_splits",
-    "mqa_decode_plan", "mqa_decode_step_noalloc", "mqa_project_memory_kv", "mqa_memory_decode_step",
+    "mqa_decode_plan", "mqa_decode_step_noalloc", "mqa_project_memory_kv", "mqa_project_memory_kv_ws", "mqa_memory_decode_step",
     "mqa_stream_read", "mqa_stream_copy", "mqa_status_string",
     "mqa_stack_layernorm", "mqa_stack_embed", "mqa_stack_add", "mqa_stack_relu", "mqa_stack_argmax",
 ]
@@ -56,6 +56,10 @@ def load_library(path: str = LIB_PATH):
     lib.mqa_project_qkvo_ex.argtypes = [ci, vp, vp, vp, ci, ci, ci, ci, ci, vp]
     lib.mqa_project_append_qkv.argtypes = [vp] * 9 + [ci] * 8 + [vp]
     lib.mqa_project_append_kv_rows.argtypes = [vp] * 7 + [ci] * 8 + [vp]
+    lib.mqa_project_append_kv_rows_ws.argtypes = [vp] * 7 + [ci] * 8 + [vp, sz, vp]
+    lib.mqa_project_memory_kv_ws.argtypes = [vp] * 7 + [ci] * 8 + [vp, sz, vp]
+    lib.mqa_project_kv_workspace_bytes.argtypes = [ci] * 7
+    lib.mqa_project_kv_workspace_bytes.restype = sz
     lib.mqa_project_plan.argtypes = [ci] * 5
     lib.mqa_project_kv_plan.argtypes = [ci] * 7
     lib.mqa_append_kv.argtypes = [vp, vp, vp, vp, vp, ci, ci, ci, ci, ci, ci, vp]
@@ -97,7 +101,7 @@ def load_library(path: str = LIB_PATH):
     lib.mqa_status_string.restype = ctypes.c_char_p
     for name in EXPORTS:
         if name not in ("mqa_decode_workspace_bytes", "mha_decode_workspace_bytes", "mqa_status_string",
-                        "mqa_decode_beams_workspace_bytes", "mqa_decode_workspace_bytes_default"):
+                        "mqa_decode_beams_workspace_bytes", "mqa_decode_workspace_bytes_default", "mqa_project_kv_workspace_bytes"):
             getattr(lib, name).restype = ci
     _lib = lib
     return lib
@@ -192,6 +196,18 @@ def _default_workspace(device, nbytes, stream=None):
             ws = torch.empty(nbytes, dtype=torch.uint8, device=device)
         _ws_cache[key] = ws
     return ws
+
+
+def _call_workspace(nbytes, device, stream):
+    """Scratch memory for one call of several launches, and its size: a block of torch's caching allocator, allocated
+    with the call's stream current, so that it goes to later work of that stream only (calls of other threads
+    on the same stream get blocks of their own)."""
+    if nbytes == 0:
+        return None, 0
+    if stream is None:
+        return torch.empty(nbytes, dtype=torch.uint8, device=device), nbytes
+    with torch.cuda.stream(stream):
+        return torch.empty(nbytes, dtype=torch.uint8, device=device), nbytes
 
 
 def mqa_decode_num_splits(b, h, cap, k, v, dt, multi_head=False, tuning=None) -> int:
@@ -407,10 +423,12 @@ def mqa_project_append_kv_rows(x, P_k, P_v, K, V, lens_in, lens_out, stream=None
             or K.shape != ((b, cap, k) if one else (b, h_kv, cap, k)) or V.shape != ((b, cap, v) if one else (b, h_kv, cap, v))
             or K.dtype != V.dtype or lens_in.numel() != b or lens_out.numel() != b):
         raise ValueError("shape mismatch in mqa_project_append_kv_rows")
-    rc = lib.mqa_project_append_kv_rows(_ptr(x), _ptr(P_k), _ptr(P_v), _ptr(K), _ptr(V), _ptr(lens_in), _ptr(lens_out),
-                                        b, n, d, h_kv, cap, k, v, _cache_dtype(K), _stream(stream))
+    dt = _cache_dtype(K)
+    ws, nbytes = _call_workspace(lib.mqa_project_kv_workspace_bytes(b, n, d, h_kv, k, v, dt), x.device, stream)
+    rc = lib.mqa_project_append_kv_rows_ws(_ptr(x), _ptr(P_k), _ptr(P_v), _ptr(K), _ptr(V), _ptr(lens_in), _ptr(lens_out),
+                                           b, n, d, h_kv, cap, k, v, dt, _ptr(ws), nbytes, _stream(stream))
     if rc != 0:
-        raise MqaError("mqa_project_append_kv_rows", rc)
+        raise MqaError("mqa_project_append_kv_rows", "mqa_project_append_kv_rows_ws", "mqa_project_kv_workspace_bytes", rc)
 
 
 def mqa_project_memory_kv(M, P_k, P_v, K, V, lens, mem_lens=None, stream=None):
@@ -431,10 +449,12 @@ def mqa_project_memory_kv(M, P_k, P_v, K, V, lens, mem_lens=None, stream=None):
             or (K.dim() == 3) != (P_k.dim() == 2) or K.shape != kshape or V.shape != kshape[:-1] + (v,)
             or K.dtype != V.dtype or lens.numel() != b or (mem_lens is not None and mem_lens.numel() != b)):
         raise ValueError("shape mismatch in mqa_project_memory_kv")
-    rc = lib.mqa_project_memory_kv(_ptr(M), _ptr(P_k), _ptr(P_v), _ptr(K), _ptr(V), _ptr(mem_lens), _ptr(lens),
-                                   b, m, d, h_kv, cap, k, v, _cache_dtype(K), _stream(stream))
+    dt = _cache_dtype(K)
+    ws, nbytes = _call_workspace(lib.mqa_project_kv_workspace_bytes(b, m, d, h_kv, k, v, dt), M.device, stream)
+    rc = lib.mqa_project_memory_kv_ws(_ptr(M), _ptr(P_k), _ptr(P_v), _ptr(K), _ptr(V), _ptr(mem_lens), _ptr(lens),
+                                      b, m, d, h_kv, cap, k, v, dt, _ptr(ws), nbytes, _stream(stream))
     if rc != 0:
-        raise MqaError("mqa_project_memory_kv", rc)
+        raise MqaError("mqa_project_memory_kv", "mqa_project_memory_kv_ws", rc)
 
 
 def mqa_memory_decode_step(q, K, V, lens, o=None, scale=1.0, workspace=None, stream=None):

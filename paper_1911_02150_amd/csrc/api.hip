@@ -274,6 +274,26 @@ int project_impl(int mode, const float* in, const float* P, float* out, int rows
   return MQA_OK;
 }
 
+// n new K / V rows per sequence: a memory's, or behind the lens_in[] rows there are (append).
+int kv_rows_impl(const float* x, const float* P_k, const float* P_v, void* K, void* V, const int32_t* lens_in, int32_t* lens_out,
+                 int b, int n, int append, int d, int h_kv, int cap, int k, int v, int dt, void* workspace,
+                 size_t workspace_bytes, void* stream) {
+  if (!x || !P_k || !P_v || !K || !V || !lens_out) return MQA_ERR_NULL;
+  if (dt != MQA_F32 && dt != MQA_BF16) return MQA_ERR_DTYPE;
+  if (b <= 0 || n <= 0 || d <= 0 || h_kv <= 0 || cap <= 0 || k <= 0 || v <= 0 || n > cap) return MQA_ERR_SHAPE;
+  if ((d & 7) || (k & 15) || (v & 15) || (long long)b * n > (1ll << 30)) return MQA_ERR_SHAPE;
+  if (misaligned(x) || misaligned(P_k) || misaligned(P_v) || misaligned(K) || misaligned(V) || misaligned(lens_out) ||
+      (lens_in && misaligned(lens_in)) || (workspace && misaligned(workspace)))
+    return MQA_ERR_ALIGN;
+  hipStream_t st = static_cast<hipStream_t>(stream);
+  const size_t want = workspace ? mqa_project_kv_workspace_bytes(b, n, d, h_kv, k, v, (mqa_dtype)dt) : 0;
+  const hipError_t e = want && workspace_bytes >= want
+                           ? launch_project_kv_rows(x, P_k, P_v, K, V, lens_in, lens_out, b * n, n, append, d, h_kv, cap, k, v, workspace, st)
+                           : launch_project_qkv_append(x, nullptr, P_k, P_v, nullptr, K, V, lens_in, lens_out, b * n, d, 0, h_kv,
+                                                       cap, k, v, dt == MQA_BF16, n, append, st);
+  return e == hipSuccess ? MQA_OK : MQA_ERR_LAUNCH;
+}
+
 }  // namespace
 
 extern "C" {
@@ -568,39 +588,41 @@ int mqa_project_plan(mqa_proj_mode mode, int rows, int d, int h, int kv) {
 int mqa_project_kv_plan(int rows, int d, int h, int h_kv, int k, int v, mqa_dtype dt) {
   if (dt != MQA_F32 && dt != MQA_BF16) return -MQA_ERR_DTYPE;
   if (rows <= 0 || d <= 0 || h < 0 || h_kv <= 0 || k <= 0 || v <= 0 || (d & 7) || (k & 15) || (v & 15)) return -MQA_ERR_SHAPE;
-  return dt == MQA_BF16 && (h == 0 || gemm_form(MQA_PROJ_Q, rows, d, h, k, kApart)) && project_kv_exact_pays(rows, d, h_kv, k, v);
+  if (dt != MQA_BF16) return 0;
+  if (h == 0) return project_kv_exact_pays(rows, d, h_kv, k, v) || project_kv_rows_pays(rows, d, h_kv, k, v);
+  return gemm_form(MQA_PROJ_Q, rows, d, h, k, kApart) && project_kv_exact_pays(rows, d, h_kv, k, v);
 }
 
 int mqa_project_append_kv_rows(const float* x, const float* P_k, const float* P_v, void* K, void* V,
                                const int32_t* lens_in, int32_t* lens_out, int b, int n, int d, int h_kv, int cap,
                                int k, int v, mqa_dtype dt, void* stream) {
-  if (!x || !P_k || !P_v || !K || !V || !lens_in || !lens_out) return MQA_ERR_NULL;
-  if (dt != MQA_F32 && dt != MQA_BF16) return MQA_ERR_DTYPE;
-  if (b <= 0 || n <= 0 || d <= 0 || h_kv <= 0 || cap <= 0 || k <= 0 || v <= 0 || n > cap) return MQA_ERR_SHAPE;
-  if ((d & 7) || (k & 15) || (v & 15) || (long long)b * n > (1ll << 30) || lens_in == lens_out) return MQA_ERR_SHAPE;
-  if (misaligned(x) || misaligned(P_k) || misaligned(P_v) || misaligned(K) || misaligned(V) || misaligned(lens_in) ||
-      misaligned(lens_out))
-    return MQA_ERR_ALIGN;
-  if (launch_project_qkv_append(x, nullptr, P_k, P_v, nullptr, K, V, lens_in, lens_out, b * n, d, 0, h_kv, cap, k, v,
-                                dt == MQA_BF16, n, 1, static_cast<hipStream_t>(stream)) != hipSuccess)
-    return MQA_ERR_LAUNCH;
-  return MQA_OK;
+  return mqa_project_append_kv_rows_ws(x, P_k, P_v, K, V, lens_in, lens_out, b, n, d, h_kv, cap, k, v, dt, nullptr, 0, stream);
+}
+
+int mqa_project_append_kv_rows_ws(const float* x, const float* P_k, const float* P_v, void* K, void* V,
+                                  const int32_t* lens_in, int32_t* lens_out, int b, int n, int d, int h_kv, int cap,
+                                  int k, int v, mqa_dtype dt, void* workspace, size_t workspace_bytes, void* stream) {
+  if (!lens_in) return MQA_ERR_NULL;
+  if (lens_in == lens_out) return MQA_ERR_SHAPE;
+  return kv_rows_impl(x, P_k, P_v, K, V, lens_in, lens_out, b, n, 1, d, h_kv, cap, k, v, (int)dt, workspace, workspace_bytes, stream);
 }
 
 int mqa_project_memory_kv(const float* M, const float* P_k, const float* P_v, void* K, void* V,
                           const int32_t* mem_lens, int32_t* lens, int b, int m, int d, int h_kv, int cap,
                           int k, int v, mqa_dtype dt, void* stream) {
-  if (!M || !P_k || !P_v || !K || !V || !lens) return MQA_ERR_NULL;
-  if (dt != MQA_F32 && dt != MQA_BF16) return MQA_ERR_DTYPE;
-  if (b <= 0 || m <= 0 || d <= 0 || h_kv <= 0 || cap <= 0 || k <= 0 || v <= 0 || m > cap) return MQA_ERR_SHAPE;
-  if ((d & 7) || (k & 15) || (v & 15) || (long long)b * m > (1ll << 30)) return MQA_ERR_SHAPE;
-  if (misaligned(M) || misaligned(P_k) || misaligned(P_v) || misaligned(K) || misaligned(V) || misaligned(lens) ||
-      (mem_lens && misaligned(mem_lens)))
-    return MQA_ERR_ALIGN;
-  if (launch_project_qkv_append(M, nullptr, P_k, P_v, nullptr, K, V, mem_lens, lens, b * m, d, 0, h_kv, cap, k, v,
-                                dt == MQA_BF16, m, 0, static_cast<hipStream_t>(stream)) != hipSuccess)
-    return MQA_ERR_LAUNCH;
-  return MQA_OK;
+  return mqa_project_memory_kv_ws(M, P_k, P_v, K, V, mem_lens, lens, b, m, d, h_kv, cap, k, v, dt, nullptr, 0, stream);
+}
+
+int mqa_project_memory_kv_ws(const float* M, const float* P_k, const float* P_v, void* K, void* V,
+                             const int32_t* mem_lens, int32_t* lens, int b, int m, int d, int h_kv, int cap,
+                             int k, int v, mqa_dtype dt, void* workspace, size_t workspace_bytes, void* stream) {
+  return kv_rows_impl(M, P_k, P_v, K, V, mem_lens, lens, b, m, 0, d, h_kv, cap, k, v, (int)dt, workspace, workspace_bytes, stream);
+}
+
+size_t mqa_project_kv_workspace_bytes(int b, int n, int d, int h_kv, int k, int v, mqa_dtype dt) {
+  if (dt != MQA_BF16 || b <= 0 || n <= 0 || d <= 0 || h_kv <= 0 || k <= 0 || v <= 0) return 0;
+  if ((d & 7) || (k & 15) || (v & 15) || (long long)b * n > (1ll << 30) || !project_kv_rows_pays(b * n, d, h_kv, k, v)) return 0;
+  return project_kv_rows_workspace(d, h_kv, k, v);
 }
 
 int mqa_memory_decode_step(const float* q, const void* K, const void* V, const int32_t* lens, float* o,

@@ -134,6 +134,13 @@ hipError_t launch_project_kv_exact(const float* x, const float* P_k, const float
                                    const int32_t* lens_in, int32_t* lens_out, int rows, int n, int append, int d, int h_kv,
                                    int cap, int k, int v, hipStream_t st);
 
+// project_kv_rows.hip: the same from a workspace of project_kv_rows_workspace(...) bytes (not append: lens_in may be null)
+bool project_kv_rows_pays(int rows, int d, int h_kv, int k, int v);
+size_t project_kv_rows_workspace(int d, int h_kv, int k, int v);
+hipError_t launch_project_kv_rows(const float* x, const float* P_k, const float* P_v, void* K, void* V,
+                                  const int32_t* lens_in, int32_t* lens_out, int rows, int n, int append, int d, int h_kv,
+                                  int cap, int k, int v, void* workspace, hipStream_t st);
+
 // stack_kernels.hip
 hipError_t launch_layernorm(const float* x, float* y, int rows, int d, float eps, hipStream_t st);
 hipError_t launch_embed(const int32_t* tokens, const int32_t* pos, const float* E, const float* P, float* x,

@@ -1,4 +1,5 @@
-// New K / V rows of many positions at once (a memory, a prompt) into a bf16 cache: the correctly rounded
+// New K / V rows of many positions at once (a memory, a prompt, for callers without a workspace: project_kv_rows.hip is the
+// faster one with; or one position of very many sequences) into a bf16 cache: the correctly rounded
 // value of the product, which is what the float64 kernel of project.hip writes, without its cost.  (Where the products
 // cancel so far that the rounding of the float64 sums themselves decides the bf16 value, the order of those sums shows,
 // as it does between any two float64 kernels.)
@@ -25,16 +26,14 @@
 // operands finds the largest values (they come from L2 the second time); then stages of 32 contraction indices go
 // global -> registers (one stage ahead) -> digits -> LDS (two buffers, one barrier per stage), waves 0..3 staging
 // rows before they multiply, waves 4..7 columns after they have.
-#include "common.hpp"
+#include "kv_fixed.hpp"
 
 #include <type_traits>
 
 namespace mqa {
 namespace {
 
-typedef __attribute__((ext_vector_type(4))) int int4v;
-typedef __attribute__((ext_vector_type(16))) int int16v;
-typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
+using namespace kv_fixed;
 
 constexpr int kTile = 128;
 constexpr int kBlock = 64 * 16 + 64;            // 16 indices of 64 lines, 16 bytes per line; what eight lanes write (four rows' two
@@ -42,12 +41,6 @@ constexpr int kHalf = 2 * kBlock;              // halves, or four columns of eac
 constexpr int kPlane = 2 * kHalf;              // one digit of 32 indices
 constexpr int kOperand = 4 * kPlane;
 constexpr int kStage = 2 * kOperand;
-// Open elements of a tile from which its waves sum all of it in float64 instead.  A wave spends some 8 us on one element (the
-// weights are a cache line each), the whole tile takes 270 us: us for 32768 rows, d = 1024, with one channel of the rows 2^6
-// times the others and its weights as much smaller (210 open elements a tile) one by one 439, all 485; 2^8 times (650) 978
-// and 481; 2^10 times 2419 and 478; the float64 kernel takes 410, normal deviates 213.
-constexpr int kMostOpen = 256;
-constexpr int kMaxC = 16384;                   // four products of 2^14 per index in an int32
 
 struct KvParams {
   const float* x;                // [rows, C]
@@ -59,75 +52,6 @@ struct KvParams {
   int kv[2], tiles[2];           // columns per head, column tiles of K and V
   int append, tiles_m;
 };
-
-// what the float64 kernel stores
-__device__ __forceinline__ uint32_t to_bf16(double s) { return float_to_bf16_rne((float)s); }
-
-// The scale (a power of two) that takes the largest magnitude `bits` to [2^29, 2^31 - 2^24]: the top digit stays
-// an int8 with what the lower ones carry into it.
-__device__ __forceinline__ int fixed_exponent(uint32_t bits) {           // x . 2^exponent
-  const int e = (int)(bits >> 23);
-  if (e == 0) return 127;                                               // (a subnormal, or zero; 30 .. 254 at most below)
-  int up = 30 + 127 - e;
-  if ((bits & 0x7fffffu) > 0x7d0000u) --up;                             // (2 - 2^-6) 2^30 = 2^31 - 2^24
-  return up > 127 ? 127 : up;
-}
-
-// 32 rows x 64 columns by one wave, in float64 from global memory: register e of lane (i, kk) of a 16 x 16 block is row
-// 4 e + kk, column i; step s contracts the indices 4 kk + s of sixteen.
-template <typename Place>
-__device__ __forceinline__ void float64_tile(const KvParams& p, const float* P, int which, int row0, int n0, int lane, Place&& place) {
-  typedef __attribute__((ext_vector_type(4))) double double4v;
-  const int i = lane & 15, kk = lane >> 4, kv = p.kv[which], N = p.h_kv * kv, C = p.C;
-  const float* xr[2];
-  const float* w[4];
-#pragma unroll
-  for (int r = 0; r < 2; ++r) xr[r] = p.x + (size_t)min(row0 + 16 * r + i, p.rows - 1) * C;
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const int n = min(n0 + 16 * j + i, N - 1);
-    w[j] = P + (size_t)(n / kv) * C * kv + n % kv;
-  }
-  double4v acc[2][4];
-#pragma unroll
-  for (int r = 0; r < 2; ++r)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) acc[r][j] = double4v{0., 0., 0., 0.};
-  for (int c0 = 0; c0 < C; c0 += 16) {
-    const int c = min(c0 + 4 * kk, C - 4);
-    const bool in = c0 + 4 * kk < C;           // (C is a multiple of 8)
-    float a[2][4], b[4][4];
-#pragma unroll
-    for (int r = 0; r < 2; ++r) {
-      const float4 v = *reinterpret_cast<const float4*>(xr[r] + c);
-      a[r][0] = in ? v.x : 0.f; a[r][1] = in ? v.y : 0.f; a[r][2] = in ? v.z : 0.f; a[r][3] = in ? v.w : 0.f;
-    }
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-#pragma unroll
-      for (int s = 0; s < 4; ++s) {
-        const float v = w[j][(size_t)(c + s) * kv];
-        b[j][s] = in ? v : 0.f;
-      }
-#pragma unroll
-    for (int s = 0; s < 4; ++s)
-#pragma unroll
-      for (int r = 0; r < 2; ++r)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[r][j] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)a[r][s], (double)b[j][s], acc[r][j], 0, 0, 0);
-  }
-#pragma unroll
-  for (int r = 0; r < 2; ++r)
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int row = row0 + 16 * r + 4 * e + kk, n = n0 + 16 * j + i;
-        if (row >= p.rows || n >= N) continue;
-        uint16_t* at = place(row, n);
-        if (at) *at = (uint16_t)to_bf16(acc[r][j][e]);
-      }
-}
 
 __global__ __launch_bounds__(512)
 void project_kv_exact_kernel(KvParams p) {
@@ -245,17 +169,10 @@ void project_kv_exact_kernel(KvParams p) {
       int4v d[4];
 #pragma unroll
       for (int w = 0; w < 4; ++w) {            // bytes of four values -> four digits' words
-        uint32_t y[4];
+        const float* x = rg.x + 4 * w;
+        const Digits4 t = digits_of(x[0] * by[w >> 1], x[1] * by[w >> 1], x[2] * by[w >> 1], x[3] * by[w >> 1]);
 #pragma unroll
-        for (int k = 0; k < 4; ++k) y[k] = (uint32_t)((int)(rg.x[4 * w + k] * by[w >> 1])) + 0x00808080u;
-        const uint32_t t0 = __builtin_amdgcn_perm(y[1], y[0], 0x05010400u);           // bytes 0, 0', 1, 1'
-        const uint32_t t1 = __builtin_amdgcn_perm(y[1], y[0], 0x07030602u);           // bytes 2, 2', 3, 3'
-        const uint32_t t2 = __builtin_amdgcn_perm(y[3], y[2], 0x05010400u);
-        const uint32_t t3 = __builtin_amdgcn_perm(y[3], y[2], 0x07030602u);
-        d[0][w] = (int)(__builtin_amdgcn_perm(t2, t0, 0x05040100u) ^ 0x80808080u);
-        d[1][w] = (int)(__builtin_amdgcn_perm(t2, t0, 0x07060302u) ^ 0x80808080u);
-        d[2][w] = (int)(__builtin_amdgcn_perm(t3, t1, 0x05040100u) ^ 0x80808080u);
-        d[3][w] = (int)__builtin_amdgcn_perm(t3, t1, 0x07060302u);
+        for (int q = 0; q < 4; ++q) d[q][w] = t.word[q];
 #pragma unroll
         for (int q = 0; q < 4; ++q) sq[q] = __builtin_amdgcn_sdot4(d[q][w], d[q][w], sq[q], false);
       }
@@ -295,20 +212,12 @@ void project_kv_exact_kernel(KvParams p) {
     }
     return p.dst[which] + (((size_t)seq * p.h_kv + col / kv) * p.cap + at) * kv + col % kv;
   };
-  // What a line (row or column) adds to the bounds, as floats rounded up: 0.2 % covers their own rounding.
-  float* share = reinterpret_cast<float*>(norm);             // [256][4]: |d0|, |d1|, |d2| and sqrt(C) |d3| + C
-  if (tid < 256) {
-    const int d3 = norm[4 * tid + 3];
-    const float a[3] = {(float)norm[4 * tid], (float)norm[4 * tid + 1], (float)norm[4 * tid + 2]};
-#pragma unroll
-    for (int q = 0; q < 3; ++q) share[4 * tid + q] = sqrtf(a[q]) * 1.001f;
-    share[4 * tid + 3] = (sqrtf((float)C) * sqrtf((float)d3) + (float)C) * 1.001f;
-  }
+  // the lines take the places of their sums of squares
+  static_assert(sizeof(Line) <= 16, "a line takes the place of its four sums");
+  auto line_at = [&](int i) -> Line& { return *reinterpret_cast<Line*>(norm + 4 * i); };
+  if (tid < 256) line_at(tid) = line_of(norm + 4 * tid, most[tid], C);
   __syncthreads();
-  const float4 col[2] = {reinterpret_cast<const float4*>(share)[128 + slot], reinterpret_cast<const float4*>(share)[192 + slot]};
-  const uint32_t col_most[2] = {most[128 + slot], most[192 + slot]};
-  const int col_up[2] = {fixed_exponent(col_most[0]), fixed_exponent(col_most[1])};
-  const float rest = 0.52f * (float)C + 2.f;
+  const Line col[2] = {line_at(128 + slot), line_at(192 + slot)};
   for (int chunk = 0; chunk < 4; ++chunk) {
 #pragma unroll
     for (int e4 = 0; e4 < 4; ++e4) {
@@ -323,31 +232,12 @@ void project_kv_exact_kernel(KvParams p) {
             for (int j = 0; j < 2; ++j) t[q][j] = acc[q][j][4 * c + e4];
       const int r = wr * 32 + 8 * chunk + 4 * g + e4, row = row0 + r;
       if (row >= rows || n >= N) continue;
-      const uint32_t row_most = most[r];
-      const int row_up = fixed_exponent(row_most);
-      const float4 mine = reinterpret_cast<const float4*>(share)[r];
+      const Line mine = line_at(r);
       uint32_t out = 0;
       bool open[2];
 #pragma unroll
       for (int j = 0; j < 2; ++j) {
-        // the sum in units of 2^24 (exact in 64 bits), as the float it is rounded to first
-        const float mid = (float)fma((double)t[3][j], 0x1p24, fma((double)t[2][j], 0x1p16, fma((double)t[1][j], 0x1p8, (double)t[0][j])));
-        const float err = (mine.w + col[j].w + rest + 0x1p-8f * (mine.z * col[j].x + mine.y * col[j].y + mine.x * col[j].z)) * 1.001f;
-        const uint32_t bits = __float_as_uint(mid);
-        const int e = (int)(bits >> 23) & 255, e_out = e + 24 - row_up - col_up[j];
-        // the sum's bf16 is open if a tie (the middle of the low 16 bits) is no further off than the bound and the
-        // rounding to float, in units of the last place; one that leaves the normal floats is open as well
-        // (just above a power of two the tie below is in the next binade: half the spacing, 0x4000 below the power itself)
-        const int low = (int)(bits & 0xffffu);
-        const float off = (bits & 0x7f0000u) ? fabsf((float)(low - 0x8000)) - 1.f : (float)min(abs(low - 0x8000) - 1, low + 0x4000 - 2);
-        open[j] = e == 0 || e_out < 2 || e_out > 253 || !(ldexpf(err, 150 - e) < off);
-        uint32_t v = float_to_bf16_rne(__uint_as_float((bits & 0x807fffffu) | (uint32_t)(e_out & 255) << 23));
-        if (row_most == 0 || col_most[j] == 0) { v = 0; open[j] = false; }
-        if (row_most >= 0x7f800000u || col_most[j] >= 0x7f800000u) {
-          open[j] = true;
-          if (row_most > 0x7f800000u || col_most[j] > 0x7f800000u) { v = 0x7fc0u; open[j] = false; }
-        }
-        out |= v << (16 * j);
+        out |= rounded_sum(digit_sum(t[0][j], t[1][j], t[2][j], t[3][j]), mine, col[j], &open[j]) << (16 * j);
         if (open[j]) list[atomicAdd(count, 1)] = (uint16_t)(r << 7 | (2 * slot + j));
       }
       uint16_t* at = place(row, n);
@@ -360,7 +250,16 @@ void project_kv_exact_kernel(KvParams p) {
   }
   __syncthreads();
   const int left = *count;
-  if (left > kMostOpen) float64_tile(p, P, which, row0 + wr * 32, n0 + wc * 64, lane, place);
+  if (left > kMostOpen) {
+    const int r0 = row0 + wr * 32, c0 = n0 + wc * 64;
+    float64_tile(
+        lane, C, [&](int r) { return p.x + (size_t)min(r0 + r, rows - 1) * C; },
+        [&](int c) { const int at = min(c0 + c, N - 1); return P + (size_t)(at / kv) * head_stride + at % kv; }, kv,
+        [&](int r, int c, uint32_t v) {
+          uint16_t* at = r0 + r < rows && c0 + c < N ? place(r0 + r, c0 + c) : nullptr;
+          if (at) *at = (uint16_t)v;
+        });
+  }
   else for (int i = wave; i < left; i += 8) {
     const int r = list[i] >> 7, col = n0 + (list[i] & 127);
     const float* xr = p.x + (size_t)(row0 + r) * C;

@@ -202,3 +202,24 @@ def test_decode_step_to_any_length(m, b, d, h, k, v, integer):
     assert after.tolist() == [L + 1 if 0 <= L < cap else L for L in lens.tolist()]
     want = torch.stack([x.double() @ P_q[j].double() for j in range(h)], 1)
     assert float((q.double() - want).abs().max()) < 1e-5
+
+
+@pytest.mark.parametrize("share", [0, 0.5, 1])
+@pytest.mark.parametrize("b,n,d,heads,k,v", [s for s in SHAPES if s[0] > 3] + [(33, 129, 1032, 0, 32, 16), (9, 1000, 64, 0, 128, 128)])
+def test_rows_with_and_without_a_workspace(m, b, n, d, heads, k, v, share):
+    """The call without a workspace (or with less than it asks for) and the one with: the same rows and lengths, nothing beside
+    them.  One row and one column past tiles of 64 x 128, a contraction that ends in the first octet of a stage of 64."""
+    from paper_1911_02150_amd import binding
+    lib = binding.load_library()
+    x, P_k, P_v = inputs(b, n, d, heads, k, v, n + 5)
+    K, V = caches(b, heads, n + 3, k, v)
+    lens, valid = torch.zeros(b, dtype=torch.int32, device=DEV), torch.arange(b, dtype=torch.int32, device=DEV)
+    nbytes = int(share * lib.mqa_project_kv_workspace_bytes(b, n, d, heads or 1, k, v, m.MQA_BF16))
+    assert share == 0 or nbytes > 0 or (b, n) == (33, 129) or (b, n) == (9, 1000)
+    ws = torch.full((max(16, nbytes),), 255, dtype=torch.uint8, device=DEV)
+    rc = lib.mqa_project_memory_kv_ws(x.data_ptr(), P_k.data_ptr(), P_v.data_ptr(), K.data_ptr(), V.data_ptr(), valid.data_ptr(),
+                                      lens.data_ptr(), b, n, d, heads or 1, n + 3, k, v, m.MQA_BF16, ws.data_ptr() if share else None,
+                                      nbytes, torch.cuda.current_stream().cuda_stream)
+    assert rc == 0
+    assert torch.equal(K[..., :n, :], expected(x, P_k, heads)) and torch.equal(V[..., :n, :], expected(x, P_v, heads))
+    assert (K[..., n:, :] == 7).all() and (V[..., n:, :] == 7).all() and torch.equal(lens, valid.clamp(max=n))
