@@ -428,7 +428,7 @@ def mqa_project_append_kv_rows(x, P_k, P_v, K, V, lens_in, lens_out, stream=None
     rc = lib.mqa_project_append_kv_rows_ws(_ptr(x), _ptr(P_k), _ptr(P_v), _ptr(K), _ptr(V), _ptr(lens_in), _ptr(lens_out),
                                            b, n, d, h_kv, cap, k, v, dt, _ptr(ws), nbytes, _stream(stream))
     if rc != 0:
-        raise MqaError("mqa_project_append_kv_rows", "mqa_project_append_kv_rows_ws", "mqa_project_kv_workspace_bytes", rc)
+        raise MqaError("mqa_project_append_kv_rows", rc)
 
 
 def mqa_project_memory_kv(M, P_k, P_v, K, V, lens, mem_lens=None, stream=None):
@@ -454,7 +454,7 @@ def mqa_project_memory_kv(M, P_k, P_v, K, V, lens, mem_lens=None, stream=None):
     rc = lib.mqa_project_memory_kv_ws(_ptr(M), _ptr(P_k), _ptr(P_v), _ptr(K), _ptr(V), _ptr(mem_lens), _ptr(lens),
                                       b, m, d, h_kv, cap, k, v, dt, _ptr(ws), nbytes, _stream(stream))
     if rc != 0:
-        raise MqaError("mqa_project_memory_kv", "mqa_project_memory_kv_ws", rc)
+        raise MqaError("mqa_project_memory_kv", rc)
 
 
 def mqa_memory_decode_step(q, K, V, lens, o=None, scale=1.0, workspace=None, stream=None):

@@ -223,3 +223,15 @@ def test_rows_with_and_without_a_workspace(m, b, n, d, heads, k, v, share):
     assert rc == 0
     assert torch.equal(K[..., :n, :], expected(x, P_k, heads)) and torch.equal(V[..., :n, :], expected(x, P_v, heads))
     assert (K[..., n:, :] == 7).all() and (V[..., n:, :] == 7).all() and torch.equal(lens, valid.clamp(max=n))
+
+
+def test_refused_sizes_keep_their_error(m):
+    """A size that the library refuses (a head of 20 columns) raises the library's error with its status, from both calls."""
+    x = torch.zeros(2, 3, 64, device=DEV)
+    P = torch.zeros(64, 20, device=DEV)
+    K, V = caches(2, 0, 3, 20, 20)
+    a, b = torch.zeros(2, dtype=torch.int32, device=DEV), torch.zeros(2, dtype=torch.int32, device=DEV)
+    with pytest.raises(m.MqaError, match="mqa_project_memory_kv failed"):
+        m.mqa_project_memory_kv(x, P, P, K, V, a)
+    with pytest.raises(m.MqaError, match="mqa_project_append_kv_rows failed"):
+        m.mqa_project_append_kv_rows(x, P, P, K, V, a, b)
