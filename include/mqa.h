@@ -170,9 +170,20 @@ int mqa_project_memory_kv_ws(const float* M, const float* P_k, const float* P_v,
                              int k, int v, mqa_dtype dt, void* workspace, size_t workspace_bytes, void* stream);
 
 /*
+ * A projection added to the residual and the layernorm that follows: x[r,:] += in . P (mode MQA_PROJ_O or MQA_PROJ_LINEAR, as
+ * mqa_project_qkvo_ex with MQA_EPI_ADD), then y[r,:] = layernorm(x[r,:]) (as mqa_stack_layernorm).  Given
+ * mqa_project_add_layernorm_workspace_bytes(...) bytes (16-byte aligned) the contraction of a decode-sized product is cut
+ * among workgroups, whose parts are summed in the layernorm's launch (128 rows, 4096 x 1024: 27 -> 18 us).  0 means that this shape uses
+ * none; given less (or NULL) the call is the two it stands for.  The workspace is written and read by this call's launches only.
+ */
+size_t mqa_project_add_layernorm_workspace_bytes(mqa_proj_mode mode, int rows, int d, int h, int kv);
+int mqa_project_add_layernorm(mqa_proj_mode mode, const float* in, const float* P, float* x, float* y, int rows, int d, int h,
+                              int kv, float eps, void* workspace, size_t workspace_bytes, void* stream);
+
+/*
  * Which kernel a projection takes (on the host; nothing is launched).  mqa_project_plan: the edge (32, 64, 128, 256) of the
- * tiles of the split-operand kernel that mqa_project_qkvo(_ex) uses for this product, or 0 for the float32 (new K / V rows:
- * float64) kernel.  mqa_project_kv_plan: 1 if the K / V rows of mqa_project_memory_kv and mqa_project_append_kv_rows
+ * tiles of the split-operand kernel that mqa_project_qkvo(_ex) uses for this product, 1 for the three-term kernel of
+ * decode-sized products, or 0 for the float32 (new K / V rows: float64) kernel.  mqa_project_kv_plan: 1 if the K / V rows of mqa_project_memory_kv and mqa_project_append_kv_rows
  * (h = 0; rows = b*m, b*n; with a workspace) or of mqa_project_append_qkv (h heads of q; rows = b) come from integer products, 0 if
  * from float64 ones (the same values).  Negative: -(the status the call itself would return for the sizes).
  */

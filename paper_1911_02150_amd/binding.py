@@ -17,7 +17,7 @@ MQA_PROJ_Q, MQA_PROJ_KV, MQA_PROJ_KV_MH, MQA_PROJ_O, MQA_PROJ_LINEAR = 0, 1, 2, 
 MQA_EPI_STORE, MQA_EPI_RELU, MQA_EPI_ADD = 0, 1, 2
 
 EXPORTS = [
-    "mqa_project_qkvo", "mqa_project_qkvo_ex", "mqa_project_append_qkv", "mqa_project_append_kv_rows", "mqa_project_append_kv_rows_ws", "mqa_project_kv_workspace_bytes", "mqa_project_plan", "mqa_project_kv_plan", "mqa_append_kv", "mqa_decode_step", "mha_decode_step",
+    "mqa_project_qkvo", "mqa_project_qkvo_ex", "mqa_project_add_layernorm", "mqa_project_add_layernorm_workspace_bytes", "mqa_project_append_qkv", "mqa_project_append_kv_rows", "mqa_project_append_kv_rows_ws", "mqa_project_kv_workspace_bytes", "mqa_project_plan", "mqa_project_kv_plan", "mqa_append_kv", "mqa_decode_step", "mha_decode_step",
     "mqa_decode_step_window", "mha_decode_step_window", "mqa_append_kv_rows", "mqa_prefill_attention", "mha_prefill_attention",
     "mqa_decode_step_beams", "mqa_decode_beams_workspace_bytes", "mqa_beam_reorder_kv", "mqa_decode_step_ex", "mha_decode_step_ex", "mqa_decode_partials", "mqa_decode_combine",
     "mqa_decode_workspace_bytes", "mha_decode_workspace_bytes", "mqa_decode_workspace_bytes_default", "mqa_decode_num_splits",
@@ -54,6 +54,9 @@ def load_library(path: str = LIB_PATH):
     dec = [vp, vp, vp, vp, vp, ci, ci, ci, ci, ci, ci, cf, vp, sz, vp]
     lib.mqa_project_qkvo.argtypes = [ci, vp, vp, vp, ci, ci, ci, ci, vp]
     lib.mqa_project_qkvo_ex.argtypes = [ci, vp, vp, vp, ci, ci, ci, ci, ci, vp]
+    lib.mqa_project_add_layernorm.argtypes = [ci, vp, vp, vp, vp, ci, ci, ci, ci, cf, vp, sz, vp]
+    lib.mqa_project_add_layernorm_workspace_bytes.argtypes = [ci] * 5
+    lib.mqa_project_add_layernorm_workspace_bytes.restype = sz
     lib.mqa_project_append_qkv.argtypes = [vp] * 9 + [ci] * 8 + [vp]
     lib.mqa_project_append_kv_rows.argtypes = [vp] * 7 + [ci] * 8 + [vp]
     lib.mqa_project_append_kv_rows_ws.argtypes = [vp] * 7 + [ci] * 8 + [vp, sz, vp]
@@ -101,7 +104,8 @@ def load_library(path: str = LIB_PATH):
     lib.mqa_status_string.restype = ctypes.c_char_p
     for name in EXPORTS:
         if name not in ("mqa_decode_workspace_bytes", "mha_decode_workspace_bytes", "mqa_status_string",
-                        "mqa_decode_beams_workspace_bytes", "mqa_decode_workspace_bytes_default", "mqa_project_kv_workspace_bytes"):
+                        "mqa_decode_beams_workspace_bytes", "mqa_decode_workspace_bytes_default", "mqa_project_kv_workspace_bytes",
+                        "mqa_project_add_layernorm_workspace_bytes"):
             getattr(lib, name).restype = ci
     _lib = lib
     return lib
@@ -576,6 +580,42 @@ def mqa_project_qkvo(mode, x, P, out=None, stream=None):
 def mqa_project_qkvo_ex(mode, x, P, out=None, epilogue=MQA_EPI_STORE, stream=None):
     """As mqa_project_qkvo with an epilogue: MQA_EPI_RELU stores max(x, 0), MQA_EPI_ADD adds to `out`."""
     return _project("mqa_project_qkvo_ex", mode, x, P, out, epilogue, stream)
+
+
+def mqa_project_add_layernorm_workspace_bytes(mode, rows, d, h, kv) -> int:
+    """Scratch bytes that mqa_project_add_layernorm uses for these sizes (0: none)."""
+    return int(load_library().mqa_project_add_layernorm_workspace_bytes(int(mode), rows, d, h, kv))
+
+
+def mqa_project_add_layernorm(mode, x, P, acc, out=None, eps=1e-6, workspace=None, stream=None):
+    """acc += x . P (mode O: x [rows,h,kv], P [h,d,kv]; LINEAR: x [rows,d], P [d,kv]), then out = layernorm(acc).  Returns out."""
+    lib = load_library()
+    _check(x, "in", torch.float32), _check(P, "P", torch.float32), _check(acc, "acc", torch.float32)
+    rows = x.shape[0]
+    if mode == MQA_PROJ_LINEAR:
+        (d, kv), h = P.shape, 1
+        ok, width = x.shape == (rows, d), kv
+    elif mode == MQA_PROJ_O:
+        h, d, kv = P.shape
+        ok, width = x.shape == (rows, h, kv), d
+    else:
+        raise ValueError("mqa_project_add_layernorm: mode O or LINEAR")
+    if not ok or acc.shape != (rows, width):
+        raise ValueError(f"shape mismatch: in {tuple(x.shape)} P {tuple(P.shape)} acc {tuple(acc.shape)} mode {mode}")
+    if out is None:
+        out = torch.empty_like(acc)
+    _check(out, "out", torch.float32)
+    if out.shape != acc.shape:
+        raise ValueError("out has the wrong size")
+    if workspace is None:
+        workspace, nbytes = _call_workspace(lib.mqa_project_add_layernorm_workspace_bytes(mode, rows, d, h, kv), x.device, stream)
+    else:
+        nbytes = workspace.numel() * workspace.element_size()
+    rc = lib.mqa_project_add_layernorm(mode, _ptr(x), _ptr(P), _ptr(acc), _ptr(out), rows, d, h, kv, float(eps), _ptr(workspace), nbytes,
+                                       _stream(stream))
+    if rc != 0:
+        raise MqaError("mqa_project_add_layernorm", rc)
+    return out
 
 
 def mqa_stream_read(src, sink, stream=None):

@@ -582,7 +582,30 @@ int mqa_project_plan(mqa_proj_mode mode, int rows, int d, int h, int kv) {
   if ((int)mode < 0 || (int)mode > 4) return -MQA_ERR_DTYPE;
   if (mode == MQA_PROJ_KV || mode == MQA_PROJ_LINEAR) h = 1;
   if (rows <= 0 || d <= 0 || h <= 0 || kv <= 0 || (d & 7) || (kv & 7)) return -MQA_ERR_SHAPE;
-  return (mode == MQA_PROJ_KV || mode == MQA_PROJ_KV_MH) ? 0 : gemm_form(mode, rows, d, h, kv, 0);
+  if (mode == MQA_PROJ_KV || mode == MQA_PROJ_KV_MH) return 0;
+  return terms_form(mode == MQA_PROJ_O, rows, d, h, kv).S ? 1 : gemm_form(mode, rows, d, h, kv, 0);
+}
+
+size_t mqa_project_add_layernorm_workspace_bytes(mqa_proj_mode mode, int rows, int d, int h, int kv) {
+  if (mode == MQA_PROJ_LINEAR) h = 1;
+  if ((mode != MQA_PROJ_LINEAR && mode != MQA_PROJ_O) || rows <= 0 || d <= 0 || h <= 0 || kv <= 0 || (d & 7) || (kv & 7)) return 0;
+  return terms_parts_bytes(mode == MQA_PROJ_O, rows, d, h, kv);
+}
+
+int mqa_project_add_layernorm(mqa_proj_mode mode, const float* in, const float* P, float* x, float* y, int rows, int d, int h, int kv,
+                              float eps, void* workspace, size_t workspace_bytes, void* stream) {
+  if (!in || !P || !x || !y) return MQA_ERR_NULL;
+  if (mode != MQA_PROJ_LINEAR && mode != MQA_PROJ_O) return MQA_ERR_DTYPE;
+  if (mode == MQA_PROJ_LINEAR) h = 1;
+  if (rows <= 0 || d <= 0 || h <= 0 || kv <= 0 || (d & 7) || (kv & 7)) return MQA_ERR_SHAPE;
+  if (misaligned(in) || misaligned(P) || misaligned(x) || misaligned(y) || (workspace && misaligned(workspace))) return MQA_ERR_ALIGN;
+  const size_t want = workspace ? mqa_project_add_layernorm_workspace_bytes(mode, rows, d, h, kv) : 0;
+  hipStream_t st = static_cast<hipStream_t>(stream);
+  if (want && workspace_bytes >= want)
+    return launch_project_add_layernorm(mode == MQA_PROJ_O, in, P, x, y, rows, d, h, kv, eps, workspace, st) == hipSuccess ? MQA_OK : MQA_ERR_LAUNCH;
+  const int rc = project_impl(mode, in, P, x, rows, d, h, kv, MQA_EPI_ADD, stream);
+  if (rc != MQA_OK) return rc;
+  return launch_layernorm(x, y, rows, mode == MQA_PROJ_O ? d : kv, eps, st) == hipSuccess ? MQA_OK : MQA_ERR_LAUNCH;
 }
 
 int mqa_project_kv_plan(int rows, int d, int h, int h_kv, int k, int v, mqa_dtype dt) {

@@ -134,6 +134,16 @@ hipError_t launch_project_kv_exact(const float* x, const float* P_k, const float
                                    const int32_t* lens_in, int32_t* lens_out, int rows, int n, int append, int d, int h_kv,
                                    int cap, int k, int v, hipStream_t st);
 
+// project_terms.hip: decode-sized products; tiles of 16 RB x 16 CB, the contraction cut among S workgroups (S = 0: not there)
+struct TermsForm { int RB, CB, S; };
+TermsForm terms_form(bool outp, int rows, int d, int h, int kv);
+TermsForm terms_parts_form(bool outp, int rows, int d, int h, int kv);
+size_t terms_parts_bytes(bool outp, int rows, int d, int h, int kv);
+hipError_t launch_project_terms(bool outp, const float* in, const float* P, float* out, int rows, int d, int h, int kv, int epilogue,
+                                hipStream_t st);
+hipError_t launch_project_add_layernorm(bool outp, const float* in, const float* P, float* x, float* y, int rows, int d, int h, int kv,
+                                        float eps, void* workspace, hipStream_t st);
+
 // project_kv_rows.hip: the same from a workspace of project_kv_rows_workspace(...) bytes (not append: lens_in may be null)
 bool project_kv_rows_pays(int rows, int d, int h_kv, int k, int v);
 size_t project_kv_rows_workspace(int d, int h_kv, int k, int v);

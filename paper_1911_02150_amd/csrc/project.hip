@@ -333,6 +333,8 @@ hipError_t launch_project(int mode, const float* in, const float* P, float* out,
   const bool outp = (mode == 3);
   const bool f64 = (mode == 1 || mode == 2);        // new K / V rows: float64 accumulation, split-contraction kernel only
   if (!f64) {
+    const hipError_t terms = launch_project_terms(outp, in, P, out, rows, d, h, kv, epilogue, st);     // a round of larger tiles (project_terms.hip)
+    if (terms != hipErrorNotSupported) return terms;
     const hipError_t big = launch_gemm_tiled(mode, in, P, out, rows, d, h, kv, epilogue, 0, st);     // large GEMMs: the split-operand kernel (gemm.hip)
     if (big != hipErrorNotSupported) return big;
   }

@@ -1,0 +1,356 @@
+// Projections of a decode step's rows: out[rows, N] = in[rows, C] . B[C, N], B addressed inside the projection tensor
+// P [h, d, kv] as in project.hip, from three bfloat16 terms per float32 operand.
+//
+// x = a1 + a2 + a3, each the nearest bfloat16 of what the ones before it leave: exact (8 + 8 + 8 significant bits) for
+// 2^-110 <= |x| < 2^127, off by at most 2^-134 below.  Of the nine products of terms the six largest are added,
+//   a1 b1 + (a1 b2 + a2 b1) + (a1 b3 + a2 b2 + a3 b1)          (the rest is below 2^-24 |a||b|, 2^-27 typically)
+// on v_mfma_f32_16x16x32_bf16: 6 / 16 of the time of the float32 instructions, and one rounding of the running sum for every 32
+// indices and product of terms where they round for every four.  No scales are needed (bfloat16 has float32's exponents),
+// so nothing has to be known of a row or column before it is multiplied.  A wave that meets an infinity or a value from 2^127 on (its
+// first term would be one) multiplies those 32 indices on v_mfma_f32_16x16x4_f32, from the same registers.  Relative error
+// of a 1024-term sum of normal deviates 1.6e-7 (project.hip 2.1e-7, gemm.hip 1.6e-7), of a 4096-term one in four parts 1.7e-7 (4.1e-7).
+//
+// As in project.hip the waves of a workgroup cut the contraction among them and are summed through LDS; operands come
+// from L2 straight into their registers, two steps in flight.  S > 1: the contraction is cut among S workgroups as well, and their
+// partial tiles (in the workspace) are summed by finish_kernel, together with what follows the product: the residual and
+// the next layernorm.
+// Measured (128 rows, 4096 x 1024, weights from HBM): 15 us + 3.5 of finish_kernel (project.hip 25 and a layernorm of 3); 64 rows: 13.5
+// with both (22).  Of the 15: vector instructions 7 (splitting: 11 for two values), matrix cores 3, the first operands 3; on
+// the float32 instructions alone it takes the same time (they need no splitting, and 8 us).  Tiles of 64 x 64: 29 (spills), of
+// 64 x 32: 19.5.
+#include "common.hpp"
+
+#include <math.h>
+
+namespace mqa {
+namespace {
+
+typedef __attribute__((ext_vector_type(4))) float floatx4;
+typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
+typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
+
+constexpr int kWaves = 8, kStep = 32;          // (a step: the indices of one instruction)
+
+struct Terms { u32x4 t[3]; };                  // eight values
+
+__device__ __forceinline__ void split3(float a, float b, Terms& x, int at) {
+#pragma unroll
+  for (int p = 0; p < 3; ++p) {
+    uint32_t u = pack_bf16_pair(a, b);
+    asm("" : "+v"(u));                         // (the halves are read from the packed register, not rounded once more each)
+    x.t[p][at] = u;
+    a -= __uint_as_float(u << 16);
+    b -= __uint_as_float(u & 0xffff0000u);
+  }
+}
+
+template <bool KC, int RB, int CB>
+__global__ __launch_bounds__(kWaves * 64, 2)
+void project_terms_kernel(const float* __restrict__ in, const float* __restrict__ P, float* out, float* part,
+                          int rows, int d, int h, int kv, int epilogue) {
+  constexpr int TM = RB * 16, TN = CB * 16;
+  extern __shared__ __align__(16) float red_raw[];
+  float (*red)[TM * TN] = reinterpret_cast<float (*)[TM * TN]>(red_raw);
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int i = lane & 15, kk = lane >> 4;
+  const int C = KC ? h * kv : d, N = KC ? d : h * kv;
+  const int n0 = blockIdx.x * TN, row0 = blockIdx.y * TM;
+  const int steps = (C + kStep - 1) / kStep, per = (steps + gridDim.z - 1) / gridDim.z;
+  const int first = blockIdx.z * per, end = min(first + per, steps);
+
+  const float* arow[RB];
+#pragma unroll
+  for (int r = 0; r < RB; ++r) arow[r] = in + (size_t)min(row0 + 16 * r + i, rows - 1) * C;
+  int ncol[CB];                                // c contiguous: column n0 + 16 j + i of block j; else the lane's CB adjacent columns
+#pragma unroll
+  for (int j = 0; j < CB; ++j) ncol[j] = min(n0 + 16 * j + i, N - 1);
+  const int nb = min(n0 + CB * i, N - CB);
+  const float* bcol = P + (size_t)(nb / kv) * d * kv + nb % kv;
+
+  typedef __attribute__((ext_vector_type(CB))) float vec;
+  struct Raw { float a[RB][8]; float b[CB][8]; };
+  auto load = [&](int step, Raw& x) {
+    const int c = min(kStep * step + 8 * kk, C - 8);
+#pragma unroll
+    for (int r = 0; r < RB; ++r)
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        const floatx4 v = *reinterpret_cast<const floatx4*>(arow[r] + c + 4 * q);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) x.a[r][4 * q + e] = v[e];
+      }
+    if constexpr (KC) {                        // (eight indices stay inside one head: kv % 8 == 0)
+      const float* bp = P + (size_t)(c / kv) * d * kv + c % kv;
+#pragma unroll
+      for (int j = 0; j < CB; ++j)
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+          const floatx4 v = *reinterpret_cast<const floatx4*>(bp + (size_t)ncol[j] * kv + 4 * q);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) x.b[j][4 * q + e] = v[e];
+        }
+    } else {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const vec v = *reinterpret_cast<const vec*>(bcol + (size_t)(c + e) * kv);
+#pragma unroll
+        for (int j = 0; j < CB; ++j) x.b[j][e] = v[j];
+      }
+    }
+  };
+  floatx4 acc[RB][CB];
+#pragma unroll
+  for (int r = 0; r < RB; ++r)
+#pragma unroll
+    for (int j = 0; j < CB; ++j) acc[r][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+  auto multiply = [&](int step, Raw& x) {
+    if (kStep * (step + 1) > C && kStep * step + 8 * kk >= C) {        // (C is a multiple of 8)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+#pragma unroll
+        for (int r = 0; r < RB; ++r) x.a[r][e] = 0.f;
+#pragma unroll
+        for (int j = 0; j < CB; ++j) x.b[j][e] = 0.f;
+      }
+    }
+    float most = 0.f;                          // (passes over NaN, which stays one in its terms)
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+#pragma unroll
+      for (int r = 0; r < RB; ++r) most = fmaxf(most, fabsf(x.a[r][e]));
+#pragma unroll
+      for (int j = 0; j < CB; ++j) most = fmaxf(most, fabsf(x.b[j][e]));
+    }
+    if (__builtin_expect(__any(!(most < 0x1p127f)), 0)) {
+#pragma unroll
+      for (int e = 0; e < 8; ++e)              // slots 8 kk + e
+#pragma unroll
+        for (int r = 0; r < RB; ++r)
+#pragma unroll
+          for (int j = 0; j < CB; ++j) acc[r][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(x.a[r][e], x.b[j][e], acc[r][j], 0, 0, 0);
+      return;
+    }
+    Terms b[CB];
+#pragma unroll
+    for (int j = 0; j < CB; ++j)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) split3(x.b[j][2 * q], x.b[j][2 * q + 1], b[j], q);
+#pragma unroll
+    for (int r = 0; r < RB; ++r) {
+      Terms a;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) split3(x.a[r][2 * q], x.a[r][2 * q + 1], a, q);
+      auto product = [&](int pa, int pb) {
+#pragma unroll
+        for (int j = 0; j < CB; ++j)
+          acc[r][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a.t[pa]), __builtin_bit_cast(bf16x8, b[j].t[pb]), acc[r][j], 0, 0, 0);
+      };
+      product(0, 2), product(1, 1), product(2, 0);             // smallest first
+      product(0, 1), product(1, 0);
+      product(0, 0);
+    }
+  };
+  Raw x0, x1;
+  int step = first + wave;
+  if (step < end) load(step, x0);
+  while (step < end) {
+    if (step + kWaves < end) load(step + kWaves, x1);
+    multiply(step, x0);
+    step += kWaves;
+    if (step >= end) break;
+    if (step + kWaves < end) load(step + kWaves, x0);
+    multiply(step, x1);
+    step += kWaves;
+  }
+  // D layout: register e of lane (i, g) is row 4 g + e of the block, column i (KC) or the lane's CB adjacent ones
+#pragma unroll
+  for (int r = 0; r < RB; ++r)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      float* at = red[wave] + (16 * r + 4 * kk + e) * TN;
+      if constexpr (KC) {
+#pragma unroll
+        for (int j = 0; j < CB; ++j) at[16 * j + i] = acc[r][j][e];
+      } else {
+        vec v;
+#pragma unroll
+        for (int j = 0; j < CB; ++j) v[j] = acc[r][j][e];
+        *reinterpret_cast<vec*>(at + CB * i) = v;
+      }
+    }
+  __syncthreads();
+  for (int q = tid; q < TM * TN / 4; q += kWaves * 64) {
+    const int row = row0 + 4 * q / TN, n = n0 + 4 * q % TN;
+    if (row >= rows || n >= N) continue;       // (N is a multiple of 8)
+    floatx4 s[kWaves];
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) s[w] = *reinterpret_cast<const floatx4*>(red[w] + 4 * q);
+    floatx4 y = ((s[0] + s[1]) + (s[2] + s[3])) + ((s[4] + s[5]) + (s[6] + s[7]));
+    if (gridDim.z > 1) {
+      *reinterpret_cast<floatx4*>(part + ((size_t)blockIdx.z * rows + row) * N + n) = y;
+    } else {
+      float* dst = out + (size_t)row * N + n;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) y[e] = apply_epilogue(y[e], dst + e, epilogue);
+      *reinterpret_cast<floatx4*>(dst) = y;
+    }
+  }
+}
+
+__device__ __forceinline__ float block_sum(float x, float* red) {
+  x = wave_sum(x);
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  __syncthreads();
+  if (lane == 0) red[wave] = x;
+  __syncthreads();
+  return red[0] + red[1] + red[2] + red[3];
+}
+
+// x[row] += the sum of the row's S partial products (in order: the same every time); y[row] = layernorm(x[row]) (gain 1, bias 0).  One workgroup per row of
+// at most 1024 NV columns, all loads in flight together.
+template <int NV>
+__global__ __launch_bounds__(256)
+void finish_kernel(const float* __restrict__ part, float* x, float* __restrict__ y, int rows, int N, int S, float eps) {
+  __shared__ float red[4];
+  const int n4 = N >> 2;
+  floatx4* xr = reinterpret_cast<floatx4*>(x + (size_t)blockIdx.x * N);
+  const floatx4* pr = reinterpret_cast<const floatx4*>(part + (size_t)blockIdx.x * N);
+  const size_t stride = (size_t)rows * n4;
+  floatx4 v[NV];
+#pragma unroll
+  for (int u = 0; u < NV; ++u) {
+    const int at = min((int)threadIdx.x + 256 * u, n4 - 1);
+    const floatx4 was = xr[at];
+    floatx4 s = pr[at];
+    int p = 1;
+    for (; p + 2 < S; p += 3) {
+      const floatx4 a = pr[at + p * stride], b = pr[at + (p + 1) * stride], c = pr[at + (p + 2) * stride];
+      s += a, s += b, s += c;
+    }
+    for (; p < S; ++p) s += pr[at + p * stride];
+    v[u] = was + s;
+  }
+  float sum = 0.f;
+#pragma unroll
+  for (int u = 0; u < NV; ++u)
+    if (threadIdx.x + 256 * u < n4) sum += (v[u][0] + v[u][1]) + (v[u][2] + v[u][3]);
+  const float mean = block_sum(sum, red) / N;
+  float q = 0.f;
+#pragma unroll
+  for (int u = 0; u < NV; ++u)
+    if (threadIdx.x + 256 * u < n4) {
+      const floatx4 c = v[u] - mean;
+      q += (c[0] * c[0] + c[1] * c[1]) + (c[2] * c[2] + c[3] * c[3]);
+    }
+  const float rstd = 1.0f / sqrtf(block_sum(q, red) / N + eps);
+  floatx4* yr = reinterpret_cast<floatx4*>(y + (size_t)blockIdx.x * N);
+#pragma unroll
+  for (int u = 0; u < NV; ++u) {
+    const int at = threadIdx.x + 256 * u;
+    if (at < n4) {
+      xr[at] = v[u];
+      yr[at] = (v[u] - mean) * rstd;
+    }
+  }
+}
+
+template <bool KC, int RB, int CB>
+hipError_t launch_tile(int S, const float* in, const float* P, float* out, float* part, int rows, int d, int h, int kv, int epilogue,
+                       hipStream_t st) {
+  const int N = KC ? d : h * kv;
+  constexpr int lds = kWaves * RB * CB * 1024;             // 64 KiB at most
+  const dim3 grid((N + 16 * CB - 1) / (16 * CB), (rows + 16 * RB - 1) / (16 * RB), S), block(kWaves * 64);
+  hipLaunchKernelGGL((project_terms_kernel<KC, RB, CB>), grid, block, lds, st, in, P, out, part, rows, d, h, kv, epilogue);
+  return hipGetLastError();
+}
+
+hipError_t launch_tiles(bool outp, TermsForm f, const float* in, const float* P, float* out, float* part, int rows, int d, int h, int kv,
+                        int epilogue, hipStream_t st) {
+#define MQA_TERMS(RB_, CB_)                                                                                   \
+  if (f.RB == RB_ && f.CB == CB_)                                                                             \
+    return outp ? launch_tile<true, RB_, CB_>(f.S, in, P, out, part, rows, d, h, kv, epilogue, st)            \
+                : launch_tile<false, RB_, CB_>(f.S, in, P, out, part, rows, d, h, kv, epilogue, st);
+  MQA_TERMS(1, 1) MQA_TERMS(1, 2) MQA_TERMS(1, 4) MQA_TERMS(2, 2) MQA_TERMS(2, 4)
+#undef MQA_TERMS
+  return hipErrorNotSupported;
+}
+
+long long workgroups(int RB, int CB, int rows, int N) {
+  return (long long)((rows + 16 * RB - 1) / (16 * RB)) * ((N + 16 * CB - 1) / (16 * CB));
+}
+
+}  // namespace
+
+// Is a product of its own the faster one here?  us, the kernel that otherwise takes it / this one:
+//   weights n contiguous, C x N: 4096 x 1024, rows = 128: 24.3 / 21.7, 256: 32.4 / 27.9, 384: 55.3 / 37.2; 1024 x 4096, 64: 11.6 / 10.8,
+//   128: 16.3 / 14.0; 2048 x 2048, 128: 19.3 / 16.7, 192: 30.4 / 21.4; 1024 x 1024, 192: 10.0 / 9.3, 384: 16.3 / 12.3
+//   c contiguous: 1024 x 1024, 192: 12.8 / 10.6; 1536 x 1280, 128: 19.0 / 15.1
+// The smallest tile of at most 256 workgroups (one per compute unit; a second round takes as long again: 2048 x 2048, 512: 33.8 /
+// 40.6).  Where that is 16 x 16, or 16 x 32 and the contraction short, project.hip's are as fast (4096 x 1024, 32: 21.0 / 20.4;
+// 1024 x 1024, 128: 7.6 / 7.6; 512 x 640: 5.5 / 5.9), and with c contiguous gemm.hip's are where 32 x 64 is the smallest (1024 x 1024, 384: 15.2 / 15.6;
+// 1536 x 1280, 384: 19.7 / 22.6).  A full round of the widest rows stays with gemm.hip as well (512 rows, 1024 x 1024: 14.6 / 12.7).
+TermsForm terms_form(bool outp, int rows, int d, int h, int kv) {
+  const int N = outp ? d : h * kv, C = outp ? h * kv : d;
+  static const TermsForm order[] = {{1, 1, 1}, {1, 2, 1}, {2, 2, 1}, {2, 4, 1}};
+  for (const TermsForm& f : order) {
+    const long long n = workgroups(f.RB, f.CB, rows, N);
+    if (n > 256) continue;
+    if ((f.RB == 1 && f.CB == 1) || (f.RB == 1 && C <= 1024) || (f.RB == 2 && rows <= 16) || (n > 240 && rows > 192)) break;
+    if (outp && f.CB == 4 && gemm_form(3, rows, d, h, kv, 0)) break;
+    return f;
+  }
+  return TermsForm{0, 0, 0};
+}
+
+// The same for a product whose contraction is cut among S workgroups, its parts summed by the launch that adds it to the
+// residual and normalises the rows, against a product and a layernorm (us):
+//   weights n contiguous: 4096 x 1024, rows = 1: 19.8 / 10.4, 64: 22.2 / 13.5, 128: 27.4 / 18.0, 384: 59.2 / 40.9, 512: 44.5 / 44.9;
+//   2048 x 512, 128: 11.5 / 9.1; 2048 x 2048, 192: 33.8 / 27.1, 256: 27.6 / 30.3; 640 x 2560, 64: 11.5 / 11.2, 128: 15.7 / 16.4
+//   c contiguous: 1024 x 1024, 1: 7.2 / 6.7, 128: 11.6 / 10.3, 256: 14.5 / 13.9, 384: 18.5 / 21.0; 1536 x 1280, 256: 30.9 / 26.0,
+//   384: 23.3 / 29.2
+// Tile and S: the least of 6 us for the launches, a round of up to 256 workgroups at `w` us for 1024 indices (measured, within 2 us
+// over 100 sizes), and 1 us per MiB of parts.
+TermsForm terms_parts_form(bool outp, int rows, int d, int h, int kv) {
+  const int N = outp ? d : h * kv, C = outp ? h * kv : d;
+  const TermsForm none{0, 0, 0};
+  if (N > 4096 || workgroups(2, 4, rows, N) > (outp ? 160 : C >= N ? 240 : 128)) return none;
+  static const struct { int RB, CB; double w[2]; } tiles[] = {{1, 1, {4.2, 3.8}}, {1, 2, {5.0, 6.0}}, {1, 4, {6.3, 9.0}}, {2, 2, {6.4, 8.0}}, {2, 4, {8.8, 13.0}}};
+  TermsForm best = none;
+  double least = 0.;
+  for (const auto& t : tiles) {
+    if (t.RB == 2 && rows <= 16) continue;
+    for (int S = 2; S <= 16 && C >= 4 * kStep * S; S *= 2) {
+      const double rounds = (double)((workgroups(t.RB, t.CB, rows, N) * S + 255) / 256);
+      const double us = 6.2 + t.w[outp] * rounds * C / (1024. * S) + (double)S * rows * N / 262144.;
+      if (!best.S || us < least) best = TermsForm{t.RB, t.CB, S}, least = us;
+    }
+  }
+  return best;
+}
+size_t terms_parts_bytes(bool outp, int rows, int d, int h, int kv) {
+  return (size_t)terms_parts_form(outp, rows, d, h, kv).S * rows * (size_t)(outp ? d : h * kv) * 4;
+}
+
+// hipErrorNotSupported: no form (terms_form)
+hipError_t launch_project_terms(bool outp, const float* in, const float* P, float* out, int rows, int d, int h, int kv, int epilogue,
+                                hipStream_t st) {
+  const TermsForm f = terms_form(outp, rows, d, h, kv);
+  return f.S ? launch_tiles(outp, f, in, P, out, nullptr, rows, d, h, kv, epilogue, st) : hipErrorNotSupported;
+}
+
+// x += in . B, y = layernorm(x), in two launches; workspace: terms_parts_bytes(...).  hipErrorNotSupported: no form (terms_parts_form)
+hipError_t launch_project_add_layernorm(bool outp, const float* in, const float* P, float* x, float* y, int rows, int d, int h, int kv,
+                                        float eps, void* workspace, hipStream_t st) {
+  const TermsForm f = terms_parts_form(outp, rows, d, h, kv);
+  if (!f.S) return hipErrorNotSupported;
+  const int N = outp ? d : h * kv;
+  float* part = static_cast<float*>(workspace);
+  const hipError_t e = launch_tiles(outp, f, in, P, nullptr, part, rows, d, h, kv, 0, st);
+  if (e != hipSuccess) return e;
+  if (N <= 1024) hipLaunchKernelGGL(finish_kernel<1>, dim3(rows), dim3(256), 0, st, part, x, y, rows, N, f.S, eps);
+  else if (N <= 2048) hipLaunchKernelGGL(finish_kernel<2>, dim3(rows), dim3(256), 0, st, part, x, y, rows, N, f.S, eps);
+  else hipLaunchKernelGGL(finish_kernel<4>, dim3(rows), dim3(256), 0, st, part, x, y, rows, N, f.S, eps);
+  return hipGetLastError();
+}
+
+}  // namespace mqa

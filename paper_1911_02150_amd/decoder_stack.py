@@ -50,8 +50,10 @@ class DecoderStack:
 
     def attention_append_fused(self, l: int, x: torch.Tensor) -> torch.Tensor:
         """LN, then q and the append of the new K/V rows in one launch.  Returns q."""
+        return self._append_fused(l, B.mqa_stack_layernorm(x))
+
+    def _append_fused(self, l: int, hx: torch.Tensor) -> torch.Tensor:
         w = self.layers[l]
-        hx = B.mqa_stack_layernorm(x)
         q = B.mqa_project_append_qkv(hx, w["P_q"], w["P_k"], w["P_v"], self.K[l], self.V[l], self.lens[l],
                                      self._lens_next[l])
         self.lens[l], self._lens_next[l] = self._lens_next[l], self.lens[l]      # the lengths alternate between two arrays
@@ -71,21 +73,27 @@ class DecoderStack:
         return B.mqa_project_qkvo(B.MQA_PROJ_LINEAR, u, w["W2"])
 
     def logits(self, x: torch.Tensor) -> torch.Tensor:
-        hx = B.mqa_stack_layernorm(x)
+        return self._logits(B.mqa_stack_layernorm(x))
+
+    def _logits(self, hx: torch.Tensor) -> torch.Tensor:
         return B.mqa_project_qkvo(B.MQA_PROJ_O, hx.view(self.b, 1, self.d), self.E.view(1, -1, self.d))
 
-    # -- one decoding step for the whole stack: per layer 8 launches (layernorm, fused q/K/V + append,
-    #    attention (+ merge), output projection added into x, layernorm, W1 with relu, W2 added into x)
+    # -- one decoding step for the whole stack: per layer 7 launches (fused q/K/V + append, attention (+ merge), output
+    #    projection in parts, their sum added into x with the layernorm, W1 with relu, W2 in parts, the same)
     def step(self, tokens: torch.Tensor, t: int) -> torch.Tensor:
         x = self.embed(tokens, t)
         dec = B.mha_decode_step if self.multi_head else B.mqa_decode_step
+        parts = max(B.mqa_project_add_layernorm_workspace_bytes(B.MQA_PROJ_O, self.b, self.d, self.h, self.v),
+                    B.mqa_project_add_layernorm_workspace_bytes(B.MQA_PROJ_LINEAR, self.b, self.layers[0]["W1"].shape[1], 1, self.d))
+        ws = torch.empty(max(16, parts), dtype=torch.uint8, device=self.dev)      # (of this step: calls on several streams do not share it)
+        hx = B.mqa_stack_layernorm(x)
         for l, w in enumerate(self.layers):
-            q = self.attention_append_fused(l, x)
+            q = self._append_fused(l, hx)
             o = dec(q, self.K[l], self.V[l], self.lens[l])
-            B.mqa_project_qkvo_ex(B.MQA_PROJ_O, o, w["P_o"], out=x, epilogue=B.MQA_EPI_ADD)
-            u = B.mqa_project_qkvo_ex(B.MQA_PROJ_LINEAR, B.mqa_stack_layernorm(x), w["W1"], epilogue=B.MQA_EPI_RELU)
-            B.mqa_project_qkvo_ex(B.MQA_PROJ_LINEAR, u, w["W2"], out=x, epilogue=B.MQA_EPI_ADD)
-        return self.logits(x)
+            hx = B.mqa_project_add_layernorm(B.MQA_PROJ_O, o, w["P_o"], x, workspace=ws)
+            u = B.mqa_project_qkvo_ex(B.MQA_PROJ_LINEAR, hx, w["W1"], epilogue=B.MQA_EPI_RELU)
+            hx = B.mqa_project_add_layernorm(B.MQA_PROJ_LINEAR, u, w["W2"], x, workspace=ws)
+        return self._logits(hx)
 
     # -- a whole prompt at once (multi-query only): bulk append + fused causal attention per layer
     def prefill(self, prompts: torch.Tensor) -> torch.Tensor:

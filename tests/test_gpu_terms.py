@@ -1,0 +1,124 @@
+"""Decode-sized products from three bfloat16 terms (csrc/project_terms.hip), alone and in parts with the residual and the layernorm:
+every tile and split, both weight layouts, last tiles and steps that are not full, and values without terms."""
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+DEV = "cuda:0"
+
+
+@pytest.fixture(scope="module")
+def m():
+    import paper_1911_02150_amd as lib
+    lib.load_library()
+    return lib
+
+
+def weights(layout, W, kv):
+    """W [C,N] as the library's operand: (mode, P, shape of a row of the input)."""
+    import paper_1911_02150_amd as m
+    C, N = W.shape
+    if layout == "n":
+        return m.MQA_PROJ_LINEAR, W, (C,)
+    return m.MQA_PROJ_O, W.t().contiguous().view(N, C // kv, kv).permute(1, 0, 2).contiguous(), (C // kv, kv)
+
+
+def bound(x, W):
+    # six products a step of 32 indices round the running sum once each (2^-24 of it), the steps' sums of up to 8 waves and 16
+    # parts another 24 times; the products of terms that are left out are below 2^-24 |a||b|
+    return (0.1875 * x.shape[1] + 32) * 2.0 ** -24 * (x.double().abs() @ W.double().abs())
+
+
+# rows, C, N, kv (c contiguous): rows and columns past whole tiles, a last step of 8, 16 and 24 indices, heads inside a step
+ALONE = [(65, 2056, 1032, 8), (190, 1024, 1000, 128), (65, 2048, 2048, 512), (250, 512, 648, 64), (129, 4072, 1024, 8)]
+PARTS = [(1, 4096, 1024, 128), (16, 264, 40, 24), (17, 1048, 1032, 8), (31, 272, 4096, 16), (64, 4096, 1024, 128), (128, 2072, 512, 56),
+         (129, 1024, 1024, 128), (190, 2048, 1288, 64), (224, 520, 136, 40), (3, 256, 8, 8)]
+
+
+@pytest.mark.parametrize("layout,rows,C,N,kv", [(layout, *s) for layout in "nc" for s in ALONE] + [("n", 120, 1048, 4088, 8)])
+def test_product(m, layout, rows, C, N, kv):
+    g = torch.Generator(device=DEV)
+    g.manual_seed(rows + C + N)
+    x = torch.randn(rows, C, generator=g, device=DEV) * torch.exp(5 * torch.randn(rows, 1, generator=g, device=DEV))
+    x[1], x[2, ::3] = 0, 1e-30
+    W = torch.randn(C, N, generator=g, device=DEV) * torch.exp(4 * torch.randn(C, 1, generator=g, device=DEV))
+    mode, P, row = weights(layout, W, kv)
+    sizes = (1, N) if layout == "n" else (C // kv, kv)
+    assert m.mqa_project_plan(mode, rows, C if layout == "n" else N, *sizes) == 1
+    ref, most = x.double() @ W.double(), bound(x, W)
+    for epilogue, want, slack in ((m.MQA_EPI_STORE, ref, 0), (m.MQA_EPI_RELU, ref.clamp(min=0), 0), (m.MQA_EPI_ADD, ref + 3, 2.0 ** -23 * (ref.abs() + 3))):
+        out = torch.full((rows, N), 3.0, device=DEV)
+        got = m.mqa_project_qkvo_ex(mode, x.view(rows, *row), P, out=out, epilogue=epilogue)
+        assert ((got.double() - want).abs() <= most + slack).all()
+
+
+@pytest.mark.parametrize("layout", ["n", "c"])
+def test_values_without_terms(m, layout):
+    """Infinities, NaN, the largest floats (their first term would be an infinity) and overflowing sums."""
+    rows, C, N = 65, 2048, 2048
+    g = torch.Generator(device=DEV)
+    g.manual_seed(5)
+    x = torch.randn(rows, C, generator=g, device=DEV)
+    W = torch.randn(C, N, generator=g, device=DEV) / 16
+    big = float(np.finfo(np.float32).max)
+    x[3, 5], x[rows - 1, 0], x[13, C - 1] = float("inf"), float("-inf"), float("inf")
+    x[7], x[60, C - 1] = float("nan"), float("nan")
+    x[9] = 0
+    x[9, 11] = big
+    x[11, :8] = 1e30
+    W[:8, 2] = 1e30
+    W[:, N - 1] = 0
+    mode, P, row = weights(layout, W, 128)
+    ref = (x.double() @ W.double()).float()
+    got = m.mqa_project_qkvo_ex(mode, x.view(rows, *row), P)
+    assert torch.equal(torch.isnan(got), torch.isnan(ref))
+    assert torch.equal(torch.isposinf(got), torch.isposinf(ref)) and torch.equal(torch.isneginf(got), torch.isneginf(ref))
+    fine = torch.isfinite(ref)
+    lim = torch.nan_to_num(bound(x, W), nan=0.0, posinf=0.0)
+    assert ((got.double() - ref.double()).abs()[fine] <= lim[fine] + 2.0 ** -23 * ref.double().abs()[fine]).all()
+
+
+@pytest.mark.parametrize("with_workspace", [True, False])
+@pytest.mark.parametrize("layout", ["n", "c"])
+@pytest.mark.parametrize("rows,C,N,kv", PARTS)
+def test_add_layernorm(m, layout, rows, C, N, kv, with_workspace):
+    """In parts (given the workspace) and as the two calls it stands for; nothing behind x, y and the workspace is written."""
+    g = torch.Generator(device=DEV)
+    g.manual_seed(rows + C + N)
+    x = torch.randn(rows, C, generator=g, device=DEV)
+    W = torch.randn(C, N, generator=g, device=DEV) * C ** -0.5
+    mode, P, row = weights(layout, W, kv)
+    nbytes = m.mqa_project_add_layernorm_workspace_bytes(mode, rows, *((C, 1, N) if layout == "n" else (N, C // kv, kv)))
+    assert nbytes > 0 and nbytes % (4 * rows * N) == 0
+    buffers = torch.full((2, rows + 1, N), 7.0, device=DEV)
+    acc, y = buffers[0, :rows], buffers[1, :rows]
+    acc.copy_(torch.randn(rows, N, generator=g, device=DEV))
+    was = acc.double()
+    ws = torch.full((nbytes + 64,), 255, dtype=torch.uint8, device=DEV)      # (NaN, should a part be read that was not written)
+    assert m.mqa_project_add_layernorm(mode, x.view(rows, *row), P, acc, out=y, workspace=ws[:nbytes if with_workspace else nbytes - 16]) is y
+    want = was + x.double() @ W.double()
+    off = bound(x, W) + 2.0 ** -23 * (want.abs() + was.abs())
+    assert ((acc.double() - want).abs() <= off).all()
+    c = want - want.mean(1, keepdim=True)
+    std = (c.square().mean(1, keepdim=True) + 1e-6).sqrt()
+    # an error e of the row is (e + mean |e| + |y| rms e) / std of the result; the sums and the root are off by some 2^-20 of it
+    e = off / std
+    norm = c / std
+    assert ((y.double() - norm).abs() <= e + e.mean(1, keepdim=True) + norm.abs() * e.square().mean(1, keepdim=True).sqrt() + 2.0 ** -20 * (1 + norm.abs())).all()
+    assert (buffers[:, rows] == 7).all() and (ws[nbytes:] == 255).all()
+    if with_workspace:
+        again, y2 = was.float(), torch.empty_like(y)
+        m.mqa_project_add_layernorm(mode, x.view(rows, *row), P, again, out=y2)
+        assert torch.equal(again, acc) and torch.equal(y2, y)                # (the same every time)
+
+
+def test_add_layernorm_refuses(m):
+    x, W, acc = torch.zeros(4, 64, device=DEV), torch.zeros(64, 32, device=DEV), torch.zeros(4, 32, device=DEV)
+    with pytest.raises(ValueError):
+        m.mqa_project_add_layernorm(m.MQA_PROJ_Q, x, W.view(1, 64, 32), acc)
+    with pytest.raises(ValueError):
+        m.mqa_project_add_layernorm(m.MQA_PROJ_LINEAR, x, W, acc[:3])
+    with pytest.raises(m.MqaError, match="status 2"):
+        m.mqa_project_add_layernorm(m.MQA_PROJ_LINEAR, torch.zeros(4, 60, device=DEV), torch.zeros(60, 32, device=DEV), acc)
