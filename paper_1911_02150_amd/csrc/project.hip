@@ -237,15 +237,25 @@ void project_qkv_append_kernel(const float* __restrict__ x, const float* __restr
                                const float* __restrict__ P_k, const float* __restrict__ P_v,
                                float* __restrict__ q, CT* __restrict__ K, CT* __restrict__ V,
                                const int32_t* __restrict__ lens_in, int32_t* __restrict__ lens_out,
-                               int rows, int d, int h, int h_kv, int cap, int k, int v, int nq_tiles, int kv_narrow,
+                               int rows, int d, int h, int h_kv, int cap, int k, int v, int nq_tiles, int kv_tiles, int kv_blocks, int kv_narrow,
                                int mem_rows, int append) {
   constexpr int TM = RB * T, TN = CB * T;
   __shared__ __align__(16) double red_raw[NWAVES * T * TN];       // = RB <= 2 float32 row blocks
   static_assert(RB <= 2, "a q tile's float32 partial tiles must fit the float64 buffer");
-  const int row0 = blockIdx.y * TM;
   const int nq = h * k, nk = h_kv * k;
-  if ((int)blockIdx.x < nq_tiles) {    // a tile of q
-    const int n0 = blockIdx.x * TN;
+  // one row of the grid per row tile, its q tiles first; or (kv_blocks > 0) that many workgroups for the K / V tiles of all
+  // row tiles, then all q tiles
+  int column = blockIdx.x, row_tile = blockIdx.y, first_kv = nq_tiles;
+  if (kv_blocks) {
+    const bool of_q = (int)blockIdx.x >= kv_blocks;
+    const int at = blockIdx.x - (of_q ? kv_blocks : 0), columns = of_q ? nq_tiles : kv_tiles;
+    row_tile = at / columns;
+    column = at - row_tile * columns;
+    if (!of_q) first_kv = 0;
+  }
+  const int row0 = row_tile * TM;
+  if (column < first_kv) {             // a tile of q
+    const int n0 = column * TN;
     float (*red)[TM * TN] = reinterpret_cast<float (*)[TM * TN]>(red_raw);
     gemm_tile<false, T, RB, CB>(x, P_q, rows, d, h, k, row0, n0, red);
     for (int e = threadIdx.x; e < TM * TN; e += NWAVES * 64) {
@@ -258,7 +268,7 @@ void project_qkv_append_kernel(const float* __restrict__ x, const float* __restr
   // rows (a decode step) the tiles are a single block of 16 columns wide: four times the
   // workgroups, a quarter of the time each; for many rows (a prompt) they keep the q tiles' width
   // and with it the re-use of the input rows.
-  const int kvt = blockIdx.x - nq_tiles;
+  const int kvt = column - first_kv;
   const int width = kv_narrow ? T : TN;
   int n0 = kvt * width;
   const int which = n0 >= nk ? 2 : 1;      // 1: K row, 2: V row
@@ -386,16 +396,21 @@ hipError_t launch_project_qkv_append(const float* x, const float* P_q, const flo
   // a decode step's rows and K / V columns that are a small part of the product (multi-query): K / V tiles of
   // 16 columns (b=128, h=8: 14.2 -> 10.4 us; multi-head, where they are two thirds of it: 25.9 -> 31.6 us, so not there)
   const int kv_narrow = (rows <= 512 && 2 * (ntot - nq) <= nq) ? 1 : 0;
+  // The float64 tiles take the longest, so in a launch of more than one round (256 workgroups, one per compute unit) they go
+  // first and q's short ones fill the end (multi-head, b=128: 27.2 -> 23.3 us, b=256: 39.3 -> 35.5; multi-query, b=512: 31.2 -> 27.6).
   const dim3 block(NWAVES * 64);
   bool launched = false;
 #define MQA_QKV(RB_, CB_)                                                                                            \
   if (!launched && t.RB == RB_ && t.CB == CB_) {                                                                     \
     const int nq_tiles = q_done ? 0 : nq / (CB_ * 16);                                                               \
-    const dim3 grid(nq_tiles + (ntot - nq) / (kv_narrow ? 16 : CB_ * 16), (rows + RB_ * 16 - 1) / (RB_ * 16));       \
+    const int kv_tiles = (ntot - nq) / (kv_narrow ? 16 : CB_ * 16);                                                  \
+    const long long row_tiles = (rows + RB_ * 16 - 1) / (RB_ * 16), blocks = (nq_tiles + kv_tiles) * row_tiles;      \
+    const int kv_blocks = nq_tiles && blocks > 256 && blocks < (1 << 20) ? (int)(kv_tiles * row_tiles) : 0;          \
+    const dim3 grid = kv_blocks ? dim3((unsigned)blocks) : dim3(nq_tiles + kv_tiles, (unsigned)row_tiles);           \
     if (is_bf16) hipLaunchKernelGGL((project_qkv_append_kernel<16, RB_, CB_, uint16_t>), grid, block, 0, st, x, P_q, P_k, P_v, q, \
-                                    (uint16_t*)K, (uint16_t*)V, lens_in, lens_out, rows, d, h, h_kv, cap, k, v, nq_tiles, kv_narrow, mem_rows, append); \
+                                    (uint16_t*)K, (uint16_t*)V, lens_in, lens_out, rows, d, h, h_kv, cap, k, v, nq_tiles, kv_tiles, kv_blocks, kv_narrow, mem_rows, append); \
     else hipLaunchKernelGGL((project_qkv_append_kernel<16, RB_, CB_, float>), grid, block, 0, st, x, P_q, P_k, P_v, q, \
-                            (float*)K, (float*)V, lens_in, lens_out, rows, d, h, h_kv, cap, k, v, nq_tiles, kv_narrow, mem_rows, append);  \
+                            (float*)K, (float*)V, lens_in, lens_out, rows, d, h, h_kv, cap, k, v, nq_tiles, kv_tiles, kv_blocks, kv_narrow, mem_rows, append);  \
     launched = true;                                                                                                 \
   }
   MQA_TILES(MQA_QKV)
