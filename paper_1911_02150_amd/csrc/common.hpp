@@ -164,6 +164,12 @@ hipError_t launch_argmax(const float* x, int32_t* out, int rows, int n, hipStrea
 __device__ __forceinline__ int window_lo(int L, int window) { return window > 0 ? max(0, L - window) : 0; }
 __device__ __forceinline__ int window_base(int L, int window) { return window_lo(L, window) & ~31; }
 
+// Workgroups go to the eight XCDs in turn: the column tile of workgroup x of a row of them, such that neighbouring tiles
+// (that share cache lines of weights with n contiguous) are on one XCD and every XCD has a run of them.  For tiles of 16
+// columns, half a line: 1024 x 4096, 1 row: 8.3 -> 7.0 us, 8: 8.5 -> 8.0; multi-head q/K/V of one row 7.8 -> 6.6.  Wider tiles are better spread
+// (project_terms.hip, 128 rows: 15.0 / 15.7).
+__device__ __forceinline__ int column_tile(int x, int tiles) { return tiles % 8 ? x : x % 8 * (tiles / 8) + x / 8; }
+
 // what a GEMM does with a finished output element (see launch_project)
 __device__ __forceinline__ float apply_epilogue(float x, const float* dst, int epilogue) {
   if (epilogue == 1) return fmaxf(x, 0.f);

@@ -202,7 +202,7 @@ void project_mfma_kernel(const float* __restrict__ in, const float* __restrict__
   constexpr int TM = RB * T, TN = CB * T;
   __shared__ ACC red[NWAVES][TM * TN];
   const int N = OUT_PROJ ? d : h * kv;
-  const int row0 = blockIdx.y * TM, n0 = blockIdx.x * TN;
+  const int row0 = blockIdx.y * TM, n0 = (!OUT_PROJ && CB == 1 ? column_tile(blockIdx.x, gridDim.x) : (int)blockIdx.x) * TN;
   gemm_tile<OUT_PROJ, T, RB, CB, ACC>(in, P, rows, d, h, kv, row0, n0, red);
   for (int e = threadIdx.x; e < TM * TN; e += NWAVES * 64) {
     const int r = e / TN, c = e % TN;
@@ -255,7 +255,7 @@ void project_qkv_append_kernel(const float* __restrict__ x, const float* __restr
   }
   const int row0 = row_tile * TM;
   if (column < first_kv) {             // a tile of q
-    const int n0 = column * TN;
+    const int n0 = (CB == 1 ? column_tile(column, nq_tiles) : column) * TN;
     float (*red)[TM * TN] = reinterpret_cast<float (*)[TM * TN]>(red_raw);
     gemm_tile<false, T, RB, CB>(x, P_q, rows, d, h, k, row0, n0, red);
     for (int e = threadIdx.x; e < TM * TN; e += NWAVES * 64) {
@@ -268,7 +268,7 @@ void project_qkv_append_kernel(const float* __restrict__ x, const float* __restr
   // rows (a decode step) the tiles are a single block of 16 columns wide: four times the
   // workgroups, a quarter of the time each; for many rows (a prompt) they keep the q tiles' width
   // and with it the re-use of the input rows.
-  const int kvt = column - first_kv;
+  const int kvt = CB == 1 || kv_narrow ? column_tile(column - first_kv, kv_tiles) : column - first_kv;
   const int width = kv_narrow ? T : TN;
   int n0 = kvt * width;
   const int which = n0 >= nk ? 2 : 1;      // 1: K row, 2: V row

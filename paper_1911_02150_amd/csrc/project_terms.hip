@@ -291,11 +291,12 @@ long long workgroups(int RB, int CB, int rows, int N) {
 // 1536 x 1280, 384: 19.7 / 22.6).  A full round of the widest rows stays with gemm.hip as well (512 rows, 1024 x 1024: 14.6 / 12.7).
 TermsForm terms_form(bool outp, int rows, int d, int h, int kv) {
   const int N = outp ? d : h * kv, C = outp ? h * kv : d;
+  if (rows <= 16) return TermsForm{0, 0, 0};               // (1024 x 4096, 16: 8.6 / 9.2)
   static const TermsForm order[] = {{1, 1, 1}, {1, 2, 1}, {2, 2, 1}, {2, 4, 1}};
   for (const TermsForm& f : order) {
     const long long n = workgroups(f.RB, f.CB, rows, N);
     if (n > 256) continue;
-    if ((f.RB == 1 && f.CB == 1) || (f.RB == 1 && C <= 1024) || (f.RB == 2 && rows <= 16) || (n > 240 && rows > 192)) break;
+    if ((f.RB == 1 && f.CB == 1) || (f.RB == 1 && C <= 1024) || (n > 240 && rows > 192)) break;
     if (outp && f.CB == 4 && gemm_form(3, rows, d, h, kv, 0)) break;
     return f;
   }
