@@ -119,6 +119,10 @@ hipError_t launch_project(int mode, const float* in, const float* P, float* out,
 
 // gemm.hip: the same GEMM for large row counts / wide outputs (hipErrorNotSupported: too small, use launch_project's own kernel)
 int gemm_form(int mode, int rows, int d, int h, int kv, int apart);      // the edge of its tiles; 0: not this kernel
+bool gemm_fits(bool outp, int d, int h, int kv, int edge);               // do its 32-bit offsets inside a tile fit?
+double gemm_us(bool outp, int rows, int N, int C);                       // its time, or the split-contraction kernel's, by the rule there
+hipError_t launch_gemm_parts(int mode, const float* in, const float* P, float* out, int rows, int d, int h, int kv, int epilogue,
+                             int edge, int S, hipStream_t st);           // S parts of the contraction, one behind another in `out`
 constexpr int kApart = 4;      // `apart` of the fused q/K/V projection, us: a launch of its own for q
 hipError_t launch_gemm_tiled(int mode, const float* in, const float* P, float* out,
                              int rows, int d, int h, int kv, int epilogue, int apart, hipStream_t st);
@@ -134,7 +138,8 @@ hipError_t launch_project_kv_exact(const float* x, const float* P_k, const float
                                    const int32_t* lens_in, int32_t* lens_out, int rows, int n, int append, int d, int h_kv,
                                    int cap, int k, int v, hipStream_t st);
 
-// project_terms.hip: decode-sized products; tiles of 16 RB x 16 CB, the contraction cut among S workgroups (S = 0: not there)
+// project_terms.hip: decode-sized products; tiles of 16 RB x 16 CB, the contraction cut among S workgroups (S = 0: not there;
+// parts with RB = CB = 8: gemm.hip's 128 x 128 tiles)
 struct TermsForm { int RB, CB, S; };
 TermsForm terms_form(bool outp, int rows, int d, int h, int kv);
 TermsForm terms_parts_form(bool outp, int rows, int d, int h, int kv);

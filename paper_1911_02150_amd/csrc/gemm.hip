@@ -91,7 +91,7 @@ template <typename V> __device__ __forceinline__ V load_at(const float* base, ui
 template <bool B_KCONTIG, int BM, int BN, int WR, int WC, int KG, int PD>
 __global__ __launch_bounds__(512, KG >= 4 ? 4 : 2)      // (waves per SIMD: two workgroups per compute unit of the small tiles)
 void gemm_split_kernel(const float* __restrict__ in, const float* __restrict__ P, float* out,
-                       int rows, int d, int h, int kv, int epilogue, int tiles_m, int tiles_n) {
+                       int rows, int d, int h, int kv, int epilogue, int tiles_m, int tiles_n, int per) {
   static_assert(WR * WC * KG == 8 && BM * KG == 256 && BN * KG == 256, "512 threads, 16 staged values of each operand per thread of a half");
   constexpr int RB = BM / WR / 32, JB = BN / WC / 32;      // 32x32 blocks per wave
   typedef SplitTile<BM, BN, JB, KG> L;
@@ -111,11 +111,13 @@ void gemm_split_kernel(const float* __restrict__ in, const float* __restrict__ P
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int i32 = lane & 31, g = lane >> 5;
   const int kg = wave / (WR * WC), wr = (wave / WC) % WR, wc = wave % WC;
-  const int C = B_KCONTIG ? h * kv : d;
+  // this workgroup's part of the contraction: the C indices from `from` on of the whole (per: a multiple of a stage's)
+  const int whole = B_KCONTIG ? h * kv : d, from = blockIdx.y * per, C = min(per, whole - from);
   const int N = B_KCONTIG ? d : h * kv;
   const size_t head_stride = (size_t)d * kv;
   const int ts = tid & 255;
   const int nst = (C + 16 * KG - 1) / (16 * KG);
+  out += (size_t)blockIdx.y * rows * N;
   uint32_t* most = reinterpret_cast<uint32_t*>(smem + L::STATE);        // [BM + BN] bits of the largest |value| seen
   int* expo = reinterpret_cast<int*>(most + BM + BN);                   // [BM + BN] the tile holds x . 2^-expo
   int* shorts = expo + BM + BN;                                         // [BM + BN] octets with a value that the terms hold in few bits
@@ -144,12 +146,12 @@ void gemm_split_kernel(const float* __restrict__ in, const float* __restrict__ P
     int short_octets[2], zero_octets[2];
     float peak[2], suspect;
     // a base that is the same in every lane (scalar registers) and a 32-bit offset in bytes of the lane (split_fits)
-    const float* base_of = STAGE_A ? in + (size_t)row0 * C : B_KCONTIG ? P + (size_t)n0 * kv : P + (size_t)(n0 / kv) * head_stride + n0 % kv;
+    const float* base_of = STAGE_A ? in + (size_t)row0 * whole + from : B_KCONTIG ? P + (size_t)n0 * kv : P + (size_t)(n0 / kv) * head_stride + n0 % kv + (size_t)from * kv;
     uint32_t src[BY_ROWS ? 2 : 1];
     if constexpr (BY_ROWS) {
 #pragma unroll
       for (int i = 0; i < 2; ++i)
-        src[i] = STAGE_A ? (uint32_t)min(line[i], rows - 1 - row0) * (4u * (uint32_t)C)
+        src[i] = STAGE_A ? (uint32_t)min(line[i], rows - 1 - row0) * (4u * (uint32_t)whole)
                          : (uint32_t)min(JB * (line[i] % L::QCOLS) + line[i] / L::QCOLS, N - 1 - n0) * (4u * (uint32_t)kv);        // line: the slot
     } else {
       const int n = n0 + min(2 * pair, N - 2 - n0);
@@ -159,10 +161,10 @@ void gemm_split_kernel(const float* __restrict__ in, const float* __restrict__ P
     auto load_stage = [&](int st, Regs& rg) {
       const int c0 = min(st, nst - 1) * 16 * KG, c = min(8 * (BY_ROWS ? o_row : o_col), C - 8 - c0);
       if constexpr (BY_ROWS) {
-        const float* at = base_of + c0;
+        const float* at = base_of + c0;        // (c contiguous: below)
         uint32_t off = 4u * (uint32_t)c;
         if constexpr (!STAGE_A) {              // eight indices stay inside one head (kv % 8 == 0), a stage need not
-          const int head = c0 / kv, in_head = c0 - head * kv;
+          const int head = (from + c0) / kv, in_head = from + c0 - head * kv;
           at = base_of + (size_t)head * head_stride + in_head;
           if (in_head + 16 * KG > kv) off += (uint32_t)((in_head + c) / kv) * (uint32_t)(4 * (head_stride - kv));
         }
@@ -493,7 +495,7 @@ bool split_fits(bool outp, int d, int h, int kv, int tile, int stage) {
 
 template <bool KC, int BM, int BN, int WR, int WC, int KG, int PD>
 hipError_t launch_split(const float* in, const float* P, float* out, int rows, int d, int h, int kv, int N,
-                        int epilogue, hipStream_t st) {
+                        int epilogue, int S, hipStream_t st) {
   constexpr size_t lds = SplitTile<BM, BN, BN / WC / 32, KG>::BYTES;       // 67 KiB (32, 64), 132 (128: the groups' partial tiles), 74 (256)
   auto kern = gemm_split_kernel<KC, BM, BN, WR, WC, KG, PD>;
   static bool done[64] = {};
@@ -506,8 +508,9 @@ hipError_t launch_split(const float* in, const float* P, float* out, int rows, i
   }
   const int tm = (rows + BM - 1) / BM, tn = (N + BN - 1) / BN;
   const long long tiles = (long long)tm * tn;
-  const dim3 grid((unsigned)((tiles + 7) / 8 * 8)), block(512);
-  hipLaunchKernelGGL(kern, grid, block, lds, st, in, P, out, rows, d, h, kv, epilogue, tm, tn);
+  const dim3 grid((unsigned)((tiles + 7) / 8 * 8), S), block(512);
+  const int C = KC ? h * kv : d, stage = 16 * KG, per = S > 1 ? ((C + stage - 1) / stage + S - 1) / S * stage : C;
+  hipLaunchKernelGGL(kern, grid, block, lds, st, in, P, out, rows, d, h, kv, epilogue, tm, tn, per);
   return hipGetLastError();
 }
 
@@ -523,10 +526,8 @@ hipError_t launch_split(const float* in, const float* P, float* out, int rows, i
 // and the split-contraction kernel on float32 instructions 5 (less below C = 1024, in proportion) + 2 rows N C / 64
 // TFLOP/s (80 with n contiguous): 128 x 512 x 4096: 9.1 (32 x 32 tiles 10.6); 128 x 1024 x 1024: 9.2; 128 x 4096 x 1024, long sums and few tiles: 24, 32 x 32 tiles 26; 1024 x 1024 x 1024: 32; 768 x
 // 4096 x 1024: 104, 64 x 64 tiles 50.
-int gemm_form(int mode, int rows, int d, int h, int kv, int apart) {
-  const bool outp = (mode == 3);
-  const int N = outp ? d : h * kv;
-  const double C = outp ? (double)h * kv : (double)d;
+struct GemmCost { int edge; double tiles_us, split_us; };
+static GemmCost gemm_cost(bool outp, int rows, int N, double C) {
   auto tiles = [&](int t) { return (double)((N + t - 1) / t) * (double)((rows + t - 1) / t); };
   auto rounds = [&](int t, double per_round) { return ceil(tiles(t) / per_round); };
   const double w[4] = {tiles(32) <= 256 ? 5.7 : 10.5 * rounds(32, 512), tiles(64) <= 256 ? 12. : 22.5 * rounds(64, 512),
@@ -535,20 +536,29 @@ int gemm_form(int mode, int rows, int d, int h, int kv, int apart) {
   for (int f = 1; f < 4; ++f)
     if (w[f] < w[best]) best = f;
   const double split_contraction = (C < 1024. ? 5. * C / 1024. : 5.) + 2. * ((rows + 15) / 16 * 16) * N * C / (outp ? 64e6 : 80e6);
-  if (5. + apart + C / 1024. * w[best] > 0.9 * split_contraction) return 0;
-  const int edge = 32 << best;
-  return split_fits(outp, d, h, kv, edge, 16 * (256 / edge)) ? edge : 0;
+  return GemmCost{32 << best, 5. + C / 1024. * w[best], split_contraction};
+}
+bool gemm_fits(bool outp, int d, int h, int kv, int edge) { return split_fits(outp, d, h, kv, edge, 16 * (256 / edge)); }
+double gemm_us(bool outp, int rows, int N, int C) {
+  const GemmCost c = gemm_cost(outp, rows, N, C);
+  return c.tiles_us < c.split_us ? c.tiles_us : c.split_us;
+}
+int gemm_form(int mode, int rows, int d, int h, int kv, int apart) {
+  const bool outp = (mode == 3);
+  const GemmCost c = gemm_cost(outp, rows, outp ? d : h * kv, outp ? (double)h * kv : (double)d);
+  if (c.tiles_us + apart > 0.9 * c.split_us) return 0;
+  return gemm_fits(outp, d, h, kv, c.edge) ? c.edge : 0;
 }
 
-// hipErrorNotSupported: no form (gemm_form); the caller then uses the split-contraction kernel
-hipError_t launch_gemm_tiled(int mode, const float* in, const float* P, float* out,
-                             int rows, int d, int h, int kv, int epilogue, int apart, hipStream_t st) {
+// S > 1: the contraction in S parts, their products one behind another in `out` (S x rows x N); edge: of the tiles
+hipError_t launch_gemm_parts(int mode, const float* in, const float* P, float* out,
+                             int rows, int d, int h, int kv, int epilogue, int edge, int S, hipStream_t st) {
   const bool outp = (mode == 3);
   const int N = outp ? d : h * kv;
 #define MQA_SPLIT(BM, WR, WC, KG, PD) \
-  return outp ? launch_split<true, BM, BM, WR, WC, KG, PD>(in, P, out, rows, d, h, kv, N, epilogue, st) \
-              : launch_split<false, BM, BM, WR, WC, KG, PD>(in, P, out, rows, d, h, kv, N, epilogue, st)
-  switch (gemm_form(mode, rows, d, h, kv, apart)) {
+  return outp ? launch_split<true, BM, BM, WR, WC, KG, PD>(in, P, out, rows, d, h, kv, N, epilogue, S, st) \
+              : launch_split<false, BM, BM, WR, WC, KG, PD>(in, P, out, rows, d, h, kv, N, epilogue, S, st)
+  switch (edge) {
     case 32: MQA_SPLIT(32, 1, 1, 8, 1);
     case 64: MQA_SPLIT(64, 2, 1, 4, 1);
     case 128: MQA_SPLIT(128, 2, 2, 2, 3);
@@ -556,6 +566,12 @@ hipError_t launch_gemm_tiled(int mode, const float* in, const float* P, float* o
   }
 #undef MQA_SPLIT
   return hipErrorNotSupported;
+}
+
+// hipErrorNotSupported: no form (gemm_form); the caller then uses the split-contraction kernel
+hipError_t launch_gemm_tiled(int mode, const float* in, const float* P, float* out,
+                             int rows, int d, int h, int kv, int epilogue, int apart, hipStream_t st) {
+  return launch_gemm_parts(mode, in, P, out, rows, d, h, kv, epilogue, gemm_form(mode, rows, d, h, kv, apart), 1, st);
 }
 
 }  // namespace mqa

@@ -30,6 +30,7 @@ typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 
 constexpr int kWaves = 8, kStep = 32;          // (a step: the indices of one instruction)
+constexpr int kWideStage = 32;                 // indices of a stage of gemm.hip's 128 x 128 tiles: parts are whole stages
 
 struct Terms { u32x4 t[3]; };                  // eight values
 
@@ -311,20 +312,35 @@ TermsForm terms_form(bool outp, int rows, int d, int h, int kv) {
 //   384: 23.3 / 29.2
 // Tile and S: the least of 6 us for the launches, a round of up to 256 workgroups at `w` us for 1024 indices (measured, within 2 us
 // over 100 sizes), and 1 us per MiB of parts.
+//   More rows, or parts that are longer than that: gemm.hip's 128 x 128 tiles, one round of up to 256, of parts of the contraction: 9 us, 33 for
+// 1024 indices and 0.4 per MiB (4096 x 1024, 512 rows: 49 / 32, 1024: 71 / 48, 2048: 99 / 80; 5120 x 1280, 512: 84 / 49, 1536: 120 / 93;
+// 1024 x 1024, 1024: 23 / 25), against a product by gemm_form and a layernorm; up to 256 rows the smaller tiles are as fast (a stack step of 256
+// rows: 394, with these 400).
 TermsForm terms_parts_form(bool outp, int rows, int d, int h, int kv) {
   const int N = outp ? d : h * kv, C = outp ? h * kv : d;
-  const TermsForm none{0, 0, 0};
-  if (N > 4096 || workgroups(2, 4, rows, N) > (outp ? 160 : C >= N ? 240 : 128)) return none;
-  static const struct { int RB, CB; double w[2]; } tiles[] = {{1, 1, {4.2, 3.8}}, {1, 2, {5.0, 6.0}}, {1, 4, {6.3, 9.0}}, {2, 2, {6.4, 8.0}}, {2, 4, {8.8, 13.0}}};
-  TermsForm best = none;
-  double least = 0.;
-  for (const auto& t : tiles) {
-    if (t.RB == 2 && rows <= 16) continue;
-    for (int S = 2; S <= 16 && C >= 4 * kStep * S; S *= 2) {
-      const double rounds = (double)((workgroups(t.RB, t.CB, rows, N) * S + 255) / 256);
-      const double us = 6.2 + t.w[outp] * rounds * C / (1024. * S) + (double)S * rows * N / 262144.;
-      if (!best.S || us < least) best = TermsForm{t.RB, t.CB, S}, least = us;
+  TermsForm best{0, 0, 0};
+  if (N > 4096) return best;
+  double least = 1e30;
+  if (workgroups(2, 4, rows, N) <= (outp ? 160 : C >= N ? 240 : 128)) {
+    static const struct { int RB, CB; double w[2]; } tiles[] = {{1, 1, {4.2, 3.8}}, {1, 2, {5.0, 6.0}}, {1, 4, {6.3, 9.0}}, {2, 2, {6.4, 8.0}}, {2, 4, {8.8, 13.0}}};
+    for (const auto& t : tiles) {
+      if (t.RB == 2 && rows <= 16) continue;
+      for (int S = 2; S <= 16 && C >= 4 * kStep * S; S *= 2) {
+        const double rounds = (double)((workgroups(t.RB, t.CB, rows, N) * S + 255) / 256);
+        const double us = 6.2 + t.w[outp] * rounds * C / (1024. * S) + (double)S * rows * N / 262144.;
+        if (us < least) best = TermsForm{t.RB, t.CB, S}, least = us;
+      }
     }
+  }
+  const long long wide = workgroups(8, 8, rows, N);
+  if (rows > (best.S ? 256 : 128) && wide <= 128 && gemm_fits(outp, d, h, kv, 128)) {
+    int S = 2;
+    while (S < 16 && 2 * S * wide <= 256 && C >= 512 * S) S *= 2;
+    const int stages = (C + kWideStage - 1) / kWideStage, per = (stages + S - 1) / S;
+    S = (stages + per - 1) / per;              // (no empty parts)
+    const double us = 8.7 + 33. * per * kWideStage / 1024. + 0.4 * S * rows * N / 262144.;
+    const double apart = gemm_us(outp, rows, N, C) + 3.5 + 0.8 * rows * N / 262144.;
+    if (S > 1 && us < least && (best.S || us < 0.82 * apart)) best = TermsForm{8, 8, S};
   }
   return best;
 }
@@ -346,7 +362,8 @@ hipError_t launch_project_add_layernorm(bool outp, const float* in, const float*
   if (!f.S) return hipErrorNotSupported;
   const int N = outp ? d : h * kv;
   float* part = static_cast<float*>(workspace);
-  const hipError_t e = launch_tiles(outp, f, in, P, nullptr, part, rows, d, h, kv, 0, st);
+  const hipError_t e = f.RB == 8 ? launch_gemm_parts(outp ? 3 : 0, in, P, part, rows, d, h, kv, 0, 128, f.S, st)
+                                 : launch_tiles(outp, f, in, P, nullptr, part, rows, d, h, kv, 0, st);
   if (e != hipSuccess) return e;
   if (N <= 1024) hipLaunchKernelGGL(finish_kernel<1>, dim3(rows), dim3(256), 0, st, part, x, y, rows, N, f.S, eps);
   else if (N <= 2048) hipLaunchKernelGGL(finish_kernel<2>, dim3(rows), dim3(256), 0, st, part, x, y, rows, N, f.S, eps);

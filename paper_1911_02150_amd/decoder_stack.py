@@ -103,8 +103,8 @@ class DecoderStack:
         b, n = prompts.shape
         positions = torch.arange(n, dtype=torch.int32, device=self.dev).repeat(b)
         x = B.mqa_stack_embed(prompts.reshape(-1).to(torch.int32).contiguous(), positions, self.E, self.pos)   # [b*n,d]
+        hx = B.mqa_stack_layernorm(x)
         for l, w in enumerate(self.layers):
-            hx = B.mqa_stack_layernorm(x)
             q = B.mqa_project_qkvo(B.MQA_PROJ_Q, hx, w["P_q"]).view(b, n, self.h, self.k)
             if self.k % 16 == 0 and self.v % 16 == 0:
                 now = self._lens_next[l]
@@ -115,9 +115,12 @@ class DecoderStack:
                 vn = B.mqa_project_qkvo(B.MQA_PROJ_KV, hx, w["P_v"]).view(b, n, self.v)
                 B.mqa_append_kv_rows(self.K[l], self.V[l], kn, vn, self.lens[l])
             o = B.mqa_prefill_attention(q, self.K[l], self.V[l], now)
-            B.mqa_project_qkvo_ex(B.MQA_PROJ_O, o.view(b * n, self.h, self.v), w["P_o"], out=x, epilogue=B.MQA_EPI_ADD)
-            u = B.mqa_project_qkvo_ex(B.MQA_PROJ_LINEAR, B.mqa_stack_layernorm(x), w["W1"], epilogue=B.MQA_EPI_RELU)
-            B.mqa_project_qkvo_ex(B.MQA_PROJ_LINEAR, u, w["W2"], out=x, epilogue=B.MQA_EPI_ADD)
+            hx = B.mqa_project_add_layernorm(B.MQA_PROJ_O, o.view(b * n, self.h, self.v), w["P_o"], x)
+            u = B.mqa_project_qkvo_ex(B.MQA_PROJ_LINEAR, hx, w["W1"], epilogue=B.MQA_EPI_RELU)
+            if l + 1 < len(self.layers):
+                hx = B.mqa_project_add_layernorm(B.MQA_PROJ_LINEAR, u, w["W2"], x)
+            else:                             # (the last positions are all that is normalised)
+                B.mqa_project_qkvo_ex(B.MQA_PROJ_LINEAR, u, w["W2"], out=x, epilogue=B.MQA_EPI_ADD)
         if now is not self.lens[-1]:      # the lengths advance in the arrays they are in: a caller may hold them
             torch._foreach_copy_(self.lens, self._lens_next)
         last = x.view(b, n, self.d)[:, n - 1].contiguous()

@@ -34,7 +34,8 @@ def bound(x, W):
 # rows, C, N, kv (c contiguous): rows and columns past whole tiles, a last step of 8, 16 and 24 indices, heads inside a step
 ALONE = [(65, 2056, 1032, 8), (190, 1024, 1000, 128), (65, 2048, 2048, 512), (250, 512, 648, 64), (129, 4072, 1024, 8)]
 PARTS = [(1, 4096, 1024, 128), (16, 264, 40, 24), (17, 1048, 1032, 8), (31, 272, 4096, 16), (64, 4096, 1024, 128), (128, 2072, 512, 56),
-         (129, 1024, 1024, 128), (190, 2048, 1288, 64), (224, 520, 136, 40), (3, 256, 8, 8)]
+         (129, 1024, 1024, 128), (190, 2048, 1288, 64), (224, 520, 136, 40), (3, 256, 8, 8),
+         (385, 4072, 1024, 8), (513, 5120, 1288, 40), (1000, 4096, 1024, 128), (1300, 4104, 1016, 24)]      # (parts in tiles of 128 x 128)
 
 
 @pytest.mark.parametrize("layout,rows,C,N,kv", [(layout, *s) for layout in "nc" for s in ALONE] + [("n", 120, 1048, 4088, 8)])
