@@ -214,6 +214,10 @@ def _call_workspace(nbytes, device, stream):
         return torch.empty(nbytes, dtype=torch.uint8, device=device), nbytes
 
 
+# products of new K / V rows below which the library asks for no workspace (small calls are spared the question)
+_KV_ROWS_SMALL = 1 << 28
+
+
 def mqa_decode_num_splits(b, h, cap, k, v, dt, multi_head=False, tuning=None) -> int:
     return int(load_library().mqa_decode_num_splits(b, h, cap, k, v, dt, int(multi_head), _tuning(tuning)))
 
@@ -427,10 +431,12 @@ def mqa_project_append_kv_rows(x, P_k, P_v, K, V, lens_in, lens_out, stream=None
             or K.shape != ((b, cap, k) if one else (b, h_kv, cap, k)) or V.shape != ((b, cap, v) if one else (b, h_kv, cap, v))
             or K.dtype != V.dtype or lens_in.numel() != b or lens_out.numel() != b):
         raise ValueError("shape mismatch in mqa_project_append_kv_rows")
-    dt = _cache_dtype(K)
-    ws, nbytes = _call_workspace(lib.mqa_project_kv_workspace_bytes(b, n, d, h_kv, k, v, dt), x.device, stream)
-    rc = lib.mqa_project_append_kv_rows_ws(_ptr(x), _ptr(P_k), _ptr(P_v), _ptr(K), _ptr(V), _ptr(lens_in), _ptr(lens_out),
-                                           b, n, d, h_kv, cap, k, v, dt, _ptr(ws), nbytes, _stream(stream))
+    dt, args = _cache_dtype(K), (_ptr(x), _ptr(P_k), _ptr(P_v), _ptr(K), _ptr(V), _ptr(lens_in), _ptr(lens_out), b, n, d, h_kv, cap, k, v)
+    if b * n * d * h_kv * (k + v) < _KV_ROWS_SMALL:
+        rc = lib.mqa_project_append_kv_rows(*args, dt, _stream(stream))
+    else:
+        ws, nbytes = _call_workspace(lib.mqa_project_kv_workspace_bytes(b, n, d, h_kv, k, v, dt), x.device, stream)
+        rc = lib.mqa_project_append_kv_rows_ws(*args, dt, _ptr(ws), nbytes, _stream(stream))
     if rc != 0:
         raise MqaError("mqa_project_append_kv_rows", rc)
 
@@ -453,10 +459,12 @@ def mqa_project_memory_kv(M, P_k, P_v, K, V, lens, mem_lens=None, stream=None):
             or (K.dim() == 3) != (P_k.dim() == 2) or K.shape != kshape or V.shape != kshape[:-1] + (v,)
             or K.dtype != V.dtype or lens.numel() != b or (mem_lens is not None and mem_lens.numel() != b)):
         raise ValueError("shape mismatch in mqa_project_memory_kv")
-    dt = _cache_dtype(K)
-    ws, nbytes = _call_workspace(lib.mqa_project_kv_workspace_bytes(b, m, d, h_kv, k, v, dt), M.device, stream)
-    rc = lib.mqa_project_memory_kv_ws(_ptr(M), _ptr(P_k), _ptr(P_v), _ptr(K), _ptr(V), _ptr(mem_lens), _ptr(lens),
-                                      b, m, d, h_kv, cap, k, v, dt, _ptr(ws), nbytes, _stream(stream))
+    dt, args = _cache_dtype(K), (_ptr(M), _ptr(P_k), _ptr(P_v), _ptr(K), _ptr(V), _ptr(mem_lens), _ptr(lens), b, m, d, h_kv, cap, k, v)
+    if b * m * d * h_kv * (k + v) < _KV_ROWS_SMALL:
+        rc = lib.mqa_project_memory_kv(*args, dt, _stream(stream))
+    else:
+        ws, nbytes = _call_workspace(lib.mqa_project_kv_workspace_bytes(b, m, d, h_kv, k, v, dt), M.device, stream)
+        rc = lib.mqa_project_memory_kv_ws(*args, dt, _ptr(ws), nbytes, _stream(stream))
     if rc != 0:
         raise MqaError("mqa_project_memory_kv", rc)
 
