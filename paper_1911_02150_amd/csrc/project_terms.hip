@@ -5,9 +5,11 @@
 // 2^-110 <= |x| < 2^127, off by at most 2^-134 below.  Of the nine products of terms the six largest are added,
 //   a1 b1 + (a1 b2 + a2 b1) + (a1 b3 + a2 b2 + a3 b1)          (the rest is below 2^-24 |a||b|, 2^-27 typically)
 // on v_mfma_f32_16x16x32_bf16: 6 / 16 of the time of the float32 instructions, and one rounding of the running sum for every 32
-// indices and product of terms where they round for every four.  No scales are needed (bfloat16 has float32's exponents),
-// so nothing has to be known of a row or column before it is multiplied.  A wave that meets an infinity or a value from 2^127 on (its
-// first term would be one) multiplies those 32 indices on v_mfma_f32_16x16x4_f32, from the same registers.  Relative error
+// indices and product of terms where they round for every four (terms of bfloat16 and which of their products count: Henry, Tang
+// and Heinecke 2019).  No scales are needed (bfloat16 has float32's exponents), so nothing has to be known of a row or column
+// before it is multiplied.  A product of terms can overflow where the product of the operands does not, or leave an infinity of the
+// other sign or a NaN where that is one infinity: a wave whose sums are not finite at the end multiplies its part
+// again on v_mfma_f32_16x16x4_f32 (as it does where an operand was an infinity or NaN).  Relative error
 // of a 1024-term sum of normal deviates 1.6e-7 (project.hip 2.1e-7, gemm.hip 1.6e-7), of a 4096-term one in four parts 1.7e-7 (4.1e-7).
 //
 // As in project.hip the waves of a workgroup cut the contraction among them and are summed through LDS; operands come
@@ -100,12 +102,8 @@ void project_terms_kernel(const float* __restrict__ in, const float* __restrict_
     }
   };
   floatx4 acc[RB][CB];
-#pragma unroll
-  for (int r = 0; r < RB; ++r)
-#pragma unroll
-    for (int j = 0; j < CB; ++j) acc[r][j] = floatx4{0.f, 0.f, 0.f, 0.f};
-  auto multiply = [&](int step, Raw& x) {
-    if (kStep * (step + 1) > C && kStep * step + 8 * kk >= C) {        // (C is a multiple of 8)
+  auto drop_tail = [&](int step, Raw& x) {     // (C is a multiple of 8)
+    if (kStep * (step + 1) > C && kStep * step + 8 * kk >= C) {
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
 #pragma unroll
@@ -114,23 +112,16 @@ void project_terms_kernel(const float* __restrict__ in, const float* __restrict_
         for (int j = 0; j < CB; ++j) x.b[j][e] = 0.f;
       }
     }
-    float most = 0.f;                          // (passes over NaN, which stays one in its terms)
+  };
+  auto multiply_plain = [&](const Raw& x) {
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
+    for (int e = 0; e < 8; ++e)                // slots 8 kk + e
 #pragma unroll
-      for (int r = 0; r < RB; ++r) most = fmaxf(most, fabsf(x.a[r][e]));
+      for (int r = 0; r < RB; ++r)
 #pragma unroll
-      for (int j = 0; j < CB; ++j) most = fmaxf(most, fabsf(x.b[j][e]));
-    }
-    if (__builtin_expect(__any(!(most < 0x1p127f)), 0)) {
-#pragma unroll
-      for (int e = 0; e < 8; ++e)              // slots 8 kk + e
-#pragma unroll
-        for (int r = 0; r < RB; ++r)
-#pragma unroll
-          for (int j = 0; j < CB; ++j) acc[r][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(x.a[r][e], x.b[j][e], acc[r][j], 0, 0, 0);
-      return;
-    }
+        for (int j = 0; j < CB; ++j) acc[r][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(x.a[r][e], x.b[j][e], acc[r][j], 0, 0, 0);
+  };
+  auto multiply_terms = [&](const Raw& x) {
     Terms b[CB];
 #pragma unroll
     for (int j = 0; j < CB; ++j)
@@ -151,17 +142,39 @@ void project_terms_kernel(const float* __restrict__ in, const float* __restrict_
       product(0, 0);
     }
   };
-  Raw x0, x1;
-  int step = first + wave;
-  if (step < end) load(step, x0);
-  while (step < end) {
-    if (step + kWaves < end) load(step + kWaves, x1);
-    multiply(step, x0);
-    step += kWaves;
-    if (step >= end) break;
-    if (step + kWaves < end) load(step + kWaves, x0);
-    multiply(step, x1);
-    step += kWaves;
+  auto sweep = [&](auto&& multiply) {          // this wave's steps, one in flight while the one before is multiplied
+    Raw x0, x1;
+    int step = first + wave;
+    if (step < end) load(step, x0);
+    while (step < end) {
+      if (step + kWaves < end) load(step + kWaves, x1);
+      drop_tail(step, x0), multiply(x0);
+      step += kWaves;
+      if (step >= end) break;
+      if (step + kWaves < end) load(step + kWaves, x0);
+      drop_tail(step, x1), multiply(x1);
+      step += kWaves;
+    }
+  };
+  auto clear = [&]() {
+#pragma unroll
+    for (int r = 0; r < RB; ++r)
+#pragma unroll
+      for (int j = 0; j < CB; ++j) acc[r][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+  };
+  clear();
+  sweep(multiply_terms);
+  // Whatever overflowed on the way (an operand's first term, a product, a sum) has left an infinity or a NaN behind.
+  float over = 0.f;
+#pragma unroll
+  for (int r = 0; r < RB; ++r)
+#pragma unroll
+    for (int j = 0; j < CB; ++j)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) over = fmaf(acc[r][j][e], 0.f, over);
+  if (__builtin_expect(__any(!(over == 0.f)), 0)) {
+    clear();
+    sweep(multiply_plain);
   }
   // D layout: register e of lane (i, g) is row 4 g + e of the block, column i (KC) or the lane's CB adjacent ones
 #pragma unroll

@@ -81,6 +81,58 @@ def test_values_without_terms(m, layout):
     assert ((got.double() - ref.double()).abs()[fine] <= lim[fine] + 2.0 ** -23 * ref.double().abs()[fine]).all()
 
 
+# one size of every tile, alone and in parts
+FORMS = [(65, 2056, 1032, 8, False), (65, 2048, 2048, 512, False), (129, 4072, 1024, 8, False), (1, 4096, 1024, 128, True), (16, 264, 40, 24, True),
+         (64, 4096, 1024, 128, True), (129, 1024, 1024, 128, True), (190, 2048, 1288, 64, True), (385, 4072, 1024, 8, True)]
+
+
+def results(m, layout, x, W, kv, parts):
+    """(the sums, what they should be) for every epilogue, or of the call with the layernorm."""
+    rows, C, N = x.shape[0], x.shape[1], W.shape[1]
+    mode, P, row = weights(layout, W, kv)
+    sizes = (C, 1, N) if layout == "n" else (N, C // kv, kv)
+    ref = x.double() @ W.double()
+    acc = torch.full((rows, N), 3.0, device=DEV)
+    if parts:
+        assert m.mqa_project_add_layernorm_workspace_bytes(mode, rows, *sizes) > 0
+        m.mqa_project_add_layernorm(mode, x.view(rows, *row), P, acc)
+        return [(acc, ref + 3)]
+    assert m.mqa_project_plan(mode, rows, *sizes) == 1
+    product = lambda e, out=None: m.mqa_project_qkvo_ex(mode, x.view(rows, *row), P, out=out, epilogue=e)  # noqa: E731
+    return [(product(m.MQA_EPI_STORE), ref), (product(m.MQA_EPI_RELU), ref.clamp(min=0)), (product(m.MQA_EPI_ADD, acc), ref + 3)]
+
+
+def agree(got, want, most):
+    """Infinities where the float32 result has them, no NaN, and the rest within `most` and a rounding of the result."""
+    ref = want.float()
+    assert not torch.isnan(got).any()
+    assert torch.equal(torch.isposinf(got), torch.isposinf(ref)) and torch.equal(torch.isneginf(got), torch.isneginf(ref))
+    fine = torch.isfinite(ref)
+    assert ((got.double() - want).abs()[fine] <= (most + 2.0 ** -22 * (want.abs() + 3))[fine]).all()
+
+
+@pytest.mark.parametrize("layout", ["n", "c"])
+@pytest.mark.parametrize("rows,C,N,kv,parts", FORMS)
+def test_products_past_the_largest_float(m, layout, rows, C, N, kv, parts):
+    """Finite operands whose products are past the largest float, or just below it (where the product of the first terms is not)."""
+    g = torch.Generator(device=DEV)
+    g.manual_seed(rows + N)
+    x, W = torch.randn(rows, C, generator=g, device=DEV), torch.randn(C, N, generator=g, device=DEV) / 16
+    at = [C // 5, C // 2, C - 3]               # in steps of their own, and rows of their own where there are as many
+    near = 1.997 * 2.0 ** 63
+    for i, r in zip(range(3), (rows - 1, rows // 2, 0)):
+        if i and rows < 3:
+            break
+        x[r, at[i]] = (1e30, -1e30, near)[i]
+        W[at[i], 3 * i] = (1e30, 1e30, near)[i]
+    if rows >= 3:
+        x[0, :at[2]], x[0, at[2] + 1:] = 0, 0
+    most = torch.nan_to_num(bound(x, W), posinf=0.0)
+    for got, want in results(m, layout, x, W, kv, parts):
+        assert torch.isposinf(got[rows - 1, 0])
+        agree(got, want, most)
+
+
 @pytest.mark.parametrize("with_workspace", [True, False])
 @pytest.mark.parametrize("layout", ["n", "c"])
 @pytest.mark.parametrize("rows,C,N,kv", PARTS)
