@@ -2,14 +2,15 @@
 // P [h, d, kv] as in project.hip, from three bfloat16 terms per float32 operand.
 //
 // x = a1 + a2 + a3, each the nearest bfloat16 of what the ones before it leave: exact (8 + 8 + 8 significant bits) for
-// 2^-110 <= |x| < 2^127, off by at most 2^-134 below.  Of the nine products of terms the six largest are added,
+// 2^-110 <= |x| < 2^127 and 0 (below, the last bits of the third term are past bfloat16's smallest).  Of the nine products of terms the six largest are added,
 //   a1 b1 + (a1 b2 + a2 b1) + (a1 b3 + a2 b2 + a3 b1)          (the rest is below 2^-24 |a||b|, 2^-27 typically)
 // on v_mfma_f32_16x16x32_bf16: 6 / 16 of the time of the float32 instructions, and one rounding of the running sum for every 32
 // indices and product of terms where they round for every four (terms of bfloat16 and which of their products count: Henry, Tang
 // and Heinecke 2019).  No scales are needed (bfloat16 has float32's exponents), so nothing has to be known of a row or column
 // before it is multiplied.  A product of terms can overflow where the product of the operands does not, or leave an infinity of the
-// other sign or a NaN where that is one infinity: a wave whose sums are not finite at the end multiplies its part
-// again on v_mfma_f32_16x16x4_f32 (as it does where an operand was an infinity or NaN).  Relative error
+// other sign or a NaN where that is one infinity: a wave whose sums are not finite at the end, or that met an operand below
+// 2^-110 other than 0, multiplies its part again on v_mfma_f32_16x16x4_f32 (as it does where an operand was an infinity or
+// NaN).  Relative error
 // of a 1024-term sum of normal deviates 1.6e-7 (project.hip 2.1e-7, gemm.hip 1.6e-7), of a 4096-term one in four parts 1.7e-7 (4.1e-7).
 //
 // As in project.hip the waves of a workgroup cut the contraction among them and are summed through LDS; operands come
@@ -33,6 +34,8 @@ typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 
 constexpr int kWaves = 8, kStep = 32;          // (a step: the indices of one instruction)
 constexpr int kWideStage = 32;                 // indices of a stage of gemm.hip's 128 x 128 tiles: parts are whole stages
+
+constexpr uint32_t kLeast = (0x08800000u << 1) - 1;          // 2^-110, in the order of the kernel's `least`
 
 struct Terms { u32x4 t[3]; };                  // eight values
 
@@ -121,7 +124,16 @@ void project_terms_kernel(const float* __restrict__ in, const float* __restrict_
 #pragma unroll
         for (int j = 0; j < CB; ++j) acc[r][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(x.a[r][e], x.b[j][e], acc[r][j], 0, 0, 0);
   };
+  uint32_t least = ~0u;                        // of the operands' magnitudes in order, zero last
+  auto look = [&](float v) { least = min(least, (__float_as_uint(v) << 1) - 1u); };
   auto multiply_terms = [&](const Raw& x) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+#pragma unroll
+      for (int r = 0; r < RB; ++r) look(x.a[r][e]);
+#pragma unroll
+      for (int j = 0; j < CB; ++j) look(x.b[j][e]);
+    }
     Terms b[CB];
 #pragma unroll
     for (int j = 0; j < CB; ++j)
@@ -164,7 +176,8 @@ void project_terms_kernel(const float* __restrict__ in, const float* __restrict_
   };
   clear();
   sweep(multiply_terms);
-  // Whatever overflowed on the way (an operand's first term, a product, a sum) has left an infinity or a NaN behind.
+  // An operand too small for its terms; and whatever overflowed on the way (an operand's first term, a product, a sum) has left an
+  // infinity or a NaN behind.
   float over = 0.f;
 #pragma unroll
   for (int r = 0; r < RB; ++r)
@@ -172,7 +185,7 @@ void project_terms_kernel(const float* __restrict__ in, const float* __restrict_
     for (int j = 0; j < CB; ++j)
 #pragma unroll
       for (int e = 0; e < 4; ++e) over = fmaf(acc[r][j][e], 0.f, over);
-  if (__builtin_expect(__any(!(over == 0.f)), 0)) {
+  if (__builtin_expect(__any(!(over == 0.f) || least < kLeast), 0)) {
     clear();
     sweep(multiply_plain);
   }

@@ -92,14 +92,14 @@ def results(m, layout, x, W, kv, parts):
     mode, P, row = weights(layout, W, kv)
     sizes = (C, 1, N) if layout == "n" else (N, C // kv, kv)
     ref = x.double() @ W.double()
-    acc = torch.full((rows, N), 3.0, device=DEV)
+    acc = torch.zeros(rows, N, device=DEV)
     if parts:
         assert m.mqa_project_add_layernorm_workspace_bytes(mode, rows, *sizes) > 0
         m.mqa_project_add_layernorm(mode, x.view(rows, *row), P, acc)
-        return [(acc, ref + 3)]
+        return [(acc, ref)]
     assert m.mqa_project_plan(mode, rows, *sizes) == 1
     product = lambda e, out=None: m.mqa_project_qkvo_ex(mode, x.view(rows, *row), P, out=out, epilogue=e)  # noqa: E731
-    return [(product(m.MQA_EPI_STORE), ref), (product(m.MQA_EPI_RELU), ref.clamp(min=0)), (product(m.MQA_EPI_ADD, acc), ref + 3)]
+    return [(product(m.MQA_EPI_STORE), ref), (product(m.MQA_EPI_RELU), ref.clamp(min=0)), (product(m.MQA_EPI_ADD, acc), ref)]
 
 
 def agree(got, want, most):
@@ -108,7 +108,7 @@ def agree(got, want, most):
     assert not torch.isnan(got).any()
     assert torch.equal(torch.isposinf(got), torch.isposinf(ref)) and torch.equal(torch.isneginf(got), torch.isneginf(ref))
     fine = torch.isfinite(ref)
-    assert ((got.double() - want).abs()[fine] <= (most + 2.0 ** -22 * (want.abs() + 3))[fine]).all()
+    assert ((got.double() - want).abs()[fine] <= (most + 2.0 ** -23 * want.abs())[fine]).all()
 
 
 @pytest.mark.parametrize("layout", ["n", "c"])
@@ -131,6 +131,24 @@ def test_products_past_the_largest_float(m, layout, rows, C, N, kv, parts):
     for got, want in results(m, layout, x, W, kv, parts):
         assert torch.isposinf(got[rows - 1, 0])
         agree(got, want, most)
+
+
+@pytest.mark.parametrize("small", ["rows", "columns"])
+@pytest.mark.parametrize("layout", ["n", "c"])
+@pytest.mark.parametrize("rows,C,N,kv,parts", FORMS)
+def test_operands_near_the_smallest_float(m, layout, rows, C, N, kv, parts, small):
+    """Rows (columns) down to subnormal values against columns (rows) that bring the sums back into range, among zeros."""
+    g = torch.Generator(device=DEV)
+    g.manual_seed(rows + N)
+    x, W = torch.randn(rows, C, generator=g, device=DEV), torch.randn(C, N, generator=g, device=DEV)
+    x[:, 1::7], W[2::5] = 0, 0
+    lines, others = (x, W.t()) if small == "rows" else (W.t(), x)
+    for i, e in {i * lines.shape[0] // 5: e for i, e in enumerate((-111, -116, -124, -132, -146))}.items():
+        lines[i] *= 2.0 ** e
+    others[others.shape[0] // 2:] *= 2.0 ** 70
+    # the products and their sums are rounded to whole subnormals besides
+    for got, want in results(m, layout, x, W, kv, parts):
+        agree(got, want, bound(x, W) + C * 2.0 ** -149)
 
 
 @pytest.mark.parametrize("with_workspace", [True, False])
