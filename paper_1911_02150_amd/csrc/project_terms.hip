@@ -4,21 +4,23 @@
 // x = a1 + a2 + a3, each the nearest bfloat16 of what the ones before it leave: exact (8 + 8 + 8 significant bits) for
 // 2^-110 <= |x| < 2^127 and 0 (below, the last bits of the third term are past bfloat16's smallest).  Of the nine products of terms the six largest are added,
 //   a1 b1 + (a1 b2 + a2 b1) + (a1 b3 + a2 b2 + a3 b1)          (the rest is below 2^-24 |a||b|, 2^-27 typically)
-// on v_mfma_f32_16x16x32_bf16: 6 / 16 of the time of the float32 instructions, and one rounding of the running sum for every 32
-// indices and product of terms where they round for every four (terms of bfloat16 and which of their products count: Henry, Tang
-// and Heinecke 2019).  No scales are needed (bfloat16 has float32's exponents), so nothing has to be known of a row or column
+// on v_mfma_f32_16x16x32_bf16: 6 / 16 of the time of the float32 instructions (terms of bfloat16 and which of their products
+// count: Henry, Tang and Heinecke 2019).  a1 b1 and the five small ones have a running sum each, added at the end: the small ones' is
+// some 2^-8 of the other, so what is left is one rounding of the sum for every 32 indices where the float32 instructions
+// round for every four.  No scales are needed (bfloat16 has float32's exponents), so nothing has to be known of a row or column
 // before it is multiplied.  A product of terms can overflow where the product of the operands does not, or leave an infinity of the
 // other sign or a NaN where that is one infinity: a wave whose sums are not finite at the end, or that met an operand below
 // 2^-110 other than 0, multiplies its part again on v_mfma_f32_16x16x4_f32 (as it does where an operand was an infinity or
-// NaN).  Relative error
-// of a 1024-term sum of normal deviates 1.6e-7 (project.hip 2.1e-7, gemm.hip 1.6e-7), of a 4096-term one in four parts 1.7e-7 (4.1e-7).
+// NaN).  Relative error of a 1024-term sum of normal deviates 8.1e-8 (all six products in one running sum 1.6e-7, project.hip
+// 2.1e-7, gemm.hip 1.6e-7), of a 4096-term one 1.4e-7 (3.5e-7, 4.1e-7), in eight parts 9.1e-8; with every other x a zero, as behind
+// a relu, 7.1e-8 (1.6e-7, 1.5e-7), 1.1e-7 (3.3e-7, 2.9e-7) and 8.2e-8.
 //
 // As in project.hip the waves of a workgroup cut the contraction among them and are summed through LDS; operands come
 // from L2 straight into their registers, two steps in flight.  S > 1: the contraction is cut among S workgroups as well, and their
 // partial tiles (in the workspace) are summed by finish_kernel, together with what follows the product: the residual and
 // the next layernorm.
-// Measured (128 rows, 4096 x 1024, weights from HBM): 15 us + 3.5 of finish_kernel (project.hip 25 and a layernorm of 3); 64 rows: 13.5
-// with both (22).  Of the 15: vector instructions 7 (splitting: 11 for two values), matrix cores 3, the first operands 3; on
+// Measured (128 rows, 4096 x 1024, weights from HBM): 14.5 us + 3.5 of finish_kernel (project.hip 25 and a layernorm of 3); 64 rows: 13.5
+// with both (22).  Of the 14.5: vector instructions 7 (splitting: 11 for two values), matrix cores 3, the first operands 3; on
 // the float32 instructions alone it takes the same time (they need no splitting, and 8 us).  Tiles of 64 x 64: 29 (spills), of
 // 64 x 32: 19.5.
 #include "common.hpp"
@@ -104,7 +106,7 @@ void project_terms_kernel(const float* __restrict__ in, const float* __restrict_
       }
     }
   };
-  floatx4 acc[RB][CB];
+  floatx4 acc[RB][CB], low[RB][CB];
   auto drop_tail = [&](int step, Raw& x) {     // (C is a multiple of 8)
     if (kStep * (step + 1) > C && kStep * step + 8 * kk >= C) {
 #pragma unroll
@@ -144,14 +146,14 @@ void project_terms_kernel(const float* __restrict__ in, const float* __restrict_
       Terms a;
 #pragma unroll
       for (int q = 0; q < 4; ++q) split3(x.a[r][2 * q], x.a[r][2 * q + 1], a, q);
-      auto product = [&](int pa, int pb) {
+      auto product = [&](floatx4 (&to)[CB], int pa, int pb) {
 #pragma unroll
         for (int j = 0; j < CB; ++j)
-          acc[r][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a.t[pa]), __builtin_bit_cast(bf16x8, b[j].t[pb]), acc[r][j], 0, 0, 0);
+          to[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a.t[pa]), __builtin_bit_cast(bf16x8, b[j].t[pb]), to[j], 0, 0, 0);
       };
-      product(0, 2), product(1, 1), product(2, 0);             // smallest first
-      product(0, 1), product(1, 0);
-      product(0, 0);
+      product(acc[r], 0, 0);
+      product(low[r], 0, 1), product(low[r], 1, 0);
+      product(low[r], 1, 1), product(low[r], 0, 2), product(low[r], 2, 0);
     }
   };
   auto sweep = [&](auto&& multiply) {          // this wave's steps, one in flight while the one before is multiplied
@@ -172,10 +174,14 @@ void project_terms_kernel(const float* __restrict__ in, const float* __restrict_
 #pragma unroll
     for (int r = 0; r < RB; ++r)
 #pragma unroll
-      for (int j = 0; j < CB; ++j) acc[r][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+      for (int j = 0; j < CB; ++j) acc[r][j] = low[r][j] = floatx4{0.f, 0.f, 0.f, 0.f};
   };
   clear();
   sweep(multiply_terms);
+#pragma unroll
+  for (int r = 0; r < RB; ++r)
+#pragma unroll
+    for (int j = 0; j < CB; ++j) acc[r][j] += low[r][j];
   // An operand too small for its terms; and whatever overflowed on the way (an operand's first term, a product, a sum) has left an
   // infinity or a NaN behind.
   float over = 0.f;
@@ -342,6 +348,11 @@ TermsForm terms_form(bool outp, int rows, int d, int h, int kv) {
 // 1024 indices and 0.4 per MiB (4096 x 1024, 512 rows: 49 / 32, 1024: 71 / 48, 2048: 99 / 80; 5120 x 1280, 512: 84 / 49, 1536: 120 / 93;
 // 1024 x 1024, 1024: 23 / 25), against a product by gemm_form and a layernorm; up to 256 rows the smaller tiles are as fast (a stack step of 256
 // rows: 394, with these 400).
+//   Those tiles hold an operand in 22 to 24 bits.  Where the product alone would be one of all 24 (gemm_form 0), they are taken only if the sum is long
+// enough for their error to be the smaller one, whatever the values (relative error of float32 instructions / these; normal deviates, every other x a
+// zero, wide tails, one channel in 97 of 30 times the rest, all positive): 4096 terms, 260 to 448 rows 4.1e-7 / 2.1e-7, 2.9e-7 / 2.1e-7, 4.1e-7 / 2.1e-7,
+// 4.1e-7 / 2.1e-7, 1.3e-7 / 6.5e-8; 2048, 600 rows 2.9e-7 / 1.7e-7, 2.1e-7 / 1.7e-7, 2.9e-7 / 1.7e-7, 3.0e-7 / 1.7e-7, 8.4e-8 / 5.2e-8; but 1024, 260 rows
+// 2.1e-7 / 1.6e-7, 1.53e-7 / 1.60e-7, 2.1e-7 / 1.7e-7, 2.2e-7 / 1.7e-7, 7.4e-8 / 5.9e-8.
 TermsForm terms_parts_form(bool outp, int rows, int d, int h, int kv) {
   const int N = outp ? d : h * kv, C = outp ? h * kv : d;
   TermsForm best{0, 0, 0};
@@ -359,7 +370,7 @@ TermsForm terms_parts_form(bool outp, int rows, int d, int h, int kv) {
     }
   }
   const long long wide = workgroups(8, 8, rows, N);
-  if (rows > (best.S ? 256 : 128) && wide <= 128 && gemm_fits(outp, d, h, kv, 128)) {
+  if (rows > (best.S ? 256 : 128) && wide <= 128 && gemm_fits(outp, d, h, kv, 128) && (C >= 1280 || gemm_form(outp ? 3 : 0, rows, d, h, kv, 0))) {
     int S = 2;
     while (S < 16 && 2 * S * wide <= 256 && C >= 512 * S) S *= 2;
     const int stages = (C + kWideStage - 1) / kWideStage, per = (stages + S - 1) / S;
