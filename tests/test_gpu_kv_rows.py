@@ -140,6 +140,31 @@ def test_rows_of_any_values(m):
     assert same(K, want) and same(V, expected(x, P_v, 0))
 
 
+@pytest.mark.parametrize("with_workspace", [True, False])
+def test_lines_with_a_nan(m, with_workspace):
+    """A NaN (of either sign) makes its row or column the quiet NaN that the integer kernels store, without summing: as many as open a
+    whole tile to the float64 sums otherwise.  So does an infinity against a row of zeros."""
+    from paper_1911_02150_amd import binding
+    lib = binding.load_library()
+    b, n, d = 64, 300, 200
+    x, P_k, P_v = inputs(b, n, d, 0, 128, 128, 11)
+    nan = torch.tensor([0x7fc00000, -0x400000], dtype=torch.int32, device=DEV).view(torch.float32)
+    x[::2, ::20, 7] = nan[0]
+    x[1::2, ::20, d - 1] = nan[1]
+    P_k[5, 3], P_v[d - 1, 127] = nan[1], nan[0]
+    P_v[0, 5], x[4, 10] = float("inf"), 0
+    K, V = caches(b, 0, n, 128, 128)
+    lens = torch.zeros(b, dtype=torch.int32, device=DEV)
+    nbytes = lib.mqa_project_kv_workspace_bytes(b, n, d, 1, 128, 128, m.MQA_BF16) if with_workspace else 0
+    assert m.mqa_project_kv_plan(b * n, d, 0, 1, 128, 128, m.MQA_BF16) == 1 and (nbytes > 0) == with_workspace
+    ws = torch.empty(max(16, nbytes), dtype=torch.uint8, device=DEV)
+    assert lib.mqa_project_memory_kv_ws(x.data_ptr(), P_k.data_ptr(), P_v.data_ptr(), K.data_ptr(), V.data_ptr(), None, lens.data_ptr(), b, n, d, 1, n,
+                                        128, 128, m.MQA_BF16, ws.data_ptr(), nbytes, torch.cuda.current_stream().cuda_stream) == 0
+    for got, P in ((K, P_k), (V, P_v)):
+        want = expected(x, P, 0)
+        assert same(got, want) and (got.view(torch.int16)[torch.isnan(want)] == 0x7fc0).all()
+
+
 @pytest.mark.parametrize("sign", [1, -1])
 def test_sums_around_a_power_of_two(m, sign):
     """Sums that end just above and just below 2^42, whose error bound (what the fixed point drops of the values beside one
