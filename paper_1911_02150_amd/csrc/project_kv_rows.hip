@@ -25,6 +25,12 @@ using namespace kv_fixed;
 constexpr int kRows = 64, kColumns = 128;      // of a tile
 constexpr int kGroups = 512;                   // two workgroups per compute unit
 
+// Open elements of a tile (of 8192) from which its waves sum all of it in float64.  One element costs half a wave about 5 us of latency
+// (more from 1024 indices on), all of them 0.26 us for each index.  us, with one channel of the rows 2^7 / 2^8 / 2^9 / 2^10 times the others and its
+// weights as much smaller, one by one against all: 32768 rows, d = 1024: 209 / 265 / 360 / 525 against 406; 19200 rows, d = 200:
+// 74 / 100 / 144 / 231 against 82; one row with an infinity (128 open) in every 1024: 221 against 401 and 137 against 82.
+__device__ __forceinline__ int most_open(int C) { return min(3 * C / 8, 512); }
+
 // Workspace: digits [column block of 32][step of 32 indices][digit][lane][16 bytes], columns [N][C] floats, lines [columns
 // padded] (of 16 bytes).
 struct KvPrepared {
@@ -335,7 +341,7 @@ void kv_rows_kernel(KvRowsParams p) {
     __syncthreads();
     const int left = *count;
     const float* columns = reinterpret_cast<const float*>(p.ws + w.columns());
-    if (left > kMostOpen * kRows * kColumns / 16384) {
+    if (left > most_open(C)) {
       // the whole tile in float64: 32 rows x 64 columns per wave
       const int r0 = wave / 2 * 32, c0 = wave % 2 * 64;
       float64_tile(
@@ -371,7 +377,7 @@ void kv_rows_kernel(KvRowsParams p) {
       uint16_t* const at = place(r);
       if (at) *reinterpret_cast<uint4*>(at) = *reinterpret_cast<const uint4*>(out + r * T::ROW + 2 * c8);
     };
-    if (left > kMostOpen * kRows * kColumns / 16384) {
+    if (left > most_open(C)) {
       for (int r = tid / (kColumns / 8); r < kRows; r += PASS) finish(r);
     } else {
       // a listed element's eight columns, by the threads that have that part of a row
