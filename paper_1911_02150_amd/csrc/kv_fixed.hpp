@@ -70,9 +70,7 @@ __device__ __forceinline__ float digit_sum(int t0, int t1, int t2, int t3) {
 // The element's bf16 from that sum, and whether the bound leaves it open: if a tie (the middle of the low 16 bits) is no
 // further off than the bound and the rounding to float (one unit of the last place); just above a power of two the tie below
 // is in the next binade: half the spacing, 0x4000 below the power itself.  A sum that leaves the normal floats is open as
-// well, and so is 0 (nothing is left of the sum) unless a line is all zeros.  A NaN for a bound is one for the element (a NaN in a
-// line, or an infinity against a line of zeros): nothing is open then (left to float64, one row of NaN in every 64 of a memory of
-// 64 x 512, d = 1024: 405 -> 116 us with a workspace, 465 -> 175 without).
+// well, and so is 0 (nothing is left of the sum) unless a line is all zeros.
 __device__ __forceinline__ uint32_t rounded_sum(float mid, Line row, Line col, bool* is_open) {
   const float bound = fmaf(row.r, col.r, row.w + col.w);
   const int scale = row.exponent + col.exponent;
@@ -83,9 +81,17 @@ __device__ __forceinline__ uint32_t rounded_sum(float mid, Line row, Line col, b
   const int e_out = (int)(bits << 1 >> 24) + scale;
   const bool apart = bound < (float)(off - 1) * unit && e_out >= 2 && e_out <= 253;
   const uint32_t out = bits + ((uint32_t)scale << 23);
-  const bool nan = bound != bound;
-  *is_open = !nan && (mid == 0.f ? !(bound < 0.f) : !apart);
-  return nan ? 0x7fc0u : mid == 0.f ? 0 : (out + 0x7fffu + (out >> 16 & 1u)) >> 16;
+  *is_open = mid == 0.f ? !(bound < 0.f) : !apart;
+  return mid == 0.f ? 0 : (out + 0x7fffu + (out >> 16 & 1u)) >> 16;
+}
+
+// Of an open element: is it NaN (a NaN in a line, or an infinity against a line of zeros)?  It needs no summing then: one row of NaN in
+// every 64 of a memory of 64 x 512, d = 1024: 405 -> 116 us with a workspace, 465 -> 175 without.  (Asked for every element in
+// rounded_sum it cost 0.8 us of the 140 of such a memory without a NaN.)
+constexpr uint32_t kNan = 0x7fc0u;
+__device__ __forceinline__ bool is_nan(Line row, Line col) {
+  const float w = row.w + col.w;
+  return w != w;
 }
 
 // 32 rows x 64 columns by one wave, in float64 from global memory: register e of lane (i, kk) of a 16 x 16 block is row

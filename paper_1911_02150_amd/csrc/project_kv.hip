@@ -237,8 +237,12 @@ void project_kv_exact_kernel(KvParams p) {
       bool open[2];
 #pragma unroll
       for (int j = 0; j < 2; ++j) {
-        out |= rounded_sum(digit_sum(t[0][j], t[1][j], t[2][j], t[3][j]), mine, col[j], &open[j]) << (16 * j);
-        if (open[j]) list[atomicAdd(count, 1)] = (uint16_t)(r << 7 | (2 * slot + j));
+        uint32_t v = rounded_sum(digit_sum(t[0][j], t[1][j], t[2][j], t[3][j]), mine, col[j], &open[j]);
+        if (open[j]) {
+          if (is_nan(mine, col[j])) v = kNan, open[j] = false;
+          else list[atomicAdd(count, 1)] = (uint16_t)(r << 7 | (2 * slot + j));
+        }
+        out |= v << (16 * j);
       }
       uint16_t* at = place(row, n);
       if (at) {

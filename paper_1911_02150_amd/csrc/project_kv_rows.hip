@@ -329,6 +329,11 @@ void kv_rows_kernel(KvRowsParams p) {
         v[j] = rounded_sum((&mid[j >> 2].x)[j & 3], mine, cols[j], &o);
         open |= o ? 1u << j : 0u;
       }
+      if (open) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+          if ((open >> j & 1u) && is_nan(mine, cols[j])) v[j] = kNan, open &= ~(1u << j);
+      }
       const uint4 packed = make_uint4(v[0] | v[1] << 16, v[2] | v[3] << 16, v[4] | v[5] << 16, v[6] | v[7] << 16);
       uint16_t* const at = place(r);
       if (open && at) {                        // (written once they are known)
