@@ -215,7 +215,11 @@ void project_kv_exact_kernel(KvParams p) {
   // the lines take the places of their sums of squares
   static_assert(sizeof(Line) <= 16, "a line takes the place of its four sums");
   auto line_at = [&](int i) -> Line& { return *reinterpret_cast<Line*>(norm + 4 * i); };
-  if (tid < 256) line_at(tid) = line_of(norm + 4 * tid, most[tid], C);
+  if (tid < 256) {
+    const int4v sums = *reinterpret_cast<const int4v*>(norm + 4 * tid);      // (all of them, before the first float goes into their place)
+    const int squares[4] = {sums[0], sums[1], sums[2], sums[3]};
+    line_at(tid) = line_of(squares, most[tid], C);
+  }
   __syncthreads();
   const Line col[2] = {line_at(128 + slot), line_at(192 + slot)};
   for (int chunk = 0; chunk < 4; ++chunk) {
