@@ -278,10 +278,10 @@ int project_impl(int mode, const float* in, const float* P, float* out, int rows
 int kv_rows_impl(const float* x, const float* P_k, const float* P_v, void* K, void* V, const int32_t* lens_in, int32_t* lens_out,
                  int b, int n, int append, int d, int h_kv, int cap, int k, int v, int dt, void* workspace,
                  size_t workspace_bytes, void* stream) {
-  if (!x || !P_k || !P_v || !K || !V || !lens_out) return MQA_ERR_NULL;
+  if (!x || !P_k || !P_v || !K || !V || !lens_out || (append && !lens_in)) return MQA_ERR_NULL;
   if (dt != MQA_F32 && dt != MQA_BF16) return MQA_ERR_DTYPE;
   if (b <= 0 || n <= 0 || d <= 0 || h_kv <= 0 || cap <= 0 || k <= 0 || v <= 0 || n > cap) return MQA_ERR_SHAPE;
-  if ((d & 7) || (k & 15) || (v & 15) || (long long)b * n > (1ll << 30)) return MQA_ERR_SHAPE;
+  if ((d & 7) || (k & 15) || (v & 15) || (long long)b * n > (1ll << 30) || (append && lens_in == lens_out)) return MQA_ERR_SHAPE;
   if (misaligned(x) || misaligned(P_k) || misaligned(P_v) || misaligned(K) || misaligned(V) || misaligned(lens_out) ||
       (lens_in && misaligned(lens_in)) || (workspace && misaligned(workspace)))
     return MQA_ERR_ALIGN;
@@ -625,8 +625,6 @@ int mqa_project_append_kv_rows(const float* x, const float* P_k, const float* P_
 int mqa_project_append_kv_rows_ws(const float* x, const float* P_k, const float* P_v, void* K, void* V,
                                   const int32_t* lens_in, int32_t* lens_out, int b, int n, int d, int h_kv, int cap,
                                   int k, int v, mqa_dtype dt, void* workspace, size_t workspace_bytes, void* stream) {
-  if (!lens_in) return MQA_ERR_NULL;
-  if (lens_in == lens_out) return MQA_ERR_SHAPE;
   return kv_rows_impl(x, P_k, P_v, K, V, lens_in, lens_out, b, n, 1, d, h_kv, cap, k, v, (int)dt, workspace, workspace_bytes, stream);
 }
 

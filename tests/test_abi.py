@@ -123,6 +123,24 @@ def test_argument_validation_without_gpu():
     assert rd(A, 24, A, None) == 2 and rd(None, 32, A, None) == 1
 
 
+@pytest.mark.parametrize("name", ["mqa_project_append_kv_rows", "mqa_project_append_kv_rows_ws"])
+def test_append_rows_reports_the_first_fault(name):
+    """Missing tensors before the type, the type before the sizes and the lengths' place, the alignment last."""
+    fn = getattr(ctypes.CDLL(LIB), name)
+    vp, ci = ctypes.c_void_p, ctypes.c_int
+    fn.argtypes = [vp] * 7 + [ci] * 8 + ([vp, ctypes.c_size_t] if name.endswith("ws") else []) + [vp]
+    A, B, U = 0x10000, 0x20000, 0x10004
+
+    def call(ptrs, dt=1, k=128):
+        return fn(*ptrs, 2, 4, 128, 1, 64, k, 128, dt, *([None, 0] if name.endswith("ws") else []), None)
+
+    for missing in range(7):
+        assert call([None if i == missing else A for i in range(7)]) == 1
+    assert call([None] + [A] * 6) == 1 and call([A] * 7, dt=9) == 5
+    assert call([A] * 7) == 2 and call([U] + [A] * 6) == 2 and call([A] * 6 + [B], k=100) == 2
+    assert call([U] + [A] * 5 + [B]) == 3 and call([A] * 5 + [U, B]) == 3
+
+
 def test_beam_entry_points_validate_without_gpu():
     import paper_1911_02150_amd as m
     lib = ctypes.CDLL(LIB)
