@@ -309,8 +309,11 @@ hipError_t launch_tiles(bool outp, TermsForm f, const float* in, const float* P,
 }
 
 long long workgroups(int RB, int CB, int rows, int N) {
-  return (long long)((rows + 16 * RB - 1) / (16 * RB)) * ((N + 16 * CB - 1) / (16 * CB));
+  return ((long long)rows + 16 * RB - 1) / (16 * RB) * (((long long)N + 16 * CB - 1) / (16 * CB));
 }
+
+// (sizes whose columns or contraction do not fit an int have no form)
+bool counts(int h, int kv) { return (long long)h * kv <= 1ll << 30; }
 
 }  // namespace
 
@@ -323,6 +326,7 @@ long long workgroups(int RB, int CB, int rows, int N) {
 // 1024 x 1024, 128: 7.6 / 7.6; 512 x 640: 5.5 / 5.9), and with c contiguous gemm.hip's are where 32 x 64 is the smallest (1024 x 1024, 384: 15.2 / 15.6;
 // 1536 x 1280, 384: 19.7 / 22.6).  A full round of the widest rows stays with gemm.hip as well (512 rows, 1024 x 1024: 14.6 / 12.7).
 TermsForm terms_form(bool outp, int rows, int d, int h, int kv) {
+  if (!counts(h, kv)) return TermsForm{0, 0, 0};
   const int N = outp ? d : h * kv, C = outp ? h * kv : d;
   if (rows <= 16) return TermsForm{0, 0, 0};               // (1024 x 4096, 16: 8.6 / 9.2)
   static const TermsForm order[] = {{1, 1, 1}, {1, 2, 1}, {2, 2, 1}, {2, 4, 1}};
@@ -354,8 +358,9 @@ TermsForm terms_form(bool outp, int rows, int d, int h, int kv) {
 // 4.1e-7 / 2.1e-7, 1.3e-7 / 6.5e-8; 2048, 600 rows 2.9e-7 / 1.7e-7, 2.1e-7 / 1.7e-7, 2.9e-7 / 1.7e-7, 3.0e-7 / 1.7e-7, 8.4e-8 / 5.2e-8; but 1024, 260 rows
 // 2.1e-7 / 1.6e-7, 1.53e-7 / 1.60e-7, 2.1e-7 / 1.7e-7, 2.2e-7 / 1.7e-7, 7.4e-8 / 5.9e-8.
 TermsForm terms_parts_form(bool outp, int rows, int d, int h, int kv) {
-  const int N = outp ? d : h * kv, C = outp ? h * kv : d;
   TermsForm best{0, 0, 0};
+  if (!counts(h, kv)) return best;
+  const int N = outp ? d : h * kv, C = outp ? h * kv : d;
   if (N > 4096) return best;
   double least = 1e30;
   if (workgroups(2, 4, rows, N) <= (outp ? 160 : C >= N ? 240 : 128)) {

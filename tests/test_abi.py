@@ -141,6 +141,17 @@ def test_append_rows_reports_the_first_fault(name):
     assert call([U] + [A] * 5 + [B]) == 3 and call([A] * 5 + [U, B]) == 3
 
 
+def test_workspace_of_sizes_past_the_integers():
+    """Rows, and heads times columns, whose tiles are more than an int holds: no parts, so no workspace."""
+    import paper_1911_02150_amd as m
+    query = m.mqa_project_add_layernorm_workspace_bytes
+    for rows in (2 ** 31 - 1, 2 ** 31 - 100):
+        assert query(m.MQA_PROJ_O, rows, 8, 1, 1024) == 0 and query(m.MQA_PROJ_LINEAR, rows, 1024, 1, 8) == 0
+    for h, kv in ((2 ** 20, 2 ** 12), (2 ** 20, 2 ** 12 + 8), (2 ** 28, 24)):
+        assert all(query(m.MQA_PROJ_O, rows, 1024, h, kv) == 0 for rows in (1, 300))
+    assert query(m.MQA_PROJ_O, 128, 1024, 8, 128) > 0
+
+
 def test_beam_entry_points_validate_without_gpu():
     import paper_1911_02150_amd as m
     lib = ctypes.CDLL(LIB)
