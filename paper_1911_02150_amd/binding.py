@@ -205,13 +205,29 @@ def _default_workspace(device, nbytes, stream=None):
 def _call_workspace(nbytes, device, stream):
     """Scratch memory for one call of several launches, and its size: a block of torch's caching allocator, allocated
     with the call's stream current, so that it goes to later work of that stream only (calls of other threads
-    on the same stream get blocks of their own)."""
+    on the same stream get blocks of their own).  (None, 0), which every such call takes as well, where there is no such
+    block: while the stream is captured (a graph that torch does not capture itself would keep writing to a block that the
+    allocator has given to others), for tensors of another device than the one whose stream is taken, and without memory."""
     if nbytes == 0:
         return None, 0
-    if stream is None:
-        return torch.empty(nbytes, dtype=torch.uint8, device=device), nbytes
-    with torch.cuda.stream(stream):
-        return torch.empty(nbytes, dtype=torch.uint8, device=device), nbytes
+    if stream is not None and not isinstance(stream, torch.cuda.Stream):      # (any object with a cuda_stream will do)
+        handle = stream.cuda_stream
+        stream = torch.cuda.ExternalStream(handle, device=device) if handle else torch.cuda.default_stream(device)
+    if device.index != (torch.cuda.current_device() if stream is None else stream.device_index):
+        return None, 0
+    try:
+        with torch.cuda.stream(stream):                                       # (None: as it is)
+            if torch.cuda.is_current_stream_capturing():
+                return None, 0
+            return torch.empty(nbytes, dtype=torch.uint8, device=device), nbytes
+    except torch.OutOfMemoryError:
+        return None, 0
+
+
+def _kv_rows_workspace(workspace, lib, b, n, d, h_kv, k, v, dt, device, stream):
+    if workspace is not None:
+        return workspace, workspace.numel() * workspace.element_size()
+    return _call_workspace(lib.mqa_project_kv_workspace_bytes(b, n, d, h_kv, k, v, dt), device, stream)
 
 
 # products of new K / V rows below which the library asks for no workspace (small calls are spared the question)
@@ -406,7 +422,8 @@ def mqa_project_append_qkv(x, P_q, P_k, P_v, K, V, lens_in, lens_out, q=None, st
 
 
 def mqa_project_plan(mode, rows, d, h, kv) -> int:
-    """The edge of the split-operand kernel's tiles that mqa_project_qkvo uses for this product, or 0 (see mqa.h)."""
+    """The edge of the split-operand kernel's tiles that mqa_project_qkvo uses for this product, 1 for the three-term kernel, or 0
+    (see mqa.h)."""
     return load_library().mqa_project_plan(int(mode), rows, d, h, kv)
 
 
@@ -415,9 +432,15 @@ def mqa_project_kv_plan(rows, d, h, h_kv, k, v, dt) -> int:
     return load_library().mqa_project_kv_plan(rows, d, h, h_kv, k, v, int(dt))
 
 
-def mqa_project_append_kv_rows(x, P_k, P_v, K, V, lens_in, lens_out, stream=None):
+def mqa_project_kv_workspace_bytes(b, n, d, h_kv, k, v, dt) -> int:
+    """Scratch bytes that the K / V rows of b sequences of n positions use (0: none)."""
+    return int(load_library().mqa_project_kv_workspace_bytes(b, n, d, h_kv, k, v, int(dt)))
+
+
+def mqa_project_append_kv_rows(x, P_k, P_v, K, V, lens_in, lens_out, stream=None, workspace=None):
     """x [b,n,d], P_k [d,k] or [h,d,k], P_v likewise, caches K/V ([b,cap,k] or [b,h,cap,k]), lens_in/lens_out [b] int32
-    (different tensors): projects the new rows of n positions per sequence and appends them, in one launch."""
+    (different tensors): projects the new rows of n positions per sequence and appends them.  Many rows are two launches with
+    scratch memory between them, allocated here unless given (a captured call is one launch, and slower, without)."""
     lib = load_library()
     f32, i32 = torch.float32, torch.int32
     _check(x, "x", f32), _check(P_k, "P_k", f32), _check(P_v, "P_v", f32), _check(K, "K"), _check(V, "V")
@@ -432,18 +455,19 @@ def mqa_project_append_kv_rows(x, P_k, P_v, K, V, lens_in, lens_out, stream=None
             or K.dtype != V.dtype or lens_in.numel() != b or lens_out.numel() != b):
         raise ValueError("shape mismatch in mqa_project_append_kv_rows")
     dt, args = _cache_dtype(K), (_ptr(x), _ptr(P_k), _ptr(P_v), _ptr(K), _ptr(V), _ptr(lens_in), _ptr(lens_out), b, n, d, h_kv, cap, k, v)
-    if b * n * d * h_kv * (k + v) < _KV_ROWS_SMALL:
+    if workspace is None and b * n * d * h_kv * (k + v) < _KV_ROWS_SMALL:
         rc = lib.mqa_project_append_kv_rows(*args, dt, _stream(stream))
     else:
-        ws, nbytes = _call_workspace(lib.mqa_project_kv_workspace_bytes(b, n, d, h_kv, k, v, dt), x.device, stream)
+        ws, nbytes = _kv_rows_workspace(workspace, lib, b, n, d, h_kv, k, v, dt, x.device, stream)
         rc = lib.mqa_project_append_kv_rows_ws(*args, dt, _ptr(ws), nbytes, _stream(stream))
     if rc != 0:
         raise MqaError("mqa_project_append_kv_rows", rc)
 
 
-def mqa_project_memory_kv(M, P_k, P_v, K, V, lens, mem_lens=None, stream=None):
+def mqa_project_memory_kv(M, P_k, P_v, K, V, lens, mem_lens=None, stream=None, workspace=None):
     """M [b,m,d], P_k [d,k] or [h,d,k], P_v likewise, caches K/V ([b,cap,k] or [b,h,cap,k]), lens [b] int32
-    (output), mem_lens [b] int32 or None: projects the whole memory into the caches in one launch."""
+    (output), mem_lens [b] int32 or None: projects the whole memory into the caches (launches and workspace: as
+    mqa_project_append_kv_rows)."""
     lib = load_library()
     for name, t in (("M", M), ("P_k", P_k), ("P_v", P_v)):
         _check(t, name, torch.float32)
@@ -460,10 +484,10 @@ def mqa_project_memory_kv(M, P_k, P_v, K, V, lens, mem_lens=None, stream=None):
             or K.dtype != V.dtype or lens.numel() != b or (mem_lens is not None and mem_lens.numel() != b)):
         raise ValueError("shape mismatch in mqa_project_memory_kv")
     dt, args = _cache_dtype(K), (_ptr(M), _ptr(P_k), _ptr(P_v), _ptr(K), _ptr(V), _ptr(mem_lens), _ptr(lens), b, m, d, h_kv, cap, k, v)
-    if b * m * d * h_kv * (k + v) < _KV_ROWS_SMALL:
+    if workspace is None and b * m * d * h_kv * (k + v) < _KV_ROWS_SMALL:
         rc = lib.mqa_project_memory_kv(*args, dt, _stream(stream))
     else:
-        ws, nbytes = _call_workspace(lib.mqa_project_kv_workspace_bytes(b, m, d, h_kv, k, v, dt), M.device, stream)
+        ws, nbytes = _kv_rows_workspace(workspace, lib, b, m, d, h_kv, k, v, dt, M.device, stream)
         rc = lib.mqa_project_memory_kv_ws(*args, dt, _ptr(ws), nbytes, _stream(stream))
     if rc != 0:
         raise MqaError("mqa_project_memory_kv", rc)
@@ -596,7 +620,8 @@ def mqa_project_add_layernorm_workspace_bytes(mode, rows, d, h, kv) -> int:
 
 
 def mqa_project_add_layernorm(mode, x, P, acc, out=None, eps=1e-6, workspace=None, stream=None):
-    """acc += x . P (mode O: x [rows,h,kv], P [h,d,kv]; LINEAR: x [rows,d], P [d,kv]), then out = layernorm(acc).  Returns out."""
+    """acc += x . P (mode O: x [rows,h,kv], P [h,d,kv]; LINEAR: x [rows,d], P [d,kv]), then out = layernorm(acc).  Returns out.  The
+    workspace is allocated here unless given (a captured call is the two it stands for without)."""
     lib = load_library()
     _check(x, "in", torch.float32), _check(P, "P", torch.float32), _check(acc, "acc", torch.float32)
     rows = x.shape[0]

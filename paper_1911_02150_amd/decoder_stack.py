@@ -78,14 +78,19 @@ class DecoderStack:
     def _logits(self, hx: torch.Tensor) -> torch.Tensor:
         return B.mqa_project_qkvo(B.MQA_PROJ_O, hx.view(self.b, 1, self.d), self.E.view(1, -1, self.d))
 
+    def _workspace(self, rows: int, kv_rows: int = 0) -> torch.Tensor:
+        """Scratch memory for the calls of one pass over `rows` rows, one after another on its stream (a pass's own: calls on several
+        streams do not share it)."""
+        parts = [B.mqa_project_add_layernorm_workspace_bytes(B.MQA_PROJ_O, rows, self.d, self.h, self.v), kv_rows, 16]
+        parts += [B.mqa_project_add_layernorm_workspace_bytes(B.MQA_PROJ_LINEAR, rows, ff, 1, self.d) for ff in {w["W1"].shape[1] for w in self.layers}]
+        return torch.empty(max(parts), dtype=torch.uint8, device=self.dev)
+
     # -- one decoding step for the whole stack: per layer 7 launches (fused q/K/V + append, attention (+ merge), output
     #    projection in parts, their sum added into x with the layernorm, W1 with relu, W2 in parts, the same)
     def step(self, tokens: torch.Tensor, t: int) -> torch.Tensor:
         x = self.embed(tokens, t)
         dec = B.mha_decode_step if self.multi_head else B.mqa_decode_step
-        parts = max(B.mqa_project_add_layernorm_workspace_bytes(B.MQA_PROJ_O, self.b, self.d, self.h, self.v),
-                    B.mqa_project_add_layernorm_workspace_bytes(B.MQA_PROJ_LINEAR, self.b, self.layers[0]["W1"].shape[1], 1, self.d))
-        ws = torch.empty(max(16, parts), dtype=torch.uint8, device=self.dev)      # (of this step: calls on several streams do not share it)
+        ws = self._workspace(self.b)
         hx = B.mqa_stack_layernorm(x)
         for l, w in enumerate(self.layers):
             q = self._append_fused(l, hx)
@@ -103,22 +108,24 @@ class DecoderStack:
         b, n = prompts.shape
         positions = torch.arange(n, dtype=torch.int32, device=self.dev).repeat(b)
         x = B.mqa_stack_embed(prompts.reshape(-1).to(torch.int32).contiguous(), positions, self.E, self.pos)   # [b*n,d]
+        ws = self._workspace(b * n, B.mqa_project_kv_workspace_bytes(b, n, self.d, 1, self.k, self.v, B._cache_dtype(self.K[0])))
         hx = B.mqa_stack_layernorm(x)
         for l, w in enumerate(self.layers):
             q = B.mqa_project_qkvo(B.MQA_PROJ_Q, hx, w["P_q"]).view(b, n, self.h, self.k)
             if self.k % 16 == 0 and self.v % 16 == 0:
                 now = self._lens_next[l]
-                B.mqa_project_append_kv_rows(hx.view(b, n, self.d), w["P_k"], w["P_v"], self.K[l], self.V[l], self.lens[l], now)
+                B.mqa_project_append_kv_rows(hx.view(b, n, self.d), w["P_k"], w["P_v"], self.K[l], self.V[l], self.lens[l], now,
+                                             workspace=ws)
             else:
                 now = self.lens[l]
                 kn = B.mqa_project_qkvo(B.MQA_PROJ_KV, hx, w["P_k"]).view(b, n, self.k)
                 vn = B.mqa_project_qkvo(B.MQA_PROJ_KV, hx, w["P_v"]).view(b, n, self.v)
                 B.mqa_append_kv_rows(self.K[l], self.V[l], kn, vn, self.lens[l])
             o = B.mqa_prefill_attention(q, self.K[l], self.V[l], now)
-            hx = B.mqa_project_add_layernorm(B.MQA_PROJ_O, o.view(b * n, self.h, self.v), w["P_o"], x)
+            hx = B.mqa_project_add_layernorm(B.MQA_PROJ_O, o.view(b * n, self.h, self.v), w["P_o"], x, workspace=ws)
             u = B.mqa_project_qkvo_ex(B.MQA_PROJ_LINEAR, hx, w["W1"], epilogue=B.MQA_EPI_RELU)
             if l + 1 < len(self.layers):
-                hx = B.mqa_project_add_layernorm(B.MQA_PROJ_LINEAR, u, w["W2"], x)
+                hx = B.mqa_project_add_layernorm(B.MQA_PROJ_LINEAR, u, w["W2"], x, workspace=ws)
             else:                             # (the last positions are all that is normalised)
                 B.mqa_project_qkvo_ex(B.MQA_PROJ_LINEAR, u, w["W2"], out=x, epilogue=B.MQA_EPI_ADD)
         if now is not self.lens[-1]:      # the lengths advance in the arrays they are in: a caller may hold them

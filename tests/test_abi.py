@@ -152,6 +152,44 @@ def test_workspace_of_sizes_past_the_integers():
     assert query(m.MQA_PROJ_O, 128, 1024, 8, 128) > 0
 
 
+@pytest.mark.parametrize("why", ["room", "no room", "captured", "other device", "foreign stream", "foreign default stream"])
+def test_where_a_call_gets_its_workspace(monkeypatch, why):
+    """A block of torch's allocator, with the call's stream current; none (never an error) where the allocator cannot own it."""
+    import contextlib
+    import types
+
+    import torch
+
+    from paper_1911_02150_amd import binding
+    device, current, block = torch.device("cuda", 0), [], object()
+
+    @contextlib.contextmanager
+    def on(stream):
+        assert stream is None or stream.device_index == 0        # (what torch's own asks of it)
+        current.append(stream)
+        yield
+        current.pop()
+
+    def empty(n, dtype, device):
+        assert (n, dtype, device.index) == (4096, torch.uint8, 0) and [s.cuda_stream for s in current if s] == [h for h in [handle] if h is not None]
+        if why == "no room":
+            raise torch.OutOfMemoryError("no memory")
+        return block
+
+    handle = {"foreign stream": 77, "foreign default stream": 0}.get(why)
+    stream = None if handle is None else types.SimpleNamespace(cuda_stream=handle)
+    a_stream = lambda handle, device: types.SimpleNamespace(cuda_stream=handle, device_index=device.index)  # noqa: E731
+    monkeypatch.setattr(torch.cuda, "stream", on)
+    monkeypatch.setattr(torch.cuda, "ExternalStream", a_stream)
+    monkeypatch.setattr(torch.cuda, "default_stream", lambda device: a_stream(0, device))
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 1 if why == "other device" else 0)
+    monkeypatch.setattr(torch.cuda, "is_current_stream_capturing", lambda: why == "captured")
+    monkeypatch.setattr(torch, "empty", empty)
+    assert binding._call_workspace(0, device, stream) == (None, 0)
+    expected = (block, 4096) if why in ("room", "foreign stream", "foreign default stream") else (None, 0)
+    assert binding._call_workspace(4096, device, stream) == expected
+
+
 def test_beam_entry_points_validate_without_gpu():
     import paper_1911_02150_amd as m
     lib = ctypes.CDLL(LIB)

@@ -250,6 +250,63 @@ def test_rows_with_and_without_a_workspace(m, b, n, d, heads, k, v, share):
     assert (K[..., n:, :] == 7).all() and (V[..., n:, :] == 7).all() and torch.equal(lens, valid.clamp(max=n))
 
 
+@pytest.mark.parametrize("own_workspace", [True, False])
+@pytest.mark.parametrize("append", [True, False])
+def test_captured_rows(m, append, own_workspace):
+    """The call under capture, with the program's workspace (two launches) and without (one): every replay gives the eager rows of the
+    inputs it finds, with other work on the same memory between the replays."""
+    b, n, d = 64, 300, 520
+    x, P_k, P_v = inputs(b, n, d, 0, 128, 128, 21)
+    nbytes = m.mqa_project_kv_workspace_bytes(b, n, d, 1, 128, 128, m.MQA_BF16)
+    assert nbytes > 0
+    K, V = caches(b, 0, n, 128, 128)
+    lens, after = torch.zeros(b, dtype=torch.int32, device=DEV), torch.empty(b, dtype=torch.int32, device=DEV)
+    ws = torch.empty(nbytes, dtype=torch.uint8, device=DEV) if own_workspace else None
+
+    def call():
+        if append:
+            m.mqa_project_append_kv_rows(x, P_k, P_v, K, V, lens, after, workspace=ws)
+        else:
+            m.mqa_project_memory_kv(x, P_k, P_v, K, V, after, workspace=ws)
+
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        call()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        call()
+    for k in range(3):
+        x.copy_(torch.randn(b, n, d, device=DEV))
+        P_k.mul_(-1.5)
+        K.fill_(7), V.fill_(7), after.fill_(-1)
+        others = [torch.full((nbytes,), k, dtype=torch.uint8, device=DEV) for _ in range(3)]
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(K, expected(x, P_k, 0)) and torch.equal(V, expected(x, P_v, 0)) and (after == n).all()
+        assert all((o == k).all() for o in others)
+
+
+def test_rows_on_any_stream(m):
+    """A stream given as an object with a `cuda_stream`, as torch's, and as the default one."""
+    import types
+    b, n, d = 64, 300, 520
+    side = torch.cuda.Stream()
+    for stream in (side, types.SimpleNamespace(cuda_stream=side.cuda_stream), types.SimpleNamespace(cuda_stream=0), torch.cuda.ExternalStream(side.cuda_stream)):
+        x, P_k, P_v = inputs(b, n, d, 0, 128, 128, 22)
+        K, V = caches(b, 0, n, 128, 128)
+        lens, after = torch.zeros(b, dtype=torch.int32, device=DEV), torch.empty(b, dtype=torch.int32, device=DEV)
+        torch.cuda.synchronize()
+        m.mqa_project_append_kv_rows(x, P_k, P_v, K, V, lens, after, stream=stream)
+        torch.cuda.synchronize()
+        assert torch.equal(K, expected(x, P_k, 0)) and torch.equal(V, expected(x, P_v, 0)) and (after == n).all()
+        K.fill_(7), V.fill_(7)
+        torch.cuda.synchronize()
+        m.mqa_project_memory_kv(x, P_k, P_v, K, V, after, stream=stream)
+        torch.cuda.synchronize()
+        assert torch.equal(K, expected(x, P_k, 0)) and torch.equal(V, expected(x, P_v, 0)) and (after == n).all()
+
+
 def test_refused_sizes_keep_their_error(m):
     """A size that the library refuses (a head of 20 columns) raises the library's error with its status, from both calls."""
     x = torch.zeros(2, 3, 64, device=DEV)
