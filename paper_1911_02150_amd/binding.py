@@ -202,12 +202,22 @@ def _default_workspace(device, nbytes, stream=None):
     return ws
 
 
+def _kept_for_the_graph(device):
+    """While the current stream is captured: is it torch that captures it, so that what is allocated now stays the graph's?  (Its
+    blocks are then in a pool other than the allocator's common one.)"""
+    at = torch.empty(1, dtype=torch.uint8, device=device).data_ptr()
+    for segment in torch.cuda.memory_snapshot():
+        if segment["address"] <= at < segment["address"] + segment["total_size"]:
+            return tuple(segment.get("segment_pool_id", (0, 0))) != (0, 0)
+    return False
+
+
 def _call_workspace(nbytes, device, stream):
     """Scratch memory for one call of several launches, and its size: a block of torch's caching allocator, allocated
     with the call's stream current, so that it goes to later work of that stream only (calls of other threads
     on the same stream get blocks of their own).  (None, 0), which every such call takes as well, where there is no such
-    block: while the stream is captured (a graph that torch does not capture itself would keep writing to a block that the
-    allocator has given to others), for tensors of another device than the one whose stream is taken, and without memory."""
+    block: while the stream is captured by others than torch (the graph would keep writing to a block that the
+    allocator has given away), for tensors of another device than the one whose stream is taken, and without memory."""
     if nbytes == 0:
         return None, 0
     if stream is not None and not isinstance(stream, torch.cuda.Stream):      # (any object with a cuda_stream will do)
@@ -217,7 +227,7 @@ def _call_workspace(nbytes, device, stream):
         return None, 0
     try:
         with torch.cuda.stream(stream):                                       # (None: as it is)
-            if torch.cuda.is_current_stream_capturing():
+            if torch.cuda.is_current_stream_capturing() and not _kept_for_the_graph(device):
                 return None, 0
             return torch.empty(nbytes, dtype=torch.uint8, device=device), nbytes
     except torch.OutOfMemoryError:
@@ -440,7 +450,8 @@ def mqa_project_kv_workspace_bytes(b, n, d, h_kv, k, v, dt) -> int:
 def mqa_project_append_kv_rows(x, P_k, P_v, K, V, lens_in, lens_out, stream=None, workspace=None):
     """x [b,n,d], P_k [d,k] or [h,d,k], P_v likewise, caches K/V ([b,cap,k] or [b,h,cap,k]), lens_in/lens_out [b] int32
     (different tensors): projects the new rows of n positions per sequence and appends them.  Many rows are two launches with
-    scratch memory between them, allocated here unless given (a captured call is one launch, and slower, without)."""
+    scratch memory between them, allocated here unless given (one launch, and slower, without: in a graph that torch does not
+    capture, or without memory)."""
     lib = load_library()
     f32, i32 = torch.float32, torch.int32
     _check(x, "x", f32), _check(P_k, "P_k", f32), _check(P_v, "P_v", f32), _check(K, "K"), _check(V, "V")
@@ -620,8 +631,8 @@ def mqa_project_add_layernorm_workspace_bytes(mode, rows, d, h, kv) -> int:
 
 
 def mqa_project_add_layernorm(mode, x, P, acc, out=None, eps=1e-6, workspace=None, stream=None):
-    """acc += x . P (mode O: x [rows,h,kv], P [h,d,kv]; LINEAR: x [rows,d], P [d,kv]), then out = layernorm(acc).  Returns out.  The
-    workspace is allocated here unless given (a captured call is the two it stands for without)."""
+    """acc += x . P (mode O: x [rows,h,kv], P [h,d,kv]; LINEAR: x [rows,d], P [d,kv]), then out = layernorm(acc).  Returns out.
+    Workspace: as mqa_project_append_kv_rows."""
     lib = load_library()
     _check(x, "in", torch.float32), _check(P, "P", torch.float32), _check(acc, "acc", torch.float32)
     rows = x.shape[0]

@@ -253,8 +253,8 @@ def test_rows_with_and_without_a_workspace(m, b, n, d, heads, k, v, share):
 @pytest.mark.parametrize("own_workspace", [True, False])
 @pytest.mark.parametrize("append", [True, False])
 def test_captured_rows(m, append, own_workspace):
-    """The call under capture, with the program's workspace (two launches) and without (one): every replay gives the eager rows of the
-    inputs it finds, with other work on the same memory between the replays."""
+    """The call in a graph that torch captures, with the program's workspace and without: every replay gives the eager rows of the inputs
+    it finds, with other work on the same sizes of memory between the replays."""
     b, n, d = 64, 300, 520
     x, P_k, P_v = inputs(b, n, d, 0, 128, 128, 21)
     nbytes = m.mqa_project_kv_workspace_bytes(b, n, d, 1, 128, 128, m.MQA_BF16)
@@ -285,6 +285,45 @@ def test_captured_rows(m, append, own_workspace):
         torch.cuda.synchronize()
         assert torch.equal(K, expected(x, P_k, 0)) and torch.equal(V, expected(x, P_v, 0)) and (after == n).all()
         assert all((o == k).all() for o in others)
+
+
+def test_rows_in_a_graph_of_the_program(m):
+    """A capture that torch knows nothing of: no block of its allocator is the graph's, so the call takes none."""
+    import ctypes
+    from paper_1911_02150_amd import binding
+    hip = binding.load_library()               # (the runtime's functions are found through the library that uses it)
+    vp = ctypes.c_void_p
+    b, n, d = 64, 300, 520
+    x, P_k, P_v = inputs(b, n, d, 0, 128, 128, 23)
+    K, V = caches(b, 0, n, 128, 128)
+    after = torch.empty(b, dtype=torch.int32, device=DEV)
+    nbytes = m.mqa_project_kv_workspace_bytes(b, n, d, 1, 128, 128, m.MQA_BF16)
+    side = torch.cuda.Stream()
+    ws = torch.empty(nbytes, dtype=torch.uint8, device=DEV)
+    for w in (ws, torch.empty(16, dtype=torch.uint8, device=DEV)):      # (both routes, before anything is captured)
+        m.mqa_project_memory_kv(x, P_k, P_v, K, V, after, workspace=w)
+    with torch.cuda.stream(side):
+        spare = torch.empty(nbytes, dtype=torch.uint8, device=DEV)
+    del spare                                  # a block that an allocation on that stream would get
+    torch.cuda.synchronize()
+    graph, run = vp(), vp()
+    assert hip.hipStreamBeginCapture(vp(side.cuda_stream), 2) == 0       # (relaxed)
+    m.mqa_project_memory_kv(x, P_k, P_v, K, V, after, stream=side)
+    assert hip.hipStreamEndCapture(vp(side.cuda_stream), ctypes.byref(graph)) == 0
+    count = ctypes.c_size_t()
+    assert hip.hipGraphGetNodes(graph, None, ctypes.byref(count)) == 0 and count.value == 1
+    assert hip.hipGraphInstantiate(ctypes.byref(run), graph, None, None, ctypes.c_size_t(0)) == 0
+    with torch.cuda.stream(side):
+        others = [torch.full((nbytes,), 5, dtype=torch.uint8, device=DEV) for _ in range(2)]
+    for _ in range(3):
+        x.copy_(torch.randn(b, n, d, device=DEV))
+        K.fill_(7), V.fill_(7), after.fill_(-1)
+        torch.cuda.synchronize()
+        assert hip.hipGraphLaunch(run, vp(side.cuda_stream)) == 0
+        torch.cuda.synchronize()
+        assert torch.equal(K, expected(x, P_k, 0)) and torch.equal(V, expected(x, P_v, 0)) and (after == n).all()
+        assert all((o == 5).all() for o in others)
+    assert hip.hipGraphExecDestroy(run) == 0 and hip.hipGraphDestroy(graph) == 0
 
 
 def test_rows_on_any_stream(m):
