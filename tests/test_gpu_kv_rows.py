@@ -1,5 +1,5 @@
-"""New K / V rows of many positions (csrc/project_kv.hip and the float64 kernel it stands in for): the cache holds the
-correctly rounded product, bit for bit, whatever the values."""
+"""New K / V rows of many positions (csrc/project_kv_rows.hip with a workspace, csrc/project_kv.hip without, and the float64 kernel
+they stand in for): the cache holds the correctly rounded product, bit for bit, whatever the values."""
 import pytest
 import torch
 
@@ -46,6 +46,16 @@ def caches(b, heads, cap, k, v, dtype=torch.bfloat16):
     return torch.full((b, *one, cap, k), 7.0, dtype=dtype, device=DEV), torch.full((b, *one, cap, v), 7.0, dtype=dtype, device=DEV)
 
 
+ROUTES = ["with", "without"]                   # a workspace: kv_rows_kernel and project_kv_exact_kernel where integers pay
+
+
+def scratch(m, route, b, n, d, heads, k, v, dtype=torch.bfloat16, integers=True):
+    """The workspace to hand over: the one the sizes ask for, or one that is too small for any."""
+    nbytes = m.mqa_project_kv_workspace_bytes(b, n, d, heads or 1, k, v, m.MQA_BF16 if dtype == torch.bfloat16 else m.MQA_F32)
+    assert (nbytes > 0) == (integers and dtype == torch.bfloat16)
+    return torch.full((nbytes if route == "with" and nbytes else 16,), 255, dtype=torch.uint8, device=DEV)
+
+
 # rows and columns past whole tiles of 128, contraction tails of 8 and of 24 in a stage of 32, heads inside a column tile;
 # the last two are too small for the integer kernel
 SHAPES = [(64, 300, 1000, 0, 128, 128), (46, 811, 72, 0, 128, 64), (40, 500, 88, 5, 48, 80), (70, 257, 520, 2, 256, 16),
@@ -55,22 +65,26 @@ SHAPES = [(64, 300, 1000, 0, 128, 128), (46, 811, 72, 0, 128, 64), (40, 500, 88,
 def test_shapes_take_the_kernel_they_are_for(m):
     taken = [m.mqa_project_kv_plan(b * n, d, 0, heads or 1, k, v, m.MQA_BF16) for b, n, d, heads, k, v in SHAPES]
     assert taken == [1, 1, 1, 1, 0, 0]
+    asked = [m.mqa_project_kv_workspace_bytes(b, n, d, heads or 1, k, v, m.MQA_BF16) > 0 for b, n, d, heads, k, v in SHAPES]
+    assert asked == [True] * 4 + [False] * 2
     assert m.mqa_project_kv_plan(64 * 300, 1000, 0, 1, 128, 128, m.MQA_F32) == 0
 
 
+@pytest.mark.parametrize("route", ROUTES)
 @pytest.mark.parametrize("b,n,d,heads,k,v", SHAPES)
-def test_memory_rows(m, b, n, d, heads, k, v):
+def test_memory_rows(m, b, n, d, heads, k, v, route):
     x, P_k, P_v = inputs(b, n, d, heads, k, v, n)
     K, V = caches(b, heads, n + 3, k, v)
     lens = torch.zeros(b, dtype=torch.int32, device=DEV)
-    m.mqa_project_memory_kv(x, P_k, P_v, K, V, lens)
+    m.mqa_project_memory_kv(x, P_k, P_v, K, V, lens, workspace=scratch(m, route, b, n, d, heads, k, v, integers=b > 3))
     assert torch.equal(K[..., :n, :], expected(x, P_k, heads)) and torch.equal(V[..., :n, :], expected(x, P_v, heads))
     assert (K[..., n:, :] == 7).all() and (V[..., n:, :] == 7).all() and (lens == n).all()
 
 
+@pytest.mark.parametrize("route", ROUTES)
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
 @pytest.mark.parametrize("b,n,d,heads,k,v", SHAPES)
-def test_append_rows(m, b, n, d, heads, k, v, dtype):
+def test_append_rows(m, b, n, d, heads, k, v, dtype, route):
     """Behind what is there; a sequence without room (or with a negative length) stays as it is."""
     x, P_k, P_v = inputs(b, n, d, heads, k, v, n + 1)
     cap = n + 10
@@ -79,7 +93,7 @@ def test_append_rows(m, b, n, d, heads, k, v, dtype):
     lens[b - 1] = 11
     lens[0] = -2
     after = torch.zeros_like(lens)
-    m.mqa_project_append_kv_rows(x, P_k, P_v, K, V, lens, after)
+    m.mqa_project_append_kv_rows(x, P_k, P_v, K, V, lens, after, workspace=scratch(m, route, b, n, d, heads, k, v, dtype, b > 3))
     wk, wv = caches(b, heads, cap, k, v, dtype)
     for i, L in enumerate(lens.tolist()):
         if 0 <= L <= 10:
@@ -95,9 +109,10 @@ def test_append_rows(m, b, n, d, heads, k, v, dtype):
     assert after.tolist() == [L + n if 0 <= L <= 10 else L for L in lens.tolist()]
 
 
-@pytest.mark.parametrize("ratio", [2.0 ** 6, 2.0 ** 12, 2.0 ** 40])
+@pytest.mark.parametrize("route", ROUTES)
+@pytest.mark.parametrize("ratio", [2.0 ** 6, 2.0 ** 8, 2.0 ** 9, 2.0 ** 12, 2.0 ** 40])
 @pytest.mark.parametrize("b,n,d,heads,k,v", [s for s in SHAPES if s[0] > 3])
-def test_one_large_channel(m, b, n, d, heads, k, v, ratio):
+def test_one_large_channel(m, b, n, d, heads, k, v, ratio, route):
     """One channel far above the others, its weights as far below: the bounds leave from a few elements of a tile to all of
     it open."""
     x, P_k, P_v = inputs(b, n, d, heads, k, v, n + 2)
@@ -107,12 +122,14 @@ def test_one_large_channel(m, b, n, d, heads, k, v, ratio):
     P_v[..., d // 3, :] /= ratio
     K, V = caches(b, heads, n + 3, k, v)
     lens = torch.zeros(b, dtype=torch.int32, device=DEV)
-    m.mqa_project_memory_kv(x, P_k, P_v, K, V, lens)
+    m.mqa_project_memory_kv(x, P_k, P_v, K, V, lens, workspace=scratch(m, route, b, n, d, heads, k, v))
     assert torch.equal(K[..., :n, :], expected(x, P_k, heads)) and torch.equal(V[..., :n, :], expected(x, P_v, heads))
     assert (K[..., n:, :] == 7).all() and (V[..., n:, :] == 7).all()
 
 
-def test_rows_of_any_values(m):
+@pytest.mark.parametrize("append", [False, True])
+@pytest.mark.parametrize("route", ROUTES)
+def test_rows_of_any_values(m, route, append):
     """Zeros, ties, wide ranges inside a row and a column, sums that cancel, subnormals, infinities and NaN."""
     b, n, d = 64, 300, 200
     assert m.mqa_project_kv_plan(b * n, d, 0, 1, 128, 128, m.MQA_BF16) == 1
@@ -132,7 +149,11 @@ def test_rows_of_any_values(m):
     P_k[:, 10] *= 1e-35
     K, V = caches(b, 0, n, 128, 128)
     lens = torch.zeros(b, dtype=torch.int32, device=DEV)
-    m.mqa_project_memory_kv(x, P_k, P_v, K, V, lens)
+    ws = scratch(m, route, b, n, d, 0, 128, 128)
+    if append:
+        m.mqa_project_append_kv_rows(x, P_k, P_v, K, V, torch.zeros_like(lens), lens, workspace=ws)
+    else:
+        m.mqa_project_memory_kv(x, P_k, P_v, K, V, lens, workspace=ws)
     want = expected(x, P_k, 0)
     # sums that cancel to nothing are what the order of the 64-bit sum leaves: 200 roundings of sums below 100
     assert float(K[3, :, 16:64].abs().max()) < 200 * 100 * 2.0 ** -53
@@ -165,20 +186,21 @@ def test_lines_with_a_nan(m, with_workspace):
         assert same(got, want) and (got.view(torch.int16)[torch.isnan(want)] == 0x7fc0).all()
 
 
+@pytest.mark.parametrize("route,d", [("without", 8), ("without", 64), ("with", 64)])       # (zeros behind the first eight)
 @pytest.mark.parametrize("sign", [1, -1])
-def test_sums_around_a_power_of_two(m, sign):
+def test_sums_around_a_power_of_two(m, sign, route, d):
     """Sums that end just above and just below 2^42, whose error bound (what the fixed point drops of the values beside one
     of 1.25 . 2^30) reaches the nearest tie: below the power of two the ties lie half as far apart."""
-    b, n, d, big = 64, 512, 8, 1.25 * 2.0 ** 30
+    b, n, big = 64, 512, 1.25 * 2.0 ** 30
     assert m.mqa_project_kv_plan(b * n, d, 0, 1, 128, 128, m.MQA_BF16) == 1
-    x = torch.tensor([big] * 4 + [-0.99] * 3 + [0.0], device=DEV).repeat(b, n, 1)
+    x = torch.tensor([big] * 4 + [-0.99] * 3 + [0.0] * (d - 7), device=DEV).repeat(b, n, 1)
     x[..., 7] = torch.linspace(3262, 3302, b * n, device=DEV).view(b, n)
     x[::2, :, 7] = x[::2, :, 7].floor()
-    w = sign * torch.tensor([-0.99] * 4 + [big] * 4, device=DEV)
+    w = sign * torch.tensor([-0.99] * 4 + [big] * 4 + [0.0] * (d - 8), device=DEV)
     P = w[:, None] * 2.0 ** torch.arange(-64, 64, device=DEV)
     K, V = caches(b, 0, n, 128, 128)
     lens = torch.zeros(b, dtype=torch.int32, device=DEV)
-    m.mqa_project_memory_kv(x, P, P * 2, K, V, lens)
+    m.mqa_project_memory_kv(x, P, P * 2, K, V, lens, workspace=scratch(m, route, b, n, d, 0, 128, 128, integers=d >= 64))
     want = expected(x, P, 0)
     assert (want[..., 64].abs() < 2.0 ** 42).any() and (want[..., 64].abs() > 2.0 ** 42).any()
     assert torch.equal(K, want) and torch.equal(V, expected(x, P * 2, 0))
@@ -187,16 +209,17 @@ def test_sums_around_a_power_of_two(m, sign):
 FULL = [2 ** 31 - 1, 2 ** 31 - 2, 2 ** 31 - 5, 2 ** 30, -1, -2 ** 31]      # lengths no cache has room behind
 
 
+@pytest.mark.parametrize("route", ROUTES)
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
 @pytest.mark.parametrize("b,n,d,heads,k,v", [(64, 300, 1000, 0, 128, 128), (6, 9, 72, 3, 16, 32)])
-def test_append_to_any_length(m, b, n, d, heads, k, v, dtype):
+def test_append_to_any_length(m, b, n, d, heads, k, v, dtype, route):
     """Lengths up to the largest integer: the cache and the length stay as they are."""
     x, P_k, P_v = inputs(b, n, d, heads, k, v, 3)
     lens = torch.zeros(b, dtype=torch.int32, device=DEV)
     lens[:6] = torch.tensor(FULL, dtype=torch.int32, device=DEV)
     K, V = caches(b, heads, n, k, v, dtype)
     after = torch.zeros_like(lens)
-    m.mqa_project_append_kv_rows(x, P_k, P_v, K, V, lens, after)
+    m.mqa_project_append_kv_rows(x, P_k, P_v, K, V, lens, after, workspace=scratch(m, route, b, n, d, heads, k, v, dtype, b > 6))
     assert after.tolist() == FULL + [n] * (b - 6) and (K[:6] == 7).all() and (V[:6] == 7).all()
     K2, V2 = caches(b, heads, n, k, v, dtype)
     one = (b, n, heads) if heads else (b, n)
