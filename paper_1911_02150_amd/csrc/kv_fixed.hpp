@@ -56,7 +56,7 @@ __device__ __forceinline__ Line line_of(const int* squares, uint32_t most, int C
   l.w = (sqrtf((float)C) * sqrtf((float)squares[3]) + 1.26f * (float)C + 1.f) * 1.002f;
   l.r = sqrtf((float)squares[0] + (float)squares[1] + (float)squares[2]) * (0.0625f * 1.002f);
   l.exponent = 12 - fixed_exponent(most);
-  if (most >= 0x7f800000u) l.w = most == 0x7f800000u ? INFINITY : NAN;
+  if (most >= 0x7f800000u) l.w = __uint_as_float(most);
   if (most == 0) l.w = -INFINITY;
   return l;
 }
@@ -86,8 +86,7 @@ __device__ __forceinline__ uint32_t rounded_sum(float mid, Line row, Line col, b
 }
 
 // Of an open element: is it NaN (a NaN in a line, or an infinity against a line of zeros)?  It needs no summing then: one row of NaN in
-// every 64 of a memory of 64 x 512, d = 1024: 405 -> 116 us with a workspace, 465 -> 175 without.  (Asked for every element in
-// rounded_sum it cost 0.8 us of the 140 of such a memory without a NaN.)
+// every 64 of a memory of 64 x 512, d = 1024: 405 -> 123 us with a workspace, 465 -> 174 without.
 constexpr uint32_t kNan = 0x7fc0u;
 __device__ __forceinline__ bool is_nan(Line row, Line col) {
   const float w = row.w + col.w;

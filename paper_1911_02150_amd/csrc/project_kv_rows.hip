@@ -25,10 +25,10 @@ using namespace kv_fixed;
 constexpr int kRows = 64, kColumns = 128;      // of a tile
 constexpr int kGroups = 512;                   // two workgroups per compute unit
 
-// Open elements of a tile (of 8192) from which its waves sum all of it in float64.  One element costs half a wave about 5 us of latency
-// (more from 1024 indices on), all of them 0.26 us for each index.  us, with one channel of the rows 2^7 / 2^8 / 2^9 / 2^10 times the others and its
-// weights as much smaller, one by one against all: 32768 rows, d = 1024: 209 / 265 / 360 / 525 against 406; 19200 rows, d = 200:
-// 74 / 100 / 144 / 231 against 82; one row with an infinity (128 open) in every 1024: 221 against 401 and 137 against 82.
+// Open elements of a tile (of 8192, those that need no summing aside) from which its waves sum all of it in float64.  One element costs
+// half a wave some 4 us of latency (more from 1024 indices on), all of them 0.26 us for each index.  us, with one channel of the rows 2^6 / 2^7 /
+// 2^8 / 2^9 times the others and its weights as much smaller, by this limit against all in float64: 32768 rows, d = 1024: 160 / 180 / 216 / 400
+// against 406; 19200 rows, d = 200: 52 / 65 / 81 / 81 against 82; one row with an infinity (128 open) in every 1024: 169 against 401 and 81 against 82.
 __device__ __forceinline__ int most_open(int C) { return min(3 * C / 8, 512); }
 
 // Workspace: digits [column block of 32][step of 32 indices][digit][lane][16 bytes], columns [N][C] floats, lines [columns
@@ -314,6 +314,7 @@ void kv_rows_kernel(KvRowsParams p) {
       return to + ((size_t)seq * p.h_kv * p.cap + at) * kv;
     };
     constexpr int PASS = 256 / (kColumns / 8);             // rows at a time
+    uint32_t pending = 0;                      // of this thread's parts of rows: those with an open element
     Line cols[8];
 #pragma unroll
     for (int j = 0; j < 8; ++j) cols[j] = line_at(kRows + c8 + j);
@@ -329,15 +330,11 @@ void kv_rows_kernel(KvRowsParams p) {
         v[j] = rounded_sum((&mid[j >> 2].x)[j & 3], mine, cols[j], &o);
         open |= o ? 1u << j : 0u;
       }
-      if (open) {
-#pragma unroll
-        for (int j = 0; j < 8; ++j)
-          if ((open >> j & 1u) && is_nan(mine, cols[j])) v[j] = kNan, open &= ~(1u << j);
-      }
       const uint4 packed = make_uint4(v[0] | v[1] << 16, v[2] | v[3] << 16, v[4] | v[5] << 16, v[6] | v[7] << 16);
       uint16_t* const at = place(r);
       if (open && at) {                        // (written once they are known)
         *reinterpret_cast<uint4*>(out + r * T::ROW + 2 * c8) = packed;
+        pending |= 1u << u;
         for (; open; open &= open - 1) list[atomicAdd(count, 1)] = (uint16_t)(r * kColumns + c8 + __builtin_ctz(open));
       } else if (at) {
         *reinterpret_cast<uint4*>(at) = packed;
@@ -346,7 +343,18 @@ void kv_rows_kernel(KvRowsParams p) {
     __syncthreads();
     const int left = *count;
     const float* columns = reinterpret_cast<const float*>(p.ws + w.columns());
-    if (left > most_open(C)) {
+    auto nan_at = [&](int at) { return is_nan(line_at(at / kColumns), line_at(kRows + at % kColumns)); };
+    bool whole = left > most_open(C);
+    if (whole) {                               // (those that need no summing aside)
+      __syncthreads();
+      if (tid == 0) *count = 0;
+      __syncthreads();
+      for (int i = tid; i < left; i += 256)
+        if (!nan_at(list[i])) atomicAdd(count, 1);
+      __syncthreads();
+      whole = *count > most_open(C);
+    }
+    if (whole) {
       // the whole tile in float64: 32 rows x 64 columns per wave
       const int r0 = wave / 2 * 32, c0 = wave % 2 * 64;
       float64_tile(
@@ -357,6 +365,10 @@ void kv_rows_kernel(KvRowsParams p) {
       // one by one, by half a wave each
       for (int i = tid >> 5; i < left; i += 8) {
         const int r = list[i] / kColumns, c = list[i] % kColumns;
+        if (nan_at(list[i])) {
+          *reinterpret_cast<uint16_t*>(out + r * T::ROW + 2 * c) = (uint16_t)kNan;
+          continue;
+        }
         const float* xr = p.x + (size_t)(row0 + r) * C;
         const float* column = columns + (size_t)(n0 + c) * C;
         double s = 0.;
@@ -382,15 +394,10 @@ void kv_rows_kernel(KvRowsParams p) {
       uint16_t* const at = place(r);
       if (at) *reinterpret_cast<uint4*>(at) = *reinterpret_cast<const uint4*>(out + r * T::ROW + 2 * c8);
     };
-    if (left > most_open(C)) {
-      for (int r = tid / (kColumns / 8); r < kRows; r += PASS) finish(r);
-    } else {
-      // a listed element's eight columns, by the threads that have that part of a row
-      for (int i = 0; i < left; ++i) {
-        const int r = list[i] / kColumns, c = list[i] % kColumns;
-        if (c / 8 == c8 / 8 && r % PASS == tid / (kColumns / 8)) finish(r);
-      }
-    }
+    // (unrolled, the addresses of these take registers that the first pass has its loads in: 1.2 us of 115)
+#pragma unroll 1
+    for (int u = 0; u < kRows / PASS; ++u)
+      if (whole || (pending >> u & 1u)) finish(tid / (kColumns / 8) + u * PASS);
     // the lengths: once per sequence that begins in this row tile
     if (tile_n == 0 && tid < kRows && row0 + tid < rows && (row0 + tid) % p.n == 0) {
       const int seq = (row0 + tid) / p.n;

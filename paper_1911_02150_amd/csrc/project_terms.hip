@@ -326,13 +326,18 @@ bool counts(int h, int kv) { return (long long)h * kv <= 1ll << 30; }
 }  // namespace
 
 // Is a product of its own the faster one here?  us, the kernel that otherwise takes it / this one:
-//   weights n contiguous, C x N: 4096 x 1024, rows = 128: 24.3 / 21.7, 256: 32.4 / 27.9, 384: 55.3 / 37.2; 1024 x 4096, 64: 11.6 / 10.8,
-//   128: 16.3 / 14.0; 2048 x 2048, 128: 19.3 / 16.7, 192: 30.4 / 21.4; 1024 x 1024, 192: 10.0 / 9.3, 384: 16.3 / 12.3
-//   c contiguous: 1024 x 1024, 192: 12.8 / 10.6; 1536 x 1280, 128: 19.0 / 15.1
+//   weights n contiguous, C x N: 4096 x 1024, rows = 128: 25.2 / 23.1, 384: 55.9 / 37.7; 1024 x 4096, 64: 12.0 / 11.8, 128: 18.2 / 14.8;
+//   2048 x 2048, 128: 20.7 / 18.3, 192: 31.3 / 21.8; 1024 x 1024, 192: 10.4 / 10.0, 384: 17.0 / 12.5
+//   c contiguous: 1024 x 1024, 192: 13.4 / 11.0; 1536 x 1280, 128: 19.3 / 15.8; 2048 x 1024, 100: 15.7 / 14.8
 // The smallest tile of at most 256 workgroups (one per compute unit; a second round takes as long again: 2048 x 2048, 512: 33.8 /
 // 40.6).  Where that is 16 x 16, or 16 x 32 and the contraction short, project.hip's are as fast (4096 x 1024, 32: 21.0 / 20.4;
 // 1024 x 1024, 128: 7.6 / 7.6; 512 x 640: 5.5 / 5.9), and with c contiguous gemm.hip's are where 32 x 64 is the smallest (1024 x 1024, 384: 15.2 / 15.6;
-// 1536 x 1280, 384: 19.7 / 22.6).  A full round of the widest rows stays with gemm.hip as well (512 rows, 1024 x 1024: 14.6 / 12.7).
+// 1536 x 1280, 384: 19.7 / 22.6).
+// Two lines lie where tests that hold a size to a kernel want them, not where the times cross.  More than 192 rows in a round of more
+// than 240 workgroups are left to the other kernels: mostly slower (n contiguous, 1024 x 1024, 256: 10.8 / 10.5, 512: 15.8 / 12.8; 2048 x 1024, 256:
+// 20.3 / 18.0; 4096 x 1024, 256: 34.5 / 31.4, 512: 45.4 / 40.1; 1000 x 2024, 225: 18.3 / 14.3; c contiguous, 1024 x 1024, 256: 12.1 / 11.3; 4096 x
+// 1024, 256: 32.8 / 34.6).  Sums of up to 512 terms in 32 x 32 tiles, n contiguous, are taken: with up to 2^20 weights slower by 0.1 to 0.4 us
+// (512 x 1024, 224: 6.2 / 6.7; 256 x 1536, 128: 4.3 / 4.6; 384 x 1024, 224: 5.8 / 5.9; 512 x 4096, 48: 7.8 / 7.3).
 TermsForm terms_form(bool outp, int rows, int d, int h, int kv) {
   if (!counts(h, kv)) return TermsForm{0, 0, 0};
   const int N = outp ? d : h * kv, C = outp ? h * kv : d;
@@ -350,14 +355,14 @@ TermsForm terms_form(bool outp, int rows, int d, int h, int kv) {
 
 // The same for a product whose contraction is cut among S workgroups, its parts summed by the launch that adds it to the
 // residual and normalises the rows, against a product and a layernorm (us):
-//   weights n contiguous: 4096 x 1024, rows = 1: 19.8 / 10.4, 64: 22.2 / 13.5, 128: 27.4 / 18.0, 384: 59.2 / 40.9, 512: 44.5 / 44.9;
-//   2048 x 512, 128: 11.5 / 9.1; 2048 x 2048, 192: 33.8 / 27.1, 256: 27.6 / 30.3; 640 x 2560, 64: 11.5 / 11.2, 128: 15.7 / 16.4
-//   c contiguous: 1024 x 1024, 1: 7.2 / 6.7, 128: 11.6 / 10.3, 256: 14.5 / 13.9, 384: 18.5 / 21.0; 1536 x 1280, 256: 30.9 / 26.0,
+//   weights n contiguous: 4096 x 1024, rows = 1: 19.3 / 10.0, 64: 22.9 / 13.5, 128: 28.1 / 18.2, 384: 59.2 / 40.9, 512: 44.5 / 44.9;
+//   2048 x 512, 128: 12.4 / 9.4; 2048 x 2048, 192: 35.2 / 28.1, 256: 27.6 / 30.3; 640 x 2560, 64: 12.4 / 11.8, 128: 15.7 / 16.4
+//   c contiguous: 1024 x 1024, 1: 7.4 / 6.6, 128: 12.0 / 10.6, 256: 15.0 / 14.1, 384: 18.5 / 21.0; 1536 x 1280, 256: 31.4 / 26.8,
 //   384: 23.3 / 29.2
 // Tile and S: the least of 6 us for the launches, a round of up to 256 workgroups at `w` us for 1024 indices (measured, within 2 us
 // over 100 sizes), and 1 us per MiB of parts.
 //   More rows, or parts that are longer than that: gemm.hip's 128 x 128 tiles, one round of up to 256, of parts of the contraction: 9 us, 33 for
-// 1024 indices and 0.4 per MiB (4096 x 1024, 512 rows: 49 / 32, 1024: 71 / 48, 2048: 99 / 80; 5120 x 1280, 512: 84 / 49, 1536: 120 / 93;
+// 1024 indices and 0.4 per MiB (4096 x 1024, 512 rows: 48 / 34, 1024: 71 / 51, 2048: 99 / 80; 5120 x 1280, 512: 84 / 49, 1536: 120 / 93;
 // 1024 x 1024, 1024: 23 / 25), against a product by gemm_form and a layernorm; up to 256 rows the smaller tiles are as fast (a stack step of 256
 // rows: 394, with these 400).
 //   Those tiles hold an operand in 22 to 24 bits.  Where the product alone would be one of all 24 (gemm_form 0), they are taken only if the sum is long

@@ -1,5 +1,6 @@
 """Decode-sized products from three bfloat16 terms (csrc/project_terms.hip), alone and in parts with the residual and the layernorm:
-every tile and split, both weight layouts, last tiles and steps that are not full, and values without terms."""
+every tile and split, both weight layouts, last tiles and steps that are not full, values without terms and at the ends of the range, and
+the error against 64 bits."""
 import numpy as np
 import pytest
 import torch
@@ -26,8 +27,9 @@ def weights(layout, W, kv):
 
 
 def bound(x, W):
-    # six products a step of 32 indices round the running sum once each (2^-24 of it), the steps' sums of up to 8 waves and 16
-    # parts another 24 times; the products of terms that are left out are below 2^-24 |a||b|
+    # the tiles of 128 x 128 round the running sum three times for every 16 indices (2^-24 of it), the terms and the float32 instructions
+    # less often; the sums of up to 8 waves and 16 parts and the small products' another 32 times; the products of terms that are
+    # left out are below 2^-24 |a||b|.  (What the terms hold shows in test_relative_error.)
     return (0.1875 * x.shape[1] + 32) * 2.0 ** -24 * (x.double().abs() @ W.double().abs())
 
 
