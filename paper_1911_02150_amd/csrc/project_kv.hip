@@ -5,7 +5,7 @@
 // as it does between any two float64 kernels.)
 //
 // float64 matrix instructions run at 1/32 of the 16-bit rate and bounded this product (32768 rows, d = 1024, 256
-// columns: 42 TFLOP/s, 410 us; this kernel 205: of a tile's 100 us about 20 are the first pass and 20 the open elements; the
+// columns: 42 TFLOP/s, 410 us; this kernel 180: of a tile's 90 us about 20 are the first pass and 20 the open elements; the
 // matrix cores are busy 18 %, vector instructions 34 %; two and three stages ahead measured the same).  Here the sum is found with a bound on its error from exact integer products, and
 // only the elements whose rounding to bf16 the bound leaves open (0.09 % of normal deviates at d = 1024) are summed in float64.
 // (Exact products of operands cut into slices of few bits: after Ozaki, Ogita, Oishi, Rump 2012; here in integers.)

@@ -10,7 +10,7 @@
 // straight into its operand registers (1 KiB at a time, from L2; no two waves of a workgroup need the same), only the
 // rows go through LDS (64 indices to a barrier), and a workgroup is four waves, so that two share a compute unit and one
 // multiplies while the other looks for its rows' largest magnitudes or rounds its sums.
-// Measured (32768 rows, d = 1024, 256 columns): 117 us with the preparation's 8 (project_kv.hip 180, the float64 kernel 410).
+// Measured (32768 rows, d = 1024, 256 columns): 117 us with the preparation's 7 (project_kv.hip 180, the float64 kernel 410).
 // Of a tile's 60 us, two side by side: first pass 8, products 38, sums and rounding 8, open elements 4.  Bound by the matrix
 // cores and the power they draw: the card holds 1.6 to 2.0 GHz in the products (22 us of them at that clock without the
 // conversions).  Without effect: tiles of 64 x 256 with eight waves (half the conversions, nothing beside them: 120), raised
