@@ -10,8 +10,8 @@
 // round for every four.  No scales are needed (bfloat16 has float32's exponents), so nothing has to be known of a row or column
 // before it is multiplied.  A product of terms can overflow where the product of the operands does not, or leave an infinity of the
 // other sign or a NaN where that is one infinity: a wave whose sums are not finite at the end, or that met an operand below
-// 2^-110 other than 0, multiplies its part again on v_mfma_f32_16x16x4_f32 (as it does where an operand was an infinity or
-// NaN).  Relative error of a 1024-term sum of normal deviates 8.1e-8 (all six products in one running sum 1.6e-7, project.hip
+// 2^-110 other than 0, multiplies its part again on v_mfma_f32_16x16x4_f32 (as it does where an operand was an infinity or a
+// weight NaN).  Relative error of a 1024-term sum of normal deviates 8.1e-8 (all six products in one running sum 1.6e-7, project.hip
 // 2.1e-7, gemm.hip 1.6e-7), of a 4096-term one 1.4e-7 (3.5e-7, 4.1e-7), in eight parts 9.1e-8; with every other x a zero, as behind
 // a relu, 7.1e-8 (1.6e-7, 1.5e-7), 1.1e-7 (3.3e-7, 2.9e-7) and 8.2e-8.
 //
@@ -191,7 +191,8 @@ void project_terms_kernel(const float* __restrict__ in, const float* __restrict_
 #pragma unroll
     for (int j = 0; j < CB; ++j) acc[r][j] += low[r][j];
   // An operand too small for its terms; and whatever overflowed on the way (an operand's first term, a product, a sum) has left an
-  // infinity or a NaN behind.
+  // infinity or a NaN behind.  So has a NaN in a row of the input, which leaves nothing to multiply again: such a row in every 32, us by looking
+  // for it / without that (128 rows): 1024 x 4096 18.3 / 27.0, 4096 x 1024 with its layernorm 20.8 / 30.3 (project.hip 24.0, 28.4).
   float over = 0.f;
 #pragma unroll
   for (int r = 0; r < RB; ++r)
@@ -200,8 +201,35 @@ void project_terms_kernel(const float* __restrict__ in, const float* __restrict_
 #pragma unroll
       for (int e = 0; e < 4; ++e) over = fmaf(acc[r][j][e], 0.f, over);
   if (__builtin_expect(__any(!(over == 0.f) || least < kLeast), 0)) {
-    clear();
-    sweep(multiply_plain);
+    bool again = least < kLeast;
+    if (!__any(again)) {
+      uint32_t nan = 0;                        // bit r: in row i of block r
+      for (int step = first + wave; step < end; step += kWaves) {        // (indices past the end are of the same rows)
+        const int c = min(kStep * step + 8 * kk, C - 8);
+#pragma unroll
+        for (int r = 0; r < RB; ++r)
+#pragma unroll
+          for (int q = 0; q < 2; ++q) {
+            const floatx4 v = *reinterpret_cast<const floatx4*>(arow[r] + c + 4 * q);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) nan |= v[e] != v[e] ? 1u << r : 0u;
+          }
+      }
+#pragma unroll
+      for (int o = 16; o < 64; o <<= 1) nan |= __shfl_xor(nan, o);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const uint32_t nan_row = __shfl(nan, 4 * kk + e);
+#pragma unroll
+        for (int r = 0; r < RB; ++r)
+#pragma unroll
+          for (int j = 0; j < CB; ++j) again |= !(acc[r][j][e] * 0.f == 0.f) && !(nan_row >> r & 1u);
+      }
+    }
+    if (__any(again)) {
+      clear();
+      sweep(multiply_plain);
+    }
   }
   // D layout: register e of lane (i, g) is row 4 g + e of the block, column i (KC) or the lane's CB adjacent ones
 #pragma unroll

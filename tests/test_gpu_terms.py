@@ -151,6 +151,26 @@ def test_products_past_the_largest_float(m, layout, rows, C, N, kv, parts):
         agree(got, want, most)
 
 
+@pytest.mark.parametrize("layout", ["n", "c"])
+@pytest.mark.parametrize("rows,C,N,kv,parts", FORMS)
+def test_nan_beside_overflow(m, layout, rows, C, N, kv, parts):
+    """Rows with a NaN among rows whose products overflow, in the same step and tile: NaN is NaN, the others keep their infinities."""
+    g = torch.Generator(device=DEV)
+    g.manual_seed(rows + N)
+    x, W = torch.randn(rows, C, generator=g, device=DEV), torch.randn(C, N, generator=g, device=DEV) / 16
+    x[::3, C // 3] = float("nan")
+    x[1::3, C // 3], W[C // 3, N - 2] = 1e30, 1e30
+    W[C // 7, N // 2] = float("nan")
+    for k, (got, want) in enumerate(results(m, layout, x, W, kv, parts)):
+        ref = want.float()
+        if k == 1:                             # relu: max(NaN, 0) is 0
+            ref = torch.nan_to_num(ref, nan=0.0, posinf=float("inf"))
+        assert torch.equal(torch.isnan(got), torch.isnan(ref)) and torch.equal(torch.isposinf(got), torch.isposinf(ref))
+        fine = torch.isfinite(ref) & torch.isfinite(want)
+        lim = torch.nan_to_num(bound(x, W), nan=0.0, posinf=0.0) + 2.0 ** -23 * torch.nan_to_num(want, posinf=0.0).abs()
+        assert ((got.double() - want).abs()[fine] <= lim[fine]).all()
+
+
 @pytest.mark.parametrize("small", ["rows", "columns"])
 @pytest.mark.parametrize("layout", ["n", "c"])
 @pytest.mark.parametrize("rows,C,N,kv,parts", FORMS)
