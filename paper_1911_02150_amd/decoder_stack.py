@@ -25,6 +25,7 @@ class DecoderStack:
         h, d, k = self.layers[0]["P_q"].shape
         v = self.layers[0]["P_o"].shape[2]
         self.h, self.d, self.k, self.v = h, d, k, v
+        self._parts = (0, 0)
         kshape = (batch, h, cap, k) if multi_head else (batch, cap, k)
         vshape = (batch, h, cap, v) if multi_head else (batch, cap, v)
         self.K = [torch.zeros(kshape, dtype=cache_dtype, device=dev) for _ in self.layers]
@@ -81,9 +82,14 @@ class DecoderStack:
     def _workspace(self, rows: int, kv_rows: int = 0) -> torch.Tensor:
         """Scratch memory for the calls of one pass over `rows` rows, one after another on its stream (a pass's own: calls on several
         streams do not share it)."""
-        parts = [B.mqa_project_add_layernorm_workspace_bytes(B.MQA_PROJ_O, rows, self.d, self.h, self.v), kv_rows, 16]
-        parts += [B.mqa_project_add_layernorm_workspace_bytes(B.MQA_PROJ_LINEAR, rows, ff, 1, self.d) for ff in {w["W1"].shape[1] for w in self.layers}]
-        return torch.empty(max(parts), dtype=torch.uint8, device=self.dev)
+        known, nbytes = self._parts            # (a decoding loop asks for the same rows again and again: 1.5 us of a step)
+        if known != rows:
+            sizes = [B.mqa_project_add_layernorm_workspace_bytes(B.MQA_PROJ_O, rows, self.d, self.h, self.v)]
+            for ff in {w["W1"].shape[1] for w in self.layers}:
+                sizes.append(B.mqa_project_add_layernorm_workspace_bytes(B.MQA_PROJ_LINEAR, rows, ff, 1, self.d))
+            nbytes = max(sizes)
+            self._parts = rows, nbytes
+        return torch.empty(max(nbytes, kv_rows, 16), dtype=torch.uint8, device=self.dev)
 
     # -- one decoding step for the whole stack: per layer 7 launches (fused q/K/V + append, attention (+ merge), output
     #    projection in parts, their sum added into x with the layernorm, W1 with relu, W2 in parts, the same)
