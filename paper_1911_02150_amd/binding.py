@@ -206,7 +206,11 @@ def _kept_for_the_graph(device):
     """While the current stream is captured: is it torch that captures it, so that what is allocated now stays the graph's?  (Its
     blocks are then in a pool other than the allocator's common one.)"""
     at = torch.empty(1, dtype=torch.uint8, device=device).data_ptr()
-    for segment in torch.cuda.memory_snapshot():
+    try:
+        segments = torch.cuda.memory_snapshot()
+    except RuntimeError:                       # (an allocator that does not tell)
+        return False
+    for segment in segments:
         if segment["address"] <= at < segment["address"] + segment["total_size"]:
             return tuple(segment.get("segment_pool_id", (0, 0))) != (0, 0)
     return False

@@ -152,7 +152,7 @@ def test_workspace_of_sizes_past_the_integers():
     assert query(m.MQA_PROJ_O, 128, 1024, 8, 128) > 0
 
 
-@pytest.mark.parametrize("why", ["room", "no room", "captured", "captured by torch", "other device", "foreign stream", "foreign default stream"])
+@pytest.mark.parametrize("why", ["room", "no room", "captured", "captured by torch", "captured, no telling", "other device", "foreign stream", "foreign default stream"])
 def test_where_a_call_gets_its_workspace(monkeypatch, why):
     """A block of torch's allocator, with the call's stream current; none (never an error) where the allocator cannot own it."""
     import contextlib
@@ -184,8 +184,14 @@ def test_where_a_call_gets_its_workspace(monkeypatch, why):
     monkeypatch.setattr(torch.cuda, "default_stream", lambda device: a_stream(0, device))
     monkeypatch.setattr(torch.cuda, "current_device", lambda: 1 if why == "other device" else 0)
     monkeypatch.setattr(torch.cuda, "is_current_stream_capturing", lambda: why.startswith("captured"))
-    monkeypatch.setattr(torch.cuda, "memory_snapshot", lambda: [dict(address=100, total_size=900, segment_pool_id=(0, 7)),
-                                                                dict(address=1000, total_size=9, segment_pool_id=(0, 3 if why == "captured by torch" else 0))])
+
+    def snapshot():
+        if why == "captured, no telling":
+            raise NotImplementedError
+        return [dict(address=100, total_size=900, segment_pool_id=(0, 7)),
+                dict(address=1000, total_size=9, segment_pool_id=(0, 3 if why == "captured by torch" else 0))]
+
+    monkeypatch.setattr(torch.cuda, "memory_snapshot", snapshot)
     monkeypatch.setattr(torch, "empty", empty)
     assert binding._call_workspace(0, device, stream) == (None, 0)
     expected = (block, 4096) if why in ("room", "captured by torch", "foreign stream", "foreign default stream") else (None, 0)
