@@ -146,7 +146,7 @@ TermsForm terms_parts_form(bool outp, int rows, int d, int h, int kv);
 size_t terms_parts_bytes(bool outp, int rows, int d, int h, int kv);
 hipError_t launch_project_terms(bool outp, const float* in, const float* P, float* out, int rows, int d, int h, int kv, int epilogue,
                                 hipStream_t st);
-hipError_t launch_project_add_layernorm(bool outp, const float* in, const float* P, float* x, float* y, int rows, int d, int h, int kv,
+hipError_t launch_project_add_layernorm(bool outp, const float* in, const float* P, float* x, float* y, void* packed, int rows, int d, int h, int kv,
                                         float eps, void* workspace, hipStream_t st);
 
 // project_kv_rows.hip: the same from a workspace of project_kv_rows_workspace(...) bytes (not append: lens_in may be null)
@@ -155,6 +155,16 @@ size_t project_kv_rows_workspace(int d, int h_kv, int k, int v);
 hipError_t launch_project_kv_rows(const float* x, const float* P_k, const float* P_v, void* K, void* V,
                                   const int32_t* lens_in, int32_t* lens_out, int rows, int n, int append, int d, int h_kv,
                                   int cap, int k, int v, void* workspace, hipStream_t st);
+
+// packed.hip: products of a stack's packed operands
+inline size_t packed_bytes(int lines, int C) { return (size_t)lines * C * 4; }      // (weights: and a float per line)
+bool packed_fits(int rows, int N, int C);
+int packed_plan(int mode, int rows, int d, int h, int kv, int residual);
+int packed_layernorm_scale(int N);
+hipError_t launch_pack_weights(bool outp, const float* P, const float* row_scale, void* packed, int32_t* verdict, int d, int h, int kv, hipStream_t st);
+hipError_t launch_packed_product(const void* x, const void* w, float scale, void* out, int rows, int N, int C, int epilogue, int form,
+                                 hipStream_t st);
+hipError_t launch_layernorm_packed(const float* part, int S, float* x, float* y, void* packed, int rows, int N, float eps, hipStream_t st);
 
 // stack_kernels.hip
 hipError_t launch_layernorm(const float* x, float* y, int rows, int d, float eps, hipStream_t st);

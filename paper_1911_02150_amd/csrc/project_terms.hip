@@ -438,8 +438,9 @@ hipError_t launch_project_terms(bool outp, const float* in, const float* P, floa
   return f.S ? launch_tiles(outp, f, in, P, out, nullptr, rows, d, h, kv, epilogue, st) : hipErrorNotSupported;
 }
 
-// x += in . B, y = layernorm(x), in two launches; workspace: terms_parts_bytes(...).  hipErrorNotSupported: no form (terms_parts_form)
-hipError_t launch_project_add_layernorm(bool outp, const float* in, const float* P, float* x, float* y, int rows, int d, int h, int kv,
+// x += in . B, y = layernorm(x), in two launches; workspace: terms_parts_bytes(...).  packed: the layernorm as a packed matrix, too, or instead
+// (y null).  hipErrorNotSupported: no form (terms_parts_form)
+hipError_t launch_project_add_layernorm(bool outp, const float* in, const float* P, float* x, float* y, void* packed, int rows, int d, int h, int kv,
                                         float eps, void* workspace, hipStream_t st) {
   const TermsForm f = terms_parts_form(outp, rows, d, h, kv);
   if (!f.S) return hipErrorNotSupported;
@@ -448,6 +449,7 @@ hipError_t launch_project_add_layernorm(bool outp, const float* in, const float*
   const hipError_t e = f.RB == 8 ? launch_gemm_parts(outp ? 3 : 0, in, P, part, rows, d, h, kv, 0, 128, f.S, st)
                                  : launch_tiles(outp, f, in, P, nullptr, part, rows, d, h, kv, 0, st);
   if (e != hipSuccess) return e;
+  if (packed) return launch_layernorm_packed(part, f.S, x, y, packed, rows, N, eps, st);
   if (N <= 1024) hipLaunchKernelGGL(finish_kernel<1>, dim3(rows), dim3(256), 0, st, part, x, y, rows, N, f.S, eps);
   else if (N <= 2048) hipLaunchKernelGGL(finish_kernel<2>, dim3(rows), dim3(256), 0, st, part, x, y, rows, N, f.S, eps);
   else hipLaunchKernelGGL(finish_kernel<4>, dim3(rows), dim3(256), 0, st, part, x, y, rows, N, f.S, eps);
