@@ -1,5 +1,6 @@
-"""ctypes binding of libmqa_decode.so: same names as the C ABI (include/mqa.h),
-argument marshalling only.  torch is used for device memory and the current
+"""Binding of libmqa_decode.so: same names as the C ABI (include/mqa.h),
+argument marshalling only (ctypes, and for the calls of a decoding loop with
+plain arguments the native functions of csrc/calls.cpp).  torch is used for device memory and the current
 stream; every step of the path runs in the library's HIP kernels.  There is no
 fallback: if the library is missing, loading raises."""
 from __future__ import annotations
@@ -40,11 +41,25 @@ class MqaError(RuntimeError):
 
 
 _lib = None
+_native = None             # csrc/calls.cpp: the calls of a decoding loop in their plainest form; None from it means "by the general path"
+_NATIVE_FUNCTIONS = [
+    "mqa_decode_step", "mha_decode_step", "mqa_decode_step_window", "mha_decode_step_window", "mqa_project_append_qkv", "mqa_project_qkvo_ex",
+    "mqa_project_add_layernorm", "mqa_project_memory_kv", "mqa_project_memory_kv_ws", "mqa_memory_decode_step", "mqa_decode_step_beams",
+    "mqa_beam_reorder_kv", "mqa_prefill_attention", "mha_prefill_attention",
+]
+
+
+def _load_native(lib):
+    if not os.path.exists(os.path.join(_PKG_DIR, "_calls.so")):
+        raise OSError(f"{os.path.join(_PKG_DIR, '_calls.so')} not found: build it with `python -m paper_1911_02150_amd.build`")
+    from . import _calls
+    _calls.init(MqaError, torch.nn.Parameter, *[ctypes.cast(getattr(lib, name), ctypes.c_void_p).value for name in _NATIVE_FUNCTIONS])
+    return _calls
 
 
 def load_library(path: str = LIB_PATH):
     """Loads the shared library (once).  Raises OSError if it has not been built."""
-    global _lib
+    global _lib, _native
     if _lib is not None:
         return _lib
     if not os.path.exists(path):
@@ -117,6 +132,7 @@ def load_library(path: str = LIB_PATH):
                         "mqa_decode_beams_workspace_bytes", "mqa_decode_workspace_bytes_default", "mqa_project_kv_workspace_bytes",
                         "mqa_project_add_layernorm_workspace_bytes", "mqa_stack_packed_bytes"):
             getattr(lib, name).restype = ci
+    _native = _load_native(lib)
     _lib = lib
     return lib
 
@@ -125,7 +141,8 @@ def status_string(status: int) -> str:
     return load_library().mqa_status_string(int(status)).decode()
 
 
-# A decode step is a few launches of a few microseconds: what a call costs on the host counts.  Addresses and the
+# A decode step is a few launches of a few microseconds: what a call costs on the host counts (by this path 7 us, by
+# csrc/calls.cpp 4).  Addresses and the
 # stream are passed as plain integers, and the stream is asked for as one (torch.cuda.current_stream() builds a
 # Stream object: 3.0 us of a call's 8 to 12; the call into the library with its launch is 3.1).
 def _ptr(t):
@@ -293,6 +310,10 @@ def _decode(fn_name, multi_head, q, K, V, lens, o, scale, workspace, stream, tun
 
 def mqa_decode_step(q, K, V, lens, o=None, scale=1.0, workspace=None, stream=None, tuning=None):
     """q [b,h,k] f32, K [b,cap,k], V [b,cap,v] (f32 or bf16), lens [b] int32 -> o [b,h,v] f32."""
+    if tuning is None and stream is None and workspace is not None and _native is not None:
+        done = _native.decode(False, q, K, V, lens, o, scale, workspace, None)
+        if done is not None:
+            return done
     if tuning is None:
         return _decode("mqa_decode_step", False, q, K, V, lens, o, scale, workspace, stream, None, False)
     return _decode("mqa_decode_step_ex", False, q, K, V, lens, o, scale, workspace, stream, tuning)
@@ -300,6 +321,10 @@ def mqa_decode_step(q, K, V, lens, o=None, scale=1.0, workspace=None, stream=Non
 
 def mha_decode_step(q, K, V, lens, o=None, scale=1.0, workspace=None, stream=None, tuning=None):
     """q [b,h,k] f32, K [b,h,cap,k], V [b,h,cap,v], lens [b] int32 -> o [b,h,v] f32."""
+    if tuning is None and stream is None and workspace is not None and _native is not None:
+        done = _native.decode(True, q, K, V, lens, o, scale, workspace, None)
+        if done is not None:
+            return done
     if tuning is None:
         return _decode("mha_decode_step", True, q, K, V, lens, o, scale, workspace, stream, None, False)
     return _decode("mha_decode_step_ex", True, q, K, V, lens, o, scale, workspace, stream, tuning)
@@ -324,10 +349,18 @@ def mqa_decode_step_noalloc(q, K, V, lens, o, scale=1.0, stream=None):
 
 def mqa_decode_step_window(q, K, V, lens, window, o=None, scale=1.0, workspace=None, stream=None):
     """Local attention: sequence i attends to its last `window` valid positions only."""
+    if stream is None and workspace is not None and _native is not None:
+        done = _native.decode(False, q, K, V, lens, o, scale, workspace, window)
+        if done is not None:
+            return done
     return _decode("mqa_decode_step_window", False, q, K, V, lens, o, scale, workspace, stream, None, False, window)
 
 
 def mha_decode_step_window(q, K, V, lens, window, o=None, scale=1.0, workspace=None, stream=None):
+    if stream is None and workspace is not None and _native is not None:
+        done = _native.decode(True, q, K, V, lens, o, scale, workspace, window)
+        if done is not None:
+            return done
     return _decode("mha_decode_step_window", True, q, K, V, lens, o, scale, workspace, stream, None, False, window)
 
 
@@ -381,6 +414,10 @@ def mqa_append_kv_rows(K, V, k_new, v_new, lens, stream=None):
 
 def mqa_prefill_attention(q, K, V, lens, o=None, scale=1.0, workspace=None, stream=None):
     """q [b,n,h,k], K [b,cap,k], V [b,cap,v] bf16, lens [b] (after the append) -> o [b,n,h,v]."""
+    if stream is None and workspace is not None and _native is not None:
+        done = _native.attend_rows(1, q, K, V, lens, o, scale, workspace)
+        if done is not None:
+            return done
     lib = load_library()
     _check(q, "q", torch.float32), _check(K, "K"), _check(V, "V"), _check(lens, "lens", torch.int32)
     b, n, h, k = q.shape
@@ -401,6 +438,10 @@ def mqa_prefill_attention(q, K, V, lens, o=None, scale=1.0, workspace=None, stre
 
 def mha_prefill_attention(q, K, V, lens, o=None, scale=1.0, workspace=None, stream=None):
     """q [b,h,n,k], K [b,h,cap,k], V [b,h,cap,v] bf16, lens [b] (after the append) -> o [b,h,n,v]."""
+    if stream is None and workspace is not None and _native is not None:
+        done = _native.attend_rows(2, q, K, V, lens, o, scale, workspace)
+        if done is not None:
+            return done
     lib = load_library()
     _check(q, "q", torch.float32), _check(K, "K"), _check(V, "V"), _check(lens, "lens", torch.int32)
     b, h, n, k = q.shape
@@ -422,6 +463,10 @@ def mha_prefill_attention(q, K, V, lens, o=None, scale=1.0, workspace=None, stre
 def mqa_project_append_qkv(x, P_q, P_k, P_v, K, V, lens_in, lens_out, q=None, stream=None):
     """x [b,d], P_q [h,d,k], P_k [d,k] or [h,d,k], P_v likewise, K/V caches, lens_in/lens_out [b] int32
     (different tensors) -> q [b,h,k]; the new rows are written into the caches."""
+    if stream is None and _native is not None:
+        done = _native.append_qkv(x, P_q, P_k, P_v, K, V, lens_in, lens_out, q)
+        if done is not None:
+            return done
     lib = load_library()
     f32, i32 = torch.float32, torch.int32
     _check(x, "x", f32), _check(P_q, "P_q", f32), _check(P_k, "P_k", f32), _check(P_v, "P_v", f32)
@@ -493,6 +538,8 @@ def mqa_project_memory_kv(M, P_k, P_v, K, V, lens, mem_lens=None, stream=None, w
     """M [b,m,d], P_k [d,k] or [h,d,k], P_v likewise, caches K/V ([b,cap,k] or [b,h,cap,k]), lens [b] int32
     (output), mem_lens [b] int32 or None: projects the whole memory into the caches (launches and workspace: as
     mqa_project_append_kv_rows)."""
+    if stream is None and _native is not None and _native.memory_kv(M, P_k, P_v, K, V, lens, mem_lens, workspace, _KV_ROWS_SMALL) is not None:
+        return
     lib = load_library()
     for name, t in (("M", M), ("P_k", P_k), ("P_v", P_v)):
         _check(t, name, torch.float32)
@@ -521,6 +568,10 @@ def mqa_project_memory_kv(M, P_k, P_v, K, V, lens, mem_lens=None, stream=None, w
 def mqa_memory_decode_step(q, K, V, lens, o=None, scale=1.0, workspace=None, stream=None):
     """q [b,queries,h,k] (the queries of the decoder positions sharing memory i), K [b,cap,k], V [b,cap,v],
     lens [b] -> o [b,queries,h,v]."""
+    if stream is None and workspace is not None and _native is not None:
+        done = _native.attend_rows(0, q, K, V, lens, o, scale, workspace)
+        if done is not None:
+            return done
     lib = load_library()
     _check(q, "q", torch.float32), _check(K, "K"), _check(V, "V"), _check(lens, "lens", torch.int32)
     b, nq, h, k = q.shape
@@ -547,6 +598,10 @@ def mqa_decode_step_beams(q, K_src, V_src, lens_src, K_own, V_own, lens_own, o=N
                           workspace=None, stream=None):
     """q [b,beam,h,k]; K_src [b,cap_src,k], V_src [b,cap_src,v], lens_src [b]; K_own [b,beam,cap_own,k],
     V_own [b,beam,cap_own,v], lens_own [b*beam] -> o [b,beam,h,v]."""
+    if stream is None and workspace is not None and _native is not None:
+        done = _native.beams(q, K_src, V_src, lens_src, K_own, V_own, lens_own, o, scale, workspace)
+        if done is not None:
+            return done
     lib = load_library()
     _check(q, "q", torch.float32), _check(lens_src, "lens_src", torch.int32), _check(lens_own, "lens_own", torch.int32)
     for name, t in (("K_src", K_src), ("V_src", V_src), ("K_own", K_own), ("V_own", V_own)):
@@ -574,6 +629,8 @@ def mqa_decode_step_beams(q, K_src, V_src, lens_src, K_own, V_own, lens_own, o=N
 def mqa_beam_reorder_kv(K_src, V_src, lens_src, parent, K_dst, V_dst, lens_dst, stream=None):
     """K_* [n,cap,k] or [n,h_kv,cap,k], V_* likewise, lens_* [n], parent [n] int32: slot r of the
     destination takes the valid rows and the length of slot parent[r] of the source."""
+    if stream is None and _native is not None and _native.reorder(K_src, V_src, lens_src, parent, K_dst, V_dst, lens_dst) is not None:
+        return
     lib = load_library()
     for name, t in (("K_src", K_src), ("V_src", V_src), ("K_dst", K_dst), ("V_dst", V_dst)):
         _check(t, name)
@@ -631,11 +688,19 @@ def _project(fn_name, mode, x, P, out, epilogue, stream):
 def mqa_project_qkvo(mode, x, P, out=None, stream=None):
     """mode Q/KV_MH: x [rows,d], P [h,d,kv] -> [rows,h,kv];  KV / LINEAR: P [d,kv] -> [rows,kv];
     O: x [rows,h,kv], P [h,d,kv] -> [rows,d]."""
+    if stream is None and _native is not None:
+        done = _native.project(mode, x, P, out, None)
+        if done is not None:
+            return done
     return _project("mqa_project_qkvo", mode, x, P, out, None, stream)
 
 
 def mqa_project_qkvo_ex(mode, x, P, out=None, epilogue=MQA_EPI_STORE, stream=None):
     """As mqa_project_qkvo with an epilogue: MQA_EPI_RELU stores max(x, 0), MQA_EPI_ADD adds to `out`."""
+    if stream is None and _native is not None:
+        done = _native.project(mode, x, P, out, epilogue)
+        if done is not None:
+            return done
     return _project("mqa_project_qkvo_ex", mode, x, P, out, epilogue, stream)
 
 
@@ -682,6 +747,10 @@ def _add_layernorm(fn_name, mode, x, P, acc, out, packed, eps, workspace, stream
 def mqa_project_add_layernorm(mode, x, P, acc, out=None, eps=1e-6, workspace=None, stream=None):
     """acc += x . P (mode O: x [rows,h,kv], P [h,d,kv]; LINEAR: x [rows,d], P [d,kv]), then out = layernorm(acc).  Returns out.
     Workspace: as mqa_project_append_kv_rows."""
+    if stream is None and workspace is not None and _native is not None:
+        done = _native.add_layernorm(mode, x, P, acc, out, eps, workspace)
+        if done is not None:
+            return done
     if out is None:
         out = torch.empty_like(acc)
     _add_layernorm("mqa_project_add_layernorm", mode, x, P, acc, out, None, eps, workspace, stream)

@@ -1,4 +1,4 @@
-"""Builds libmqa_decode.so (gfx950) in-tree with hipcc.  `python -m paper_1911_02150_amd.build`."""
+"""Builds libmqa_decode.so (gfx950) with hipcc and _calls.so in-tree.  `python -m paper_1911_02150_amd.build`."""
 from __future__ import annotations
 
 import os
@@ -17,9 +17,10 @@ HIPCC_FLAGS = [
 ]
 
 
-def build_library(verbose: bool = True, extra_flags=()) -> str:
-    hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
-    cmd = [hipcc, *HIPCC_FLAGS, *extra_flags, *[os.path.join(CSRC, s) for s in SOURCES], "-o", LIB_PATH]
+CALLS_PATH = os.path.join(PKG_DIR, "_calls.so")
+
+
+def _run(cmd, verbose):
     if verbose:
         print(" ".join(cmd), flush=True)
     res = subprocess.run(cmd, capture_output=True, text=True)
@@ -28,10 +29,32 @@ def build_library(verbose: bool = True, extra_flags=()) -> str:
     if verbose and out.strip():
         print(out, flush=True)
     if res.returncode != 0:
-        raise RuntimeError("hipcc failed:\n" + out)
+        raise RuntimeError(f"{os.path.basename(cmd[0])} failed:\n" + out)
+
+
+def build_calls(verbose: bool = True) -> str:
+    """The binding's native calls: host code over torch's tensor type."""
+    import sysconfig
+
+    import torch
+    torch_dir = os.path.dirname(torch.__file__)
+    rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
+    includes = [os.path.join(torch_dir, "include"), os.path.join(torch_dir, "include", "torch", "csrc", "api", "include"),
+                sysconfig.get_paths()["include"], os.path.join(rocm, "include")]
+    _run([os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-shared", "-fPIC", "-Wall", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+          "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1", *[f"-I{d}" for d in includes], os.path.join(CSRC, "calls.cpp"), "-o", CALLS_PATH,
+          f"-L{os.path.join(torch_dir, 'lib')}", "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip"], verbose)
+    return CALLS_PATH
+
+
+def build_library(verbose: bool = True, extra_flags=()) -> str:
+    hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+    cmd = [hipcc, *HIPCC_FLAGS, *extra_flags, *[os.path.join(CSRC, s) for s in SOURCES], "-o", LIB_PATH]
+    _run(cmd, verbose)
     return LIB_PATH
 
 
 if __name__ == "__main__":
     build_library()
+    build_calls()
     sys.exit(0)

@@ -205,6 +205,9 @@ class DecoderStack:
             sizes = [B.mqa_project_add_layernorm_workspace_bytes(B.MQA_PROJ_O, rows, self.d, self.h, self.v)]
             for ff in {w["W1"].shape[1] for w in self.layers}:
                 sizes.append(B.mqa_project_add_layernorm_workspace_bytes(B.MQA_PROJ_LINEAR, rows, ff, 1, self.d))
+            if rows == self.b:                 # (a step's attention)
+                dt = B._cache_dtype(self.K[0])
+                sizes.append(B.mqa_decode_workspace_bytes_default(self.b, self.h, self.cap, self.k, self.v, dt, self.multi_head))
             nbytes = max(sizes)
             self._parts = rows, nbytes
         parts = max(plan[2] & 15 for plan in plans)
@@ -221,7 +224,7 @@ class DecoderStack:
         rows = self._packed_rows(self.b, self.d) if logits_form or any(plan[1] for plan in plans) else None
         for l, w in enumerate(self.layers):
             q = self._append_fused(l, hx)
-            o = dec(q, self.K[l], self.V[l], self.lens[l])
+            o = dec(q, self.K[l], self.V[l], self.lens[l], workspace=ws)
             packed = rows if plans[l][1] else None
             self._project_norm(B.MQA_PROJ_O, o, w["P_o"], x, ws, hx if packed is None else None, packed)
             last = logits_form and l + 1 == len(self.layers)
