@@ -311,8 +311,7 @@ int add_layernorm_impl(int mode, const float* in, const float* P, float* x, floa
     return launch_project_add_layernorm(mode == MQA_PROJ_O, in, P, x, y, packed, rows, d, h, kv, eps, workspace, st) == hipSuccess ? MQA_OK : MQA_ERR_LAUNCH;
   const int rc = project_impl(mode, in, P, x, rows, d, h, kv, MQA_EPI_ADD, stream);
   if (rc != MQA_OK) return rc;
-  const hipError_t e = packed ? launch_layernorm_packed(nullptr, 0, x, y, packed, rows, N, eps, st) : launch_layernorm(x, y, rows, N, eps, st);
-  return e == hipSuccess ? MQA_OK : MQA_ERR_LAUNCH;
+  return launch_layernorm(x, y, packed, rows, N, eps, st) == hipSuccess ? MQA_OK : MQA_ERR_LAUNCH;
 }
 
 }  // namespace
@@ -694,7 +693,7 @@ int mqa_stack_layernorm(const float* x, float* y, int rows, int d, float eps, vo
   if (!x || !y) return MQA_ERR_NULL;
   if (rows <= 0 || d <= 0) return MQA_ERR_SHAPE;
   if (misaligned(x) || misaligned(y)) return MQA_ERR_ALIGN;
-  return launch_layernorm(x, y, rows, d, eps, static_cast<hipStream_t>(stream)) == hipSuccess ? MQA_OK : MQA_ERR_LAUNCH;
+  return launch_layernorm(x, y, nullptr, rows, d, eps, static_cast<hipStream_t>(stream)) == hipSuccess ? MQA_OK : MQA_ERR_LAUNCH;
 }
 
 size_t mqa_stack_packed_bytes(int lines, int C, int weights) {
@@ -719,7 +718,7 @@ int mqa_stack_product_plan(mqa_proj_mode mode, int rows, int d, int h, int kv, i
   return packed_plan(mode, rows, d, h, kv, residual != 0);
 }
 
-int mqa_stack_layernorm_exponent(int d) { return d > 0 ? packed_layernorm_scale(d) : 0; }
+int mqa_stack_layernorm_exponent(int d) { return d > 0 ? packed_layernorm_exponent(d) : 0; }
 
 int mqa_stack_product(const void* x, const void* w, float scale, void* out, int rows, int N, int C, mqa_proj_epilogue epilogue, int form, void* stream) {
   if (!x || !w || !out) return MQA_ERR_NULL;
@@ -737,7 +736,9 @@ int mqa_stack_layernorm_packed(const float* parts, int S, float* x, float* y, vo
   if (!x || (!y && !packed) || (S > 0 && !parts)) return MQA_ERR_NULL;
   if (S < 0 || rows <= 0 || d <= 0 || d > 4096 || (packed ? !packed_fits(rows, 8, d) : (d & 7) != 0)) return MQA_ERR_SHAPE;
   if (misaligned(x) || (y && misaligned(y)) || (packed && misaligned(packed)) || (parts && misaligned(parts))) return MQA_ERR_ALIGN;
-  return launch_layernorm_packed(parts, S, x, y, packed, rows, d, eps, static_cast<hipStream_t>(stream)) == hipSuccess ? MQA_OK : MQA_ERR_LAUNCH;
+  hipStream_t st = static_cast<hipStream_t>(stream);
+  const hipError_t e = S > 0 ? launch_finish(parts, S, x, y, packed, rows, d, eps, st) : launch_layernorm(x, y, packed, rows, d, eps, st);
+  return e == hipSuccess ? MQA_OK : MQA_ERR_LAUNCH;
 }
 
 int mqa_stack_embed(const int32_t* tokens, const int32_t* positions, const float* E, const float* P, float* x,

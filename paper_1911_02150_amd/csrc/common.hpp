@@ -144,6 +144,8 @@ struct TermsForm { int RB, CB, S; };
 TermsForm terms_form(bool outp, int rows, int d, int h, int kv);
 TermsForm terms_parts_form(bool outp, int rows, int d, int h, int kv);
 size_t terms_parts_bytes(bool outp, int rows, int d, int h, int kv);
+// x += the S parts, then layernorm(x) as float32 to y and packed (packed.hip) to `packed`; either may be null
+hipError_t launch_finish(const float* part, int S, float* x, float* y, void* packed, int rows, int N, float eps, hipStream_t st);
 hipError_t launch_project_terms(bool outp, const float* in, const float* P, float* out, int rows, int d, int h, int kv, int epilogue,
                                 hipStream_t st);
 hipError_t launch_project_add_layernorm(bool outp, const float* in, const float* P, float* x, float* y, void* packed, int rows, int d, int h, int kv,
@@ -160,14 +162,13 @@ hipError_t launch_project_kv_rows(const float* x, const float* P_k, const float*
 inline size_t packed_bytes(int lines, int C) { return (size_t)lines * C * 4; }      // (weights: and a float per line)
 bool packed_fits(int rows, int N, int C);
 int packed_plan(int mode, int rows, int d, int h, int kv, int residual);
-int packed_layernorm_scale(int N);
+int packed_layernorm_exponent(int N);
 hipError_t launch_pack_weights(bool outp, const float* P, const float* row_scale, void* packed, int32_t* verdict, int d, int h, int kv, hipStream_t st);
 hipError_t launch_packed_product(const void* x, const void* w, float scale, void* out, int rows, int N, int C, int epilogue, int form,
                                  hipStream_t st);
-hipError_t launch_layernorm_packed(const float* part, int S, float* x, float* y, void* packed, int rows, int N, float eps, hipStream_t st);
 
 // stack_kernels.hip
-hipError_t launch_layernorm(const float* x, float* y, int rows, int d, float eps, hipStream_t st);
+hipError_t launch_layernorm(const float* x, float* y, void* packed, int rows, int d, float eps, hipStream_t st);      // (packed: d <= 4096; either may be null)
 hipError_t launch_embed(const int32_t* tokens, const int32_t* pos, const float* E, const float* P, float* x,
                         int rows, int d, int vocab, int max_pos, hipStream_t st);
 hipError_t launch_add(float* a, const float* b, size_t n, hipStream_t st);
@@ -229,6 +230,14 @@ __device__ __forceinline__ float split_scale(float most, int top) {
   return __uint_as_float((uint32_t)min(254, 254 + top - (int)(__float_as_uint(most) >> 23)) << 23);
 }
 __device__ __forceinline__ int split_exponent(float scale) { return 127 - (int)(__float_as_uint(scale) >> 23); }
+
+// Four neighbouring values of a layernorm's row, and where they go in a packed matrix of `rows` lines (packed.hip).
+__device__ __forceinline__ void store_packed4(unsigned char* packed, float scale, int rows, int row, int column, float a, float b, float c, float d) {
+  const Split2 s = split2(a * scale, b * scale), t = split2(c * scale, d * scale);
+  unsigned char* at = packed + ((size_t)(column >> 5) * 2 * rows + row) * 64 + (column & 31) * 2;
+  *reinterpret_cast<uint2*>(at) = make_uint2(s.hi, t.hi);
+  *reinterpret_cast<uint2*>(at + (size_t)rows * 64) = make_uint2(s.lo, t.lo);
+}
 
 __device__ __forceinline__ float wave_max(float x) {
 #pragma unroll

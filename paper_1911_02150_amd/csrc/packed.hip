@@ -309,78 +309,6 @@ void finish_scales_kernel(float* most, int n) {
   if (i < n) most[i] = 1.f / split_scale(most[i] > 0.f ? most[i] : 1.f, 14);
 }
 
-// ---- x[row] += the sum of its S parts, in order (S may be 0); y[row] = layernorm(x[row]) as float32 and packed, either may be
-// left out.  W waves per row of at most 512 W NV columns, eight columns per lane, all loads in flight together.
-template <int W, int NV>
-__global__ __launch_bounds__(256)
-void layernorm_packed_kernel(const float* __restrict__ part, int S, float* x, float* __restrict__ y, unsigned char* __restrict__ packed,
-                             int rows, int N, float eps, float scale) {
-  __shared__ float red[4];
-  const int wave = threadIdx.x >> 6, t = threadIdx.x % (64 * W);
-  const int row = blockIdx.x * (4 / W) + wave / W;
-  const bool there = row < rows;
-  const size_t base = (size_t)min(row, rows - 1) * N;
-  float v[NV][8];
-#pragma unroll
-  for (int u = 0; u < NV; ++u) {
-    const int c = min(8 * (t + 64 * W * u), N - 8);
-    const floatx4 *xr = reinterpret_cast<const floatx4*>(x + base + c), *pr = reinterpret_cast<const floatx4*>(part + base + c);
-    floatx4 a = xr[0], b = xr[1];
-    if (S) {
-      floatx4 sa = pr[0], sb = pr[1];
-      const size_t stride = (size_t)rows * N / 4;
-      for (int p = 1; p < S; ++p) sa += pr[p * stride], sb += pr[p * stride + 1];
-      a += sa, b += sb;
-    }
-#pragma unroll
-    for (int e = 0; e < 4; ++e) v[u][e] = a[e], v[u][4 + e] = b[e];
-  }
-  auto row_sum = [&](float s) -> float {
-    s = wave_sum(s);
-    __syncthreads();
-    if ((threadIdx.x & 63) == 0) red[wave] = s;
-    __syncthreads();
-    return W == 2 ? red[wave & 2] + red[(wave & 2) + 1] : (red[0] + red[1]) + (red[2] + red[3]);
-  };
-  float sum = 0.f;
-#pragma unroll
-  for (int u = 0; u < NV; ++u)
-    if (8 * (t + 64 * W * u) < N)
-#pragma unroll
-      for (int e = 0; e < 8; e += 4) sum += (v[u][e] + v[u][e + 1]) + (v[u][e + 2] + v[u][e + 3]);
-  const float mean = row_sum(sum) / N;
-  float q = 0.f;
-#pragma unroll
-  for (int u = 0; u < NV; ++u)
-    if (8 * (t + 64 * W * u) < N)
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        const float c = v[u][e] - mean;
-        q += c * c;
-      }
-  const float rstd = 1.0f / sqrtf(row_sum(q) / N + eps);
-#pragma unroll
-  for (int u = 0; u < NV; ++u) {
-    const int c = 8 * (t + 64 * W * u);
-    if (!there || c >= N) continue;
-    if (S) {
-      *reinterpret_cast<floatx4*>(x + base + c) = floatx4{v[u][0], v[u][1], v[u][2], v[u][3]};
-      *reinterpret_cast<floatx4*>(x + base + c + 4) = floatx4{v[u][4], v[u][5], v[u][6], v[u][7]};
-    }
-#pragma unroll
-    for (int e = 0; e < 8; ++e) v[u][e] = (v[u][e] - mean) * rstd;
-    if (y) {
-      *reinterpret_cast<floatx4*>(y + base + c) = floatx4{v[u][0], v[u][1], v[u][2], v[u][3]};
-      *reinterpret_cast<floatx4*>(y + base + c + 4) = floatx4{v[u][4], v[u][5], v[u][6], v[u][7]};
-    }
-    if (packed) {
-#pragma unroll
-      for (int e = 0; e < 8; ++e) v[u][e] *= scale;
-      store_octet(packed + ((size_t)(c >> 5) * 2 * rows + row) * 64 + (c >> 3 & 3) * 16, (size_t)rows * 64, v[u]);
-    }
-  }
-}
-
 }  // namespace
 
 // Tiles, what a round of 256 of them takes for 1024 indices (us; measured, many rows and all parts in one round), and the relative
@@ -471,21 +399,10 @@ hipError_t launch_pack_weights(bool outp, const float* P, const float* row_scale
 }
 
 // log2 of what a packed layernorm row of N columns is scaled by: sqrt(N) comes to 2^15 at most
-int packed_layernorm_scale(int N) {
+int packed_layernorm_exponent(int N) {
   int s = 15;
   while (s > 0 && ldexp(1., 2 * (15 - s)) < N) --s;
   return s;
-}
-
-hipError_t launch_layernorm_packed(const float* part, int S, float* x, float* y, void* packed, int rows, int N, float eps, hipStream_t st) {
-  const float scale = ldexpf(1.f, packed_layernorm_scale(N));
-  unsigned char* to = static_cast<unsigned char*>(packed);
-  if (!part) part = x;                         // (not read)
-  if (N <= 1024) hipLaunchKernelGGL((layernorm_packed_kernel<2, 1>), dim3((rows + 1) / 2), dim3(256), 0, st, part, S, x, y, to, rows, N, eps, scale);
-  else if (N <= 2048) hipLaunchKernelGGL((layernorm_packed_kernel<4, 1>), dim3(rows), dim3(256), 0, st, part, S, x, y, to, rows, N, eps, scale);
-  else if (N <= 4096) hipLaunchKernelGGL((layernorm_packed_kernel<4, 2>), dim3(rows), dim3(256), 0, st, part, S, x, y, to, rows, N, eps, scale);
-  else return hipErrorNotSupported;
-  return hipGetLastError();
 }
 
 }  // namespace mqa

@@ -5,6 +5,8 @@
 // All float32; one workgroup (256 threads) per row.
 #include "common.hpp"
 
+#include <math.h>
+
 namespace mqa {
 namespace {
 
@@ -40,7 +42,7 @@ void layernorm_kernel(const float* __restrict__ x, float* __restrict__ y, int d,
 // squares and the result (the rows of a decode step are few: the launch is one memory round trip).
 template <int NV>
 __global__ __launch_bounds__(256)
-void layernorm_rows_kernel(const float* __restrict__ x, float* __restrict__ y, int d, float eps) {
+void layernorm_rows_kernel(const float* __restrict__ x, float* __restrict__ y, unsigned char* __restrict__ packed, float scale, int d, float eps) {
   __shared__ float red[4];
   const float4* xr = reinterpret_cast<const float4*>(x + (size_t)blockIdx.x * d);
   float4* yr = reinterpret_cast<float4*>(y + (size_t)blockIdx.x * d);
@@ -66,7 +68,11 @@ void layernorm_rows_kernel(const float* __restrict__ x, float* __restrict__ y, i
 #pragma unroll
   for (int u = 0; u < NV; ++u) {
     const int i = threadIdx.x + 256 * u;
-    if (i < d4) yr[i] = make_float4((r[u].x - mean) * rstd, (r[u].y - mean) * rstd, (r[u].z - mean) * rstd, (r[u].w - mean) * rstd);
+    if (i < d4) {
+      const float4 n = make_float4((r[u].x - mean) * rstd, (r[u].y - mean) * rstd, (r[u].z - mean) * rstd, (r[u].w - mean) * rstd);
+      if (y) yr[i] = n;
+      if (packed) store_packed4(packed, scale, gridDim.x, blockIdx.x, 4 * i, n.x, n.y, n.z, n.w);
+    }
   }
 }
 
@@ -135,9 +141,12 @@ void argmax_kernel(const float* __restrict__ x, int32_t* __restrict__ out, int n
 
 }  // namespace
 
-hipError_t launch_layernorm(const float* x, float* y, int rows, int d, float eps, hipStream_t st) {
-  if ((d & 3) == 0 && d <= 1024) hipLaunchKernelGGL(layernorm_rows_kernel<1>, dim3(rows), dim3(256), 0, st, x, y, d, eps);
-  else if ((d & 3) == 0 && d <= 4096) hipLaunchKernelGGL(layernorm_rows_kernel<4>, dim3(rows), dim3(256), 0, st, x, y, d, eps);
+hipError_t launch_layernorm(const float* x, float* y, void* packed, int rows, int d, float eps, hipStream_t st) {
+  unsigned char* to = static_cast<unsigned char*>(packed);
+  const float scale = ldexpf(1.f, packed_layernorm_exponent(d));
+  if ((d & 3) == 0 && d <= 1024) hipLaunchKernelGGL(layernorm_rows_kernel<1>, dim3(rows), dim3(256), 0, st, x, y, to, scale, d, eps);
+  else if ((d & 3) == 0 && d <= 4096) hipLaunchKernelGGL(layernorm_rows_kernel<4>, dim3(rows), dim3(256), 0, st, x, y, to, scale, d, eps);
+  else if (packed) return hipErrorNotSupported;
   else hipLaunchKernelGGL(layernorm_kernel, dim3(rows), dim3(256), 0, st, x, y, d, eps);
   return hipGetLastError();
 }
