@@ -15,9 +15,11 @@
 //   O              : C = h*kv, N = d,    B[c, t]  = P[c/kv][t][c%kv]   (C contiguous)
 //
 // One workgroup of 8 waves per output tile of RB x CB MFMA blocks of 16x16 (16x16 ... 32x64).
-// The contraction axis is cut into groups of 2 or 4 chunks of 16; wave w takes groups
+// The contraction axis is cut into groups of 1, 2 or 4 chunks of 16; wave w takes groups
 // w, w+8, ... (one group in flight while the previous one is multiplied) and the eight partial
-// tiles are summed through LDS.  With at most a few hundred rows these GEMMs are far from
+// tiles are summed through LDS.  Short groups start sooner and need fewer registers, long ones keep more
+// of the weights on their way where a compute unit has one workgroup and a long contraction to read (the
+// rules are at the launches).  With at most a few hundred rows these GEMMs are far from
 // HBM-bound (the weights are read once); what limits them is the number of operand loads per
 // MFMA, so operands are read straight from global memory (L2-resident) in MFMA layout and
 // shared between the blocks of a tile:
@@ -56,13 +58,12 @@ template <int GC, int CB> struct BFrag<true, GC, CB> { float4 v[GC][CB]; };
 // discarded by the caller.  Column blocks: with C contiguous (OUT_PROJ) block j is columns
 // n0 + j*T + i; with N contiguous block j is columns n0 + CB*i + j, i = 0..T-1, so that a lane's
 // CB weights of one contraction index are adjacent in memory and arrive in one load.
-template <bool OUT_PROJ, int T, int RB, int CB, typename ACC = float>
+template <bool OUT_PROJ, int T, int RB, int CB, typename ACC = float, int GC = CB == 4 ? 2 : 4>      // GC: chunks of contraction indices fetched together
 __device__ __forceinline__ void gemm_tile(const float* __restrict__ in, const float* __restrict__ P,
                                           int rows, int d, int h, int kv, int row0, int n0,
                                           ACC (*red)[RB * T * CB * T]) {
   static_assert(sizeof(ACC) == 4 || T == 16, "float64 accumulation uses the 16x16x4 blocks");
   constexpr int TN = CB * T;
-  constexpr int GC = (CB == 4) ? 2 : 4;        // chunks of contraction indices fetched together
   constexpr int CH = 256 / T;                  // contraction indices per chunk (4 per lane group)
   constexpr int NACC = T * T / 64;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -195,7 +196,7 @@ __device__ __forceinline__ float sum_partials(const ACC* red0, int e, int stride
 // T = 16: 16x16 MFMA blocks (v_mfma_f32_16x16x4_f32, chunks of 16 contraction indices), the
 // ones launched; T = 32: 32x32 blocks (v_mfma_f32_32x32x2_f32, chunks of 8).  A workgroup owns
 // an (RB*T) x (CB*T) output tile.  Lane (i, kk): i = lane % T, kk = lane / T.
-template <bool OUT_PROJ, int T, int RB, int CB, typename ACC = float>
+template <bool OUT_PROJ, int T, int RB, int CB, typename ACC = float, int GC = CB == 4 ? 2 : 4>
 __global__ __launch_bounds__(NWAVES * 64)
 void project_mfma_kernel(const float* __restrict__ in, const float* __restrict__ P, float* out,
                          int rows, int d, int h, int kv, int epilogue) {
@@ -203,7 +204,7 @@ void project_mfma_kernel(const float* __restrict__ in, const float* __restrict__
   __shared__ ACC red[NWAVES][TM * TN];
   const int N = OUT_PROJ ? d : h * kv;
   const int row0 = blockIdx.y * TM, n0 = (!OUT_PROJ && CB == 1 ? column_tile(blockIdx.x, gridDim.x) : (int)blockIdx.x) * TN;
-  gemm_tile<OUT_PROJ, T, RB, CB, ACC>(in, P, rows, d, h, kv, row0, n0, red);
+  gemm_tile<OUT_PROJ, T, RB, CB, ACC, GC>(in, P, rows, d, h, kv, row0, n0, red);
   for (int e = threadIdx.x; e < TM * TN; e += NWAVES * 64) {
     const int r = e / TN, c = e % TN;
     if (row0 + r < rows && n0 + c < N) {
@@ -231,8 +232,9 @@ template <> __device__ __forceinline__ uint16_t cache_value<uint16_t>(float x) {
 // rows per sequence, and lens_out receives it clamped to [0, mem_rows] (mem_rows if not given).
 // append: the mem_rows rows of a sequence go behind the lens_in[] rows it has; one that cannot hold them all
 // keeps its cache and its length.
-template <int T, int RB, int CB, typename CT>
-__global__ __launch_bounds__(NWAVES * 64)
+// SMALL: chunks by one or two instead of two or four, in registers for two workgroups per compute unit.
+template <int T, int RB, int CB, bool SMALL, typename CT>
+__global__ __launch_bounds__(NWAVES * 64, SMALL ? 4 : 2)
 void project_qkv_append_kernel(const float* __restrict__ x, const float* __restrict__ P_q,
                                const float* __restrict__ P_k, const float* __restrict__ P_v,
                                float* __restrict__ q, CT* __restrict__ K, CT* __restrict__ V,
@@ -240,6 +242,7 @@ void project_qkv_append_kernel(const float* __restrict__ x, const float* __restr
                                int rows, int d, int h, int h_kv, int cap, int k, int v, int nq_tiles, int kv_tiles, int kv_blocks, int kv_narrow,
                                int mem_rows, int append) {
   constexpr int TM = RB * T, TN = CB * T;
+  constexpr int GC = SMALL ? (CB == 1 ? 2 : 1) : CB == 4 ? 2 : 4, GC1 = SMALL ? 2 : 4;      // chunks at a time; of a single block of columns
   __shared__ __align__(16) double red_raw[NWAVES * T * TN];       // = RB <= 2 float32 row blocks
   static_assert(RB <= 2, "a q tile's float32 partial tiles must fit the float64 buffer");
   const int nq = h * k, nk = h_kv * k;
@@ -257,7 +260,7 @@ void project_qkv_append_kernel(const float* __restrict__ x, const float* __restr
   if (column < first_kv) {             // a tile of q
     const int n0 = (CB == 1 ? column_tile(column, nq_tiles) : column) * TN;
     float (*red)[TM * TN] = reinterpret_cast<float (*)[TM * TN]>(red_raw);
-    gemm_tile<false, T, RB, CB>(x, P_q, rows, d, h, k, row0, n0, red);
+    gemm_tile<false, T, RB, CB, float, GC>(x, P_q, rows, d, h, k, row0, n0, red);
     for (int e = threadIdx.x; e < TM * TN; e += NWAVES * 64) {
       const int r = e / TN, c = e % TN;
       if (row0 + r < rows) q[(size_t)(row0 + r) * nq + n0 + c] = sum_partials(&red[0][0], e, TM * TN);
@@ -278,8 +281,8 @@ void project_qkv_append_kernel(const float* __restrict__ x, const float* __restr
   const float* P = which == 1 ? P_k : P_v;
   for (int rb = 0; rb < RB && row0 + rb * T < rows; ++rb) {
     if (rb) __syncthreads();           // the previous row block's sums have been read
-    if (kv_narrow) gemm_tile<false, T, 1, 1, double>(x, P, rows, d, h_kv, kv, row0 + rb * T, n0, reinterpret_cast<double (*)[T * T]>(red_raw));
-    else gemm_tile<false, T, 1, CB, double>(x, P, rows, d, h_kv, kv, row0 + rb * T, n0, reinterpret_cast<double (*)[T * TN]>(red_raw));
+    if (kv_narrow) gemm_tile<false, T, 1, 1, double, GC1>(x, P, rows, d, h_kv, kv, row0 + rb * T, n0, reinterpret_cast<double (*)[T * T]>(red_raw));
+    else gemm_tile<false, T, 1, CB, double, GC>(x, P, rows, d, h_kv, kv, row0 + rb * T, n0, reinterpret_cast<double (*)[T * TN]>(red_raw));
     for (int e = threadIdx.x; e < T * width; e += NWAVES * 64) {
       const int row = row0 + rb * T + e / width, n = n0 + e % width;
       if (row >= rows) continue;
@@ -336,6 +339,9 @@ static Tile pick_tile(long long ncols, int rows, int colmult) {
   return (colmult && (colmult % 16)) ? Tile{0, 0} : Tile{1, 1};
 }
 
+// Chunks at a time (`few`: two, else one).  us, four (two with CB = 4) / two / one: 128 x 1024 (c contiguous) x 1024: 8.5 / 7.8 / 7.5; 1 row x 1024 x
+// 32768: 33.3 / 33.3 / 28.4; 128 x 1024 x 1024: 7.1 / 6.9 / 6.3; tiles of one block of columns: 64 x 1024 x 1024 5.3 / 5.1 / 5.6, 8 x 1024 (c) x
+// 1024 5.1 / 4.9 / 5.0; few tiles and a long contraction: 1 x 4096 x 1024 12.2 / 11.5 / 13.2, 1 x 2048 (c) x 2048 7.4 / 7.5 / 8.5.
 #define MQA_TILES(X) X(2, 4) X(1, 4) X(2, 2) X(1, 2) X(2, 1) X(1, 1)
 
 hipError_t launch_project(int mode, const float* in, const float* P, float* out,
@@ -356,8 +362,12 @@ hipError_t launch_project(int mode, const float* in, const float* P, float* out,
 #define MQA_PROJ(RB_, CB_)                                                                                           \
   if (!launched && t.RB == RB_ && t.CB == CB_) {                                                                     \
     const dim3 grid((N + CB_ * 16 - 1) / (CB_ * 16), (rows + RB_ * 16 - 1) / (RB_ * 16));                            \
-    if (outp) hipLaunchKernelGGL((project_mfma_kernel<true, 16, RB_, CB_>), grid, block, 0, st, in, P, out, rows, d, h, kv, epilogue); \
-    else if (!f64) hipLaunchKernelGGL((project_mfma_kernel<false, 16, RB_, CB_>), grid, block, 0, st, in, P, out, rows, d, h, kv, epilogue); \
+    const int C = outp ? h * kv : d;                                                                                 \
+    const bool few = CB_ == 1 || (C > 1536 && (long long)grid.x * grid.y <= 256);                                    \
+    if (outp && few) hipLaunchKernelGGL((project_mfma_kernel<true, 16, RB_, CB_, float, 2>), grid, block, 0, st, in, P, out, rows, d, h, kv, epilogue); \
+    else if (outp) hipLaunchKernelGGL((project_mfma_kernel<true, 16, RB_, CB_, float, 1>), grid, block, 0, st, in, P, out, rows, d, h, kv, epilogue); \
+    else if (!f64 && few) hipLaunchKernelGGL((project_mfma_kernel<false, 16, RB_, CB_, float, 2>), grid, block, 0, st, in, P, out, rows, d, h, kv, epilogue); \
+    else if (!f64) hipLaunchKernelGGL((project_mfma_kernel<false, 16, RB_, CB_, float, 1>), grid, block, 0, st, in, P, out, rows, d, h, kv, epilogue); \
     else if constexpr (RB_ * CB_ <= 4)                                                                               \
       hipLaunchKernelGGL((project_mfma_kernel<false, 16, RB_, CB_, double>), grid, block, 0, st, in, P, out, rows, d, h, kv, epilogue); \
     launched = true;                                                                                                 \
@@ -398,6 +408,10 @@ hipError_t launch_project_qkv_append(const float* x, const float* P_q, const flo
   const int kv_narrow = (rows <= 512 && 2 * (ntot - nq) <= nq) ? 1 : 0;
   // The float64 tiles take the longest, so in a launch of more than one round (256 workgroups, one per compute unit) they go
   // first and q's short ones fill the end (multi-head, b=128: 27.2 -> 23.3 us, b=256: 39.3 -> 35.5; multi-query, b=512: 31.2 -> 27.6).
+  // Short groups in registers for two workgroups per compute unit (`small`) where there is more than one round of workgroups, or only
+  // float64 tiles of one block of columns: us, before / so: multi-head b=128 22.2 / 19.3, b=256 34.9 / 29.6, d=1600, h=12, b=100 38.4 / 36.0;
+  // multi-query b=128 9.9 / 8.1 (q and K / V tiles in one round).  A single round of wide float64 tiles keeps the longer ones (b=64 14.1 / 14.8; b=1000
+  // without q 33.6 / 35.2), and so does little more than one of a long contraction, which memory bounds (d=2048, h=16, b=40: 31.4 / 34.1).
   const dim3 block(NWAVES * 64);
   bool launched = false;
 #define MQA_QKV(RB_, CB_)                                                                                            \
@@ -407,10 +421,17 @@ hipError_t launch_project_qkv_append(const float* x, const float* P_q, const flo
     const long long row_tiles = (rows + RB_ * 16 - 1) / (RB_ * 16), blocks = (nq_tiles + kv_tiles) * row_tiles;      \
     const int kv_blocks = nq_tiles && blocks > 256 && blocks < (1 << 20) ? (int)(kv_tiles * row_tiles) : 0;          \
     const dim3 grid = kv_blocks ? dim3((unsigned)blocks) : dim3(nq_tiles + kv_tiles, (unsigned)row_tiles);           \
-    if (is_bf16) hipLaunchKernelGGL((project_qkv_append_kernel<16, RB_, CB_, uint16_t>), grid, block, 0, st, x, P_q, P_k, P_v, q, \
-                                    (uint16_t*)K, (uint16_t*)V, lens_in, lens_out, rows, d, h, h_kv, cap, k, v, nq_tiles, kv_tiles, kv_blocks, kv_narrow, mem_rows, append); \
-    else hipLaunchKernelGGL((project_qkv_append_kernel<16, RB_, CB_, float>), grid, block, 0, st, x, P_q, P_k, P_v, q, \
-                            (float*)K, (float*)V, lens_in, lens_out, rows, d, h, h_kv, cap, k, v, nq_tiles, kv_tiles, kv_blocks, kv_narrow, mem_rows, append);  \
+    const bool small = RB_ == 1 && !q_done && (CB_ == 1 || kv_narrow || blocks > (d <= 1536 ? 256 : 384));          \
+    auto go = [&](auto kern, auto* Kp, auto* Vp) {                                                                   \
+      hipLaunchKernelGGL(kern, grid, block, 0, st, x, P_q, P_k, P_v, q, Kp, Vp, lens_in, lens_out, rows, d, h, h_kv, cap, k, v, nq_tiles, kv_tiles, kv_blocks, \
+                         kv_narrow, mem_rows, append);                                                               \
+    };                                                                                                               \
+    uint16_t *Kh = (uint16_t*)K, *Vh = (uint16_t*)V;                                                                 \
+    float *Kf = (float*)K, *Vf = (float*)V;                                                                          \
+    if (small && is_bf16) go(project_qkv_append_kernel<16, RB_, CB_, RB_ == 1, uint16_t>, Kh, Vh);                   \
+    else if (small) go(project_qkv_append_kernel<16, RB_, CB_, RB_ == 1, float>, Kf, Vf);                            \
+    else if (is_bf16) go(project_qkv_append_kernel<16, RB_, CB_, false, uint16_t>, Kh, Vh);                          \
+    else go(project_qkv_append_kernel<16, RB_, CB_, false, float>, Kf, Vf);                                          \
     launched = true;                                                                                                 \
   }
   MQA_TILES(MQA_QKV)
