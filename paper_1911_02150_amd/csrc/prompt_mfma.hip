@@ -11,7 +11,8 @@
 //     the positions of registers 8 t .. 8 t + 7, so the weights are B operands as they are, and V^T is stored in
 //     that order: 16 bytes = positions 16 t + 4 g + 0..3 and 16 t + 8 + 4 g + 0..3 of one column.
 //   * q and the weights are split into bf16 hi + lo terms (two products each), as in decode_mfma.hip.
-//   * Two workgroups share a compute unit; the longest rows are started first.
+//   * Two workgroups share a compute unit; the longest rows are started first.  Where there are not two for each, a workgroup is
+//     two teams of four waves over the same rows, every second tile each, whose states are merged at the end.
 // Measured (us; before: 32 rows per wave in decode_mfma.hip, every wave loading and transposing for itself; on one box): b=8,
 // n=4096, h=8: 757 -> 582 (472 TFLOP/s of causal flops, four bf16 products each: 0.94 PFLOP/s); b=32, n=1024: 241 -> 192; b=128,
 // n=128: 44.5 -> 36.8; one sequence of 4096: 168 -> 155; multi-head b=3, n=1000, h=16: 84 -> 63.  A tile's two
@@ -79,10 +80,13 @@ __device__ __forceinline__ void plain_row(const DecodeParams& p, int seq, int ro
   *reinterpret_cast<float2*>(p.o + ((size_t)seq * p.G + row) * 128 + 2 * lane) = make_float2(a * inv, b * inv);
 }
 
-__global__ __launch_bounds__(256, 2)
+template <int TEAMS>
+__global__ __launch_bounds__(256 * TEAMS, 2)
 void prompt_kernel(DecodeParams p) {
-  extern __shared__ __align__(16) unsigned char smem[];      // two buffers; at the end the waves' outputs
-  const int tid = threadIdx.x, lane = tid & 63;
+  extern __shared__ __align__(16) unsigned char smem_all[];  // per team: two buffers; at the end the waves' outputs
+  const int team = TEAMS > 1 ? __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 8) : 0;
+  unsigned char* const smem = smem_all + team * (2 * kBuffer);
+  const int tid = threadIdx.x & 255, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int i32 = lane & 31, g = lane >> 5;
 
@@ -105,8 +109,8 @@ void prompt_kernel(DecodeParams p) {
   const int lim = limit(row0 + i32), lim_min = limit(row0), lim_max = limit(row0 + 31);
   const int end = limit(row_block * 128 + 127);              // of the workgroup
   const int lim_first = limit(row_block * 128);              // its first row's
-  const int ntiles = (end + kTilePos - 1) / kTilePos;
-  int* const any_odd = reinterpret_cast<int*>(smem + 2 * kBuffer);
+  const int ntiles = (end + kTilePos - 1) / kTilePos, turns = (ntiles + TEAMS - 1) / TEAMS;      // team e: the tiles e, e + TEAMS, ...
+  int* const any_odd = reinterpret_cast<int*>(smem_all + TEAMS * 2 * kBuffer);
   int odd = 0;                                               // V holds something not finite that not all rows see
 
   // ---- staging: K chunk x = tid + 256 j (row x / 16, 16-byte chunk x % 16), kept at chunk ^ (row & 15); V rows 4 quad .. + 3,
@@ -121,8 +125,8 @@ void prompt_kernel(DecodeParams p) {
 #pragma unroll
     for (int j = 0; j < 4; ++j) vst[j] = __builtin_amdgcn_raw_buffer_load_b128(Vbuf, at + (uint32_t)((4 * quad + j) * kRowBytes + cg * 16), 0, 0);
   };
-  auto store_tile = [&](int t) {
-    unsigned char* kb = smem + (t & 1) * kBuffer;
+  auto store_tile = [&](int t, int buffer) {
+    unsigned char* kb = smem + buffer * kBuffer;
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       const int x = tid + 256 * j, row = x >> 4;
@@ -150,8 +154,8 @@ void prompt_kernel(DecodeParams p) {
       }
   };
 
-  load_tile(0);
-  if (tid == 0) *any_odd = 0;
+  load_tile(team);
+  if (threadIdx.x == 0) *any_odd = 0;
   // ---- q as B operands: lane (i, g) holds elements 16 s + 8 g .. + 7 of row i
   u32x4 qh[8], ql[8];
   {
@@ -178,8 +182,8 @@ void prompt_kernel(DecodeParams p) {
 
   // logits of a tile's two blocks of 32 positions
   floatx16 sc[2];
-  auto logits = [&](int t) {
-    const unsigned char* kb = smem + (t & 1) * kBuffer + i32 * kRowBytes;
+  auto logits = [&](int buffer) {
+    const unsigned char* kb = smem + buffer * kBuffer + i32 * kRowBytes;
 #pragma unroll
     for (int u = 0; u < 2; ++u)
 #pragma unroll
@@ -196,9 +200,9 @@ void prompt_kernel(DecodeParams p) {
     }
   };
   // online softmax (lazy rescaling, see decode_mfma.hip) and weighted sum
-  auto weigh = [&](int t) {
+  auto weigh = [&](int t, int buffer) {
     const int p0 = t * kTilePos;
-    const unsigned char* vb = smem + (t & 1) * kBuffer + kKBytes;
+    const unsigned char* vb = smem + buffer * kBuffer + kKBytes;
     if (p0 + kTilePos > lim_min) {
 #pragma unroll
       for (int u = 0; u < 2; ++u)
@@ -250,62 +254,98 @@ void prompt_kernel(DecodeParams p) {
   };
 
   if (ntiles > 0) {
-    store_tile(0);
-    load_tile(1);
+    store_tile(team, 0);
+    load_tile(team + TEAMS);
   }
   __syncthreads();
-  for (int t = 0; t < ntiles; ++t) {
-    // (buffer t + 1 was last read in round t - 1, which the barrier at its end closed)
-    const bool sees = t * kTilePos < lim_max;                // (the same for the whole wave)
-    if (t + 1 < ntiles) {
-      store_tile(t + 1);
-      load_tile(t + 2);
+  for (int u = 0; u < turns; ++u) {
+    // (buffer u + 1 was last read in round u - 1, which the barrier at its end closed)
+    const int t = u * TEAMS + team;
+    const bool sees = t * kTilePos < lim_max;                // (the same for the whole wave; past the last tile: none)
+    if (u + 1 < turns) {
+      store_tile(t + TEAMS, (u + 1) & 1);
+      load_tile(t + 2 * TEAMS);
     }
     if (odd) *any_odd = 1;
-    if (sees) { logits(t); weigh(t); }
+    if (sees) { logits(u & 1); weigh(t, u & 1); }
     __syncthreads();
   }
 
   if (__builtin_expect(*any_odd, 0)) {
-    for (int row = row0; row < min(row0 + 32, G); ++row) plain_row(p, seq, row, limit(row), lane);
+    constexpr int ROWS = 32 / TEAMS;
+    for (int row = row0 + team * ROWS; row < min(row0 + (team + 1) * ROWS, G); ++row) plain_row(p, seq, row, limit(row), lane);
     return;
+  }
+  if constexpr (TEAMS > 1) {
+    // the second team's states meet the first's in LDS: sums in its own buffers, maxima and sums of weights where the first's wave
+    // will put its rows (its own reads come before its writes)
+    float* const at = reinterpret_cast<float*>(smem_all + 2 * kBuffer) + wave * (64 * 64) + lane;
+    float* const ml = reinterpret_cast<float*>(smem_all) + wave * (32 * 128) + lane;
+    if (team == 1) {
+#pragma unroll
+      for (int cb = 0; cb < 4; ++cb)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) at[(cb * 16 + e) * 64] = acc[cb][e];
+      ml[0] = m_run;
+      ml[64] = l_run;
+    }
+    __syncthreads();
+    if (team == 0) {
+      const float m = ml[0], l = ml[64], top = fmaxf(m_run, m), ref = top == -INFINITY ? 0.f : top;
+      const float mine = __builtin_amdgcn_exp2f(m_run - ref), other = __builtin_amdgcn_exp2f(m - ref);      // (0 for a state that saw nothing)
+      l_run = l_run * mine + l * other;
+#pragma unroll
+      for (int cb = 0; cb < 4; ++cb)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc[cb][e] = acc[cb][e] * mine + at[(cb * 16 + e) * 64] * other;
+    }
   }
 
   // ---- output: through the wave's quarter of LDS, so that rows leave as whole lines.  acc[cb][e] is column 32 cb + 8 (e / 4)
   // + 4 g + e % 4 of row i32
-  const float lsum = l_run + __shfl_xor(l_run, 32);
-  const float inv = lsum > 0.f ? 1.0f / lsum : 0.f;          // (a row with nothing to see: zeros)
-  float4* rows = reinterpret_cast<float4*>(smem + wave * (32 * 512));
+  float4* rows = reinterpret_cast<float4*>(smem_all + wave * (32 * 512));
+  if (team == 0) {
+    const float lsum = l_run + __shfl_xor(l_run, 32);
+    const float inv = lsum > 0.f ? 1.0f / lsum : 0.f;        // (a row with nothing to see: zeros)
 #pragma unroll
-  for (int cb = 0; cb < 4; ++cb)
+    for (int cb = 0; cb < 4; ++cb)
 #pragma unroll
-    for (int q = 0; q < 4; ++q)
-      rows[i32 * 32 + ((8 * cb + 2 * q + g) ^ i32)] =
-          make_float4(acc[cb][4 * q] * inv, acc[cb][4 * q + 1] * inv, acc[cb][4 * q + 2] * inv, acc[cb][4 * q + 3] * inv);
+      for (int q = 0; q < 4; ++q)
+        rows[i32 * 32 + ((8 * cb + 2 * q + g) ^ i32)] =
+            make_float4(acc[cb][4 * q] * inv, acc[cb][4 * q + 1] * inv, acc[cb][4 * q + 2] * inv, acc[cb][4 * q + 3] * inv);
+  }
   __syncthreads();
 #pragma unroll
-  for (int r = 0; r < 32; r += 2) {
-    const int row = r + g;
+  for (int r = 0; r < 32 / TEAMS; r += 2) {
+    const int row = r + g + team * (32 / TEAMS);
     if (row0 + row < G) reinterpret_cast<float4*>(p.o + ((size_t)seq * G + row0 + row) * 128)[i32] = rows[row * 32 + (i32 ^ row)];
   }
 }
 
-}  // namespace
-
-hipError_t launch_prompt(const DecodeParams& p, hipStream_t st) {
-  const long long nblocks = (long long)p.nseq * p.HG;        // HG: blocks of 128 rows
-  if (nblocks > 0x7fffffffll) return hipErrorInvalidValue;
-  constexpr int lds = 2 * kBuffer + 16;
+template <int TEAMS>
+hipError_t launch_teams(const DecodeParams& p, unsigned nblocks, hipStream_t st) {
+  constexpr int lds = TEAMS * 2 * kBuffer + 16;
   static bool done[64] = {};                   // once per device
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) dev = 0;
   if (!done[dev]) {
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(prompt_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(prompt_kernel<TEAMS>), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     if (e != hipSuccess) return e;
     done[dev] = true;
   }
-  hipLaunchKernelGGL(prompt_kernel, dim3((unsigned)nblocks), dim3(256), lds, st, p);
+  hipLaunchKernelGGL(prompt_kernel<TEAMS>, dim3(nblocks), dim3(256 * TEAMS), lds, st, p);
   return hipGetLastError();
+}
+
+}  // namespace
+
+// Two teams where a compute unit has one workgroup at most and the positions are more than two tiles each.  us, one team / two: one sequence of 4096, h=8:
+// 146 / 107, of 1024: 41 / 33; multi-head n=700, prefix 100, b=4, h=5: 36 / 29; h=1, n=2000: 83 / 61; but b=16, n=128, prefix 64: 14.2 / 16.0 (the
+// merge), 256 positions the same.
+hipError_t launch_prompt(const DecodeParams& p, hipStream_t st) {
+  const long long nblocks = (long long)p.nseq * p.HG;        // HG: blocks of 128 rows
+  if (nblocks > 0x7fffffffll) return hipErrorInvalidValue;
+  return nblocks <= 256 && p.cap > 4 * kTilePos ? launch_teams<2>(p, (unsigned)nblocks, st) : launch_teams<1>(p, (unsigned)nblocks, st);
 }
 
 }  // namespace mqa

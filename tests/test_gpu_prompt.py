@@ -119,3 +119,33 @@ def test_prompt_values_that_are_not_finite(m, multi_head, n, h, prefix, at, valu
         want = causal(qj, Kj, Vj, cap)
         assert float((o[:first].double() - want[:first]).abs().max()) < TOL
         assert not torch.isfinite(o[first:]).any()
+
+
+@pytest.mark.parametrize("multi_head", [False, True])
+@pytest.mark.parametrize("n,h,prefix,cap", [
+    (300, 1, 0, 300),      # the first rows see one team's tile only
+    (40, 3, 217, 257),     # five tiles, the last of one position: one team's
+    (40, 3, 280, 320),     # five whole tiles
+    (33, 5, 352, 400),     # six, and one past the length
+    (260, 2, 125, 385),
+])
+def test_prompt_in_two_teams(m, multi_head, n, h, prefix, cap):
+    """Few workgroups and more than 256 positions: every second tile is another team's."""
+    g = torch.Generator(device=DEV)
+    g.manual_seed(n + cap)
+    b, one = 3, (h,) if multi_head else ()
+    q = torch.randn(b, *((h, n) if multi_head else (n, h)), 128, generator=g, device=DEV) * 0.25
+    K = torch.randn(b, *one, cap, 128, generator=g, device=DEV)
+    q += 0.5 * K[0].reshape(-1, 128)[0]       # logits that differ between the teams' tiles
+    K = (K * (1 + torch.arange(cap, device=DEV)[:, None] // 64 % 2)).to(torch.bfloat16)
+    V = torch.randn(b, *one, cap, 128, generator=g, device=DEV).to(torch.bfloat16)
+    lens = [n + prefix, n // 2, 0]
+    for i, L in enumerate(lens):
+        K[i, ..., L:, :], V[i, ..., L:, :] = float("nan"), float("inf")
+    attend = m.mha_prefill_attention if multi_head else m.mqa_prefill_attention
+    got = attend(q, K, V, torch.tensor(lens, dtype=torch.int32, device=DEV))
+    for i, L in enumerate(lens):
+        for j in range(h):
+            o, qj = (got[i, j], q[i, j]) if multi_head else (got[i, :, j], q[i, :, j])
+            Kj, Vj = (K[i, j], V[i, j]) if multi_head else (K[i], V[i])
+            assert float((o.double() - causal(qj, Kj, Vj, L)).abs().max()) < 5 * TOL      # (logits up to 60)
