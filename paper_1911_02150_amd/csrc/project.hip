@@ -223,8 +223,7 @@ template <> __device__ __forceinline__ uint16_t cache_value<uint16_t>(float x) {
 // float64, rounded once to float32 and then to the cache type), and lens_out[i] = lens_in[i] + 1.
 // Column tiles are numbered over q's h*k columns, then K's h_kv*k, then V's h_kv*v (k and v are
 // multiples of the tile width, so a tile belongs to one of them); the launch covers the tiles from
-// tile0 on (tile0 > 0: q was computed by another launch).  A K or V tile is worked off one row
-// block at a time so that its float64 partial tiles fit the same LDS as a q tile's float32 ones.
+// tile0 on (tile0 > 0: q was computed by another launch).
 // A sequence at capacity keeps its cache and its length.
 // mem_rows > 0 is the form for a whole memory (encoder-decoder attention: the memory M of the
 // Section 2.2 listing, projected once): input row r is row r % mem_rows of sequence r / mem_rows
@@ -233,7 +232,7 @@ template <> __device__ __forceinline__ uint16_t cache_value<uint16_t>(float x) {
 // append: the mem_rows rows of a sequence go behind the lens_in[] rows it has; one that cannot hold them all
 // keeps its cache and its length.
 // SMALL: chunks by one or two instead of two or four, in registers for two workgroups per compute unit.
-template <int T, int RB, int CB, bool SMALL, typename CT>
+template <int T, int CB, bool SMALL, typename CT>
 __global__ __launch_bounds__(NWAVES * 64, SMALL ? 4 : 2)
 void project_qkv_append_kernel(const float* __restrict__ x, const float* __restrict__ P_q,
                                const float* __restrict__ P_k, const float* __restrict__ P_v,
@@ -241,14 +240,13 @@ void project_qkv_append_kernel(const float* __restrict__ x, const float* __restr
                                const int32_t* __restrict__ lens_in, int32_t* __restrict__ lens_out,
                                int rows, int d, int h, int h_kv, int cap, int k, int v, int nq_tiles, int kv_tiles, int kv_blocks, int kv_narrow,
                                int mem_rows, int append) {
-  constexpr int TM = RB * T, TN = CB * T;
-  constexpr int GC = SMALL ? (CB == 1 ? 2 : 1) : CB == 4 ? 2 : 4, GC1 = SMALL ? 2 : 4;      // chunks at a time; of a single block of columns
-  __shared__ __align__(16) double red_raw[NWAVES * T * TN];       // = RB <= 2 float32 row blocks
-  static_assert(RB <= 2, "a q tile's float32 partial tiles must fit the float64 buffer");
+  constexpr int TN = CB * T;
+  constexpr int GC = SMALL ? (CB == 1 ? 2 : 1) : 2, GC1 = SMALL ? 2 : 4;      // chunks at a time; of a single block of columns
+  __shared__ __align__(16) double red_raw[NWAVES * T * TN];
   const int nq = h * k, nk = h_kv * k;
   // one row of the grid per row tile, its q tiles first; or (kv_blocks > 0) that many workgroups for the K / V tiles of all
   // row tiles, then all q tiles
-  int column = blockIdx.x, row_tile = blockIdx.y, first_kv = nq_tiles;
+  int column = blockIdx.x, row_tile = blockIdx.z * gridDim.y + blockIdx.y, first_kv = nq_tiles;
   if (kv_blocks) {
     const bool of_q = (int)blockIdx.x >= kv_blocks;
     const int at = blockIdx.x - (of_q ? kv_blocks : 0), columns = of_q ? nq_tiles : kv_tiles;
@@ -256,14 +254,15 @@ void project_qkv_append_kernel(const float* __restrict__ x, const float* __restr
     column = at - row_tile * columns;
     if (!of_q) first_kv = 0;
   }
-  const int row0 = row_tile * TM;
+  if ((long long)row_tile * T >= rows) return;
+  const int row0 = row_tile * T;
   if (column < first_kv) {             // a tile of q
     const int n0 = (CB == 1 ? column_tile(column, nq_tiles) : column) * TN;
-    float (*red)[TM * TN] = reinterpret_cast<float (*)[TM * TN]>(red_raw);
-    gemm_tile<false, T, RB, CB, float, GC>(x, P_q, rows, d, h, k, row0, n0, red);
-    for (int e = threadIdx.x; e < TM * TN; e += NWAVES * 64) {
+    float (*red)[T * TN] = reinterpret_cast<float (*)[T * TN]>(red_raw);
+    gemm_tile<false, T, 1, CB, float, GC>(x, P_q, rows, d, h, k, row0, n0, red);
+    for (int e = threadIdx.x; e < T * TN; e += NWAVES * 64) {
       const int r = e / TN, c = e % TN;
-      if (row0 + r < rows) q[(size_t)(row0 + r) * nq + n0 + c] = sum_partials(&red[0][0], e, TM * TN);
+      if (row0 + r < rows) q[(size_t)(row0 + r) * nq + n0 + c] = sum_partials(&red[0][0], e, T * TN);
     }
     return;
   }
@@ -279,24 +278,21 @@ void project_qkv_append_kernel(const float* __restrict__ x, const float* __restr
   const int kv = which == 2 ? v : k;
   CT* dst = which == 1 ? K : V;
   const float* P = which == 1 ? P_k : P_v;
-  for (int rb = 0; rb < RB && row0 + rb * T < rows; ++rb) {
-    if (rb) __syncthreads();           // the previous row block's sums have been read
-    if (kv_narrow) gemm_tile<false, T, 1, 1, double, GC1>(x, P, rows, d, h_kv, kv, row0 + rb * T, n0, reinterpret_cast<double (*)[T * T]>(red_raw));
-    else gemm_tile<false, T, 1, CB, double, GC>(x, P, rows, d, h_kv, kv, row0 + rb * T, n0, reinterpret_cast<double (*)[T * TN]>(red_raw));
-    for (int e = threadIdx.x; e < T * width; e += NWAVES * 64) {
-      const int row = row0 + rb * T + e / width, n = n0 + e % width;
-      if (row >= rows) continue;
-      const int seq = mem_rows > 0 ? row / mem_rows : row;
-      int L = mem_rows > 0 ? row - seq * mem_rows : lens_in[row];
-      if (append) {
-        const int have = lens_in[seq];
-        L = have < 0 || have > cap - mem_rows ? -1 : L + have;      // (mem_rows <= cap; a sum could wrap)
-      }
-      if (L < 0 || L >= cap) continue;
-      dst[(((size_t)seq * h_kv + n / kv) * cap + L) * kv + (n % kv)] = cache_value<CT>(sum_partials(red_raw, e, T * width));
+  if (kv_narrow) gemm_tile<false, T, 1, 1, double, GC1>(x, P, rows, d, h_kv, kv, row0, n0, reinterpret_cast<double (*)[T * T]>(red_raw));
+  else gemm_tile<false, T, 1, CB, double, GC>(x, P, rows, d, h_kv, kv, row0, n0, reinterpret_cast<double (*)[T * TN]>(red_raw));
+  for (int e = threadIdx.x; e < T * width; e += NWAVES * 64) {
+    const int row = row0 + e / width, n = n0 + e % width;
+    if (row >= rows) continue;
+    const int seq = mem_rows > 0 ? row / mem_rows : row;
+    int L = mem_rows > 0 ? row - seq * mem_rows : lens_in[row];
+    if (append) {
+      const int have = lens_in[seq];
+      L = have < 0 || have > cap - mem_rows ? -1 : L + have;        // (mem_rows <= cap; a sum could wrap)
     }
+    if (L < 0 || L >= cap) continue;
+    dst[(((size_t)seq * h_kv + n / kv) * cap + L) * kv + (n % kv)] = cache_value<CT>(sum_partials(red_raw, e, T * width));
   }
-  if (kvt == 0 && threadIdx.x < TM && row0 + threadIdx.x < rows) {      // the first K tile of each row tile
+  if (kvt == 0 && threadIdx.x < T && row0 + threadIdx.x < rows) {      // the first K tile of each row tile
     const int row = row0 + threadIdx.x;
     if (mem_rows > 0) {
       if (row % mem_rows == 0) {
@@ -318,8 +314,7 @@ void project_qkv_append_kernel(const float* __restrict__ x, const float* __restr
 // accesses, not by the matrix cores) but give fewer workgroups; the widest tile that still gives
 // about 160 workgroups wins at the decode-sized shapes measured (rows = 128, contraction x
 // columns, microseconds 16x16 -> chosen tile): 1024 x 4096: 33.9 -> 17.3 (32x64); 4096 x 1024:
-// 29.5 -> 22.9 (16x32); 1024 x 1024: 9.5 -> 7.8 (16x32); fused q/K/V 1024 x 1280: 12.2 -> 10.3
-// (16x64), multi-head 1024 x 3072: 21.8 -> 17.6 (32x64).  A second row block only pays when it
+// 29.5 -> 22.9 (16x32); 1024 x 1024: 9.5 -> 7.8 (16x32).  A second row block only pays when it
 // holds real rows (rows > 16).  32x32 MFMA blocks (T = 32, which gemm_tile also supports) were
 // slower than these at every such shape (1024 x 4096: 21.4) and are not instantiated.
 struct Tile { int RB, CB; };
@@ -327,16 +322,13 @@ static inline long long tiles_of(const Tile& t, long long ncols, int rows) {
   const long long tm = t.RB * 16, tn = t.CB * 16;
   return ((ncols + tn - 1) / tn) * ((rows + tm - 1) / tm);
 }
-// colmult: the column width (in floats) that a tile must divide (the fused q/K/V launch: tiles
-// must not straddle q / K / V; else 0)
-static Tile pick_tile(long long ncols, int rows, int colmult) {
+static Tile pick_tile(long long ncols, int rows) {
   static const Tile order[] = {{2, 4}, {1, 4}, {2, 2}, {1, 2}, {2, 1}, {1, 1}};
   for (const Tile& t : order) {
     if (t.RB == 2 && rows <= 16) continue;
-    if (colmult && (colmult % (t.CB * 16))) continue;
     if (tiles_of(t, ncols, rows) >= 160) return t;
   }
-  return (colmult && (colmult % 16)) ? Tile{0, 0} : Tile{1, 1};
+  return Tile{1, 1};
 }
 
 // Chunks at a time (`few`: two, else one).  us, four (two with CB = 4) / two / one: 128 x 1024 (c contiguous) x 1024: 8.5 / 7.8 / 7.5; 1 row x 1024 x
@@ -356,7 +348,7 @@ hipError_t launch_project(int mode, const float* in, const float* P, float* out,
   }
   const int N = outp ? d : h * kv;
   const dim3 block(NWAVES * 64);
-  Tile t = pick_tile(N, rows, 0);
+  Tile t = pick_tile(N, rows);
   if (f64 && t.RB == 2 && t.CB == 4) t = Tile{1, 4};        // float64 partial tiles: at most 1024 elements in 64 KiB of LDS
   bool launched = false;
 #define MQA_PROJ(RB_, CB_)                                                                                           \
@@ -397,44 +389,56 @@ hipError_t launch_project_qkv_append(const float* x, const float* P_q, const flo
   // column tiles must not straddle q / K / V: the tile width divides k and v (both multiples of 16)
   int g = k, r = v;
   while (r) { const int t2 = g % r; g = r; r = t2; }
-  Tile t = pick_tile(q_done ? ntot - nq : ntot, rows, g);
-  // A decode step whose K / V columns outweigh q's: their float64 tiles take one row block at a time, so a second one in
-  // the workgroup only makes it longer (multi-head, d=1024, h=8: b=192: 38.5 -> 33.1 us, 256: 49.6 -> 38.3, 384: 62.5 ->
-  // 57.5, 512: 74.6 -> 73.3; up to 160 rows the tiles are this narrow anyway; d = 512 and 2048, h = 4 and 16 alike; 640
-  // rows on: within 3 % either way)
-  if (t.RB == 2 && t.CB == 4 && rows <= 512 && ntot - nq > nq) t.RB = 1;
   // a decode step's rows and K / V columns that are a small part of the product (multi-query): K / V tiles of
   // 16 columns (b=128, h=8: 14.2 -> 10.4 us; multi-head, where they are two thirds of it: 25.9 -> 31.6 us, so not there)
   const int kv_narrow = (rows <= 512 && 2 * (ntot - nq) <= nq) ? 1 : 0;
-  // The float64 tiles take the longest, so in a launch of more than one round (256 workgroups, one per compute unit) they go
-  // first and q's short ones fill the end (multi-head, b=128: 27.2 -> 23.3 us, b=256: 39.3 -> 35.5; multi-query, b=512: 31.2 -> 27.6).
-  // Short groups in registers for two workgroups per compute unit (`small`) where there is more than one round of workgroups, or only
-  // float64 tiles of one block of columns: us, before / so: multi-head b=128 22.2 / 19.3, b=256 34.9 / 29.6, d=1600, h=12, b=100 38.4 / 36.0;
-  // multi-query b=128 9.9 / 8.1 (q and K / V tiles in one round).  A single round of wide float64 tiles keeps the longer ones (b=64 14.1 / 14.8; b=1000
-  // without q 33.6 / 35.2), and so does little more than one of a long contraction, which memory bounds (d=2048, h=16, b=40: 31.4 / 34.1).
+  const long long row_tiles = (rows + 15) / 16;
+  const int nq_here = q_done ? 0 : nq;
+  // Tiles of 16 rows (of 32, K and V one block at a time, as there were: us d=1024, h=8, float32 caches, multi-head b=500 68.1 -> 64.6, b=2048 230
+  // -> 202, multi-query b=4096 90.5 -> 85.9, slower nowhere), as wide as leaves the fullest compute unit the least to do: this many us (d = 1024) for
+  // a tile of so many blocks of columns, q's less where it has the unit to itself.  In more than one round of 256 workgroups the float64 tiles of K
+  // and V, which take the longest, go first (multi-head, b=128: 27.2 -> 23.3 us, b=256: 39.3 -> 35.5; multi-query, b=512: 31.2 -> 27.6), and unit 0
+  // gets every 256th.  At 200 sizes (d = 640 to 2048, h = 2 to 16, 1 to 1500 rows) the width taken is at most 8 % behind the best, 11 % at one.  us,
+  // the narrowest of 160 workgroups / this: multi-query b=256 16.5 / 12.0, b=512 26.2 / 22.7, d=2000, h=16, b=200 45.5 / 31.7; multi-head b=64
+  // 13.9 / 11.1, b=128 19.4 / 17.9, d=640, h=5, b=200 17.0 / 15.7; a memory of 256 rows, d=640, h=5, multi-head 17.4 / 13.3, of 300, d=1280,
+  // multi-query 12.6 / 10.3.
+  static const double kv_us[5] = {0, 3.0, 5.7, 0, 10.5}, q_us[5] = {0, 2.6, 3.6, 0, 5.7}, q_alone_us[5] = {0, 2.4, 3.3, 0, 4.5};
+  int width = 0;
+  double least = 1e30;
+  for (int c = 4; c >= 1; c /= 2) {
+    if (g % (16 * c)) continue;
+    const long long kvn = (ntot - nq) / (kv_narrow ? 16 : 16 * c) * row_tiles, qn = nq_here / (16 * c) * row_tiles, blocks = kvn + qn;
+    const double kv_one = kv_us[kv_narrow ? 1 : c], kv_there = kvn ? kv_one : 0., q_there = qn ? q_alone_us[c] : 0.;
+    const double mine = blocks <= 256 ? (kv_there > q_there ? kv_there : q_there)
+                                      : kv_one * (double)((kvn + 255) / 256) + q_us[c] * (double)((blocks + 255) / 256 - (kvn + 255) / 256);
+    if (mine < 0.99 * least) least = mine, width = c;
+  }
   const dim3 block(NWAVES * 64);
   bool launched = false;
-#define MQA_QKV(RB_, CB_)                                                                                            \
-  if (!launched && t.RB == RB_ && t.CB == CB_) {                                                                     \
-    const int nq_tiles = q_done ? 0 : nq / (CB_ * 16);                                                               \
+#define MQA_QKV(CB_)                                                                                                 \
+  if (!launched && width == CB_) {                                                                                   \
+    const int nq_tiles = nq_here / (CB_ * 16);                                                                       \
     const int kv_tiles = (ntot - nq) / (kv_narrow ? 16 : CB_ * 16);                                                  \
-    const long long row_tiles = (rows + RB_ * 16 - 1) / (RB_ * 16), blocks = (nq_tiles + kv_tiles) * row_tiles;      \
+    const long long blocks = (nq_tiles + kv_tiles) * row_tiles;                                                      \
     const int kv_blocks = nq_tiles && blocks > 256 && blocks < (1 << 20) ? (int)(kv_tiles * row_tiles) : 0;          \
-    const dim3 grid = kv_blocks ? dim3((unsigned)blocks) : dim3(nq_tiles + kv_tiles, (unsigned)row_tiles);           \
-    const bool small = RB_ == 1 && !q_done && (CB_ == 1 || kv_narrow || blocks > (d <= 1536 ? 256 : 384));          \
+    const unsigned deep = (unsigned)((row_tiles + 32767) / 32768);         /* (a grid is 65535 deep) */                  \
+    const dim3 grid = kv_blocks ? dim3((unsigned)blocks) : dim3(nq_tiles + kv_tiles, (unsigned)((row_tiles + deep - 1) / deep), deep); \
+    const bool small = CB_ < 4 || kv_narrow || blocks > 256;                                                         \
     auto go = [&](auto kern, auto* Kp, auto* Vp) {                                                                   \
       hipLaunchKernelGGL(kern, grid, block, 0, st, x, P_q, P_k, P_v, q, Kp, Vp, lens_in, lens_out, rows, d, h, h_kv, cap, k, v, nq_tiles, kv_tiles, kv_blocks, \
                          kv_narrow, mem_rows, append);                                                               \
     };                                                                                                               \
     uint16_t *Kh = (uint16_t*)K, *Vh = (uint16_t*)V;                                                                 \
     float *Kf = (float*)K, *Vf = (float*)V;                                                                          \
-    if (small && is_bf16) go(project_qkv_append_kernel<16, RB_, CB_, RB_ == 1, uint16_t>, Kh, Vh);                   \
-    else if (small) go(project_qkv_append_kernel<16, RB_, CB_, RB_ == 1, float>, Kf, Vf);                            \
-    else if (is_bf16) go(project_qkv_append_kernel<16, RB_, CB_, false, uint16_t>, Kh, Vh);                          \
-    else go(project_qkv_append_kernel<16, RB_, CB_, false, float>, Kf, Vf);                                          \
+    if (small && is_bf16) go(project_qkv_append_kernel<16, CB_, true, uint16_t>, Kh, Vh);                            \
+    else if (small) go(project_qkv_append_kernel<16, CB_, true, float>, Kf, Vf);                                     \
+    else if (is_bf16) go(project_qkv_append_kernel<16, CB_, CB_ < 4, uint16_t>, Kh, Vh);                             \
+    else go(project_qkv_append_kernel<16, CB_, CB_ < 4, float>, Kf, Vf);                                             \
     launched = true;                                                                                                 \
   }
-  MQA_TILES(MQA_QKV)
+  // Short groups in registers for two workgroups per compute unit (`small`), us, before / so: multi-head b=256 35.1 / 30.2, multi-query b=128 9.6 / 8.0,
+  // two blocks of columns (multi-head b=128) 23.8 / 18.0.  A single round of wide float64 tiles keeps the longer ones (multi-head b=64 13.9 / 15.2).
+  MQA_QKV(4) MQA_QKV(2) MQA_QKV(1)
 #undef MQA_QKV
   if (!launched) return hipErrorInvalidValue;
   return hipGetLastError();
