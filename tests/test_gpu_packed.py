@@ -195,3 +195,26 @@ def test_stack_follows_its_weights(m):
     stack.layers[0]["W1"][:20, 5] = 1e-9
     check()
     assert (0, "W1") in stack._unheld and stack._plan(b * n)[0][0][1:] == (0, 0, 0)
+
+
+def test_two_layers_follow_their_weights(m):
+    """The same of the layer whose every row counts: all rows of a prompt's last layer but the last positions' stop at its caches."""
+    from paper_1911_02150_amd.decoder_stack import DecoderStack
+    b, n, d, ff, vocab = 20, 40, 512, 2048, 400
+    w = _weights(4, 2, d, 2, ff, vocab, n)
+    prompts = torch.from_numpy(np.random.default_rng(3).integers(0, vocab, (b, n)).astype(np.int32)).to(DEV)
+    stack = DecoderStack(w, b, n, False, DEV)
+    assert all(stack._plan(b * n)[0][0][1:3]), "this size is to run packed"
+    for name in ("P_q", "W1", "W2"):
+        if name == "W1":
+            stack.layers[0][name].mul_(-1.5)
+        else:
+            stack.layers[0][name] = stack.layers[0][name].clone().neg_()
+        now = dict(E=w["E"], pos=w["pos"], layers=[{k: v.cpu().numpy() for k, v in layer.items()} for layer in stack.layers])
+        plain = DecoderStack(now, b, n, False, DEV)
+        plain._packs = {}
+        for lens in stack.lens:
+            lens.zero_()
+        got, ref = stack.prefill(prompts), plain.prefill(prompts)
+        assert float((got - ref).abs().max()) <= 2e-3 * float(ref.abs().max())
+        assert float((stack.K[1] - plain.K[1]).abs().max()) <= 0.05 * float(plain.K[1].abs().max())      # (bf16 near-ties of the layer before)

@@ -201,3 +201,36 @@ def test_stack_prefill_advances_the_lengths_in_place(m):
     for t in held:
         t.zero_()
     assert torch.equal(stack.prefill(prompts), logits) and all(t.tolist() == [n] * b for t in held)
+
+
+# a single layer, a single position, a batch whose steps run other kernels than its prompts, positions in ranges, more heads than a workgroup's rows
+@pytest.mark.parametrize("layers,b,n,d,h", [(1, 3, 7, 64, 2), (2, 3, 1, 64, 2), (1, 5, 1, 96, 2), (3, 70, 9, 128, 2), (2, 1, 700, 48, 4), (1, 300, 2, 96, 1), (2, 2, 5, 64, 40)])
+def test_stack_prefill_ends_at_the_last_positions(m, layers, b, n, d, h):
+    """What a prompt returns and leaves is what its tokens one by one do, eagerly and from a graph."""
+    from paper_1911_02150_amd.decoder_stack import DecoderStack
+    g = mi.rng(3300, layers * 100 + n)
+    draw = lambda *s: g.standard_normal(s, dtype=np.float32) * np.float32(0.1)
+    k, ff, vocab = 128, 160, 72
+    w = dict(E=draw(vocab, d), pos=draw(n + 1, d), layers=[dict(P_q=draw(h, d, k), P_k=draw(d, k), P_v=draw(d, k), P_o=draw(h, d, k), W1=draw(d, ff),
+                                                                W2=draw(ff, d)) for _ in range(layers)])
+    prompts = torch.from_numpy(g.integers(0, vocab, size=(b, n)).astype(np.int32)).to(DEV)
+    a, inc = (DecoderStack(w, b, n + 1, False, device=DEV) for _ in range(2))
+    got = a.prefill(prompts)
+    for t in range(n):
+        ref = inc.step(prompts[:, t].clone(), t)
+    # (as of a prompt and steps above: float32 sums in another order, and what bf16 near-ties make of them)
+    close = lambda x, y: float((x.float() - y.float()).abs().max()) <= (2e-3 if x.dtype == torch.float32 else 2.0 ** -7) * float(y.float().abs().max())
+    assert close(got, ref) and a.lens[-1].tolist() == [n] * b
+    for l in range(layers):
+        assert close(a.K[l], inc.K[l]) and close(a.V[l], inc.V[l])
+    for lens in a.lens:
+        lens.zero_()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        out = a.prefill(prompts)
+    for _ in range(3):
+        for l in range(layers):
+            a.lens[l].zero_(), a.K[l].zero_(), a.V[l].zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert close(out, ref) and all(close(a.V[l], inc.V[l]) for l in range(layers)) and a.lens[0].tolist() == [n] * b
