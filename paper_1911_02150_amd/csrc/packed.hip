@@ -38,17 +38,18 @@ template <int N> __device__ __forceinline__ void wait_and_meet() {      // at mo
   asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" :: "n"(N) : "memory");
 }
 
-// eight values -> the octet of a line's planes, `plane` bytes apart
-__device__ __forceinline__ void store_octet(unsigned char* at, size_t plane, const float (&v)[8]) {
-  u32x4 hi, lo;
+// Eight values -> the 16 bytes of a line's planes, `plane` bytes apart.
+__device__ __forceinline__ void store_packed8(unsigned char* at, size_t plane, const float (&v)[8]) {
+  uint32_t hi[4], lo[4];
 #pragma unroll
   for (int p = 0; p < 4; ++p) {
     const Split2 s = split2(v[2 * p], v[2 * p + 1]);
     hi[p] = s.hi; lo[p] = s.lo;
   }
-  *reinterpret_cast<u32x4*>(at) = hi;
-  *reinterpret_cast<u32x4*>(at + plane) = lo;
+  *reinterpret_cast<uint4*>(at) = make_uint4(hi[0], hi[1], hi[2], hi[3]);
+  *reinterpret_cast<uint4*>(at + plane) = make_uint4(lo[0], lo[1], lo[2], lo[3]);
 }
+
 struct PackedProduct {
   const unsigned char* x;      // packed [C / 32][2][rows][64]
   const unsigned char* w;      // packed [C / 32][2][N][64]
@@ -60,22 +61,33 @@ struct PackedProduct {
   int tiles_m, tiles_n, per;   // per: blocks of a part of the contraction
 };
 
-// Eight sums of neighbouring columns of one row
-__device__ __forceinline__ void finish8(const PackedProduct& p, int row, int n, int part, float (&v)[8]) {
-  if (p.epilogue == 3) {       // (the columns keep the scale of their weights)
+// Eight sums of neighbouring columns of one row; ADD: to what is there, read beforehand
+__device__ __forceinline__ float* place8(const PackedProduct& p, int row, int n, int part) {
+  return static_cast<float*>(p.out) + ((size_t)part * p.rows + row) * p.N + n;
+}
+template <bool ADD>
+__device__ __forceinline__ void finish8(const PackedProduct& p, int row, int n, int part, float (&v)[8], floatx4 was0, floatx4 was1) {
+  if (!ADD && p.epilogue == 3) {       // (the columns keep the scale of their weights)
 #pragma unroll
     for (int e = 0; e < 8; ++e) v[e] = fmaxf(v[e], 0.f) * p.scale;
-    store_octet(static_cast<unsigned char*>(p.out) + ((size_t)(n >> 5) * 2 * p.rows + row) * 64 + (n >> 3 & 3) * 16, (size_t)p.rows * 64, v);
+    store_packed8(static_cast<unsigned char*>(p.out) + ((size_t)(n >> 5) * 2 * p.rows + row) * 64 + (n >> 3 & 3) * 16, (size_t)p.rows * 64, v);
     return;
   }
   const floatx4 c0 = *reinterpret_cast<const floatx4*>(p.col_scale + n), c1 = *reinterpret_cast<const floatx4*>(p.col_scale + n + 4);
-  float* dst = static_cast<float*>(p.out) + ((size_t)part * p.rows + row) * p.N + n;
   floatx4 y0, y1;
 #pragma unroll
   for (int e = 0; e < 4; ++e) {
-    y0[e] = apply_epilogue(v[e] * c0[e] * p.scale, dst + e, p.epilogue);
-    y1[e] = apply_epilogue(v[4 + e] * c1[e] * p.scale, dst + 4 + e, p.epilogue);
+    y0[e] = v[e] * c0[e] * p.scale;
+    y1[e] = v[4 + e] * c1[e] * p.scale;
+    if (ADD) {
+      y0[e] += was0[e];
+      y1[e] += was1[e];
+    } else if (p.epilogue == 1) {
+      y0[e] = fmaxf(y0[e], 0.f);
+      y1[e] = fmaxf(y1[e], 0.f);
+    }
   }
+  float* dst = place8(p, row, n, part);
   *reinterpret_cast<floatx4*>(dst) = y0;
   *reinterpret_cast<floatx4*>(dst + 4) = y1;
 }
@@ -197,33 +209,58 @@ void packed_tile_kernel(PackedProduct p) {
       for (int b = 0; b < RM; ++b) mine[(a * RM + b) * 64] = acc[a][b];
     __syncthreads();
   }
+  auto finish = [&](auto add) {
+    constexpr bool ADD = decltype(add)::value;
+    // What a sum is added to: the loads of eight blocks in flight together.  One by one, each behind the last one's stores: 16384 x 4096 x 1024
+    // in a stack 324 us, so 297; x 1024 x 1024 131, so 98 (without the adding 85)
+    constexpr int BATCH = ADD && SHARE > 8 ? 8 : SHARE;
 #pragma unroll
-  for (int k = 0; k < SHARE; ++k) {
-    floatx4 lo, hi;
-    float v[8];
-    const int at = kg * SHARE + k, a = at / RM * 2, b = at % RM;
-    if (PAIRS % KG && at >= PAIRS) break;
-    if constexpr (KG == 1) {
-      lo = acc[k / RM * 2][k % RM];
-      hi = acc[k / RM * 2 + 1][k % RM];
-    } else {
-      lo = hi = floatx4{0.f, 0.f, 0.f, 0.f};
+    for (int k0 = 0; k0 < SHARE; k0 += BATCH) {
+      floatx4 was[ADD ? BATCH : 1][2];
+      auto place = [&](int k, int& row, int& n) {
+        const int at = kg * SHARE + k, a = at / RM * 2, b = at % RM;
+        row = row0 + wm * RM * 16 + b * 16 + i, n = n0 + wn * RN * 16 + a * 16 + 16 * (kk & 1) + 8 * (kk >> 1);
+        return !(PAIRS % KG && at >= PAIRS) && row < p.rows && n < p.N;
+      };
+      int row, n;
+      if constexpr (ADD)
 #pragma unroll
-      for (int q = 0; q < KG; ++q) {
-        const floatx4* from = part + q * (WN * WM * RN * RM * 64) + (a * RM + b) * 64;
-        lo += from[0];
-        hi += from[RM * 64];
+        for (int k = 0; k < BATCH; ++k)
+          if (k0 + k < SHARE && place(k0 + k, row, n)) {
+            const floatx4* from = reinterpret_cast<const floatx4*>(place8(p, row, n, blockIdx.y));
+            was[k][0] = from[0];
+            was[k][1] = from[1];
+          }
+#pragma unroll
+      for (int k = k0; k < k0 + BATCH && k < SHARE; ++k) {
+        floatx4 lo, hi;
+        float v[8];
+        const int at = kg * SHARE + k, a = at / RM * 2, b = at % RM;
+        if (PAIRS % KG && at >= PAIRS) break;
+        if constexpr (KG == 1) {
+          lo = acc[k / RM * 2][k % RM];
+          hi = acc[k / RM * 2 + 1][k % RM];
+        } else {
+          lo = hi = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+          for (int q = 0; q < KG; ++q) {
+            const floatx4* from = part + q * (WN * WM * RN * RM * 64) + (a * RM + b) * 64;
+            lo += from[0];
+            hi += from[RM * 64];
+          }
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          auto s = __builtin_amdgcn_permlane16_swap(__float_as_uint(lo[e]), __float_as_uint(hi[e]), false, false);
+          v[e] = __uint_as_float(s[0]);
+          v[4 + e] = __uint_as_float(s[1]);
+        }
+        if (place(k, row, n)) finish8<ADD>(p, row, n, blockIdx.y, v, was[ADD ? k - k0 : 0][0], was[ADD ? k - k0 : 0][1]);
       }
     }
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      auto s = __builtin_amdgcn_permlane16_swap(__float_as_uint(lo[e]), __float_as_uint(hi[e]), false, false);
-      v[e] = __uint_as_float(s[0]);
-      v[4 + e] = __uint_as_float(s[1]);
-    }
-    const int row = row0 + wm * RM * 16 + b * 16 + i, n = n0 + wn * RN * 16 + a * 16 + 16 * (kk & 1) + 8 * (kk >> 1);
-    if (row < p.rows && n < p.N) finish8(p, row, n, blockIdx.y, v);
-  }
+  };
+  if (p.epilogue == 2) finish(std::true_type{});
+  else finish(std::false_type{});
 }
 
 template <int TN, int TM, int WN, int WM, int KG, int NB, bool LOW>
@@ -292,7 +329,7 @@ void pack_weights_kernel(const float* __restrict__ P, const float* __restrict__ 
         few += v[e] != 0.f && fabsf(v[e]) < kSmall ? 1 : 0;
       }
       if (few) atomicAdd(&tally[j], (uint32_t)few);
-      store_octet(packed + ((size_t)(o >> 2) * 2 * N + n) * 64 + (o & 3) * 16, (size_t)N * 64, v);
+      store_packed8(packed + ((size_t)(o >> 2) * 2 * N + n) * 64 + (o & 3) * 16, (size_t)N * 64, v);
     }
   }
   __syncthreads();
