@@ -220,34 +220,36 @@ void length_order_kernel(const int32_t* lens, int lens_div, int nseq, int cap, i
 }
 
 // Beam search bookkeeping: hypothesis slot r continues hypothesis parent[r], so its cache
-// becomes a copy of that hypothesis' valid rows.  One workgroup per (slot, KV head, 64 KiB piece
-// of the rows); source and destination are different buffers, so slots may be duplicated or
-// dropped freely.  Rows at and beyond the length are not touched.
+// becomes a copy of that hypothesis' valid rows.  One workgroup per (slot, KV head, piece of 256 U
+// 16-byte words of K's rows and as many of V's): what bounds it is the latency of parent, length and
+// words one behind the other.  Source and destination are different buffers, so slots may be
+// duplicated or dropped freely.  Rows at and beyond the length are not touched.
+template <int U>
 __global__ __launch_bounds__(256)
-void reorder_kernel(const uint4* K_src, const uint4* V_src, const int32_t* lens_src, const int32_t* parent,
-                    uint4* K_dst, uint4* V_dst, int32_t* lens_dst, int n, int h_kv, int cap,
-                    int k_row16, int v_row16) {
+void reorder_kernel(const uint4* __restrict__ K_src, const uint4* __restrict__ V_src, const int32_t* __restrict__ lens_src,
+                    const int32_t* __restrict__ parent, uint4* __restrict__ K_dst, uint4* __restrict__ V_dst, int32_t* __restrict__ lens_dst,
+                    int n, int h_kv, int cap, int k_row16, int v_row16) {
   const int r = blockIdx.x / h_kv, j = blockIdx.x % h_kv;
   int par = parent[r];
   par = par < 0 ? 0 : (par >= n ? n - 1 : par);
   int L = lens_src[par];
   L = L < 0 ? 0 : (L > cap ? cap : L);
   if (blockIdx.y == 0 && j == 0 && threadIdx.x == 0) lens_dst[r] = L;
-  const size_t piece = 4096;                       // 16-byte words per workgroup and tensor
-  const size_t from = (size_t)blockIdx.y * piece;
-  {
-    const size_t words = (size_t)L * k_row16;
-    const uint4* src = K_src + ((size_t)par * h_kv + j) * cap * k_row16;
-    uint4* dst = K_dst + ((size_t)r * h_kv + j) * cap * k_row16;
-    const size_t to = min(from + piece, words);
-    for (size_t i = from + threadIdx.x; i < to; i += 256) dst[i] = src[i];
+  const size_t at = (size_t)blockIdx.y * (256 * U) + threadIdx.x, from = ((size_t)par * h_kv + j) * cap, to = ((size_t)r * h_kv + j) * cap;
+  const size_t k_words = (size_t)L * k_row16, v_words = (size_t)L * v_row16;
+  const uint4 *ks = K_src + from * k_row16, *vs = V_src + from * v_row16;
+  uint4 *kd = K_dst + to * k_row16, *vd = V_dst + to * v_row16;
+  if ((size_t)blockIdx.y * (256 * U) >= max(k_words, v_words)) return;
+  uint4 a[U], b[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u) {                    // (past the end: the last word again)
+    a[u] = ks[min(at + 256 * u, k_words - 1)];
+    b[u] = vs[min(at + 256 * u, v_words - 1)];
   }
-  {
-    const size_t words = (size_t)L * v_row16;
-    const uint4* src = V_src + ((size_t)par * h_kv + j) * cap * v_row16;
-    uint4* dst = V_dst + ((size_t)r * h_kv + j) * cap * v_row16;
-    const size_t to = min(from + piece, words);
-    for (size_t i = from + threadIdx.x; i < to; i += 256) dst[i] = src[i];
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    if (at + 256 * u < k_words) kd[at + 256 * u] = a[u];
+    if (at + 256 * u < v_words) vd[at + 256 * u] = b[u];
   }
 }
 
@@ -333,11 +335,21 @@ hipError_t launch_length_order(const int32_t* lens, int lens_div, int nseq, int 
 hipError_t launch_reorder(const void* K_src, const void* V_src, const int32_t* lens_src, const int32_t* parent,
                           void* K_dst, void* V_dst, int32_t* lens_dst, int n, int h_kv, int cap,
                           size_t k_row_bytes, size_t v_row_bytes, hipStream_t st) {
-  const size_t row16 = (k_row_bytes > v_row_bytes ? k_row_bytes : v_row_bytes) / 16;
-  const size_t pieces = ((size_t)cap * row16 + 4095) / 4096;
-  const dim3 grid((unsigned)((size_t)n * h_kv), (unsigned)pieces), block(256);
-  hipLaunchKernelGGL(reorder_kernel, grid, block, 0, st, (const uint4*)K_src, (const uint4*)V_src, lens_src, parent,
-                     (uint4*)K_dst, (uint4*)V_dst, lens_dst, n, h_kv, cap, (int)(k_row_bytes / 16), (int)(v_row_bytes / 16));
+  const size_t words = (size_t)cap * ((k_row_bytes > v_row_bytes ? k_row_bytes : v_row_bytes) / 16), slots = (size_t)n * h_kv;
+  auto go = [&](auto kern, int U) {
+    hipLaunchKernelGGL(kern, dim3((unsigned)slots, (unsigned)((words + 256 * U - 1) / (256 * U))), dim3(256), 0, st, (const uint4*)K_src, (const uint4*)V_src,
+                       lens_src, parent, (uint4*)K_dst, (uint4*)V_dst, lens_dst, n, h_kv, cap, (int)(k_row_bytes / 16), (int)(v_row_bytes / 16));
+  };
+  // One word a thread while that is at most 4096 workgroups (16 to a compute unit), else as many more: a workgroup's words come one latency after
+  // the other, but capacities that are mostly empty should not cost a workgroup each.  us, 16 words a thread (as it was) / so: 64 slots of 128
+  // rows 5.5 / 2.5 (a beam step with its attention 29.8 / 23.4), 320 of 256 rows 14.4 / 13.1, 64 of 8192 rows 105 / 98, of 100 rows of
+  // 8192 4.3 (in single words 20.5), 256 of 600 rows of 1024 23.3 / 23.7.
+  const size_t single = (words + 255) / 256 * slots;
+  if (single <= 4096) go(reorder_kernel<1>, 1);
+  else if (single <= 2 * 4096) go(reorder_kernel<2>, 2);
+  else if (single <= 4 * 4096) go(reorder_kernel<4>, 4);
+  else if (single <= 8 * 4096) go(reorder_kernel<8>, 8);
+  else go(reorder_kernel<16>, 16);
   return hipGetLastError();
 }
 

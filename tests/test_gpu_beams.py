@@ -204,3 +204,24 @@ def test_encoder_decoder_memory_with_beams(m):
     m.mqa_append_kv_rows(K2, V2, kn.view(b, cap, k), vn.view(b, cap, v), l2)
     assert int(l2.min()) == cap and float((K2.float() - K.float()).abs().max()) <= 2.0 ** -6
     assert float((K2 != K).float().mean()) < 1e-2
+
+
+# one, two, four, eight and sixteen words a thread; rows of K and V of different length, a last piece that is not full, empty and full slots
+@pytest.mark.parametrize("n,h,cap,k,v,dtype", [(3, 1, 5, 8, 24, torch.bfloat16), (64, 1, 129, 128, 128, torch.bfloat16), (40, 2, 1001, 64, 128, torch.bfloat16),
+                                               (9, 1, 30011, 128, 64, torch.bfloat16), (5, 3, 24000, 128, 128, torch.bfloat16), (7, 1, 40003, 104, 128, torch.float32)])
+def test_beam_reorder_of_any_size(m, n, h, cap, k, v, dtype):
+    g = torch.Generator(device=DEV)
+    g.manual_seed(cap)
+    shape = (n, h, cap) if h > 1 else (n, cap)
+    K, V = (torch.randn(*shape, w, generator=g, device=DEV).to(dtype) for w in (k, v))
+    lens = torch.randint(0, cap + 1, (n,), generator=g, device=DEV, dtype=torch.int32)
+    lens[0], lens[1] = cap, 0
+    parent = torch.randint(0, n, (n,), generator=g, device=DEV, dtype=torch.int32)
+    parent[0], parent[1] = 1, 0
+    out = [torch.full_like(K, 7.0), torch.full_like(V, 7.0), torch.full_like(lens, -1)]
+    m.mqa_beam_reorder_kv(K, V, lens, parent, *out)
+    assert torch.equal(out[2], lens[parent.long()])
+    for new, old in zip(out, (K, V)):
+        there = torch.arange(cap, device=DEV) < out[2][:, None]
+        there = (there[:, None] if h > 1 else there).unsqueeze(-1)
+        assert torch.equal(new, torch.where(there, old[parent.long()], torch.full_like(old, 7.0)))
