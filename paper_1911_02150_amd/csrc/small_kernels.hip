@@ -14,7 +14,7 @@ namespace {
 // and independent of the lengths, so a batch costs one memory latency; batches are folded
 // into a running (M, L, o) state.  B = 4 covers the usual 2..4 ranges in one batch.
 __device__ __forceinline__ int valid_ranges(const CombineSegment& sg, long long row) {
-  int L = sg.lens[row / sg.rows_per_len];
+  int L = sg.lens[(unsigned)row / (unsigned)sg.rows_per_len];      // (fewer than 2^31 rows)
   L = L < 0 ? 0 : (L > sg.cap ? sg.cap : L);
   return min(sg.S, (L - window_base(L, sg.window) + sg.chunk - 1) / sg.chunk);
 }
@@ -30,8 +30,8 @@ void combine_kernel(CombineParams p) {
   const unsigned wid = ((nb & 7) == 0) ? (bid & 7) * (nb >> 3) + (bid >> 3) : bid;
   const size_t idx = (size_t)wid * 256 + threadIdx.x;
   if (idx >= total) return;
-  const int c4 = (int)(idx % v4);
-  const long long row = (long long)(idx / v4);
+  const long long row = total >> 32 ? (long long)(idx / v4) : (long long)((unsigned)idx / (unsigned)v4);      // (a 64-bit division takes 0.2 us)
+  const int c4 = (int)(idx - (size_t)row * v4);
   const size_t base = (size_t)row * p.PS;
   const int n0 = valid_ranges(p.seg[0], row);
   const int s1 = p.seg[0].S;
