@@ -10,10 +10,11 @@
 // straight into its operand registers (1 KiB at a time, from L2; no two waves of a workgroup need the same), only the
 // rows go through LDS (64 indices to a barrier), and a workgroup is four waves, so that two share a compute unit and one
 // multiplies while the other looks for its rows' largest magnitudes or rounds its sums.
-// Measured (32768 rows, d = 1024, 256 columns): 117 us with the preparation's 7 (project_kv.hip 180, the float64 kernel 410).
+// Measured (32768 rows, d = 1024, 256 columns): 110.7 us with the preparation's 7 (project_kv.hip 180, the float64 kernel 410).
 // Of a tile's 60 us, two side by side: first pass 8, products 38, sums and rounding 8, open elements 4.  Bound by the matrix
 // cores and the power they draw: the card holds 1.6 to 2.0 GHz in the products (22 us of them at that clock without the
-// conversions).  Without effect: tiles of 64 x 256 with eight waves (half the conversions, nothing beside them: 120), raised
+// conversions).  v_mfma_i32_16x16x64_i8 draws less of it than 32x32x32, us before / so: 113.5 /
+// 110.7, 16384 rows 66.9 / 62.4, 12800 rows of 2048 indices 110.5 / 103.5, 8192 rows x 2048 columns 221 / 205.  Without effect: tiles of 64 x 256 with eight waves (half the conversions, nothing beside them: 120), raised
 // priority of every second workgroup, weights two steps ahead or from L1, sums in 64-bit integers.
 #include "kv_fixed.hpp"
 
@@ -145,7 +146,7 @@ void kv_rows_kernel(KvRowsParams p) {
   const KvPrepared w = p.w;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int i32 = lane & 31, g = lane >> 5;
+  const int i16 = lane & 15, i32 = lane & 31, g = lane >> 4;
   const int C = w.C, rows = p.rows;
   const int nst = w.steps / 2;
 
@@ -226,56 +227,57 @@ void kv_rows_kernel(KvRowsParams p) {
       for (int q = 0; q < 4; ++q) *reinterpret_cast<int4v*>(dst + q * T::DIGIT) = d[q];
     };
 
-    int16v acc[4][2];                          // sums of the digit products with i + j = 3 + t, per row block
+    int4v acc[4][4][2];                        // sums of the digit products with i + j = 3 + t, per row block and column block of 16
 #pragma unroll
     for (int t = 0; t < 4; ++t)
 #pragma unroll
-      for (int r = 0; r < 2; ++r)
+      for (int r = 0; r < 4; ++r)
 #pragma unroll
-        for (int e = 0; e < 16; ++e) acc[t][r][e] = 0;
+        for (int c = 0; c < 2; ++c) acc[t][r][c] = int4v{0, 0, 0, 0};
     const __amdgpu_buffer_rsrc_t weights = __builtin_amdgcn_make_buffer_rsrc(
         p.ws + w.digits() + (size_t)((n0 >> 5) + wave) * w.steps * 4096, 0, (uint32_t)w.steps * 4096u, 0x00020000u);
-    auto weights_of = [&](int step, int q) {
-      return __builtin_bit_cast(int4v, __builtin_amdgcn_raw_buffer_load_b128(weights, (uint32_t)lane * 16u, (uint32_t)min(step, w.steps - 1) * 4096u + (uint32_t)q * 1024u, 0));
+    // lane (i16, g) of a stage: column i16 of a block, indices 16 g ..
+    const uint32_t in_stage = (uint32_t)((g >> 1) * 4096 + ((g & 1) * 32 + i16) * 16);
+    auto weights_of = [&](int st, int q, int c) {
+      return __builtin_bit_cast(int4v, __builtin_amdgcn_raw_buffer_load_b128(weights, in_stage + (uint32_t)c * 256u, (uint32_t)min(st, nst - 1) * 8192u + (uint32_t)q * 1024u, 0));
     };
-    // One step of 32 indices.  The registers of a weight digit take the step after the next as soon as its last product
-    // is issued: an L2 access takes about as long as a step (left to itself the compiler moves these loads to the end).
-    auto multiply = [&](int buf, int step, int4v (&b)[4], int then) {
-      const unsigned char* As = smem + buf * T::STAGE + step * T::STEP + g * T::HALF + i32 * 16;
-      int4v a[2][2];
-      auto rows_of = [&](int i) {
+    int4v b[4][2];
+    // A stage.  The registers of a weight digit take the next stage as soon as its last product is issued (left to itself the
+    // compiler moves these loads to the end).
+    auto multiply = [&](int st) {
+      const unsigned char* As = smem + (st & 1) * T::STAGE + (g >> 1) * T::STEP + (g & 1) * T::HALF + i16 * 16;
+      int4v a[4];
 #pragma unroll
-        for (int r = 0; r < 2; ++r) a[i & 1][r] = *reinterpret_cast<const int4v*>(As + i * T::DIGIT + r * 512);
-      };
-      rows_of(3);
+      for (int r = 0; r < 4; ++r) a[r] = *reinterpret_cast<const int4v*>(As + 3 * T::DIGIT + r * 256);
 #pragma unroll
       for (int i = 3; i >= 0; --i) {
-        if (i > 0) rows_of(i - 1);
 #pragma unroll
-        for (int e = 3; e >= 3 - i; --e)
+        for (int r = 0; r < 4; ++r) {
 #pragma unroll
-          for (int r = 0; r < 2; ++r) acc[i + e - 3][r] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a[i & 1][r], b[e], acc[i + e - 3][r], 0, 0, 0);
-        b[3 - i] = weights_of(then, 3 - i);
+          for (int e = 3 - i; e <= 3; ++e)
+#pragma unroll
+            for (int c = 0; c < 2; ++c) acc[i + e - 3][r][c] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a[r], b[e][c], acc[i + e - 3][r][c], 0, 0, 0);
+          if (i > 0) a[r] = *reinterpret_cast<const int4v*>(As + (i - 1) * T::DIGIT + r * 256);
+        }
+#pragma unroll
+        for (int c = 0; c < 2; ++c) b[3 - i][c] = weights_of(st + 1, 3 - i, c);
         __builtin_amdgcn_sched_barrier(0);
       }
     };
 
     Regs regs;
-    int4v b0[4], b1[4];
     load_stage(src, 0, regs);
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      b0[q] = weights_of(0, q);
-      b1[q] = weights_of(1, q);
-    }
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+      for (int c = 0; c < 2; ++c) b[q][c] = weights_of(0, q, c);
     store_stage(0, regs);
     load_stage(src, 1, regs);
     __syncthreads();
     for (int st = 0; st < nst; ++st) {
       store_stage(st + 1, regs);               // (past the end: digits of zero, into a buffer nobody reads)
       load_stage(src, st + 2, regs);
-      multiply(st & 1, 0, b0, 2 * st + 2);
-      multiply(st & 1, 1, b1, 2 * st + 3);
+      multiply(st);
       __syncthreads();
     }
     {
@@ -291,11 +293,13 @@ void kv_rows_kernel(KvRowsParams p) {
     unsigned char* const out = smem + T::SUMS;
     uint16_t* const list = reinterpret_cast<uint16_t*>(smem + T::SUMS + T::OUT);
 #pragma unroll
-    for (int rb = 0; rb < 2; ++rb)
+    for (int r = 0; r < 4; ++r)
 #pragma unroll
-      for (int e = 0; e < 16; ++e)
-        *reinterpret_cast<float*>(sums + (rb * 32 + 8 * (e >> 2) + 4 * g + (e & 3)) * T::SUM_ROW + 4 * (wave * 32 + i32)) =
-            digit_sum(acc[0][rb][e], acc[1][rb][e], acc[2][rb][e], acc[3][rb][e]);
+      for (int c = 0; c < 2; ++c)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          *reinterpret_cast<float*>(sums + (r * 16 + 4 * g + e) * T::SUM_ROW + 4 * (wave * 32 + c * 16 + i16)) =
+              digit_sum(acc[0][r][c][e], acc[1][r][c][e], acc[2][r][c][e], acc[3][r][c][e]);
     __syncthreads();
     const int c8 = tid % (kColumns / 8) * 8, nn = n0 + c8;      // eight columns of one head (N is a multiple of 16)
     const int which = nn >= p.h_kv * p.kv[0] ? 1 : 0, kv = p.kv[which];
