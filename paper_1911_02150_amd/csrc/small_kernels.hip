@@ -340,15 +340,16 @@ hipError_t launch_reorder(const void* K_src, const void* V_src, const int32_t* l
     hipLaunchKernelGGL(kern, dim3((unsigned)slots, (unsigned)((words + 256 * U - 1) / (256 * U))), dim3(256), 0, st, (const uint4*)K_src, (const uint4*)V_src,
                        lens_src, parent, (uint4*)K_dst, (uint4*)V_dst, lens_dst, n, h_kv, cap, (int)(k_row_bytes / 16), (int)(v_row_bytes / 16));
   };
-  // One word a thread while that is at most 4096 workgroups (16 to a compute unit), else as many more: a workgroup's words come one latency after
-  // the other, but capacities that are mostly empty should not cost a workgroup each.  us, 16 words a thread (as it was) / so: 64 slots of 128
-  // rows 5.5 / 2.5 (a beam step with its attention 29.8 / 23.4), 320 of 256 rows 14.4 / 13.1, 64 of 8192 rows 105 / 98, of 100 rows of
-  // 8192 4.3 (in single words 20.5), 256 of 600 rows of 1024 23.3 / 23.7.
+  // One word a thread while that is at most 4096 workgroups (16 to a compute unit), else more: a workgroup's words come one latency after the other,
+  // but capacities that are mostly empty should not cost a workgroup each.  us, sixteen words a thread in two loops (as it was) / so: 64 slots
+  // of 128 rows 5.5 / 2.5 (a beam step with its attention 29.8 / 23.4), 320 of 256 rows 14.4 / 13.1, 64 of 8192 rows 102 / 98, of 100 rows of 8192
+  // 7.6 / 4.3 (in single words 20.5), 256 of 600 rows of 1024 23.1 / 23.7, 4096 of 256 rows 187 / 181, float32 378 / 360, of 10 rows of 256
+  // 7.8 / 8.3 (four words: 10.4, and 172 full).  Sixteen where the grid would be too deep.
   const size_t single = (words + 255) / 256 * slots;
   if (single <= 4096) go(reorder_kernel<1>, 1);
   else if (single <= 2 * 4096) go(reorder_kernel<2>, 2);
   else if (single <= 4 * 4096) go(reorder_kernel<4>, 4);
-  else if (single <= 8 * 4096) go(reorder_kernel<8>, 8);
+  else if (words <= (size_t)65535 * 256 * 8) go(reorder_kernel<8>, 8);
   else go(reorder_kernel<16>, 16);
   return hipGetLastError();
 }

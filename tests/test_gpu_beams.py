@@ -206,7 +206,7 @@ def test_encoder_decoder_memory_with_beams(m):
     assert float((K2 != K).float().mean()) < 1e-2
 
 
-# one, two, four, eight and sixteen words a thread; rows of K and V of different length, a last piece that is not full, empty and full slots
+# one, two, four and eight words a thread; rows of K and V of different length, a last piece that is not full, empty and full slots
 @pytest.mark.parametrize("n,h,cap,k,v,dtype", [(3, 1, 5, 8, 24, torch.bfloat16), (64, 1, 129, 128, 128, torch.bfloat16), (40, 2, 1001, 64, 128, torch.bfloat16),
                                                (9, 1, 30011, 128, 64, torch.bfloat16), (5, 3, 24000, 128, 128, torch.bfloat16), (7, 1, 40003, 104, 128, torch.float32)])
 def test_beam_reorder_of_any_size(m, n, h, cap, k, v, dtype):
@@ -225,3 +225,15 @@ def test_beam_reorder_of_any_size(m, n, h, cap, k, v, dtype):
         there = torch.arange(cap, device=DEV) < out[2][:, None]
         there = (there[:, None] if h > 1 else there).unsqueeze(-1)
         assert torch.equal(new, torch.where(there, old[parent.long()], torch.full_like(old, 7.0)))
+
+
+def test_beam_reorder_of_a_deep_grid(m):
+    """Sixteen words a thread: where pieces of eight would be more than 65535 (K rows of 2 GiB)."""
+    cap = 65535 * 256 * 8 // 64 + 9
+    K, V = torch.empty(1, cap, 256, device=DEV).normal_(), torch.empty(1, cap, 8, device=DEV).normal_()
+    lens, parent = torch.tensor([cap - 2], dtype=torch.int32, device=DEV), torch.zeros(1, dtype=torch.int32, device=DEV)
+    out = [torch.zeros_like(K), torch.zeros_like(V), torch.zeros_like(lens)]
+    m.mqa_beam_reorder_kv(K, V, lens, parent, *out)
+    assert out[2].item() == cap - 2
+    for new, old in zip(out, (K, V)):
+        assert torch.equal(new[:, :-2], old[:, :-2]) and not new[:, -2:].any()
