@@ -234,3 +234,13 @@ def test_stack_prefill_ends_at_the_last_positions(m, layers, b, n, d, h):
         graph.replay()
         torch.cuda.synchronize()
         assert close(out, ref) and all(close(a.V[l], inc.V[l]) for l in range(layers)) and a.lens[0].tolist() == [n] * b
+
+
+@pytest.mark.parametrize("d", [1, 7, 74, 72, 1024, 1028])
+def test_embed_of_any_width(m, d):
+    g = torch.Generator(device=DEV)
+    g.manual_seed(d)
+    E, P = torch.randn(50, d, generator=g, device=DEV), torch.randn(9, d, generator=g, device=DEV)
+    tokens = torch.randint(0, 50, (33,), generator=g, device=DEV, dtype=torch.int32)
+    positions = torch.arange(33, device=DEV, dtype=torch.int32) % 9
+    assert torch.equal(m.mqa_stack_embed(tokens, positions, E, P), E[tokens.long()] + P[positions.long()])
