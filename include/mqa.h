@@ -442,16 +442,6 @@ int mqa_stack_add_layernorm_packed(mqa_proj_mode mode, const float* in, const fl
 int mqa_stack_product_plan(mqa_proj_mode mode, int rows, int d, int h, int kv, int residual);
 int mqa_stack_product(const void* x, const void* w, float scale, void* out, int rows, int N, int C, mqa_proj_epilogue epilogue, int form,
                       void* stream);
-/*
- * The output projection of a prompt from packed attention:
- *   prefill_attention_packed: mqa_prefill_attention whose outputs [b n][h v] leave as a packed matrix, each line by a power of two of
- *                   its own: row_scale [b n] (float32) takes it back.  h: a power of two, up to 32; n h > 32; bf16 caches, k = v = 128.
- *   product_rows:   product with those scales, line by line, in the place of one for all (not MQA_EPI_RELU_PACKED).
- */
-int mqa_stack_prefill_attention_packed(const float* q, const void* K, const void* V, const int32_t* lens, void* packed, float* row_scale,
-                                       int b, int n, int h, int cap, int k, int v, mqa_dtype dt, float scale, void* stream);
-int mqa_stack_product_rows(const void* x, const float* row_scale, const void* w, float* out, int rows, int N, int C, mqa_proj_epilogue epilogue,
-                           int form, void* stream);
 
 const char* mqa_status_string(int status);
 

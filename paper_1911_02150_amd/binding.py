@@ -26,7 +26,7 @@ EXPORTS = [
     "mqa_stream_read", "mqa_stream_copy", "mqa_status_string",
     "mqa_stack_layernorm", "mqa_stack_embed", "mqa_stack_add", "mqa_stack_relu", "mqa_stack_argmax",
     "mqa_stack_packed_bytes", "mqa_stack_pack", "mqa_stack_layernorm_exponent", "mqa_stack_layernorm_packed", "mqa_stack_add_layernorm_packed",
-    "mqa_stack_product_plan", "mqa_stack_product", "mqa_stack_product_rows", "mqa_stack_prefill_attention_packed",
+    "mqa_stack_product_plan", "mqa_stack_product",
 ]
 
 
@@ -125,8 +125,6 @@ def load_library(path: str = LIB_PATH):
     lib.mqa_stack_add_layernorm_packed.argtypes = [ci, vp, vp, vp, vp, vp, ci, ci, ci, ci, cf, vp, sz, vp]
     lib.mqa_stack_product_plan.argtypes = [ci] * 6
     lib.mqa_stack_product.argtypes = [vp, vp, cf, vp, ci, ci, ci, ci, ci, vp]
-    lib.mqa_stack_product_rows.argtypes = [vp, vp, vp, vp, ci, ci, ci, ci, ci, vp]
-    lib.mqa_stack_prefill_attention_packed.argtypes = [vp] * 6 + [ci] * 7 + [cf, vp]
     lib.mqa_status_string.argtypes = [ci]
     lib.mqa_status_string.restype = ctypes.c_char_p
     for name in EXPORTS:
@@ -823,34 +821,13 @@ class PackedWeights:
 
 
 def mqa_stack_product(x, w, scale, out, rows, form, epilogue=MQA_EPI_STORE, stream=None):
-    """x: packed rows, w: PackedWeights, form: w.plan(rows); scale: a number, or a tensor of the rows' own."""
+    """x: packed rows, w: PackedWeights, form: w.plan(rows)."""
     _check(x, "x"), _check(out, "out")
     need = rows * w.N * 4 * (form & 15)
     if x.numel() * x.element_size() != 4 * rows * w.C or out.numel() * out.element_size() < need:
         raise ValueError(f"size mismatch in mqa_stack_product: x {tuple(x.shape)} out {tuple(out.shape)} for {rows} rows, {w.N} columns of {w.C}")
-    if isinstance(scale, torch.Tensor):
-        _check(scale, "scale", torch.float32), _check(out, "out", torch.float32)
-        if scale.numel() != rows:
-            raise ValueError(f"shape mismatch in mqa_stack_product: {scale.numel()} scales for {rows} rows")
-        _rc("mqa_stack_product", load_library().mqa_stack_product_rows(_ptr(x), _ptr(scale), _ptr(w.data), _ptr(out), rows, w.N, w.C, epilogue, form,
-                                                                       _stream(stream)))
-        return out
     _rc("mqa_stack_product", load_library().mqa_stack_product(_ptr(x), _ptr(w.data), scale, _ptr(out), rows, w.N, w.C, epilogue, form, _stream(stream)))
     return out
-
-
-def mqa_stack_prefill_attention_packed(q, K, V, lens, packed, row_scale, scale=1.0, stream=None):
-    """mqa_prefill_attention to packed lines [b n][h v] and what takes each back (see mqa.h)."""
-    _check(q, "q", torch.float32), _check(K, "K"), _check(V, "V"), _check(lens, "lens", torch.int32)
-    _check(packed, "packed"), _check(row_scale, "row_scale", torch.float32)
-    b, n, h, k = q.shape
-    cap, v = V.shape[-2], V.shape[-1]
-    if K.shape != (b, cap, k) or V.shape != (b, cap, v) or lens.numel() != b or packed.numel() * packed.element_size() != 4 * b * n * h * v or \
-            row_scale.numel() != b * n:
-        raise ValueError("shape mismatch in mqa_stack_prefill_attention_packed")
-    _rc("mqa_stack_prefill_attention_packed", load_library().mqa_stack_prefill_attention_packed(
-        _ptr(q), _ptr(K), _ptr(V), _ptr(lens), _ptr(packed), _ptr(row_scale), b, n, h, cap, k, v, _cache_dtype(K), float(scale), _stream(stream)))
-    return packed
 
 
 def mqa_stack_layernorm_packed(x, packed, out=None, parts=None, S=0, eps=1e-6, stream=None):

@@ -726,8 +726,7 @@ int mqa_stack_product_plan(mqa_proj_mode mode, int rows, int d, int h, int kv, i
 
 int mqa_stack_layernorm_exponent(int d) { return d > 0 ? packed_layernorm_exponent(d) : 0; }
 
-static int packed_product(const void* x, const void* w, float scale, const float* row_scale, void* out, int rows, int N, int C, mqa_proj_epilogue epilogue,
-                          int form, void* stream) {
+int mqa_stack_product(const void* x, const void* w, float scale, void* out, int rows, int N, int C, mqa_proj_epilogue epilogue, int form, void* stream) {
   if (!x || !w || !out) return MQA_ERR_NULL;
   if ((int)epilogue < 0 || (int)epilogue > MQA_EPI_RELU_PACKED) return MQA_ERR_DTYPE;
   const int S = form & 15;
@@ -735,35 +734,8 @@ static int packed_product(const void* x, const void* w, float scale, const float
   const int per = (C / 32 + S - 1) / S;
   if ((C / 32 + per - 1) / per != S || (epilogue == MQA_EPI_RELU_PACKED && (N & 31))) return MQA_ERR_SHAPE;
   if (misaligned(x) || misaligned(w) || misaligned(out)) return MQA_ERR_ALIGN;
-  return launch_packed_product(x, w, scale, row_scale, out, rows, N, C, (int)epilogue, form, static_cast<hipStream_t>(stream)) == hipSuccess
-             ? MQA_OK : MQA_ERR_LAUNCH;
-}
-int mqa_stack_product(const void* x, const void* w, float scale, void* out, int rows, int N, int C, mqa_proj_epilogue epilogue, int form, void* stream) {
-  return packed_product(x, w, scale, nullptr, out, rows, N, C, epilogue, form, stream);
-}
-int mqa_stack_product_rows(const void* x, const float* row_scale, const void* w, float* out, int rows, int N, int C, mqa_proj_epilogue epilogue, int form,
-                           void* stream) {
-  if (!row_scale) return MQA_ERR_NULL;
-  if (epilogue == MQA_EPI_RELU_PACKED) return MQA_ERR_DTYPE;
-  if (misaligned(row_scale)) return MQA_ERR_ALIGN;
-  return packed_product(x, w, 1.f, row_scale, out, rows, N, C, epilogue, form, stream);
-}
-
-int mqa_stack_prefill_attention_packed(const float* q, const void* K, const void* V, const int32_t* lens, void* packed, float* row_scale,
-                                       int b, int n, int h, int cap, int k, int v, mqa_dtype dt, float scale, void* stream) {
-  if (!row_scale) return MQA_ERR_NULL;
-  if (n <= 0 || n > cap || h <= 0 || h > 32 || (h & (h - 1)) || (long long)n * h <= 32 || (long long)n * h > (1 << 20)) return MQA_ERR_SHAPE;
-  const int G = n * h;
-  const int rc = check_decode_args(q, K, V, lens, static_cast<float*>(packed), b, G, cap, k, v, (int)dt, true);
-  if (rc) return rc;
-  if (!mfma_shape_ok(G, k, v, dt == MQA_BF16, cap) || (long long)b * n > 1 << 25) return MQA_ERR_SHAPE;
-  if (misaligned(row_scale)) return MQA_ERR_ALIGN;
-  DecodeParams p = {};
-  p.q = q; p.K = K; p.V = V; p.lens = lens;
-  p.nseq = b; p.G = G; p.cap = cap; p.lens_div = 1;
-  p.k = k; p.v = v; p.causal_h = h; p.chunk = cap; p.S = 1; p.HG = (G + 127) / 128;
-  p.qscale = scale * kLog2e;
-  return launch_prompt_packed(p, packed, row_scale, static_cast<hipStream_t>(stream)) == hipSuccess ? MQA_OK : MQA_ERR_LAUNCH;
+  return launch_packed_product(x, w, scale, out, rows, N, C, (int)epilogue, form, static_cast<hipStream_t>(stream)) == hipSuccess ? MQA_OK
+                                                                                                                                  : MQA_ERR_LAUNCH;
 }
 
 int mqa_stack_layernorm_packed(const float* parts, int S, float* x, float* y, void* packed, int rows, int d, float eps, void* stream) {

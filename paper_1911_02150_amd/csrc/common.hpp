@@ -92,9 +92,6 @@ hipError_t launch_decode_mfma_two(const DecodeParams& p, long long nblocks0, lon
 
 // prompt_mfma.hip: causal rows, bf16 cache, k = v = 128, p.HG blocks of 128 rows per group
 hipError_t launch_prompt(const DecodeParams& p, hipStream_t st);
-// ... its outputs packed: positions as lines, heads x 128 as columns, row_scale[position] = what takes its line back (heads: a power of two
-// up to 32, more than 32 rows of a sequence)
-hipError_t launch_prompt_packed(const DecodeParams& p, void* packed, float* row_scale, hipStream_t st);
 
 // decode_direct.hip: k = v = 64 or 128 in float32, 64 in bf16 (hipErrorNotSupported: another shape).
 bool direct_shape_ok(int k, int v, int is_bf16, int cap);
@@ -167,7 +164,7 @@ bool packed_fits(int rows, int N, int C);
 int packed_plan(int mode, int rows, int d, int h, int kv, int residual);
 int packed_layernorm_exponent(int N);
 hipError_t launch_pack_weights(bool outp, const float* P, const float* row_scale, void* packed, int32_t* verdict, int d, int h, int kv, hipStream_t st);
-hipError_t launch_packed_product(const void* x, const void* w, float scale, const float* row_scale, void* out, int rows, int N, int C, int epilogue, int form,
+hipError_t launch_packed_product(const void* x, const void* w, float scale, void* out, int rows, int N, int C, int epilogue, int form,
                                  hipStream_t st);
 
 // stack_kernels.hip
@@ -240,18 +237,6 @@ __device__ __forceinline__ void store_packed4(unsigned char* packed, float scale
   unsigned char* at = packed + ((size_t)(column >> 5) * 2 * rows + row) * 64 + (column & 31) * 2;
   *reinterpret_cast<uint2*>(at) = make_uint2(s.hi, t.hi);
   *reinterpret_cast<uint2*>(at + (size_t)rows * 64) = make_uint2(s.lo, t.lo);
-}
-
-// Eight values -> the 16 bytes of a line's planes, `plane` bytes apart.
-__device__ __forceinline__ void store_packed8(unsigned char* at, size_t plane, const float (&v)[8]) {
-  uint32_t hi[4], lo[4];
-#pragma unroll
-  for (int p = 0; p < 4; ++p) {
-    const Split2 s = split2(v[2 * p], v[2 * p + 1]);
-    hi[p] = s.hi; lo[p] = s.lo;
-  }
-  *reinterpret_cast<uint4*>(at) = make_uint4(hi[0], hi[1], hi[2], hi[3]);
-  *reinterpret_cast<uint4*>(at + plane) = make_uint4(lo[0], lo[1], lo[2], lo[3]);
 }
 
 __device__ __forceinline__ float wave_max(float x) {

@@ -38,12 +38,23 @@ template <int N> __device__ __forceinline__ void wait_and_meet() {      // at mo
   asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" :: "n"(N) : "memory");
 }
 
+// Eight values -> the 16 bytes of a line's planes, `plane` bytes apart.
+__device__ __forceinline__ void store_packed8(unsigned char* at, size_t plane, const float (&v)[8]) {
+  uint32_t hi[4], lo[4];
+#pragma unroll
+  for (int p = 0; p < 4; ++p) {
+    const Split2 s = split2(v[2 * p], v[2 * p + 1]);
+    hi[p] = s.hi; lo[p] = s.lo;
+  }
+  *reinterpret_cast<uint4*>(at) = make_uint4(hi[0], hi[1], hi[2], hi[3]);
+  *reinterpret_cast<uint4*>(at + plane) = make_uint4(lo[0], lo[1], lo[2], lo[3]);
+}
+
 struct PackedProduct {
   const unsigned char* x;      // packed [C / 32][2][rows][64]
   const unsigned char* w;      // packed [C / 32][2][N][64]
   const float* col_scale;      // [N] what takes a finished sum of a column back
   float scale;                 // ... and what all of them have in common
-  const float* row_scale;      // [rows] or NULL: ... and those of a row
   void* out;                   // float32 [parts][rows][N] or packed [N / 32][2][rows][64]
   int rows, N, blocks;         // blocks: of 32 indices
   int epilogue;                // 0 store, 1 relu, 2 add to what out holds, 3 relu into a packed matrix
@@ -63,12 +74,11 @@ __device__ __forceinline__ void finish8(const PackedProduct& p, int row, int n, 
     return;
   }
   const floatx4 c0 = *reinterpret_cast<const floatx4*>(p.col_scale + n), c1 = *reinterpret_cast<const floatx4*>(p.col_scale + n + 4);
-  const float back = p.row_scale ? p.row_scale[row] : p.scale;
   floatx4 y0, y1;
 #pragma unroll
   for (int e = 0; e < 4; ++e) {
-    y0[e] = v[e] * c0[e] * back;
-    y1[e] = v[4 + e] * c1[e] * back;
+    y0[e] = v[e] * c0[e] * p.scale;
+    y1[e] = v[4 + e] * c1[e] * p.scale;
     if (ADD) {
       y0[e] += was0[e];
       y1[e] += was1[e];
@@ -391,10 +401,10 @@ int packed_plan(int mode, int rows, int d, int h, int kv, int residual) {
   return form < 0 ? 0 : form;
 }
 
-hipError_t launch_packed_product(const void* x, const void* w, float scale, const float* row_scale, void* out, int rows, int N, int C, int epilogue, int form,
+hipError_t launch_packed_product(const void* x, const void* w, float scale, void* out, int rows, int N, int C, int epilogue, int form,
                                  hipStream_t st) {
   const unsigned char* wp = static_cast<const unsigned char*>(w);
-  const PackedProduct p{static_cast<const unsigned char*>(x), wp, reinterpret_cast<const float*>(wp + packed_bytes(N, C)), scale, row_scale, out, rows, N, C / 32, epilogue, 0, 0, 0};
+  const PackedProduct p{static_cast<const unsigned char*>(x), wp, reinterpret_cast<const float*>(wp + packed_bytes(N, C)), scale, out, rows, N, C / 32, epilogue, 0, 0, 0};
   const int S = form & 15;
   switch (form >> 4) {
     case 0: return launch_tile<256, 256, 4, 2, 1, 2, false>(p, S, st);

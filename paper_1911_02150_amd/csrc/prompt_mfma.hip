@@ -50,8 +50,8 @@ __device__ __forceinline__ void split_pair(float a, float b, uint32_t& hi, uint3
 }
 
 // One row by one wave in plain float32 over the positions below its limit: a lane has a position of 64 for the
-// logits, then two columns for the weighted sum: columns 2 lane and 2 lane + 1.
-__device__ __forceinline__ float2 plain_row(const DecodeParams& p, int seq, int row, int lim, int lane) {
+// logits, then two columns for the weighted sum.
+__device__ __forceinline__ void plain_row(const DecodeParams& p, int seq, int row, int lim, int lane) {
   const float* q = p.q + ((size_t)seq * p.G + row) * 128;
   const uint16_t* K = static_cast<const uint16_t*>(p.K) + (size_t)seq * p.cap * 128;
   const uint32_t* V = static_cast<const uint32_t*>(p.V) + (size_t)seq * p.cap * 64;
@@ -77,13 +77,12 @@ __device__ __forceinline__ float2 plain_row(const DecodeParams& p, int seq, int 
     }
   }
   const float inv = l > 0.f ? 1.0f / l : 0.f;                // (a row with nothing to see: zeros)
-  return make_float2(a * inv, b * inv);
+  *reinterpret_cast<float2*>(p.o + ((size_t)seq * p.G + row) * 128 + 2 * lane) = make_float2(a * inv, b * inv);
 }
 
-// PACKED: the outputs leave as two fp16 terms of 2^s times them, a line per position (packed.hip), s by the line's largest value; row_scale: 2^-s.
-template <int TEAMS, bool PACKED>
+template <int TEAMS>
 __global__ __launch_bounds__(256 * TEAMS, 2)
-void prompt_kernel(DecodeParams p, unsigned char* packed, float* row_scale) {
+void prompt_kernel(DecodeParams p) {
   extern __shared__ __align__(16) unsigned char smem_all[];  // per team: two buffers; at the end the waves' outputs
   const int team = TEAMS > 1 ? __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 8) : 0;
   unsigned char* const smem = smem_all + team * (2 * kBuffer);
@@ -272,19 +271,12 @@ void prompt_kernel(DecodeParams p, unsigned char* packed, float* row_scale) {
     __syncthreads();
   }
 
-  // outputs go through the wave's quarter of LDS, so that rows leave as whole lines: float4 c of row r at c ^ r
-  float4* rows = reinterpret_cast<float4*>(smem_all + wave * (32 * 512));
-  const bool by_rows = __builtin_expect(*any_odd, 0);
-  if (by_rows) {
+  if (__builtin_expect(*any_odd, 0)) {
     constexpr int ROWS = 32 / TEAMS;
-    for (int row = row0 + team * ROWS; row < min(row0 + (team + 1) * ROWS, G); ++row) {
-      const float2 o = plain_row(p, seq, row, limit(row), lane);
-      if constexpr (PACKED) reinterpret_cast<float2*>(rows + (row - row0) * 32 + ((lane >> 1) ^ (row - row0)))[lane & 1] = o;
-      else *reinterpret_cast<float2*>(p.o + ((size_t)seq * G + row) * 128 + 2 * lane) = o;
-    }
-    if (!PACKED) return;
+    for (int row = row0 + team * ROWS; row < min(row0 + (team + 1) * ROWS, G); ++row) plain_row(p, seq, row, limit(row), lane);
+    return;
   }
-  if constexpr (TEAMS > 1) if (!by_rows) {
+  if constexpr (TEAMS > 1) {
     // the second team's states meet the first's in LDS: sums in its own buffers, maxima and sums of weights where the first's wave
     // will put its rows (its own reads come before its writes)
     float* const at = reinterpret_cast<float*>(smem_all + 2 * kBuffer) + wave * (64 * 64) + lane;
@@ -309,8 +301,10 @@ void prompt_kernel(DecodeParams p, unsigned char* packed, float* row_scale) {
     }
   }
 
-  // ---- output: acc[cb][e] is column 32 cb + 8 (e / 4) + 4 g + e % 4 of row i32
-  if (team == 0 && !by_rows) {
+  // ---- output: through the wave's quarter of LDS, so that rows leave as whole lines.  acc[cb][e] is column 32 cb + 8 (e / 4)
+  // + 4 g + e % 4 of row i32
+  float4* rows = reinterpret_cast<float4*>(smem_all + wave * (32 * 512));
+  if (team == 0) {
     const float lsum = l_run + __shfl_xor(l_run, 32);
     const float inv = lsum > 0.f ? 1.0f / lsum : 0.f;        // (a row with nothing to see: zeros)
 #pragma unroll
@@ -321,32 +315,6 @@ void prompt_kernel(DecodeParams p, unsigned char* packed, float* row_scale) {
             make_float4(acc[cb][4 * q] * inv, acc[cb][4 * q + 1] * inv, acc[cb][4 * q + 2] * inv, acc[cb][4 * q + 3] * inv);
   }
   __syncthreads();
-  if constexpr (PACKED) {
-    // a position's h rows are in one wave (h: a power of two up to 32); lane i32 has the scale of row i32
-    float most = 0.f;
-#pragma unroll
-    for (int c = 0; c < 16; ++c) {
-      const float4 f = rows[i32 * 32 + ((2 * c + g) ^ i32)];
-      most = fmaxf(fmaxf(most, fmaxf(fabsf(f.x), fabsf(f.y))), fmaxf(fabsf(f.z), fabsf(f.w)));
-    }
-    most = fmaxf(most, __shfl_xor(most, 32));
-    for (int s = 1; s < h; s <<= 1) most = fmaxf(most, __shfl_xor(most, s));
-    const float scale = split_scale(most > 0.f && most < INFINITY ? most : 1.f, 14);
-    const int in_wave = 32 / h, line0 = seq * nq + row0 / h;
-    const size_t lines = (size_t)p.nseq * nq;
-    if (team == 0 && g == 0 && i32 % h == 0 && row0 + i32 < G) row_scale[line0 + i32 / h] = 1.f / scale;
-    const int octet = lane & 15;
-#pragma unroll
-    for (int j = 0; j < 8 / TEAMS; ++j) {
-      // the positions of one head next to one another: 64 bytes each of the head's planes
-      const int at = (team * (8 / TEAMS) + j) * 4 + (lane >> 4), head = at / in_wave, position = at - head * in_wave, r = position * h + head;
-      const float4 a = rows[r * 32 + ((2 * octet) ^ r)], b = rows[r * 32 + ((2 * octet + 1) ^ r)];
-      const float by = __shfl(scale, r);
-      const float v[8] = {a.x * by, a.y * by, a.z * by, a.w * by, b.x * by, b.y * by, b.z * by, b.w * by};
-      if (row0 + r < G) store_packed8(packed + ((size_t)(head * 4 + (octet >> 2)) * 2 * lines + line0 + position) * 64 + (octet & 3) * 16, lines * 64, v);
-    }
-    return;
-  }
 #pragma unroll
   for (int r = 0; r < 32 / TEAMS; r += 2) {
     const int row = r + g + team * (32 / TEAMS);
@@ -354,27 +322,19 @@ void prompt_kernel(DecodeParams p, unsigned char* packed, float* row_scale) {
   }
 }
 
-template <int TEAMS, bool PACKED>
-hipError_t launch_teams(const DecodeParams& p, unsigned nblocks, void* packed, float* row_scale, hipStream_t st) {
+template <int TEAMS>
+hipError_t launch_teams(const DecodeParams& p, unsigned nblocks, hipStream_t st) {
   constexpr int lds = TEAMS * 2 * kBuffer + 16;
   static bool done[64] = {};                   // once per device
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) dev = 0;
   if (!done[dev]) {
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(prompt_kernel<TEAMS, PACKED>), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(prompt_kernel<TEAMS>), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     if (e != hipSuccess) return e;
     done[dev] = true;
   }
-  hipLaunchKernelGGL((prompt_kernel<TEAMS, PACKED>), dim3(nblocks), dim3(256 * TEAMS), lds, st, p, static_cast<unsigned char*>(packed), row_scale);
+  hipLaunchKernelGGL(prompt_kernel<TEAMS>, dim3(nblocks), dim3(256 * TEAMS), lds, st, p);
   return hipGetLastError();
-}
-
-template <bool PACKED>
-hipError_t launch_rows(const DecodeParams& p, void* packed, float* row_scale, hipStream_t st) {
-  const long long nblocks = (long long)p.nseq * p.HG;        // HG: blocks of 128 rows
-  if (nblocks > 0x7fffffffll) return hipErrorInvalidValue;
-  return nblocks <= 256 && p.cap > 4 * kTilePos ? launch_teams<2, PACKED>(p, (unsigned)nblocks, packed, row_scale, st)
-                                                : launch_teams<1, PACKED>(p, (unsigned)nblocks, packed, row_scale, st);
 }
 
 }  // namespace
@@ -382,9 +342,10 @@ hipError_t launch_rows(const DecodeParams& p, void* packed, float* row_scale, hi
 // Two teams where a compute unit has one workgroup at most and the positions are more than two tiles each.  us, one team / two: one sequence of 4096, h=8:
 // 146 / 107, of 1024: 41 / 33; multi-head n=700, prefix 100, b=4, h=5: 36 / 29; h=1, n=2000: 83 / 61; but b=16, n=128, prefix 64: 14.2 / 16.0 (the
 // merge), 256 positions the same.
-hipError_t launch_prompt(const DecodeParams& p, hipStream_t st) { return launch_rows<false>(p, nullptr, nullptr, st); }
-hipError_t launch_prompt_packed(const DecodeParams& p, void* packed, float* row_scale, hipStream_t st) {
-  return launch_rows<true>(p, packed, row_scale, st);
+hipError_t launch_prompt(const DecodeParams& p, hipStream_t st) {
+  const long long nblocks = (long long)p.nseq * p.HG;        // HG: blocks of 128 rows
+  if (nblocks > 0x7fffffffll) return hipErrorInvalidValue;
+  return nblocks <= 256 && p.cap > 4 * kTilePos ? launch_teams<2>(p, (unsigned)nblocks, st) : launch_teams<1>(p, (unsigned)nblocks, st);
 }
 
 }  // namespace mqa

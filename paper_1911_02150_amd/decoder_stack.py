@@ -68,8 +68,6 @@ class DecoderStack:
         for l, w in enumerate(self.layers):
             if not self.multi_head:                # (prompts only)
                 yield (l, "P_q"), B.MQA_PROJ_Q, w["P_q"]
-                if l + 1 < len(self.layers):
-                    yield (l, "P_o"), B.MQA_PROJ_O, w["P_o"]
             yield (l, "W1"), B.MQA_PROJ_LINEAR, w["W1"]
             yield (l, "W2"), B.MQA_PROJ_LINEAR, w["W2"]
         yield (-1, "E"), B.MQA_PROJ_O, self.E.unsqueeze(0)
@@ -104,20 +102,6 @@ class DecoderStack:
             self._plans[rows] = plan
         return plan
 
-    def _prompt_forms(self, n: int):
-        """The forms of a prompt's output projections from packed attention (0: from float32)."""
-        if self.multi_head or self.h > 32 or self.h & (self.h - 1) or n * self.h <= 32 or self.k != 128 or self.v != 128 or \
-                self.K[0].dtype != torch.bfloat16 or not self._fresh():
-            return [0] * len(self.layers)
-        forms = self._plans.get(("P_o", n))
-        if forms is None:
-            forms = [self._packs[key][0].plan(self.b * n, True) if key in self._packs and key not in self._unheld else 0
-                     for key in ((l, "P_o") for l in range(len(self.layers)))]
-            if len(self._plans) >= 16:
-                self._plans.clear()
-            self._plans["P_o", n] = forms
-        return forms
-
     def _packed_rows(self, rows: int, C: int) -> torch.Tensor:
         return torch.empty(4 * rows * C, dtype=torch.uint8, device=self.dev)
 
@@ -132,15 +116,8 @@ class DecoderStack:
         # |hx 2^e . W1| <= sqrt(d) 2^e sqrt(d) 2^15 (the columns' largest values are below 2^15), and sqrt(d) 2^e <= 2^15: to 2^15 at most
         return B.mqa_stack_product(hx, W1, 2.0 ** (self._exponent - 30), self._packed_rows(rows, W1.N), rows, form, B.MQA_EPI_RELU_PACKED)
 
-    def _add_product(self, u, W, scale, x: torch.Tensor, rows: int, form: int, ws, out, packed):
-        """x += u W of packed operands, and the layernorm."""
-        if form & 15 == 1:
-            B.mqa_stack_product(u, W, scale, x, rows, form, B.MQA_EPI_ADD)
-            self._norm(x, out, packed)
-        else:
-            parts = ws[:4 * (form & 15) * rows * self.d].view(torch.float32)
-            B.mqa_stack_product(u, W, scale, parts, rows, form, B.MQA_EPI_STORE)
-            B.mqa_stack_layernorm_packed(x, packed, out=out, parts=parts, S=form & 15)
+    def _add_hidden(self, l: int, u, out: torch.Tensor, rows: int, form: int, epilogue: int):
+        B.mqa_stack_product(u, self._packs[l, "W2"][0], 2.0 ** (30 - 2 * self._exponent), out, rows, form, epilogue)
 
     def _feed_forward(self, l: int, plan, hx, x: torch.Tensor, ws: torch.Tensor, out, packed):
         """x += relu(hx W1) W2 with hx packed or not, by the plan; then the layernorm of x to out and packed (either may be None)."""
@@ -148,8 +125,12 @@ class DecoderStack:
         u = self._hidden(l, hx, x.shape[0], w1, w2)
         if not w2:
             self._project_norm(B.MQA_PROJ_LINEAR, u, self.layers[l]["W2"], x, ws, out, packed)
+        elif w2 & 15 == 1:
+            self._add_hidden(l, u, x, x.shape[0], w2, B.MQA_EPI_ADD)
+            self._norm(x, out, packed)
         else:
-            self._add_product(u, self._packs[l, "W2"][0], 2.0 ** (30 - 2 * self._exponent), x, x.shape[0], w2, ws, out, packed)
+            self._add_hidden(l, u, ws, x.shape[0], w2, B.MQA_EPI_STORE)
+            B.mqa_stack_layernorm_packed(x, packed, out=out, parts=ws, S=w2 & 15)
 
     def _norm(self, x, out, packed):
         if packed is None:
@@ -216,7 +197,7 @@ class DecoderStack:
         out = torch.empty((self.b, self.E.shape[0]), dtype=torch.float32, device=self.dev)
         return B.mqa_stack_product(hx, self._packs[-1, "E"][0], 2.0 ** -self._exponent, out, self.b, form)
 
-    def _workspace(self, plans, rows: int, kv_rows: int = 0, forms=()) -> torch.Tensor:
+    def _workspace(self, plans, rows: int, kv_rows: int = 0) -> torch.Tensor:
         """Scratch memory for the calls of one pass over `rows` rows, one after another on its stream (a pass's own: calls on several
         streams do not share it)."""
         nbytes = self._parts.get(rows)         # (a decoding loop asks for the same rows again and again: 1.5 us of a step)
@@ -230,7 +211,7 @@ class DecoderStack:
             if len(self._parts) >= 16:
                 self._parts.clear()
             nbytes = self._parts[rows] = max(sizes)
-        parts = max(*(plan[2] & 15 for plan in plans), *(form & 15 for form in forms), 0)
+        parts = max(plan[2] & 15 for plan in plans)
         return torch.empty(max(nbytes, kv_rows, 16, 4 * parts * rows * self.d if parts > 1 else 0), dtype=torch.uint8, device=self.dev)
 
     # -- one decoding step for the whole stack: per layer 7 launches (fused q/K/V + append, attention (+ merge), output
@@ -261,8 +242,7 @@ class DecoderStack:
         positions = torch.arange(n, dtype=torch.int32, device=self.dev).repeat(b)
         x = B.mqa_stack_embed(prompts.reshape(-1).to(torch.int32).contiguous(), positions, self.E, self.pos)   # [b*n,d]
         plans, _ = self._plan(rows)
-        forms_o = self._prompt_forms(n) if b == self.b else [0] * len(self.layers)
-        ws = self._workspace(plans, rows, B.mqa_project_kv_workspace_bytes(b, n, self.d, 1, self.k, self.v, B._cache_dtype(self.K[0])), forms_o)
+        ws = self._workspace(plans, rows, B.mqa_project_kv_workspace_bytes(b, n, self.d, 1, self.k, self.v, B._cache_dtype(self.K[0])))
         hx = torch.empty_like(x)
         packed = self._packed_rows(rows, self.d) if any(plan[0] or plan[1] for plan in plans) else None
         end = len(self.layers) - 1
@@ -291,20 +271,14 @@ class DecoderStack:
                 B.mqa_stack_product(packed, self._packs[l, "P_q"][0], 2.0 ** -self._exponent, q, rows, form_q)
             else:
                 q = B.mqa_project_qkvo(B.MQA_PROJ_Q, hx, w["P_q"]).view(b, rows // b, self.h, self.k)
-            out, terms = None if form_1 else hx, packed if form_1 else None
-            if l < end and forms_o[l]:
-                o, back = self._packed_rows(rows, self.h * self.v), torch.empty(rows, dtype=torch.float32, device=self.dev)
-                B.mqa_stack_prefill_attention_packed(q, self.K[l], self.V[l], now, o, back)
-                self._add_product(o, self._packs[l, "P_o"][0], back, x, rows, forms_o[l], ws, out, terms)
-            else:
-                o = B.mqa_prefill_attention(q, self.K[l], self.V[l], now, workspace=ws if l == end else None)
-                self._project_norm(B.MQA_PROJ_O, o.view(rows, self.h, self.v), w["P_o"], x, ws, out, terms)
+            o = B.mqa_prefill_attention(q, self.K[l], self.V[l], now, workspace=ws if l == end else None)
+            self._project_norm(B.MQA_PROJ_O, o.view(rows, self.h, self.v), w["P_o"], x, ws, None if form_1 else hx, packed if form_1 else None)
             if l < end:
                 self._feed_forward(l, plans[l], packed if form_1 else hx, x, ws, hx, packed if l + 1 < end and plans[l + 1][0] else None)
             else:                             # (logits() normalises)
                 u = self._hidden(l, packed if form_1 else hx, rows, form_1, form_2)
                 if form_2:
-                    B.mqa_stack_product(u, self._packs[l, "W2"][0], 2.0 ** (30 - 2 * self._exponent), x, rows, form_2, B.MQA_EPI_ADD)
+                    self._add_hidden(l, u, x, rows, form_2, B.MQA_EPI_ADD)
                 else:
                     B.mqa_project_qkvo_ex(B.MQA_PROJ_LINEAR, u, w["W2"], out=x, epilogue=B.MQA_EPI_ADD)
         if now is not self.lens[-1]:      # the lengths advance in the arrays they are in: a caller may hold them

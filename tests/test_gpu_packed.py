@@ -218,43 +218,3 @@ def test_two_layers_follow_their_weights(m):
         got, ref = stack.prefill(prompts), plain.prefill(prompts)
         assert float((got - ref).abs().max()) <= 2e-3 * float(ref.abs().max())
         assert float((stack.K[1] - plain.K[1]).abs().max()) <= 0.05 * float(plain.K[1].abs().max())      # (bf16 near-ties of the layer before)
-
-
-# heads to a line, blocks of one and of two teams of waves, a last block that is not full, positions with nothing to see, values that are not finite
-@pytest.mark.parametrize("b, n, h, cap, odd", [(3, 33, 1, 40, False), (2, 37, 2, 64, False), (70, 65, 8, 130, False), (5, 9, 32, 64, False), (2, 300, 16, 700, False),
-                                               (2, 40, 8, 300, True), (64, 70, 4, 80, True)])
-def test_packed_attention(m, b, n, h, cap, odd):
-    q, K, V = _normal(1, b, n, h, 128, std=0.1), _normal(2, b, cap, 128).bfloat16(), _normal(3, b, cap, 128).bfloat16()
-    V[:, :, 64:] *= 2.0 ** -6                                     # (columns apart)
-    lens = (torch.arange(b, device=DEV, dtype=torch.int32) * 31) % (cap - n + 1) + n
-    lens[1] = n - 5                                               # (its first five see nothing)
-    if odd:
-        V[0, int(lens[0]) - 3, 7] = float("inf")                  # (the last three positions see it)
-    ref = m.mqa_prefill_attention(q, K, V, lens).view(b * n, h * 128)
-    packed, back = torch.zeros(4 * ref.numel() + 64, dtype=torch.uint8, device=DEV), torch.zeros(b * n + 1, device=DEV)
-    m.mqa_stack_prefill_attention_packed(q, K, V, lens, packed[:-64], back[:-1])
-    got = _terms(packed, b * n, h * 128) * back[:-1].double()[:, None]
-    held = torch.isfinite(ref).all(1)
-    assert held.logical_not().sum() == (3 if odd else 0) and (packed[-64:] == 0).all() and back[-1] == 0
-    top = ref.abs().amax(1, keepdim=True).double()
-    assert ((got - ref.double()).abs() <= 2.0 ** -22 * ref.double().abs() + 2.0 ** -39 * top)[held].all()
-    assert not torch.isfinite(got[~held]).all(1).any()
-    frac = torch.frexp(top[held & (top[:, 0] > 0)] / back[:-1].double()[held & (top[:, 0] > 0), None])[1]
-    assert (frac == 15).all()                                     # (a line's largest value in [2^14, 2^15))
-    N = 40
-    P = _normal(4, h, N, 128, std=(h * 128) ** -0.5)
-    w = m.PackedWeights(m.MQA_PROJ_O, P)
-    flat = P.permute(1, 0, 2).reshape(N, h * 128).t()
-    want, bound = ref.double() @ flat.double(), _bound(ref, flat, h * 128)
-    for form in range(6):
-        out = _normal(5, b * n, N)
-        was = out.double()
-        m.mqa_stack_product(packed[:-64], w, back[:-1], out, b * n, 16 * form + 1, m.MQA_EPI_ADD)
-        assert ((out - (was + want)).abs() <= bound + EPS * (was.abs() + want.abs()))[held].all()
-        assert not torch.isfinite(out[~held]).any()
-    refused = [(4, 8, 128), (2, 40, 3), (1, 1, 64)]
-    for b_, n_, h_ in refused:
-        with pytest.raises(m.MqaError):
-            m.mqa_stack_prefill_attention_packed(_normal(1, b_, n_, h_, 128), K[:1].expand(b_, cap, 128).contiguous(), V[:1].expand(b_, cap, 128).contiguous(),
-                                                 lens[:1].expand(b_).contiguous(), torch.zeros(4 * b_ * n_ * h_ * 128, dtype=torch.uint8, device=DEV),
-                                                 torch.zeros(b_ * n_, device=DEV))
