@@ -48,7 +48,7 @@ class DecoderStack:
 
     def _pack(self, weights, old):
         for key, mode, t in weights:
-            lines, C = (t.shape[-2], t.shape[-1]) if mode == B.MQA_PROJ_O else (t.numel() // t.shape[-2], t.shape[-2])
+            C, lines = t.shape
             before = self._packs.get((key[0], "W1")) if key[1] == "W2" else None
             if lines % 8 or C % 32 or t.shape[-1] % 8 or not t.is_contiguous() or t.dtype != torch.float32 or t.device != self.K[0].device or \
                     t.data_ptr() % 16 or (key[1] == "W2" and before is None) or B.load_library().mqa_stack_packed_bytes(lines, C, 1) == 0:
@@ -66,37 +66,27 @@ class DecoderStack:
 
     def _packable(self):
         for l, w in enumerate(self.layers):
-            if not self.multi_head:                # (prompts only)
-                yield (l, "P_q"), B.MQA_PROJ_Q, w["P_q"]
             yield (l, "W1"), B.MQA_PROJ_LINEAR, w["W1"]
             yield (l, "W2"), B.MQA_PROJ_LINEAR, w["W2"]
-        yield (-1, "E"), B.MQA_PROJ_O, self.E.unsqueeze(0)
 
     def _fresh(self) -> bool:
-        for (l, name), (_, t, version) in self._packs.items():
-            if l >= 0:
-                if self.layers[l][name] is not t or t._version != version:
-                    return False
-            elif self.E.data_ptr() != t.data_ptr() or self.E.shape != t.shape[1:] or t._version != version:
-                return False
-        return True
+        return all(self.layers[l][name] is t and t._version == version for (l, name), (_, t, version) in self._packs.items())
 
     def _plan(self, rows: int):
-        """How the products of a pass over `rows` rows run from packed weights (mqa_stack_product_plan; 0: they do not): per layer q's, W1's,
-        W2's and a last W2's without a layernorm behind it, then the logits' over the batch."""
+        """How the products of a pass over `rows` rows run from packed weights (mqa_stack_product_plan; 0: they do not): per layer W1's,
+        W2's and a last W2's without a layernorm behind it."""
         if not self._fresh():
             if torch.cuda.is_current_stream_capturing():      # (the packing asks the device: this pass goes without)
-                return [(0, 0, 0, 0)] * len(self.layers), 0
+                return [(0, 0, 0)] * len(self.layers)
             self.pack()
         plan = self._plans.get(rows)
         if plan is None:
             def form(key, n, residual=False):
                 return self._packs[key][0].plan(n, residual) if key in self._packs and key not in self._unheld else 0
-            layers = []
+            plan = []
             for l in range(len(self.layers)):
                 w1 = form((l, "W1"), rows)
-                layers.append((form((l, "P_q"), rows), w1, w1 and form((l, "W2"), rows, True), w1 and form((l, "W2"), rows)))
-            plan = layers, form((-1, "E"), self.b)
+                plan.append((w1, w1 and form((l, "W2"), rows, True), w1 and form((l, "W2"), rows)))
             if len(self._plans) >= 16:             # (prompts of many lengths)
                 self._plans.clear()
             self._plans[rows] = plan
@@ -121,7 +111,7 @@ class DecoderStack:
 
     def _feed_forward(self, l: int, plan, hx, x: torch.Tensor, ws: torch.Tensor, out, packed):
         """x += relu(hx W1) W2 with hx packed or not, by the plan; then the layernorm of x to out and packed (either may be None)."""
-        _, w1, w2, _ = plan
+        w1, w2, _ = plan
         u = self._hidden(l, hx, x.shape[0], w1, w2)
         if not w2:
             self._project_norm(B.MQA_PROJ_LINEAR, u, self.layers[l]["W2"], x, ws, out, packed)
@@ -185,17 +175,10 @@ class DecoderStack:
         return B.mqa_project_qkvo(B.MQA_PROJ_LINEAR, u, w["W2"])
 
     def logits(self, x: torch.Tensor) -> torch.Tensor:
-        _, form = self._plan(self.b)
-        if not form:
-            return self._logits(B.mqa_stack_layernorm(x), 0)
-        packed = self._packed_rows(self.b, self.d)
-        return self._logits(B.mqa_stack_layernorm_packed(x, packed), form)
+        return self._logits(B.mqa_stack_layernorm(x))
 
-    def _logits(self, hx: torch.Tensor, form: int) -> torch.Tensor:
-        if not form:
-            return B.mqa_project_qkvo(B.MQA_PROJ_O, hx.view(self.b, 1, self.d), self.E.view(1, -1, self.d))
-        out = torch.empty((self.b, self.E.shape[0]), dtype=torch.float32, device=self.dev)
-        return B.mqa_stack_product(hx, self._packs[-1, "E"][0], 2.0 ** -self._exponent, out, self.b, form)
+    def _logits(self, hx: torch.Tensor) -> torch.Tensor:
+        return B.mqa_project_qkvo(B.MQA_PROJ_O, hx.view(self.b, 1, self.d), self.E.view(1, -1, self.d))
 
     def _workspace(self, plans, rows: int, kv_rows: int = 0) -> torch.Tensor:
         """Scratch memory for the calls of one pass over `rows` rows, one after another on its stream (a pass's own: calls on several
@@ -211,7 +194,7 @@ class DecoderStack:
             if len(self._parts) >= 16:
                 self._parts.clear()
             nbytes = self._parts[rows] = max(sizes)
-        parts = max(plan[2] & 15 for plan in plans)
+        parts = max(plan[1] & 15 for plan in plans)
         return torch.empty(max(nbytes, kv_rows, 16, 4 * parts * rows * self.d if parts > 1 else 0), dtype=torch.uint8, device=self.dev)
 
     # -- one decoding step for the whole stack: per layer 7 launches (fused q/K/V + append, attention (+ merge), output
@@ -219,18 +202,17 @@ class DecoderStack:
     def step(self, tokens: torch.Tensor, t: int) -> torch.Tensor:
         x = self.embed(tokens, t)
         dec = B.mha_decode_step if self.multi_head else B.mqa_decode_step
-        plans, logits_form = self._plan(self.b)
+        plans = self._plan(self.b)
         ws = self._workspace(plans, self.b)
         hx = B.mqa_stack_layernorm(x)
-        rows = self._packed_rows(self.b, self.d) if logits_form or any(plan[1] for plan in plans) else None
+        rows = self._packed_rows(self.b, self.d) if any(plan[0] for plan in plans) else None
         for l, w in enumerate(self.layers):
             q = self._append_fused(l, hx)
             o = dec(q, self.K[l], self.V[l], self.lens[l], workspace=ws)
-            packed = rows if plans[l][1] else None
+            packed = rows if plans[l][0] else None
             self._project_norm(B.MQA_PROJ_O, o, w["P_o"], x, ws, hx if packed is None else None, packed)
-            last = logits_form and l + 1 == len(self.layers)
-            self._feed_forward(l, plans[l], hx if packed is None else packed, x, ws, None if last else hx, rows if last else None)
-        return self._logits(rows if logits_form else hx, logits_form)
+            self._feed_forward(l, plans[l], hx if packed is None else packed, x, ws, hx, None)
+        return self._logits(hx)
 
     # -- a whole prompt at once (multi-query only): bulk append + fused causal attention per layer
     def prefill(self, prompts: torch.Tensor) -> torch.Tensor:
@@ -241,12 +223,12 @@ class DecoderStack:
         rows = b * n
         positions = torch.arange(n, dtype=torch.int32, device=self.dev).repeat(b)
         x = B.mqa_stack_embed(prompts.reshape(-1).to(torch.int32).contiguous(), positions, self.E, self.pos)   # [b*n,d]
-        plans, _ = self._plan(rows)
+        plans = self._plan(rows)
         ws = self._workspace(plans, rows, B.mqa_project_kv_workspace_bytes(b, n, self.d, 1, self.k, self.v, B._cache_dtype(self.K[0])))
         hx = torch.empty_like(x)
-        packed = self._packed_rows(rows, self.d) if any(plan[0] or plan[1] for plan in plans) else None
+        packed = self._packed_rows(rows, self.d) if any(plan[0] for plan in plans) else None
         end = len(self.layers) - 1
-        self._norm(x, hx, packed if end and plans[0][0] else None)
+        B.mqa_stack_layernorm(x, out=hx)
         for l, w in enumerate(self.layers):
             if self.k % 16 == 0 and self.v % 16 == 0:
                 now = self._lens_next[l]
@@ -261,20 +243,16 @@ class DecoderStack:
                 # Of the last layer, behind its K and V rows, only the last positions lead to a result, and each depends on itself and the
                 # caches alone: the rest of the layer is a step's (six layers, b=128, n=128, d=1024, ff=4096: 6260 -> 5270 us)
                 x = x.view(b, n, self.d)[:, n - 1].contiguous()
-                rows, plans = b, self._plan(b)[0]
+                rows, plans = b, self._plan(b)
                 ws, hx = self._workspace(plans[end:], b), torch.empty_like(x)
-                packed = self._packed_rows(b, self.d) if plans[end][0] or plans[end][1] else None
-                self._norm(x, hx, packed if plans[end][0] else None)
-            form_q, form_1, _, form_2 = plans[l]
-            if form_q:
-                q = torch.empty((b, rows // b, self.h, self.k), dtype=torch.float32, device=self.dev)
-                B.mqa_stack_product(packed, self._packs[l, "P_q"][0], 2.0 ** -self._exponent, q, rows, form_q)
-            else:
-                q = B.mqa_project_qkvo(B.MQA_PROJ_Q, hx, w["P_q"]).view(b, rows // b, self.h, self.k)
+                packed = self._packed_rows(b, self.d) if plans[end][0] else None
+                B.mqa_stack_layernorm(x, out=hx)
+            form_1, _, form_2 = plans[l]
+            q = B.mqa_project_qkvo(B.MQA_PROJ_Q, hx, w["P_q"]).view(b, rows // b, self.h, self.k)
             o = B.mqa_prefill_attention(q, self.K[l], self.V[l], now, workspace=ws if l == end else None)
             self._project_norm(B.MQA_PROJ_O, o.view(rows, self.h, self.v), w["P_o"], x, ws, None if form_1 else hx, packed if form_1 else None)
             if l < end:
-                self._feed_forward(l, plans[l], packed if form_1 else hx, x, ws, hx, packed if l + 1 < end and plans[l + 1][0] else None)
+                self._feed_forward(l, plans[l], packed if form_1 else hx, x, ws, hx, None)
             else:                             # (logits() normalises)
                 u = self._hidden(l, packed if form_1 else hx, rows, form_1, form_2)
                 if form_2:

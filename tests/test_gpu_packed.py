@@ -152,7 +152,7 @@ def test_stack_with_and_without(m, b, n, d, ff, vocab):
     used = packed._plan(b * n)
     print(b, n, used, packed._plan(b))
     assert not packed._packs or not packed._unheld
-    assert plain._plan(b * n) == ([(0, 0, 0, 0)] * 2, 0) and (d % 32 == 0 or not packed._packs)
+    assert plain._plan(b * n) == [(0, 0, 0)] * 2 and (d % 32 == 0 or not packed._packs)
     for got, ref in ((packed.prefill(prompts), plain.prefill(prompts)), (packed.step(prompts[:, 0].contiguous(), n), plain.step(prompts[:, 0].contiguous(), n))):
         scale = float(ref.abs().max())
         assert float((got - ref).abs().max()) <= 2e-3 * scale      # (cache elements that round the other way, as between prompt and steps)
@@ -168,8 +168,7 @@ def test_stack_follows_its_weights(m):
     w = _weights(3, 1, d, 2, ff, vocab, n)
     prompts = torch.from_numpy(np.random.default_rng(2).integers(0, vocab, (b, n)).astype(np.int32)).to(DEV)
     stack = DecoderStack(w, b, n, False, DEV)
-    plans, logits = stack._plan(b * n)
-    assert plans[0][1] and logits, "this size is to run packed"
+    assert stack._plan(b * n)[0][0], "this size is to run packed"
     stack.prefill(prompts)
     place = stack._packs[0, "W1"][0].data.data_ptr()
 
@@ -194,7 +193,7 @@ def test_stack_follows_its_weights(m):
     check()
     stack.layers[0]["W1"][:20, 5] = 1e-9
     check()
-    assert (0, "W1") in stack._unheld and stack._plan(b * n)[0][0][1:] == (0, 0, 0)
+    assert (0, "W1") in stack._unheld and stack._plan(b * n)[0] == (0, 0, 0)
 
 
 def test_two_layers_follow_their_weights(m):
@@ -204,7 +203,7 @@ def test_two_layers_follow_their_weights(m):
     w = _weights(4, 2, d, 2, ff, vocab, n)
     prompts = torch.from_numpy(np.random.default_rng(3).integers(0, vocab, (b, n)).astype(np.int32)).to(DEV)
     stack = DecoderStack(w, b, n, False, DEV)
-    assert all(stack._plan(b * n)[0][0][1:3]), "this size is to run packed"
+    assert all(stack._plan(b * n)[0][:2]), "this size is to run packed"
     for name in ("P_q", "W1", "W2"):
         if name == "W1":
             stack.layers[0][name].mul_(-1.5)

@@ -57,7 +57,7 @@ def _same(stack, logits, fresh, prompts, n):
         assert torch.equal(stack.K[l], fresh.K[l]) and torch.equal(stack.V[l], fresh.V[l]) and torch.equal(stack.lens[l], fresh.lens[l])
 
 
-SIZES = [(4, 100, 2, 1024, 8, 64, 264)]
+SIZES = [(4, 100, 2, 1024, 8, 64, 264), (3, 200, 2, 1024, 8, 96, 9000), (600, 1, 2, 512, 4, 64, 32768)]
 
 
 @pytest.mark.parametrize("b, n, layers, d, h, ff, vocab", SIZES)
@@ -144,7 +144,7 @@ def _logits(m, stack, x):
     return m.mqa_project_qkvo(m.MQA_PROJ_O, m.mqa_stack_layernorm(x).view(-1, 1, stack.d), stack.E.view(1, -1, stack.d))
 
 
-@pytest.mark.parametrize("b, n, d, h, ff, vocab", [(4, 100, 1024, 8, 64, 264), (2, 5, 64, 40, 128, 264)])
+@pytest.mark.parametrize("b, n, d, h, ff, vocab", [(4, 100, 1024, 8, 64, 264), (3, 200, 1024, 8, 96, 9000), (1, 50, 1024, 8, 64, 32768), (2, 5, 64, 40, 128, 264)])
 def test_prompt_is_its_calls(m, b, n, d, h, ff, vocab):
     """Up to some thousand rows a prompt is what the public calls make of the float32 weights, bit for bit: every product in their precision."""
     from paper_1911_02150_amd.decoder_stack import DecoderStack
@@ -153,3 +153,12 @@ def test_prompt_is_its_calls(m, b, n, d, h, ff, vocab):
     assert torch.equal(stack.prefill(prompts), want)
     for l, (K, V) in enumerate(caches):
         assert torch.equal(stack.K[l], K) and torch.equal(stack.V[l], V)
+
+
+@pytest.mark.parametrize("b", [1, 8, 16, 128, 300])
+def test_logits_are_their_call(m, b):
+    """So are the logits, of however few rows: of 1 to 16 the products of float32 instructions."""
+    from paper_1911_02150_amd.decoder_stack import DecoderStack
+    stack = DecoderStack(_weights(b, 1, 1024, 2, 64, 32768, 4), b, 4, False, DEV)
+    x = torch.from_numpy(np.random.default_rng(b).standard_normal((b, 1024), dtype=np.float32)).to(DEV)
+    assert torch.equal(stack.logits(x), _logits(m, stack, x))
