@@ -121,7 +121,7 @@ int mqa_project_qkvo(mqa_proj_mode mode, const float* in, const float* P, float*
  * MQA_EPI_STORE as above; MQA_EPI_RELU stores max(x, 0); MQA_EPI_ADD adds x to what `out`
  * already holds (the residual connection around the attention of Section 4.1's layers).
  */
-typedef enum { MQA_EPI_STORE = 0, MQA_EPI_RELU = 1, MQA_EPI_ADD = 2, MQA_EPI_RELU_PACKED = 3 /* mqa_stack_product only */ } mqa_proj_epilogue;
+typedef enum { MQA_EPI_STORE = 0, MQA_EPI_RELU = 1, MQA_EPI_ADD = 2 } mqa_proj_epilogue;
 int mqa_project_qkvo_ex(mqa_proj_mode mode, const float* in, const float* P, float* out,
                         int rows, int d, int h, int kv, mqa_proj_epilogue epilogue, void* stream);
 
@@ -413,35 +413,16 @@ int mqa_stack_relu(float* a, size_t n, void* stream);
 int mqa_stack_argmax(const float* x, int32_t* out, int rows, int n, void* stream);
 
 /*
- * Products of that stack from operands that are laid out beforehand ("packed": two fp16 terms per value under a power of two, the
- * contraction in blocks of 32 indices; the layout is the library's own).  Weights are packed once, by the program that keeps them; the
- * activations they meet come packed out of the calls that make them.
- *   packed_bytes:   of a packed matrix of `lines` lines of C indices (C % 32 = 0); weights: lines are the product's columns, and their
- *                   scales lie behind them.  0: no such matrix.
- *   pack:           the weights of mqa_project_qkvo's Q, O or LINEAR mode, each row c multiplied by row_scale[c] unless that is NULL;
- *                   *verdict (int32 on the device, 0 beforehand) becomes 1 if two terms do not hold them (more than 6 of 256
- *                   neighbouring values of a column below 2^-17 of its largest, zeros aside, a NaN, an infinity): the packed matrix is then not to be used.
- *   layernorm_packed: x[r,:] += parts[0][r,:] + ... + parts[S-1][r,:] (S = 0: none), then layernorm(x) as float32 to y and as a packed
- *                   matrix of 2^e times it, e = mqa_stack_layernorm_exponent(d); either may be NULL.  d % 32 = 0 (packed), d <= 4096.
- *   add_layernorm_packed: mqa_project_add_layernorm with that packed matrix beside, or (y NULL) in the place of, y.
- *   product:        out[r,n] = scale * (x . w)[r,n]; epilogue MQA_EPI_STORE, _RELU, _ADD (rows x N float32), or
- *                   MQA_EPI_RELU_PACKED: out is packed, and holds max(x . w, 0) * scale before the columns' own scales are taken back; the
- *                   weights it meets next are packed with row_scale = those scales (behind the packed weights).  `form` is what
- *                   product_plan says: the tiles, and in its last four bits the parts of the contraction (more than one, with MQA_EPI_STORE
- *                   only: out is [parts][rows][N], for layernorm_packed).
- *   product_plan:   the form for these sizes (arguments as mqa_project_qkvo; residual: the product is added to the residual and
- *                   normalised, in parts if that is faster), or 0: not faster than, or not as exact as, the call from float32 weights.
+ * The feed-forward of that stack's long prompts in one call: x += relu(layernorm(x) . W1) . W2, x [rows,d], W1 [d,ff], W2 [ff,d].
+ * The products are those of mqa_project_qkvo_ex from operands split beforehand, in the workspace, by this call; where two fp16 terms do not hold
+ * the values they are that call's own (decided on the device: a captured call does what the weights of each replay want).
+ *   plan:  0: no such form of these sizes (d, ff: multiples of 32, d <= 4096; the call is then refused with MQA_ERR_SHAPE); else bit 0 says whether
+ *          it is faster than layernorm, product with MQA_EPI_RELU and product with MQA_EPI_ADD, bits 4..7 and 8..11 which tiles the products take.
+ *          *workspace_bytes (unless NULL): what the call needs (MQA_ERR_WORKSPACE with less), about 4 (rows + 2 d) (d + ff) bytes.
  */
-size_t mqa_stack_packed_bytes(int lines, int C, int weights);
-int mqa_stack_pack(mqa_proj_mode mode, const float* P, const float* row_scale, int d, int h, int kv, void* packed, int32_t* verdict,
-                   void* stream);
-int mqa_stack_layernorm_exponent(int d);
-int mqa_stack_layernorm_packed(const float* parts, int S, float* x, float* y, void* packed, int rows, int d, float eps, void* stream);
-int mqa_stack_add_layernorm_packed(mqa_proj_mode mode, const float* in, const float* P, float* x, float* y, void* packed, int rows, int d,
-                                   int h, int kv, float eps, void* workspace, size_t workspace_bytes, void* stream);
-int mqa_stack_product_plan(mqa_proj_mode mode, int rows, int d, int h, int kv, int residual);
-int mqa_stack_product(const void* x, const void* w, float scale, void* out, int rows, int N, int C, mqa_proj_epilogue epilogue, int form,
-                      void* stream);
+int mqa_stack_feed_forward_plan(int rows, int d, int ff, size_t* workspace_bytes);
+int mqa_stack_feed_forward(const float* W1, const float* W2, float* x, int rows, int d, int ff, float eps, void* workspace,
+                           size_t workspace_bytes, void* stream);
 
 const char* mqa_status_string(int status);
 

@@ -15,7 +15,7 @@ LIB_PATH = os.path.join(_PKG_DIR, "libmqa_decode.so")
 
 MQA_F32, MQA_BF16 = 0, 1
 MQA_PROJ_Q, MQA_PROJ_KV, MQA_PROJ_KV_MH, MQA_PROJ_O, MQA_PROJ_LINEAR = 0, 1, 2, 3, 4
-MQA_EPI_STORE, MQA_EPI_RELU, MQA_EPI_ADD, MQA_EPI_RELU_PACKED = 0, 1, 2, 3
+MQA_EPI_STORE, MQA_EPI_RELU, MQA_EPI_ADD = 0, 1, 2
 
 EXPORTS = [
     "mqa_project_qkvo", "mqa_project_qkvo_ex", "mqa_project_add_layernorm", "mqa_project_add_layernorm_workspace_bytes", "mqa_project_append_qkv", "mqa_project_append_kv_rows", "mqa_project_append_kv_rows_ws", "mqa_project_kv_workspace_bytes", "mqa_project_plan", "mqa_project_kv_plan", "mqa_append_kv", "mqa_decode_step", "mha_decode_step",
@@ -25,8 +25,7 @@ EXPORTS = [
     "mqa_decode_plan", "mqa_decode_step_noalloc", "mqa_project_memory_kv", "mqa_project_memory_kv_ws", "mqa_memory_decode_step",
     "mqa_stream_read", "mqa_stream_copy", "mqa_status_string",
     "mqa_stack_layernorm", "mqa_stack_embed", "mqa_stack_add", "mqa_stack_relu", "mqa_stack_argmax",
-    "mqa_stack_packed_bytes", "mqa_stack_pack", "mqa_stack_layernorm_exponent", "mqa_stack_layernorm_packed", "mqa_stack_add_layernorm_packed",
-    "mqa_stack_product_plan", "mqa_stack_product",
+    "mqa_stack_feed_forward_plan", "mqa_stack_feed_forward",
 ]
 
 
@@ -117,20 +116,14 @@ def load_library(path: str = LIB_PATH):
     lib.mqa_stack_add.argtypes = [vp, vp, sz, vp]
     lib.mqa_stack_relu.argtypes = [vp, sz, vp]
     lib.mqa_stack_argmax.argtypes = [vp, vp, ci, ci, vp]
-    lib.mqa_stack_packed_bytes.argtypes = [ci, ci, ci]
-    lib.mqa_stack_packed_bytes.restype = sz
-    lib.mqa_stack_pack.argtypes = [ci, vp, vp, ci, ci, ci, vp, vp, vp]
-    lib.mqa_stack_layernorm_exponent.argtypes = [ci]
-    lib.mqa_stack_layernorm_packed.argtypes = [vp, ci, vp, vp, vp, ci, ci, cf, vp]
-    lib.mqa_stack_add_layernorm_packed.argtypes = [ci, vp, vp, vp, vp, vp, ci, ci, ci, ci, cf, vp, sz, vp]
-    lib.mqa_stack_product_plan.argtypes = [ci] * 6
-    lib.mqa_stack_product.argtypes = [vp, vp, cf, vp, ci, ci, ci, ci, ci, vp]
+    lib.mqa_stack_feed_forward_plan.argtypes = [ci, ci, ci, ctypes.POINTER(sz)]
+    lib.mqa_stack_feed_forward.argtypes = [vp, vp, vp, ci, ci, ci, cf, vp, sz, vp]
     lib.mqa_status_string.argtypes = [ci]
     lib.mqa_status_string.restype = ctypes.c_char_p
     for name in EXPORTS:
         if name not in ("mqa_decode_workspace_bytes", "mha_decode_workspace_bytes", "mqa_status_string",
                         "mqa_decode_beams_workspace_bytes", "mqa_decode_workspace_bytes_default", "mqa_project_kv_workspace_bytes",
-                        "mqa_project_add_layernorm_workspace_bytes", "mqa_stack_packed_bytes"):
+                        "mqa_project_add_layernorm_workspace_bytes"):
             getattr(lib, name).restype = ci
     _native = _load_native(lib)
     _lib = lib
@@ -709,41 +702,6 @@ def mqa_project_add_layernorm_workspace_bytes(mode, rows, d, h, kv) -> int:
     return int(load_library().mqa_project_add_layernorm_workspace_bytes(int(mode), rows, d, h, kv))
 
 
-def _add_layernorm(fn_name, mode, x, P, acc, out, packed, eps, workspace, stream):
-    lib = load_library()
-    _check(x, "in", torch.float32), _check(P, "P", torch.float32), _check(acc, "acc", torch.float32)
-    rows = x.shape[0]
-    if mode == MQA_PROJ_LINEAR:
-        (d, kv), h = P.shape, 1
-        ok, width = x.shape == (rows, d), kv
-    elif mode == MQA_PROJ_O:
-        h, d, kv = P.shape
-        ok, width = x.shape == (rows, h, kv), d
-    else:
-        raise ValueError(f"{fn_name}: mode O or LINEAR")
-    if not ok or acc.shape != (rows, width):
-        raise ValueError(f"shape mismatch: in {tuple(x.shape)} P {tuple(P.shape)} acc {tuple(acc.shape)} mode {mode}")
-    if out is not None:
-        _check(out, "out", torch.float32)
-        if out.shape != acc.shape:
-            raise ValueError("out has the wrong size")
-    if packed is not None and packed.numel() * packed.element_size() != 4 * acc.numel():
-        raise ValueError("packed has the wrong size")
-    if workspace is None:
-        workspace, nbytes = _call_workspace(lib.mqa_project_add_layernorm_workspace_bytes(mode, rows, d, h, kv), x.device, stream)
-    else:
-        nbytes = workspace.numel() * workspace.element_size()
-    args = (mode, _ptr(x), _ptr(P), _ptr(acc), _ptr(out))
-    sizes = (rows, d, h, kv, float(eps), _ptr(workspace), nbytes, _stream(stream))
-    if packed is None:
-        rc = lib.mqa_project_add_layernorm(*args, *sizes)
-    else:
-        _check(packed, "packed")
-        rc = lib.mqa_stack_add_layernorm_packed(*args, _ptr(packed), *sizes)
-    if rc != 0:
-        raise MqaError(fn_name, rc)
-
-
 def mqa_project_add_layernorm(mode, x, P, acc, out=None, eps=1e-6, workspace=None, stream=None):
     """acc += x . P (mode O: x [rows,h,kv], P [h,d,kv]; LINEAR: x [rows,d], P [d,kv]), then out = layernorm(acc).  Returns out.
     Workspace: as mqa_project_append_kv_rows."""
@@ -751,16 +709,33 @@ def mqa_project_add_layernorm(mode, x, P, acc, out=None, eps=1e-6, workspace=Non
         done = _native.add_layernorm(mode, x, P, acc, out, eps, workspace)
         if done is not None:
             return done
+    lib = load_library()
+    _check(x, "in", torch.float32), _check(P, "P", torch.float32), _check(acc, "acc", torch.float32)
+    rows = x.shape[0]
+    if mode == MQA_PROJ_LINEAR:
+        d, kv = P.shape
+        h, ok, width = 1, x.shape == (rows, d), kv
+    elif mode == MQA_PROJ_O:
+        h, d, kv = P.shape
+        ok, width = x.shape == (rows, h, kv), d
+    else:
+        raise ValueError("mqa_project_add_layernorm: mode O or LINEAR")
+    if not ok or acc.shape != (rows, width):
+        raise ValueError(f"shape mismatch: in {tuple(x.shape)} P {tuple(P.shape)} acc {tuple(acc.shape)} mode {mode}")
     if out is None:
         out = torch.empty_like(acc)
-    _add_layernorm("mqa_project_add_layernorm", mode, x, P, acc, out, None, eps, workspace, stream)
+    _check(out, "out", torch.float32)
+    if out.shape != acc.shape:
+        raise ValueError("out has the wrong size")
+    if workspace is None:
+        workspace, nbytes = _call_workspace(lib.mqa_project_add_layernorm_workspace_bytes(mode, rows, d, h, kv), x.device, stream)
+    else:
+        nbytes = workspace.numel() * workspace.element_size()
+    rc = lib.mqa_project_add_layernorm(mode, _ptr(x), _ptr(P), _ptr(acc), _ptr(out), rows, d, h, kv, float(eps), _ptr(workspace), nbytes,
+                                       _stream(stream))
+    if rc != 0:
+        raise MqaError("mqa_project_add_layernorm", rc)
     return out
-
-
-def mqa_stack_add_layernorm_packed(mode, x, P, acc, packed, out=None, eps=1e-6, workspace=None, stream=None):
-    """mqa_project_add_layernorm with the layernorm packed, and as float32 to out unless that is None.  Returns packed."""
-    _add_layernorm("mqa_stack_add_layernorm_packed", mode, x, P, acc, out, packed, eps, workspace, stream)
-    return packed
 
 
 def mqa_stream_read(src, sink, stream=None):
@@ -791,61 +766,22 @@ def mqa_stack_layernorm(x, out=None, eps=1e-6, stream=None):
     return out
 
 
-class PackedWeights:
-    """The weights of a Q, O or LINEAR product laid out for mqa_stack_product (see mqa.h).  row_scale: another PackedWeights whose relu'd,
-    packed outputs these weights meet.  `verdict` (int32 on the device) is not 0 if they are not to be used."""
-
-    def __init__(self, mode, P, row_scale=None, stream=None):
-        self.mode, self.row_scale = mode, row_scale
-        self.h, self.d, self.kv = (1, *P.shape) if P.dim() == 2 else P.shape
-        self.N, self.C = (self.d, self.h * self.kv) if mode == MQA_PROJ_O else (self.h * self.kv, self.d)
-        nbytes = load_library().mqa_stack_packed_bytes(self.N, self.C, 1)
-        if nbytes == 0 or self.N % 8:
-            raise ValueError(f"no packed form of {self.N} columns of {self.C}")
-        self.data = torch.empty(nbytes, dtype=torch.uint8, device=P.device)
-        self.verdict = torch.empty(1, dtype=torch.int32, device=P.device)
-        self.pack(P, stream)
-
-    def pack(self, P, stream=None):
-        """(Again, after the weights have changed in place.)"""
-        _check(P, "P", torch.float32)
-        if P.numel() != self.N * self.C:
-            raise ValueError(f"P {tuple(P.shape)}: {self.N} columns of {self.C} were packed")
-        scales = None if self.row_scale is None else self.row_scale.data.data_ptr() + 4 * self.row_scale.N * self.row_scale.C
-        self.verdict.zero_()
-        _rc("mqa_stack_pack", load_library().mqa_stack_pack(self.mode, _ptr(P), scales, self.d, self.h, self.kv, _ptr(self.data),
-                                                           _ptr(self.verdict), _stream(stream)))
-
-    def plan(self, rows, residual=False) -> int:
-        return load_library().mqa_stack_product_plan(self.mode, rows, self.d, self.h, self.kv, int(residual))
+def mqa_stack_feed_forward_plan(rows, d, ff):
+    """(what the plan says: 0 or bits as in mqa.h, bytes of workspace)"""
+    nbytes = ctypes.c_size_t(0)
+    return load_library().mqa_stack_feed_forward_plan(rows, d, ff, ctypes.byref(nbytes)), nbytes.value
 
 
-def mqa_stack_product(x, w, scale, out, rows, form, epilogue=MQA_EPI_STORE, stream=None):
-    """x: packed rows, w: PackedWeights, form: w.plan(rows)."""
-    _check(x, "x"), _check(out, "out")
-    need = rows * w.N * 4 * (form & 15)
-    if x.numel() * x.element_size() != 4 * rows * w.C or out.numel() * out.element_size() < need:
-        raise ValueError(f"size mismatch in mqa_stack_product: x {tuple(x.shape)} out {tuple(out.shape)} for {rows} rows, {w.N} columns of {w.C}")
-    _rc("mqa_stack_product", load_library().mqa_stack_product(_ptr(x), _ptr(w.data), scale, _ptr(out), rows, w.N, w.C, epilogue, form, _stream(stream)))
-    return out
-
-
-def mqa_stack_layernorm_packed(x, packed, out=None, parts=None, S=0, eps=1e-6, stream=None):
-    """x += the S parts; layernorm(x) to out and packed (either may be None).  Returns packed."""
-    _check(x, "x", torch.float32)
+def mqa_stack_feed_forward(x, W1, W2, workspace, eps=1e-6, stream=None):
+    """x [rows,d] += relu(layernorm(x) . W1) . W2 with W1 [d,ff], W2 [ff,d], from a workspace of the plan's size.  Returns x."""
+    _check(x, "x", torch.float32), _check(W1, "W1", torch.float32), _check(W2, "W2", torch.float32), _check(workspace, "workspace")
     rows, d = x.shape
-    if packed is not None:
-        _check(packed, "packed")
-    if out is not None:
-        _check(out, "out", torch.float32)
-    if S:
-        _check(parts, "parts")
-    if (packed is not None and packed.numel() * packed.element_size() != 4 * rows * d) or (out is not None and out.shape != x.shape) or \
-            (S and parts.numel() * parts.element_size() < 4 * S * rows * d):
-        raise ValueError("size mismatch in mqa_stack_layernorm_packed")
-    _rc("mqa_stack_layernorm_packed", load_library().mqa_stack_layernorm_packed(_ptr(parts), S, _ptr(x), _ptr(out), _ptr(packed), rows, d, float(eps),
-                                                                               _stream(stream)))
-    return packed
+    ff = W1.shape[-1]
+    if W1.shape != (d, ff) or W2.shape != (ff, d):
+        raise ValueError(f"shape mismatch: x {tuple(x.shape)} W1 {tuple(W1.shape)} W2 {tuple(W2.shape)}")
+    _rc("mqa_stack_feed_forward", load_library().mqa_stack_feed_forward(_ptr(W1), _ptr(W2), _ptr(x), rows, d, ff, float(eps), _ptr(workspace),
+                                                                       workspace.numel() * workspace.element_size(), _stream(stream)))
+    return x
 
 
 def mqa_stack_embed(tokens, positions, E, P, out=None, stream=None):

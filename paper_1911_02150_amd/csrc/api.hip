@@ -300,26 +300,6 @@ int kv_rows_impl(const float* x, const float* P_k, const float* P_v, void* K, vo
   return e == hipSuccess ? MQA_OK : MQA_ERR_LAUNCH;
 }
 
-// x += in . P, y = layernorm(x); packed (may be null; then y is not): the layernorm as a packed matrix
-int add_layernorm_impl(int mode, const float* in, const float* P, float* x, float* y, void* packed, int rows, int d, int h, int kv, float eps,
-                       void* workspace, size_t workspace_bytes, void* stream) {
-  if (!in || !P || !x) return MQA_ERR_NULL;
-  if (mode != MQA_PROJ_LINEAR && mode != MQA_PROJ_O) return MQA_ERR_DTYPE;
-  if (mode == MQA_PROJ_LINEAR) h = 1;
-  if (rows <= 0 || d <= 0 || h <= 0 || kv <= 0 || (d & 7) || (kv & 7)) return MQA_ERR_SHAPE;
-  const int N = mode == MQA_PROJ_O ? d : kv;
-  if (packed && (N > 4096 || !packed_fits(rows, 8, N))) return MQA_ERR_SHAPE;
-  if (misaligned(in) || misaligned(P) || misaligned(x) || (y && misaligned(y)) || (workspace && misaligned(workspace)) || (packed && misaligned(packed)))
-    return MQA_ERR_ALIGN;
-  const size_t want = workspace ? mqa_project_add_layernorm_workspace_bytes((mqa_proj_mode)mode, rows, d, h, kv) : 0;
-  hipStream_t st = static_cast<hipStream_t>(stream);
-  if (want && workspace_bytes >= want)
-    return launch_project_add_layernorm(mode == MQA_PROJ_O, in, P, x, y, packed, rows, d, h, kv, eps, workspace, st) == hipSuccess ? MQA_OK : MQA_ERR_LAUNCH;
-  const int rc = project_impl(mode, in, P, x, rows, d, h, kv, MQA_EPI_ADD, stream);
-  if (rc != MQA_OK) return rc;
-  return launch_layernorm(x, y, packed, rows, N, eps, st) == hipSuccess ? MQA_OK : MQA_ERR_LAUNCH;
-}
-
 }  // namespace
 
 extern "C" {
@@ -620,14 +600,18 @@ size_t mqa_project_add_layernorm_workspace_bytes(mqa_proj_mode mode, int rows, i
 
 int mqa_project_add_layernorm(mqa_proj_mode mode, const float* in, const float* P, float* x, float* y, int rows, int d, int h, int kv,
                               float eps, void* workspace, size_t workspace_bytes, void* stream) {
-  if (!y) return MQA_ERR_NULL;
-  return add_layernorm_impl(mode, in, P, x, y, nullptr, rows, d, h, kv, eps, workspace, workspace_bytes, stream);
-}
-
-int mqa_stack_add_layernorm_packed(mqa_proj_mode mode, const float* in, const float* P, float* x, float* y, void* packed, int rows, int d, int h,
-                                   int kv, float eps, void* workspace, size_t workspace_bytes, void* stream) {
-  if (!packed) return MQA_ERR_NULL;
-  return add_layernorm_impl(mode, in, P, x, y, packed, rows, d, h, kv, eps, workspace, workspace_bytes, stream);
+  if (!in || !P || !x || !y) return MQA_ERR_NULL;
+  if (mode != MQA_PROJ_LINEAR && mode != MQA_PROJ_O) return MQA_ERR_DTYPE;
+  if (mode == MQA_PROJ_LINEAR) h = 1;
+  if (rows <= 0 || d <= 0 || h <= 0 || kv <= 0 || (d & 7) || (kv & 7)) return MQA_ERR_SHAPE;
+  if (misaligned(in) || misaligned(P) || misaligned(x) || misaligned(y) || (workspace && misaligned(workspace))) return MQA_ERR_ALIGN;
+  const size_t want = workspace ? mqa_project_add_layernorm_workspace_bytes(mode, rows, d, h, kv) : 0;
+  hipStream_t st = static_cast<hipStream_t>(stream);
+  if (want && workspace_bytes >= want)
+    return launch_project_add_layernorm(mode == MQA_PROJ_O, in, P, x, y, rows, d, h, kv, eps, workspace, st) == hipSuccess ? MQA_OK : MQA_ERR_LAUNCH;
+  const int rc = project_impl(mode, in, P, x, rows, d, h, kv, MQA_EPI_ADD, stream);
+  if (rc != MQA_OK) return rc;
+  return launch_layernorm(x, y, rows, mode == MQA_PROJ_O ? d : kv, eps, st) == hipSuccess ? MQA_OK : MQA_ERR_LAUNCH;
 }
 
 int mqa_project_kv_plan(int rows, int d, int h, int h_kv, int k, int v, mqa_dtype dt) {
@@ -699,52 +683,23 @@ int mqa_stack_layernorm(const float* x, float* y, int rows, int d, float eps, vo
   if (!x || !y) return MQA_ERR_NULL;
   if (rows <= 0 || d <= 0) return MQA_ERR_SHAPE;
   if (misaligned(x) || misaligned(y)) return MQA_ERR_ALIGN;
-  return launch_layernorm(x, y, nullptr, rows, d, eps, static_cast<hipStream_t>(stream)) == hipSuccess ? MQA_OK : MQA_ERR_LAUNCH;
+  return launch_layernorm(x, y, rows, d, eps, static_cast<hipStream_t>(stream)) == hipSuccess ? MQA_OK : MQA_ERR_LAUNCH;
 }
 
-size_t mqa_stack_packed_bytes(int lines, int C, int weights) {
-  if (!packed_fits(1, 8, C) || lines <= 0 || lines > 1 << 25) return 0;
-  return packed_bytes(lines, C) + (weights ? (size_t)lines * 4 : 0);
+int mqa_stack_feed_forward_plan(int rows, int d, int ff, size_t* workspace_bytes) {
+  const FeedForwardPlan f = feed_forward_plan(rows, d, ff);
+  if (workspace_bytes) *workspace_bytes = f.bytes;
+  return f.bytes ? f.faster | (f.form1 + 1) << 4 | (f.form2 + 1) << 8 : 0;
 }
 
-int mqa_stack_pack(mqa_proj_mode mode, const float* P, const float* row_scale, int d, int h, int kv, void* packed, int32_t* verdict, void* stream) {
-  if (!P || !packed || !verdict) return MQA_ERR_NULL;
-  if (mode != MQA_PROJ_Q && mode != MQA_PROJ_O && mode != MQA_PROJ_LINEAR) return MQA_ERR_DTYPE;
-  if (mode == MQA_PROJ_LINEAR) h = 1;
-  if (d <= 0 || h <= 0 || kv <= 0 || (d & 7) || (kv & 7) || (long long)h * kv > 1 << 24) return MQA_ERR_SHAPE;
-  const bool outp = mode == MQA_PROJ_O;
-  if (!packed_fits(1, outp ? d : h * kv, outp ? h * kv : d)) return MQA_ERR_SHAPE;
-  if (misaligned(P) || misaligned(packed) || misaligned(verdict) || (row_scale && misaligned(row_scale))) return MQA_ERR_ALIGN;
-  return launch_pack_weights(outp, P, row_scale, packed, verdict, d, h, kv, static_cast<hipStream_t>(stream)) == hipSuccess ? MQA_OK : MQA_ERR_LAUNCH;
-}
-
-int mqa_stack_product_plan(mqa_proj_mode mode, int rows, int d, int h, int kv, int residual) {
-  if (mode == MQA_PROJ_LINEAR) h = 1;
-  if ((mode != MQA_PROJ_Q && mode != MQA_PROJ_O && mode != MQA_PROJ_LINEAR) || rows <= 0 || d <= 0 || h <= 0 || kv <= 0 || (d & 7) || (kv & 7)) return 0;
-  return packed_plan(mode, rows, d, h, kv, residual != 0);
-}
-
-int mqa_stack_layernorm_exponent(int d) { return d > 0 ? packed_layernorm_exponent(d) : 0; }
-
-int mqa_stack_product(const void* x, const void* w, float scale, void* out, int rows, int N, int C, mqa_proj_epilogue epilogue, int form, void* stream) {
-  if (!x || !w || !out) return MQA_ERR_NULL;
-  if ((int)epilogue < 0 || (int)epilogue > MQA_EPI_RELU_PACKED) return MQA_ERR_DTYPE;
-  const int S = form & 15;
-  if (!packed_fits(rows, N, C) || form < 0 || form >> 4 > 5 || S < 1 || S > C / 32 || (S > 1 && epilogue != MQA_EPI_STORE)) return MQA_ERR_SHAPE;
-  const int per = (C / 32 + S - 1) / S;
-  if ((C / 32 + per - 1) / per != S || (epilogue == MQA_EPI_RELU_PACKED && (N & 31))) return MQA_ERR_SHAPE;
-  if (misaligned(x) || misaligned(w) || misaligned(out)) return MQA_ERR_ALIGN;
-  return launch_packed_product(x, w, scale, out, rows, N, C, (int)epilogue, form, static_cast<hipStream_t>(stream)) == hipSuccess ? MQA_OK
-                                                                                                                                  : MQA_ERR_LAUNCH;
-}
-
-int mqa_stack_layernorm_packed(const float* parts, int S, float* x, float* y, void* packed, int rows, int d, float eps, void* stream) {
-  if (!x || (!y && !packed) || (S > 0 && !parts)) return MQA_ERR_NULL;
-  if (S < 0 || rows <= 0 || d <= 0 || d > 4096 || (packed ? !packed_fits(rows, 8, d) : (d & 7) != 0)) return MQA_ERR_SHAPE;
-  if (misaligned(x) || (y && misaligned(y)) || (packed && misaligned(packed)) || (parts && misaligned(parts))) return MQA_ERR_ALIGN;
-  hipStream_t st = static_cast<hipStream_t>(stream);
-  const hipError_t e = S > 0 ? launch_finish(parts, S, x, y, packed, rows, d, eps, st) : launch_layernorm(x, y, packed, rows, d, eps, st);
-  return e == hipSuccess ? MQA_OK : MQA_ERR_LAUNCH;
+int mqa_stack_feed_forward(const float* W1, const float* W2, float* x, int rows, int d, int ff, float eps, void* workspace, size_t workspace_bytes,
+                           void* stream) {
+  if (!W1 || !W2 || !x) return MQA_ERR_NULL;
+  const FeedForwardPlan f = feed_forward_plan(rows, d, ff);
+  if (!f.bytes) return MQA_ERR_SHAPE;
+  if (!workspace || workspace_bytes < f.bytes) return MQA_ERR_WORKSPACE;
+  if (misaligned(W1) || misaligned(W2) || misaligned(x) || misaligned(workspace)) return MQA_ERR_ALIGN;
+  return launch_feed_forward(f, W1, W2, x, rows, d, ff, eps, workspace, static_cast<hipStream_t>(stream)) == hipSuccess ? MQA_OK : MQA_ERR_LAUNCH;
 }
 
 int mqa_stack_embed(const int32_t* tokens, const int32_t* positions, const float* E, const float* P, float* x,

@@ -144,11 +144,9 @@ struct TermsForm { int RB, CB, S; };
 TermsForm terms_form(bool outp, int rows, int d, int h, int kv);
 TermsForm terms_parts_form(bool outp, int rows, int d, int h, int kv);
 size_t terms_parts_bytes(bool outp, int rows, int d, int h, int kv);
-// x += the S parts, then layernorm(x) as float32 to y and packed (packed.hip) to `packed`; either may be null
-hipError_t launch_finish(const float* part, int S, float* x, float* y, void* packed, int rows, int N, float eps, hipStream_t st);
 hipError_t launch_project_terms(bool outp, const float* in, const float* P, float* out, int rows, int d, int h, int kv, int epilogue,
                                 hipStream_t st);
-hipError_t launch_project_add_layernorm(bool outp, const float* in, const float* P, float* x, float* y, void* packed, int rows, int d, int h, int kv,
+hipError_t launch_project_add_layernorm(bool outp, const float* in, const float* P, float* x, float* y, int rows, int d, int h, int kv,
                                         float eps, void* workspace, hipStream_t st);
 
 // project_kv_rows.hip: the same from a workspace of project_kv_rows_workspace(...) bytes (not append: lens_in may be null)
@@ -158,17 +156,21 @@ hipError_t launch_project_kv_rows(const float* x, const float* P_k, const float*
                                   const int32_t* lens_in, int32_t* lens_out, int rows, int n, int append, int d, int h_kv,
                                   int cap, int k, int v, void* workspace, hipStream_t st);
 
-// packed.hip: products of a stack's packed operands
-inline size_t packed_bytes(int lines, int C) { return (size_t)lines * C * 4; }      // (weights: and a float per line)
-bool packed_fits(int rows, int N, int C);
-int packed_plan(int mode, int rows, int d, int h, int kv, int residual);
-int packed_layernorm_exponent(int N);
-hipError_t launch_pack_weights(bool outp, const float* P, const float* row_scale, void* packed, int32_t* verdict, int d, int h, int kv, hipStream_t st);
-hipError_t launch_packed_product(const void* x, const void* w, float scale, void* out, int rows, int N, int C, int epilogue, int form,
-                                 hipStream_t st);
+// gemm.hip: a product of two plain matrices in its tiles, and if *only on the device is not 0
+int gemm_edge(int rows, int N, int C);
+hipError_t launch_gemm_if(const int32_t* only, int edge, const float* in, const float* P, float* out, int rows, int C, int N, int epilogue, hipStream_t st);
 
-// stack_kernels.hip
-hipError_t launch_layernorm(const float* x, float* y, void* packed, int rows, int d, float eps, hipStream_t st);      // (packed: d <= 4096; either may be null)
+// packed.hip: a stack's feed-forward from packed operands.  bytes: of its workspace, 0 where there is no such form; faster: than the calls it stands for;
+// forms and edges: the tiles of its products, and of those in their place where two terms do not hold the values
+struct FeedForwardPlan { size_t bytes; int faster, form1, form2, edge1, edge2; };
+FeedForwardPlan feed_forward_plan(int rows, int d, int ff);
+hipError_t launch_feed_forward(const FeedForwardPlan& f, const float* W1, const float* W2, float* x, int rows, int d, int ff, float eps, void* workspace,
+                               hipStream_t st);
+
+// stack_kernels.hip (packed, if: d a multiple of 32 up to 4096)
+hipError_t launch_layernorm(const float* x, float* y, int rows, int d, float eps, hipStream_t st);
+hipError_t launch_layernorm_packed(const int32_t* flag, const float* x, unsigned char* packed, float scale, int rows, int d, float eps, hipStream_t st);
+hipError_t launch_layernorm_if(const int32_t* only, const float* x, float* y, int rows, int d, float eps, hipStream_t st);
 hipError_t launch_embed(const int32_t* tokens, const int32_t* pos, const float* E, const float* P, float* x,
                         int rows, int d, int vocab, int max_pos, hipStream_t st);
 hipError_t launch_add(float* a, const float* b, size_t n, hipStream_t st);

@@ -88,10 +88,13 @@ template <typename V> __device__ __forceinline__ V load_at(const float* base, ui
 
 // B_KCONTIG = false: B[c][n] = P[(n / kv) * d * kv + c * kv + n % kv]   (C = d, N = h * kv)
 // B_KCONTIG = true : B[c][n] = P[(c / kv) * d * kv + n * kv + c % kv]   (C = h * kv, N = d)
-template <bool B_KCONTIG, int BM, int BN, int WR, int WC, int KG, int PD>
+// ONLY: nothing happens unless *only is not 0
+template <bool B_KCONTIG, int BM, int BN, int WR, int WC, int KG, int PD, bool ONLY>
 __global__ __launch_bounds__(512, KG >= 4 ? 4 : 2)      // (waves per SIMD: two workgroups per compute unit of the small tiles)
 void gemm_split_kernel(const float* __restrict__ in, const float* __restrict__ P, float* out,
-                       int rows, int d, int h, int kv, int epilogue, int tiles_m, int tiles_n, int per) {
+                       int rows, int d, int h, int kv, int epilogue, int tiles_m, int tiles_n, int per, const int32_t* __restrict__ only) {
+  if constexpr (ONLY)
+    if (*only == 0) return;
   static_assert(WR * WC * KG == 8 && BM * KG == 256 && BN * KG == 256, "512 threads, 16 staged values of each operand per thread of a half");
   constexpr int RB = BM / WR / 32, JB = BN / WC / 32;      // 32x32 blocks per wave
   typedef SplitTile<BM, BN, JB, KG> L;
@@ -493,11 +496,11 @@ bool split_fits(bool outp, int d, int h, int kv, int tile, int stage) {
   return h == 1 || kv % reach == 0 || (long long)d * kv * (reach / kv + 2) < most;
 }
 
-template <bool KC, int BM, int BN, int WR, int WC, int KG, int PD>
+template <bool KC, int BM, int BN, int WR, int WC, int KG, int PD, bool ONLY = false>
 hipError_t launch_split(const float* in, const float* P, float* out, int rows, int d, int h, int kv, int N,
-                        int epilogue, int S, hipStream_t st) {
+                        int epilogue, int S, hipStream_t st, const int32_t* only = nullptr) {
   constexpr size_t lds = SplitTile<BM, BN, BN / WC / 32, KG>::BYTES;       // 67 KiB (32, 64), 132 (128: the groups' partial tiles), 74 (256)
-  auto kern = gemm_split_kernel<KC, BM, BN, WR, WC, KG, PD>;
+  auto kern = gemm_split_kernel<KC, BM, BN, WR, WC, KG, PD, ONLY>;
   static bool done[64] = {};
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) dev = 0;
@@ -510,7 +513,7 @@ hipError_t launch_split(const float* in, const float* P, float* out, int rows, i
   const long long tiles = (long long)tm * tn;
   const dim3 grid((unsigned)((tiles + 7) / 8 * 8), S), block(512);
   const int C = KC ? h * kv : d, stage = 16 * KG, per = S > 1 ? ((C + stage - 1) / stage + S - 1) / S * stage : C;
-  hipLaunchKernelGGL(kern, grid, block, lds, st, in, P, out, rows, d, h, kv, epilogue, tm, tn, per);
+  hipLaunchKernelGGL(kern, grid, block, lds, st, in, P, out, rows, d, h, kv, epilogue, tm, tn, per, only);
   return hipGetLastError();
 }
 
@@ -548,6 +551,19 @@ int gemm_form(int mode, int rows, int d, int h, int kv, int apart) {
   const GemmCost c = gemm_cost(outp, rows, outp ? d : h * kv, outp ? (double)h * kv : (double)d);
   if (c.tiles_us + apart > 0.9 * c.split_us) return 0;
   return gemm_fits(outp, d, h, kv, c.edge) ? c.edge : 0;
+}
+
+// The same for a product rows x C . C x N that is one of these tiles in any case; 0: the offsets do not fit
+int gemm_edge(int rows, int N, int C) {
+  const GemmCost c = gemm_cost(false, rows, N, C);
+  return gemm_fits(false, C, 1, N, c.edge) ? c.edge : 0;
+}
+
+// in [rows, C] . P [C, N] if *only is not 0 on the device
+hipError_t launch_gemm_if(const int32_t* only, int edge, const float* in, const float* P, float* out, int rows, int C, int N, int epilogue, hipStream_t st) {
+  if (edge == 128) return launch_split<false, 128, 128, 2, 2, 2, 3, true>(in, P, out, rows, C, 1, N, N, epilogue, 1, st, only);
+  if (edge == 256) return launch_split<false, 256, 256, 4, 2, 1, 1, true>(in, P, out, rows, C, 1, N, N, epilogue, 1, st, only);
+  return hipErrorNotSupported;
 }
 
 // S > 1: the contraction in S parts, their products one behind another in `out` (S x rows x N); edge: of the tiles

@@ -1,22 +1,22 @@
-// Products of the decoder stack whose operands are laid out beforehand.
+// The feed-forward of a stack's long prompts, x += relu(layernorm(x) . W1) . W2, from operands that are laid out on the way.
 //
 // A packed matrix [lines][C] (C a multiple of 32) holds x 2^s as two fp16 terms, hi + lo, each the nearest fp16 of what is
 // left (22 to 24 significant bits, gemm.hip's operands): for every 32 indices a plane of hi and one of lo, in each line after line 64 bytes.
 // What a product wants of 16 neighbouring lines is then 1 KiB in one piece, and what makes a row writes 64 bytes at a time.
 //
-// Packed are the weights, once (a line is a column of the product, scaled by the power of two that takes its largest value to
-// [2^14, 2^15)), and the activations that the stack makes itself, whose range is known before they are: a layernorm's row has a norm of at most
+// Packed are, in every call, the weights (a line is a column of the product, scaled by the power of two that takes its largest value to
+// [2^14, 2^15)) and the activations between, whose range is known before they are: a layernorm's row has a norm of at most
 // sqrt(d), so one scale holds it whatever comes; so has relu(layernorm . W1), each column of which is at most d times the
 // largest value of its column of W1: it keeps that column's scale, which the rows of W2 have been divided by.  So a product
 // is nothing but loads and fp16 instructions:
 //   a.b = ah bh + (ah bl + al bh)                           (al bl is below 2^-22 |a||b|, 2^-25 typically)
 // Weights that two terms do not hold (a column with more than a few values below 2^-17 of its largest next to one another, a NaN, an infinity) are
-// told by the pack (`verdict`) and multiplied by gemm.hip, which looks at its operands at run time.
+// told by a flag on the device: the packed products then return at once, and the launches behind them, which return at once otherwise, are
+// gemm.hip's on the float32 values.  Nothing is kept from one call for the next, and nothing is asked of the device.
 //
 // What bounds it: the matrix cores and the power they draw.  Against gemm.hip, which splits both operands on the way to LDS (us, TFLOP/s of
 // the float32 product): 16384 x 1024 x 4096: 417 -> 337 (408), 16384 x 4096 x 1024: 393 -> 315 (436: 1.31 PFLOP/s of fp16 products; a
-// library product of 8192^3 reaches 1.35), 3000 x 1024 x 1024: 33.7 -> 27.7, 600 x 4096 x 1024: 57 -> 28 (in four parts), 1 x 1024 x
-// 32768: 26.4 -> 24, 128 x 1024 x 32768: 43 -> 36.5.  Of that: no splitting in the way 417 -> 376; v_mfma_f32_16x16x32 in the place of
+// library product of 8192^3 reaches 1.35).  Of that: no splitting in the way 417 -> 376; v_mfma_f32_16x16x32 in the place of
 // 32x32x16 376 -> 368 (less power: 402 -> 330 at 4096 x 1024); LDS reads without bank conflicts 368 -> 337.  One wave per SIMD with
 // 128 x 128 sums: 401.
 #include "common.hpp"
@@ -51,45 +51,36 @@ __device__ __forceinline__ void store_packed8(unsigned char* at, size_t plane, c
 }
 
 struct PackedProduct {
+  const int32_t* flag;         // not 0: this product is not to be
   const unsigned char* x;      // packed [C / 32][2][rows][64]
   const unsigned char* w;      // packed [C / 32][2][N][64]
-  const float* col_scale;      // [N] what takes a finished sum of a column back
-  float scale;                 // ... and what all of them have in common
-  void* out;                   // float32 [parts][rows][N] or packed [N / 32][2][rows][64]
+  const uint32_t* most;        // [N] bits of the largest value of each column of the weights, as scaled for packing
+  float scale;                 // of the finished sums
+  void* out;                   // float32 [rows][N], added to, or packed [N / 32][2][rows][64]
   int rows, N, blocks;         // blocks: of 32 indices
-  int epilogue;                // 0 store, 1 relu, 2 add to what out holds, 3 relu into a packed matrix
-  int tiles_m, tiles_n, per;   // per: blocks of a part of the contraction
+  int tiles_m, tiles_n;
 };
 
-// Eight sums of neighbouring columns of one row; ADD: to what is there, read beforehand
-__device__ __forceinline__ float* place8(const PackedProduct& p, int row, int n, int part) {
-  return static_cast<float*>(p.out) + ((size_t)part * p.rows + row) * p.N + n;
-}
+__device__ __forceinline__ float column_scale(uint32_t most) { return split_scale(most ? __uint_as_float(most) : 1.f, 14); }
+
+// Eight sums of neighbouring columns of one row.  ADD: to what is there, read beforehand; else relu, packed (the columns keep the scale of their weights)
 template <bool ADD>
-__device__ __forceinline__ void finish8(const PackedProduct& p, int row, int n, int part, float (&v)[8], floatx4 was0, floatx4 was1) {
-  if (!ADD && p.epilogue == 3) {       // (the columns keep the scale of their weights)
+__device__ __forceinline__ void finish8(const PackedProduct& p, int row, int n, float (&v)[8], floatx4 was0, floatx4 was1) {
+  if constexpr (!ADD) {
 #pragma unroll
     for (int e = 0; e < 8; ++e) v[e] = fmaxf(v[e], 0.f) * p.scale;
     store_packed8(static_cast<unsigned char*>(p.out) + ((size_t)(n >> 5) * 2 * p.rows + row) * 64 + (n >> 3 & 3) * 16, (size_t)p.rows * 64, v);
-    return;
-  }
-  const floatx4 c0 = *reinterpret_cast<const floatx4*>(p.col_scale + n), c1 = *reinterpret_cast<const floatx4*>(p.col_scale + n + 4);
-  floatx4 y0, y1;
+  } else {
+    const u32x4 m0 = *reinterpret_cast<const u32x4*>(p.most + n), m1 = *reinterpret_cast<const u32x4*>(p.most + n + 4);
 #pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    y0[e] = v[e] * c0[e] * p.scale;
-    y1[e] = v[4 + e] * c1[e] * p.scale;
-    if (ADD) {
-      y0[e] += was0[e];
-      y1[e] += was1[e];
-    } else if (p.epilogue == 1) {
-      y0[e] = fmaxf(y0[e], 0.f);
-      y1[e] = fmaxf(y1[e], 0.f);
+    for (int e = 0; e < 4; ++e) {
+      was0[e] += v[e] * (1.f / column_scale(m0[e])) * p.scale;
+      was1[e] += v[4 + e] * (1.f / column_scale(m1[e])) * p.scale;
     }
+    floatx4* dst = reinterpret_cast<floatx4*>(static_cast<float*>(p.out) + (size_t)row * p.N + n);
+    dst[0] = was0;
+    dst[1] = was1;
   }
-  float* dst = place8(p, row, n, part);
-  *reinterpret_cast<floatx4*>(dst) = y0;
-  *reinterpret_cast<floatx4*>(dst + 4) = y1;
 }
 
 // Tile of TM rows x TN columns, 8 waves: WN x WM of them in each of KG groups; a stage is KG blocks, group kg works on block kg; NB
@@ -105,9 +96,10 @@ struct PackedTile {
   static constexpr int LDS = NB * STAGE > PART ? NB * STAGE : PART;
   static_assert(WN * WM * KG == 8 && (NX + NW) % 8 == 0 && LDS <= 160 * 1024, "8 waves, every one with as many loads");
 };
-template <int TN, int TM, int WN, int WM, int KG, int NB, bool LOW>
+template <int TN, int TM, int WN, int WM, int KG, int NB, bool LOW, bool ADD>
 __global__ __launch_bounds__(512, 2)
 void packed_tile_kernel(PackedProduct p) {
+  if (*p.flag) return;
   typedef PackedTile<TN, TM, WN, WM, KG, NB, LOW> L;
   constexpr int RN = TN / WN / 16, RM = TM / WM / 16, LJ = L::LJ;
   extern __shared__ __align__(16) unsigned char smem[];
@@ -123,7 +115,7 @@ void packed_tile_kernel(PackedProduct p) {
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int i = lane & 15, kk = lane >> 4;
   const int kg = wave / (WN * WM), wn = wave / WM % WN, wm = wave % WM;
-  const int first = blockIdx.y * p.per, blocks = min(p.per, p.blocks - first), nst = (blocks + KG - 1) / KG;
+  const int blocks = p.blocks, nst = (blocks + KG - 1) / KG;
 
   // Staging: an instruction brings 16 lines of a plane; the four 16-byte pieces of line r are in the order piece ^ f(r / 4 & 3),
   // f = 0, 2, 3, 1, so that 16 lanes that read one piece of 16 lines, or two neighbouring pieces of eight each, meet 16
@@ -140,7 +132,7 @@ void packed_tile_kernel(PackedProduct p) {
 #pragma unroll
     for (int j = 0; j < LJ; ++j) {
       const int at = j * 8 + wave, unit = at < L::NX ? at * 16 / TM : (at - L::NX) * 16 / TN;      // (group, plane)
-      const int b = first + min(st * KG + (unit >> 1), blocks - 1);
+      const int b = min(st * KG + (unit >> 1), blocks - 1);
       const unsigned char* base = at < L::NX ? p.x + ((size_t)b * 2 + (unit & 1)) * p.rows * 64 : p.w + ((size_t)b * 2 + (unit & 1)) * p.N * 64;
       load_lds16(base + off[j], to + j * 8192);
     }
@@ -209,64 +201,59 @@ void packed_tile_kernel(PackedProduct p) {
       for (int b = 0; b < RM; ++b) mine[(a * RM + b) * 64] = acc[a][b];
     __syncthreads();
   }
-  auto finish = [&](auto add) {
-    constexpr bool ADD = decltype(add)::value;
-    // What a sum is added to: the loads of eight blocks in flight together.  One by one, each behind the last one's stores: 16384 x 4096 x 1024
-    // in a stack 324 us, so 297; x 1024 x 1024 131, so 98 (without the adding 85)
-    constexpr int BATCH = ADD && SHARE > 8 ? 8 : SHARE;
+  // What a sum is added to: the loads of eight blocks in flight together.  One by one, each behind the last one's stores: 16384 x 4096 x 1024
+  // in a stack 324 us, so 297; x 1024 x 1024 131, so 98 (without the adding 85)
+  constexpr int BATCH = ADD && SHARE > 8 ? 8 : SHARE;
 #pragma unroll
-    for (int k0 = 0; k0 < SHARE; k0 += BATCH) {
-      floatx4 was[ADD ? BATCH : 1][2];
-      auto place = [&](int k, int& row, int& n) {
-        const int at = kg * SHARE + k, a = at / RM * 2, b = at % RM;
-        row = row0 + wm * RM * 16 + b * 16 + i, n = n0 + wn * RN * 16 + a * 16 + 16 * (kk & 1) + 8 * (kk >> 1);
-        return !(PAIRS % KG && at >= PAIRS) && row < p.rows && n < p.N;
-      };
-      int row, n;
-      if constexpr (ADD)
+  for (int k0 = 0; k0 < SHARE; k0 += BATCH) {
+    floatx4 was[ADD ? BATCH : 1][2];
+    auto place = [&](int k, int& row, int& n) {
+      const int at = kg * SHARE + k, a = at / RM * 2, b = at % RM;
+      row = row0 + wm * RM * 16 + b * 16 + i, n = n0 + wn * RN * 16 + a * 16 + 16 * (kk & 1) + 8 * (kk >> 1);
+      return !(PAIRS % KG && at >= PAIRS) && row < p.rows && n < p.N;
+    };
+    int row, n;
+    if constexpr (ADD)
 #pragma unroll
-        for (int k = 0; k < BATCH; ++k)
-          if (k0 + k < SHARE && place(k0 + k, row, n)) {
-            const floatx4* from = reinterpret_cast<const floatx4*>(place8(p, row, n, blockIdx.y));
-            was[k][0] = from[0];
-            was[k][1] = from[1];
-          }
-#pragma unroll
-      for (int k = k0; k < k0 + BATCH && k < SHARE; ++k) {
-        floatx4 lo, hi;
-        float v[8];
-        const int at = kg * SHARE + k, a = at / RM * 2, b = at % RM;
-        if (PAIRS % KG && at >= PAIRS) break;
-        if constexpr (KG == 1) {
-          lo = acc[k / RM * 2][k % RM];
-          hi = acc[k / RM * 2 + 1][k % RM];
-        } else {
-          lo = hi = floatx4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-          for (int q = 0; q < KG; ++q) {
-            const floatx4* from = part + q * (WN * WM * RN * RM * 64) + (a * RM + b) * 64;
-            lo += from[0];
-            hi += from[RM * 64];
-          }
+      for (int k = 0; k < BATCH; ++k)
+        if (k0 + k < SHARE && place(k0 + k, row, n)) {
+          const floatx4* from = reinterpret_cast<const floatx4*>(static_cast<const float*>(p.out) + (size_t)row * p.N + n);
+          was[k][0] = from[0];
+          was[k][1] = from[1];
         }
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          auto s = __builtin_amdgcn_permlane16_swap(__float_as_uint(lo[e]), __float_as_uint(hi[e]), false, false);
-          v[e] = __uint_as_float(s[0]);
-          v[4 + e] = __uint_as_float(s[1]);
+    for (int k = k0; k < k0 + BATCH && k < SHARE; ++k) {
+      floatx4 lo, hi;
+      float v[8];
+      const int at = kg * SHARE + k, a = at / RM * 2, b = at % RM;
+      if (PAIRS % KG && at >= PAIRS) break;
+      if constexpr (KG == 1) {
+        lo = acc[k / RM * 2][k % RM];
+        hi = acc[k / RM * 2 + 1][k % RM];
+      } else {
+        lo = hi = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int q = 0; q < KG; ++q) {
+          const floatx4* from = part + q * (WN * WM * RN * RM * 64) + (a * RM + b) * 64;
+          lo += from[0];
+          hi += from[RM * 64];
         }
-        if (place(k, row, n)) finish8<ADD>(p, row, n, blockIdx.y, v, was[ADD ? k - k0 : 0][0], was[ADD ? k - k0 : 0][1]);
       }
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        auto s = __builtin_amdgcn_permlane16_swap(__float_as_uint(lo[e]), __float_as_uint(hi[e]), false, false);
+        v[e] = __uint_as_float(s[0]);
+        v[4 + e] = __uint_as_float(s[1]);
+      }
+      if (place(k, row, n)) finish8<ADD>(p, row, n, v, was[ADD ? k - k0 : 0][0], was[ADD ? k - k0 : 0][1]);
     }
-  };
-  if (p.epilogue == 2) finish(std::true_type{});
-  else finish(std::false_type{});
+  }
 }
 
-template <int TN, int TM, int WN, int WM, int KG, int NB, bool LOW>
-hipError_t launch_tile(PackedProduct p, int S, hipStream_t st) {
+template <int TN, int TM, int WN, int WM, int KG, int NB, bool LOW, bool ADD>
+hipError_t launch_tile(PackedProduct p, hipStream_t st) {
   typedef PackedTile<TN, TM, WN, WM, KG, NB, LOW> L;
-  auto kern = packed_tile_kernel<TN, TM, WN, WM, KG, NB, LOW>;
+  auto kern = packed_tile_kernel<TN, TM, WN, WM, KG, NB, LOW, ADD>;
   static bool done[64] = {};
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) dev = 0;
@@ -276,170 +263,178 @@ hipError_t launch_tile(PackedProduct p, int S, hipStream_t st) {
     done[dev] = true;
   }
   p.tiles_m = (p.rows + TM - 1) / TM, p.tiles_n = (p.N + TN - 1) / TN;
-  p.per = (p.blocks + S - 1) / S;
   const long long tiles = (long long)p.tiles_m * p.tiles_n;
-  hipLaunchKernelGGL(kern, dim3((unsigned)((tiles + 7) / 8 * 8), S), dim3(512), L::LDS, st, p);
+  hipLaunchKernelGGL(kern, dim3((unsigned)((tiles + 7) / 8 * 8)), dim3(512), L::LDS, st, p);
   return hipGetLastError();
 }
 
-// ---- Weights: 32 columns x 256 indices per workgroup; the largest value of each column, then (WRITE) its scale and the terms.
-constexpr float kSmall = 0.125f;               // scaled values from here on are held to 2^-22 of themselves
-constexpr int kFew = 6;                        // ... of 256 neighbouring ones of a column that may be smaller
-
-__global__ __launch_bounds__(256)
-void clear_kernel(float* a, int n) {
-  const int i = blockIdx.x * 256 + threadIdx.x;
-  if (i < n) a[i] = 0.f;
-}
-
-// most: [N] bits of the columns' largest values on the way in, 1 / scale on the way out of `finish_scales_kernel`
-template <bool KC, bool WRITE>
-__global__ __launch_bounds__(256)
-void pack_weights_kernel(const float* __restrict__ P, const float* __restrict__ row_scale, unsigned char* __restrict__ packed,
-                         uint32_t* most, int32_t* __restrict__ verdict, int d, int h, int kv) {
-  __shared__ uint32_t tally[32];               // largest values, or counts of small ones
-  const int C = KC ? h * kv : d, N = KC ? d : h * kv;
-  if (threadIdx.x < 32) tally[threadIdx.x] = 0;
-  __syncthreads();
-  bool bad = false;
-#pragma unroll
-  for (int u = 0; u < 4; ++u) {                // neighbouring lanes where the weights are contiguous
-    const int j = KC ? (threadIdx.x >> 5) + 8 * u : threadIdx.x & 31, o = blockIdx.y * 32 + (KC ? threadIdx.x & 31 : (threadIdx.x >> 5) + 8 * u);
-    const int n = blockIdx.x * 32 + j, c = 8 * o;
-    if (n >= N || c >= C) continue;            // (C is a multiple of 32, and eight indices stay inside one head: kv % 8 == 0)
-    const float* at = KC ? P + (size_t)(c / kv) * d * kv + (size_t)n * kv + c % kv : P + (size_t)(n / kv) * d * kv + (size_t)c * kv + n % kv;
-    float v[8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) v[e] = at[KC ? e : (size_t)e * kv] * (row_scale ? row_scale[c + e] : 1.f);
-    if constexpr (!WRITE) {
-      float peak = 0.f;
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        bad |= !(fabsf(v[e]) < 0x1p100f);      // (a NaN, too)
-        peak = fmaxf(peak, fabsf(v[e]));
-      }
-      bad |= peak > 0.f && peak < 0x1p-100f;   // (so small that the scale is not there)
-      atomicMax(&tally[j], __float_as_uint(peak));
-    } else {
-      const float m = __uint_as_float(most[n]), scale = split_scale(m > 0.f ? m : 1.f, 14);
-      int few = 0;
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        v[e] *= scale;
-        few += v[e] != 0.f && fabsf(v[e]) < kSmall ? 1 : 0;
-      }
-      if (few) atomicAdd(&tally[j], (uint32_t)few);
-      store_packed8(packed + ((size_t)(o >> 2) * 2 * N + n) * 64 + (o & 3) * 16, (size_t)N * 64, v);
-    }
-  }
-  __syncthreads();
-  if (threadIdx.x < 32) {
-    const int n = blockIdx.x * 32 + threadIdx.x;
-    if constexpr (WRITE) bad = tally[threadIdx.x] > kFew;
-    else if (n < N) atomicMax(&most[n], tally[threadIdx.x]);
-  }
-  if (bad) *verdict = 1;                       // (whoever finds it writes the same)
-}
-__global__ __launch_bounds__(256)
-void finish_scales_kernel(float* most, int n) {
-  const int i = blockIdx.x * 256 + threadIdx.x;
-  if (i < n) most[i] = 1.f / split_scale(most[i] > 0.f ? most[i] : 1.f, 14);
-}
-
-}  // namespace
-
-// Tiles, what a round of 256 of them takes for 1024 indices (us; measured, many rows and all parts in one round), and the relative
-// error of a sum of 1024 normal deviates (x 1e-7; it grows with the root of the length).
-struct PackedForm { int TN, TM; double us, error; };
-static const PackedForm kForms[] = {{256, 256, 70, 3.57}, {256, 128, 42, 2.19}, {128, 128, 23.5, 1.68}, {128, 64, 15, 1.68}, {64, 64, 8.2, 1.38}, {128, 32, 9, 1.38}};
-constexpr int kPackedForms = 6;
-
-bool packed_fits(int rows, int N, int C) {
-  return rows > 0 && N > 0 && C > 0 && C % 32 == 0 && N % 8 == 0 && C <= 1 << 24 && rows <= 1 << 25 && N <= 1 << 25;      // (32-bit offsets inside a plane)
-}
-
-// The form and the parts of the contraction (1: none) that take the least time here, by
-//   4 us + rounds of 256 tiles x `us` x C / 1024 / parts + 0.4 us per MiB of parts (what a launch that reads the row anyway spends on them),
-// among those whose error is no larger than `error` (x 1e-7 for 1024 terms of a chain, `length` of them in it); -1: none.
-int packed_form(int rows, int N, int C, bool parts, double error, int length) {
-  int best = -1;
-  double least = 1e30;
-  for (int f = 0; f < kPackedForms; ++f)
-    for (int S = 1; S <= (parts ? 8 : 1) && (S == 1 || C >= 256 * S); S *= 2) {
-      const int blocks = C / 32, per = (blocks + S - 1) / S;
-      if (S > 1 && (blocks + per - 1) / per != S) continue;             // (no empty parts)
-      const double len = 32. * per > 512. ? 32. * per : 512., len0 = length > 512 ? length : 512.;
-      if (kForms[f].error * sqrt(len) > error * sqrt(len0)) continue;
-      const double tiles = (double)((N + kForms[f].TN - 1) / kForms[f].TN) * ((rows + kForms[f].TM - 1) / kForms[f].TM) * S;
-      const double us = 4. + ceil(tiles / 256.) * kForms[f].us * 32. * per / 1024. + (S > 1 ? 0.4 * S * rows * (double)N / 262144. : 0.);
-      if (us < least) least = us, best = 16 * f + S;
-    }
-  return best;
-}
-
-// The form of a stack's product of packed operands, 16 x its number + parts; 0 where it stays with the kernels that read the float32 weights:
-// a product of few rows that is one of three exact terms there (project_terms.hip), whose error two terms do not reach, and
-// sizes without a form.  residual: x += product, layernorm follows (mqa_project_add_layernorm's sizes).
-int packed_plan(int mode, int rows, int d, int h, int kv, int residual) {
-  const bool outp = mode == 3;
-  if ((long long)h * kv > 1 << 24) return 0;
-  const int N = outp ? d : h * kv, C = outp ? h * kv : d;
-  if (!packed_fits(rows, N, C) || C < 64 || (residual && N > 4096)) return 0;
-  int edge = 0, length = C;
-  if (residual) {
-    const TermsForm f = terms_parts_form(outp, rows, d, h, kv);
-    if (f.S && f.RB != 8) return 0;
-    if (f.S) edge = 128, length = (C + f.S - 1) / f.S;
-  }
-  if (!edge) {
-    if (terms_form(outp, rows, d, h, kv).S) return 0;
-    edge = gemm_form(mode, rows, d, h, kv, 0);
-  }
-  const double error = edge == 256 ? 3.62 : edge == 128 ? 2.65 : edge == 64 ? 2.0 : edge == 32 ? 1.6 : 2.07;      // (of 1024 terms: gemm.hip, project.hip)
-  if (!edge && (double)N * C < 8e6) return 0;  // (few rows: 16 x 1024 x 4096 6.3 there, 7.5 here; 1 x 1024 x 32768 26.4 / 24)
-  const int form = packed_form(rows, N, C, residual, error, length);
-  return form < 0 ? 0 : form;
-}
-
-hipError_t launch_packed_product(const void* x, const void* w, float scale, void* out, int rows, int N, int C, int epilogue, int form,
-                                 hipStream_t st) {
-  const unsigned char* wp = static_cast<const unsigned char*>(w);
-  const PackedProduct p{static_cast<const unsigned char*>(x), wp, reinterpret_cast<const float*>(wp + packed_bytes(N, C)), scale, out, rows, N, C / 32, epilogue, 0, 0, 0};
-  const int S = form & 15;
-  switch (form >> 4) {
-    case 0: return launch_tile<256, 256, 4, 2, 1, 2, false>(p, S, st);
-    case 1: return launch_tile<256, 128, 4, 2, 1, 3, true>(p, S, st);
-    case 2: return launch_tile<128, 128, 2, 2, 2, 2, true>(p, S, st);
-    case 3: return launch_tile<128, 64, 2, 2, 2, 3, true>(p, S, st);
-    case 4: return launch_tile<64, 64, 2, 1, 4, 2, true>(p, S, st);
-    case 5: return launch_tile<128, 32, 2, 1, 4, 2, true>(p, S, st);
+template <bool ADD>
+hipError_t launch_product(const PackedProduct& p, int form, hipStream_t st) {
+  switch (form) {
+    case 0: return launch_tile<256, 256, 4, 2, 1, 2, false, ADD>(p, st);
+    case 1: return launch_tile<256, 128, 4, 2, 1, 3, true, ADD>(p, st);
+    case 2: return launch_tile<128, 128, 2, 2, 2, 2, true, ADD>(p, st);
   }
   return hipErrorNotSupported;
 }
 
-hipError_t launch_pack_weights(bool outp, const float* P, const float* row_scale, void* packed, int32_t* verdict, int d, int h, int kv, hipStream_t st) {
-  const int N = outp ? d : h * kv, C = outp ? h * kv : d;
-  unsigned char* to = static_cast<unsigned char*>(packed);
-  float* scales = reinterpret_cast<float*>(to + packed_bytes(N, C));
-  uint32_t* most = reinterpret_cast<uint32_t*>(scales);
-  const dim3 grid((N + 31) / 32, (C + 255) / 256), lines((N + 255) / 256), block(256);
-  hipLaunchKernelGGL(clear_kernel, lines, block, 0, st, scales, N);
-  if (outp) {
-    hipLaunchKernelGGL((pack_weights_kernel<true, false>), grid, block, 0, st, P, row_scale, to, most, verdict, d, h, kv);
-    hipLaunchKernelGGL((pack_weights_kernel<true, true>), grid, block, 0, st, P, row_scale, to, most, verdict, d, h, kv);
-  } else {
-    hipLaunchKernelGGL((pack_weights_kernel<false, false>), grid, block, 0, st, P, row_scale, to, most, verdict, d, h, kv);
-    hipLaunchKernelGGL((pack_weights_kernel<false, true>), grid, block, 0, st, P, row_scale, to, most, verdict, d, h, kv);
+// ---- Weights [C][N]: 32 columns x 256 indices per workgroup, four columns x eight indices per thread, all loads in flight together (in single
+// words 14 us for 1024 x 4096, so 6); first the largest value of each column, then (WRITE) the terms.
+constexpr float kSmall = 0.125f;               // scaled values from here on are held to 2^-22 of themselves
+constexpr int kFew = 6;                        // ... of 256 neighbouring ones of a column that may be smaller
+
+__global__ __launch_bounds__(256)
+void clear_kernel(uint32_t* a, int n) {
+  const int i = blockIdx.x * 256 + threadIdx.x;
+  if (i < n) a[i] = 0;
+}
+
+struct PackWeights {
+  const float* P;
+  const uint32_t* before;      // NULL, or the largest values of the columns of the weights before these, whose scales the rows are divided by
+  unsigned char* packed;
+  uint32_t* most;
+  int C, N, tiles_n;           // (C and N are multiples of 32)
+};
+
+template <bool WRITE>
+__device__ __forceinline__ void pack_tile(const PackWeights& p, int tile, int32_t* flag, uint32_t* tally) {
+  const int n0 = tile % p.tiles_n * 32, o = tile / p.tiles_n * 32 + (threadIdx.x >> 3), q = threadIdx.x & 7, n = n0 + 4 * q, c = 8 * o;
+  if (threadIdx.x < 32) tally[threadIdx.x] = 0;      // largest values, or counts of small ones
+  __syncthreads();
+  bool bad = false;
+  if (c < p.C) {
+    floatx4 v[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[e] = *reinterpret_cast<const floatx4*>(p.P + (size_t)(c + e) * p.N + n);
+    if (p.before) {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) v[e] *= 1.f / column_scale(p.before[c + e]);
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      if constexpr (!WRITE) {
+        float peak = 0.f;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          bad |= !(fabsf(v[e][j]) < 0x1p100f);      // (a NaN, too)
+          peak = fmaxf(peak, fabsf(v[e][j]));
+        }
+        bad |= peak > 0.f && peak < 0x1p-100f;      // (so small that the scale is not there)
+        atomicMax(&tally[4 * q + j], __float_as_uint(peak));
+      } else {
+        const float scale = column_scale(p.most[n + j]);
+        float t[8];
+        int few = 0;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          t[e] = v[e][j] * scale;
+          few += t[e] != 0.f && fabsf(t[e]) < kSmall ? 1 : 0;
+        }
+        if (few) atomicAdd(&tally[4 * q + j], (uint32_t)few);
+        store_packed8(p.packed + ((size_t)(o >> 2) * 2 * p.N + n + j) * 64 + (o & 3) * 16, (size_t)p.N * 64, t);
+      }
+    }
   }
-  hipLaunchKernelGGL(finish_scales_kernel, lines, block, 0, st, scales, N);
-  return hipGetLastError();
+  __syncthreads();
+  if (threadIdx.x < 32) {
+    if constexpr (WRITE) bad = tally[threadIdx.x] > kFew;
+    else atomicMax(&p.most[n0 + threadIdx.x], tally[threadIdx.x]);
+  }
+  if (bad) *flag = 1;                          // (whoever finds it writes the same)
+}
+
+// `first` tiles: the largest values of `look`; then the terms of `write`
+__global__ __launch_bounds__(256)
+void pack_kernel(PackWeights look, PackWeights write, int first, int32_t* flag) {
+  __shared__ uint32_t tally[32];
+  if (*flag) return;                           // (not to be used: the same for all that matters)
+  if ((int)blockIdx.x < first) pack_tile<false>(look, blockIdx.x, flag, tally);
+  else pack_tile<true>(write, blockIdx.x - first, flag, tally);
+}
+
+// Tiles, what a round of 256 of them takes for 1024 indices (us; measured), and the relative error of a sum of 1024 normal deviates
+// (x 1e-7; it grows with the root of the length).
+struct PackedForm { int TN, TM; double us, error; };
+const PackedForm kForms[] = {{256, 256, 70, 3.57}, {256, 128, 42, 2.19}, {128, 128, 23.5, 1.68}};
+
+// The form that takes the least time, rounds of 256 tiles x `us` x C / 1024, among those whose error is no larger than gemm.hip's
+// in tiles of this edge; -1: none.
+int packed_form(int rows, int N, int C, int edge) {
+  const double error = edge == 256 ? 3.62 : edge == 128 ? 2.65 : 0.;
+  int best = -1;
+  double least = 0.;
+  for (int f = 0; f < 3; ++f) {
+    if (kForms[f].error > error) continue;
+    const double tiles = (double)((N + kForms[f].TN - 1) / kForms[f].TN) * ((rows + kForms[f].TM - 1) / kForms[f].TM);
+    const double us = ceil(tiles / 256.) * kForms[f].us;
+    if (best < 0 || us < least) least = us, best = f;
+  }
+  return best;
 }
 
 // log2 of what a packed layernorm row of N columns is scaled by: sqrt(N) comes to 2^15 at most
-int packed_layernorm_exponent(int N) {
+int layernorm_exponent(int N) {
   int s = 15;
   while (s > 0 && ldexp(1., 2 * (15 - s)) < N) --s;
   return s;
+}
+
+// A call's workspace, in bytes from its beginning: the flag and the columns' largest values, the packed weights, then the packed (or, where those
+// are not to be used, the float32) layernorm and hidden rows.
+struct Places {
+  size_t most1, most2, w1, w2, rows, hidden, bytes;
+  Places(int rows_, int d, int ff) {
+    most1 = 16, most2 = most1 + 4 * (size_t)ff, w1 = most2 + 4 * (size_t)d, w2 = w1 + 4 * (size_t)d * ff, rows = w2 + 4 * (size_t)d * ff;
+    hidden = rows + 4 * (size_t)rows_ * d, bytes = hidden + 4 * (size_t)rows_ * ff;
+  }
+};
+
+}  // namespace
+
+FeedForwardPlan feed_forward_plan(int rows, int d, int ff) {
+  FeedForwardPlan f{};
+  if (rows <= 0 || d <= 0 || ff <= 0 || (d & 31) || (ff & 31) || d > 4096 || ff > 1 << 20 || rows > 1 << 25) return f;      // (32-bit offsets inside a plane)
+  f.edge1 = gemm_edge(rows, ff, d), f.edge2 = gemm_edge(rows, d, ff);
+  f.form1 = packed_form(rows, ff, d, f.edge1), f.form2 = packed_form(rows, d, ff, f.edge2);
+  if (f.form1 < 0 || f.form2 < 0) return f;
+  f.bytes = Places(rows, d, ff).bytes;
+  // The weights cost as much for few rows as for many: 30 us for 2 x 1024 x 4096, and the launches that do nothing 15.  us, the three calls / this, values
+  // that two terms hold | do not: 16384 x 1024 x 4096 849 / 692 | 841 / 894, 6000 432 / 340 | 431 / 475, 4000 243 / 215, 2500 199 / 195; 16384 x 512 x 2048
+  // 273 / 221, 8192 141 / 132; 6000 x 768 x 3072 333 / 273; 8192 x 1280 x 2048 314 / 287, 4000 x 1280 x 5120 511 / 418, 2500 258 / 247.
+  f.faster = rows >= 4096 && (double)rows * d * ff >= 12e9 ? 1 : 0;
+  return f;
+}
+
+// x += relu(layernorm(x) . W1) . W2 from a workspace of the plan's size
+hipError_t launch_feed_forward(const FeedForwardPlan& f, const float* W1, const float* W2, float* x, int rows, int d, int ff, float eps, void* workspace,
+                               hipStream_t st) {
+  unsigned char* const ws = static_cast<unsigned char*>(workspace);
+  const Places at(rows, d, ff);
+  int32_t* flag = reinterpret_cast<int32_t*>(ws);
+  uint32_t *most1 = reinterpret_cast<uint32_t*>(ws + at.most1), *most2 = reinterpret_cast<uint32_t*>(ws + at.most2);
+  const int ints = (int)(at.w1 / 4);
+  hipLaunchKernelGGL(clear_kernel, dim3((ints + 255) / 256), dim3(256), 0, st, reinterpret_cast<uint32_t*>(ws), ints);
+  const PackWeights one{W1, nullptr, ws + at.w1, most1, d, ff, ff / 32}, two{W2, most1, ws + at.w2, most2, ff, d, d / 32};
+  const int tiles1 = ff / 32 * ((d + 255) / 256), tiles2 = d / 32 * ((ff + 255) / 256);
+  hipLaunchKernelGGL(pack_kernel, dim3(tiles1), dim3(256), 0, st, one, one, tiles1, flag);
+  hipLaunchKernelGGL(pack_kernel, dim3(tiles2 + tiles1), dim3(256), 0, st, two, one, tiles2, flag);
+  hipLaunchKernelGGL(pack_kernel, dim3(tiles2), dim3(256), 0, st, two, two, 0, flag);
+  const int s = layernorm_exponent(d);
+  hipError_t e = launch_layernorm_packed(flag, x, ws + at.rows, ldexpf(1.f, s), rows, d, eps, st);
+  if (e != hipSuccess) return e;
+  // |hx 2^s . W1| <= sqrt(d) 2^s sqrt(d) 2^15 (the columns' largest values are below 2^15), and sqrt(d) 2^s <= 2^15: the hidden rows come to 2^15 at most
+  PackedProduct p{flag, ws + at.rows, ws + at.w1, most1, ldexpf(1.f, s - 30), ws + at.hidden, rows, ff, d / 32, 0, 0};
+  e = launch_product<false>(p, f.form1, st);
+  if (e != hipSuccess) return e;
+  p = PackedProduct{flag, ws + at.hidden, ws + at.w2, most2, ldexpf(1.f, 30 - 2 * s), x, rows, d, ff / 32, 0, 0};
+  e = launch_product<true>(p, f.form2, st);
+  if (e != hipSuccess) return e;
+  float *hx = reinterpret_cast<float*>(ws + at.rows), *u = reinterpret_cast<float*>(ws + at.hidden);
+  e = launch_layernorm_if(flag, x, hx, rows, d, eps, st);
+  if (e == hipSuccess) e = launch_gemm_if(flag, f.edge1, hx, W1, u, rows, d, ff, 1, st);
+  if (e == hipSuccess) e = launch_gemm_if(flag, f.edge2, u, W2, x, rows, ff, d, 2, st);
+  return e;
 }
 
 }  // namespace mqa

@@ -275,12 +275,11 @@ __device__ __forceinline__ float block_sum(float x, float* red) {
   return red[0] + red[1] + red[2] + red[3];
 }
 
-// x[row] += the sum of the row's S partial products (in order: the same every time); y[row] = layernorm(x[row]) (gain 1, bias 0), packed beside it
-// or in its place.  One workgroup per row of
+// x[row] += the sum of the row's S partial products (in order: the same every time); y[row] = layernorm(x[row]) (gain 1, bias 0).  One workgroup per row of
 // at most 1024 NV columns, all loads in flight together.
 template <int NV>
 __global__ __launch_bounds__(256)
-void finish_kernel(const float* __restrict__ part, float* x, float* __restrict__ y, unsigned char* __restrict__ packed, float scale, int rows, int N, int S, float eps) {
+void finish_kernel(const float* __restrict__ part, float* x, float* __restrict__ y, int rows, int N, int S, float eps) {
   __shared__ float red[4];
   const int n4 = N >> 2;
   floatx4* xr = reinterpret_cast<floatx4*>(x + (size_t)blockIdx.x * N);
@@ -319,9 +318,7 @@ void finish_kernel(const float* __restrict__ part, float* x, float* __restrict__
     const int at = threadIdx.x + 256 * u;
     if (at < n4) {
       xr[at] = v[u];
-      const floatx4 n = (v[u] - mean) * rstd;
-      if (y) yr[at] = n;
-      if (packed) store_packed4(packed, scale, rows, blockIdx.x, 4 * at, n[0], n[1], n[2], n[3]);
+      yr[at] = (v[u] - mean) * rstd;
     }
   }
 }
@@ -441,19 +438,8 @@ hipError_t launch_project_terms(bool outp, const float* in, const float* P, floa
   return f.S ? launch_tiles(outp, f, in, P, out, nullptr, rows, d, h, kv, epilogue, st) : hipErrorNotSupported;
 }
 
-hipError_t launch_finish(const float* part, int S, float* x, float* y, void* packed, int rows, int N, float eps, hipStream_t st) {
-  unsigned char* to = static_cast<unsigned char*>(packed);
-  const float scale = ldexpf(1.f, packed_layernorm_exponent(N));
-  if (N <= 1024) hipLaunchKernelGGL(finish_kernel<1>, dim3(rows), dim3(256), 0, st, part, x, y, to, scale, rows, N, S, eps);
-  else if (N <= 2048) hipLaunchKernelGGL(finish_kernel<2>, dim3(rows), dim3(256), 0, st, part, x, y, to, scale, rows, N, S, eps);
-  else if (N <= 4096) hipLaunchKernelGGL(finish_kernel<4>, dim3(rows), dim3(256), 0, st, part, x, y, to, scale, rows, N, S, eps);
-  else return hipErrorNotSupported;
-  return hipGetLastError();
-}
-
-// x += in . B, y = layernorm(x), in two launches; workspace: terms_parts_bytes(...).  packed: the layernorm as a packed matrix, too, or instead
-// (y null).  hipErrorNotSupported: no form (terms_parts_form)
-hipError_t launch_project_add_layernorm(bool outp, const float* in, const float* P, float* x, float* y, void* packed, int rows, int d, int h, int kv,
+// x += in . B, y = layernorm(x), in two launches; workspace: terms_parts_bytes(...).  hipErrorNotSupported: no form (terms_parts_form)
+hipError_t launch_project_add_layernorm(bool outp, const float* in, const float* P, float* x, float* y, int rows, int d, int h, int kv,
                                         float eps, void* workspace, hipStream_t st) {
   const TermsForm f = terms_parts_form(outp, rows, d, h, kv);
   if (!f.S) return hipErrorNotSupported;
@@ -462,7 +448,10 @@ hipError_t launch_project_add_layernorm(bool outp, const float* in, const float*
   const hipError_t e = f.RB == 8 ? launch_gemm_parts(outp ? 3 : 0, in, P, part, rows, d, h, kv, 0, 128, f.S, st)
                                  : launch_tiles(outp, f, in, P, nullptr, part, rows, d, h, kv, 0, st);
   if (e != hipSuccess) return e;
-  return launch_finish(part, f.S, x, y, packed, rows, N, eps, st);
+  if (N <= 1024) hipLaunchKernelGGL(finish_kernel<1>, dim3(rows), dim3(256), 0, st, part, x, y, rows, N, f.S, eps);
+  else if (N <= 2048) hipLaunchKernelGGL(finish_kernel<2>, dim3(rows), dim3(256), 0, st, part, x, y, rows, N, f.S, eps);
+  else hipLaunchKernelGGL(finish_kernel<4>, dim3(rows), dim3(256), 0, st, part, x, y, rows, N, f.S, eps);
+  return hipGetLastError();
 }
 
 }  // namespace mqa

@@ -5,8 +5,6 @@
 // All float32; one workgroup (256 threads) per row.
 #include "common.hpp"
 
-#include <math.h>
-
 namespace mqa {
 namespace {
 
@@ -40,12 +38,12 @@ void layernorm_kernel(const float* __restrict__ x, float* __restrict__ y, int d,
 // The same for rows of a multiple of 4 and at most 256 * 4 * NV floats: the row is read once, with
 // 16-byte loads all in flight together, and kept in registers for the mean, the centred sum of
 // squares and the result (the rows of a decode step are few: the launch is one memory round trip).
-template <int NV>
-__global__ __launch_bounds__(256)
-void layernorm_rows_kernel(const float* __restrict__ x, float* __restrict__ y, unsigned char* __restrict__ packed, float scale, int d, float eps) {
-  __shared__ float red[4];
-  const float4* xr = reinterpret_cast<const float4*>(x + (size_t)blockIdx.x * d);
-  float4* yr = reinterpret_cast<float4*>(y + (size_t)blockIdx.x * d);
+// PACKED: they leave as two fp16 terms of `scale` times them (packed.hip) in the place of float32.
+template <int NV, bool PACKED>
+__device__ __forceinline__ void layernorm_row(const float* __restrict__ x, float* __restrict__ y, unsigned char* __restrict__ packed, float scale, int rows, int row,
+                                              int d, float eps, float* red) {
+  const float4* xr = reinterpret_cast<const float4*>(x + (size_t)row * d);
+  float4* yr = reinterpret_cast<float4*>(y + (size_t)row * d);
   const int d4 = d >> 2;
   float4 r[NV];
 #pragma unroll
@@ -68,12 +66,34 @@ void layernorm_rows_kernel(const float* __restrict__ x, float* __restrict__ y, u
 #pragma unroll
   for (int u = 0; u < NV; ++u) {
     const int i = threadIdx.x + 256 * u;
-    if (i < d4) {
-      const float4 n = make_float4((r[u].x - mean) * rstd, (r[u].y - mean) * rstd, (r[u].z - mean) * rstd, (r[u].w - mean) * rstd);
-      if (y) yr[i] = n;
-      if (packed) store_packed4(packed, scale, gridDim.x, blockIdx.x, 4 * i, n.x, n.y, n.z, n.w);
-    }
+    if (i >= d4) continue;
+    const float4 n = make_float4((r[u].x - mean) * rstd, (r[u].y - mean) * rstd, (r[u].z - mean) * rstd, (r[u].w - mean) * rstd);
+    if constexpr (PACKED) store_packed4(packed, scale, rows, row, 4 * i, n.x, n.y, n.z, n.w);
+    else yr[i] = n;
   }
+}
+template <int NV>
+__global__ __launch_bounds__(256)
+void layernorm_rows_kernel(const float* __restrict__ x, float* __restrict__ y, int d, float eps) {
+  __shared__ float red[4];
+  layernorm_row<NV, false>(x, y, nullptr, 0.f, 0, blockIdx.x, d, eps, red);
+}
+// Every XCD takes a run of neighbouring rows: two of them share a 128-byte line of the packed matrix (16384 x 1024: 44 -> 23 us).  *flag: not to be.
+template <int NV>
+__global__ __launch_bounds__(256)
+void layernorm_packed_kernel(const int32_t* __restrict__ flag, const float* __restrict__ x, unsigned char* __restrict__ packed, float scale, int rows, int d, float eps) {
+  __shared__ float red[4];
+  const int row = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
+  if (*flag || row >= rows) return;
+  layernorm_row<NV, true>(x, nullptr, packed, scale, rows, row, d, eps, red);
+}
+// ... if *only is not 0 (few workgroups, so that nothing costs little)
+template <int NV>
+__global__ __launch_bounds__(256)
+void layernorm_if_kernel(const int32_t* __restrict__ only, const float* __restrict__ x, float* __restrict__ y, int rows, int d, float eps) {
+  __shared__ float red[4];
+  if (*only == 0) return;
+  for (int row = blockIdx.x; row < rows; row += gridDim.x) layernorm_row<NV, false>(x, y, nullptr, 0.f, 0, row, d, eps, red);      // (block_sum begins with a barrier)
 }
 
 // x[row] = E[token[row]] + P[pos[row]]; indices outside the tables are clamped (they live on the
@@ -148,15 +168,27 @@ void argmax_kernel(const float* __restrict__ x, int32_t* __restrict__ out, int n
 
 }  // namespace
 
-hipError_t launch_layernorm(const float* x, float* y, void* packed, int rows, int d, float eps, hipStream_t st) {
-  unsigned char* to = static_cast<unsigned char*>(packed);
-  const float scale = ldexpf(1.f, packed_layernorm_exponent(d));
-  if ((d & 3) == 0 && d <= 1024) hipLaunchKernelGGL(layernorm_rows_kernel<1>, dim3(rows), dim3(256), 0, st, x, y, to, scale, d, eps);
-  else if ((d & 3) == 0 && d <= 4096) hipLaunchKernelGGL(layernorm_rows_kernel<4>, dim3(rows), dim3(256), 0, st, x, y, to, scale, d, eps);
-  else if (packed) return hipErrorNotSupported;
+hipError_t launch_layernorm(const float* x, float* y, int rows, int d, float eps, hipStream_t st) {
+  if ((d & 3) == 0 && d <= 1024) hipLaunchKernelGGL(layernorm_rows_kernel<1>, dim3(rows), dim3(256), 0, st, x, y, d, eps);
+  else if ((d & 3) == 0 && d <= 4096) hipLaunchKernelGGL(layernorm_rows_kernel<4>, dim3(rows), dim3(256), 0, st, x, y, d, eps);
   else hipLaunchKernelGGL(layernorm_kernel, dim3(rows), dim3(256), 0, st, x, y, d, eps);
   return hipGetLastError();
 }
+
+hipError_t launch_layernorm_packed(const int32_t* flag, const float* x, unsigned char* packed, float scale, int rows, int d, float eps, hipStream_t st) {
+  const dim3 grid((rows + 7) / 8 * 8), block(256);
+  if (d <= 1024) hipLaunchKernelGGL(layernorm_packed_kernel<1>, grid, block, 0, st, flag, x, packed, scale, rows, d, eps);
+  else hipLaunchKernelGGL(layernorm_packed_kernel<4>, grid, block, 0, st, flag, x, packed, scale, rows, d, eps);
+  return hipGetLastError();
+}
+
+hipError_t launch_layernorm_if(const int32_t* only, const float* x, float* y, int rows, int d, float eps, hipStream_t st) {
+  const dim3 grid(rows < 2048 ? rows : 2048), block(256);
+  if (d <= 1024) hipLaunchKernelGGL(layernorm_if_kernel<1>, grid, block, 0, st, only, x, y, rows, d, eps);
+  else hipLaunchKernelGGL(layernorm_if_kernel<4>, grid, block, 0, st, only, x, y, rows, d, eps);
+  return hipGetLastError();
+}
+
 hipError_t launch_embed(const int32_t* tokens, const int32_t* pos, const float* E, const float* P, float* x,
                         int rows, int d, int vocab, int max_pos, hipStream_t st) {
   hipLaunchKernelGGL(embed_kernel, dim3(rows), dim3(256), 0, st, tokens, pos, E, P, x, d, vocab, max_pos);

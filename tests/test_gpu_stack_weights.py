@@ -57,7 +57,8 @@ def _same(stack, logits, fresh, prompts, n):
         assert torch.equal(stack.K[l], fresh.K[l]) and torch.equal(stack.V[l], fresh.V[l]) and torch.equal(stack.lens[l], fresh.lens[l])
 
 
-SIZES = [(4, 100, 2, 1024, 8, 64, 264), (3, 200, 2, 1024, 8, 96, 9000), (600, 1, 2, 512, 4, 64, 32768)]
+# prompts of some hundred and of some thousand rows (whose feed-forward packs its weights), steps of few and of many sequences
+SIZES = [(4, 100, 2, 1024, 8, 64, 264), (20, 40, 2, 512, 4, 2048, 9000), (600, 1, 2, 512, 4, 1024, 32768), (64, 128, 3, 1024, 2, 2048, 520)]
 
 
 @pytest.mark.parametrize("b, n, layers, d, h, ff, vocab", SIZES)
@@ -144,7 +145,7 @@ def _logits(m, stack, x):
     return m.mqa_project_qkvo(m.MQA_PROJ_O, m.mqa_stack_layernorm(x).view(-1, 1, stack.d), stack.E.view(1, -1, stack.d))
 
 
-@pytest.mark.parametrize("b, n, d, h, ff, vocab", [(4, 100, 1024, 8, 64, 264), (3, 200, 1024, 8, 96, 9000), (1, 50, 1024, 8, 64, 32768), (2, 5, 64, 40, 128, 264)])
+@pytest.mark.parametrize("b, n, d, h, ff, vocab", [(4, 100, 1024, 8, 64, 264), (3, 200, 1024, 8, 1024, 9000), (20, 40, 512, 2, 2048, 400), (1, 50, 1024, 8, 512, 32768), (2, 5, 64, 40, 128, 264)])
 def test_prompt_is_its_calls(m, b, n, d, h, ff, vocab):
     """Up to some thousand rows a prompt is what the public calls make of the float32 weights, bit for bit: every product in their precision."""
     from paper_1911_02150_amd.decoder_stack import DecoderStack
@@ -162,3 +163,27 @@ def test_logits_are_their_call(m, b):
     stack = DecoderStack(_weights(b, 1, 1024, 2, 64, 32768, 4), b, 4, False, DEV)
     x = torch.from_numpy(np.random.default_rng(b).standard_normal((b, 1024), dtype=np.float32)).to(DEV)
     assert torch.equal(stack.logits(x), _logits(m, stack, x))
+
+
+def test_long_prompt_is_near_its_calls(m, monkeypatch):
+    """With the feed-forward in one call: the same but for float32 sums in another order and the cache elements that these round the other way;
+    without memory for its workspace: the same bits."""
+    from paper_1911_02150_amd.decoder_stack import DecoderStack
+    b, n, d, h, ff, vocab = 40, 128, 1024, 2, 2560, 264
+    assert m.mqa_stack_feed_forward_plan(b * n, d, ff)[0] & 1
+    stack, prompts = DecoderStack(_weights(n, 3, d, h, ff, vocab, n), b, n, False, DEV), _prompts(1, b, n, vocab)
+    want, caches = _by_calls(m, stack, prompts)
+    for close in (lambda x, y: float((x.float() - y.float()).abs().max()) <= (2e-3 if x.dtype == torch.float32 else 2.0 ** -7) * float(y.float().abs().max()), torch.equal):
+        for lens in stack.lens:
+            lens.zero_()
+        assert close(stack.prefill(prompts), want)
+        for l, (K, V) in enumerate(caches):
+            assert close(stack.K[l], K) and close(stack.V[l], V)
+        whole = stack._workspace
+
+        def no_room(rows, nbytes=0):
+            if nbytes > 4 * rows * (d + ff):
+                raise torch.OutOfMemoryError
+            return whole(rows, nbytes)
+
+        monkeypatch.setattr(stack, "_workspace", no_room)
