@@ -418,7 +418,7 @@ int mqa_stack_argmax(const float* x, int32_t* out, int rows, int n, void* stream
  * the values they are that call's own (decided on the device: a captured call does what the weights of each replay want).
  *   plan:  0: no such form of these sizes (d, ff: multiples of 32, d <= 4096; the call is then refused with MQA_ERR_SHAPE); else bit 0 says whether
  *          it is faster than layernorm, product with MQA_EPI_RELU and product with MQA_EPI_ADD, bits 4..7 and 8..11 which tiles the products take.
- *          *workspace_bytes (unless NULL): what the call needs (MQA_ERR_WORKSPACE with less), about 4 (rows + 2 d) (d + ff) bytes.
+ *          *workspace_bytes (unless NULL): what the call needs (MQA_ERR_WORKSPACE with less), about 4 rows (d + ff) + 8 d ff bytes.
  */
 int mqa_stack_feed_forward_plan(int rows, int d, int ff, size_t* workspace_bytes);
 int mqa_stack_feed_forward(const float* W1, const float* W2, float* x, int rows, int d, int ff, float eps, void* workspace,

@@ -156,9 +156,10 @@ hipError_t launch_project_kv_rows(const float* x, const float* P_k, const float*
                                   const int32_t* lens_in, int32_t* lens_out, int rows, int n, int append, int d, int h_kv,
                                   int cap, int k, int v, void* workspace, hipStream_t st);
 
-// gemm.hip: a product of two plain matrices in its tiles, and if *only on the device is not 0
+// gemm.hip: a product of two plain matrices in its tiles, and if *only on the device is not 0, or only_rows[i] for the rows 256 i .. 256 i + 255
 int gemm_edge(int rows, int N, int C);
-hipError_t launch_gemm_if(const int32_t* only, int edge, const float* in, const float* P, float* out, int rows, int C, int N, int epilogue, hipStream_t st);
+hipError_t launch_gemm_if(const int32_t* only, const int32_t* only_rows, int edge, const float* in, const float* P, float* out, int rows, int C, int N, int epilogue,
+                          hipStream_t st);
 
 // packed.hip: a stack's feed-forward from packed operands.  bytes: of its workspace, 0 where there is no such form; faster: than the calls it stands for;
 // forms and edges: the tiles of its products, and of those in their place where two terms do not hold the values
@@ -169,8 +170,8 @@ hipError_t launch_feed_forward(const FeedForwardPlan& f, const float* W1, const 
 
 // stack_kernels.hip (packed, if: d a multiple of 32 up to 4096)
 hipError_t launch_layernorm(const float* x, float* y, int rows, int d, float eps, hipStream_t st);
-hipError_t launch_layernorm_packed(const int32_t* flag, const float* x, unsigned char* packed, float scale, int rows, int d, float eps, hipStream_t st);
-hipError_t launch_layernorm_if(const int32_t* only, const float* x, float* y, int rows, int d, float eps, hipStream_t st);
+hipError_t launch_layernorm_packed(const int32_t* flag, int32_t* bad, const float* x, unsigned char* packed, float scale, int rows, int d, float eps, hipStream_t st);
+hipError_t launch_layernorm_if(const int32_t* only, const int32_t* only_rows, const float* x, float* y, int rows, int d, float eps, hipStream_t st);
 hipError_t launch_embed(const int32_t* tokens, const int32_t* pos, const float* E, const float* P, float* x,
                         int rows, int d, int vocab, int max_pos, hipStream_t st);
 hipError_t launch_add(float* a, const float* b, size_t n, hipStream_t st);
@@ -240,6 +241,11 @@ __device__ __forceinline__ void store_packed4(unsigned char* packed, float scale
   *reinterpret_cast<uint2*>(at) = make_uint2(s.hi, t.hi);
   *reinterpret_cast<uint2*>(at + (size_t)rows * 64) = make_uint2(s.lo, t.lo);
 }
+
+// A row's values in two fp16 terms, by gemm.hip's measure (`holds`): few octets (eight neighbouring values; none of up to 7 with any but zeros, 2 and an
+// eighth of more) have one below kFull, which the terms cut off at 2^-25 of 1, and if one has, some value is from kFarAbove on
+constexpr float kFull = 0.0625f, kFarAbove = 128.f;
+__device__ __forceinline__ bool row_holds(int small, int octets, int far) { return small <= (octets < 8 ? 0 : 2 + octets / 8) && (small == 0 || far > 0); }
 
 __device__ __forceinline__ float wave_max(float x) {
 #pragma unroll

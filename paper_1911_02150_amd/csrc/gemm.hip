@@ -56,7 +56,7 @@ typedef __attribute__((ext_vector_type(8))) _Float16 halfx8;
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 
 constexpr int kFirstTop = 9, kLastTop = 14;    // log2 of what the scales take a line's largest value to: in the first stage, of all
-constexpr float kFull = 0.0625f;               // scaled values from here on are held to 2^-21 of themselves, 2^-23 from 2^-2 on
+// (scaled values from kFull on are held to 2^-21 of themselves, 2^-23 from 2^-2 on)
 
 // LDS of a stage, in bytes: per group A's two planes, then B's two planes; a plane is two halves g
 // of 16 bytes per row (A) or slot (B): contraction indices 8g .. 8g+7.  Column n of the tile lives in slot
@@ -88,13 +88,11 @@ template <typename V> __device__ __forceinline__ V load_at(const float* base, ui
 
 // B_KCONTIG = false: B[c][n] = P[(n / kv) * d * kv + c * kv + n % kv]   (C = d, N = h * kv)
 // B_KCONTIG = true : B[c][n] = P[(c / kv) * d * kv + n * kv + c % kv]   (C = h * kv, N = d)
-// ONLY: nothing happens unless *only is not 0
+// ONLY: nothing happens unless *only is not 0, or that of the tile's 256 rows
 template <bool B_KCONTIG, int BM, int BN, int WR, int WC, int KG, int PD, bool ONLY>
 __global__ __launch_bounds__(512, KG >= 4 ? 4 : 2)      // (waves per SIMD: two workgroups per compute unit of the small tiles)
 void gemm_split_kernel(const float* __restrict__ in, const float* __restrict__ P, float* out,
-                       int rows, int d, int h, int kv, int epilogue, int tiles_m, int tiles_n, int per, const int32_t* __restrict__ only) {
-  if constexpr (ONLY)
-    if (*only == 0) return;
+                       int rows, int d, int h, int kv, int epilogue, int tiles_m, int tiles_n, int per, const int32_t* __restrict__ only, const int32_t* __restrict__ only_rows) {
   static_assert(WR * WC * KG == 8 && BM * KG == 256 && BN * KG == 256, "512 threads, 16 staged values of each operand per thread of a half");
   constexpr int RB = BM / WR / 32, JB = BN / WC / 32;      // 32x32 blocks per wave
   typedef SplitTile<BM, BN, JB, KG> L;
@@ -109,6 +107,8 @@ void gemm_split_kernel(const float* __restrict__ in, const float* __restrict__ P
   const int band = tile / (8 * tiles_n), in_band = tile - band * 8 * tiles_n;
   const int band_rows = min(8, tiles_m - band * 8);
   const int row0 = (band * 8 + in_band % band_rows) * BM, n0 = (in_band / band_rows) * BN;
+  if constexpr (ONLY)
+    if (*only == 0 && only_rows[row0 >> 8] == 0) return;
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -297,7 +297,7 @@ void gemm_split_kernel(const float* __restrict__ in, const float* __restrict__ P
     // 2 and an eighth of more) hold a value that is not
     auto holds = [&](int i) -> bool {
       const int n = my_short[line[i]], octets = (nst + 1) * KO - my_zeros[line[i]];
-      return n <= (octets < 8 ? 0 : 2 + octets / 8) && (n == 0 || __uint_as_float(my_most[line[i]]) * scale[i] >= 128.f);
+      return n <= (octets < 8 ? 0 : 2 + octets / 8) && (n == 0 || __uint_as_float(my_most[line[i]]) * scale[i] >= kFarAbove);
     };
     bool plain = C < 64;                       // (too few octets to tell)
     auto tell_counts = [&]() {
@@ -498,7 +498,7 @@ bool split_fits(bool outp, int d, int h, int kv, int tile, int stage) {
 
 template <bool KC, int BM, int BN, int WR, int WC, int KG, int PD, bool ONLY = false>
 hipError_t launch_split(const float* in, const float* P, float* out, int rows, int d, int h, int kv, int N,
-                        int epilogue, int S, hipStream_t st, const int32_t* only = nullptr) {
+                        int epilogue, int S, hipStream_t st, const int32_t* only = nullptr, const int32_t* only_rows = nullptr) {
   constexpr size_t lds = SplitTile<BM, BN, BN / WC / 32, KG>::BYTES;       // 67 KiB (32, 64), 132 (128: the groups' partial tiles), 74 (256)
   auto kern = gemm_split_kernel<KC, BM, BN, WR, WC, KG, PD, ONLY>;
   static bool done[64] = {};
@@ -513,7 +513,7 @@ hipError_t launch_split(const float* in, const float* P, float* out, int rows, i
   const long long tiles = (long long)tm * tn;
   const dim3 grid((unsigned)((tiles + 7) / 8 * 8), S), block(512);
   const int C = KC ? h * kv : d, stage = 16 * KG, per = S > 1 ? ((C + stage - 1) / stage + S - 1) / S * stage : C;
-  hipLaunchKernelGGL(kern, grid, block, lds, st, in, P, out, rows, d, h, kv, epilogue, tm, tn, per, only);
+  hipLaunchKernelGGL(kern, grid, block, lds, st, in, P, out, rows, d, h, kv, epilogue, tm, tn, per, only, only_rows);
   return hipGetLastError();
 }
 
@@ -559,10 +559,11 @@ int gemm_edge(int rows, int N, int C) {
   return gemm_fits(false, C, 1, N, c.edge) ? c.edge : 0;
 }
 
-// in [rows, C] . P [C, N] if *only is not 0 on the device
-hipError_t launch_gemm_if(const int32_t* only, int edge, const float* in, const float* P, float* out, int rows, int C, int N, int epilogue, hipStream_t st) {
-  if (edge == 128) return launch_split<false, 128, 128, 2, 2, 2, 3, true>(in, P, out, rows, C, 1, N, N, epilogue, 1, st, only);
-  if (edge == 256) return launch_split<false, 256, 256, 4, 2, 1, 1, true>(in, P, out, rows, C, 1, N, N, epilogue, 1, st, only);
+// in [rows, C] . P [C, N] if *only is not 0 on the device, or only_rows[i] for the rows 256 i .. 256 i + 255
+hipError_t launch_gemm_if(const int32_t* only, const int32_t* only_rows, int edge, const float* in, const float* P, float* out, int rows, int C, int N, int epilogue,
+                          hipStream_t st) {
+  if (edge == 128) return launch_split<false, 128, 128, 2, 2, 2, 3, true>(in, P, out, rows, C, 1, N, N, epilogue, 1, st, only, only_rows);
+  if (edge == 256) return launch_split<false, 256, 256, 4, 2, 1, 1, true>(in, P, out, rows, C, 1, N, N, epilogue, 1, st, only, only_rows);
   return hipErrorNotSupported;
 }
 

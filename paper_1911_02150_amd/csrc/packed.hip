@@ -6,12 +6,13 @@
 //
 // Packed are, in every call, the weights (a line is a column of the product, scaled by the power of two that takes its largest value to
 // [2^14, 2^15)) and the activations between, whose range is known before they are: a layernorm's row has a norm of at most
-// sqrt(d), so one scale holds it whatever comes; so has relu(layernorm . W1), each column of which is at most d times the
-// largest value of its column of W1: it keeps that column's scale, which the rows of W2 have been divided by.  So a product
-// is nothing but loads and fp16 instructions:
+// sqrt(d), so one scale holds it whatever comes; relu(layernorm . W1), each column of which is at most d times the
+// largest value of its column of W1, keeps that column's scale, which the rows of W2 have been divided by, to an eighth of that (of normal deviates it
+// reaches 2^-5 of it).  So a product is nothing but loads and fp16 instructions:
 //   a.b = ah bh + (ah bl + al bh)                           (al bl is below 2^-22 |a||b|, 2^-25 typically)
-// Weights that two terms do not hold (a column with more than a few values below 2^-17 of its largest next to one another, a NaN, an infinity) are
-// told by a flag on the device: the packed products then return at once, and the launches behind them, which return at once otherwise, are
+// What two terms do not hold is looked for where it is packed, and told on the device.  Weights: a column with more than a few values below 2^-17 of its
+// largest next to one another, a NaN, an infinity: the whole call.  Rows, by gemm.hip's measure (`row_holds`), or a hidden value past fp16's range: the
+// 256 rows around them.  Their packed products return at once, and the launches behind, which return at once otherwise, are
 // gemm.hip's on the float32 values.  Nothing is kept from one call for the next, and nothing is asked of the device.
 //
 // What bounds it: the matrix cores and the power they draw.  Against gemm.hip, which splits both operands on the way to LDS (us, TFLOP/s of
@@ -52,6 +53,9 @@ __device__ __forceinline__ void store_packed8(unsigned char* at, size_t plane, c
 
 struct PackedProduct {
   const int32_t* flag;         // not 0: this product is not to be
+  int32_t* bad;                // [rows / 256] not 0: of these rows it is not
+  uint32_t* tallies;           // [tally_tiles][rows] of the hidden values in one tile: octets (eight neighbouring columns) with a value that the terms hold
+  int tally_tiles;             // in few bits, with any but zeros << 8, and with one far above << 16
   const unsigned char* x;      // packed [C / 32][2][rows][64]
   const unsigned char* w;      // packed [C / 32][2][N][64]
   const uint32_t* most;        // [N] bits of the largest value of each column of the weights, as scaled for packing
@@ -63,12 +67,21 @@ struct PackedProduct {
 
 __device__ __forceinline__ float column_scale(uint32_t most) { return split_scale(most ? __uint_as_float(most) : 1.f, 14); }
 
-// Eight sums of neighbouring columns of one row.  ADD: to what is there, read beforehand; else relu, packed (the columns keep the scale of their weights)
+// Eight sums of neighbouring columns of one row.  ADD: to what is there, read beforehand; else relu, packed (the columns keep the scale of their weights),
+// and counted
 template <bool ADD>
-__device__ __forceinline__ void finish8(const PackedProduct& p, int row, int n, float (&v)[8], floatx4 was0, floatx4 was1) {
+__device__ __forceinline__ void finish8(const PackedProduct& p, int row, int n, float (&v)[8], floatx4 was0, floatx4 was1, uint32_t& tally) {
   if constexpr (!ADD) {
+    float most = 0.f;
+    bool small = false;
 #pragma unroll
-    for (int e = 0; e < 8; ++e) v[e] = fmaxf(v[e], 0.f) * p.scale;
+    for (int e = 0; e < 8; ++e) {
+      v[e] = fmaxf(v[e], 0.f) * p.scale;
+      most = fmaxf(most, v[e]);
+      small |= v[e] != 0.f && v[e] < kFull;
+    }
+    tally += (small ? 1u : 0u) + (most > 0.f ? 1u << 8 : 0u) + (most >= kFarAbove ? 1u << 16 : 0u);
+    if (__builtin_expect(!(most < 65504.f), 0)) p.bad[row >> 8] = 1;
     store_packed8(static_cast<unsigned char*>(p.out) + ((size_t)(n >> 5) * 2 * p.rows + row) * 64 + (n >> 3 & 3) * 16, (size_t)p.rows * 64, v);
   } else {
     const u32x4 m0 = *reinterpret_cast<const u32x4*>(p.most + n), m1 = *reinterpret_cast<const u32x4*>(p.most + n + 4);
@@ -93,7 +106,8 @@ struct PackedTile {
   static constexpr int LJ = (NX + NW) / 8;
   static constexpr int STAGE = (NX + NW) * 1024;
   static constexpr int PART = KG > 1 ? KG * TN * TM * 4 : 0;
-  static constexpr int LDS = NB * STAGE > PART ? NB * STAGE : PART;
+  static constexpr int STATE = NB * STAGE > PART ? NB * STAGE : PART;
+  static constexpr int LDS = STATE + 4 * TM;                             // (behind it the rows' tallies)
   static_assert(WN * WM * KG == 8 && (NX + NW) % 8 == 0 && LDS <= 160 * 1024, "8 waves, every one with as many loads");
 };
 template <int TN, int TM, int WN, int WM, int KG, int NB, bool LOW, bool ADD>
@@ -109,9 +123,31 @@ void packed_tile_kernel(PackedProduct p) {
   if (tile >= p.tiles_m * p.tiles_n) return;
   const int band = tile / (8 * p.tiles_n), in_band = tile - band * 8 * p.tiles_n;
   const int band_rows = min(8, p.tiles_m - band * 8);
-  const int row0 = (band * 8 + in_band % band_rows) * TM, n0 = (in_band / band_rows) * TN;
+  const int tile_n = in_band / band_rows, row0 = (band * 8 + in_band % band_rows) * TM, n0 = tile_n * TN;
 
   const int tid = threadIdx.x, lane = tid & 63;
+  uint32_t* const tally = reinterpret_cast<uint32_t*>(smem + L::STATE);
+  if constexpr (ADD) {
+    // do the terms hold the hidden values of these 256 rows?  (every tile of theirs comes to the same)
+    const int block = row0 >> 8, r = block * 256 + (tid & 255);
+    int small = 0, octets = 0, far = 0;
+    if (r < p.rows)
+      for (int t = tid >> 8; t < p.tally_tiles; t += 2) {
+        const uint32_t w = p.tallies[(size_t)t * p.rows + r];
+        small += w & 255, octets += w >> 8 & 255, far += w >> 16;
+      }
+    int (*half)[256] = reinterpret_cast<int (*)[256]>(smem);
+    if (tid >= 256) half[0][tid & 255] = small, half[1][tid & 255] = octets, half[2][tid & 255] = far;
+    __syncthreads();
+    bool bad = p.bad[block] != 0;
+    if (tid < 256) bad |= !row_holds(small + half[0][tid], octets + half[1][tid], far + half[2][tid]);
+    if (__syncthreads_or(bad)) {
+      if (tid == 0) p.bad[block] = 1;
+      return;
+    }
+  } else if (tid < TM) {
+    tally[tid] = 0;                            // (barriers between this and its use: below)
+  }
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int i = lane & 15, kk = lane >> 4;
   const int kg = wave / (WN * WM), wn = wave / WM % WN, wm = wave % WM;
@@ -204,6 +240,8 @@ void packed_tile_kernel(PackedProduct p) {
   // What a sum is added to: the loads of eight blocks in flight together.  One by one, each behind the last one's stores: 16384 x 4096 x 1024
   // in a stack 324 us, so 297; x 1024 x 1024 131, so 98 (without the adding 85)
   constexpr int BATCH = ADD && SHARE > 8 ? 8 : SHARE;
+  static_assert(SHARE % RM == 0 && PAIRS % KG == 0, "block k of a share is of rows k % RM");
+  uint32_t counts[RM] = {};
 #pragma unroll
   for (int k0 = 0; k0 < SHARE; k0 += BATCH) {
     floatx4 was[ADD ? BATCH : 1][2];
@@ -245,8 +283,14 @@ void packed_tile_kernel(PackedProduct p) {
         v[e] = __uint_as_float(s[0]);
         v[4 + e] = __uint_as_float(s[1]);
       }
-      if (place(k, row, n)) finish8<ADD>(p, row, n, v, was[ADD ? k - k0 : 0][0], was[ADD ? k - k0 : 0][1]);
+      if (place(k, row, n)) finish8<ADD>(p, row, n, v, was[ADD ? k - k0 : 0][0], was[ADD ? k - k0 : 0][1], counts[k % RM]);
     }
+  }
+  if constexpr (!ADD) {
+#pragma unroll
+    for (int b = 0; b < RM; ++b) atomicAdd(&tally[wm * RM * 16 + b * 16 + i], counts[b]);
+    __syncthreads();
+    if (tid < TM && row0 + tid < p.rows) p.tallies[(size_t)tile_n * p.rows + row0 + tid] = tally[tid];
   }
 }
 
@@ -380,13 +424,14 @@ int layernorm_exponent(int N) {
   return s;
 }
 
-// A call's workspace, in bytes from its beginning: the flag and the columns' largest values, the packed weights, then the packed (or, where those
-// are not to be used, the float32) layernorm and hidden rows.
+// A call's workspace, in bytes from its beginning: the flag, the columns' largest values and the blocks of rows (cleared by every call), the packed weights,
+// then the packed (or, where those are not to be used, the float32) layernorm and hidden rows, and the tallies of these.
 struct Places {
-  size_t most1, most2, w1, w2, rows, hidden, bytes;
+  size_t most1, most2, bad, w1, w2, rows, hidden, tallies, bytes;
   Places(int rows_, int d, int ff) {
-    most1 = 16, most2 = most1 + 4 * (size_t)ff, w1 = most2 + 4 * (size_t)d, w2 = w1 + 4 * (size_t)d * ff, rows = w2 + 4 * (size_t)d * ff;
-    hidden = rows + 4 * (size_t)rows_ * d, bytes = hidden + 4 * (size_t)rows_ * ff;
+    most1 = 16, most2 = most1 + 4 * (size_t)ff, bad = most2 + 4 * (size_t)d, w1 = bad + ((size_t)rows_ + 1023) / 1024 * 16;
+    w2 = w1 + 4 * (size_t)d * ff, rows = w2 + 4 * (size_t)d * ff, hidden = rows + 4 * (size_t)rows_ * d;
+    tallies = hidden + 4 * (size_t)rows_ * ff, bytes = tallies + 4 * (size_t)((ff + 127) / 128) * rows_;
   }
 };
 
@@ -411,7 +456,8 @@ hipError_t launch_feed_forward(const FeedForwardPlan& f, const float* W1, const 
                                hipStream_t st) {
   unsigned char* const ws = static_cast<unsigned char*>(workspace);
   const Places at(rows, d, ff);
-  int32_t* flag = reinterpret_cast<int32_t*>(ws);
+  int32_t *flag = reinterpret_cast<int32_t*>(ws), *bad = reinterpret_cast<int32_t*>(ws + at.bad);
+  uint32_t* tallies = reinterpret_cast<uint32_t*>(ws + at.tallies);
   uint32_t *most1 = reinterpret_cast<uint32_t*>(ws + at.most1), *most2 = reinterpret_cast<uint32_t*>(ws + at.most2);
   const int ints = (int)(at.w1 / 4);
   hipLaunchKernelGGL(clear_kernel, dim3((ints + 255) / 256), dim3(256), 0, st, reinterpret_cast<uint32_t*>(ws), ints);
@@ -421,19 +467,21 @@ hipError_t launch_feed_forward(const FeedForwardPlan& f, const float* W1, const 
   hipLaunchKernelGGL(pack_kernel, dim3(tiles2 + tiles1), dim3(256), 0, st, two, one, tiles2, flag);
   hipLaunchKernelGGL(pack_kernel, dim3(tiles2), dim3(256), 0, st, two, two, 0, flag);
   const int s = layernorm_exponent(d);
-  hipError_t e = launch_layernorm_packed(flag, x, ws + at.rows, ldexpf(1.f, s), rows, d, eps, st);
+  hipError_t e = launch_layernorm_packed(flag, bad, x, ws + at.rows, ldexpf(1.f, s), rows, d, eps, st);
   if (e != hipSuccess) return e;
-  // |hx 2^s . W1| <= sqrt(d) 2^s sqrt(d) 2^15 (the columns' largest values are below 2^15), and sqrt(d) 2^s <= 2^15: the hidden rows come to 2^15 at most
-  PackedProduct p{flag, ws + at.rows, ws + at.w1, most1, ldexpf(1.f, s - 30), ws + at.hidden, rows, ff, d / 32, 0, 0};
+  // |hx 2^s . W1| <= sqrt(d) 2^s sqrt(d) 2^15 (the columns' largest values are below 2^15), and sqrt(d) 2^s <= 2^15: the hidden rows come to 2^18 at
+  // most, and to 2^15 if they are not nearly parallel to a column of W1
+  const int tiles = (ff + kForms[f.form1].TN - 1) / kForms[f.form1].TN;
+  PackedProduct p{flag, bad, tallies, tiles, ws + at.rows, ws + at.w1, most1, ldexpf(1.f, s - 27), ws + at.hidden, rows, ff, d / 32, 0, 0};
   e = launch_product<false>(p, f.form1, st);
   if (e != hipSuccess) return e;
-  p = PackedProduct{flag, ws + at.hidden, ws + at.w2, most2, ldexpf(1.f, 30 - 2 * s), x, rows, d, ff / 32, 0, 0};
+  p = PackedProduct{flag, bad, tallies, tiles, ws + at.hidden, ws + at.w2, most2, ldexpf(1.f, 27 - 2 * s), x, rows, d, ff / 32, 0, 0};
   e = launch_product<true>(p, f.form2, st);
   if (e != hipSuccess) return e;
   float *hx = reinterpret_cast<float*>(ws + at.rows), *u = reinterpret_cast<float*>(ws + at.hidden);
-  e = launch_layernorm_if(flag, x, hx, rows, d, eps, st);
-  if (e == hipSuccess) e = launch_gemm_if(flag, f.edge1, hx, W1, u, rows, d, ff, 1, st);
-  if (e == hipSuccess) e = launch_gemm_if(flag, f.edge2, u, W2, x, rows, ff, d, 2, st);
+  e = launch_layernorm_if(flag, bad, x, hx, rows, d, eps, st);
+  if (e == hipSuccess) e = launch_gemm_if(flag, bad, f.edge1, hx, W1, u, rows, d, ff, 1, st);
+  if (e == hipSuccess) e = launch_gemm_if(flag, bad, f.edge2, u, W2, x, rows, ff, d, 2, st);
   return e;
 }
 

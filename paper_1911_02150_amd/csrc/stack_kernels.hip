@@ -38,9 +38,9 @@ void layernorm_kernel(const float* __restrict__ x, float* __restrict__ y, int d,
 // The same for rows of a multiple of 4 and at most 256 * 4 * NV floats: the row is read once, with
 // 16-byte loads all in flight together, and kept in registers for the mean, the centred sum of
 // squares and the result (the rows of a decode step are few: the launch is one memory round trip).
-// PACKED: they leave as two fp16 terms of `scale` times them (packed.hip) in the place of float32.
+// PACKED: they leave as two fp16 terms of `scale` times them (packed.hip) in the place of float32; false if those do not hold them.
 template <int NV, bool PACKED>
-__device__ __forceinline__ void layernorm_row(const float* __restrict__ x, float* __restrict__ y, unsigned char* __restrict__ packed, float scale, int rows, int row,
+__device__ __forceinline__ bool layernorm_row(const float* __restrict__ x, float* __restrict__ y, unsigned char* __restrict__ packed, float scale, int rows, int row,
                                               int d, float eps, float* red) {
   const float4* xr = reinterpret_cast<const float4*>(x + (size_t)row * d);
   float4* yr = reinterpret_cast<float4*>(y + (size_t)row * d);
@@ -63,14 +63,28 @@ __device__ __forceinline__ void layernorm_row(const float* __restrict__ x, float
       q += (a * a + b * b) + (c * c + e * e);
     }
   const float rstd = 1.0f / sqrtf(block_sum(q, red) / d + eps);
+  int small = 0, filled = 0, far = 0;              // fours of values (two of them: an octet), as `row_holds` wants them
 #pragma unroll
   for (int u = 0; u < NV; ++u) {
     const int i = threadIdx.x + 256 * u;
     if (i >= d4) continue;
     const float4 n = make_float4((r[u].x - mean) * rstd, (r[u].y - mean) * rstd, (r[u].z - mean) * rstd, (r[u].w - mean) * rstd);
-    if constexpr (PACKED) store_packed4(packed, scale, rows, row, 4 * i, n.x, n.y, n.z, n.w);
-    else yr[i] = n;
+    if constexpr (PACKED) {
+      store_packed4(packed, scale, rows, row, 4 * i, n.x, n.y, n.z, n.w);
+      const float a = fabsf(n.x) * scale, b = fabsf(n.y) * scale, c = fabsf(n.z) * scale, e = fabsf(n.w) * scale, most = fmaxf(fmaxf(a, b), fmaxf(c, e));
+      small += (a != 0.f && a < kFull) || (b != 0.f && b < kFull) || (c != 0.f && c < kFull) || (e != 0.f && e < kFull) ? 1 : 0;
+      filled += most > 0.f ? 1 : 0;
+      far += most >= kFarAbove ? 1 : 0;
+    } else {
+      yr[i] = n;
+    }
   }
+  if constexpr (PACKED) {
+    if (!__syncthreads_or(small)) return true;     // (of normal deviates: 19 rows of 20)
+    small = (int)block_sum((float)small, red), filled = (int)block_sum((float)filled, red), far = (int)block_sum((float)far, red);
+    return row_holds(small, filled / 2, far);
+  }
+  return true;
 }
 template <int NV>
 __global__ __launch_bounds__(256)
@@ -79,21 +93,25 @@ void layernorm_rows_kernel(const float* __restrict__ x, float* __restrict__ y, i
   layernorm_row<NV, false>(x, y, nullptr, 0.f, 0, blockIdx.x, d, eps, red);
 }
 // Every XCD takes a run of neighbouring rows: two of them share a 128-byte line of the packed matrix (16384 x 1024: 44 -> 23 us).  *flag: not to be.
+// bad[row / 256]: what the terms do not hold.
 template <int NV>
 __global__ __launch_bounds__(256)
-void layernorm_packed_kernel(const int32_t* __restrict__ flag, const float* __restrict__ x, unsigned char* __restrict__ packed, float scale, int rows, int d, float eps) {
+void layernorm_packed_kernel(const int32_t* __restrict__ flag, int32_t* __restrict__ bad, const float* __restrict__ x, unsigned char* __restrict__ packed, float scale,
+                             int rows, int d, float eps) {
   __shared__ float red[4];
   const int row = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
   if (*flag || row >= rows) return;
-  layernorm_row<NV, true>(x, nullptr, packed, scale, rows, row, d, eps, red);
+  if (!layernorm_row<NV, true>(x, nullptr, packed, scale, rows, row, d, eps, red)) bad[row >> 8] = 1;
 }
-// ... if *only is not 0 (few workgroups, so that nothing costs little)
+// ... if *only is not 0, or of the rows for whose 256 only_rows is not (few workgroups, so that nothing costs little)
 template <int NV>
 __global__ __launch_bounds__(256)
-void layernorm_if_kernel(const int32_t* __restrict__ only, const float* __restrict__ x, float* __restrict__ y, int rows, int d, float eps) {
+void layernorm_if_kernel(const int32_t* __restrict__ only, const int32_t* __restrict__ only_rows, const float* __restrict__ x, float* __restrict__ y, int rows, int d,
+                         float eps) {
   __shared__ float red[4];
-  if (*only == 0) return;
-  for (int row = blockIdx.x; row < rows; row += gridDim.x) layernorm_row<NV, false>(x, y, nullptr, 0.f, 0, row, d, eps, red);      // (block_sum begins with a barrier)
+  const bool all = *only != 0;
+  for (int row = blockIdx.x; row < rows; row += gridDim.x)
+    if (all || only_rows[row >> 8]) layernorm_row<NV, false>(x, y, nullptr, 0.f, 0, row, d, eps, red);      // (block_sum begins with a barrier)
 }
 
 // x[row] = E[token[row]] + P[pos[row]]; indices outside the tables are clamped (they live on the
@@ -175,17 +193,17 @@ hipError_t launch_layernorm(const float* x, float* y, int rows, int d, float eps
   return hipGetLastError();
 }
 
-hipError_t launch_layernorm_packed(const int32_t* flag, const float* x, unsigned char* packed, float scale, int rows, int d, float eps, hipStream_t st) {
+hipError_t launch_layernorm_packed(const int32_t* flag, int32_t* bad, const float* x, unsigned char* packed, float scale, int rows, int d, float eps, hipStream_t st) {
   const dim3 grid((rows + 7) / 8 * 8), block(256);
-  if (d <= 1024) hipLaunchKernelGGL(layernorm_packed_kernel<1>, grid, block, 0, st, flag, x, packed, scale, rows, d, eps);
-  else hipLaunchKernelGGL(layernorm_packed_kernel<4>, grid, block, 0, st, flag, x, packed, scale, rows, d, eps);
+  if (d <= 1024) hipLaunchKernelGGL(layernorm_packed_kernel<1>, grid, block, 0, st, flag, bad, x, packed, scale, rows, d, eps);
+  else hipLaunchKernelGGL(layernorm_packed_kernel<4>, grid, block, 0, st, flag, bad, x, packed, scale, rows, d, eps);
   return hipGetLastError();
 }
 
-hipError_t launch_layernorm_if(const int32_t* only, const float* x, float* y, int rows, int d, float eps, hipStream_t st) {
+hipError_t launch_layernorm_if(const int32_t* only, const int32_t* only_rows, const float* x, float* y, int rows, int d, float eps, hipStream_t st) {
   const dim3 grid(rows < 2048 ? rows : 2048), block(256);
-  if (d <= 1024) hipLaunchKernelGGL(layernorm_if_kernel<1>, grid, block, 0, st, only, x, y, rows, d, eps);
-  else hipLaunchKernelGGL(layernorm_if_kernel<4>, grid, block, 0, st, only, x, y, rows, d, eps);
+  if (d <= 1024) hipLaunchKernelGGL(layernorm_if_kernel<1>, grid, block, 0, st, only, only_rows, x, y, rows, d, eps);
+  else hipLaunchKernelGGL(layernorm_if_kernel<4>, grid, block, 0, st, only, only_rows, x, y, rows, d, eps);
   return hipGetLastError();
 }
 

@@ -21,7 +21,7 @@ def test_plans(m):
         assert (plan == 0) == (nbytes == 0)
         if plan == 0:
             continue
-        assert d % 32 == 0 and ff % 32 == 0 and nbytes == 16 + 4 * (d + ff) + 8 * d * ff + 4 * rows * (d + ff)
+        assert d % 32 == 0 and ff % 32 == 0 and nbytes == 16 + 4 * (d + ff) + 16 * -(-rows // 1024) + 8 * d * ff + 4 * rows * (d + ff + -(-ff // 128))
         assert plan & 1 == (rows >= 4096 and rows * d * ff >= 12e9)
         forms.add((plan >> 4 & 15, plan >> 8 & 15))
         if plan & 1:                               # the layernorm and the two products are those that the call stands for, or none are faster in parts

@@ -52,7 +52,7 @@ def _reference(m, x, W1, W2):
     term = lambda C: 4 * 2.0 ** -22 + 2 * math.sqrt(3 * C) * EPS  # noqa: E731
     u, off = torch.relu(y @ w1), term(d) * (y.abs() @ w1.abs())
     s = next(s for s in range(15, -1, -1) if math.sqrt(d) * 2.0 ** s <= 2.0 ** 15)
-    scale = 2.0 ** (14 - torch.floor(torch.log2(w1.abs().amax(0).clamp(min=2.0 ** -126))) + 2 * s - 30)
+    scale = 2.0 ** (14 - torch.floor(torch.log2(w1.abs().amax(0).clamp(min=2.0 ** -126))) + 2 * s - 27)
     off += 2.0 ** -22 * u + 2.0 ** -25 / scale
     return x.double() + u @ w2, (term(ff) * u + off) @ w2.abs() + 2 * EPS * (x.double().abs() + (u @ w2).abs())
 
@@ -118,3 +118,51 @@ def test_rows_that_are_not_finite(m):
     got, want, others = _call(m, x, W1, W2), _calls(m, x, W1, W2), torch.ones(4100, dtype=torch.bool, device=DEV)
     others[rows] = False
     assert torch.equal(got[others], clean[others]) and torch.equal(got[rows].nan_to_num(), want[rows].nan_to_num()) and torch.equal(got[rows].isnan(), want[rows].isnan())
+
+
+def _spread(decades):
+    """1024 values, each beside its negative: 1 down to 10^decades."""
+    return torch.logspace(0, decades, 512, device=DEV).repeat_interleave(2) * torch.tensor([1.0, -1.0], device=DEV).repeat(512)
+
+
+@pytest.mark.parametrize("what, packed", [("spread", False), ("one far above", False), ("nearly equal", False), ("few", True), ("some small", True), ("hidden spread", False),
+                                          ("hidden far above", False)])
+def test_rows_that_two_terms_hold_or_not(m, what, packed):
+    """One row that they do not hold: the 256 around it are those of the three calls, bit for bit, all others what they are without it."""
+    x, W1, W2 = _inputs(4100, 1024, 1024)
+    row, sign = torch.randn(1024, device=DEV), x[7].sign()
+    if what.startswith("hidden"):                  # columns of one value each, or of one size
+        W1 = torch.diag(torch.full((1024,), 1.0, device=DEV)) if what == "hidden spread" else W1.index_fill(1, torch.tensor([5], device=DEV), 0).add_(
+            torch.nn.functional.pad(0.1 * sign[:, None], (5, 1018)))
+    clean = _call(m, x, W1, W2)
+    if what.endswith("spread"):
+        row = _spread(-9 if what == "spread" else -4.8)      # (of the hidden spread the layernorm's values lie between 1e-4 and 10)
+    elif what == "one far above":
+        row[7], row[8] = 1e6, -1e6
+    elif what == "nearly equal":                   # (the layernorm's eps)
+        row = row * 1e-9 + 1e-9
+    elif what == "few":
+        row = torch.zeros_like(row)
+        row[3], row[900] = 1.0, -1.0
+    elif what == "some small":
+        row[::100] = row.mean() + 1e-5
+    else:
+        row = sign
+    x[2100] = row
+    got, want, block = _call(m, x, W1, W2), _calls(m, x, W1, W2), slice(2048, 2304)
+    others = torch.ones(4100, dtype=torch.bool, device=DEV)
+    others[2100 if packed else block] = False
+    assert torch.equal(got[others], clean[others])
+    assert torch.equal(got[block], want[block]) != packed
+    if packed:
+        ref, bound = _reference(m, x[block], W1, W2)
+        assert ((got[block] - ref).abs() <= bound).all()
+
+
+def test_small_values_that_alone_count(m):
+    """Hidden values far below the largest of their row, each the only one in its output: as good as products of float32 numbers."""
+    x = _spread(-4.8).expand(4100, 1024).contiguous()
+    y = m.mqa_stack_layernorm(x)
+    W1, W2 = torch.eye(1024, device=DEV), torch.diag(1e3 / y[0].abs())
+    got, want = _call(m, x, W1, W2), x.double() + torch.relu(y.double()) @ W2.double()
+    assert ((got - want).abs() <= 2.0 ** -20 * want.abs()).all()
