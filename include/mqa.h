@@ -279,8 +279,7 @@ int mha_decode_step_window(const float* q, const void* K, const void* V, const i
  *     o [b,n,h,v].  Call after the append: query j of sequence i sits at position
  *     lens[i]-n+j and attends to positions 0..lens[i]-n+j.  lens[i] >= n is required (a query
  *     with nothing to attend to yields zeros).  bf16 cache with k = v = 128 only
- *     (MQA_ERR_SHAPE otherwise).  The n*h rows of a sequence share each K/V tile they read.  No workspace
- *     is needed; a single query (n = 1) of many positions runs as a decode step in the ranges that it has room for.
+ *     (MQA_ERR_SHAPE otherwise).  The n*h rows of a sequence share each K/V tile they read.
  */
 int mqa_append_kv_rows(void* K, void* V, const float* k_new, const float* v_new, int32_t* lens,
                        int b, int n, int h_kv, int cap, int k, int v, mqa_dtype dt, void* stream);

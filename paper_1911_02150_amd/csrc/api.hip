@@ -184,12 +184,6 @@ int decode_impl(const float* q, const void* K, const void* V, const int32_t* len
   const int nseq = multi_head ? b * h : b;
   const int G = multi_head ? (causal_n > 0 ? causal_n : 1) : h;
   Plan pl;
-  // One query per sequence sees every row: a decode step, its positions in ranges if the workspace holds their partial states.  us, causal rows /
-  // so: b=1, h=8, 4096 positions 38.3 / 13.9, multi-head 48.0 / 14.1; b=32, h=16, 2048 29.5 / 13.9, multi-head 102 / 81; b=4, 64 heads, 1024 39.6 /
-  // 13.6.  Up to 1024 positions and 32 heads a second launch costs what the ranges give (b=8, h=8, 1024 12.9 / 13.9; b=1, 512 11.0 / 13.7).
-  if (causal_n == 1 && (G > 32 || cap > 1024) && plan_decode(nseq, G, cap, window, k, v, dt == MQA_BF16, tn, &pl) == MQA_OK && pl.use_mfma &&
-      (pl.S == 1 || (workspace && !misaligned(workspace) && workspace_bytes >= partial_bytes((long long)nseq * G, pl.S, v))))
-    causal_n = 0;
   if (causal_n > 0) tn.splits = 1;     // rows end at different positions: one range per workgroup, no merge pass
   rc = plan_decode(nseq, G, cap, window, k, v, dt == MQA_BF16, tn, &pl, causal_n > 0);
   if (rc) return rc;

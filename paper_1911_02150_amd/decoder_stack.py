@@ -152,7 +152,7 @@ class DecoderStack:
                 x, hx = (t.view(b, n, self.d)[:, n - 1].contiguous() for t in (x, hx))
                 rows, ws = b, self._workspace(b)
             q = B.mqa_project_qkvo(B.MQA_PROJ_Q, hx, w["P_q"]).view(b, rows // b, self.h, self.k)
-            o = B.mqa_prefill_attention(q, self.K[l], self.V[l], now, workspace=ws if l == end else None).view(rows, self.h, self.v)
+            o = B.mqa_prefill_attention(q, self.K[l], self.V[l], now, workspace=ws).view(rows, self.h, self.v)
             if l < end and in_one[l]:
                 B.mqa_project_qkvo_ex(B.MQA_PROJ_O, o, w["P_o"], out=x, epilogue=B.MQA_EPI_ADD)
                 B.mqa_stack_feed_forward(x, w["W1"], w["W2"], ws)
