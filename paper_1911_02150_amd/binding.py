@@ -49,9 +49,13 @@ _NATIVE_FUNCTIONS = [
 
 
 def _load_native(lib):
-    if not os.path.exists(os.path.join(_PKG_DIR, "_calls.so")):
-        raise OSError(f"{os.path.join(_PKG_DIR, '_calls.so')} not found: build it with `python -m paper_1911_02150_amd.build`")
-    from . import _calls
+    """The native calls, or None, which costs time only: where they have not been built, or for another Python (their file's name) or torch."""
+    try:
+        from . import _calls
+    except ImportError:
+        return None
+    if _calls.torch_version() != str(torch.__version__):
+        return None
     _calls.init(MqaError, torch.nn.Parameter, *[ctypes.cast(getattr(lib, name), ctypes.c_void_p).value for name in _NATIVE_FUNCTIONS])
     return _calls
 

@@ -1,9 +1,10 @@
-"""Builds libmqa_decode.so (gfx950) with hipcc and _calls.so in-tree.  `python -m paper_1911_02150_amd.build`."""
+"""Builds libmqa_decode.so (gfx950) with hipcc and the binding's native calls in-tree.  `python -m paper_1911_02150_amd.build`."""
 from __future__ import annotations
 
 import os
 import subprocess
 import sys
+import sysconfig
 
 PKG_DIR = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(PKG_DIR, "csrc")
@@ -17,7 +18,7 @@ HIPCC_FLAGS = [
 ]
 
 
-CALLS_PATH = os.path.join(PKG_DIR, "_calls.so")
+CALLS_PATH = os.path.join(PKG_DIR, "_calls" + sysconfig.get_config_var("EXT_SUFFIX"))      # (another Python does not load it)
 
 
 def _run(cmd, verbose):
@@ -34,15 +35,13 @@ def _run(cmd, verbose):
 
 def build_calls(verbose: bool = True) -> str:
     """The binding's native calls: host code over torch's tensor type."""
-    import sysconfig
-
     import torch
     torch_dir = os.path.dirname(torch.__file__)
     rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
     includes = [os.path.join(torch_dir, "include"), os.path.join(torch_dir, "include", "torch", "csrc", "api", "include"),
                 sysconfig.get_paths()["include"], os.path.join(rocm, "include")]
     _run([os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-shared", "-fPIC", "-Wall", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
-          "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1", *[f"-I{d}" for d in includes], os.path.join(CSRC, "calls.cpp"), "-o", CALLS_PATH,
+          "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1", f'-DMQA_TORCH_VERSION="{torch.__version__}"', *[f"-I{d}" for d in includes], os.path.join(CSRC, "calls.cpp"), "-o", CALLS_PATH,
           f"-L{os.path.join(torch_dir, 'lib')}", "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip"], verbose)
     return CALLS_PATH
 

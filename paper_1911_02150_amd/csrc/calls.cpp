@@ -328,8 +328,11 @@ PyObject* init(PyObject*, PyObject* const* a, Py_ssize_t n) {
   Py_RETURN_NONE;
 }
 
+// of the torch whose tensors these functions know from within
+PyObject* torch_version(PyObject*, PyObject* const*, Py_ssize_t) { return PyUnicode_FromString(MQA_TORCH_VERSION); }
+
 #define ENTRY(NAME) {#NAME, reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)(void)>(NAME)), METH_FASTCALL, nullptr}
-PyMethodDef methods[] = {ENTRY(init), ENTRY(decode), ENTRY(append_qkv), ENTRY(project), ENTRY(add_layernorm), ENTRY(memory_kv), ENTRY(attend_rows), ENTRY(beams),
+PyMethodDef methods[] = {ENTRY(init), ENTRY(torch_version), ENTRY(decode), ENTRY(append_qkv), ENTRY(project), ENTRY(add_layernorm), ENTRY(memory_kv), ENTRY(attend_rows), ENTRY(beams),
                          ENTRY(reorder), {nullptr, nullptr, 0, nullptr}};
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "_calls", "Native argument marshalling of binding.py", -1, methods, nullptr, nullptr, nullptr, nullptr};
 
