@@ -1,7 +1,8 @@
 // The calls of a decoding loop from Python without the interpreter's share of them: checks of the tensors, their addresses,
 // the current stream and the call into libmqa_decode.so in one native function each (a CPython extension over torch's own tensor
-// type).  They take what the binding's general path takes in its plainest form only, torch tensors on the GPU, contiguous, of the
-// right types and shapes; for anything else they return None, nothing has happened, and the general path accepts it or says what is wrong.
+// type).  They take what the binding's general path takes in its plainest form only, torch tensors on the current GPU, contiguous, of the
+// right types and shapes, with no mode of torch active; for anything else they return None, nothing has happened, and the general path accepts it or says
+// what is wrong.
 // Measured (us a call among others, general path through ctypes / here; GPU alone, from a graph): one attention 7.1 / 4.5 (4.3), a layer's
 // three calls 21.7 / 17.3 (16.9), a memory and its step 15.3 / 9.4 (9.0), a beam step and its reorder 18.8 / 12.7 (11.5).  The launch
 // itself is 3.2 of a call.
@@ -9,6 +10,9 @@
 #include <Python.h>
 
 #include <ATen/ATen.h>
+#include <ATen/PythonTorchFunctionTLS.h>
+#include <c10/core/impl/TorchDispatchModeTLS.h>
+#include <c10/hip/HIPFunctions.h>
 #include <c10/hip/HIPStream.h>
 #include <torch/csrc/autograd/python_variable.h>
 
@@ -36,11 +40,16 @@ PyObject* parameter_class = nullptr;
 const uint64_t kPlainKeys = (c10::DispatchKeySet(c10::DispatchKey::CUDA) | c10::DispatchKeySet(c10::DispatchKey::AutogradCUDA) |
                              c10::DispatchKeySet(c10::DispatchKey::ADInplaceOrView) | c10::DispatchKeySet(c10::DispatchKey::AutocastCUDA)).raw_repr();
 
-// A tensor that is no more than memory on the GPU (no subclass, no wrapper of a transform), contiguous, of this type; else null.
+// Nobody looks on: the output is made without a word to a function mode or a dispatch mode.
+bool no_modes() { return !at::impl::torch_function_mode_enabled() && !c10::impl::TorchDispatchModeTLS::any_modes_set(); }
+
+thread_local c10::DeviceIndex device = 0;      // the current one, of a call
+
+// A tensor that is no more than memory on that GPU (no subclass, no wrapper of a transform), contiguous, of this type; else null.
 const at::Tensor* plain(PyObject* o) {
   if (reinterpret_cast<PyObject*>(Py_TYPE(o)) != THPVariableClass && reinterpret_cast<PyObject*>(Py_TYPE(o)) != parameter_class) return nullptr;
   const at::Tensor& t = THPVariable_Unpack(o);
-  if (!t.defined() || (t.unsafeGetTensorImpl()->key_set().raw_repr() & ~kPlainKeys) || !t.is_cuda() || !t.is_contiguous()) return nullptr;
+  if (!t.defined() || (t.unsafeGetTensorImpl()->key_set().raw_repr() & ~kPlainKeys) || !t.is_cuda() || t.device().index() != device || !t.is_contiguous()) return nullptr;
   return &t;
 }
 const at::Tensor* plain(PyObject* o, at::ScalarType type) {
@@ -98,7 +107,7 @@ struct Held {                                  // a reference that goes with an 
   PyObject* NAME##_body(PyObject* const* a);                                              \
   PyObject* NAME(PyObject*, PyObject* const* a, Py_ssize_t n) {                           \
     if (n != COUNT) { PyErr_SetString(PyExc_TypeError, #NAME ": " #COUNT " arguments"); return nullptr; } \
-    try { return NAME##_body(a); } catch (const std::exception&) { NOT_HERE; }            \
+    try { if (!no_modes()) NOT_HERE; device = c10::hip::current_device(); return NAME##_body(a); } catch (const std::exception&) { NOT_HERE; }            \
   }                                                                                       \
   PyObject* NAME##_body(PyObject* const* a)
 #define WITHOUT_GIL(EXPR) [&] { int rc_; Py_BEGIN_ALLOW_THREADS rc_ = (EXPR); Py_END_ALLOW_THREADS return rc_; }()

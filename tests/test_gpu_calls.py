@@ -138,6 +138,34 @@ def test_left_to_the_general_path(m, monkeypatch):
     assert refused.value.status == 3 and "mqa_decode_step failed" in str(refused.value)
 
 
+def test_modes_see_what_they_saw(m, monkeypatch):
+    """A function mode and a dispatch mode are told of the output, as by the general path."""
+    from torch.overrides import TorchFunctionMode
+    from torch.utils._python_dispatch import TorchDispatchMode
+    x, P = _t(1, 3, 64), _t(2, 64, 128)
+    ref = m.mqa_project_qkvo(m.MQA_PROJ_LINEAR, x, P)
+    watch = _Watch(m._native, True)
+    monkeypatch.setattr(m, "_native", watch)
+    seen = []
+
+    class Functions(TorchFunctionMode):
+        def __torch_function__(self, func, types, args=(), kwargs=None):
+            seen.append(func)
+            return func(*args, **(kwargs or {}))
+
+    class Dispatches(TorchDispatchMode):
+        def __torch_dispatch__(self, func, types, args=(), kwargs=None):
+            seen.append(func)
+            return func(*args, **(kwargs or {}))
+
+    for mode, what in ((Functions, torch.empty), (Dispatches, torch.ops.aten.empty.memory_format)):
+        seen.clear()
+        with mode():
+            got = m.mqa_project_qkvo(m.MQA_PROJ_LINEAR, x, P)
+        assert what in seen and torch.equal(got, ref) and watch.took.pop() == ("project", False)
+    assert torch.equal(m.mqa_project_qkvo(m.MQA_PROJ_LINEAR, x, P), ref) and watch.took.pop() == ("project", True)
+
+
 def test_parameters_threads_and_streams(m):
     """Weights as Parameters, calls from threads on streams of their own, buffers that are new every time."""
     import threading
