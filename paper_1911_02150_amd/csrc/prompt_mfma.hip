@@ -109,7 +109,9 @@ void prompt_kernel(DecodeParams p) {
   const int lim = limit(row0 + i32), lim_min = limit(row0), lim_max = limit(row0 + 31);
   const int end = limit(row_block * 128 + 127);              // of the workgroup
   const int lim_first = limit(row_block * 128);              // its first row's
-  const int ntiles = (end + kTilePos - 1) / kTilePos, turns = (ntiles + TEAMS - 1) / TEAMS;      // team e: the tiles e, e + TEAMS, ...
+  const int ntiles = (end + kTilePos - 1) / kTilePos;
+  const int teams = TEAMS > 1 && ntiles > 4 ? TEAMS : 1;     // team e: the tiles e, e + teams, ...; of few tiles the first has them all (no merge)
+  const int turns = (ntiles + teams - 1) / teams;
   int* const any_odd = reinterpret_cast<int*>(smem_all + TEAMS * 2 * kBuffer);
   int odd = 0;                                               // V holds something not finite that not all rows see
 
@@ -154,11 +156,11 @@ void prompt_kernel(DecodeParams p) {
       }
   };
 
-  load_tile(team);
+  if (team < teams) load_tile(team);
   if (threadIdx.x == 0) *any_odd = 0;
   // ---- q as B operands: lane (i, g) holds elements 16 s + 8 g .. + 7 of row i
   u32x4 qh[8], ql[8];
-  {
+  if (team < teams) {
     const float4* src = reinterpret_cast<const float4*>(p.q + ((size_t)seq * G + min(row0 + i32, G - 1)) * 128) + 2 * g;
 #pragma unroll
     for (int s = 0; s < 8; ++s) {
@@ -253,18 +255,18 @@ void prompt_kernel(DecodeParams p) {
     l_run += sum[0] + sum[1];
   };
 
-  if (ntiles > 0) {
+  if (ntiles > 0 && team < teams) {
     store_tile(team, 0);
-    load_tile(team + TEAMS);
+    load_tile(team + teams);
   }
   __syncthreads();
   for (int u = 0; u < turns; ++u) {
     // (buffer u + 1 was last read in round u - 1, which the barrier at its end closed)
-    const int t = u * TEAMS + team;
-    const bool sees = t * kTilePos < lim_max;                // (the same for the whole wave; past the last tile: none)
-    if (u + 1 < turns) {
-      store_tile(t + TEAMS, (u + 1) & 1);
-      load_tile(t + 2 * TEAMS);
+    const int t = u * teams + team;
+    const bool sees = team < teams && t * kTilePos < lim_max;      // (the same for the whole wave; past the last tile: none)
+    if (u + 1 < turns && team < teams) {
+      store_tile(t + teams, (u + 1) & 1);
+      load_tile(t + 2 * teams);
     }
     if (odd) *any_odd = 1;
     if (sees) { logits(u & 1); weigh(t, u & 1); }
@@ -276,7 +278,7 @@ void prompt_kernel(DecodeParams p) {
     for (int row = row0 + team * ROWS; row < min(row0 + (team + 1) * ROWS, G); ++row) plain_row(p, seq, row, limit(row), lane);
     return;
   }
-  if constexpr (TEAMS > 1) {
+  if (teams > 1) {
     // the second team's states meet the first's in LDS: sums in its own buffers, maxima and sums of weights where the first's wave
     // will put its rows (its own reads come before its writes)
     float* const at = reinterpret_cast<float*>(smem_all + 2 * kBuffer) + wave * (64 * 64) + lane;
@@ -339,9 +341,10 @@ hipError_t launch_teams(const DecodeParams& p, unsigned nblocks, hipStream_t st)
 
 }  // namespace
 
-// Two teams where a compute unit has one workgroup at most and the positions are more than two tiles each.  us, one team / two: one sequence of 4096, h=8:
-// 146 / 107, of 1024: 41 / 33; multi-head n=700, prefix 100, b=4, h=5: 36 / 29; h=1, n=2000: 83 / 61; but b=16, n=128, prefix 64: 14.2 / 16.0 (the
-// merge), 256 positions the same.
+// Two teams where a compute unit has one workgroup at most and the capacity is more than two tiles each.  us, one team / two: one sequence of 4096, h=8:
+// 146 / 107, of 1024: 41 / 33; multi-head n=700, prefix 100, b=4, h=5: 36 / 29; h=1, n=2000: 83 / 61.  A workgroup that turns out to have four tiles
+// or fewer leaves them to its first team, the second one waiting at the barriers without its q: 128 positions of 2048, b=16 11.7 / 11.4 (shared and
+// merged 13.2), 64 of 1024, b=32 9.1 / 9.4 (12.1).
 hipError_t launch_prompt(const DecodeParams& p, hipStream_t st) {
   const long long nblocks = (long long)p.nseq * p.HG;        // HG: blocks of 128 rows
   if (nblocks > 0x7fffffffll) return hipErrorInvalidValue;

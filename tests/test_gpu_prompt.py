@@ -128,6 +128,9 @@ def test_prompt_values_that_are_not_finite(m, multi_head, n, h, prefix, at, valu
     (40, 3, 280, 320),     # five whole tiles
     (33, 5, 352, 400),     # six, and one past the length
     (260, 2, 125, 385),
+    (128, 8, 0, 1000),     # few tiles of a large cache: one team's
+    (40, 3, 216, 1000),    # four tiles, the last one full
+    (130, 3, 127, 1000),   # of the first row blocks four, of the last one five
 ])
 def test_prompt_in_two_teams(m, multi_head, n, h, prefix, cap):
     """Few workgroups and more than 256 positions: every second tile is another team's."""
