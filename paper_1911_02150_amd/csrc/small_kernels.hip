@@ -220,36 +220,66 @@ void length_order_kernel(const int32_t* lens, int lens_div, int nseq, int cap, i
 }
 
 // Beam search bookkeeping: hypothesis slot r continues hypothesis parent[r], so its cache
-// becomes a copy of that hypothesis' valid rows.  One workgroup per (slot, KV head, piece of 256 U
-// 16-byte words of K's rows and as many of V's): what bounds it is the latency of parent, length and
-// words one behind the other.  Source and destination are different buffers, so slots may be
-// duplicated or dropped freely.  Rows at and beyond the length are not touched.
+// becomes a copy of that hypothesis' valid rows.  One workgroup per (slot, KV head, piece
+// of K's rows and as much of V's): what bounds it is the latency of parent, length and
+// words one behind the other, and, where most pieces are empty, what a wave does before it knows.  Source and destination are different buffers,
+// so slots may be duplicated or dropped freely.  Rows at and beyond the length are not touched.
+struct ReorderSizes { int n, h_kv, cap, k_row16, v_row16; };
+struct ReorderRows { uint32_t k_words, v_words; size_t from, to; };      // (words: below 2^29)
+// false: nothing of this slot from word `first` on
+__device__ __forceinline__ bool reorder_rows(const ReorderSizes& c, const int32_t* lens_src, const int32_t* parent, int32_t* lens_dst, uint32_t first, ReorderRows* w) {
+  const int r = blockIdx.x / c.h_kv, j = blockIdx.x % c.h_kv;
+  int par = parent[r];
+  par = par < 0 ? 0 : (par >= c.n ? c.n - 1 : par);
+  int L = lens_src[par];
+  L = L < 0 ? 0 : (L > c.cap ? c.cap : L);
+  if (blockIdx.y == 0 && j == 0 && threadIdx.x == 0) lens_dst[r] = L;
+  w->k_words = (uint32_t)L * c.k_row16, w->v_words = (uint32_t)L * c.v_row16;
+  if (first >= max(w->k_words, w->v_words)) return false;      // (before the 64-bit products: 4096 empty slots 4.5 -> 3.2 us)
+  w->from = ((size_t)par * c.h_kv + j) * c.cap, w->to = ((size_t)r * c.h_kv + j) * c.cap;
+  return true;
+}
+
+// Pieces of 256 U words, all of a thread's on their way together
 template <int U>
 __global__ __launch_bounds__(256)
 void reorder_kernel(const uint4* __restrict__ K_src, const uint4* __restrict__ V_src, const int32_t* __restrict__ lens_src,
-                    const int32_t* __restrict__ parent, uint4* __restrict__ K_dst, uint4* __restrict__ V_dst, int32_t* __restrict__ lens_dst,
-                    int n, int h_kv, int cap, int k_row16, int v_row16) {
-  const int r = blockIdx.x / h_kv, j = blockIdx.x % h_kv;
-  int par = parent[r];
-  par = par < 0 ? 0 : (par >= n ? n - 1 : par);
-  int L = lens_src[par];
-  L = L < 0 ? 0 : (L > cap ? cap : L);
-  if (blockIdx.y == 0 && j == 0 && threadIdx.x == 0) lens_dst[r] = L;
-  const size_t at = (size_t)blockIdx.y * (256 * U) + threadIdx.x, from = ((size_t)par * h_kv + j) * cap, to = ((size_t)r * h_kv + j) * cap;
-  const size_t k_words = (size_t)L * k_row16, v_words = (size_t)L * v_row16;
-  const uint4 *ks = K_src + from * k_row16, *vs = V_src + from * v_row16;
-  uint4 *kd = K_dst + to * k_row16, *vd = V_dst + to * v_row16;
-  if ((size_t)blockIdx.y * (256 * U) >= max(k_words, v_words)) return;
+                    const int32_t* __restrict__ parent, uint4* __restrict__ K_dst, uint4* __restrict__ V_dst, int32_t* __restrict__ lens_dst, ReorderSizes c) {
+  ReorderRows w;
+  if (!reorder_rows(c, lens_src, parent, lens_dst, blockIdx.y * (uint32_t)(256 * U), &w)) return;
+  const uint32_t at = blockIdx.y * (uint32_t)(256 * U) + threadIdx.x;
+  const uint4 *ks = K_src + w.from * c.k_row16, *vs = V_src + w.from * c.v_row16;
+  uint4 *kd = K_dst + w.to * c.k_row16, *vd = V_dst + w.to * c.v_row16;
   uint4 a[U], b[U];
 #pragma unroll
   for (int u = 0; u < U; ++u) {                    // (past the end: the last word again)
-    a[u] = ks[min(at + 256 * u, k_words - 1)];
-    b[u] = vs[min(at + 256 * u, v_words - 1)];
+    a[u] = ks[min(at + 256 * u, w.k_words - 1)];
+    b[u] = vs[min(at + 256 * u, w.v_words - 1)];
   }
 #pragma unroll
   for (int u = 0; u < U; ++u) {
-    if (at + 256 * u < k_words) kd[at + 256 * u] = a[u];
-    if (at + 256 * u < v_words) vd[at + 256 * u] = b[u];
+    if (at + 256 * u < w.k_words) kd[at + 256 * u] = a[u];
+    if (at + 256 * u < w.v_words) vd[at + 256 * u] = b[u];
+  }
+}
+
+// Pieces of 4096 words, one per thread at a time: few registers, so that many waves wait beside one another
+__global__ __launch_bounds__(256)
+void reorder_in_turn_kernel(const uint4* K_src, const uint4* V_src, const int32_t* lens_src, const int32_t* parent, uint4* K_dst, uint4* V_dst, int32_t* lens_dst,
+                            ReorderSizes c) {
+  ReorderRows w;
+  const uint32_t first = blockIdx.y * 4096u;
+  if (!reorder_rows(c, lens_src, parent, lens_dst, first, &w)) return;
+  const uint32_t k_to = min(first + 4096u, w.k_words), v_to = min(first + 4096u, w.v_words);
+  {
+    const uint4* src = K_src + w.from * c.k_row16;
+    uint4* dst = K_dst + w.to * c.k_row16;
+    for (uint32_t i = first + threadIdx.x; i < k_to; i += 256) dst[i] = src[i];
+  }
+  {
+    const uint4* src = V_src + w.from * c.v_row16;
+    uint4* dst = V_dst + w.to * c.v_row16;
+    for (uint32_t i = first + threadIdx.x; i < v_to; i += 256) dst[i] = src[i];
   }
 }
 
@@ -336,21 +366,21 @@ hipError_t launch_reorder(const void* K_src, const void* V_src, const int32_t* l
                           void* K_dst, void* V_dst, int32_t* lens_dst, int n, int h_kv, int cap,
                           size_t k_row_bytes, size_t v_row_bytes, hipStream_t st) {
   const size_t words = (size_t)cap * ((k_row_bytes > v_row_bytes ? k_row_bytes : v_row_bytes) / 16), slots = (size_t)n * h_kv;
-  auto go = [&](auto kern, int U) {
-    hipLaunchKernelGGL(kern, dim3((unsigned)slots, (unsigned)((words + 256 * U - 1) / (256 * U))), dim3(256), 0, st, (const uint4*)K_src, (const uint4*)V_src,
-                       lens_src, parent, (uint4*)K_dst, (uint4*)V_dst, lens_dst, n, h_kv, cap, (int)(k_row_bytes / 16), (int)(v_row_bytes / 16));
+  const ReorderSizes c{n, h_kv, cap, (int)(k_row_bytes / 16), (int)(v_row_bytes / 16)};
+  auto go = [&](auto kern, int words_each) {
+    hipLaunchKernelGGL(kern, dim3((unsigned)slots, (unsigned)((words + 256 * words_each - 1) / (256 * words_each))), dim3(256), 0, st, (const uint4*)K_src,
+                       (const uint4*)V_src, lens_src, parent, (uint4*)K_dst, (uint4*)V_dst, lens_dst, c);
   };
-  // One word a thread while that is at most 4096 workgroups (16 to a compute unit), else more: a workgroup's words come one latency after the other,
-  // but capacities that are mostly empty should not cost a workgroup each.  us, sixteen words a thread in two loops (as it was) / so: 64 slots
-  // of 128 rows 5.5 / 2.5 (a beam step with its attention 29.8 / 23.4), 320 of 256 rows 14.4 / 13.1, 64 of 8192 rows 102 / 98, of 100 rows of 8192
-  // 7.6 / 4.3 (in single words 20.5), 256 of 600 rows of 1024 23.1 / 23.7, 4096 of 256 rows 187 / 181, float32 378 / 360, of 10 rows of 256
-  // 7.8 / 8.3 (four words: 10.4, and 172 full).  Sixteen where the grid would be too deep.
+  // One word a thread while that is at most 4096 workgroups (16 to a compute unit), then two and four: a workgroup's words come one latency after the
+  // other.  Beyond that, and where a slot alone is long, in turn: the chip is full, and capacities that are mostly empty should cost few waves.  us, in
+  // turn / so: 64 slots of 128 rows 4.8 / 2.9 (a beam step with its attention 29.8 / 23.4), 4 of 8192 8.8 / 5.5, 320 of 256 14.6 / 13.7, 1000 of 256 46.0 /
+  // 41.8, 64 of 4096 42.5 / 41.0, but 128 of 1024 20.5 / 21.4; in turn / eight words a thread (which it was): 16 of 8192 21.0 / 23.6, 33 of 8192 48.0 / 52.8,
+  // 64 of 8192 119 / 111, 300 of 1024 51.8 / 53.9, 4096 of 256 205 / 206, of 10 rows of 256 7.2 / 8.6, empty 3.2 / 4.5.
   const size_t single = (words + 255) / 256 * slots;
   if (single <= 4096) go(reorder_kernel<1>, 1);
-  else if (single <= 2 * 4096) go(reorder_kernel<2>, 2);
-  else if (single <= 4 * 4096) go(reorder_kernel<4>, 4);
-  else if (words <= (size_t)65535 * 256 * 8) go(reorder_kernel<8>, 8);
-  else go(reorder_kernel<16>, 16);
+  else if (single <= 2 * 4096 && words <= 65536) go(reorder_kernel<2>, 2);
+  else if (single <= 4 * 4096 && words <= 65536) go(reorder_kernel<4>, 4);
+  else go(reorder_in_turn_kernel, 16);
   return hipGetLastError();
 }
 

@@ -206,9 +206,10 @@ def test_encoder_decoder_memory_with_beams(m):
     assert float((K2 != K).float().mean()) < 1e-2
 
 
-# one, two, four and eight words a thread; rows of K and V of different length, a last piece that is not full, empty and full slots
+# one, two and four words a thread, words in turn (also of a slot alone); rows of K and V of different length, a last piece that is not full, empty and full slots
 @pytest.mark.parametrize("n,h,cap,k,v,dtype", [(3, 1, 5, 8, 24, torch.bfloat16), (64, 1, 129, 128, 128, torch.bfloat16), (40, 2, 1001, 64, 128, torch.bfloat16),
-                                               (9, 1, 30011, 128, 64, torch.bfloat16), (5, 3, 24000, 128, 128, torch.bfloat16), (7, 1, 40003, 104, 128, torch.float32)])
+                                               (9, 1, 30011, 128, 64, torch.bfloat16), (5, 3, 24000, 128, 128, torch.bfloat16), (7, 1, 40003, 104, 128, torch.float32),
+                                               (60, 2, 1501, 128, 64, torch.bfloat16), (5, 1, 4097, 8, 256, torch.float32), (300, 1, 1029, 128, 120, torch.bfloat16)])
 def test_beam_reorder_of_any_size(m, n, h, cap, k, v, dtype):
     g = torch.Generator(device=DEV)
     g.manual_seed(cap)
