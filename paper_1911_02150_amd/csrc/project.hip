@@ -433,8 +433,10 @@ hipError_t launch_project_qkv_append(const float* x, const float* P_q, const flo
     float *Kf = (float*)K, *Vf = (float*)V;                                                                          \
     if (small && is_bf16) go(project_qkv_append_kernel<16, CB_, true, uint16_t>, Kh, Vh);                            \
     else if (small) go(project_qkv_append_kernel<16, CB_, true, float>, Kf, Vf);                                     \
-    else if (is_bf16) go(project_qkv_append_kernel<16, CB_, CB_ < 4, uint16_t>, Kh, Vh);                             \
-    else go(project_qkv_append_kernel<16, CB_, CB_ < 4, float>, Kf, Vf);                                             \
+    if constexpr (CB_ == 4) {                                                                                        \
+      if (!small && is_bf16) go(project_qkv_append_kernel<16, CB_, false, uint16_t>, Kh, Vh);                        \
+      else if (!small) go(project_qkv_append_kernel<16, CB_, false, float>, Kf, Vf);                                 \
+    }                                                                                                                \
     launched = true;                                                                                                 \
   }
   // Short groups in registers for two workgroups per compute unit (`small`), us, before / so: multi-head b=256 35.1 / 30.2, multi-query b=128 9.6 / 8.0,
