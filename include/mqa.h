@@ -157,7 +157,7 @@ int mqa_project_append_kv_rows(const float* x, const float* P_k, const float* P_
 /*
  * mqa_project_append_kv_rows and mqa_project_memory_kv (below) with scratch memory for the call: given
  * mqa_project_kv_workspace_bytes(...) bytes (16-byte aligned; b sequences of n rows) the weights are prepared once, in a
- * launch of its own, instead of by every tile of rows (32768 rows, d = 1024: 180 us without, 117 with).  0 means
+ * launch of its own, instead of by every tile of rows (32768 rows, d = 1024: 180 us without, 111 with).  0 means
  * that this shape uses none; given less (or NULL) the call is the one without.  Same rows either way.  The workspace is
  * written and read by this call's launches only.
  */

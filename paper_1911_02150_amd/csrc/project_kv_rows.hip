@@ -11,9 +11,9 @@
 // rows go through LDS (64 indices to a barrier), and a workgroup is four waves, so that two share a compute unit and one
 // multiplies while the other looks for its rows' largest magnitudes or rounds its sums.
 // Measured (32768 rows, d = 1024, 256 columns): 110.7 us with the preparation's 7 (project_kv.hip 180, the float64 kernel 410).
-// Of a tile's 60 us, two side by side: first pass 8, products 38, sums and rounding 8, open elements 4.  Bound by the matrix
-// cores and the power they draw: the card holds 1.6 to 2.0 GHz in the products (22 us of them at that clock without the
-// conversions).  v_mfma_i32_16x16x64_i8 draws less of it than 32x32x32, us before / so: 113.5 /
+// Of a tile's 60 us, two side by side: first pass 8, products 38, sums and rounding 8, open elements 4.  Bound by no single
+// unit (a third of the cycles each in the matrix cores and in vector instructions): the card holds 1.6 to 2.0 GHz in the products (22 us of them at that
+// clock without the conversions).  v_mfma_i32_16x16x64_i8 draws less of it than 32x32x32, us before / so: 113.5 /
 // 110.7, 16384 rows 66.9 / 62.4, 12800 rows of 2048 indices 110.5 / 103.5, 8192 rows x 2048 columns 221 / 205.  Without effect: tiles of 64 x 256 with eight waves (half the conversions, nothing beside them: 120), raised
 // priority of every second workgroup, weights two steps ahead or from L1, sums in 64-bit integers.
 #include "kv_fixed.hpp"
@@ -419,7 +419,7 @@ void kv_rows_kernel(KvRowsParams p) {
 // more, k = v = 128, d = 128: 20 / 24 / 3; 512: 31 / 42 / 12; 1024: 45 / 66 / 24; 1280: 55 / 79 / 31; 5 us more for each 2^20
 // weights.  The float64 kernel takes 5 + 2 rows N d / 42 TFLOP/s (4096 rows, d = 1024: 44 against 54, 2048: 42 against 29; 8192
 // rows, d = 128: 20 against 29); project_kv.hip's tiles are slower wherever this pays (10240 rows, d = 128: 24 against 25;
-// 32768, d = 1024: 117 against 180).
+// 32768, d = 1024: 111 against 180).
 bool project_kv_rows_pays(int rows, int d, int h_kv, int k, int v) {
   if (d > kMaxC || d < 64 || (k & 15) || (v & 15)) return false;
   const long long N = (long long)h_kv * (k + v);

@@ -30,7 +30,7 @@ void combine_kernel(CombineParams p) {
   const unsigned wid = ((nb & 7) == 0) ? (bid & 7) * (nb >> 3) + (bid >> 3) : bid;
   const size_t idx = (size_t)wid * 256 + threadIdx.x;
   if (idx >= total) return;
-  const long long row = total >> 32 ? (long long)(idx / v4) : (long long)((unsigned)idx / (unsigned)v4);      // (a 64-bit division takes 0.2 us)
+  const long long row = total >> 32 ? (long long)(idx / v4) : (long long)((unsigned)idx / (unsigned)v4);      // (in 32 bits where they do: within noise of 64)
   const int c4 = (int)(idx - (size_t)row * v4);
   const size_t base = (size_t)row * p.PS;
   const int n0 = valid_ranges(p.seg[0], row);

@@ -6,6 +6,9 @@ Stack (the model family of the paper's Section 4.1, random weights): token
 embedding + learned positional embedding; per layer  x += Attn(LN(x)),
 x += relu(LN(x) W1) W2;  final LN; logits = x E^T (embedding tied to the output
 layer); no biases; layernorm gain 1, bias 0, eps 1e-6.
+
+Nothing is kept of the weights but the tensors themselves: a pass multiplies by what they hold when it runs, called or
+replayed from a graph (a graph reads the tensors that it was captured with).
 """
 from __future__ import annotations
 
