@@ -415,7 +415,7 @@ int mqa_stack_argmax(const float* x, int32_t* out, int rows, int n, void* stream
  * The feed-forward of that stack's long prompts in one call: x += relu(layernorm(x) . W1) . W2, x [rows,d], W1 [d,ff], W2 [ff,d].
  * The products are those of mqa_project_qkvo_ex from operands split beforehand, in the workspace, by this call; where two fp16 terms do not hold
  * the values they are that call's own (decided on the device: a captured call does what the weights of each replay want).
- *   plan:  0: no such form of these sizes (d, ff: multiples of 32, d <= 4096; the call is then refused with MQA_ERR_SHAPE); else bit 0 says whether
+ *   plan:  0: no such form of these sizes (d, ff: multiples of 32, d <= 4096; the call is then refused with MQA_ERR_SHAPE, as it is with eps < 0); else bit 0 says whether
  *          it is faster than layernorm, product with MQA_EPI_RELU and product with MQA_EPI_ADD, bits 4..7 and 8..11 which tiles the products take.
  *          *workspace_bytes (unless NULL): what the call needs (MQA_ERR_WORKSPACE with less), about 4 rows (d + ff) + 8 d ff bytes.
  */

@@ -690,7 +690,7 @@ int mqa_stack_feed_forward(const float* W1, const float* W2, float* x, int rows,
                            void* stream) {
   if (!W1 || !W2 || !x) return MQA_ERR_NULL;
   const FeedForwardPlan f = feed_forward_plan(rows, d, ff);
-  if (!f.bytes) return MQA_ERR_SHAPE;
+  if (!f.bytes || !(eps >= 0.f)) return MQA_ERR_SHAPE;      // (a layernorm's row is then no longer than sqrt(d))
   if (!workspace || workspace_bytes < f.bytes) return MQA_ERR_WORKSPACE;
   if (misaligned(W1) || misaligned(W2) || misaligned(x) || misaligned(workspace)) return MQA_ERR_ALIGN;
   return launch_feed_forward(f, W1, W2, x, rows, d, ff, eps, workspace, static_cast<hipStream_t>(stream)) == hipSuccess ? MQA_OK : MQA_ERR_LAUNCH;

@@ -42,9 +42,9 @@ def test_refused(m):
     lib, A, nbytes = m.load_library(), 0x10000, ctypes.c_size_t(0)
     lib.mqa_stack_feed_forward_plan(16384, 1024, 4096, ctypes.byref(nbytes))
 
-    def status(W1=A, W2=A, x=A, rows=16384, d=1024, ff=4096, ws=A, n=nbytes.value):
-        return lib.mqa_stack_feed_forward(W1, W2, x, rows, d, ff, 1e-6, ws, n, None)
+    def status(W1=A, W2=A, x=A, rows=16384, d=1024, ff=4096, ws=A, n=nbytes.value, eps=1e-6):
+        return lib.mqa_stack_feed_forward(W1, W2, x, rows, d, ff, eps, ws, n, None)
 
-    for change, want in ((dict(W1=None), 1), (dict(W2=None), 1), (dict(x=None), 1), (dict(d=1000), 2), (dict(rows=0), 2), (dict(rows=128), 2), (dict(x=A + 4), 3), (dict(ws=A + 8), 3),
+    for change, want in ((dict(W1=None), 1), (dict(W2=None), 1), (dict(x=None), 1), (dict(d=1000), 2), (dict(rows=0), 2), (dict(rows=128), 2), (dict(eps=-1e-3), 2), (dict(eps=float("nan")), 2), (dict(x=A + 4), 3), (dict(ws=A + 8), 3),
                          (dict(W2=A + 8), 3), (dict(ws=None), 4), (dict(n=nbytes.value - 1), 4), ({}, 6)):
         assert status(**change) == want, change
