@@ -85,17 +85,19 @@ class DecoderStack:
     def _workspace(self, rows: int, nbytes: int = 0) -> torch.Tensor:
         """Scratch memory for the calls of one pass over `rows` rows, one after another on its stream (a pass's own: calls on several
         streams do not share it), nbytes at least."""
-        known = self._parts.get(rows)          # (a decoding loop asks for the same rows again and again: 1.5 us of a step)
+        cap = max(V.shape[-2] for V in self.V) if rows == self.b else 0        # (a step's attention; a program may have put other caches in)
+        key = rows, cap, self.K[0].dtype
+        known = self._parts.get(key)           # (a decoding loop asks for the same rows again and again: 1.5 us of a step)
         if known is None:
             sizes = [16, B.mqa_project_add_layernorm_workspace_bytes(B.MQA_PROJ_O, rows, self.d, self.h, self.v)]
             for ff in {w["W1"].shape[1] for w in self.layers}:
                 sizes.append(B.mqa_project_add_layernorm_workspace_bytes(B.MQA_PROJ_LINEAR, rows, ff, 1, self.d))
-            if rows == self.b:                 # (a step's attention)
+            if cap:
                 dt = B._cache_dtype(self.K[0])
-                sizes.append(B.mqa_decode_workspace_bytes_default(self.b, self.h, self.cap, self.k, self.v, dt, self.multi_head))
+                sizes.append(B.mqa_decode_workspace_bytes_default(self.b, self.h, cap, self.k, self.v, dt, self.multi_head))
             if len(self._parts) >= 16:
                 self._parts.clear()
-            known = self._parts[rows] = max(sizes)
+            known = self._parts[key] = max(sizes)
         return torch.empty(max(known, nbytes), dtype=torch.uint8, device=self.dev)
 
     # -- one decoding step for the whole stack: per layer 7 launches (fused q/K/V + append, attention (+ merge), output

@@ -187,3 +187,21 @@ def test_long_prompt_is_near_its_calls(m, monkeypatch):
             return whole(rows, nbytes)
 
         monkeypatch.setattr(stack, "_workspace", no_room)
+
+
+@pytest.mark.parametrize("multi_head", [False, True])
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+def test_other_caches(m, multi_head, dtype):
+    """A program may put larger caches in, or of the other type: a step's attention takes what it needs."""
+    from paper_1911_02150_amd.decoder_stack import DecoderStack
+    w = _weights(1, 2, 64, 2, 64, 72, 9000)
+    if multi_head:
+        for layer in w["layers"]:
+            layer["P_k"], layer["P_v"] = (np.stack([layer[name], -layer[name]]) for name in ("P_k", "P_v"))
+    small, large = (DecoderStack(w, 1, cap, multi_head, DEV, cache_dtype=kind) for cap, kind in ((40, torch.bfloat16), (8200, dtype)))
+    token = torch.tensor([5], dtype=torch.int32, device=DEV)
+    small.step(token, 0)
+    for l in range(2):
+        small.K[l], small.V[l] = torch.zeros_like(large.K[l]), torch.zeros_like(large.V[l])
+        small.lens[l].fill_(8000), large.lens[l].fill_(8000)
+    assert torch.equal(small.step(token, 8000), large.step(token, 8000))
