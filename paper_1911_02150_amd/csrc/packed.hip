@@ -392,7 +392,10 @@ __device__ __forceinline__ void pack_tile(const PackWeights& p, int tile, int32_
 __global__ __launch_bounds__(256)
 void pack_kernel(PackWeights look, PackWeights write, int first, int32_t* flag) {
   __shared__ uint32_t tally[32];
-  if (*flag) return;                           // (not to be used: the same for all that matters)
+  __shared__ int done;
+  if (threadIdx.x == 0) done = *flag;          // (other workgroups of this launch may set it: one look for all waves of this one)
+  __syncthreads();
+  if (done) return;
   if ((int)blockIdx.x < first) pack_tile<false>(look, blockIdx.x, flag, tally);
   else pack_tile<true>(write, blockIdx.x - first, flag, tally);
 }
